@@ -81,6 +81,8 @@ static hipError_t get_tables(Tables* out, hipStream_t st, bool sync_device, void
         if (e != hipSuccess) return e;
         e = note(coop_fill_tables(&g_tab[dev].ctab, st), "fill coop tables");
         if (e != hipSuccess) return e;
+        e = note(valu_fill_tables(&g_tab[dev].ftw, st), "fill fp32 tables");
+        if (e != hipSuccess) return e;
         void* sp = nullptr;
         e = note(hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)), "hipGetSymbolAddress(scratch)");
         if (e != hipSuccess) return e;
@@ -144,19 +146,8 @@ Plan make_plan(int64_t N, int io)
     pl.log2L2 = pl.log2L < cap ? pl.log2L : cap;
     pl.log2R = pl.log2L - pl.log2L2;
     if (pl.log2R > 5) { pl.log2R = 5; pl.log2L2 = pl.log2L - 5; }   // not reachable for supported N
-    const float invL = 1.0f / (float)(int64_t(1) << pl.log2L);
-    if (pl.engine == ENGINE_VALU) {
-        pl.order.ndig = 0;
-        pl.order.wave_lg = 0;
-        pl.order.coop_lg = 0;
-        pl.order.outer_bits = 0;
-        if (pl.log2R) pl.order.bits[pl.order.ndig++] = (unsigned char)pl.log2R;
-        for (int i = 0; i < pl.log2L2; ++i) pl.order.bits[pl.order.ndig++] = 1;
-        pl.kscale = invL;
-        pl.dkscale = invL;
-    } else {
-        mfma_fill_plan(pl);
-    }
+    if (pl.engine == ENGINE_VALU) valu_fill_plan(pl);
+    else mfma_fill_plan(pl);
     return pl;
 }
 
@@ -187,6 +178,7 @@ struct WsLayout {
 // dealt to `nsplit` workgroups (about 384 in all), whose partial dk and dD are then summed in a fixed order.
 static int dk_nsplit(int64_t B, int64_t H, const Plan& pl)
 {
+    if (pl.engine == ENGINE_VALU) return valu_bwd_nsplit(H, (int)((B + 1) / 2), pl);
     if (pl.engine != ENGINE_MFMA || pl.log2R || !(pl.order.wave_lg || pl.order.coop_lg)) return 1;
     const int64_t npairs = (B + 1) / 2;
     int64_t s = 384 / H;
@@ -210,18 +202,22 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     w.kspec = off; off += up256(spec_total_bytes(H, L, pl));
     // pass-A output of k, for the spectrum routes that run pass A as a kernel of its own
     const bool mc = pl.engine == ENGINE_MFMA && (pl.order.wave_lg || pl.order.coop_lg);
-    const bool kscr = mc ? (pl.log2R && !pl.fuse_a) : (pl.log2L > VALU_KSPEC_MAX_LOG2);
+    const bool kscr = mc && pl.log2R && !pl.fuse_a;
     w.kscratch = off; if (kscr) off += up256((size_t)H * L * sizeof(float2));
     w.hscale = off; off += up256(head_stats_floats(H, N) * sizeof(float));
     w.ws1 = off; if (pl.log2R) off += up256((size_t)H * npairs * L * cw_bytes(pl));
-    w.ws2 = off; if (pl.log2R && backward) off += up256((size_t)H * npairs * L * cw_bytes(pl));
+    // (the fp32 engine takes pass A inside its kernels)
+    w.ws2 = off; if (pl.log2R && backward && pl.engine == ENGINE_MFMA) off += up256((size_t)H * npairs * L * cw_bytes(pl));
     w.wsA = off; if (pl.log2R && backward) off += up256((size_t)H * L * cw_bytes(pl));
     w.nblk = (int)(npairs * ((size_t(1) << pl.log2L2) / 256));
     const size_t npart = (size_t)w.nblk > (size_t(1) << pl.log2R) ? (size_t)w.nblk : (size_t(1) << pl.log2R);
     w.dpart = off; if (pl.log2R && backward) off += up256((size_t)H * npart * sizeof(float));
-    w.zbuf = off; if (backward && pl.order.coop_lg) off += up256((size_t)H * L * sizeof(__half2));
     w.nsplit = backward ? dk_nsplit(B, H, pl) : 1;
-    w.dkpart = off; if (w.nsplit > 1) off += up256((size_t)w.nsplit * H * (L / 2) * sizeof(float));
+    w.zbuf = off;
+    if (backward && pl.order.coop_lg) off += up256((size_t)H * L * sizeof(__half2));
+    if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(H, w.nsplit, pl));
+    // partial dk rows, or (fp32 engine, multi-pass) partial sets of pass C's complex chunks
+    w.dkpart = off; if (w.nsplit > 1) off += up256((size_t)w.nsplit * H * (pl.log2R ? 2 * L : L / 2) * sizeof(float));
     w.ddpart = off; if (w.nsplit > 1) off += up256((size_t)w.nsplit * H * sizeof(float));
     // bf16 rows of the multi-pass plans with pass A inside the inner kernels: per-head maxima of u and dy
     w.rowmx = off; if (rows_rescaled(pl, io)) off += up256((size_t)2 * H * sizeof(uint32_t));
@@ -262,18 +258,15 @@ static hipError_t run_kspec(const float* k, const float* D, float2* kspec, float
         if (pl.fuse_a) return coop_kspec(k, nullptr, D, hscale, kspec, H, N, pl, tb, st);
         if (pl.log2R) {
             Problem pk{1, H, N, LONGCONV_F32, 1};
-            e = outer_fwd(k, nullptr, kscratch, nullptr, nullptr, pk, pl.log2R, pl.log2L2, 1.0f, true, tw, st, hscale);
+            e = outer_fwd(k, nullptr, kscratch, nullptr, nullptr, pk, pl.log2R, pl.log2L2, 1.0f, tw, st, hscale);
             if (e != hipSuccess) return e;
         }
         return coop_kspec(k, (const __half2*)kscratch, D, hscale, kspec, H, N, pl, tb, st);
     }
-    const int lg2 = pl.log2L < VALU_KSPEC_MAX_LOG2 ? pl.log2L : VALU_KSPEC_MAX_LOG2;
-    const int lgR = pl.log2L - lg2;
-    if (lgR == 0) return valu_kspec(k, nullptr, D, kspec, H, N, 0, lg2, pl.order, pl.kscale, tw, st);
-    Problem pk{1, H, N, LONGCONV_F32, 1};
-    hipError_t e = outer_fwd(k, nullptr, kscratch, nullptr, nullptr, pk, lgR, lg2, 1.0f, false, tw, st);
-    if (e != hipSuccess) return e;
-    return valu_kspec(nullptr, kscratch, D, kspec, H, N, lgR, lg2, pl.order, pl.kscale, tw, st);
+    if (pl.engine == ENGINE_VALU) return valu_kspec(k, D, kspec, H, N, nullptr, pl.kscale, tb, pl.log2R, pl.log2L2, st);
+    // staged matrix-core kernel: fp32 spectrum in that kernel's digit-reversed order
+    const int lg2 = pl.log2L < VALU_INNER_MAX_LOG2 ? pl.log2L : VALU_INNER_MAX_LOG2;
+    return valu_kspec(k, D, kspec, H, N, &pl.order, pl.kscale, tb, pl.log2L - lg2, lg2, st);
 }
 
 // y = conv(in, spectrum) (or correlation when conj): all passes of the plan.
@@ -285,12 +278,12 @@ static hipError_t run_conv(const void* in, const float2* kspec, void* out, void*
     const float2* tw = tb.tw;
     const bool f16ws = pl.engine == ENGINE_MFMA;
     const bool fuse_a = pl.engine == ENGINE_MFMA && pl.fuse_a && !ws1_ready;   // pass A inside the inner kernel
-    if (pl.log2R && !ws1_ready && !fuse_a) {
-        e = outer_fwd(in, nullptr, ws1, nullptr, nullptr, pr, pl.log2R, pl.log2L2, 1.0f, f16ws, tw, st);
+    if (pl.engine == ENGINE_MFMA && pl.log2R && !ws1_ready && !fuse_a) {
+        e = outer_fwd(in, nullptr, ws1, nullptr, nullptr, pr, pl.log2R, pl.log2L2, 1.0f, tw, st);
         if (e != hipSuccess) return e;
     }
     if (pl.engine == ENGINE_VALU)
-        e = valu_conv(in, kspec, out, (float2*)ws1, conj, pr, pl, tw, st);
+        e = valu_conv(in, kspec, out, (float2*)ws1, conj, pr, pl, tb, st);
     else
         e = mfma_conv(in, kspec, out, (__half2*)ws1, conj, fuse_a, pr, pl, tb, st);
     if (e != hipSuccess) return e;
@@ -505,23 +498,36 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
         if (note(e, "bwd") != hipSuccess) return LONGCONV_ERR_HIP;
         return LONGCONV_OK;
     }
+    if (want_dkD && pl.engine == ENGINE_VALU) {
+        // one kernel for what is asked for (du alone: the convolution kernel, below)
+        const float2* ks = (const float2*)kspec;
+        if (du && !ks) {
+            if (note(run_kspec(k, D, (float2*)(base + w.kspec), nullptr, nullptr, H, N, pl, tb, st), "kspec") != hipSuccess)
+                return LONGCONV_ERR_HIP;
+            ks = (const float2*)(base + w.kspec);
+        }
+        const int ns = w.nsplit;
+        const bool multi = pl.log2R != 0;
+        float* dkp = (float*)(base + w.dkpart);
+        float* ddp = (float*)(base + w.ddpart);
+        float* acc = multi ? (float*)(base + w.wsA) : dk;         // where the (summed) dk rows or chunks belong
+        const size_t n_acc = dk ? (size_t)H * (multi ? 4 * N : N) : 0;
+        float* to = dk ? (ns > 1 ? dkp : acc) : nullptr;
+        hipError_t e = valu_bwd(dy, u, ks, du, du ? (float2*)(base + w.ws1) : nullptr, multi ? nullptr : to,
+                                multi ? (float2*)to : nullptr, dD ? (ns > 1 ? ddp : dD) : nullptr, base + w.zbuf, ns, pr, pl,
+                                tb, st);
+        if (e == hipSuccess && ns > 1) e = sum_partials(dkp, n_acc ? acc : nullptr, n_acc, ddp, dD, (size_t)H, ns, st);
+        if (e == hipSuccess && multi && dk)
+            e = outer_inv(base + w.wsA, dk, Problem{1, H, N, LONGCONV_F32, 1}, pl.log2R, pl.log2L2, pl.dkscale, false, tw, st);
+        if (e == hipSuccess && multi && du) e = outer_inv(base + w.ws1, du, pr, pl.log2R, pl.log2L2, 1.0f, false, tw, st);
+        return note(e, "bwd") == hipSuccess ? LONGCONV_OK : LONGCONV_ERR_HIP;
+    }
     if (want_dkD) {
         hipError_t e = hipSuccess;
         float* dpart = (float*)(base + w.dpart);
         int cR = pl.log2R, cL2 = pl.log2L2;        // the split and scale pass C of dk works with
         float cscale = pl.dkscale;
-        if (pl.engine == ENGINE_VALU) {
-            if (pl.log2R) {
-                // pass A for u (-> ws2) and dy (-> ws1) in one launch, with the dD partial sums
-                e = outer_fwd(dy, u, base + w.ws1, base + w.ws2, dD ? dpart : nullptr, pr, pl.log2R, pl.log2L2,
-                              1.0f, false, tw, st);
-                dy_ready = true;
-                if (e == hipSuccess && dD) e = reduce_dD(dpart, dD, H, w.nblk, st);
-            }
-            if (e == hipSuccess && (dk || !pl.log2R))
-                e = valu_dk(dy, u, dk, dD, (const float2*)(base + w.ws2), (const float2*)(base + w.ws1),
-                            (float2*)(base + w.wsA), pr, pl, tw, st);
-        } else if (coop_dk_rows_ok(pl)) {
+        if (coop_dk_rows_ok(pl)) {
             // straight from the rows, as outer radix 8 or 16 around 16384-point transforms (no pass A kernel);
             // dD is the rows' dot product, taken by the workgroup of each head's first chunk
             cR += 1; cL2 -= 1;
@@ -532,8 +538,8 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
         } else {
             if (pl.log2R) {
                 // pass A for u and dy in one launch; its blocks also leave dD's partial dot products
-                e = outer_fwd(dy, u, base + w.ws1, base + w.ws2, dD ? dpart : nullptr, pr, pl.log2R, pl.log2L2, 1.0f,
-                              true, tw, st);
+                e = outer_fwd(dy, u, base + w.ws1, base + w.ws2, dD ? dpart : nullptr, pr, pl.log2R, pl.log2L2, 1.0f, tw,
+                              st);
                 dy_ready = true;
                 if (e == hipSuccess && dD) e = reduce_dD(dpart, dD, H, w.nblk, st);
             }

@@ -29,6 +29,7 @@ struct Tables {
     const float2* stw;   // stage twiddles
     const void* wtab;    // lane-ordered constants of the wave-autonomous kernels
     const void* ctab;    // lane-ordered constants of the cooperative chained kernels
+    const float2* ftw;   // stage twiddles of the fp32 engine
 };
 
 // exp(-2*pi*i*idx/TW_L) for any idx in [0, TW_L)

@@ -1,309 +1,782 @@
-// fp32 engine: the whole FFT convolution of one row pair in LDS with plain vector-ALU
-// radix-2 butterflies.  It serves fp32 I/O (where fp16 matrix-core operands cannot meet
-// the accuracy bound) and the kernel-spectrum precompute for every dtype.
+// fp32 engine: the whole FFT convolution of one row pair on the vector ALUs.  It serves fp32 I/O (where fp16
+// matrix-core operands cannot meet the accuracy bound) and, for every dtype, the spectrum of plans whose consumer is
+// the staged matrix-core kernel.
 //
-// Transform convention (paper Eq. 2 with the sequence zero padded to L = 2N):
-//   forward : decimation in frequency, natural order in, bit-reversed order out
-//   inverse : decimation in time, bit-reversed order in, natural order out
-// so the pointwise product with a spectrum stored in bit-reversed order sits between the
-// two with no permutation (Section 3.2, "eliminates permutations over the input").
+// Transform convention (paper Eq. 2 with the sequence zero padded to L = 2N): mixed radix, in place.  A stage of
+// radix r and span Ls (stride M = Ls / r) takes position blk*Ls + d*M + q to blk*Ls + k*M + q,
+//     forward (decimation in frequency): DFT over d, then w_Ls^(k q);     inverse: w_Ls^(-k q), then DFT^-1 over k,
+// so the digit-reversed order in which the forward stages leave the frequencies is what the inverse stages start
+// from and the pointwise product needs no permutation (Section 3.2, "eliminates permutations over the input").
+//
+// Layout: a workgroup of T = L2 / P threads owns one sequence of L2 = 2^LG points, P per thread in registers.  Every
+// stage is a butterfly of up to P points in registers; between two stages the points cross LDS once, each thread
+// writing the positions it holds and reading those of its next butterfly (one barrier: the positions a thread reads
+// are the ones it writes next).  Stage 0 takes its P points straight from the rows (thread q: samples q + d T, so every
+// load is a unit-stride run) and the last inverse stage stores them the same way.  What bounds it: about 60
+// vector instructions per point and transform at 3 or 4 exchanges, against LDS at 16 bytes per point and exchange; the
+// radix-2 form it replaces crossed LDS once per bit (14 times at L = 16384) with a table look-up per butterfly, and
+// ran N = 8192, B=4, H=96 at 108 us per convolution and 152 us for dk.
 #include "engines.hpp"
 
 namespace lc {
 namespace {
 
-// In-place radix-2 FFT of s[0..2^lg) in LDS by the whole block.  Ends with a barrier.
+// ---- radix schedule ---------------------------------------------------------------------------------------------
+// Points per thread by length: more points mean fewer exchanges, fewer points more waves for the same work.
+constexpr int points_log2(int LG) { return LG <= 8 ? 2 : LG <= 11 ? 3 : 4; }
+constexpr int stages(int LG) { return (LG + points_log2(LG) - 1) / points_log2(LG); }
+// bits of stage s: the first one as wide as a thread holds points (it reads the rows), the others as even as they go
+constexpr int stage_bits(int LG, int s)
+{
+    const int lp = points_log2(LG), n = stages(LG) - 1;
+    if (s == 0) return lp;
+    const int rem = LG - lp;
+    return rem / n + (s - 1 < rem % n ? 1 : 0);
+}
+// log2 of the span of stage s
+constexpr int span_log2(int LG, int s)
+{
+    int l = LG;
+    for (int i = 0; i < s; ++i) l -= stage_bits(LG, i);
+    return l;
+}
+
+// LDS position of point p: one slot of padding in nine, conflict-free for the strides 1, 8, 16 and above of the stages
+__host__ __device__ constexpr int phys(int p) { return p + (p >> 3); }
+// whether the backward kernel parks the transform of u in memory (see fbwd_kernel)
+constexpr bool valu_parks(int LG) { return LG >= 14; }
+constexpr size_t lds_bytes(int LG) { return sizeof(float2) * ((size_t(1) << LG) * 9 / 8); }
+
+// ---- butterflies in registers -------------------------------------------------------------------------------------
+// v * exp(-+ 2 pi i m / 32): m a compile-time constant after unrolling
 template <bool INV>
-__device__ void fft_lds(float2* s, int lg, const float2* __restrict__ tw, int tid, int nt)
+__device__ __forceinline__ float2 rot32(float2 v, int m)
 {
-    const int half = 1 << (lg - 1);
-    if (!INV) {
-        for (int lm = lg - 1; lm >= 0; --lm) {
-            const int m = 1 << lm;
-            for (int j = tid; j < half; j += nt) {
-                const int q = j & (m - 1);
-                const int i = ((j >> lm) << (lm + 1)) + q;
-                const float2 a = s[i], b = s[i + m];
-                const float2 w = tw[(uint32_t)q << (TW_LOG2 - 1 - lm)];   // exp(-2 pi i q / 2m)
-                s[i] = cadd(a, b);
-                s[i + m] = cmul(csub(a, b), w);
-            }
-            __syncthreads();
-        }
-    } else {
-        for (int lm = 0; lm < lg; ++lm) {
-            const int m = 1 << lm;
-            for (int j = tid; j < half; j += nt) {
-                const int q = j & (m - 1);
-                const int i = ((j >> lm) << (lm + 1)) + q;
-                const float2 w = tw[(uint32_t)q << (TW_LOG2 - 1 - lm)];
-                const float2 a = s[i], b = cmulc(s[i + m], w);
-                s[i] = cadd(a, b);
-                s[i + m] = csub(a, b);
-            }
-            __syncthreads();
-        }
+    constexpr float C[5] = {1.f, 0.98078528040323043f, 0.92387953251128674f, 0.83146961230254524f, 0.70710678118654752f};
+    constexpr float S[5] = {0.f, 0.19509032201612825f, 0.38268343236508977f, 0.55557023301960218f, 0.70710678118654752f};
+    m &= 31;
+    const int q = m >> 3, r = m & 7;
+    float2 t = v;
+    if (r == 4) {
+        t = INV ? make_float2((v.x - v.y) * C[4], (v.x + v.y) * C[4]) : make_float2((v.x + v.y) * C[4], (v.y - v.x) * C[4]);
+    } else if (r) {
+        const float c = r < 4 ? C[r] : S[8 - r], s = (r < 4 ? S[r] : C[8 - r]) * (INV ? 1.f : -1.f);
+        t = make_float2(v.x * c - v.y * s, v.x * s + v.y * c);
     }
+    if (q == 0) return t;
+    if (q == 2) return make_float2(-t.x, -t.y);
+    return ((q == 1) != INV) ? make_float2(t.y, -t.x) : make_float2(-t.y, t.x);
 }
 
-// -------------------------------------------------------------------------------------
-// Kernel spectrum (Algorithm 2 lines 1-2).  One block per (head, chunk k1).
-//   REAL input  (log2R == 0): s[n] = k[h,n] for n < N, zero above.
-//   CHUNK input (log2R  > 0): s[n2] = ws[h*L + k1*L2 + n2] (output of outer_fwd).
-// After the forward transform position p holds inner frequency k2 = bitrev(p); the full
-// frequency is f = k1 + R*k2.  The skip term D[h]*u is the convolution with a delta of
-// height D[h], whose spectrum is the constant D[h]; it is added here so the fused kernels
-// never touch D.  The value is scaled and scattered to the consumer's storage order.
-// -------------------------------------------------------------------------------------
-__global__ void kspec_kernel(const float* __restrict__ k, const float2* __restrict__ ws,
-                             const float* __restrict__ D, float2* __restrict__ kspec, int64_t N,
-                             int log2R, int log2L2, SpecOrder consumer, float scale,
-                             const float2* __restrict__ tw)
+// natural order in and out, stride ST between the elements
+template <int R, bool INV, int ST = 1>
+__device__ __forceinline__ void dft(float2* x)
 {
-    extern __shared__ float2 s[];
-    const int h = blockIdx.y, k1 = blockIdx.x;
-    const int L2 = 1 << log2L2;
-    const int64_t L = (int64_t)L2 << log2R;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    if (log2R == 0) {
-        const float* kr = k + (size_t)h * N;
-        for (int n = tid; n < L2; n += nt) s[n] = make_float2(n < N ? kr[n] : 0.f, 0.f);
+    if constexpr (R == 2) {
+        const float2 a = x[0], b = x[ST];
+        x[0] = cadd(a, b);
+        x[ST] = csub(a, b);
+    } else if constexpr (R == 4) {
+        const float2 a = cadd(x[0], x[2 * ST]), b = csub(x[0], x[2 * ST]);
+        const float2 c = cadd(x[ST], x[3 * ST]), d = csub(x[ST], x[3 * ST]);
+        const float2 e = INV ? make_float2(-d.y, d.x) : make_float2(d.y, -d.x);
+        x[0] = cadd(a, c);
+        x[ST] = cadd(b, e);
+        x[2 * ST] = csub(a, c);
+        x[3 * ST] = csub(b, e);
     } else {
-        const float2* c = ws + (size_t)h * L + (size_t)k1 * L2;
-        for (int n = tid; n < L2; n += nt) s[n] = c[n];
-    }
-    __syncthreads();
-    fft_lds<false>(s, log2L2, tw, tid, nt);
-    const float d = D ? D[h] : 0.f;
-    float2* out = kspec + (size_t)h * L;
-    for (int p = tid; p < L2; p += nt) {
-        const uint32_t k2 = __brev((uint32_t)p) >> (32 - log2L2);
-        const uint32_t f = (uint32_t)k1 + (k2 << log2R);
-        float2 v = s[p];
-        v.x += d;
-        out[spec_pos(f, consumer)] = make_float2(v.x * scale, v.y * scale);
-    }
-}
-
-// -------------------------------------------------------------------------------------
-// Fused convolution of one row pair (Eq. 2 fused as in Section 3.2 "Kernel Fusion").
-//   single pass (log2R == 0): z[n] = in[2p,h,n] + i*in[2p+1,h,n], zero padded to L; forward,
-//     multiply by the stored spectrum (or its conjugate: correlation, used for du), inverse,
-//     keep the first N samples: re -> out row 2p, im -> out row 2p+1.  Convolution with a real
-//     kernel is real-linear, so the two rows never mix.
-//   multi pass  (log2R  > 0): the same on chunk k1 of the pair's complex workspace, in place,
-//     with slice k1 of the spectrum (Eq. 3: m independent convolutions of length l).
-// grid = (npairs, H, R)
-// -------------------------------------------------------------------------------------
-template <class IO>
-__global__ void conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec,
-                            typename IO::T* __restrict__ out, float2* __restrict__ ws, int conj,
-                            int64_t B, int64_t H, int64_t N, int log2R, int log2L2,
-                            const float2* __restrict__ tw)
-{
-    extern __shared__ float2 s[];
-    const int p = blockIdx.x, h = blockIdx.y, k1 = blockIdx.z;
-    const int npairs = gridDim.x;
-    const int L2 = 1 << log2L2;
-    const int64_t L = (int64_t)L2 << log2R;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const bool has_b = (2 * p + 1) < B;
-    float2* chunk = nullptr;
-    if (log2R == 0) {
-        const typename IO::T* ra = in + row_off(2 * p, h, H, N);
-        const typename IO::T* rb = in + row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-        for (int n = tid; n < L2; n += nt) {
-            float2 v = make_float2(0.f, 0.f);
-            if (n < N) { v.x = IO::ld(ra, n); v.y = has_b ? IO::ld(rb, n) : 0.f; }
-            s[n] = v;
-        }
-    } else {
-        chunk = ws + ((size_t)h * npairs + p) * L + (size_t)k1 * L2;
-        for (int n = tid; n < L2; n += nt) s[n] = chunk[n];
-    }
-    __syncthreads();
-    fft_lds<false>(s, log2L2, tw, tid, nt);
-    const float2* ks = kspec + (size_t)h * L + (size_t)k1 * L2;
-    for (int q = tid; q < L2; q += nt) s[q] = conj ? cmulc(s[q], ks[q]) : cmul(s[q], ks[q]);
-    __syncthreads();
-    fft_lds<true>(s, log2L2, tw, tid, nt);
-    if (log2R == 0) {
-        typename IO::T* ya = out + row_off(2 * p, h, H, N);
-        typename IO::T* yb = out + row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-        for (int n = tid; n < N; n += nt) {
-            const float2 v = s[n];
-            IO::st(ya, n, v.x);
-            if (has_b) IO::st(yb, n, v.y);
-        }
-    } else {
-        for (int n = tid; n < L2; n += nt) chunk[n] = s[n];
-    }
-}
-
-// -------------------------------------------------------------------------------------
-// dk and dD.  One block per (head, chunk): loops over the head's row pairs in order
-// (deterministic), accumulating A += conj(Z) * W in registers, where Z, W are the
-// transforms of the u pair and of the dy pair.  The real part of the inverse transform of A
-// is sum over both rows of the pair of the correlation dy (x) u, i.e. the pair's share of dk
-// (the cross terms between the two rows are purely imaginary).  dD is the plain dot product,
-// taken while both rows are in registers.
-// MAXPT = L2 / blockDim.x accumulators per thread.
-// -------------------------------------------------------------------------------------
-template <class IO, int MAXPT>
-__global__ void dk_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
-                          float* __restrict__ dk, float* __restrict__ dD,
-                          const float2* __restrict__ ws_u, const float2* __restrict__ ws_dy,
-                          float2* __restrict__ ws_A, int64_t B, int64_t H, int64_t N, int npairs,
-                          int log2R, int log2L2, float scale, const float2* __restrict__ tw)
-{
-    extern __shared__ float2 s[];
-    __shared__ float red[32];
-    const int h = blockIdx.x, k1 = blockIdx.y;
-    const int L2 = 1 << log2L2;
-    const int64_t L = (int64_t)L2 << log2R;
-    float2* sz = s;
-    float2* sw = s + L2;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    float2 acc[MAXPT];
+        // n = A n1 + n2 (n1 < B), k = k1 + B k2
+        constexpr int B = 4, A = R / 4;
+        float2 t[R];
 #pragma unroll
-    for (int i = 0; i < MAXPT; ++i) acc[i] = make_float2(0.f, 0.f);
-    float dsum = 0.f;
-    for (int p = 0; p < npairs; ++p) {
-        if (log2R == 0) {
-            const bool has_b = (2 * p + 1) < B;
-            const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-            for (int n = tid; n < L2; n += nt) {
-                float2 z = make_float2(0.f, 0.f), w = z;
-                if (n < N) {
-                    z.x = IO::ld(u, oa + n); w.x = IO::ld(dy, oa + n);
-                    if (has_b) { z.y = IO::ld(u, ob + n); w.y = IO::ld(dy, ob + n); }
-                    dsum += z.x * w.x + z.y * w.y;
-                }
-                sz[n] = z; sw[n] = w;
-            }
+        for (int n2 = 0; n2 < A; ++n2) {
+            float2 y[B];
+#pragma unroll
+            for (int n1 = 0; n1 < B; ++n1) y[n1] = x[(A * n1 + n2) * ST];
+            dft<B, INV>(y);
+#pragma unroll
+            for (int k1 = 0; k1 < B; ++k1) t[k1 * A + n2] = rot32<INV>(y[k1], n2 * k1 * (32 / R));
+        }
+#pragma unroll
+        for (int k1 = 0; k1 < B; ++k1) {
+            dft<A, INV>(t + k1 * A);
+#pragma unroll
+            for (int k2 = 0; k2 < A; ++k2) x[(k1 + B * k2) * ST] = t[k1 * A + k2];
+        }
+    }
+}
+
+// forward DFT of R points whose upper half is zero (zero padding): x[0 .. R/2) in, x[0 .. R) out
+template <int R>
+__device__ __forceinline__ void dft_half_in(float2* x)
+{
+    float2 e[R / 2], o[R / 2];
+#pragma unroll
+    for (int n = 0; n < R / 2; ++n) { e[n] = x[n]; o[n] = rot32<false>(x[n], n * (32 / R)); }
+    dft<R / 2, false>(e);
+    dft<R / 2, false>(o);
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) { x[2 * k] = e[k]; x[2 * k + 1] = o[k]; }
+}
+// inverse DFT of R points of which only outputs 0 .. R/2 are wanted (truncation)
+template <int R>
+__device__ __forceinline__ void dft_half_out(float2* x)
+{
+    float2 e[R / 2], o[R / 2];
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) { e[k] = x[2 * k]; o[k] = x[2 * k + 1]; }
+    dft<R / 2, true>(e);
+    dft<R / 2, true>(o);
+#pragma unroll
+    for (int n = 0; n < R / 2; ++n) x[n] = cadd(e[n], rot32<true>(o[n], n * (32 / R)));
+}
+
+// ---- stage twiddles -----------------------------------------------------------------------------------------------
+// The table holds w_{2^l}^q, q < 2^(l-1), at entry 2^(l-1) + q.  w_Ls^(k q) for a radix-r stage needs q < Ls / r: the
+// powers 1, 2, 4, 8 are unit-stride runs of the tables of l = lgs, lgs-1, lgs-2, lgs-3, the others products of them.
+template <int BITS>
+struct StageTw {
+    float2 w[BITS];
+    __device__ __forceinline__ void load(const float2* __restrict__ ft, int lgs, int q)
+    {
+#pragma unroll
+        for (int i = 0; i < BITS; ++i) w[i] = ft[(1 << (lgs - 1 - i)) + q];
+    }
+    // x[k] *= w^k (INV: conj), as w^(k & ~3) and then w^(k & 3): as many multiplications as forming all the powers, and
+    // only six of them live
+    template <bool INV>
+    __device__ __forceinline__ void apply(float2* x) const
+    {
+        constexpr int R = 1 << BITS;
+        const auto mul = [](float2 v, float2 t) { return INV ? cmulc(v, t) : cmul(v, t); };
+#pragma unroll
+        for (int g = 1; g < R / 4; ++g) {
+            const float2 t = g == 1 ? w[2] : g == 2 ? w[BITS - 1] : cmul(w[2], w[BITS - 1]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[4 * g + k] = mul(x[4 * g + k], t);
+        }
+        if constexpr (BITS == 1) {
+            x[1] = mul(x[1], w[0]);
         } else {
-            const size_t off = ((size_t)h * npairs + p) * L + (size_t)k1 * L2;
-            for (int n = tid; n < L2; n += nt) { sz[n] = ws_u[off + n]; sw[n] = ws_dy[off + n]; }
-        }
-        __syncthreads();
-        fft_lds<false>(sz, log2L2, tw, tid, nt);
-        fft_lds<false>(sw, log2L2, tw, tid, nt);
+            const float2 t3 = cmul(w[0], w[1]);
 #pragma unroll
-        for (int i = 0; i < MAXPT; ++i) {
-            const int q = tid + i * nt;
-            if (q < L2) {
-                const float2 z = sz[q], w = sw[q];          // acc += conj(z) * w
-                acc[i].x += z.x * w.x + z.y * w.y;
-                acc[i].y += z.x * w.y - z.y * w.x;
+            for (int g = 0; g < R / 4; ++g) {
+                x[4 * g + 1] = mul(x[4 * g + 1], w[0]);
+                x[4 * g + 2] = mul(x[4 * g + 2], w[1]);
+                x[4 * g + 3] = mul(x[4 * g + 3], t3);
             }
         }
-        __syncthreads();
     }
+};
+
+// The compiler keeps what it can prove unchanged: without this it would hold every twiddle and spectrum value of a
+// transform in registers from one transform (and one turn of the pair loop) to the next, and spill.
+template <class T>
+__device__ __forceinline__ T* fresh(T* p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ int fresh(int v)      // the same for addresses derived from the thread's number
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+template <int LG>
+struct Fft {
+    static constexpr int P = 1 << points_log2(LG), T = (1 << LG) / P, S = stages(LG);
+
+    template <int s>
+    struct St {
+        static constexpr int bits = stage_bits(LG, s), r = 1 << bits, G = P / r;
+        static constexpr int lgs = span_log2(LG, s), lgM = lgs - bits;
+        StageTw<bits> tw[G];
+        // butterfly g of thread tid: number tid + g T, q = its low lgM bits
+        __device__ __forceinline__ static int q_of(int tid, int g) { return (tid + g * T) & ((1 << lgM) - 1); }
+        __device__ __forceinline__ static int base(int tid, int g)
+        {
+            const int b = tid + g * T;
+            return ((b >> lgM) << lgs) | (b & ((1 << lgM) - 1));
+        }
+        __device__ __forceinline__ void load_tw(const float2* __restrict__ ft, int tid)
+        {
+            if constexpr (lgM > 0) {
 #pragma unroll
-    for (int i = 0; i < MAXPT; ++i) {
-        const int q = tid + i * nt;
-        if (q < L2) sz[q] = acc[i];
-    }
-    __syncthreads();
-    fft_lds<true>(sz, log2L2, tw, tid, nt);
-    if (log2R == 0) {
-        if (dk) for (int n = tid; n < N; n += nt) dk[(size_t)h * N + n] = sz[n].x * scale;
-        if (dD) {
-            // fixed-order block reduction
-            for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
-            if ((tid & 63) == 0) red[tid >> 6] = dsum;
+                for (int g = 0; g < G; ++g) tw[g].load(ft, lgs, q_of(tid, g));
+            }
+        }
+        template <bool INV>
+        __device__ __forceinline__ void twiddle(float2 (&x)[P]) const
+        {
+            if constexpr (lgM > 0) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) tw[g].template apply<INV>(x + g * r);
+            }
+        }
+        __device__ __forceinline__ static void write(const float2 (&x)[P], float2* sm, int tid)
+        {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float2* b = sm + phys(base(tid, g));
+#pragma unroll
+                for (int d = 0; d < r; ++d) b[phys(d << lgM)] = x[g * r + d];
+            }
+        }
+        __device__ __forceinline__ static void read(float2 (&x)[P], const float2* sm, int tid)
+        {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float2* b = sm + phys(base(tid, g));
+#pragma unroll
+                for (int d = 0; d < r; ++d) x[g * r + d] = b[phys(d << lgM)];
+            }
+        }
+    };
+
+    // x holds the points of stage s; HALF: those of stage 0 have a zero upper half
+    template <bool HALF, int s = 0>
+    static __device__ __forceinline__ void fwd_from(float2 (&x)[P], const St<s>& st, float2* sm,
+                                                    const float2* __restrict__ ft, int tid)
+    {
+        using C = St<s>;
+#pragma unroll
+        for (int g = 0; g < C::G; ++g) {
+            if constexpr (HALF && s == 0) dft_half_in<C::r>(x + g * C::r);
+            else dft<C::r, false>(x + g * C::r);
+        }
+        st.template twiddle<false>(x);
+        if constexpr (s + 1 < S) {
+            St<s + 1> nx;
+            __builtin_amdgcn_sched_barrier(0);
+            nx.load_tw(ft, tid);               // in front of the barrier: the loads fly while the waves meet
+            C::write(x, sm, tid);
             __syncthreads();
-            if (tid == 0) {
-                float t = 0.f;
-                for (int w = 0; w < (nt >> 6); ++w) t += red[w];
-                dD[h] = t;
+            St<s + 1>::read(x, sm, tid);
+            __builtin_amdgcn_sched_barrier(0);
+            fwd_from<HALF, s + 1>(x, nx, sm, ft, tid);
+        }
+    }
+    template <bool HALF>
+    static __device__ __forceinline__ void fwd(float2 (&x)[P], float2* sm, const float2* __restrict__ ft, int tid)
+    {
+        ft = fresh(ft);
+        tid = fresh(tid);
+        St<0> st;
+        st.load_tw(ft, tid);
+        fwd_from<HALF, 0>(x, st, sm, ft, tid);
+    }
+    // inverse of the above; HALF: only the lower half of stage 0's points is wanted
+    template <bool HALF, int s = S - 1>
+    static __device__ __forceinline__ void inv_from(float2 (&x)[P], const St<s>& st, float2* sm,
+                                                    const float2* __restrict__ ft, int tid)
+    {
+        using C = St<s>;
+        st.template twiddle<true>(x);
+#pragma unroll
+        for (int g = 0; g < C::G; ++g) {
+            if constexpr (HALF && s == 0) dft_half_out<C::r>(x + g * C::r);
+            else dft<C::r, true>(x + g * C::r);
+        }
+        if constexpr (s > 0) {
+            St<s - 1> nx;
+            __builtin_amdgcn_sched_barrier(0);
+            nx.load_tw(ft, tid);
+            C::write(x, sm, tid);
+            __syncthreads();
+            St<s - 1>::read(x, sm, tid);
+            __builtin_amdgcn_sched_barrier(0);
+            inv_from<HALF, s - 1>(x, nx, sm, ft, tid);
+        }
+    }
+    template <bool HALF>
+    static __device__ __forceinline__ void inv(float2 (&x)[P], float2* sm, const float2* __restrict__ ft, int tid)
+    {
+        ft = fresh(ft);
+        tid = fresh(tid);
+        St<S - 1> st;
+        st.load_tw(ft, tid);
+        inv_from<HALF, S - 1>(x, st, sm, ft, tid);
+    }
+
+    // inner frequency of register j of thread tid after the forward stages (digits k_0 + r_0 (k_1 + r_1 (...)))
+    static __device__ __forceinline__ uint32_t freq_of(int tid, int j)
+    {
+        using C = St<S - 1>;
+        const uint32_t pos = (uint32_t)C::base(tid, j / C::r) + (j % C::r);
+        uint32_t f = 0;
+        int have = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int b = stage_bits(LG, s);
+            f |= ((pos >> (span_log2(LG, s) - b)) & ((1u << b) - 1u)) << have;
+            have += b;
+        }
+        return f;
+    }
+    // the stored spectrum of a chunk: registers 2i and 2i+1 of a thread side by side, neighbouring threads next to
+    // each other, so that every load is a unit-stride run of 16 bytes per lane
+    static __device__ __forceinline__ size_t spec_at(int tid, int i) { return (size_t)i * (2 * T) + 2 * tid; }
+};
+
+// ---- pass A while loading (multi-pass split) ------------------------------------------------------------------------
+// Chunk k1's input sample n2 is w_L^(n2 k1) sum_{n1 < R/2} w_R^(n1 k1) z[n1 L2 + n2] (Section 3.2, "Three-Pass
+// Algorithm"): formed from the rows by every chunk's workgroup, so that no complex workspace is written and read in
+// front of the inner transforms.  The twist of sample q + d T is that of q times a factor that only depends on d.
+template <int LG>
+struct Chunk {
+    int log2R, k1;
+    float2 wq;                  // w_L^(k1 q)
+    const float2* tw;
+    __device__ __forceinline__ void init(const float2* __restrict__ tw_, int log2R_, int k1_, int tid)
+    {
+        tw = tw_; log2R = log2R_; k1 = k1_;
+        wq = tw_full(tw, ((uint32_t)(k1 * tid) << (TW_LOG2 - LG - log2R)) & (TW_L - 1));
+    }
+    __device__ __forceinline__ float2 root(int n1) const      // w_R^(n1 k1)
+    {
+        return tw_full(tw, (uint32_t)((n1 * k1) & ((1 << log2R) - 1)) << (TW_LOG2 - log2R));
+    }
+    __device__ __forceinline__ float2 twist(int d) const      // w_L^(k1 (q + d T))
+    {
+        using F = Fft<LG>;
+        return cmul(wq, tw_full(tw, ((uint32_t)(k1 * d * F::T) << (TW_LOG2 - LG - log2R)) & (TW_L - 1)));
+    }
+};
+
+// ---- kernel spectrum (Algorithm 2 lines 1-2) -------------------------------------------------------------------------
+// grid = (R, H).  The skip term D[h]*u is the convolution with a delta of height D[h], whose spectrum is the constant
+// D[h]; it is added here so the fused kernels never touch D.  OWN: stored in the lane order of this file's kernels;
+// otherwise scattered to the consumer's order.
+template <int LG, bool OWN>
+__global__ void __launch_bounds__(Fft<LG>::T)
+fkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* __restrict__ kspec, int64_t N, int log2R,
+              SpecOrder consumer, float scale, const float2* __restrict__ tw, const float2* __restrict__ ft)
+{
+    using F = Fft<LG>;
+    constexpr int P = F::P, T = F::T;
+    extern __shared__ float2 sm[];
+    const int k1 = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+    const float* kr = k + (size_t)h * N;
+    float2 x[P];
+    if (log2R == 0) {
+#pragma unroll
+        for (int d = 0; d < P / 2; ++d) x[d] = make_float2(kr[tid + d * T], 0.f);
+        F::template fwd<true>(x, sm, ft, tid);
+    } else {
+        Chunk<LG> c;
+        c.init(tw, log2R, k1, tid);
+#pragma unroll
+        for (int d = 0; d < P; ++d) x[d] = make_float2(0.f, 0.f);
+        for (int n1 = 0; n1 < (1 << log2R) / 2; ++n1) {
+            const float2 w = c.root(n1);
+#pragma unroll
+            for (int d = 0; d < P; ++d) {
+                const float v = kr[((size_t)n1 << LG) + tid + d * T];
+                x[d].x += w.x * v;
+                x[d].y += w.y * v;
             }
         }
-    } else {
-        float2* o = ws_A + (size_t)h * L + (size_t)k1 * L2;
-        for (int n = tid; n < L2; n += nt) o[n] = sz[n];
+#pragma unroll
+        for (int d = 0; d < P; ++d) x[d] = cmul(x[d], c.twist(d));
+        F::template fwd<false>(x, sm, ft, tid);
+    }
+    const float dh = D ? D[h] : 0.f;
+    float2* out = kspec + ((size_t)h << (LG + log2R));
+    if (OWN) out += (size_t)k1 << LG;
+#pragma unroll
+    for (int i = 0; i < P / 2; ++i) {
+        const float2 a = make_float2((x[2 * i].x + dh) * scale, x[2 * i].y * scale);
+        const float2 b = make_float2((x[2 * i + 1].x + dh) * scale, x[2 * i + 1].y * scale);
+        if (OWN) {
+            *reinterpret_cast<float4*>(out + F::spec_at(tid, i)) = make_float4(a.x, a.y, b.x, b.y);
+        } else {
+            out[spec_pos((uint32_t)k1 + (F::freq_of(tid, 2 * i) << log2R), consumer)] = a;
+            out[spec_pos((uint32_t)k1 + (F::freq_of(tid, 2 * i + 1) << log2R), consumer)] = b;
+        }
     }
 }
 
-int block_for(int log2L2) { return log2L2 <= 10 ? 256 : (log2L2 <= 11 ? 512 : 1024); }
+// the points of stage 0 of one source's row pair
+template <int LG, class IO, bool CHUNK>
+__device__ __forceinline__ void load_pair(float2 (&x)[Fft<LG>::P], const typename IO::T* __restrict__ ra,
+                                          const typename IO::T* __restrict__ rb, bool has_b, const Chunk<LG>& c, int tid)
+{
+    tid = fresh(tid);
+    constexpr int P = Fft<LG>::P, T = Fft<LG>::T;
+    if constexpr (!CHUNK) {
+#pragma unroll
+        for (int d = 0; d < P / 2; ++d) {          // (a missing second row: rb = ra, read and dropped, no branches)
+            const float a = IO::ld(ra, tid + d * T), b = IO::ld(rb, tid + d * T);
+            x[d] = make_float2(a, has_b ? b : 0.f);
+        }
+    } else {
+#pragma unroll
+        for (int d = 0; d < P; ++d) x[d] = make_float2(0.f, 0.f);
+        for (int n1 = 0; n1 < (1 << c.log2R) / 2; ++n1) {
+            const float2 w = c.root(n1);
+            const typename IO::T* pa = ra + ((size_t)n1 << LG);
+            const typename IO::T* pb = rb + ((size_t)n1 << LG);
+            if (has_b) {
+#pragma unroll
+                for (int d = 0; d < P; ++d) {
+                    const float2 z = make_float2(IO::ld(pa, tid + d * T), IO::ld(pb, tid + d * T));
+                    x[d].x += z.x * w.x - z.y * w.y;
+                    x[d].y += z.x * w.y + z.y * w.x;
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < P; ++d) {
+                    const float v = IO::ld(pa, tid + d * T);
+                    x[d].x += v * w.x;
+                    x[d].y += v * w.y;
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < P; ++d) x[d] = cmul(x[d], c.twist(d));
+    }
+}
+// rows (or chunk k1 of the pair's complex workspace) <- the points of stage 0
+template <int LG, class IO, bool CHUNK>
+__device__ __forceinline__ void store_pair(const float2 (&x)[Fft<LG>::P], typename IO::T* __restrict__ ra,
+                                           typename IO::T* __restrict__ rb, bool has_b, float2* __restrict__ chunk, int tid)
+{
+    tid = fresh(tid);
+    constexpr int P = Fft<LG>::P, T = Fft<LG>::T;
+    if constexpr (!CHUNK) {
+#pragma unroll
+        for (int d = 0; d < P / 2; ++d) IO::st(ra, tid + d * T, x[d].x);
+        if (has_b) {
+#pragma unroll
+            for (int d = 0; d < P / 2; ++d) IO::st(rb, tid + d * T, x[d].y);
+        }
+    } else {
+#pragma unroll
+        for (int d = 0; d < P; ++d) chunk[tid + d * T] = x[d];
+    }
+}
+
+template <int LG, bool CONJ>
+__device__ __forceinline__ void times_spectrum(float2 (&x)[Fft<LG>::P], const float2* __restrict__ ks, int tid)
+{
+    tid = fresh(tid);
+#pragma unroll
+    for (int i = 0; i < Fft<LG>::P / 2; ++i) {
+        const float4 k = *reinterpret_cast<const float4*>(ks + Fft<LG>::spec_at(tid, i));
+        const float2 ka = make_float2(k.x, k.y), kb = make_float2(k.z, k.w);
+        x[2 * i] = CONJ ? cmulc(x[2 * i], ka) : cmul(x[2 * i], ka);
+        x[2 * i + 1] = CONJ ? cmulc(x[2 * i + 1], kb) : cmul(x[2 * i + 1], kb);
+    }
+}
+
+// ---- fused convolution of one row pair (Eq. 2 fused as in Section 3.2 "Kernel Fusion") --------------------------------
+//   single pass: z[n] = in[2p,h,n] + i*in[2p+1,h,n], zero padded to L; forward, multiply by the stored spectrum (or its
+//     conjugate: correlation, used for du), inverse, keep the first N samples: re -> out row 2p, im -> out row 2p+1.
+//     Convolution with a real kernel is real-linear, so the two rows never mix.
+//   CHUNK: the same on chunk k1 of the multi-pass split, pass A taken while loading, result to the pair's complex
+//     workspace (Eq. 3: m independent convolutions of length l).
+// grid = (npairs, H, R)
+template <int LG, class IO, bool CHUNK>
+__global__ void __launch_bounds__(Fft<LG>::T)
+fconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
+             float2* __restrict__ ws, int conj, int64_t B, int64_t H, int64_t N, int log2R, const float2* __restrict__ tw,
+             const float2* __restrict__ ft)
+{
+    using F = Fft<LG>;
+    extern __shared__ float2 sm[];
+    const int p = blockIdx.x, h = blockIdx.y, k1 = blockIdx.z, tid = threadIdx.x;
+    const bool has_b = (2 * p + 1) < B;
+    const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
+    float2 x[F::P];
+    Chunk<LG> c;
+    if constexpr (CHUNK) c.init(tw, log2R, k1, tid);
+    load_pair<LG, IO, CHUNK>(x, in + oa, in + ob, has_b, c, tid);
+    F::template fwd<!CHUNK>(x, sm, ft, tid);
+    const float2* ks = kspec + ((size_t)h << (LG + log2R)) + ((size_t)k1 << LG);
+    if (conj) times_spectrum<LG, true>(x, ks, tid);
+    else times_spectrum<LG, false>(x, ks, tid);
+    F::template inv<!CHUNK>(x, sm, ft, tid);
+    float2* chunk = CHUNK ? ws + (((size_t)h * gridDim.x + p) << (LG + log2R)) + ((size_t)k1 << LG) : nullptr;
+    store_pair<LG, IO, CHUNK>(x, out + oa, out + ob, has_b, chunk, tid);
+}
+
+// ---- backward: du, dk and dD in one walk over the head's row pairs ------------------------------------------------------
+// One workgroup per (share, head, chunk); share s of nsplit takes pairs s, s + nsplit, ... in order (deterministic).
+// Per pair: u -> Z, dy -> W, A += conj(Z) W in registers, then (du asked for) W conj(K) back through the inverse.  The
+// real part of the inverse transform of A is the sum over both rows of the correlation dy (x) u, i.e. the pair's share of
+// dk (the cross terms between the two rows are purely imaginary).  dD is the plain dot product, taken while both
+// sources' rows are in registers.  dy is read and transformed once for both gradients.
+//   dk: [nsplit][H][N] real samples times `scale`, or (CHUNK) A: [nsplit][H][R][L2] complex for pass C
+//   dD: [nsplit][H]
+// At L2 = 16384 a thread may hold 128 registers (sixteen waves); accumulators, Z and the points in work do not fit into
+// them (spilled: 120 registers a thread), so Z waits in zbuf, [R][H][nsplit] sequences that stay in L2, written and
+// read by the same thread (B=4, H=96, N=8192: 62 -> 47 us).
+template <int LG, class IO, bool CHUNK>
+__global__ void __launch_bounds__(Fft<LG>::T)
+fbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ kspec,
+            typename IO::T* __restrict__ du, float2* __restrict__ ws_du, float* __restrict__ dk, float2* __restrict__ ws_A,
+            float* __restrict__ dD, float4* __restrict__ zbuf, int64_t B, int64_t H, int64_t N, int npairs, int log2R,
+            float scale, const float2* __restrict__ tw, const float2* __restrict__ ft)
+{
+    constexpr bool PARK = valu_parks(LG);
+    constexpr bool PREFETCH = LG <= 13;       // dy's rows fetched with u's: where the registers for them are there
+    if constexpr (PARK) zbuf += ((size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) << (LG - 1);
+    using F = Fft<LG>;
+    constexpr int P = F::P, T = F::T;
+    extern __shared__ float2 sm[];
+    __shared__ float red[T >= 64 ? T / 64 : 1];
+    const int share = blockIdx.x, nsplit = gridDim.x, h = blockIdx.y, k1 = blockIdx.z, tid = threadIdx.x;
+    const bool want_du = CHUNK ? ws_du != nullptr : du != nullptr;
+    const float2* ks = kspec + ((size_t)h << (LG + log2R)) + ((size_t)k1 << LG);
+    Chunk<LG> c;
+    if constexpr (CHUNK) c.init(tw, log2R, k1, tid);
+    float2 acc[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) acc[i] = make_float2(0.f, 0.f);
+    float dsum = 0.f;
+    for (int p = share; p < npairs; p += nsplit) {
+        const bool has_b = (2 * p + 1) < B;
+        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
+        float2 z[P], w[P];
+        load_pair<LG, IO, CHUNK>(z, u + oa, u + ob, has_b, c, tid);
+        if constexpr (!CHUNK && PREFETCH) {
+            load_pair<LG, IO, CHUNK>(w, dy + oa, dy + ob, has_b, c, tid);
+#pragma unroll
+            for (int d = 0; d < P / 2; ++d) dsum += z[d].x * w[d].x + z[d].y * w[d].y;
+        } else if (CHUNK && k1 == 0 && dD) {
+            // (several samples in flight: one at a time, N = 65536 took 64 round trips to memory in a row)
+            for (int row = 0; row < (has_b ? 2 : 1); ++row) {
+                const typename IO::T* pu = u + (row ? ob : oa);
+                const typename IO::T* pd = dy + (row ? ob : oa);
+#pragma unroll 16
+                for (int n = 0; n < (int)N; n += T) dsum += IO::ld(pu, n + tid) * IO::ld(pd, n + tid);
+            }
+        }
+        F::template fwd<!CHUNK>(z, sm, ft, tid);
+        if constexpr (PARK) {
+            const int t = fresh(tid);
+#pragma unroll
+            for (int i = 0; i < P / 2; ++i) zbuf[i * T + t] = make_float4(z[2 * i].x, z[2 * i].y, z[2 * i + 1].x, z[2 * i + 1].y);
+        }
+        if constexpr (CHUNK || !PREFETCH) load_pair<LG, IO, CHUNK>(w, dy + oa, dy + ob, has_b, c, tid);
+        if constexpr (!CHUNK && !PREFETCH) {  // (u once more, from L2, instead of dy's rows held through z's transform)
+            if (dD) {
+                float2 v[P];
+                load_pair<LG, IO, CHUNK>(v, u + oa, u + ob, has_b, c, fresh(tid));
+#pragma unroll
+                for (int d = 0; d < P / 2; ++d) dsum += v[d].x * w[d].x + v[d].y * w[d].y;
+            }
+        }
+        __syncthreads();                      // the last stage of z has been read everywhere
+        F::template fwd<!CHUNK>(w, sm, ft, tid);
+        if constexpr (PARK) {
+            const float4* zb = fresh(zbuf);
+            const int t = fresh(tid);
+#pragma unroll
+            for (int i = 0; i < P / 2; ++i) {
+                const float4 v = zb[i * T + t];
+                z[2 * i] = make_float2(v.x, v.y);
+                z[2 * i + 1] = make_float2(v.z, v.w);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) {         // acc += conj(z) * w
+            acc[i].x += z[i].x * w[i].x + z[i].y * w[i].y;
+            acc[i].y += z[i].x * w[i].y - z[i].y * w[i].x;
+        }
+        if (want_du) {
+            times_spectrum<LG, true>(w, fresh(ks), tid);
+            F::template inv<!CHUNK>(w, sm, ft, tid);
+            float2* chunk = CHUNK ? ws_du + (((size_t)h * npairs + p) << (LG + log2R)) + ((size_t)k1 << LG) : nullptr;
+            store_pair<LG, IO, CHUNK>(w, du + oa, du + ob, has_b, chunk, tid);
+        } else {
+            __syncthreads();
+        }
+    }
+    if (CHUNK ? ws_A != nullptr : dk != nullptr) {
+        __syncthreads();
+        F::template inv<!CHUNK>(acc, sm, ft, tid);
+        const size_t row = (size_t)share * H + h;
+        if constexpr (!CHUNK) {
+            float* o = dk + row * N;
+#pragma unroll
+            for (int d = 0; d < P / 2; ++d) o[tid + d * T] = acc[d].x * scale;
+        } else {
+            float2* o = ws_A + (row << (LG + log2R)) + ((size_t)k1 << LG);
+#pragma unroll
+            for (int d = 0; d < P; ++d) o[tid + d * T] = acc[d];
+        }
+    }
+    if (dD && k1 == 0) {                      // fixed-order sum over the workgroup
+        for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
+        if ((tid & 63) == 0) red[tid >> 6] = dsum;
+        __syncthreads();
+        if (tid == 0) {
+            float t = 0.f;
+            for (int i = 0; i < (T + 63) / 64; ++i) t += red[i];
+            dD[(size_t)share * H + h] = t;
+        }
+    }
+}
 
 template <class F>
 hipError_t set_lds(F* f, size_t bytes)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)bytes);
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+// twiddles of the stages: entry 2^(l-1) + q = w_{2^l}^q
+__device__ float2 g_ftw[1 << VALU_INNER_MAX_LOG2];
+__global__ void fill_ftw_kernel(float2* ft)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 1 || i >= (1 << VALU_INNER_MAX_LOG2)) return;
+    const int l = 32 - __clz(i), q = i - (1 << (l - 1));
+    double s, c;
+    sincospi(-2.0 * (double)q / (double)(1 << l), &s, &c);
+    ft[i] = make_float2((float)c, (float)s);
+}
+
+#define LC_LG_SWITCH(lg, CALL)                \
+    switch (lg) {                             \
+        case 8: return CALL(8);               \
+        case 9: return CALL(9);               \
+        case 10: return CALL(10);             \
+        case 11: return CALL(11);             \
+        case 12: return CALL(12);             \
+        case 13: return CALL(13);             \
+        case 14: return CALL(14);             \
+        default: return hipErrorInvalidValue; \
+    }
+
+template <int LG>
+hipError_t kspec_go(const float* k, const float* D, float2* kspec, int64_t H, int64_t N, int log2R, const SpecOrder* consumer,
+                    float scale, const Tables& tb, hipStream_t st)
+{
+    const dim3 grid(1u << log2R, (unsigned)H);
+    hipError_t e;
+    if (!consumer) {
+        if ((e = set_lds(fkspec_kernel<LG, true>, lds_bytes(LG))) != hipSuccess) return e;
+        hipLaunchKernelGGL((fkspec_kernel<LG, true>), grid, dim3(Fft<LG>::T), lds_bytes(LG), st, k, D, kspec, N, log2R,
+                           SpecOrder{}, scale, tb.tw, tb.ftw);
+    } else {
+        if ((e = set_lds(fkspec_kernel<LG, false>, lds_bytes(LG))) != hipSuccess) return e;
+        hipLaunchKernelGGL((fkspec_kernel<LG, false>), grid, dim3(Fft<LG>::T), lds_bytes(LG), st, k, D, kspec, N, log2R,
+                           *consumer, scale, tb.tw, tb.ftw);
+    }
+    return hipGetLastError();
+}
+
+template <int LG, class IO, bool CHUNK>
+hipError_t conv_go(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr, int log2R,
+                   const Tables& tb, hipStream_t st)
+{
+    using T = typename IO::T;
+    const hipError_t e = set_lds(fconv_kernel<LG, IO, CHUNK>, lds_bytes(LG));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fconv_kernel<LG, IO, CHUNK>), dim3(pr.npairs, (unsigned)pr.H, 1u << log2R), dim3(Fft<LG>::T),
+                       lds_bytes(LG), st, (const T*)in, kspec, (T*)out, ws, conj ? 1 : 0, pr.B, pr.H, pr.N, log2R, tb.tw,
+                       tb.ftw);
+    return hipGetLastError();
+}
+
+template <class IO>
+hipError_t conv_io(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
+                   const Plan& pl, const Tables& tb, hipStream_t st)
+{
+#define CALL(LG)                                                                            \
+    (pl.log2R ? conv_go<LG, IO, true>(in, kspec, out, ws, conj, pr, pl.log2R, tb, st)        \
+              : conv_go<LG, IO, false>(in, kspec, out, ws, conj, pr, 0, tb, st))
+    LC_LG_SWITCH(pl.log2L2, CALL)
+#undef CALL
+}
+
+template <int LG, class IO, bool CHUNK>
+hipError_t bwd_go(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
+                  float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
+{
+    using T = typename IO::T;
+    const hipError_t e = set_lds(fbwd_kernel<LG, IO, CHUNK>, lds_bytes(LG));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fbwd_kernel<LG, IO, CHUNK>), dim3(nsplit, (unsigned)pr.H, 1u << pl.log2R), dim3(Fft<LG>::T),
+                       lds_bytes(LG), st, (const T*)dy, (const T*)u, kspec, (T*)du, ws_du, dk, ws_A, dD, (float4*)zbuf, pr.B, pr.H, pr.N,
+                       pr.npairs, pl.log2R, pl.dkscale, tb.tw, tb.ftw);
+    return hipGetLastError();
+}
+
+template <class IO>
+hipError_t bwd_io(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
+                  float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
+{
+#define CALL(LG)                                                                                            \
+    (pl.log2R ? bwd_go<LG, IO, true>(dy, u, kspec, nullptr, ws_du, nullptr, ws_A, dD, zbuf, nsplit, pr, pl, tb, st) \
+              : bwd_go<LG, IO, false>(dy, u, kspec, du, nullptr, dk, nullptr, dD, zbuf, nsplit, pr, pl, tb, st))
+    LC_LG_SWITCH(pl.log2L2, CALL)
+#undef CALL
 }
 
 }  // namespace
 
-hipError_t valu_kspec(const float* k, const float2* ws, const float* D, float2* kspec, int64_t H,
-                      int64_t N, int log2R, int log2L2, const SpecOrder& consumer, float scale,
-                      const float2* tw, hipStream_t st)
+hipError_t valu_fill_tables(const float2** ftw, hipStream_t st)
 {
-    const size_t lds = sizeof(float2) << log2L2;
-    hipError_t e = set_lds(kspec_kernel, lds);
+    float2* p = nullptr;
+    const hipError_t e = hipGetSymbolAddress((void**)&p, HIP_SYMBOL(g_ftw));
     if (e != hipSuccess) return e;
-    dim3 grid(1u << log2R, (unsigned)H);
-    hipLaunchKernelGGL(kspec_kernel, grid, dim3(block_for(log2L2)), lds, st, k, ws, D, kspec, N, log2R,
-                       log2L2, consumer, scale, tw);
+    constexpr int n = 1 << VALU_INNER_MAX_LOG2;
+    hipLaunchKernelGGL(fill_ftw_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p);
+    *ftw = p;
     return hipGetLastError();
 }
 
-template <class IO>
-static hipError_t conv_launch(const void* in, const float2* kspec, void* out, float2* ws, bool conj,
-                              const Problem& pr, const Plan& pl, const float2* tw, hipStream_t st)
+void valu_fill_plan(Plan& pl)
 {
-    const size_t lds = sizeof(float2) << pl.log2L2;
-    hipError_t e = set_lds(conv_kernel<IO>, lds);
-    if (e != hipSuccess) return e;
-    dim3 grid(pr.npairs, (unsigned)pr.H, 1u << pl.log2R);
-    hipLaunchKernelGGL(conv_kernel<IO>, grid, dim3(block_for(pl.log2L2)), lds, st,
-                       (const typename IO::T*)in, kspec, (typename IO::T*)out, ws, conj ? 1 : 0, pr.B,
-                       pr.H, pr.N, pl.log2R, pl.log2L2, tw);
-    return hipGetLastError();
+    pl.order = SpecOrder{};
+    if (pl.log2R) pl.order.bits[pl.order.ndig++] = (unsigned char)pl.log2R;
+    for (int s = 0; s < stages(pl.log2L2); ++s) pl.order.bits[pl.order.ndig++] = (unsigned char)stage_bits(pl.log2L2, s);
+    pl.kscale = pl.dkscale = 1.0f / (float)(int64_t(1) << pl.log2L);
 }
 
-hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj,
-                     const Problem& pr, const Plan& pl, const float2* tw, hipStream_t st)
+hipError_t valu_kspec(const float* k, const float* D, float2* kspec, int64_t H, int64_t N, const SpecOrder* consumer,
+                      float scale, const Tables& tb, int log2R, int log2L2, hipStream_t st)
+{
+#define CALL(LG) kspec_go<LG>(k, D, kspec, H, N, log2R, consumer, scale, tb, st)
+    LC_LG_SWITCH(log2L2, CALL)
+#undef CALL
+}
+
+hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
+                     const Plan& pl, const Tables& tb, hipStream_t st)
 {
     switch (pr.io) {
-        case LONGCONV_F32: return conv_launch<IoF32>(in, kspec, out, ws, conj, pr, pl, tw, st);
-        case LONGCONV_F16: return conv_launch<IoF16>(in, kspec, out, ws, conj, pr, pl, tw, st);
-        default: return conv_launch<IoBF16>(in, kspec, out, ws, conj, pr, pl, tw, st);
+        case LONGCONV_F32: return conv_io<IoF32>(in, kspec, out, ws, conj, pr, pl, tb, st);
+        case LONGCONV_F16: return conv_io<IoF16>(in, kspec, out, ws, conj, pr, pl, tb, st);
+        default: return conv_io<IoBF16>(in, kspec, out, ws, conj, pr, pl, tb, st);
     }
 }
 
-template <class IO>
-static hipError_t dk_launch(const void* dy, const void* u, float* dk, float* dD, const float2* ws_u,
-                            const float2* ws_dy, float2* ws_A, const Problem& pr, const Plan& pl,
-                            const float2* tw, hipStream_t st)
+// Workgroups that fill the device: one, two or about four of them per compute unit by their LDS
+int valu_bwd_nsplit(int64_t H, int npairs, const Plan& pl)
 {
-    const size_t lds = 2 * (sizeof(float2) << pl.log2L2);
-    const int nt = block_for(pl.log2L2);
-    dim3 grid((unsigned)pr.H, 1u << pl.log2R);
-    using T = typename IO::T;
-#define LC_DK(MAXPT)                                                                                  \
-    {                                                                                                 \
-        hipError_t e = set_lds(dk_kernel<IO, MAXPT>, lds);                                            \
-        if (e != hipSuccess) return e;                                                                \
-        hipLaunchKernelGGL((dk_kernel<IO, MAXPT>), grid, dim3(nt), lds, st, (const T*)dy, (const T*)u, \
-                           dk, dD, ws_u, ws_dy, ws_A, pr.B, pr.H, pr.N, pr.npairs, pl.log2R,           \
-                           pl.log2L2, pl.dkscale, tw);                                                 \
-    }
-    const int per = (1 << pl.log2L2) / nt;
-    if (per <= 1) LC_DK(1) else if (per <= 2) LC_DK(2) else if (per <= 4) LC_DK(4) else LC_DK(8)
-#undef LC_DK
-    return hipGetLastError();
+    const int target = pl.log2L2 >= 14 ? 256 : pl.log2L2 == 13 ? 512 : 1024;
+    int64_t s = target / (H << pl.log2R);
+    if (s > npairs) s = npairs;
+    if (s > 64) s = 64;
+    return s < 1 ? 1 : (int)s;
 }
 
-hipError_t valu_dk(const void* dy, const void* u, float* dk, float* dD, const float2* ws_u,
-                   const float2* ws_dy, float2* ws_A, const Problem& pr, const Plan& pl, const float2* tw,
-                   hipStream_t st)
+size_t valu_zbuf_bytes(int64_t H, int nsplit, const Plan& pl)
+{
+    return valu_parks(pl.log2L2) ? ((size_t)H * nsplit << pl.log2L) * sizeof(float2) : 0;
+}
+
+hipError_t valu_bwd(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
+                    float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     switch (pr.io) {
-        case LONGCONV_F32: return dk_launch<IoF32>(dy, u, dk, dD, ws_u, ws_dy, ws_A, pr, pl, tw, st);
-        case LONGCONV_F16: return dk_launch<IoF16>(dy, u, dk, dD, ws_u, ws_dy, ws_A, pr, pl, tw, st);
-        default: return dk_launch<IoBF16>(dy, u, dk, dD, ws_u, ws_dy, ws_A, pr, pl, tw, st);
+        case LONGCONV_F32: return bwd_io<IoF32>(dy, u, kspec, du, ws_du, dk, ws_A, dD, zbuf, nsplit, pr, pl, tb, st);
+        case LONGCONV_F16: return bwd_io<IoF16>(dy, u, kspec, du, ws_du, dk, ws_A, dD, zbuf, nsplit, pr, pl, tb, st);
+        default: return bwd_io<IoBF16>(dy, u, kspec, du, ws_du, dk, ws_A, dD, zbuf, nsplit, pr, pl, tb, st);
     }
 }
 

@@ -40,13 +40,13 @@ hipError_t rows_absmax(const void* in, uint32_t* mx, const Problem& pr, hipStrea
 bool conv_applies_gate(const Plan& pl, bool fuse_a);
 
 // ---- outer passes of the multi-pass split (multipass.hip) ------------------------
-// Pass A: ws[(h*npairs+p)*L + k1*L2 + n2] = scale * w_L^(n2*k1) * sum_{n1<R/2} w_R^(n1*k1) z[n1*L2+n2],
+// Pass A (matrix-core engine, fp16 workspace): ws[(h*npairs+p)*L + k1*L2 + n2] = scale * w_L^(n2*k1) * sum_{n1<R/2} w_R^(n1*k1) z[n1*L2+n2],
 // z = row(2p) + i*row(2p+1) of `in` (I/O dtype `io`; rows beyond B read as zero).
 // If in2/ws2 are given the same is done for a second tensor in the same launch and, if
 // dD_part != NULL, per-block partial sums of in*in2 are written for the dD reduction.
 hipError_t outer_fwd(const void* in, const void* in2, void* ws, void* ws2, float* dD_part,
-                     const Problem& pr, int log2R, int log2L2, float scale, bool ws_f16,
-                     const float2* tw, hipStream_t st, const float* head_max = nullptr);
+                     const Problem& pr, int log2R, int log2L2, float scale, const float2* tw, hipStream_t st,
+                     const float* head_max = nullptr);
 // stats[h] = max_n |k[h,n]| (consumers derive the head's power-of-two pre-scale with head_scale_of()),
 // stats[H + h] and stats[2H + h] = the upper and lower bound statistics of spec_exponent(); the buffer holds
 // head_stats_floats(H, N) floats (the three statistics and the partial results they are summed from).
@@ -100,19 +100,23 @@ hipError_t kreg_bwd(const float* k, const float* mask, const float* dkbar, float
                     float lam, hipStream_t st);
 
 // ---- fp32 VALU engine (engine_valu.hip) --------------------------------------------
-// Spectrum of one head (or of one chunk of the multi-pass split) in fp32, scattered to the
-// consumer's storage order.  Used for every dtype: the spectrum is always computed in fp32.
-// Handles inner lengths up to 2^14; longer transforms go through outer_fwd first.
-hipError_t valu_kspec(const float* k, const float2* ws, const float* D, float2* kspec, int64_t H,
-                      int64_t N, int log2R, int log2L2, const SpecOrder& consumer, float scale,
-                      const float2* tw, hipStream_t st);
-constexpr int VALU_KSPEC_MAX_LOG2 = 14;
-constexpr int VALU_INNER_MAX_LOG2 = 13;
-hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj,
-                     const Problem& pr, const Plan& pl, const float2* tw, hipStream_t st);
-hipError_t valu_dk(const void* dy, const void* u, float* dk, float* dD, const float2* ws_u,
-                   const float2* ws_dy, float2* ws_A, const Problem& pr, const Plan& pl, const float2* tw,
-                   hipStream_t st);
+constexpr int VALU_INNER_MAX_LOG2 = 14;
+hipError_t valu_fill_tables(const float2** ftw, hipStream_t st);
+void valu_fill_plan(Plan& pl);
+// Spectrum of all heads in fp32, as R = 2^log2R chunks of 2^log2L2 points (pass A taken inside the kernel), stored in
+// the order of the engine's own kernels, or scattered to `consumer`'s order if that is given.
+hipError_t valu_kspec(const float* k, const float* D, float2* kspec, int64_t H, int64_t N, const SpecOrder* consumer,
+                      float scale, const Tables& tb, int log2R, int log2L2, hipStream_t st);
+// Multi-pass plans: pass A is taken inside the kernels, ws receives pass C's input.
+hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
+                     const Plan& pl, const Tables& tb, hipStream_t st);
+// du, dk and dD in one kernel; any of du / ws_du (multi-pass), dk / ws_A (multi-pass) and dD may be null.  nsplit > 1: dk
+// (or ws_A) and dD point to partial buffers [nsplit][...] that sum_partials() adds up in share order.
+// zbuf: valu_zbuf_bytes() of scratch.
+int valu_bwd_nsplit(int64_t H, int npairs, const Plan& pl);
+size_t valu_zbuf_bytes(int64_t H, int nsplit, const Plan& pl);
+hipError_t valu_bwd(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
+                    float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 
 // ---- fp16 MFMA engine (engine_mfma.hip) ---------------------------------------------
 constexpr int MFMA_INNER_MAX_LOG2 = 15;

@@ -477,20 +477,13 @@ hipError_t inv_r(const void* ws, void* out, const Problem& pr, int log2R, int lo
 int outer_fwd_blocks_per_head(const Problem& pr, int log2L2) { return pr.npairs * ((1 << log2L2) / OB); }
 
 hipError_t outer_fwd(const void* in, const void* in2, void* ws, void* ws2, float* dD_part, const Problem& pr,
-                     int log2R, int log2L2, float scale, bool ws_f16, const float2* tw, hipStream_t st,
-                     const float* head_scale)
+                     int log2R, int log2L2, float scale, const float2* tw, hipStream_t st, const float* head_scale)
 {
     if ((1 << log2L2) < OB) return hipErrorInvalidValue;
-#define GO(IO, CW) return fwd_r<IO, CW>(in, in2, ws, ws2, dD_part, pr, log2R, log2L2, scale, tw, st, head_scale)
-    if (ws_f16) {
-        if (pr.io == LONGCONV_F32) GO(IoF32, CwF16);
-        if (pr.io == LONGCONV_F16) GO(IoF16, CwF16);
-        GO(IoBF16, CwF16);
-    } else {
-        if (pr.io == LONGCONV_F32) GO(IoF32, CwF32);
-        if (pr.io == LONGCONV_F16) GO(IoF16, CwF32);
-        GO(IoBF16, CwF32);
-    }
+#define GO(IO) return fwd_r<IO, CwF16>(in, in2, ws, ws2, dD_part, pr, log2R, log2L2, scale, tw, st, head_scale)
+    if (pr.io == LONGCONV_F32) GO(IoF32);
+    if (pr.io == LONGCONV_F16) GO(IoF16);
+    GO(IoBF16);
 #undef GO
 }
 

@@ -211,3 +211,19 @@ def test_full_size_sampled(key):
     from gpu_harness import check_sampled, sample_heads
     w = wl.WORKLOADS[key]
     check_sampled(wl.generate(w), sample_heads(w.H, w.B, seed=w.N + w.wid))
+
+
+@pytest.mark.parametrize("N,B,H", [(256, 3, 2), (512, 1, 3), (1024, 6, 1), (2048, 3, 2), (4096, 3, 2), (8192, 3, 2),
+                                   (16384, 3, 1), (32768, 1, 2)])
+def test_fp32_engine_every_length(N, B, H):
+    # every radix schedule of the fp32 engine, the last pair half empty or the pairs dealt to several workgroups, and
+    # the gradients asked for alone (the fused backward kernel without du, the convolution kernel for du)
+    from gpu_harness import GpuRun, check_full
+    inp = wl.generate(_w("1", N=N), B=B, H=H)
+    check_full(inp, label=f"fp32 N={N}")
+    g = GpuRun(inp)
+    du, dk, dD = [a.copy() for a in g.bwd()]
+    g.dk.fill_(float("nan")), g.dD.fill_(float("nan")), g.du.fill_(float("nan"))
+    dk1, dD1 = g.bwd(du=False)[1:]
+    assert np.array_equal(dk1, dk) and np.array_equal(dD1, dD)
+    assert wl.rel_l2(g.bwd(dk=False, dD=False)[0], du) < 1e-6
