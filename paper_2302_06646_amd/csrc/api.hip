@@ -1,5 +1,5 @@
 // C-ABI layer of liblongconv: argument validation, planning, workspace carving, dispatch.
-// Every step of the path runs in the kernels of engine_wave.hip (512..4096 points), engine_coop.hip
+// Every step of the path runs in the kernels of engine_rows.hip (rows of 256..4096 samples), engine_coop.hip
 // (8192..32768 points, and the inner transforms of longer ones), multipass.hip (outer passes), engine_valu.hip
 // (fp32 I/O), engine_mfma.hip (first-generation in-place kernel, kept as a cross-check behind a switch and
 // for 256-point inner transforms), kreg.hip (kernel regularisers), gate.hip (the gate's streaming pass) and
@@ -77,7 +77,7 @@ static hipError_t get_tables(Tables* out, hipStream_t st, bool sync_device, void
         hipLaunchKernelGGL(fill_stw_kernel, dim3((STW_TOTAL + 255) / 256), dim3(256), 0, st, q);
         e = note(hipGetLastError(), "fill tables");
         if (e != hipSuccess) return e;
-        e = note(wave_fill_tables(&g_tab[dev].wtab, st), "fill wave tables");
+        e = note(rows_fill_tables(&g_tab[dev].rtab, st), "fill row tables");
         if (e != hipSuccess) return e;
         e = note(coop_fill_tables(&g_tab[dev].ctab, st), "fill coop tables");
         if (e != hipSuccess) return e;
@@ -179,7 +179,8 @@ struct WsLayout {
 static int dk_nsplit(int64_t B, int64_t H, const Plan& pl)
 {
     if (pl.engine == ENGINE_VALU) return valu_bwd_nsplit(H, (int)((B + 1) / 2), pl);
-    if (pl.engine != ENGINE_MFMA || pl.log2R || !(pl.order.wave_lg || pl.order.coop_lg)) return 1;
+    if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_nsplit(B, H, pl.order.wave_lg);
+    if (pl.engine != ENGINE_MFMA || pl.log2R || !pl.order.coop_lg) return 1;
     const int64_t npairs = (B + 1) / 2;
     int64_t s = 384 / H;
     if (s > npairs) s = npairs;
@@ -244,12 +245,12 @@ static bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 
 // Spectrum of all heads into `kspec` (storage order and scale of plan `pl`).
 static hipError_t run_kspec(const float* k, const float* D, float2* kspec, float2* kscratch, float* hscale,
-                            int64_t H, int64_t N, const Plan& pl, const Tables& tb, hipStream_t st)
+                            int64_t H, int64_t N, const Plan& pl, const Tables& tb, hipStream_t st, uint32_t pad = 0)
 {
     const float2* tw = tb.tw;
     if (pl.engine == ENGINE_MFMA && (pl.order.wave_lg || pl.order.coop_lg)) {
         // matrix-core route: per-head power-of-two pre-scale, (pass A,) forward half of the fused kernel
-        if (pl.order.wave_lg) return wave_kspec(k, D, kspec, H, N, pl, tb, st);
+        if (pl.order.wave_lg) return rows_kspec(k, D, kspec, H, pl, pad, tb, st);
         // single pass, or pass A taken inside the kernel: it reads k itself and finds the maxima
         // (outer radix 8: eight chunks per head would each scan 512 KB, so the maxima are found once, in front)
         if (!pl.log2R || (pl.fuse_a && pl.log2R < 3)) return coop_kspec(k, nullptr, D, nullptr, kspec, H, N, pl, tb, st);
@@ -348,7 +349,7 @@ int longconv_kspec_compute(const float* k, const float* D, void* kspec, int64_t 
 // otherwise the caller's.
 static int fwd_impl(const void* u, const float* k, const float* D, const void* kspec, void* y, int64_t B,
                     int64_t H, int64_t N, int io, void* workspace, size_t workspace_bytes, void* stream,
-                    bool own_scratch, const void* gate = nullptr)
+                    bool own_scratch, const void* gate = nullptr, uint32_t pad = 0)
 {
     int s = check_shape(B, H, N, io);
     if (s != LONGCONV_OK) return s;
@@ -369,11 +370,12 @@ static int fwd_impl(const void* u, const float* k, const float* D, const void* k
     const float2* ks = (const float2*)kspec;
     if (!ks) {
         if (note(run_kspec(k, D, (float2*)(base + w.kspec), (float2*)(base + w.kscratch), (float*)(base + w.hscale),
-                           H, N, pl, tb, st), "kspec") != hipSuccess)
+                           H, N, pl, tb, st, pad), "kspec") != hipSuccess)
             return LONGCONV_ERR_HIP;
         ks = (const float2*)(base + w.kspec);
     }
     Problem pr{B, H, N, io, (int)((B + 1) / 2)};
+    pr.pad = pad;
     if (rows_rescaled(pl, io)) {
         uint32_t* mx = (uint32_t*)(base + w.rowmx);
         if (note(rows_absmax(u, mx, pr, st), "rows max") != hipSuccess) return LONGCONV_ERR_HIP;
@@ -447,9 +449,9 @@ int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float
     return LONGCONV_OK;
 }
 
-int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, const void* kspec, void* du,
-                 float* dk, float* dD, int64_t B, int64_t H, int64_t N, int io, void* workspace,
-                 size_t workspace_bytes, void* stream)
+static int bwd_impl(const void* dy, const void* u, const float* k, const float* D, const void* kspec, void* du,
+                    float* dk, float* dD, int64_t B, int64_t H, int64_t N, int io, void* workspace,
+                    size_t workspace_bytes, void* stream, uint32_t pad)
 {
     int s = check_shape(B, H, N, io);
     if (s != LONGCONV_OK) return s;
@@ -467,6 +469,7 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
     const float2* tw = tb.tw;
     char* base = (char*)workspace;
     Problem pr{B, H, N, io, (int)((B + 1) / 2)};
+    pr.pad = pad;
     const bool f16ws = pl.engine == ENGINE_MFMA;
     bool dy_ready = false;   // multi-pass: pass A of dy already in ws1
     uint32_t* mx_u = nullptr;      // bf16 rows of these multi-pass plans: per-head maxima of u and dy
@@ -480,21 +483,21 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
         if (note(e, "rows max") != hipSuccess) return LONGCONV_ERR_HIP;
     }
 
-    if (want_dkD && du && pl.engine == ENGINE_MFMA && wave_bwd_ok(pl)) {
+    if (want_dkD && du && pl.engine == ENGINE_MFMA && pl.fuse_bwd) {
         // everything from one kernel: dy and u are read once, dy is transformed once
         const float2* ks = (const float2*)kspec;
         if (!ks) {
             if (note(run_kspec(k, D, (float2*)(base + w.kspec), (float2*)(base + w.kscratch),
-                               (float*)(base + w.hscale), H, N, pl, tb, st), "kspec") != hipSuccess)
+                               (float*)(base + w.hscale), H, N, pl, tb, st, pad), "kspec") != hipSuccess)
                 return LONGCONV_ERR_HIP;
             ks = (const float2*)(base + w.kspec);
         }
         const int ns = w.nsplit;
         float* dkp = (float*)(base + w.dkpart);
         float* ddp = (float*)(base + w.ddpart);
-        hipError_t e = wave_bwd(dy, u, ks, du, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD ? ddp : nullptr) : dD, ns,
+        hipError_t e = rows_bwd(dy, u, ks, du, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD ? ddp : nullptr) : dD, ns,
                                 pr, pl, tb, st);
-        if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * N, ddp, dD, (size_t)H, ns, st);
+        if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * (pad ? N / 2 : N), ddp, dD, (size_t)H, ns, st);
         if (note(e, "bwd") != hipSuccess) return LONGCONV_ERR_HIP;
         return LONGCONV_OK;
     }
@@ -551,7 +554,7 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
                 e = mfma_dk(dy, u, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD1 ? ddp : nullptr) : dD1, ns,
                             (const __half2*)(base + w.ws2), (const __half2*)(base + w.ws1), (__half2*)(base + w.wsA),
                             nullptr, base + w.zbuf, pr, pl, tb, st);
-                if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * N, ddp, dD1, (size_t)H, ns, st);
+                if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * (pad ? N / 2 : N), ddp, dD1, (size_t)H, ns, st);
             }
         }
         if (e == hipSuccess && pl.log2R && dk) {
@@ -570,7 +573,7 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
         const float2* ks = (const float2*)kspec;
         if (!ks) {
             if (note(run_kspec(k, D, (float2*)(base + w.kspec), (float2*)(base + w.kscratch),
-                               (float*)(base + w.hscale), H, N, pl, tb, st), "kspec") != hipSuccess)
+                               (float*)(base + w.hscale), H, N, pl, tb, st, pad), "kspec") != hipSuccess)
                 return LONGCONV_ERR_HIP;
             ks = (const float2*)(base + w.kspec);
         }
@@ -582,7 +585,17 @@ int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, 
     return LONGCONV_OK;
 }
 
+int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, const void* kspec, void* du,
+                 float* dk, float* dD, int64_t B, int64_t H, int64_t N, int io, void* workspace,
+                 size_t workspace_bytes, void* stream)
+{
+    return bwd_impl(dy, u, k, D, kspec, du, dk, dD, B, H, N, io, workspace, workspace_bytes, stream, 0);
+}
+
 // ---- 2-D long convolution: rows padded to twice their width, then the 1-D path on the row-major sequence -------
+// The single-row kernels pad while they load and drop the padding while they store; for the other plans padded copies
+// are made in the workspace.
+static bool pads_itself(const Plan& pl) { return pl.engine == ENGINE_MFMA && pl.order.wave_lg; }
 
 struct Ws2d {
     size_t base, kp, up, yp, dup, dkp, total;     // byte offsets; base = size of the 1-D call's own workspace
@@ -626,6 +639,8 @@ int longconv2d_fwd(const void* u, const float* k, const float* D, void* y, int64
     const int64_t N = 2 * N1 * N2;
     const Ws2d w = carve2d(B, H, N, io, false);
     if (!workspace || workspace_bytes < w.total) return LONGCONV_ERR_WORKSPACE;
+    if (pads_itself(make_plan(N, io)))
+        return fwd_impl(u, k, D, nullptr, y, B, H, N, io, workspace, w.base, stream, false, nullptr, (uint32_t)N2);
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)workspace;
     if (note(pad_rows(k, ws + w.kp, (size_t)H * N1, (size_t)N2 * sizeof(float), st), "pad k") != hipSuccess ||
@@ -651,6 +666,8 @@ int longconv2d_bwd(const void* dy, const void* u, const float* k, const float* D
     const Ws2d w = carve2d(B, H, N, io, true);
     if (!workspace || workspace_bytes < w.total) return LONGCONV_ERR_WORKSPACE;
     if (!du && !dk && !dD) return LONGCONV_OK;
+    if (pads_itself(make_plan(N, io)))
+        return bwd_impl(dy, u, k, D, nullptr, du, dk, dD, B, H, N, io, workspace, w.base, stream, (uint32_t)N2);
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)workspace;
     const size_t rows = (size_t)B * H * N1, rb = (size_t)N2 * io_bytes(io);

@@ -528,9 +528,9 @@ void mfma_fill_plan(Plan& pl)
     pl.order.outer_bits = pl.log2R;
     const Options& opt = options();
     const bool staged = opt.staged != 0;           // the in-place staged kernel everywhere (cross-check)
-    if (!staged && pl.log2R == 0 && pl.log2L2 >= WAVE_MIN_LOG2 && pl.log2L2 <= WAVE_MAX_LOG2)
-        pl.order.wave_lg = pl.log2L2;
-    if (!staged && pl.log2L2 >= COOP_MIN_LOG2 && pl.log2L2 <= COOP_MAX_LOG2) pl.order.coop_lg = pl.log2L2;
+    if (!staged && pl.log2R == 0 && pl.log2L - 1 >= ROWS_MIN_LOG2 && pl.log2L - 1 <= ROWS_MAX_LOG2)
+        pl.order.wave_lg = pl.log2L - 1;
+    if (!staged && !pl.order.wave_lg && pl.log2L2 >= COOP_MIN_LOG2 && pl.log2L2 <= COOP_MAX_LOG2) pl.order.coop_lg = pl.log2L2;
     if (pl.log2R) pl.order.bits[pl.order.ndig++] = (unsigned char)pl.log2R;
     const int S = n_stages(pl.log2L2);
     for (int i = 0; i < S - 1; ++i) pl.order.bits[pl.order.ndig++] = 4;
@@ -540,17 +540,22 @@ void mfma_fill_plan(Plan& pl)
     const float c = 1.0f / (float)(1 << total_shift(pl.log2L2));
     pl.kscale = 1.0f / (L * c * c);
     pl.dkscale = 1.0f / (L * c * c * c);
+    if (pl.order.wave_lg) {
+        const float n = 0.5f * L, cr = rows_chain_scale(pl.order.wave_lg);
+        pl.kscale = 1.0f / (n * cr * cr);
+        pl.dkscale = 1.0f / (n * cr * cr * cr);
+    }
     // outer radix 4 or 8 around the 32768-point cooperative kernels: the convolutions take pass A in their
     // staging (switch fuse_pass_a = 0 keeps the separate pass, for comparison)
     pl.fuse_a = pl.order.coop_lg == COOP_MAX_LOG2 && pl.log2R >= 1 && pl.log2R <= 3 && opt.fuse_pass_a;
-    // one backward kernel where a wave group holds a head's accumulators (switch fuse_bwd = 0: separate kernels)
-    pl.fuse_bwd = pl.order.wave_lg && pl.log2R == 0 && opt.fuse_bwd;
+    // one backward kernel where a wave group holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
+    pl.fuse_bwd = pl.order.wave_lg && opt.fuse_bwd;
 }
 
 hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
-    if (pl.order.wave_lg) return wave_conv(in, kspec, out, conj, pr, pl, tb, st);
+    if (pl.order.wave_lg) return rows_conv(in, kspec, out, conj, pr, pl, tb, st);
     if (pl.order.coop_lg) return coop_conv(in, kspec, out, ws, conj, fuse_a, pr, pl, tb, st);
     if (pr.io == LONGCONV_F16) { LC_LG_SWITCH(conv_go, IoF16, in, kspec, out, ws, conj, pr, pl, tb, st) }
     if (pr.io == LONGCONV_BF16) { LC_LG_SWITCH(conv_go, IoBF16, in, kspec, out, ws, conj, pr, pl, tb, st) }
@@ -572,7 +577,7 @@ hipError_t mfma_dk(const void* dy, const void* u, float* dk, float* dD, int nspl
                    const __half2* ws_dy, __half2* ws_A, float* dD_part, void* zbuf, const Problem& pr, const Plan& pl,
                    const Tables& tb, hipStream_t st)
 {
-    if (pl.order.wave_lg) return wave_dk(dy, u, dk, dD, nsplit, pr, pl, tb, st);
+    if (pl.order.wave_lg) return rows_bwd(dy, u, nullptr, nullptr, dk, dD, nsplit, pr, pl, tb, st);
     if (pl.order.coop_lg) return coop_dk(dy, u, dk, dD, nsplit, ws_u, ws_dy, ws_A, dD_part, zbuf, pr, pl, tb, st);
     if (nsplit != 1) return hipErrorInvalidValue;
     if (pl.log2R == 0 && dD) {

@@ -1,0 +1,1428 @@
+// Matrix-core engine for single rows of N = 256 .. 4096 samples: spectrum, convolution (forward and du) and the
+// whole backward pass.
+//
+// A real row needs only N complex points, without zero padding and without a second row to pair it with.  The
+// causal convolution of two rows of N samples has 2N - 1 samples, so it equals its own remainder modulo
+// x^2N + 1 = (x^N - i)(x^N + i) over the reals, and that ring is the complex numbers' C[z]/(z^N - i): with
+// w = exp(i pi / 2N), w^N = i, the twisted row x[n] w^-n has an ordinary N-point transform
+//     X[f] = sum_n x[n] exp(-2 pi i n (4 f + 1) / 4N),
+// products of such transforms are convolutions modulo z^N - i, c[n] + i c[n+N], and the real part is the causal
+// convolution truncated to N samples.  The conjugate spectrum gives the correlation the same way.  (Right-angle
+// convolution: R. E. Blahut, Fast Algorithms for Digital Signal Processing, and Nussbaumer's negacyclic rings.)
+// Against two rows as real and imaginary part of a 2N-point transform this takes one factor of two less in every
+// transform (4096 samples are 16*16*16, two digits in registers and one exchange through LDS, instead of four
+// digits), half the spectrum bins, no lost half at an odd batch, and rows that are scaled one by one.
+//
+// N = 16*16*TC, n = (d_a 16 + d_b) TC + d_c, f = k_a + 16 k_b + 256 k_c.  An MFMA tile has two index positions,
+// X = lane % 16 and Y = (lane / 16, register); a contraction runs over Y, data as B operand keeps (X, Y), data as
+// A operand comes out transposed.
+//   phase 1 (tile d_c):   samples, X = d_b, Y = d_a  -[F16 over d_a, real input]-> X = k_a, Y = d_b  * w_256^(k_a d_b)
+//                         -[F16 over d_b]-> X = k_a, Y = k_b -> LDS
+//   phase 2 (tile = 16 columns (k_a, k_b) times the TC values of d_c): [F_TC over d_c] * spectrum [F_TC^-1]
+//   phase 3 (tile d_c):   X = k_a, Y = k_b -[F16^-1 over k_b]-> X = d_b, Y = k_a * conj(w_256^(k_a d_b))
+//                         -[F16^-1 over k_a, real part only]-> X = d_b, Y = d_a: samples
+// The twist w^-n and all factors that depend on d_c are folded into the matrices of the tile's two 16-point blocks,
+// so one twiddle table (four words per lane) serves every tile and both directions.  A wave owns tiles 2w, 2w+1 of
+// all three phases and keeps their constants in registers; TC/2 waves share a row.
+#include "engines.hpp"
+#include "mfma_util.hpp"
+
+namespace lc {
+namespace {
+using namespace mu;
+
+struct Yes { static constexpr bool value = true; };
+struct No { static constexpr bool value = false; };
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+#define MFMA16(a, b, acc) __builtin_amdgcn_mfma_f32_16x16x16f16((a), (b), (acc), 0, 0, 0)
+
+template <int LG>
+struct RC {
+    static constexpr int N = 1 << LG, cb = LG - 8, TC = 1 << cb;
+    static constexpr int NWR = TC >= 4 ? TC / 2 : 1;      // waves that share a row
+    static constexpr int RPI = TC == 1 ? 2 : 1;           // rows a group of waves takes at a time
+    static constexpr int NS = TC == 1 ? 1 : 2;            // tiles of a wave with constants and bins of their own
+    // words between the planes of two d_c in the exchange buffer: phase 2 reads four planes at once, and these
+    // strides put its 64 lanes on 64 banks
+    static constexpr int P = TC == 16 ? 260 : (TC == 8 ? 264 : 256);
+    static constexpr int XW = TC == 1 ? 0 : TC * P;       // words of one exchange buffer
+    static constexpr int COLS = 256 / TC;                 // columns of a phase-2 tile
+    static constexpr int SHIFT = 4 + (cb >= 3 ? 2 : (cb >= 1 ? 1 : 0));     // log2 of a chain's scale
+};
+
+// ---- constant tables: lane-ordered 16-byte units, per length 6 units per tile and 4 common ones ---------------------
+constexpr int ROWS_MIN = 8, ROWS_MAX = 12;
+__host__ __device__ constexpr int tab_units(int lg) { return 6 * (1 << (lg - 8)) + 4; }
+__host__ __device__ constexpr int tab_offset(int lg)
+{
+    int o = 0;
+    for (int l = ROWS_MIN; l < lg; ++l) o += tab_units(l);
+    return o;
+}
+constexpr int TAB_TOTAL = tab_offset(ROWS_MAX + 1);
+static __device__ uint4 g_rows_tab[TAB_TOTAL * 64];
+
+// d_b at index position i: natural, except at N = 256 (even ones first, see load_words256)
+__device__ __forceinline__ int db_of(int lg, int i) { return lg == 8 ? 2 * (i & 7) + (i >> 3) : i; }
+// phase 2's Y position -> (column group, d_c or k_c)
+__device__ __forceinline__ void yc_of(int cb, int i, int& s, int& d)
+{
+    const int y = i >> 2, r = i & 3;
+    if (cb == 4) { s = 0; d = i; }
+    else if (cb == 3) { s = y >> 1; d = 4 * (y & 1) + r; }
+    else if (cb == 2) { s = y; d = r; }
+    else { s = y + 4 * (r >> 1); d = r & 1; }
+}
+
+__global__ void fill_rows_tab_kernel(uint4* tab, int lg)
+{
+    const int cb = lg - 8, TC = 1 << cb;
+    const double N = (double)(1 << lg);
+    const int unit = blockIdx.x, lane = threadIdx.x, x = lane & 15, y = lane >> 4;
+    union { _Float16 h[8]; uint4 u; } o;
+    // exp(-2 pi i t), scaled
+    auto w = [](double t, double sc, double& re, double& im) {
+        double s, c;
+        sincospi(-2.0 * t, &s, &c);
+        re = c * sc; im = s * sc;
+    };
+    double re, im;
+    if (unit < 6 * TC) {
+        const int dc = unit / 6, what = unit % 6;
+        for (int q = 0; q < 4; ++q) {
+            const int yr = 4 * y + q;
+            // block over d_a, and the one over d_b with the inner twiddle; each scaled by 1/4
+            auto fa = [&](int ka, int da) { w(da * ka / 16.0 + da / 64.0 + dc * (4.0 * ka + 1.0) / (4.0 * N), 0.25, re, im); };
+            auto fb = [&](int kb, int db) { w(db * kb / 16.0 + db / 1024.0 + (double)dc * kb / (16.0 * TC), 0.25, re, im); };
+            switch (what) {
+                case 0: fa(x, yr); o.h[q] = (_Float16)re; o.h[4 + q] = (_Float16)im; break;
+                case 1: fb(x, db_of(lg, yr)); o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)(-im); break;
+                case 2: fb(x, db_of(lg, yr)); o.h[2 * q] = (_Float16)im; o.h[2 * q + 1] = (_Float16)re; break;
+                // conjugates, other index on the lanes
+                case 3: fb(yr, db_of(lg, x)); o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)im; break;
+                case 4: fb(yr, db_of(lg, x)); o.h[2 * q] = (_Float16)(-im); o.h[2 * q + 1] = (_Float16)re; break;
+                default: fa(yr, x); o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)im; break;
+            }
+        }
+    } else {
+        const int what = unit - 6 * TC;
+        for (int q = 0; q < 4; ++q) {
+            const int yr = 4 * y + q;
+            if (what == 0) {
+                w(x * db_of(lg, yr) / 256.0, 1.0, re, im);
+                o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)im;
+            } else if (what == 1) {
+                w(db_of(lg, x) * yr / 256.0, 1.0, re, im);
+                o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)im;
+            } else {
+                re = im = 0.0;
+                if (TC > 1) {
+                    int si, ki, sk, dk;
+                    yc_of(cb, x, si, ki);
+                    yc_of(cb, yr, sk, dk);
+                    if (si == sk) w((double)(ki * dk % TC) / TC, cb >= 3 ? 0.25 : 0.5, re, im);
+                }
+                o.h[2 * q] = (_Float16)(what == 2 ? re : im);
+                o.h[2 * q + 1] = (_Float16)(what == 2 ? -im : re);
+            }
+        }
+    }
+    tab[(size_t)unit * 64 + lane] = o.u;
+}
+
+template <int LG>
+struct RK {
+    h4 fa_re[RC<LG>::NS], fa_im[RC<LG>::NS];      // [F16 over d_a]: B operand of a 16x16x16 product
+    h8 b_re[RC<LG>::NS], b_im[RC<LG>::NS];        // [F16 over d_b]: A operand
+    h8 bi_re[RC<LG>::NS], bi_im[RC<LG>::NS];      // its adjoint: B operand
+    h8 ai[RC<LG>::NS];                            // adjoint of [F16 over d_a], real rows of the product only
+    H8U t1, t1i;                                  // w_256^(k_a d_b), k_a (t1) or d_b (t1i) on the lanes
+    h8 c_re, c_im;                                // I (x) F_TC
+};
+template <int LG>
+__device__ __forceinline__ void load_consts(RK<LG>& K, const uint4* __restrict__ tab, int t0, int lane)
+{
+    using C = RC<LG>;
+    const uint4* p = tab + (size_t)tab_offset(LG) * 64 + lane;
+    union { uint4 u; struct { h4 a, b; } h; } v;
+    H8U x;
+#pragma unroll
+    for (int k = 0; k < C::NS; ++k) {
+        const uint4* q = p + (size_t)(t0 + k) * 6 * 64;
+        v.u = q[0]; K.fa_re[k] = v.h.a; K.fa_im[k] = v.h.b;
+        x.u = q[64]; K.b_re[k] = x.v;
+        x.u = q[128]; K.b_im[k] = x.v;
+        x.u = q[192]; K.bi_re[k] = x.v;
+        x.u = q[256]; K.bi_im[k] = x.v;
+        x.u = q[320]; K.ai[k] = x.v;
+    }
+    p += (size_t)C::TC * 6 * 64;
+    K.t1.u = p[0];
+    K.t1i = K.t1;
+    if (C::TC == 1) K.t1i.u = p[64];
+    else { x.u = p[128]; K.c_re = x.v; x.u = p[192]; K.c_im = x.v; }
+}
+
+// ---- global memory: a row (two rows at N = 256) behind a buffer descriptor; lanes that must not touch memory carry
+// an offset beyond it (loads give zero, stores do nothing) ------------------------------------------------------------
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr uint32_t NOWHERE = 0x80000000u;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+__device__ __forceinline__ uint32_t buf_load(rsrc_t r, uint32_t off)
+{
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+}
+__device__ __forceinline__ void buf_store(rsrc_t r, uint32_t off, uint32_t v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, 0);
+}
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+// Sample n of the row -> element of memory.  pad = 0: itself.  pad = N2 (2-D layer): rows of N2 elements stand for
+// rows of 2 N2 samples whose second half is zero: nothing is kept for n with bit N2 set.
+__device__ __forceinline__ uint32_t elem_of(uint32_t n, uint32_t pad)
+{
+    if (pad == 0) return n;
+    return (n & pad) ? NOWHERE : (((n & ~(2 * pad - 1)) >> 1) | (n & (pad - 1)));
+}
+// byte offsets of the four words (register r = d_a % 4) of this lane's samples: tiles t0, t0+1 side by side; at
+// N = 256 the samples of d_b = 2j, 2j+1, j = lane % 8, of row (lane / 8) % 2
+template <int LG>
+__device__ __forceinline__ void word_offsets(uint32_t (&off)[4], int t0, int lane, uint32_t pad, uint32_t row_step)
+{
+    using C = RC<LG>;
+    const int x = lane & 15, y = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int da = 4 * y + r;
+        const uint32_t n = C::TC == 1 ? da * 16 + 2 * (x & 7) : (da * 16 + x) * C::TC + t0;
+        const uint32_t e = elem_of(n, pad);
+        off[r] = e == NOWHERE ? NOWHERE : 2u * e + (C::TC == 1 && x >= 8 ? row_step : 0u);
+    }
+}
+
+// ---- bf16 rows: exponent of the power of two a row is divided by -----------------------------------------------------
+// Largest-magnitude pattern over the words of one wave: the stand-in BAND_LOW if the cheap test shows that they lie in
+// 2 .. 8, otherwise measured.  At N = 256 lanes 0-7 and 8-15 of every 16 hold different rows: m[0], m[1].
+template <int RPI>
+__device__ __forceinline__ void words_max(const uint32_t (&w)[4], uint32_t (&m)[RPI])
+{
+    uint32_t a = 0u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a = absmax_acc(a, w[r]);
+    if constexpr (RPI == 1) {
+        m[0] = a;
+        band_or_exact<1>(m);
+    } else {
+        const uint32_t v = max(a & 0x7fffu, (a >> 16) & 0x7fffu);
+        const bool big = __builtin_amdgcn_ballot_w64(v >= BAND_HIGH) != 0;
+        const uint64_t lg = __builtin_amdgcn_ballot_w64(v >= BAND_LOW);
+        if (__builtin_expect(big || !(lg & 0x00ff00ff00ff00ffull) || !(lg & 0xff00ff00ff00ff00ull), 0)) {
+            uint32_t q = v;
+            q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0xB1, 0xf, 0xf, true));
+            q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x4E, 0xf, 0xf, true));
+            q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x141, 0xf, 0xf, true));
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                uint32_t s = 0u;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s = max(s, (uint32_t)__builtin_amdgcn_readlane((int)q, 16 * j + 8 * i));
+                m[i] = s;
+            }
+        } else {
+            m[0] = m[1] = BAND_LOW;
+        }
+    }
+}
+
+// ---- phases -----------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ h4 h4_of(uint32_t a, uint32_t b)
+{
+    union { uint32_t w[2]; h4 v; } u;
+    u.w[0] = a; u.w[1] = b;
+    return u.v;
+}
+// y * w and y * conj(w) of packed words
+__device__ __forceinline__ uint32_t cmul_h2(uint32_t yw, h2 w)
+{
+    union { uint32_t u; h2 h; } y, o;
+    y.u = yw;
+    const h2 yx = {y.h[0], y.h[0]}, yy = {y.h[1], y.h[1]};
+    const h2 ws = {-w[1], w[0]};
+    o.h = __builtin_elementwise_fma(yy, ws, yx * w);
+    return o.u;
+}
+// (yr + i yi) * w with real and imaginary part exchanged in the result word; CONJ: * conj(w)
+template <bool CONJ>
+__device__ __forceinline__ uint32_t cmul_swap(float yr, float yi, h2 w)
+{
+    const f2 v = {yr, yi};
+    const h2 y = __builtin_convertvector(v, h2);
+    const h2 yx = {y[0], y[0]}, yy = {y[1], y[1]};
+    union { h2 h; uint32_t u; } cv;
+    if (CONJ) {
+        const h2 a = {-w[1], w[0]};                       // im, re of yr conj(w) ...
+        cv.h = __builtin_elementwise_fma(yx, a, yy * w);  // ... and of i yi conj(w) = yi (w1 + i w0)
+    } else {
+        const h2 a = {w[1], w[0]}, b = {w[0], -w[1]};
+        cv.h = __builtin_elementwise_fma(yx, a, yy * b);
+    }
+    return cv.u;
+}
+
+// Phase 1 of the wave's two tiles.  w: raw words of the row(s); e: exponents (bf16 rows only).  The result goes to the
+// exchange buffer at xw (this lane's place in plane t0), at N = 256 it stays in registers: z[row][k_b % 4] complex.
+template <int LG, class IO>
+__device__ __forceinline__ void phase1_ops(const uint32_t (&w)[4], int e0, int e1, int lane, h4 (&op)[2])
+{
+    using C = RC<LG>;
+    if constexpr (IsBf<IO>::v) {
+        float lo[4], hi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { lo[r] = __uint_as_float(w[r] << 16); hi[r] = __uint_as_float(w[r] & 0xffff0000u); }
+        if (__builtin_expect((e0 | e1) != 0, 0)) {
+            const int e = C::TC == 1 && (lane & 8) ? e1 : e0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { lo[r] = ldexpf(lo[r], -e); hi[r] = ldexpf(hi[r], -e); }
+        }
+        op[0] = h4_of(pack_h2(lo[0], lo[1]), pack_h2(lo[2], lo[3]));
+        op[1] = h4_of(pack_h2(hi[0], hi[1]), pack_h2(hi[2], hi[3]));
+    } else {
+        op[0] = h4_of(__builtin_amdgcn_perm(w[1], w[0], 0x05040100u), __builtin_amdgcn_perm(w[3], w[2], 0x05040100u));
+        op[1] = h4_of(__builtin_amdgcn_perm(w[1], w[0], 0x07060302u), __builtin_amdgcn_perm(w[3], w[2], 0x07060302u));
+    }
+}
+template <int LG>
+__device__ __forceinline__ void phase1(const h4 (&op)[2], const RK<LG>& K, uint32_t* xw, f4 (&zr)[2], f4 (&zi)[2])
+{
+    using C = RC<LG>;
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 r[2], s[2];
+    H8U m[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        r[k] = MFMA16(op[k], K.fa_re[k % C::NS], zero);
+        s[k] = MFMA16(op[k], K.fa_im[k % C::NS], zero);
+    }
+    if constexpr (C::TC == 1) {
+        // tile k holds d_b = 2j + k of row 0 in its first 32 lanes and of row 1 in the others: exchanged to tile = row
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const auto q = __builtin_amdgcn_permlane32_swap(pack_h2(r[0][j], s[0][j]), pack_h2(r[1][j], s[1][j]), false, false);
+            m[0].w[j] = cmul_h2(q[0], K.t1.c[j]);
+            m[1].w[j] = cmul_h2(q[1], K.t1.c[j]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) m[k].w[j] = cmul_pack(r[k][j], s[k][j], K.t1.c[j]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        zr[k] = MFMA(K.b_re[k % C::NS], m[k].v, zero);
+        zi[k] = MFMA(K.b_im[k % C::NS], m[k].v, zero);
+    }
+    if constexpr (C::TC > 1) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            *reinterpret_cast<uint4*>(xw + k * C::P) = make_uint4(pack_h2(zr[k][0], zi[k][0]), pack_h2(zr[k][1], zi[k][1]),
+                                                                  pack_h2(zr[k][2], zi[k][2]), pack_h2(zr[k][3], zi[k][3]));
+    }
+}
+
+// word offset of register r from the lane's place in a phase-2 tile
+template <int LG>
+__device__ __forceinline__ constexpr int p2_off(int r)
+{
+    return RC<LG>::cb == 1 ? (r & 1) * RC<LG>::P + (r >> 1) * 64 : r * RC<LG>::P;
+}
+// the lane's place in phase-2 tile t
+template <int LG>
+__device__ __forceinline__ int p2_base(int t, int lane)
+{
+    using C = RC<LG>;
+    const int x = lane & 15, y = lane >> 4;
+    int a = t * C::COLS + x;
+    if (C::cb == 4) a += 4 * y * C::P;
+    else if (C::cb == 3) a += 4 * (y & 1) * C::P + (y >> 1) * 16;
+    else a += y * 16;
+    return a;
+}
+// forward half: [F_TC over d_c] of the wave's two tiles
+template <int LG>
+__device__ __forceinline__ void phase2_fwd(const uint32_t* xp, const RK<LG>& K, f4 (&yr)[2], f4 (&yi)[2])
+{
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    H8U m[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[k].w[r] = xp[k * RC<LG>::COLS + p2_off<LG>(r)];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) { yr[k] = MFMA(K.c_re, m[k].v, zero); yi[k] = MFMA(K.c_im, m[k].v, zero); }
+}
+// inverse half, in place; m: words with real and imaginary part exchanged (the forward blocks then give the
+// adjoint's result, exchanged again)
+template <int LG>
+__device__ __forceinline__ void phase2_inv(uint32_t* xp, const RK<LG>& K, const H8U (&m)[2])
+{
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 zr[2], zi[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) { zr[k] = MFMA(K.c_re, m[k].v, zero); zi[k] = MFMA(K.c_im, m[k].v, zero); }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xp[k * RC<LG>::COLS + p2_off<LG>(r)] = pack_h2(zi[k][r], zr[k][r]);
+}
+
+// Phase 3 of the wave's two tiles: v[k] = samples, register r = d_a % 4, X = d_b (N = 256: tile k = samples
+// d_b = 2j + k, as loaded).  xw: as in phase 1; N = 256: words of the two rows in z.
+template <int LG>
+__device__ __forceinline__ void phase3(const uint32_t* xw, const H8U (&z)[2], const RK<LG>& K, f4 (&v)[2])
+{
+    using C = RC<LG>;
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 r[2], s[2];
+    H8U m[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if constexpr (C::TC > 1) m[k].u = *reinterpret_cast<const uint4*>(xw + k * C::P);
+        else m[k] = z[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        r[k] = MFMA(m[k].v, K.bi_re[k % C::NS], zero);
+        s[k] = MFMA(m[k].v, K.bi_im[k % C::NS], zero);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[k].w[j] = cmul_pack_conj(r[k][j], s[k][j], K.t1i.c[j]);
+    if constexpr (C::TC == 1) {
+        // tile = row -> tile k = the d_b = 2j + k of both rows (row 0 in lanes 0-7 of every 16)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int a = (int)m[0].w[j], b = (int)m[1].w[j];
+            m[0].w[j] = (uint32_t)__builtin_amdgcn_update_dpp(a, b, 0x128, 0xf, 0xC, false);      // row_ror:8
+            m[1].w[j] = (uint32_t)__builtin_amdgcn_update_dpp(b, a, 0x128, 0xf, 0x3, false);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) v[k] = MFMA(K.ai[k % C::NS], m[k].v, zero);
+}
+template <class IO>
+__device__ __forceinline__ uint32_t pack_io(float a, float b) { return IsBf<IO>::v ? pack_bf2(a, b) : pack_h2(a, b); }
+template <class IO>
+__device__ __forceinline__ float lo_of(uint32_t w)
+{
+    if (IsBf<IO>::v) return __uint_as_float(w << 16);
+    union { uint32_t u; h2 h; } c; c.u = w; return (float)c.h[0];
+}
+template <class IO>
+__device__ __forceinline__ float hi_of(uint32_t w)
+{
+    if (IsBf<IO>::v) return __uint_as_float(w & 0xffff0000u);
+    union { uint32_t u; h2 h; } c; c.u = w; return (float)c.h[1];
+}
+template <class IO>
+__device__ __forceinline__ float dot_words(uint32_t a, uint32_t b, float s)
+{
+    union { uint32_t u; h2 h; bf2 b; } x, y;
+    x.u = a; y.u = b;
+    return IsBf<IO>::v ? __builtin_amdgcn_fdot2_f32_bf16(x.b, y.b, s, false) : __builtin_amdgcn_fdot2(x.h, y.h, s, false);
+}
+// The wave's two words of a row come one barrier earlier to an LDS copy of the output row, which then leaves in
+// 16-byte pieces, a wave's pieces side by side (words of 4 bytes, a fraction of every 16 per wave, would make the
+// memory side write most lines several times).  Word index with the bits exchanged that would put lanes on one bank.
+template <int LG>
+__device__ __forceinline__ int stage_word(int w)
+{
+    return RC<LG>::TC == 16 ? w ^ ((w >> 4) & 4) : (RC<LG>::TC == 4 ? w ^ ((w >> 2) & 32) : w);
+}
+
+// which workgroup of a persistent grid: consecutive ones on one XCD (they share a head's spectrum in its L2)
+__device__ __forceinline__ int xcd_swizzle(int b, int n) { return (n & 7) ? b : (b & 7) * (n >> 3) + (b >> 3); }
+
+struct RowIt {        // row `b` of head `h`, walked head by head
+    int h, b;
+    __device__ __forceinline__ void next(int B) { if (++b == B) { b = 0; ++h; } }
+};
+
+// -------------------------------------------------------------------------------------
+// Convolution of all rows, rows shared by NWR waves (N >= 1024).  Persistent workgroups, each with a run of consecutive
+// rows (head by head).  Software pipeline over rows, one barrier per row: iteration t runs phase 1 of row t, phase 2 of
+// row t - 1, phase 3 of row t - 2 and stores row t - 3, on three exchange buffers in turn, so every iteration has three
+// independent chains to overlap; row t + 2 is being loaded meanwhile.
+// -------------------------------------------------------------------------------------
+template <int LG, class IO, bool CONJ, bool GATE>
+__global__ void __launch_bounds__(RC<LG>::NWR * 64)
+rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
+             const typename IO::T* __restrict__ gate, int B, int H, int items, uint32_t pad, const uint4* __restrict__ tab)
+{
+    using C = RC<LG>;
+    constexpr bool BF = IsBf<IO>::v;
+    constexpr int SW = C::N / 2;                                          // words of a staged row
+    __shared__ __align__(16) uint32_t xbuf[3 * C::XW];
+    __shared__ __align__(16) uint32_t stg[2 * SW];
+    __shared__ __align__(16) uint32_t mxs[2 * 8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t0 = 2 * wave;
+    const int x = lane & 15, y = lane >> 4;
+    const int g = xcd_swizzle(blockIdx.x, gridDim.x);
+    const int i0 = (int)((int64_t)items * g / gridDim.x), i1 = (int)((int64_t)items * (g + 1) / gridDim.x);
+    const int n = i1 - i0;
+    if (n <= 0) return;
+    const uint32_t row_elems = pad ? C::N / 2 : C::N, row_bytes = row_elems * 2u;
+    auto row_of = [&](const RowIt& it, const void* p) {
+        return make_rsrc(reinterpret_cast<const char*>(p) + ((size_t)it.b * H + it.h) * row_bytes, row_bytes);
+    };
+    RowIt il = {i0 / B, i0 % B};                    // next row to load
+    RowIt i_1 = il, i_k = il, i_f = il;             // row of phase 1 (spectrum), of the gate's load, of the store
+    uint32_t off[4];
+    word_offsets<LG>(off, t0, lane, pad, 0u);
+    uint32_t wa[4], wb[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) wa[r] = wb[r] = 0u;
+    {
+        const rsrc_t d = row_of(il, in);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wa[r] = buf_load(d, off[r]);
+        il.next(B);
+    }
+    if (n > 1) {
+        const rsrc_t d = row_of(il, in);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wb[r] = buf_load(d, off[r]);
+        il.next(B);
+    }
+    RK<LG> K;
+    load_consts<LG>(K, tab, t0, lane);
+    uint32_t* xw = xbuf + (size_t)t0 * C::P + x * 16 + 4 * y;     // phases 1 and 3
+    uint32_t* xp = xbuf + p2_base<LG>(t0, lane);                  // phase 2
+    int sw[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sw[r] = stage_word<LG>((((4 * y + r) * 16 + x) * C::TC + t0) / 2);
+    const uint32_t fe = elem_of(8u * threadIdx.x, pad), foff = fe == NOWHERE ? NOWHERE : 2u * fe;
+    H8U kk[2], kn[2];
+    kk[0].u = kk[1].u = kn[0].u = kn[1].u = make_uint4(0u, 0u, 0u, 0u);
+    int es1 = 0, es2 = 0, esn = 0;         // spectrum exponents of the rows in phases 2 and 3
+    int e1 = 0, e2 = 0;                    // row exponents (bf16) of the rows in phases 2 and 3
+    uint32_t ga[4] = {0u, 0u, 0u, 0u};
+    uint32_t m[1];
+    if constexpr (BF) {
+        words_max<1>(wa, m);
+        if (lane == 0) mxs[wave] = m[0];
+        __syncthreads();
+    }
+    int b1 = 0, b2 = 0, b3 = 0;            // exchange buffers of phases 1, 2, 3
+    auto body = [&](auto full_, int t) {
+        constexpr bool FULL = decltype(full_)::value;
+        const bool do1 = FULL || t < n, do2 = FULL || (t >= 1 && t - 1 < n), do3 = FULL || (t >= 2 && t - 2 < n);
+        int e0 = 0;
+        if (do1) {
+            if constexpr (BF) {
+                uint32_t mm = 0u;
+#pragma unroll
+                for (int w = 0; w < C::NWR; ++w) mm = max(mm, mxs[(t & 1) * 8 + w]);
+                e0 = row_exponent(__builtin_amdgcn_readfirstlane((int)mm));
+            }
+            if (FULL ? i_1.b == 0 : (t == 0 || i_1.b == 0)) {           // the next phase 2 is another head's
+                const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)i_1.h * 2 * C::N);
+                kn[0].u = ks[t0 * 64 + lane];
+                kn[1].u = ks[(t0 + 1) * 64 + lane];
+                esn = spec_exp_of(kspec, H, 2 * C::N)[i_1.h];
+            }
+            i_1.next(B);
+            h4 op[2];
+            f4 zr[2], zi[2];
+            phase1_ops<LG, IO>(wa, e0, 0, lane, op);
+            phase1<LG>(op, K, xw + b1, zr, zi);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wa[r] = wb[r];
+        if (FULL || t + 2 < n) {
+            const rsrc_t d = row_of(il, in);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) wb[r] = buf_load(d, off[r]);
+            il.next(B);
+        }
+        f4 v[2];
+        if (do3) {
+            H8U nz[2];
+            phase3<LG>(xw + b3, nz, K, v);
+        }
+        if (do2) {
+            f4 yr[2], yi[2];
+            phase2_fwd<LG>(xp + b2, K, yr, yi);
+            H8U mm[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mm[k].w[r] = cmul_swap<CONJ>(yr[k][r], yi[k][r], kk[k].c[r]);
+            phase2_inv<LG>(xp + b2, K, mm);
+        }
+        if (do3) {
+            uint32_t* st = stg + (t & 1) * SW;
+            uint32_t o[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (GATE) o[r] = pack_io<IO>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]));
+                else o[r] = pack_io<IO>(v[0][r], v[1][r]);
+            }
+            const int ex = es2 + e2;
+            if (__builtin_expect(ex != 0, 0)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st[sw[r]] = o[r];
+        }
+        if (GATE && do2) {
+            const rsrc_t d = row_of(i_k, gate);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ga[r] = buf_load(d, off[r]);
+            i_k.next(B);
+        }
+        if (FULL || t >= 3) {
+            const u4v q = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * SW + stage_word<LG>(4 * threadIdx.x));
+            __builtin_amdgcn_raw_buffer_store_b128(q, row_of(i_f, out), (int)foff, 0, 0);
+            i_f.next(B);
+        }
+        es2 = es1; e2 = e1;
+        es1 = esn; e1 = e0;
+        kk[0] = kn[0]; kk[1] = kn[1];
+        if constexpr (BF) {
+            if (FULL || t + 1 < n) {
+                words_max<1>(wa, m);
+                if (lane == 0) mxs[((t + 1) & 1) * 8 + wave] = m[0];
+            }
+        }
+        b3 = b2; b2 = b1;
+        b1 = b1 == 2 * C::XW ? 0 : b1 + C::XW;
+        __syncthreads();
+    };
+    int t = 0;
+    for (; t < 3; ++t) body(No{}, t);
+    for (; t + 2 < n; ++t) body(Yes{}, t);
+    for (; t < n + 3; ++t) body(No{}, t);
+}
+
+// The same for rows that one wave owns (N = 256: two rows at a time; N = 512): no barrier, no staging (a wave's words
+// already cover 32 or 64 contiguous bytes).
+template <int LG, class IO, bool CONJ, bool GATE>
+__global__ void __launch_bounds__(256)
+rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
+              const typename IO::T* __restrict__ gate, int B, int H, int bpi, int items, uint32_t pad,
+              const uint4* __restrict__ tab)
+{
+    using C = RC<LG>;
+    constexpr bool BF = IsBf<IO>::v;
+    constexpr int NSP = C::NS;
+    __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : 4 * C::XW];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = lane & 15, y = lane >> 4;
+    const int ng = gridDim.x * 4, g = xcd_swizzle(blockIdx.x, gridDim.x) * 4 + wave;
+    const int i0 = (int)((int64_t)items * g / ng), i1 = (int)((int64_t)items * (g + 1) / ng);
+    if (i1 <= i0) return;
+    const uint32_t row_bytes = pad ? C::N : 2 * C::N;
+    const uint32_t row_step = (uint32_t)H * row_bytes;            // from a row to the next of its head
+    auto row_of = [&](const RowIt& it, const void* p) {           // it.b counts passes of RPI rows
+        const int b = it.b * C::RPI;
+        const uint32_t bytes = row_bytes + (C::RPI == 2 && b + 1 < B ? row_step : 0u);
+        return make_rsrc(reinterpret_cast<const char*>(p) + ((size_t)b * H + it.h) * row_bytes, bytes);
+    };
+    RowIt il = {i0 / bpi, i0 % bpi}, ic = il;
+    uint32_t off[4];
+    word_offsets<LG>(off, 0, lane, pad, row_step);
+    uint32_t wn[4], gn[4] = {0u, 0u, 0u, 0u};
+    {
+        const rsrc_t d = row_of(il, in);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wn[r] = buf_load(d, off[r]);
+        if (GATE) {
+            const rsrc_t dg = row_of(il, gate);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) gn[r] = buf_load(dg, off[r]);
+        }
+        il.next(bpi);
+    }
+    RK<LG> K;
+    load_consts<LG>(K, tab, 0, lane);
+    uint32_t* xb = xbuf + (C::TC == 1 ? 0 : wave * C::XW);
+    uint32_t* xw = xb + x * 16 + 4 * y;
+    uint32_t* xp = xb + p2_base<LG>(0, lane);
+    H8U kk[NSP];
+    int es = 0;
+    for (int i = i0; i < i1; ++i) {
+        uint32_t w[4], ga[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { w[r] = wn[r]; ga[r] = gn[r]; }
+        if (i == i0 || ic.b == 0) {
+            const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)ic.h * 2 * C::N);
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) kk[k].u = ks[k * 64 + lane];
+            es = spec_exp_of(kspec, H, 2 * C::N)[ic.h];
+        }
+        int e[2] = {0, 0};
+        if constexpr (BF) {
+            uint32_t m[C::RPI];
+            words_max<C::RPI>(w, m);
+#pragma unroll
+            for (int k = 0; k < C::RPI; ++k) e[k] = row_exponent(m[k]);
+        }
+        h4 op[2];
+        phase1_ops<LG, IO>(w, e[0], e[1], lane, op);
+        if (i + 1 < i1) {
+            const rsrc_t d = row_of(il, in);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) wn[r] = buf_load(d, off[r]);
+            if (GATE) {
+                const rsrc_t dg = row_of(il, gate);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) gn[r] = buf_load(dg, off[r]);
+            }
+            il.next(bpi);
+        }
+        f4 zr[2], zi[2], v[2];
+        H8U m[2];
+        phase1<LG>(op, K, xw, zr, zi);
+        if constexpr (C::TC == 1) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    m[k].w[r] = CONJ ? cmul_pack_conj(zr[k][r], zi[k][r], kk[0].c[r]) : cmul_pack(zr[k][r], zi[k][r], kk[0].c[r]);
+        } else {
+            wave_lds_fence();
+            f4 yr[2], yi[2];
+            phase2_fwd<LG>(xp, K, yr, yi);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_swap<CONJ>(yr[k][r], yi[k][r], kk[k % NSP].c[r]);
+            phase2_inv<LG>(xp, K, m);
+            wave_lds_fence();
+        }
+        phase3<LG>(xw, m, K, v);
+        uint32_t o[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (GATE) o[r] = pack_io<IO>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]));
+            else o[r] = pack_io<IO>(v[0][r], v[1][r]);
+        }
+        if (__builtin_expect((es | e[0] | e[1]) != 0, 0)) {
+            const int ex = es + (C::TC == 1 && (lane & 8) ? e[1] : e[0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
+        }
+        const rsrc_t d = row_of(ic, out);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) buf_store(d, off[r], o[r]);
+        ic.next(bpi);
+    }
+}
+
+// -------------------------------------------------------------------------------------
+// Spectrum of the kernel (Algorithm 2 lines 1-2), one group of NWR waves per head: phase 1 and the forward half of
+// phase 2 of the row scaled by a power of two to magnitude one.  Stored: (kscale FFT + kscale D) 2^-e_h as fp16
+// complex in phase 2's lane order (word (tile 64 + lane) 4 + register), e_h in the trailer (spec_exponent).
+// -------------------------------------------------------------------------------------
+template <int LG>
+__global__ void __launch_bounds__(RC<LG>::NWR * 64)
+rkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* __restrict__ kspec, int H, float kscale,
+              uint32_t pad, const uint4* __restrict__ tab)
+{
+    using C = RC<LG>;
+    __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : C::XW];
+    __shared__ float wmax[3][8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t0 = 2 * wave;
+    const int x = lane & 15, y = lane >> 4;
+    const int h = blockIdx.x;
+    const uint32_t row_bytes = (pad ? C::N / 2 : C::N) * 4u;
+    const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(k) + (size_t)h * row_bytes, row_bytes);
+    uint32_t off[4];
+    word_offsets<LG>(off, t0, lane, pad, NOWHERE);      // N = 256: the other row's lanes read zeros
+    float v[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t o = (off[r] & NOWHERE) ? NOWHERE : 2u * off[r];
+        v[r][0] = __uint_as_float(buf_load(d, o));
+        v[r][1] = __uint_as_float(buf_load(d, o == NOWHERE ? NOWHERE : o + 4u));
+    }
+    const float Dh = D[h];
+    RK<LG> K;
+    load_consts<LG>(K, tab, t0, lane);
+    float m = 0.f, a = 0.f, mp = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            m = fmaxf(m, fabsf(v[r][i]));
+            const float z = fabsf(v[r][i] + ((r == 0 && i == 0 && threadIdx.x == 0) ? Dh : 0.f));     // thread 0 holds k_0
+            a += z;
+            mp = fmaxf(mp, z);
+        }
+    for (int o = 32; o > 0; o >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, o, 64));
+        mp = fmaxf(mp, __shfl_xor(mp, o, 64));
+        a += __shfl_xor(a, o, 64);
+    }
+    if (C::NWR > 1) {
+        if (lane == 0) { wmax[0][wave] = m; wmax[1][wave] = a; wmax[2][wave] = mp; }
+        __syncthreads();
+        m = wmax[0][0]; a = wmax[1][0]; mp = wmax[2][0];
+#pragma unroll
+        for (int w = 1; w < C::NWR; ++w) { m = fmaxf(m, wmax[0][w]); a += wmax[1][w]; mp = fmaxf(mp, wmax[2][w]); }
+    }
+    const float s = head_scale_of(m);
+    const int es = spec_exponent(kscale * a, kscale * mp);
+    if (threadIdx.x == 0) spec_exp_of(kspec, H, 2 * C::N)[h] = es;
+    uint32_t w[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = pack_h2(v[r][0] * s, v[r][1] * s);
+    h4 op[2];
+    phase1_ops<LG, IoF16>(w, 0, 0, lane, op);
+    f4 yr[2], yi[2];
+    phase1<LG>(op, K, xbuf + (C::TC == 1 ? 0 : t0 * C::P + x * 16 + 4 * y), yr, yi);
+    if constexpr (C::TC > 1) {
+        if (C::NWR > 1) __syncthreads(); else wave_lds_fence();
+        phase2_fwd<LG>(xbuf + p2_base<LG>(t0, lane), K, yr, yi);
+    }
+    const float alpha = ldexpf(kscale * (float)(1 << C::SHIFT) / s, -es), beta = ldexpf(Dh * kscale, -es);
+    uint4* o = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+#pragma unroll
+    for (int q = 0; q < C::NS; ++q)
+        o[(t0 + q) * 64 + lane] = make_uint4(pack_h2(yr[q][0] * alpha + beta, yi[q][0] * alpha),
+                                             pack_h2(yr[q][1] * alpha + beta, yi[q][1] * alpha),
+                                             pack_h2(yr[q][2] * alpha + beta, yi[q][2] * alpha),
+                                             pack_h2(yr[q][3] * alpha + beta, yi[q][3] * alpha));
+}
+
+// dk accumulators of rows with different scales (bf16): kept in units of 2^eref, eref = the largest exponent sum met so
+// far.  A row with a larger sum rescales them; a row with a smaller one has its term scaled by 2^(return value).
+template <int NA>
+__device__ __forceinline__ int acc_align(float2 (&acc)[NA][4], int& eref, int ep)
+{
+    if (__builtin_expect(ep == eref, 1)) return 0;
+    if (ep > eref) {
+        const int d = eref - ep;
+#pragma unroll
+        for (int k = 0; k < NA; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { acc[k][j].x = ldexpf(acc[k][j].x, d); acc[k][j].y = ldexpf(acc[k][j].y, d); }
+        eref = ep;
+        return 0;
+    }
+    return ep - eref;
+}
+// acc += conj(U) W 2^down
+__device__ __forceinline__ void acc_tile(float2 (&acc)[4], const f4& ur, const f4& ui, const f4& wr, const f4& wi, int down)
+{
+    if (__builtin_expect(down != 0, 0)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float a = ldexpf(wr[j], down), b = ldexpf(wi[j], down);
+            acc[j].x = __builtin_fmaf(ui[j], b, __builtin_fmaf(ur[j], a, acc[j].x));
+            acc[j].y = __builtin_fmaf(-ui[j], a, __builtin_fmaf(ur[j], b, acc[j].y));
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            acc[j].x = __builtin_fmaf(ui[j], wi[j], __builtin_fmaf(ur[j], wr[j], acc[j].x));
+            acc[j].y = __builtin_fmaf(-ui[j], wr[j], __builtin_fmaf(ur[j], wi[j], acc[j].y));
+        }
+    }
+}
+
+// U of the dk-only kernels as packed fp16 (dot products without du keep one operand packed; the fused kernel keeps both
+// in fp32)
+__device__ __forceinline__ void round_h2(f4& a, f4& b)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { a[j] = (float)(_Float16)a[j]; b[j] = (float)(_Float16)b[j]; }
+}
+
+// The waves' partial accumulators through LDS (red: NWV * NA * 4 * 64 float2) and added in group order by the first
+// group's waves; returns the exponent of the sum's unit.  The caller puts a barrier in front if red is in use.
+template <int NA, int NWR, int NGRP, bool BF>
+__device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2* red, int* erefs, int wave, int lane)
+{
+    if constexpr (NGRP == 1) return BF ? eref : 0;
+#pragma unroll
+    for (int k = 0; k < NA; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) red[((wave * NA + k) * 4 + j) * 64 + lane] = acc[k][j];
+    if (BF && lane == 0 && wave % NWR == 0) erefs[wave / NWR] = eref;
+    __syncthreads();
+    int etop = 0;
+    if constexpr (BF) {
+        etop = erefs[0];
+#pragma unroll
+        for (int gi = 1; gi < NGRP; ++gi) etop = max(etop, erefs[gi]);
+        etop = __builtin_amdgcn_readfirstlane(etop);
+    }
+    if (wave < NWR) {
+#pragma unroll
+        for (int k = 0; k < NA; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float2 s = acc[k][j];
+                if constexpr (BF) { s.x = ldexpf(s.x, eref - etop); s.y = ldexpf(s.y, eref - etop); }
+#pragma unroll
+                for (int gi = 1; gi < NGRP; ++gi) {
+                    float2 v = red[(((gi * NWR + wave) * NA + k) * 4 + j) * 64 + lane];
+                    if constexpr (BF) { v.x = ldexpf(v.x, erefs[gi] - etop); v.y = ldexpf(v.y, erefs[gi] - etop); }
+                    s.x += v.x; s.y += v.y;
+                }
+                acc[k][j] = s;
+            }
+    }
+    return etop;
+}
+
+// -------------------------------------------------------------------------------------
+// Whole backward pass of a head (or of a share of its rows) per workgroup, rows shared by NWR waves (N >= 1024): du, dk
+// and dD from one read of dy and u.  Per row: W = transform of dy, U = transform of u, du = inverse of W conj(K),
+// A += conj(U) W in fp32 registers; dk is one inverse transform of A at the end.  Software pipeline as in rconv_kernel:
+// phase 1 of both rows t, phase 2 of rows t - 1, phase 3 of du's row t - 2, row t - 3 stored, one barrier per row.
+// NGRP groups of waves take every NGRP-th row and add their A at the end in group order.
+// -------------------------------------------------------------------------------------
+template <int LG> struct BwdCfg {
+    static constexpr int NGRP = LG == 10 ? 2 : 1, NWV = NGRP * RC<LG>::NWR;
+    static constexpr int GW = 5 * RC<LG>::XW + RC<LG>::N;       // LDS words of a group
+    static constexpr size_t lds = ((size_t)NGRP * GW + 2 * 8 * 2 + 8 + 8) * 4;
+};
+template <int LG, class IO, bool DU>
+__global__ void __launch_bounds__(BwdCfg<LG>::NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
+rbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ kspec,
+            typename IO::T* __restrict__ du, float* __restrict__ dk, float* __restrict__ dD, int B, int H, int nsplit,
+            float dkscale, uint32_t pad, const uint4* __restrict__ tab)
+{
+    using C = RC<LG>;
+    using Q = BwdCfg<LG>;
+    constexpr bool BF = IsBf<IO>::v;
+    constexpr int SW = C::N / 2, NGRP = Q::NGRP, NWR = C::NWR;
+    extern __shared__ uint4 lds4[];
+    uint32_t* lds = reinterpret_cast<uint32_t*>(lds4);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wave / NWR, t0 = 2 * (wave % NWR), gt = threadIdx.x % (NWR * 64);
+    const int x = lane & 15, y = lane >> 4;
+    uint32_t* xd = lds + grp * Q::GW;                   // dy: three buffers
+    uint32_t* xu = xd + 3 * C::XW;                      // u: two
+    uint32_t* stg = xu + 2 * C::XW;                     // du on its way out: two rows
+    uint32_t* mxs = lds + NGRP * Q::GW;                 // [2][8][2] patterns of the waves' words
+    float* dred = reinterpret_cast<float*>(mxs + 32);   // [8]
+    int* erefs = reinterpret_cast<int*>(dred + 8);      // [8]
+    // workgroups of a head's shares are H apart: every head's first share first
+    const int h = blockIdx.x % (unsigned)H, split = blockIdx.x / (unsigned)H;
+    const int b0 = split * NGRP, bstep = nsplit * NGRP;               // group g takes rows b0 + g, b0 + g + bstep, ...
+    const int niter = (B - b0 + bstep - 1) / bstep;                   // of the first group (>= 1); barriers stay uniform
+    const int nmine = (B - b0 - grp + bstep - 1) / bstep;             // of this group
+    const int nmin = (B - b0 - (NGRP - 1) + bstep - 1) / bstep;       // of the last
+    const uint32_t row_bytes = (pad ? C::N / 2 : C::N) * 2u;
+    auto row_of = [&](int i, const void* p) {
+        return make_rsrc(reinterpret_cast<const char*>(p) + ((size_t)(b0 + grp + i * bstep) * H + h) * row_bytes, row_bytes);
+    };
+    uint32_t off[4];
+    word_offsets<LG>(off, t0, lane, pad, 0u);
+    uint32_t da[4], db[4], ua[4], ub[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) da[r] = db[r] = ua[r] = ub[r] = 0u;
+    auto load = [&](int i, uint32_t (&d)[4], uint32_t (&v)[4]) {
+        const rsrc_t rd = row_of(i, dy), ru = row_of(i, u);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[r] = buf_load(rd, off[r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = buf_load(ru, off[r]);
+    };
+    if (0 < nmine) load(0, da, ua);
+    if (1 < nmine) load(1, db, ub);
+    RK<LG> K;
+    load_consts<LG>(K, tab, t0, lane);
+    H8U kk[2];
+    kk[0].u = kk[1].u = make_uint4(0u, 0u, 0u, 0u);
+    int es = 0;
+    if (DU) {
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+        kk[0].u = ks[t0 * 64 + lane];
+        kk[1].u = ks[(t0 + 1) * 64 + lane];
+        es = spec_exp_of(kspec, H, 2 * C::N)[h];
+    }
+    const int xwo = t0 * C::P + x * 16 + 4 * y, xpo = p2_base<LG>(t0, lane);
+    int sw[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sw[r] = stage_word<LG>((((4 * y + r) * 16 + x) * C::TC + t0) / 2);
+    const uint32_t fe = elem_of(8u * gt, pad), foff = fe == NOWHERE ? NOWHERE : 2u * fe;
+    float2 acc[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[k][j] = make_float2(0.f, 0.f);
+    float dsum = 0.f;
+    int eref = EXP_NONE, ep1 = 0, ed1 = 0, ed2 = 0;
+    uint32_t m1[1], m2[1];
+    auto publish = [&](int par) {
+        words_max<1>(da, m1);
+        words_max<1>(ua, m2);
+        if (lane == 0) *reinterpret_cast<uint2*>(mxs + (par * 8 + wave) * 2) = make_uint2(m1[0], m2[0]);
+    };
+    if constexpr (BF) {
+        publish(0);
+        __syncthreads();
+    }
+    int c1 = 0, c2 = 0, c3 = 0;
+    auto body = [&](auto full_, int t) {
+        constexpr bool FULL = decltype(full_)::value;
+        const bool do1 = FULL || t < nmine, do2 = FULL || (t >= 1 && t - 1 < nmine);
+        const bool do3 = DU && (FULL || (t >= 2 && t - 2 < nmine));
+        int ed0 = 0, ep0 = 0;
+        if (do1) {
+            int eu0 = 0;
+            if constexpr (BF) {
+                uint32_t md = 0u, mu_ = 0u;
+#pragma unroll
+                for (int w = 0; w < NWR; ++w) {
+                    const uint2 q = *reinterpret_cast<const uint2*>(mxs + ((t & 1) * 8 + grp * NWR + w) * 2);
+                    md = max(md, q.x); mu_ = max(mu_, q.y);
+                }
+                md = __builtin_amdgcn_readfirstlane((int)md);
+                mu_ = __builtin_amdgcn_readfirstlane((int)mu_);
+                ed0 = row_exponent(md);
+                eu0 = row_exponent(mu_);
+                ep0 = md && mu_ ? ed0 + eu0 : EXP_NONE;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(da[r], ua[r], dsum);
+            h4 op[2];
+            f4 zr[2], zi[2];
+            phase1_ops<LG, IO>(da, ed0, 0, lane, op);
+            phase1<LG>(op, K, xd + xwo + c1, zr, zi);
+            phase1_ops<LG, IO>(ua, eu0, 0, lane, op);
+            phase1<LG>(op, K, xu + xwo + (t & 1) * C::XW, zr, zi);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { da[r] = db[r]; ua[r] = ub[r]; }
+        if (FULL || t + 2 < nmine) load(t + 2, db, ub);
+        f4 v[2];
+        if (do3) {
+            H8U nz[2];
+            phase3<LG>(xd + xwo + c3, nz, K, v);
+        }
+        if (do2) {
+            f4 wr[2], wi[2], yr[2], yi[2];
+            phase2_fwd<LG>(xd + xpo + c2, K, wr, wi);
+            phase2_fwd<LG>(xu + xpo + ((t - 1) & 1) * C::XW, K, yr, yi);
+            if (DU) {
+                H8U mm[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mm[k].w[r] = cmul_swap<true>(wr[k][r], wi[k][r], kk[k].c[r]);
+                phase2_inv<LG>(xd + xpo + c2, K, mm);
+            }
+            int down = 0;
+            if constexpr (BF) down = acc_align<2>(acc, eref, ep1);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                if (!DU) round_h2(yr[k], yi[k]);
+                acc_tile(acc[k], yr[k], yi[k], wr[k], wi[k], down);
+            }
+        }
+        if (do3) {
+            uint32_t* st = stg + (t & 1) * SW;
+            uint32_t o[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = pack_io<IO>(v[0][r], v[1][r]);
+            const int ex = es + ed2;
+            if (__builtin_expect(ex != 0, 0)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st[sw[r]] = o[r];
+        }
+        if (DU && (FULL || (t >= 3 && t - 3 < nmine))) {
+            const u4v q = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * SW + stage_word<LG>(4 * gt));
+            __builtin_amdgcn_raw_buffer_store_b128(q, row_of(t - 3, du), (int)foff, 0, 0);
+        }
+        ed2 = ed1; ed1 = ed0; ep1 = ep0;
+        if constexpr (BF) {
+            if (FULL || t + 1 < nmine) publish((t + 1) & 1);
+        }
+        c3 = c2; c2 = c1;
+        c1 = c1 == 2 * C::XW ? 0 : c1 + C::XW;
+        __syncthreads();
+    };
+    const int last = niter + (DU ? 3 : 1);
+    int t = 0;
+    for (; t < 3 && t < last; ++t) body(No{}, t);
+    for (; t + 2 < nmin; ++t) body(Yes{}, t);
+    for (; t < last; ++t) body(No{}, t);
+
+    for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
+    if (lane == 0) dred[wave] = dsum;
+    const int etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
+    const size_t ho = (size_t)split * H + h;
+    if (NGRP > 1 || !dk) __syncthreads();              // (red lies in the buffers that follow)
+    if (dk) {
+        float* fs = reinterpret_cast<float*>(lds + 3 * C::XW);        // the row of dk in the u buffers of the first group
+        if (grp == 0) {
+            H8U mm[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mm[k].w[r] = pack_h2(acc[k][r].y, acc[k][r].x);
+            phase2_inv<LG>(lds + xpo, K, mm);
+        }
+        __syncthreads();
+        if (grp == 0) {
+            H8U nz[2];
+            f4 v[2];
+            phase3<LG>(lds + xwo, nz, K, v);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<float2*>(fs + ((4 * y + r) * 16 + x) * C::TC + t0) =
+                    make_float2(ldexpf(v[0][r] * dkscale, etop), ldexpf(v[1][r] * dkscale, etop));
+        }
+        __syncthreads();
+        const uint32_t kb = (pad ? C::N / 2 : C::N) * 4u;
+        const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(dk) + ho * kb, kb);
+        for (int q = threadIdx.x; q < C::N / 4; q += Q::NWV * 64) {
+            const uint32_t e = elem_of(4u * q, pad);
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u4v*>(fs + 4 * q), d,
+                                                   (int)(e == NOWHERE ? NOWHERE : 4u * e), 0, 0);
+        }
+    }
+    if (threadIdx.x == 0 && dD) {
+        float s = 0.f;
+        for (int w = 0; w < Q::NWV; ++w) s += dred[w];
+        dD[ho] = s;
+    }
+}
+
+// The same for rows that one wave owns (N = 256: two rows at a time; N = 512): four independent waves per workgroup.
+template <int LG, class IO, bool DU>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+rbwd1_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ kspec,
+             typename IO::T* __restrict__ du, float* __restrict__ dk, float* __restrict__ dD, int B, int H, int nsplit,
+             float dkscale, uint32_t pad, const uint4* __restrict__ tab)
+{
+    using C = RC<LG>;
+    constexpr bool BF = IsBf<IO>::v;
+    constexpr int NS = C::NS, NWV = 4;
+    __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : NWV * 2 * C::XW];
+    __shared__ float2 red[NWV * NS * 4 * 64];
+    __shared__ float dred[NWV];
+    __shared__ int erefs[NWV];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = lane & 15, y = lane >> 4;
+    const int h = blockIdx.x % (unsigned)H, split = blockIdx.x / (unsigned)H;
+    const int npass = (B + C::RPI - 1) / C::RPI, pstep = nsplit * NWV;
+    const uint32_t row_bytes = pad ? C::N : 2 * C::N, row_step = (uint32_t)H * row_bytes;
+    auto row_of = [&](int p, const void* q) {
+        const int b = p * C::RPI;
+        const uint32_t bytes = row_bytes + (C::RPI == 2 && b + 1 < B ? row_step : 0u);
+        return make_rsrc(reinterpret_cast<const char*>(q) + ((size_t)b * H + h) * row_bytes, bytes);
+    };
+    uint32_t off[4];
+    word_offsets<LG>(off, 0, lane, pad, row_step);
+    uint32_t dn[4], un[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dn[r] = un[r] = 0u;
+    auto load = [&](int p) {
+        const rsrc_t rd = row_of(p, dy), ru = row_of(p, u);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dn[r] = buf_load(rd, off[r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) un[r] = buf_load(ru, off[r]);
+    };
+    const int p0 = split * NWV + wave;
+    if (p0 < npass) load(p0);
+    RK<LG> K;
+    load_consts<LG>(K, tab, 0, lane);
+    H8U kk[NS];
+    int es = 0;
+    if (DU) {
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+#pragma unroll
+        for (int k = 0; k < NS; ++k) kk[k].u = ks[k * 64 + lane];
+        es = spec_exp_of(kspec, H, 2 * C::N)[h];
+    }
+    uint32_t* xd = xbuf + (C::TC == 1 ? 0 : wave * 2 * C::XW);
+    uint32_t* xu = xd + C::XW;
+    const int xwo = C::TC == 1 ? 0 : x * 16 + 4 * y, xpo = C::TC == 1 ? 0 : p2_base<LG>(0, lane);
+    float2 acc[NS][4];
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[k][j] = make_float2(0.f, 0.f);
+    float dsum = 0.f;
+    int eref = EXP_NONE;
+    for (int p = p0; p < npass; p += pstep) {
+        uint32_t wd[4], wu[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { wd[r] = dn[r]; wu[r] = un[r]; }
+        if (p + pstep < npass) load(p + pstep);
+        int ed[2] = {0, 0}, eu[2] = {0, 0}, ep[2] = {0, 0};
+        if constexpr (BF) {
+            uint32_t md[C::RPI], mu_[C::RPI];
+            words_max<C::RPI>(wd, md);
+            words_max<C::RPI>(wu, mu_);
+#pragma unroll
+            for (int k = 0; k < C::RPI; ++k) {
+                ed[k] = row_exponent(md[k]);
+                eu[k] = row_exponent(mu_[k]);
+                ep[k] = md[k] && mu_[k] ? ed[k] + eu[k] : EXP_NONE;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(wd[r], wu[r], dsum);
+        h4 op[2];
+        f4 wr[2], wi[2], yr[2], yi[2], v[2];
+        H8U m[2];
+        phase1_ops<LG, IO>(wd, ed[0], ed[1], lane, op);
+        phase1<LG>(op, K, xd + xwo, wr, wi);
+        phase1_ops<LG, IO>(wu, eu[0], eu[1], lane, op);
+        phase1<LG>(op, K, xu + xwo, yr, yi);
+        if constexpr (C::TC > 1) {
+            wave_lds_fence();
+            phase2_fwd<LG>(xd + xpo, K, wr, wi);
+            phase2_fwd<LG>(xu + xpo, K, yr, yi);
+        }
+        if (DU) {
+            if constexpr (C::TC == 1) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_pack_conj(wr[k][r], wi[k][r], kk[0].c[r]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_swap<true>(wr[k][r], wi[k][r], kk[k % NS].c[r]);
+                phase2_inv<LG>(xd + xpo, K, m);
+                wave_lds_fence();
+            }
+            phase3<LG>(xd + xwo, m, K, v);
+            uint32_t o[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = pack_io<IO>(v[0][r], v[1][r]);
+            if (__builtin_expect((es | ed[0] | ed[1]) != 0, 0)) {
+                const int ex = es + (C::TC == 1 && (lane & 8) ? ed[1] : ed[0]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
+            }
+            const rsrc_t d = row_of(p, du);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) buf_store(d, off[r], o[r]);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            int down = 0;
+            // N = 256: tile k is row k and both add to the same bins; otherwise one exponent for the row's two tiles
+            if constexpr (BF) down = C::TC == 1 || k == 0 ? acc_align<NS>(acc, eref, ep[C::TC == 1 ? k : 0]) : (ep[0] < eref ? ep[0] - eref : 0);
+            if (!DU) round_h2(yr[k], yi[k]);
+            acc_tile(acc[k % NS], yr[k], yi[k], wr[k], wi[k], down);
+        }
+    }
+
+    for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
+    if (lane == 0) dred[wave] = dsum;
+    const int etop = acc_reduce<NS, 1, NWV, BF>(acc, eref, red, erefs, wave, lane);
+    const size_t ho = (size_t)split * H + h;
+    if (wave != 0) return;
+    if (lane == 0 && dD) dD[ho] = ((dred[0] + dred[1]) + dred[2]) + dred[3];
+    if (!dk) return;
+    H8U m[2];
+    f4 v[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (C::TC == 1) m[k].w[r] = k == 0 ? pack_h2(acc[0][r].x, acc[0][r].y) : 0u;
+            else m[k].w[r] = pack_h2(acc[k % NS][r].y, acc[k % NS][r].x);
+        }
+    if constexpr (C::TC > 1) {
+        phase2_inv<LG>(xd + xpo, K, m);
+        wave_lds_fence();
+    }
+    phase3<LG>(xd + xwo, m, K, v);
+    const uint32_t kb = (pad ? C::N / 2 : C::N) * 4u;
+    const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(dk) + ho * kb, kb);
+    word_offsets<LG>(off, 0, lane, pad, NOWHERE);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+        const u2v q = {__float_as_uint(ldexpf(v[0][r] * dkscale, etop)), __float_as_uint(ldexpf(v[1][r] * dkscale, etop))};
+        __builtin_amdgcn_raw_buffer_store_b64(q, d, (int)((off[r] & NOWHERE) ? NOWHERE : 2u * off[r]), 0, 0);
+    }
+}
+
+// ---- launches ----------------------------------------------------------------------------------------------------------
+// Workgroups of kernel `f` the device holds at once.
+template <class F>
+hipError_t resident(F f, int threads, size_t lds, int& cache)
+{
+    if (cache) return hipSuccess;
+    int nb = 0;
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, threads, lds);
+    if (e != hipSuccess) return e;
+    cache = (nb < 1 ? 1 : nb) * compute_units();
+    return hipSuccess;
+}
+
+template <int LG, class IO, bool CONJ, bool GATE>
+hipError_t rconv_run(const void* in, const float2* kspec, void* out, const Problem& pr, const uint4* tab, hipStream_t st)
+{
+    using T = typename IO::T;
+    using C = RC<LG>;
+    static int cap = 0;
+    hipError_t e;
+    if constexpr (C::NWR > 1) {
+        const int items = (int)(pr.B * pr.H);
+        e = resident(rconv_kernel<LG, IO, CONJ, GATE>, C::NWR * 64, 0, cap);
+        if (e != hipSuccess) return e;
+        const int nb = items < cap ? items : cap;
+        hipLaunchKernelGGL((rconv_kernel<LG, IO, CONJ, GATE>), dim3(nb), dim3(C::NWR * 64), 0, st, (const T*)in, kspec, (T*)out,
+                           (const T*)pr.gate, (int)pr.B, (int)pr.H, items, pr.pad, tab);
+    } else {
+        const int bpi = (int)((pr.B + C::RPI - 1) / C::RPI), items = bpi * (int)pr.H;
+        e = resident(rconv1_kernel<LG, IO, CONJ, GATE>, 256, 0, cap);
+        if (e != hipSuccess) return e;
+        const int want = (items + 3) / 4, nb = want < cap ? want : cap;
+        hipLaunchKernelGGL((rconv1_kernel<LG, IO, CONJ, GATE>), dim3(nb), dim3(256), 0, st, (const T*)in, kspec, (T*)out,
+                           (const T*)pr.gate, (int)pr.B, (int)pr.H, bpi, items, pr.pad, tab);
+    }
+    return hipGetLastError();
+}
+template <int LG, class IO>
+hipError_t rconv_go(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr, const uint4* tab, hipStream_t st)
+{
+    if (pr.gate) return conj ? hipErrorInvalidValue : rconv_run<LG, IO, false, true>(in, kspec, out, pr, tab, st);
+    return conj ? rconv_run<LG, IO, true, false>(in, kspec, out, pr, tab, st)
+                : rconv_run<LG, IO, false, false>(in, kspec, out, pr, tab, st);
+}
+template <int LG>
+hipError_t rkspec_go(const float* k, const float* D, float2* kspec, int64_t H, float kscale, uint32_t pad, const uint4* tab, hipStream_t st)
+{
+    hipLaunchKernelGGL((rkspec_kernel<LG>), dim3((unsigned)H), dim3(RC<LG>::NWR * 64), 0, st, k, D, kspec, (int)H, kscale, pad, tab);
+    return hipGetLastError();
+}
+template <int LG, class IO, bool DU>
+hipError_t rbwd_run(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+                    const Problem& pr, const Plan& pl, const uint4* tab, hipStream_t st)
+{
+    using T = typename IO::T;
+    if constexpr (RC<LG>::NWR > 1) {
+        using Q = BwdCfg<LG>;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rbwd_kernel<LG, IO, DU>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q::lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((rbwd_kernel<LG, IO, DU>), dim3((unsigned)(pr.H * nsplit)), dim3(Q::NWV * 64), Q::lds, st, (const T*)dy,
+                           (const T*)u, kspec, (T*)du, dk, dD, (int)pr.B, (int)pr.H, nsplit, pl.dkscale, pr.pad, tab);
+    } else {
+        hipLaunchKernelGGL((rbwd1_kernel<LG, IO, DU>), dim3((unsigned)(pr.H * nsplit)), dim3(256), 0, st, (const T*)dy,
+                           (const T*)u, kspec, (T*)du, dk, dD, (int)pr.B, (int)pr.H, nsplit, pl.dkscale, pr.pad, tab);
+    }
+    return hipGetLastError();
+}
+template <int LG, class IO>
+hipError_t rbwd_go(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+                   const Problem& pr, const Plan& pl, const uint4* tab, hipStream_t st)
+{
+    return du ? rbwd_run<LG, IO, true>(dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st)
+              : rbwd_run<LG, IO, false>(dy, u, nullptr, nullptr, dk, dD, nsplit, pr, pl, tab, st);
+}
+
+#define ROWS_SWITCH(lg, FN, ...)                                  \
+    switch (lg) {                                                 \
+        case 8: return FN(8) __VA_ARGS__;                         \
+        case 9: return FN(9) __VA_ARGS__;                         \
+        case 10: return FN(10) __VA_ARGS__;                       \
+        case 11: return FN(11) __VA_ARGS__;                       \
+        case 12: return FN(12) __VA_ARGS__;                       \
+        default: return hipErrorInvalidValue;                     \
+    }
+
+}  // namespace
+
+hipError_t rows_fill_tables(const void** tab_out, hipStream_t st)
+{
+    uint4* p = nullptr;
+    hipError_t e = hipGetSymbolAddress((void**)&p, HIP_SYMBOL(g_rows_tab));
+    if (e != hipSuccess) return e;
+    for (int lg = ROWS_MIN; lg <= ROWS_MAX; ++lg)
+        hipLaunchKernelGGL(fill_rows_tab_kernel, dim3(tab_units(lg)), dim3(64), 0, st, p + (size_t)tab_offset(lg) * 64, lg);
+    *tab_out = p;
+    return hipGetLastError();
+}
+
+// Shares of a head's rows in the backward kernel: about as many workgroups as the device holds at once when heads are
+// few, and at least two rows (passes of two rows at N = 256) for every group of waves.
+int rows_bwd_nsplit(int64_t B, int64_t H, int lg)
+{
+    const int ngrp = lg == 12 || lg == 11 ? 1 : (lg == 10 ? 2 : 4);
+    const int64_t units = lg == 8 ? (B + 1) / 2 : B;
+    const int64_t most = (units + 2 * ngrp - 1) / (2 * ngrp);
+    int64_t s = (lg == 12 ? 256 : 512) / H;
+    if (s > most) s = most;
+    if (s > 64) s = 64;
+    return s < 1 ? 1 : (int)s;
+}
+float rows_chain_scale(int lg)
+{
+    switch (lg) {
+        case 8: return 1.0f / (1 << RC<8>::SHIFT);
+        case 9: return 1.0f / (1 << RC<9>::SHIFT);
+        case 10: return 1.0f / (1 << RC<10>::SHIFT);
+        case 11: return 1.0f / (1 << RC<11>::SHIFT);
+        default: return 1.0f / (1 << RC<12>::SHIFT);
+    }
+}
+
+hipError_t rows_kspec(const float* k, const float* D, float2* kspec, int64_t H, const Plan& pl, uint32_t pad, const Tables& tb,
+                      hipStream_t st)
+{
+    const uint4* tab = (const uint4*)tb.rtab;
+#define RF(L) rkspec_go<L>
+    ROWS_SWITCH(pl.order.wave_lg, RF, (k, D, kspec, H, pl.kscale, pad, tab, st))
+#undef RF
+}
+template <class IO>
+static hipError_t conv_io(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr, int lg, const uint4* tab,
+                          hipStream_t st)
+{
+#define RF(L) rconv_go<L, IO>
+    ROWS_SWITCH(lg, RF, (in, kspec, out, conj, pr, tab, st))
+#undef RF
+}
+hipError_t rows_conv(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr, const Plan& pl,
+                     const Tables& tb, hipStream_t st)
+{
+    const uint4* tab = (const uint4*)tb.rtab;
+    if (pr.io == LONGCONV_F16) return conv_io<IoF16>(in, kspec, out, conj, pr, pl.order.wave_lg, tab, st);
+    if (pr.io == LONGCONV_BF16) return conv_io<IoBF16>(in, kspec, out, conj, pr, pl.order.wave_lg, tab, st);
+    return hipErrorInvalidValue;
+}
+template <class IO>
+static hipError_t bwd_io(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+                         const Problem& pr, const Plan& pl, const uint4* tab, hipStream_t st)
+{
+#define RF(L) rbwd_go<L, IO>
+    ROWS_SWITCH(pl.order.wave_lg, RF, (dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st))
+#undef RF
+}
+hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+                    const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
+{
+    const uint4* tab = (const uint4*)tb.rtab;
+    if (pr.io == LONGCONV_F16) return bwd_io<IoF16>(dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st);
+    if (pr.io == LONGCONV_BF16) return bwd_io<IoBF16>(dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace lc

@@ -33,6 +33,9 @@ struct Problem {
     // convolutions of the multi-pass plans with an fp16 spectrum: the per-head exponents of the stored spectrum
     // (spec_exponent), which pass C gives back; NULL = none
     const int* spec_exp = nullptr;
+    // single-row kernels: N2 of the 2-D layer, whose image rows of N2 elements stand for 2 N2 samples, the second half
+    // zero (not stored, and dropped on output); 0 = rows as they are
+    uint32_t pad = 0;
 };
 // mx[h] = bf16 pattern of max |in[b,h,:]| over b (zeroed first); rows of 16-bit floats only
 hipError_t rows_absmax(const void* in, uint32_t* mx, const Problem& pr, hipStream_t st);
@@ -132,23 +135,21 @@ hipError_t mfma_dk(const void* dy, const void* u, float* dk, float* dD, int nspl
 hipError_t sum_partials(const float* dk_part, float* dk, size_t n_dk, const float* dD_part, float* dD, size_t n_dD,
                         int nsplit, hipStream_t st);
 
-// ---- wave-autonomous matrix-core kernels for 512 <= L <= 4096 (engine_wave.hip) ----------
-constexpr int WAVE_MIN_LOG2 = 9, WAVE_MAX_LOG2 = 12;
-hipError_t wave_fill_tables(const void** tab_out, hipStream_t st);
-hipError_t wave_conv(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr,
-                     const Plan& pl, const Tables& tb, hipStream_t st);
-// nsplit > 1 (single-pass dk kernels): the pairs of a head are dealt to nsplit workgroups, dk and dD then point to
-// partial buffers [nsplit][H][N] and [nsplit][H] that sum_partials() adds up in share order.
-hipError_t wave_dk(const void* dy, const void* u, float* dk, float* dD, int nsplit, const Problem& pr, const Plan& pl,
-                   const Tables& tb, hipStream_t st);
-// du, dk and dD in one kernel, from one read of dy and u (single-pass plans up to 4096 points; dk and dD may be
-// null, du not).
-inline bool wave_bwd_ok(const Plan& pl) { return pl.fuse_bwd != 0; }
-hipError_t wave_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+// ---- single rows of N = 256 .. 4096 samples on the matrix cores (engine_rows.hip) -----------
+constexpr int ROWS_MIN_LOG2 = 8, ROWS_MAX_LOG2 = 12;
+hipError_t rows_fill_tables(const void** tab_out, hipStream_t st);
+float rows_chain_scale(int lg);      // scale of one transform of N = 2^lg samples
+// Spectrum (finds each head's pre-scale itself).  pad: see Problem::pad.
+hipError_t rows_kspec(const float* k, const float* D, float2* kspec, int64_t H, const Plan& pl, uint32_t pad, const Tables& tb,
+                      hipStream_t st);
+hipError_t rows_conv(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr, const Plan& pl,
+                     const Tables& tb, hipStream_t st);
+// du, dk and dD in one kernel, from one read of dy and u; du (and with it kspec), dk and dD may be null.  nsplit > 1: the
+// rows of a head are dealt to nsplit workgroups, dk and dD then point to partial buffers [nsplit][H][N] and [nsplit][H]
+// that sum_partials() adds up in share order.
+int rows_bwd_nsplit(int64_t B, int64_t H, int lg);
+hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
-// Spectrum on the matrix cores (finds each head's pre-scale itself).
-hipError_t wave_kspec(const float* k, const float* D, float2* kspec, int64_t H, int64_t N,
-                      const Plan& pl, const Tables& tb, hipStream_t st);
 
 // ---- cooperative chained matrix-core kernels for 2^13 <= L2 <= 2^15 (engine_coop.hip) --------
 constexpr int COOP_MIN_LOG2 = 13, COOP_MAX_LOG2 = 15;
