@@ -414,6 +414,10 @@ int longconv_fwd_gated(const void* u, const float* k, const float* D, const void
     return s;
 }
 
+static int bwd_impl(const void* dy, const void* u, const float* k, const float* D, const void* kspec, void* du,
+                    float* dk, float* dD, int64_t B, int64_t H, int64_t N, int io, void* workspace,
+                    size_t workspace_bytes, void* stream, uint32_t pad, const void* gate = nullptr, void* dg = nullptr);
+
 int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float* k, const float* D,
                        const void* kspec, void* du, float* dk, float* dD, void* dg, int64_t B, int64_t H,
                        int64_t N, int io, void* workspace, size_t workspace_bytes, void* stream)
@@ -426,6 +430,9 @@ int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float
     if (!workspace || workspace_bytes < base + gated_dz_bytes(B, H, N, io)) return LONGCONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const size_t n = (size_t)B * H * N;
+    const Plan pl = make_plan(N, io);
+    if (pl.engine == ENGINE_MFMA && pl.fuse_bwd && du && dg && (dk || dD))      // all of it from one kernel
+        return bwd_impl(dy, u, k, D, kspec, du, dk, dD, B, H, N, io, workspace, base, stream, 0, g, dg);
     if (du || dk || dD) {
         // dz = dy * g is what the convolution's backward pass receives
         void* dz = (char*)workspace + base;
@@ -451,7 +458,7 @@ int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float
 
 static int bwd_impl(const void* dy, const void* u, const float* k, const float* D, const void* kspec, void* du,
                     float* dk, float* dD, int64_t B, int64_t H, int64_t N, int io, void* workspace,
-                    size_t workspace_bytes, void* stream, uint32_t pad)
+                    size_t workspace_bytes, void* stream, uint32_t pad, const void* gate, void* dg)
 {
     int s = check_shape(B, H, N, io);
     if (s != LONGCONV_OK) return s;
@@ -470,6 +477,7 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
     char* base = (char*)workspace;
     Problem pr{B, H, N, io, (int)((B + 1) / 2)};
     pr.pad = pad;
+    pr.gate = gate;
     const bool f16ws = pl.engine == ENGINE_MFMA;
     bool dy_ready = false;   // multi-pass: pass A of dy already in ws1
     uint32_t* mx_u = nullptr;      // bf16 rows of these multi-pass plans: per-head maxima of u and dy
@@ -495,7 +503,7 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
         const int ns = w.nsplit;
         float* dkp = (float*)(base + w.dkpart);
         float* ddp = (float*)(base + w.ddpart);
-        hipError_t e = rows_bwd(dy, u, ks, du, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD ? ddp : nullptr) : dD, ns,
+        hipError_t e = rows_bwd(dy, u, ks, du, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD ? ddp : nullptr) : dD, dg, ns,
                                 pr, pl, tb, st);
         if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * (pad ? N / 2 : N), ddp, dD, (size_t)H, ns, st);
         if (note(e, "bwd") != hipSuccess) return LONGCONV_ERR_HIP;

@@ -577,7 +577,7 @@ hipError_t mfma_dk(const void* dy, const void* u, float* dk, float* dD, int nspl
                    const __half2* ws_dy, __half2* ws_A, float* dD_part, void* zbuf, const Problem& pr, const Plan& pl,
                    const Tables& tb, hipStream_t st)
 {
-    if (pl.order.wave_lg) return rows_bwd(dy, u, nullptr, nullptr, dk, dD, nsplit, pr, pl, tb, st);
+    if (pl.order.wave_lg) return rows_bwd(dy, u, nullptr, nullptr, dk, dD, nullptr, nsplit, pr, pl, tb, st);
     if (pl.order.coop_lg) return coop_dk(dy, u, dk, dD, nsplit, ws_u, ws_dy, ws_A, dD_part, zbuf, pr, pl, tb, st);
     if (nsplit != 1) return hipErrorInvalidValue;
     if (pl.log2R == 0 && dD) {

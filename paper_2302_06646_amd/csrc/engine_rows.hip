@@ -31,9 +31,10 @@ namespace lc {
 namespace {
 using namespace mu;
 
-struct Yes { static constexpr bool value = true; };
-struct No { static constexpr bool value = false; };
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+// keeps the phases of an iteration apart in the instruction stream: mixed by the scheduler they need more than the 128
+// registers that four waves per SIMD leave
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 #define MFMA16(a, b, acc) __builtin_amdgcn_mfma_f32_16x16x16f16((a), (b), (acc), 0, 0, 0)
 
 template <int LG>
@@ -46,6 +47,7 @@ struct RC {
     // strides put its 64 lanes on 64 banks
     static constexpr int P = TC == 16 ? 260 : (TC == 8 ? 264 : 256);
     static constexpr int XW = TC == 1 ? 0 : TC * P;       // words of one exchange buffer
+    static constexpr int SW = N / 2 + (TC == 4 ? 128 : 0);   // words of a staged row (see stage_word)
     static constexpr int COLS = 256 / TC;                 // columns of a phase-2 tile
     static constexpr int SHIFT = 4 + (cb >= 3 ? 2 : (cb >= 1 ? 1 : 0));     // log2 of a chain's scale
 };
@@ -163,6 +165,23 @@ __device__ __forceinline__ void load_consts(RK<LG>& K, const uint4* __restrict__
     else { x.u = p[128]; K.c_re = x.v; x.u = p[192]; K.c_im = x.v; }
 }
 
+// Constants that a loop is about to use have to have arrived: a wait in front of the loop (an empty statement that reads
+// them).  Otherwise the loop's own waits have to allow for them in every iteration, and with them for whatever was asked
+// for since.
+__device__ __forceinline__ void arrived(h8& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void arrived(h4& v) { asm volatile("" : "+v"(v)); }
+template <int LG>
+__device__ __forceinline__ void arrived(RK<LG>& K)
+{
+#pragma unroll
+    for (int k = 0; k < RC<LG>::NS; ++k) {
+        arrived(K.fa_re[k]); arrived(K.fa_im[k]); arrived(K.ai[k]);
+        arrived(K.b_re[k]); arrived(K.b_im[k]); arrived(K.bi_re[k]); arrived(K.bi_im[k]);
+    }
+    arrived(K.t1.v); arrived(K.t1i.v);
+    if (RC<LG>::TC > 1) { arrived(K.c_re); arrived(K.c_im); }
+}
+
 // ---- global memory: a row (two rows at N = 256) behind a buffer descriptor; lanes that must not touch memory carry
 // an offset beyond it (loads give zero, stores do nothing) ------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -179,7 +198,6 @@ __device__ __forceinline__ void buf_store(rsrc_t r, uint32_t off, uint32_t v)
 {
     __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, 0);
 }
-typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
 // Sample n of the row -> element of memory.  pad = 0: itself.  pad = N2 (2-D layer): rows of N2 elements stand for
 // rows of 2 N2 samples whose second half is zero: nothing is kept for n with bit N2 set.
@@ -275,7 +293,7 @@ __device__ __forceinline__ uint32_t cmul_swap(float yr, float yi, h2 w)
 
 // Phase 1 of the wave's two tiles.  w: raw words of the row(s); e: exponents (bf16 rows only).  The result goes to the
 // exchange buffer at xw (this lane's place in plane t0), at N = 256 it stays in registers: z[row][k_b % 4] complex.
-template <int LG, class IO>
+template <int LG, class IO, bool SCALED>
 __device__ __forceinline__ void phase1_ops(const uint32_t (&w)[4], int e0, int e1, int lane, h4 (&op)[2])
 {
     using C = RC<LG>;
@@ -283,7 +301,7 @@ __device__ __forceinline__ void phase1_ops(const uint32_t (&w)[4], int e0, int e
         float lo[4], hi[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) { lo[r] = __uint_as_float(w[r] << 16); hi[r] = __uint_as_float(w[r] & 0xffff0000u); }
-        if (__builtin_expect((e0 | e1) != 0, 0)) {
+        if constexpr (SCALED) {
             const int e = C::TC == 1 && (lane & 8) ? e1 : e0;
 #pragma unroll
             for (int r = 0; r < 4; ++r) { lo[r] = ldexpf(lo[r], -e); hi[r] = ldexpf(hi[r], -e); }
@@ -352,16 +370,23 @@ __device__ __forceinline__ int p2_base(int t, int lane)
     else a += y * 16;
     return a;
 }
-// forward half: [F_TC over d_c] of the wave's two tiles
+// forward half: [F_TC over d_c] of the wave's two tiles.  The second tile's place is hidden from the compiler: it would
+// pair the tiles' words in one instruction and then need a register move per word to line up the MFMA operands.
 template <int LG>
-__device__ __forceinline__ void phase2_fwd(const uint32_t* xp, const RK<LG>& K, f4 (&yr)[2], f4 (&yi)[2])
+__device__ __forceinline__ void phase2_read(const uint32_t* xp, H8U (&m)[2])
+{
+    int d = RC<LG>::COLS;
+    asm("" : "+v"(d));
+    const uint32_t* xq = xp + d;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m[0].w[r] = xp[p2_off<LG>(r)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m[1].w[r] = xq[p2_off<LG>(r)];
+}
+template <int LG>
+__device__ __forceinline__ void phase2_fwd(const H8U (&m)[2], const RK<LG>& K, f4 (&yr)[2], f4 (&yi)[2])
 {
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    H8U m[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[k].w[r] = xp[k * RC<LG>::COLS + p2_off<LG>(r)];
 #pragma unroll
     for (int k = 0; k < 2; ++k) { yr[k] = MFMA(K.c_re, m[k].v, zero); yi[k] = MFMA(K.c_im, m[k].v, zero); }
 }
@@ -381,19 +406,19 @@ __device__ __forceinline__ void phase2_inv(uint32_t* xp, const RK<LG>& K, const 
 }
 
 // Phase 3 of the wave's two tiles: v[k] = samples, register r = d_a % 4, X = d_b (N = 256: tile k = samples
-// d_b = 2j + k, as loaded).  xw: as in phase 1; N = 256: words of the two rows in z.
+// d_b = 2j + k, as loaded).  m: words read from the exchange buffer, at N = 256 the words of the two rows.
 template <int LG>
-__device__ __forceinline__ void phase3(const uint32_t* xw, const H8U (&z)[2], const RK<LG>& K, f4 (&v)[2])
+__device__ __forceinline__ void phase3_read(const uint32_t* xw, H8U (&m)[2])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) m[k].u = *reinterpret_cast<const uint4*>(xw + k * RC<LG>::P);
+}
+template <int LG>
+__device__ __forceinline__ void phase3(H8U (&m)[2], const RK<LG>& K, f4 (&v)[2])
 {
     using C = RC<LG>;
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 r[2], s[2];
-    H8U m[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        if constexpr (C::TC > 1) m[k].u = *reinterpret_cast<const uint4*>(xw + k * C::P);
-        else m[k] = z[k];
-    }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         r[k] = MFMA(m[k].v, K.bi_re[k % C::NS], zero);
@@ -436,185 +461,196 @@ __device__ __forceinline__ float dot_words(uint32_t a, uint32_t b, float s)
     x.u = a; y.u = b;
     return IsBf<IO>::v ? __builtin_amdgcn_fdot2_f32_bf16(x.b, y.b, s, false) : __builtin_amdgcn_fdot2(x.h, y.h, s, false);
 }
-// The wave's two words of a row come one barrier earlier to an LDS copy of the output row, which then leaves in
-// 16-byte pieces, a wave's pieces side by side (words of 4 bytes, a fraction of every 16 per wave, would make the
-// memory side write most lines several times).  Word index with the bits exchanged that would put lanes on one bank.
+// Rows that several waves share travel between memory and LDS in 16-byte pieces, one per thread, side by side; the waves
+// read and write their own words (4 bytes, a fraction of every 16 per wave: straight from memory every line would be
+// fetched by each of the waves, and written several times) in these LDS copies, one barrier later or earlier.  Word index such that a wave's words spread over the banks; 16-byte pieces stay
+// whole, and a lane's four words stay N / 32 words apart.
 template <int LG>
 __device__ __forceinline__ int stage_word(int w)
 {
-    return RC<LG>::TC == 16 ? w ^ ((w >> 4) & 4) : (RC<LG>::TC == 4 ? w ^ ((w >> 2) & 32) : w);
+    return RC<LG>::TC == 16 ? w ^ ((w >> 4) & 4) : (RC<LG>::TC == 4 ? w + ((w >> 7) << 5) : w);
 }
 
 // which workgroup of a persistent grid: consecutive ones on one XCD (they share a head's spectrum in its L2)
 __device__ __forceinline__ int xcd_swizzle(int b, int n) { return (n & 7) ? b : (b & 7) * (n >> 3) + (b >> 3); }
 
-struct RowIt {        // row `b` of head `h`, walked head by head
-    int h, b;
-    __device__ __forceinline__ void next(int B) { if (++b == B) { b = 0; ++h; } }
+// a row of a [B, H, ...] tensor, walked head by head: `step` bytes to the next row of the head, `wrap` more from the row
+// behind a head's last to the next head's first
+struct RowPtr {
+    const char* p;
+    int b;
+    __device__ __forceinline__ void next(int B, int64_t step, int64_t wrap)
+    {
+        p += step;
+        if (++b == B) { b = 0; p += wrap; }
+    }
 };
+// Which code an iteration runs.  Whole: every phase has a row (no conditions).  Scaled: some power of two is not one.
+template <bool W, bool S> struct Mode { static constexpr bool whole = W, scaled = S; };
+// words of samples -> I/O dtype, times 2^ex
+template <class IO, bool SCALED>
+__device__ __forceinline__ uint32_t out_word(float a, float b, int ex)
+{
+    const uint32_t w = pack_io<IO>(a, b);
+    return SCALED ? out_rescaled<IsBf<IO>::v>(w, ex) : w;
+}
 
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u4v buf_load4(rsrc_t r, uint32_t off)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+}
 // -------------------------------------------------------------------------------------
 // Convolution of all rows, rows shared by NWR waves (N >= 1024).  Persistent workgroups, each with a run of consecutive
-// rows (head by head).  Software pipeline over rows, one barrier per row: iteration t runs phase 1 of row t, phase 2 of
-// row t - 1, phase 3 of row t - 2 and stores row t - 3, on three exchange buffers in turn, so every iteration has three
-// independent chains to overlap; row t + 2 is being loaded meanwhile.
+// rows (head by head).  Software pipeline over rows, one barrier per row: iteration t stores row t - 3, runs phase 3 of
+// row t - 2, phase 2 of row t - 1 and phase 1 of row t, puts row t + 1 into LDS and asks for row t + 2.  Phase 3 reads
+// the planes that the same wave's phase 1 then writes, so two exchange buffers serve all three phases.
+// Loads and stores are issued in every iteration, with an empty descriptor where there is no row: conditional ones
+// would make the compiler wait for younger requests than it has to.
 // -------------------------------------------------------------------------------------
 template <int LG, class IO, bool CONJ, bool GATE>
-__global__ void __launch_bounds__(RC<LG>::NWR * 64)
+__global__ void __launch_bounds__(RC<LG>::NWR * 64) __attribute__((amdgpu_waves_per_eu(4)))
 rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
              const typename IO::T* __restrict__ gate, int B, int H, int items, uint32_t pad, const uint4* __restrict__ tab)
 {
     using C = RC<LG>;
     constexpr bool BF = IsBf<IO>::v;
-    constexpr int SW = C::N / 2;                                          // words of a staged row
-    __shared__ __align__(16) uint32_t xbuf[3 * C::XW];
-    __shared__ __align__(16) uint32_t stg[2 * SW];
+    __shared__ __align__(16) uint32_t xbuf[2 * C::XW];
+    __shared__ __align__(16) uint32_t raw[2 * C::SW];
+    __shared__ __align__(16) uint32_t stg[2 * C::SW];
     __shared__ __align__(16) uint32_t mxs[2 * 8];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t0 = 2 * wave;
     const int x = lane & 15, y = lane >> 4;
     const int g = xcd_swizzle(blockIdx.x, gridDim.x);
-    const int i0 = (int)((int64_t)items * g / gridDim.x), i1 = (int)((int64_t)items * (g + 1) / gridDim.x);
-    const int n = i1 - i0;
+    const int each = items / (int)gridDim.x, more = items - each * (int)gridDim.x;
+    const int i0 = g * each + min(g, more), n = each + (g < more);          // this workgroup's rows
     if (n <= 0) return;
-    const uint32_t row_elems = pad ? C::N / 2 : C::N, row_bytes = row_elems * 2u;
-    auto row_of = [&](const RowIt& it, const void* p) {
-        return make_rsrc(reinterpret_cast<const char*>(p) + ((size_t)it.b * H + it.h) * row_bytes, row_bytes);
-    };
-    RowIt il = {i0 / B, i0 % B};                    // next row to load
-    RowIt i_1 = il, i_k = il, i_f = il;             // row of phase 1 (spectrum), of the gate's load, of the store
-    uint32_t off[4];
-    word_offsets<LG>(off, t0, lane, pad, 0u);
-    uint32_t wa[4], wb[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) wa[r] = wb[r] = 0u;
-    {
-        const rsrc_t d = row_of(il, in);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) wa[r] = buf_load(d, off[r]);
-        il.next(B);
-    }
-    if (n > 1) {
-        const rsrc_t d = row_of(il, in);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) wb[r] = buf_load(d, off[r]);
-        il.next(B);
-    }
+    const uint32_t row_bytes = (pad ? C::N / 2 : C::N) * 2u;
+    const int64_t step = (int64_t)H * row_bytes, wrap = (int64_t)row_bytes - B * step;
+    int h = i0 / B, b = i0 - h * B;                 // row of phase 1
+    const int64_t o0 = (int64_t)b * step + (int64_t)h * row_bytes;
+    RowPtr pi = {reinterpret_cast<const char*>(in) + o0, b}, po = {reinterpret_cast<const char*>(out) + o0, b};
+    RowPtr pg = {reinterpret_cast<const char*>(gate) + o0, b};
+    const uint32_t fe = elem_of(8u * threadIdx.x, pad), foff = fe == NOWHERE ? NOWHERE : 2u * fe;
+    u4v rr = buf_load4(make_rsrc(pi.p, row_bytes), foff);                   // this thread's piece of a row
+    pi.next(B, step, wrap);
+    uint32_t off[4], ga[4] = {0u, 0u, 0u, 0u};
+    if (GATE) word_offsets<LG>(off, t0, lane, pad, 0u);
     RK<LG> K;
     load_consts<LG>(K, tab, t0, lane);
-    uint32_t* xw = xbuf + (size_t)t0 * C::P + x * 16 + 4 * y;     // phases 1 and 3
+    H8U kk[2];
+    int es1 = 0, es2 = 0;                  // spectrum exponents of the rows in phases 2 and 3
+    auto load_spec = [&]() {
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+        kk[0].u = ks[t0 * 64 + lane];
+        kk[1].u = ks[(t0 + 1) * 64 + lane];
+        es1 = spec_exp_of(kspec, H, 2 * C::N)[h];
+    };
+    uint32_t* xw = xbuf + (size_t)t0 * C::P + 4 * lane;           // phases 1 and 3
     uint32_t* xp = xbuf + p2_base<LG>(t0, lane);                  // phase 2
-    int sw[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sw[r] = stage_word<LG>((((4 * y + r) * 16 + x) * C::TC + t0) / 2);
-    const uint32_t fe = elem_of(8u * threadIdx.x, pad), foff = fe == NOWHERE ? NOWHERE : 2u * fe;
-    H8U kk[2], kn[2];
-    kk[0].u = kk[1].u = kn[0].u = kn[1].u = make_uint4(0u, 0u, 0u, 0u);
-    int es1 = 0, es2 = 0, esn = 0;         // spectrum exponents of the rows in phases 2 and 3
-    int e1 = 0, e2 = 0;                    // row exponents (bf16) of the rows in phases 2 and 3
-    uint32_t ga[4] = {0u, 0u, 0u, 0u};
-    uint32_t m[1];
-    if constexpr (BF) {
-        words_max<1>(wa, m);
-        if (lane == 0) mxs[wave] = m[0];
-        __syncthreads();
-    }
-    int b1 = 0, b2 = 0, b3 = 0;            // exchange buffers of phases 1, 2, 3
-    auto body = [&](auto full_, int t) {
-        constexpr bool FULL = decltype(full_)::value;
-        const bool do1 = FULL || t < n, do2 = FULL || (t >= 1 && t - 1 < n), do3 = FULL || (t >= 2 && t - 2 < n);
-        int e0 = 0;
+    const int sw = stage_word<LG>(((4 * y * 16 + x) * C::TC + t0) / 2), sf = stage_word<LG>(4 * threadIdx.x);
+    int e0 = 0, e1 = 0, e2 = 0;            // row exponents (bf16) of the rows in phases 1, 2 and 3
+    // row t has arrived: into LDS, with the pattern of its largest sample; row t + 1 is asked for
+    auto arrive = [&](int t) {
+        if constexpr (BF) {
+            uint32_t m[1];
+            const uint32_t w[4] = {rr[0], rr[1], rr[2], rr[3]};
+            words_max<1>(w, m);
+            if (lane == 0) mxs[(t & 1) * 8 + wave] = m[0];
+        }
+        *reinterpret_cast<u4v*>(raw + (t & 1) * C::SW + sf) = rr;
+        rr = buf_load4(make_rsrc(pi.p, t + 1 < n ? row_bytes : 0u), foff);
+        pi.next(B, step, wrap);
+    };
+    load_spec();
+    arrived(K);
+    arrived(kk[0].v); arrived(kk[1].v);
+    arrive(0);
+    __syncthreads();
+    auto iter = [&](auto mode, int t) {
+        using M = decltype(mode);
+        const bool do1 = M::whole || t < n, do2 = M::whole || (t >= 1 && t - 1 < n), do3 = M::whole || (t >= 2 && t - 2 < n);
+        const int bt = (t & 1) * C::XW, bs = C::XW - bt;
+        H8U m3[2], m2[2];
+        uint32_t w[4];
         if (do1) {
-            if constexpr (BF) {
-                uint32_t mm = 0u;
+            const uint32_t* rw = raw + (t & 1) * C::SW + sw;
 #pragma unroll
-                for (int w = 0; w < C::NWR; ++w) mm = max(mm, mxs[(t & 1) * 8 + w]);
-                e0 = row_exponent(__builtin_amdgcn_readfirstlane((int)mm));
-            }
-            if (FULL ? i_1.b == 0 : (t == 0 || i_1.b == 0)) {           // the next phase 2 is another head's
-                const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)i_1.h * 2 * C::N);
-                kn[0].u = ks[t0 * 64 + lane];
-                kn[1].u = ks[(t0 + 1) * 64 + lane];
-                esn = spec_exp_of(kspec, H, 2 * C::N)[i_1.h];
-            }
-            i_1.next(B);
+            for (int r = 0; r < 4; ++r) w[r] = rw[r * (C::N / 32)];
+        }
+        if (do3) phase3_read<LG>(xw + bt, m3);
+        const u4v q = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * C::SW + sf);
+        if (do1) {
             h4 op[2];
             f4 zr[2], zi[2];
-            phase1_ops<LG, IO>(wa, e0, 0, lane, op);
-            phase1<LG>(op, K, xw + b1, zr, zi);
+            phase1_ops<LG, IO, M::scaled>(w, e0, 0, lane, op);
+            phase1<LG>(op, K, xw + bt, zr, zi);
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) wa[r] = wb[r];
-        if (FULL || t + 2 < n) {
-            const rsrc_t d = row_of(il, in);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) wb[r] = buf_load(d, off[r]);
-            il.next(B);
-        }
-        f4 v[2];
+        __builtin_amdgcn_raw_buffer_store_b128(q, make_rsrc(po.p, M::whole || t >= 3 ? row_bytes : 0u), (int)foff, 0, 0);
+        if (M::whole || t >= 3) po.next(B, step, wrap);
+        SCHED_FENCE();
+        if (do2) phase2_read<LG>(xp + bs, m2);
         if (do3) {
-            H8U nz[2];
-            phase3<LG>(xw + b3, nz, K, v);
+            f4 v[2];
+            phase3<LG>(m3, K, v);
+            uint32_t* st = stg + (t & 1) * C::SW + sw;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                st[r * (C::N / 32)] = GATE ? out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]), es2 + e2)
+                                           : out_word<IO, M::scaled>(v[0][r], v[1][r], es2 + e2);
+        }
+        SCHED_FENCE();
+        if (GATE) {                                     // the gate of row t - 1, for the next iteration's phase 3
+            const rsrc_t d = make_rsrc(pg.p, do2 ? row_bytes : 0u);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ga[r] = buf_load(d, off[r]);
+            if (do2) pg.next(B, step, wrap);
         }
         if (do2) {
             f4 yr[2], yi[2];
-            phase2_fwd<LG>(xp + b2, K, yr, yi);
+            phase2_fwd<LG>(m2, K, yr, yi);
             H8U mm[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mm[k].w[r] = cmul_swap<CONJ>(yr[k][r], yi[k][r], kk[k].c[r]);
-            phase2_inv<LG>(xp + b2, K, mm);
+            phase2_inv<LG>(xp + bs, K, mm);
         }
-        if (do3) {
-            uint32_t* st = stg + (t & 1) * SW;
-            uint32_t o[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (GATE) o[r] = pack_io<IO>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]));
-                else o[r] = pack_io<IO>(v[0][r], v[1][r]);
-            }
-            const int ex = es2 + e2;
-            if (__builtin_expect(ex != 0, 0)) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) st[sw[r]] = o[r];
+        es2 = es1; e2 = e1; e1 = e0;
+        SCHED_FENCE();
+        arrive(t + 1);
+        if (do1) {
+            if (b == 0 && t > 0) load_spec();           // the next phase 2 is another head's
+            if (++b == B) { b = 0; ++h; }
         }
-        if (GATE && do2) {
-            const rsrc_t d = row_of(i_k, gate);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ga[r] = buf_load(d, off[r]);
-            i_k.next(B);
-        }
-        if (FULL || t >= 3) {
-            const u4v q = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * SW + stage_word<LG>(4 * threadIdx.x));
-            __builtin_amdgcn_raw_buffer_store_b128(q, row_of(i_f, out), (int)foff, 0, 0);
-            i_f.next(B);
-        }
-        es2 = es1; e2 = e1;
-        es1 = esn; e1 = e0;
-        kk[0] = kn[0]; kk[1] = kn[1];
-        if constexpr (BF) {
-            if (FULL || t + 1 < n) {
-                words_max<1>(wa, m);
-                if (lane == 0) mxs[((t + 1) & 1) * 8 + wave] = m[0];
-            }
-        }
-        b3 = b2; b2 = b1;
-        b1 = b1 == 2 * C::XW ? 0 : b1 + C::XW;
         __syncthreads();
     };
-    int t = 0;
-    for (; t < 3; ++t) body(No{}, t);
-    for (; t + 2 < n; ++t) body(Yes{}, t);
-    for (; t < n + 3; ++t) body(No{}, t);
+    // exponent of row t; what kind of iteration t is: 0 at the ends, 1 whole, 2 whole and nothing scaled
+    auto prep = [&](int t) {
+        if constexpr (BF) {
+            if (t < n) {
+                uint32_t mm = 0u;
+#pragma unroll
+                for (int w = 0; w < C::NWR; ++w) mm = max(mm, mxs[(t & 1) * 8 + w]);
+                e0 = row_exponent(__builtin_amdgcn_readfirstlane((int)mm));
+            }
+        }
+        return t >= 3 && t < n ? ((e0 | e2 | es2) == 0 ? 2 : 1) : 0;
+    };
+    // (a loop of its own for each kind: iterations of one kind following each other keep everything in place)
+    for (int t = 0;;) {
+        int kind = prep(t);
+        while (kind == 2) { iter(Mode<true, false>{}, t); kind = prep(++t); }
+        while (kind == 1) { iter(Mode<true, true>{}, t); kind = prep(++t); }
+        if (t >= n + 3) break;
+        if (kind == 0) { iter(Mode<false, true>{}, t); ++t; }
+    }
 }
 
 // The same for rows that one wave owns (N = 256: two rows at a time; N = 512): no barrier, no staging (a wave's words
 // already cover 32 or 64 contiguous bytes).
 template <int LG, class IO, bool CONJ, bool GATE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
               const typename IO::T* __restrict__ gate, int B, int H, int bpi, int items, uint32_t pad,
               const uint4* __restrict__ tab)
@@ -624,71 +660,54 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
     constexpr int NSP = C::NS;
     __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : 4 * C::XW];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int x = lane & 15, y = lane >> 4;
     const int ng = gridDim.x * 4, g = xcd_swizzle(blockIdx.x, gridDim.x) * 4 + wave;
-    const int i0 = (int)((int64_t)items * g / ng), i1 = (int)((int64_t)items * (g + 1) / ng);
+    const int each = items / ng, more = items - each * ng;
+    const int i0 = g * each + min(g, more), i1 = i0 + each + (g < more);    // this wave's passes
     if (i1 <= i0) return;
     const uint32_t row_bytes = pad ? C::N : 2 * C::N;
     const uint32_t row_step = (uint32_t)H * row_bytes;            // from a row to the next of its head
-    auto row_of = [&](const RowIt& it, const void* p) {           // it.b counts passes of RPI rows
-        const int b = it.b * C::RPI;
-        const uint32_t bytes = row_bytes + (C::RPI == 2 && b + 1 < B ? row_step : 0u);
-        return make_rsrc(reinterpret_cast<const char*>(p) + ((size_t)b * H + it.h) * row_bytes, bytes);
-    };
-    RowIt il = {i0 / bpi, i0 % bpi}, ic = il;
+    const int64_t step = (int64_t)C::RPI * row_step, wrap = (int64_t)row_bytes - bpi * step;
+    int h = i0 / bpi;
+    const int b0 = i0 - h * bpi;                                  // RowPtr::b counts passes of RPI rows
+    const int64_t o0 = (int64_t)b0 * step + (int64_t)h * row_bytes;
+    RowPtr pi = {reinterpret_cast<const char*>(in) + o0, b0}, po = {reinterpret_cast<const char*>(out) + o0, b0};
+    RowPtr pg = {reinterpret_cast<const char*>(gate) + o0, b0};
+    const int odd = C::RPI == 2 ? B >> 1 : bpi;                   // the pass without a second row
+    auto rsrc = [&](const RowPtr& q) { return make_rsrc(q.p, C::RPI == 2 && q.b != odd ? row_bytes + row_step : row_bytes); };
     uint32_t off[4];
     word_offsets<LG>(off, 0, lane, pad, row_step);
-    uint32_t wn[4], gn[4] = {0u, 0u, 0u, 0u};
-    {
-        const rsrc_t d = row_of(il, in);
+    uint32_t w[4], gn[4] = {0u, 0u, 0u, 0u};
+    auto load = [&](RowPtr& q, uint32_t (&v)[4], bool any) {      // (an empty descriptor where there is no row)
+        const rsrc_t d = any ? rsrc(q) : make_rsrc(q.p, 0u);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) wn[r] = buf_load(d, off[r]);
-        if (GATE) {
-            const rsrc_t dg = row_of(il, gate);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) gn[r] = buf_load(dg, off[r]);
-        }
-        il.next(bpi);
-    }
+        for (int r = 0; r < 4; ++r) v[r] = buf_load(d, off[r]);
+        q.next(bpi, step, wrap);
+    };
+    load(pi, w, true);
+    if (GATE) load(pg, gn, true);
     RK<LG> K;
     load_consts<LG>(K, tab, 0, lane);
     uint32_t* xb = xbuf + (C::TC == 1 ? 0 : wave * C::XW);
-    uint32_t* xw = xb + x * 16 + 4 * y;
+    uint32_t* xw = xb + 4 * lane;
     uint32_t* xp = xb + p2_base<LG>(0, lane);
     H8U kk[NSP];
+    arrived(K);
     int es = 0;
-    for (int i = i0; i < i1; ++i) {
-        uint32_t w[4], ga[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { w[r] = wn[r]; ga[r] = gn[r]; }
-        if (i == i0 || ic.b == 0) {
-            const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)ic.h * 2 * C::N);
-#pragma unroll
-            for (int k = 0; k < NSP; ++k) kk[k].u = ks[k * 64 + lane];
-            es = spec_exp_of(kspec, H, 2 * C::N)[ic.h];
-        }
-        int e[2] = {0, 0};
-        if constexpr (BF) {
-            uint32_t m[C::RPI];
-            words_max<C::RPI>(w, m);
-#pragma unroll
-            for (int k = 0; k < C::RPI; ++k) e[k] = row_exponent(m[k]);
-        }
+    int ea = 0, eb = 0;                                           // exponents (bf16) of the pass's row(s)
+    auto iter = [&](auto mode, int i) {
+        using M = decltype(mode);
         h4 op[2];
-        phase1_ops<LG, IO>(w, e[0], e[1], lane, op);
-        if (i + 1 < i1) {
-            const rsrc_t d = row_of(il, in);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) wn[r] = buf_load(d, off[r]);
-            if (GATE) {
-                const rsrc_t dg = row_of(il, gate);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) gn[r] = buf_load(dg, off[r]);
-            }
-            il.next(bpi);
-        }
         f4 zr[2], zi[2], v[2];
         H8U m[2];
+        uint32_t ga[4];
+        phase1_ops<LG, IO, M::scaled>(w, ea, eb, lane, op);
+        if (GATE) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ga[r] = gn[r];
+        }
+        load(pi, w, i + 1 < i1);
+        if (GATE) load(pg, gn, i + 1 < i1);
+        SCHED_FENCE();                                  // (the loads go out here)
         phase1<LG>(op, K, xw, zr, zi);
         if constexpr (C::TC == 1) {
 #pragma unroll
@@ -699,30 +718,53 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
         } else {
             wave_lds_fence();
             f4 yr[2], yi[2];
-            phase2_fwd<LG>(xp, K, yr, yi);
+            phase2_read<LG>(xp, m);
+            phase2_fwd<LG>(m, K, yr, yi);
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_swap<CONJ>(yr[k][r], yi[k][r], kk[k % NSP].c[r]);
             phase2_inv<LG>(xp, K, m);
             wave_lds_fence();
+            phase3_read<LG>(xw, m);
         }
-        phase3<LG>(xw, m, K, v);
-        uint32_t o[4];
+        phase3<LG>(m, K, v);
+        const int ex = es + (C::TC == 1 && (lane & 8) ? eb : ea);
+        const rsrc_t d = rsrc(po);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (GATE) o[r] = pack_io<IO>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]));
-            else o[r] = pack_io<IO>(v[0][r], v[1][r]);
+        for (int r = 0; r < 4; ++r)
+            buf_store(d, off[r], GATE ? out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]), ex)
+                                      : out_word<IO, M::scaled>(v[0][r], v[1][r], ex));
+        po.next(bpi, step, wrap);
+        h += po.b == 0;
+    };
+    // the pass has arrived: spectrum of a new head, exponents; is anything scaled?
+    auto prep = [&](int i) {
+        if (i == i0 || po.b == 0) {
+            const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) kk[k].u = ks[k * 64 + lane];
+            es = spec_exp_of(kspec, H, 2 * C::N)[h];
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) arrived(kk[k].v);
         }
-        if (__builtin_expect((es | e[0] | e[1]) != 0, 0)) {
-            const int ex = es + (C::TC == 1 && (lane & 8) ? e[1] : e[0]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
+        if constexpr (BF) {
+            uint32_t m[C::RPI];
+            words_max<C::RPI>(w, m);
+            ea = row_exponent(m[0]);
+            if (C::RPI == 2) eb = row_exponent(m[C::RPI - 1]);
         }
-        const rsrc_t d = row_of(ic, out);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) buf_store(d, off[r], o[r]);
-        ic.next(bpi);
+        return (es | ea | eb) != 0;
+    };
+    for (int i = i0;;) {
+        bool scaled = prep(i);
+        while (!scaled) {
+            iter(Mode<true, false>{}, i);
+            if (++i == i1) return;
+            scaled = prep(i);
+        }
+        iter(Mode<true, true>{}, i);
+        if (++i == i1) return;
     }
 }
 
@@ -740,7 +782,6 @@ rkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* 
     __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : C::XW];
     __shared__ float wmax[3][8];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t0 = 2 * wave;
-    const int x = lane & 15, y = lane >> 4;
     const int h = blockIdx.x;
     const uint32_t row_bytes = (pad ? C::N / 2 : C::N) * 4u;
     const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(k) + (size_t)h * row_bytes, row_bytes);
@@ -785,12 +826,14 @@ rkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* 
 #pragma unroll
     for (int r = 0; r < 4; ++r) w[r] = pack_h2(v[r][0] * s, v[r][1] * s);
     h4 op[2];
-    phase1_ops<LG, IoF16>(w, 0, 0, lane, op);
+    phase1_ops<LG, IoF16, false>(w, 0, 0, lane, op);
     f4 yr[2], yi[2];
-    phase1<LG>(op, K, xbuf + (C::TC == 1 ? 0 : t0 * C::P + x * 16 + 4 * y), yr, yi);
+    phase1<LG>(op, K, xbuf + (C::TC == 1 ? 0 : t0 * C::P + 4 * lane), yr, yi);
     if constexpr (C::TC > 1) {
         if (C::NWR > 1) __syncthreads(); else wave_lds_fence();
-        phase2_fwd<LG>(xbuf + p2_base<LG>(t0, lane), K, yr, yi);
+        H8U m2[2];
+        phase2_read<LG>(xbuf + p2_base<LG>(t0, lane), m2);
+        phase2_fwd<LG>(m2, K, yr, yi);
     }
     const float alpha = ldexpf(kscale * (float)(1 << C::SHIFT) / s, -es), beta = ldexpf(Dh * kscale, -es);
     uint4* o = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (size_t)h * 2 * C::N);
@@ -820,9 +863,10 @@ __device__ __forceinline__ int acc_align(float2 (&acc)[NA][4], int& eref, int ep
     return ep - eref;
 }
 // acc += conj(U) W 2^down
+template <bool SCALED>
 __device__ __forceinline__ void acc_tile(float2 (&acc)[4], const f4& ur, const f4& ui, const f4& wr, const f4& wi, int down)
 {
-    if (__builtin_expect(down != 0, 0)) {
+    if constexpr (SCALED) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const float a = ldexpf(wr[j], down), b = ldexpf(wi[j], down);
@@ -836,6 +880,9 @@ __device__ __forceinline__ void acc_tile(float2 (&acc)[4], const f4& ur, const f
             acc[j].y = __builtin_fmaf(-ui[j], wr[j], __builtin_fmaf(ur[j], wi[j], acc[j].y));
         }
     }
+    // not to be moved past the end of the iteration: the sums read MFMA results, and no branch may come in between
+#pragma unroll
+    for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(acc[j].x), "+v"(acc[j].y));
 }
 
 // U of the dk-only kernels as packed fp16 (dot products without du keep one operand packed; the fused kernel keeps both
@@ -890,30 +937,63 @@ __device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2
 // A += conj(U) W in fp32 registers; dk is one inverse transform of A at the end.  Software pipeline as in rconv_kernel:
 // phase 1 of both rows t, phase 2 of rows t - 1, phase 3 of du's row t - 2, row t - 3 stored, one barrier per row.
 // NGRP groups of waves take every NGRP-th row and add their A at the end in group order.
+// GATE (gated layer): dy is replaced by dz = dy g (rounded to the I/O dtype) as the rows arrive, dD sums dy g u in fp32,
+// and U's own inverse of U K gives z for dg = dy z.
 // -------------------------------------------------------------------------------------
-template <int LG> struct BwdCfg {
+template <int LG, bool GATE> struct BwdCfg {
     static constexpr int NGRP = LG == 10 ? 2 : 1, NWV = NGRP * RC<LG>::NWR;
-    static constexpr int GW = 5 * RC<LG>::XW + RC<LG>::N;       // LDS words of a group
+    // LDS words of a group: two exchange buffers, two rows on the way in and two on the way out for each tensor
+    static constexpr int GW = 4 * RC<LG>::XW + (GATE ? 8 : 6) * RC<LG>::SW;
     static constexpr size_t lds = ((size_t)NGRP * GW + 2 * 8 * 2 + 8 + 8) * 4;
 };
-template <int LG, class IO, bool DU>
-__global__ void __launch_bounds__(BwdCfg<LG>::NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
-rbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ kspec,
-            typename IO::T* __restrict__ du, float* __restrict__ dk, float* __restrict__ dD, int B, int H, int nsplit,
-            float dkscale, uint32_t pad, const uint4* __restrict__ tab)
+template <class T>
+struct BwdArgs {
+    const T* dy;
+    const T* u;
+    const T* g;
+    const float2* kspec;
+    T* du;
+    T* dg;
+    float* dk;
+    float* dD;
+    int B, H, nsplit;
+    float dkscale;
+    uint32_t pad;
+    const uint4* tab;
+};
+// dz = dy g in place of dy, and the fp32 sum of dy g u
+template <class IO>
+__device__ __forceinline__ float gate_words(uint32_t (&d)[4], const uint32_t (&g)[4], const uint32_t (&u)[4], float s)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float a = lo_of<IO>(d[r]) * lo_of<IO>(g[r]), b = hi_of<IO>(d[r]) * hi_of<IO>(g[r]);
+        s = __builtin_fmaf(b, hi_of<IO>(u[r]), __builtin_fmaf(a, lo_of<IO>(u[r]), s));
+        d[r] = pack_io<IO>(a, b);
+    }
+    return s;
+}
+
+template <int LG, class IO, bool DU, bool GATE>
+__global__ void __launch_bounds__((BwdCfg<LG, GATE>::NWV * 64)) __attribute__((amdgpu_waves_per_eu(2)))
+rbwd_kernel(const BwdArgs<typename IO::T> q)
 {
     using C = RC<LG>;
-    using Q = BwdCfg<LG>;
+    using Q = BwdCfg<LG, GATE>;
+    static_assert(DU || !GATE, "the gated form comes with du");
     constexpr bool BF = IsBf<IO>::v;
-    constexpr int SW = C::N / 2, NGRP = Q::NGRP, NWR = C::NWR;
+    constexpr int NGRP = Q::NGRP, NWR = C::NWR;
     extern __shared__ uint4 lds4[];
     uint32_t* lds = reinterpret_cast<uint32_t*>(lds4);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = wave / NWR, t0 = 2 * (wave % NWR), gt = threadIdx.x % (NWR * 64);
     const int x = lane & 15, y = lane >> 4;
-    uint32_t* xd = lds + grp * Q::GW;                   // dy: three buffers
-    uint32_t* xu = xd + 3 * C::XW;                      // u: two
-    uint32_t* stg = xu + 2 * C::XW;                     // du on its way out: two rows
+    const int B = q.B, H = q.H, nsplit = q.nsplit;
+    const uint32_t pad = q.pad;
+    uint32_t* xd = lds + grp * Q::GW;                   // dy: two exchange buffers
+    uint32_t* xu = xd + 2 * C::XW;                      // u: two
+    uint32_t* raw = xu + 2 * C::XW;                     // dy (two rows), u (two rows) on the way in
+    uint32_t* stg = raw + 4 * C::SW;                    // du (and dg) on the way out: two rows each
     uint32_t* mxs = lds + NGRP * Q::GW;                 // [2][8][2] patterns of the waves' words
     float* dred = reinterpret_cast<float*>(mxs + 32);   // [8]
     int* erefs = reinterpret_cast<int*>(dred + 8);      // [8]
@@ -924,70 +1004,172 @@ rbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
     const int nmine = (B - b0 - grp + bstep - 1) / bstep;             // of this group
     const int nmin = (B - b0 - (NGRP - 1) + bstep - 1) / bstep;       // of the last
     const uint32_t row_bytes = (pad ? C::N / 2 : C::N) * 2u;
-    auto row_of = [&](int i, const void* p) {
-        return make_rsrc(reinterpret_cast<const char*>(p) + ((size_t)(b0 + grp + i * bstep) * H + h) * row_bytes, row_bytes);
+    const int64_t o0 = ((int64_t)(b0 + grp) * H + h) * row_bytes, step = (int64_t)bstep * H * row_bytes;
+    const char* pdy = reinterpret_cast<const char*>(q.dy) + o0;      // rows to load
+    const char* pu = reinterpret_cast<const char*>(q.u) + o0;
+    const char* pg = reinterpret_cast<const char*>(q.g) + o0;
+    const char* pdy3 = pdy;                                          // dy again, for dg
+    char* pdu = reinterpret_cast<char*>(q.du) + o0;                  // rows to store
+    char* pdg = reinterpret_cast<char*>(q.dg) + o0;
+    const uint32_t fe = elem_of(8u * gt, pad), foff = fe == NOWHERE ? NOWHERE : 2u * fe;
+    u4v rd, ru, rg = {0u, 0u, 0u, 0u};                               // this thread's pieces of the rows
+    auto ask = [&](int t) {
+        const uint32_t bytes = t < nmine ? row_bytes : 0u;           // (an empty descriptor where there is no row)
+        rd = buf_load4(make_rsrc(pdy, bytes), foff); pdy += step;
+        ru = buf_load4(make_rsrc(pu, bytes), foff); pu += step;
+        if (GATE) { rg = buf_load4(make_rsrc(pg, bytes), foff); pg += step; }
     };
-    uint32_t off[4];
-    word_offsets<LG>(off, t0, lane, pad, 0u);
-    uint32_t da[4], db[4], ua[4], ub[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) da[r] = db[r] = ua[r] = ub[r] = 0u;
-    auto load = [&](int i, uint32_t (&d)[4], uint32_t (&v)[4]) {
-        const rsrc_t rd = row_of(i, dy), ru = row_of(i, u);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) d[r] = buf_load(rd, off[r]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = buf_load(ru, off[r]);
-    };
-    if (0 < nmine) load(0, da, ua);
-    if (1 < nmine) load(1, db, ub);
+    ask(0);
+    uint32_t off[4], dz[4] = {0u, 0u, 0u, 0u};
+    if (GATE) word_offsets<LG>(off, t0, lane, pad, 0u);
     RK<LG> K;
-    load_consts<LG>(K, tab, t0, lane);
+    load_consts<LG>(K, q.tab, t0, lane);
     H8U kk[2];
     kk[0].u = kk[1].u = make_uint4(0u, 0u, 0u, 0u);
     int es = 0;
     if (DU) {
-        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(q.kspec) + (size_t)h * 2 * C::N);
         kk[0].u = ks[t0 * 64 + lane];
         kk[1].u = ks[(t0 + 1) * 64 + lane];
-        es = spec_exp_of(kspec, H, 2 * C::N)[h];
+        es = spec_exp_of(q.kspec, H, 2 * C::N)[h];
     }
-    const int xwo = t0 * C::P + x * 16 + 4 * y, xpo = p2_base<LG>(t0, lane);
-    int sw[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sw[r] = stage_word<LG>((((4 * y + r) * 16 + x) * C::TC + t0) / 2);
-    const uint32_t fe = elem_of(8u * gt, pad), foff = fe == NOWHERE ? NOWHERE : 2u * fe;
+    const int xwo = t0 * C::P + 4 * lane, xpo = p2_base<LG>(t0, lane);
+    const int sw = stage_word<LG>(((4 * y * 16 + x) * C::TC + t0) / 2), sf = stage_word<LG>(4 * gt);
     float2 acc[2][4];
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[k][j] = make_float2(0.f, 0.f);
     float dsum = 0.f;
-    int eref = EXP_NONE, ep1 = 0, ed1 = 0, ed2 = 0;
-    uint32_t m1[1], m2[1];
-    auto publish = [&](int par) {
-        words_max<1>(da, m1);
-        words_max<1>(ua, m2);
-        if (lane == 0) *reinterpret_cast<uint2*>(mxs + (par * 8 + wave) * 2) = make_uint2(m1[0], m2[0]);
+    int eref = EXP_NONE, ep0 = 0, ep1 = 0;                           // units of A and of the products
+    int ed0 = 0, ed1 = 0, ed2 = 0, eu0 = 0, eu1 = 0, eu2 = 0;        // row exponents (bf16) in phases 1, 2, 3
+    // rows t have arrived: gate, dot product, patterns, into LDS; rows t + 1 are asked for
+    auto arrive = [&](int t) {
+        uint32_t d[4] = {rd[0], rd[1], rd[2], rd[3]};
+        const uint32_t v[4] = {ru[0], ru[1], ru[2], ru[3]}, g[4] = {rg[0], rg[1], rg[2], rg[3]};
+        if (GATE) {
+            dsum = gate_words<IO>(d, g, v, dsum);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(d[r], v[r], dsum);
+        }
+        if constexpr (BF) {
+            uint32_t m1[1], m2[1];
+            words_max<1>(d, m1);
+            words_max<1>(v, m2);
+            if (lane == 0) *reinterpret_cast<uint2*>(mxs + ((t & 1) * 8 + wave) * 2) = make_uint2(m1[0], m2[0]);
+        }
+        *reinterpret_cast<uint4*>(raw + (t & 1) * C::SW + sf) = make_uint4(d[0], d[1], d[2], d[3]);
+        *reinterpret_cast<uint4*>(raw + (2 + (t & 1)) * C::SW + sf) = make_uint4(v[0], v[1], v[2], v[3]);
+        ask(t + 1);
     };
-    if constexpr (BF) {
-        publish(0);
-        __syncthreads();
-    }
-    int c1 = 0, c2 = 0, c3 = 0;
-    auto body = [&](auto full_, int t) {
-        constexpr bool FULL = decltype(full_)::value;
-        const bool do1 = FULL || t < nmine, do2 = FULL || (t >= 1 && t - 1 < nmine);
-        const bool do3 = DU && (FULL || (t >= 2 && t - 2 < nmine));
-        int ed0 = 0, ep0 = 0;
+    arrived(K);
+    arrived(kk[0].v); arrived(kk[1].v);
+    arrive(0);
+    __syncthreads();
+    auto iter = [&](auto mode, int t) {
+        using M = decltype(mode);
+        const bool do1 = M::whole || t < nmine, do2 = M::whole || (t >= 1 && t - 1 < nmine);
+        const bool do3 = DU && (M::whole || (t >= 2 && t - 2 < nmine));
+        const int bt = (t & 1) * C::XW, bs = C::XW - bt;             // buffers of phases 1 and 3, and of phase 2
+        H8U m3[2], n3[2], m2[2], n2[2];
+        uint32_t wd[4], wu[4];
         if (do1) {
-            int eu0 = 0;
-            if constexpr (BF) {
+            const uint32_t* rw = raw + (t & 1) * C::SW + sw;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { wd[r] = rw[r * (C::N / 32)]; wu[r] = rw[2 * C::SW + r * (C::N / 32)]; }
+        }
+        if (do3) {
+            phase3_read<LG>(xd + xwo + bt, m3);
+            if (GATE) phase3_read<LG>(xu + xwo + bt, n3);
+        }
+        if (do1) {
+            h4 op[2];
+            f4 zr[2], zi[2];
+            phase1_ops<LG, IO, M::scaled>(wd, ed0, 0, lane, op);
+            phase1<LG>(op, K, xd + xwo + bt, zr, zi);
+            phase1_ops<LG, IO, M::scaled>(wu, eu0, 0, lane, op);
+            phase1<LG>(op, K, xu + xwo + bt, zr, zi);
+        }
+        if (DU) {
+            const uint32_t bytes = M::whole || (t >= 3 && t - 3 < nmine) ? row_bytes : 0u;
+            u4v o = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * C::SW + sf);
+            __builtin_amdgcn_raw_buffer_store_b128(o, make_rsrc(pdu, bytes), (int)foff, 0, 0);
+            if (M::whole || t >= 3) pdu += step;
+            if (GATE) {
+                o = *reinterpret_cast<const u4v*>(stg + (2 + ((t - 1) & 1)) * C::SW + sf);
+                __builtin_amdgcn_raw_buffer_store_b128(o, make_rsrc(pdg, bytes), (int)foff, 0, 0);
+                if (M::whole || t >= 3) pdg += step;
+            }
+        }
+        if (do2) {
+            phase2_read<LG>(xd + xpo + bs, m2);
+            phase2_read<LG>(xu + xpo + bs, n2);
+        }
+        if (do3) {
+            f4 v[2];
+            phase3<LG>(m3, K, v);
+            uint32_t* st = stg + (t & 1) * C::SW + sw;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st[r * (C::N / 32)] = out_word<IO, M::scaled>(v[0][r], v[1][r], es + ed2);
+            if (GATE) {
+                phase3<LG>(n3, K, v);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    st[2 * C::SW + r * (C::N / 32)] =
+                        out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(dz[r]), v[1][r] * hi_of<IO>(dz[r]), es + eu2);
+            }
+        }
+        if (GATE) {                                     // dy of row t - 1, for the next iteration's dg
+            const rsrc_t r3 = make_rsrc(pdy3, do2 ? row_bytes : 0u);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dz[r] = buf_load(r3, off[r]);
+            if (do2) pdy3 += step;
+        }
+        if (do2) {
+            f4 wr[2], wi[2], yr[2], yi[2];
+            int down = 0;
+            if constexpr (BF && M::scaled) down = acc_align<2>(acc, eref, ep1);    // (its branch: not behind an MFMA)
+            phase2_fwd<LG>(m2, K, wr, wi);
+            phase2_fwd<LG>(n2, K, yr, yi);
+            if (DU) {
+                H8U mm[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mm[k].w[r] = cmul_swap<true>(wr[k][r], wi[k][r], kk[k].c[r]);
+                phase2_inv<LG>(xd + xpo + bs, K, mm);
+            }
+            if (GATE) {
+                H8U mm[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mm[k].w[r] = cmul_swap<false>(yr[k][r], yi[k][r], kk[k].c[r]);
+                phase2_inv<LG>(xu + xpo + bs, K, mm);
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                if (!DU) round_h2(yr[k], yi[k]);
+                acc_tile<BF && M::scaled>(acc[k], yr[k], yi[k], wr[k], wi[k], down);
+            }
+        }
+        ed2 = ed1; ed1 = ed0;
+        eu2 = eu1; eu1 = eu0;
+        ep1 = ep0;
+        SCHED_FENCE();                                  // (not into the middle: the rows were asked for one iteration ago)
+        arrive(t + 1);
+        __syncthreads();
+    };
+    // exponents of rows t; what kind of iteration t is: 0 at the ends, 1 whole, 2 whole and nothing scaled
+    auto prep = [&](int t) {
+        if constexpr (BF) {
+            if (t < nmine) {
                 uint32_t md = 0u, mu_ = 0u;
 #pragma unroll
                 for (int w = 0; w < NWR; ++w) {
-                    const uint2 q = *reinterpret_cast<const uint2*>(mxs + ((t & 1) * 8 + grp * NWR + w) * 2);
-                    md = max(md, q.x); mu_ = max(mu_, q.y);
+                    const uint2 v = *reinterpret_cast<const uint2*>(mxs + ((t & 1) * 8 + grp * NWR + w) * 2);
+                    md = max(md, v.x); mu_ = max(mu_, v.y);
                 }
                 md = __builtin_amdgcn_readfirstlane((int)md);
                 mu_ = __builtin_amdgcn_readfirstlane((int)mu_);
@@ -995,81 +1177,26 @@ rbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
                 eu0 = row_exponent(mu_);
                 ep0 = md && mu_ ? ed0 + eu0 : EXP_NONE;
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(da[r], ua[r], dsum);
-            h4 op[2];
-            f4 zr[2], zi[2];
-            phase1_ops<LG, IO>(da, ed0, 0, lane, op);
-            phase1<LG>(op, K, xd + xwo + c1, zr, zi);
-            phase1_ops<LG, IO>(ua, eu0, 0, lane, op);
-            phase1<LG>(op, K, xu + xwo + (t & 1) * C::XW, zr, zi);
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { da[r] = db[r]; ua[r] = ub[r]; }
-        if (FULL || t + 2 < nmine) load(t + 2, db, ub);
-        f4 v[2];
-        if (do3) {
-            H8U nz[2];
-            phase3<LG>(xd + xwo + c3, nz, K, v);
-        }
-        if (do2) {
-            f4 wr[2], wi[2], yr[2], yi[2];
-            phase2_fwd<LG>(xd + xpo + c2, K, wr, wi);
-            phase2_fwd<LG>(xu + xpo + ((t - 1) & 1) * C::XW, K, yr, yi);
-            if (DU) {
-                H8U mm[2];
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) mm[k].w[r] = cmul_swap<true>(wr[k][r], wi[k][r], kk[k].c[r]);
-                phase2_inv<LG>(xd + xpo + c2, K, mm);
-            }
-            int down = 0;
-            if constexpr (BF) down = acc_align<2>(acc, eref, ep1);
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                if (!DU) round_h2(yr[k], yi[k]);
-                acc_tile(acc[k], yr[k], yi[k], wr[k], wi[k], down);
-            }
-        }
-        if (do3) {
-            uint32_t* st = stg + (t & 1) * SW;
-            uint32_t o[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = pack_io<IO>(v[0][r], v[1][r]);
-            const int ex = es + ed2;
-            if (__builtin_expect(ex != 0, 0)) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) st[sw[r]] = o[r];
-        }
-        if (DU && (FULL || (t >= 3 && t - 3 < nmine))) {
-            const u4v q = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * SW + stage_word<LG>(4 * gt));
-            __builtin_amdgcn_raw_buffer_store_b128(q, row_of(t - 3, du), (int)foff, 0, 0);
-        }
-        ed2 = ed1; ed1 = ed0; ep1 = ep0;
-        if constexpr (BF) {
-            if (FULL || t + 1 < nmine) publish((t + 1) & 1);
-        }
-        c3 = c2; c2 = c1;
-        c1 = c1 == 2 * C::XW ? 0 : c1 + C::XW;
-        __syncthreads();
+        if (t < 3 || t >= nmin) return 0;
+        return (ed0 | eu0 | ed2 | es | (GATE ? eu2 : 0)) == 0 && (!BF || ep1 == eref) ? 2 : 1;
     };
     const int last = niter + (DU ? 3 : 1);
-    int t = 0;
-    for (; t < 3 && t < last; ++t) body(No{}, t);
-    for (; t + 2 < nmin; ++t) body(Yes{}, t);
-    for (; t < last; ++t) body(No{}, t);
+    for (int t = 0;;) {
+        int kind = prep(t);
+        while (kind == 2) { iter(Mode<true, false>{}, t); kind = prep(++t); }
+        while (kind == 1) { iter(Mode<true, true>{}, t); kind = prep(++t); }
+        if (t >= last) break;
+        if (kind == 0) { iter(Mode<false, true>{}, t); ++t; }
+    }
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
     if (lane == 0) dred[wave] = dsum;
     const int etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
-    if (NGRP > 1 || !dk) __syncthreads();              // (red lies in the buffers that follow)
-    if (dk) {
-        float* fs = reinterpret_cast<float*>(lds + 3 * C::XW);        // the row of dk in the u buffers of the first group
+    if (NGRP > 1 || !q.dk) __syncthreads();              // (the reduction's words lie in the buffers that follow)
+    if (q.dk) {
+        float* fs = reinterpret_cast<float*>(lds + 2 * C::XW);        // the row of dk in the u buffers of the first group
         if (grp == 0) {
             H8U mm[2];
 #pragma unroll
@@ -1080,38 +1207,38 @@ rbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
         }
         __syncthreads();
         if (grp == 0) {
-            H8U nz[2];
+            H8U m3[2];
             f4 v[2];
-            phase3<LG>(lds + xwo, nz, K, v);
+            phase3_read<LG>(lds + xwo, m3);
+            phase3<LG>(m3, K, v);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 *reinterpret_cast<float2*>(fs + ((4 * y + r) * 16 + x) * C::TC + t0) =
-                    make_float2(ldexpf(v[0][r] * dkscale, etop), ldexpf(v[1][r] * dkscale, etop));
+                    make_float2(ldexpf(v[0][r] * q.dkscale, etop), ldexpf(v[1][r] * q.dkscale, etop));
         }
         __syncthreads();
         const uint32_t kb = (pad ? C::N / 2 : C::N) * 4u;
-        const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(dk) + ho * kb, kb);
-        for (int q = threadIdx.x; q < C::N / 4; q += Q::NWV * 64) {
-            const uint32_t e = elem_of(4u * q, pad);
-            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u4v*>(fs + 4 * q), d,
+        const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(q.dk) + ho * kb, kb);
+        for (int i = threadIdx.x; i < C::N / 4; i += Q::NWV * 64) {
+            const uint32_t e = elem_of(4u * i, pad);
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u4v*>(fs + 4 * i), d,
                                                    (int)(e == NOWHERE ? NOWHERE : 4u * e), 0, 0);
         }
     }
-    if (threadIdx.x == 0 && dD) {
+    if (threadIdx.x == 0 && q.dD) {
         float s = 0.f;
         for (int w = 0; w < Q::NWV; ++w) s += dred[w];
-        dD[ho] = s;
+        q.dD[ho] = s;
     }
 }
 
 // The same for rows that one wave owns (N = 256: two rows at a time; N = 512): four independent waves per workgroup.
-template <int LG, class IO, bool DU>
+template <int LG, class IO, bool DU, bool GATE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-rbwd1_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ kspec,
-             typename IO::T* __restrict__ du, float* __restrict__ dk, float* __restrict__ dD, int B, int H, int nsplit,
-             float dkscale, uint32_t pad, const uint4* __restrict__ tab)
+rbwd1_kernel(const BwdArgs<typename IO::T> q)
 {
     using C = RC<LG>;
+    static_assert(DU || !GATE, "the gated form comes with du");
     constexpr bool BF = IsBf<IO>::v;
     constexpr int NS = C::NS, NWV = 4;
     __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : NWV * 2 * C::XW];
@@ -1119,115 +1246,163 @@ rbwd1_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __rest
     __shared__ float dred[NWV];
     __shared__ int erefs[NWV];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int x = lane & 15, y = lane >> 4;
+    const int B = q.B, H = q.H, nsplit = q.nsplit;
+    const uint32_t pad = q.pad;
     const int h = blockIdx.x % (unsigned)H, split = blockIdx.x / (unsigned)H;
-    const int npass = (B + C::RPI - 1) / C::RPI, pstep = nsplit * NWV;
+    const int npass = (B + C::RPI - 1) / C::RPI, pstep = nsplit * NWV, odd = C::RPI == 2 ? B >> 1 : npass;
     const uint32_t row_bytes = pad ? C::N : 2 * C::N, row_step = (uint32_t)H * row_bytes;
-    auto row_of = [&](int p, const void* q) {
-        const int b = p * C::RPI;
-        const uint32_t bytes = row_bytes + (C::RPI == 2 && b + 1 < B ? row_step : 0u);
-        return make_rsrc(reinterpret_cast<const char*>(q) + ((size_t)b * H + h) * row_bytes, bytes);
-    };
+    const int p0 = split * NWV + wave;
+    const int64_t o0 = (int64_t)p0 * C::RPI * row_step + (int64_t)h * row_bytes, step = (int64_t)pstep * C::RPI * row_step;
+    const char* pdy = reinterpret_cast<const char*>(q.dy) + o0;
+    const char* pu = reinterpret_cast<const char*>(q.u) + o0;
+    const char* pg = reinterpret_cast<const char*>(q.g) + o0;
+    char* pdu = reinterpret_cast<char*>(q.du) + o0;
+    char* pdg = reinterpret_cast<char*>(q.dg) + o0;
     uint32_t off[4];
     word_offsets<LG>(off, 0, lane, pad, row_step);
-    uint32_t dn[4], un[4];
+    uint32_t wd[4], wu[4], gn[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) dn[r] = un[r] = 0u;
-    auto load = [&](int p) {
-        const rsrc_t rd = row_of(p, dy), ru = row_of(p, u);
+    for (int r = 0; r < 4; ++r) wd[r] = wu[r] = gn[r] = 0u;
+    auto bytes_of = [&](int p) { return C::RPI == 2 && p != odd ? row_bytes + row_step : row_bytes; };
+    auto load = [&](const char*& ptr, int p, uint32_t (&w)[4]) {
+        const rsrc_t d = make_rsrc(ptr, p < npass ? bytes_of(p) : 0u);      // (an empty descriptor where there is no row)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dn[r] = buf_load(rd, off[r]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) un[r] = buf_load(ru, off[r]);
+        for (int r = 0; r < 4; ++r) w[r] = buf_load(d, off[r]);
+        ptr += step;
     };
-    const int p0 = split * NWV + wave;
-    if (p0 < npass) load(p0);
+    auto load_all = [&](int p) {
+        load(pdy, p, wd);
+        load(pu, p, wu);
+        if (GATE) load(pg, p, gn);
+    };
+    load_all(p0);
     RK<LG> K;
-    load_consts<LG>(K, tab, 0, lane);
+    load_consts<LG>(K, q.tab, 0, lane);
     H8U kk[NS];
     int es = 0;
     if (DU) {
-        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(q.kspec) + (size_t)h * 2 * C::N);
 #pragma unroll
         for (int k = 0; k < NS; ++k) kk[k].u = ks[k * 64 + lane];
-        es = spec_exp_of(kspec, H, 2 * C::N)[h];
+        es = spec_exp_of(q.kspec, H, 2 * C::N)[h];
     }
     uint32_t* xd = xbuf + (C::TC == 1 ? 0 : wave * 2 * C::XW);
     uint32_t* xu = xd + C::XW;
-    const int xwo = C::TC == 1 ? 0 : x * 16 + 4 * y, xpo = C::TC == 1 ? 0 : p2_base<LG>(0, lane);
+    const int xwo = C::TC == 1 ? 0 : 4 * lane, xpo = C::TC == 1 ? 0 : p2_base<LG>(0, lane);
     float2 acc[NS][4];
 #pragma unroll
     for (int k = 0; k < NS; ++k)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[k][j] = make_float2(0.f, 0.f);
+    arrived(K);
+    if (DU) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) arrived(kk[k].v);
+    }
     float dsum = 0.f;
     int eref = EXP_NONE;
-    for (int p = p0; p < npass; p += pstep) {
-        uint32_t wd[4], wu[4];
+    int eda = 0, edb = 0, eua = 0, eub = 0, epa = 0, epb = 0;      // exponents (bf16) of the pass's row(s), and of their products
+    uint32_t gy[4] = {0u, 0u, 0u, 0u};                   // dy's own words (gated layer)
+    auto iter = [&](auto mode, int p) {
+        using M = decltype(mode);
+        h4 od[2], ou[2];
+        f4 wr[2], wi[2], yr[2], yi[2], v[2];
+        H8U m[2], n[2];
+        uint32_t wy[4];
+        phase1_ops<LG, IO, M::scaled>(wd, eda, edb, lane, od);
+        phase1_ops<LG, IO, M::scaled>(wu, eua, eub, lane, ou);
+        if (GATE) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) { wd[r] = dn[r]; wu[r] = un[r]; }
-        if (p + pstep < npass) load(p + pstep);
-        int ed[2] = {0, 0}, eu[2] = {0, 0}, ep[2] = {0, 0};
+            for (int r = 0; r < 4; ++r) wy[r] = gy[r];
+        }
+        load_all(p + pstep);
+        SCHED_FENCE();                                  // (the loads go out here)
+        if constexpr (BF && M::scaled) acc_align<NS>(acc, eref, C::TC == 1 ? max(epa, epb) : epa);
+        phase1<LG>(od, K, xd + xwo, wr, wi);
+        phase1<LG>(ou, K, xu + xwo, yr, yi);
+        if constexpr (C::TC > 1) {
+            wave_lds_fence();
+            phase2_read<LG>(xd + xpo, m);
+            phase2_read<LG>(xu + xpo, n);
+            phase2_fwd<LG>(m, K, wr, wi);
+            phase2_fwd<LG>(n, K, yr, yi);
+        }
+        if (DU) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const h2 kw = kk[k % NS].c[r];
+                    m[k].w[r] = C::TC == 1 ? cmul_pack_conj(wr[k][r], wi[k][r], kw) : cmul_swap<true>(wr[k][r], wi[k][r], kw);
+                    if (GATE) n[k].w[r] = C::TC == 1 ? cmul_pack(yr[k][r], yi[k][r], kw) : cmul_swap<false>(yr[k][r], yi[k][r], kw);
+                }
+            if constexpr (C::TC > 1) {
+                phase2_inv<LG>(xd + xpo, K, m);
+                if (GATE) phase2_inv<LG>(xu + xpo, K, n);
+                wave_lds_fence();
+                phase3_read<LG>(xd + xwo, m);
+                if (GATE) phase3_read<LG>(xu + xwo, n);
+            }
+            phase3<LG>(m, K, v);
+            rsrc_t d = make_rsrc(pdu, bytes_of(p));
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                buf_store(d, off[r], out_word<IO, M::scaled>(v[0][r], v[1][r], es + (C::TC == 1 && (lane & 8) ? edb : eda)));
+            pdu += step;
+            if (GATE) {
+                phase3<LG>(n, K, v);
+                d = make_rsrc(pdg, bytes_of(p));
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    buf_store(d, off[r], out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(wy[r]), v[1][r] * hi_of<IO>(wy[r]),
+                                                                 es + (C::TC == 1 && (lane & 8) ? eub : eua)));
+                pdg += step;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (!DU) round_h2(yr[k], yi[k]);
+            // N = 256: tile k is row k and both add to the same bins
+            const int epk = C::TC == 1 && k == 1 ? epb : epa;
+            acc_tile<BF && M::scaled>(acc[k % NS], yr[k], yi[k], wr[k], wi[k], min(epk - eref, 0));
+        }
+    };
+    // the pass has arrived: gate, dot product, exponents; is anything scaled?
+    auto prep = [&]() {
+        if (GATE) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) gy[r] = wd[r];
+            dsum = gate_words<IO>(wd, gn, wu, dsum);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(wd[r], wu[r], dsum);
+        }
         if constexpr (BF) {
             uint32_t md[C::RPI], mu_[C::RPI];
             words_max<C::RPI>(wd, md);
             words_max<C::RPI>(wu, mu_);
-#pragma unroll
-            for (int k = 0; k < C::RPI; ++k) {
-                ed[k] = row_exponent(md[k]);
-                eu[k] = row_exponent(mu_[k]);
-                ep[k] = md[k] && mu_[k] ? ed[k] + eu[k] : EXP_NONE;
+            eda = row_exponent(md[0]);
+            eua = row_exponent(mu_[0]);
+            epa = md[0] && mu_[0] ? eda + eua : EXP_NONE;
+            if constexpr (C::RPI == 2) {
+                edb = row_exponent(md[1]);
+                eub = row_exponent(mu_[1]);
+                epb = md[1] && mu_[1] ? edb + eub : EXP_NONE;
             }
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(wd[r], wu[r], dsum);
-        h4 op[2];
-        f4 wr[2], wi[2], yr[2], yi[2], v[2];
-        H8U m[2];
-        phase1_ops<LG, IO>(wd, ed[0], ed[1], lane, op);
-        phase1<LG>(op, K, xd + xwo, wr, wi);
-        phase1_ops<LG, IO>(wu, eu[0], eu[1], lane, op);
-        phase1<LG>(op, K, xu + xwo, yr, yi);
-        if constexpr (C::TC > 1) {
-            wave_lds_fence();
-            phase2_fwd<LG>(xd + xpo, K, wr, wi);
-            phase2_fwd<LG>(xu + xpo, K, yr, yi);
+        return (es | eda | edb | eua | eub) != 0 || (BF && (epa != eref || (C::RPI == 2 && epb != eref)));
+    };
+    for (int p = p0; p < npass;) {
+        bool scaled = prep();
+        while (!scaled) {
+            iter(Mode<true, false>{}, p);
+            p += pstep;
+            if (p >= npass) break;
+            scaled = prep();
         }
-        if (DU) {
-            if constexpr (C::TC == 1) {
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_pack_conj(wr[k][r], wi[k][r], kk[0].c[r]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_swap<true>(wr[k][r], wi[k][r], kk[k % NS].c[r]);
-                phase2_inv<LG>(xd + xpo, K, m);
-                wave_lds_fence();
-            }
-            phase3<LG>(xd + xwo, m, K, v);
-            uint32_t o[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = pack_io<IO>(v[0][r], v[1][r]);
-            if (__builtin_expect((es | ed[0] | ed[1]) != 0, 0)) {
-                const int ex = es + (C::TC == 1 && (lane & 8) ? ed[1] : ed[0]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = out_rescaled<BF>(o[r], ex);
-            }
-            const rsrc_t d = row_of(p, du);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) buf_store(d, off[r], o[r]);
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            int down = 0;
-            // N = 256: tile k is row k and both add to the same bins; otherwise one exponent for the row's two tiles
-            if constexpr (BF) down = C::TC == 1 || k == 0 ? acc_align<NS>(acc, eref, ep[C::TC == 1 ? k : 0]) : (ep[0] < eref ? ep[0] - eref : 0);
-            if (!DU) round_h2(yr[k], yi[k]);
-            acc_tile(acc[k % NS], yr[k], yi[k], wr[k], wi[k], down);
-        }
+        if (p >= npass) break;
+        iter(Mode<true, true>{}, p);
+        p += pstep;
     }
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
@@ -1235,8 +1410,8 @@ rbwd1_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __rest
     const int etop = acc_reduce<NS, 1, NWV, BF>(acc, eref, red, erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
     if (wave != 0) return;
-    if (lane == 0 && dD) dD[ho] = ((dred[0] + dred[1]) + dred[2]) + dred[3];
-    if (!dk) return;
+    if (lane == 0 && q.dD) q.dD[ho] = ((dred[0] + dred[1]) + dred[2]) + dred[3];
+    if (!q.dk) return;
     H8U m[2];
     f4 v[2];
 #pragma unroll
@@ -1249,16 +1424,17 @@ rbwd1_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __rest
     if constexpr (C::TC > 1) {
         phase2_inv<LG>(xd + xpo, K, m);
         wave_lds_fence();
+        phase3_read<LG>(xd + xwo, m);
     }
-    phase3<LG>(xd + xwo, m, K, v);
+    phase3<LG>(m, K, v);
     const uint32_t kb = (pad ? C::N / 2 : C::N) * 4u;
-    const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(dk) + ho * kb, kb);
+    const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(q.dk) + ho * kb, kb);
     word_offsets<LG>(off, 0, lane, pad, NOWHERE);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-        const u2v q = {__float_as_uint(ldexpf(v[0][r] * dkscale, etop)), __float_as_uint(ldexpf(v[1][r] * dkscale, etop))};
-        __builtin_amdgcn_raw_buffer_store_b64(q, d, (int)((off[r] & NOWHERE) ? NOWHERE : 2u * off[r]), 0, 0);
+        const u2v o = {__float_as_uint(ldexpf(v[0][r] * q.dkscale, etop)), __float_as_uint(ldexpf(v[1][r] * q.dkscale, etop))};
+        __builtin_amdgcn_raw_buffer_store_b64(o, d, (int)((off[r] & NOWHERE) ? NOWHERE : 2u * off[r]), 0, 0);
     }
 }
 
@@ -1312,30 +1488,25 @@ hipError_t rkspec_go(const float* k, const float* D, float2* kspec, int64_t H, f
     hipLaunchKernelGGL((rkspec_kernel<LG>), dim3((unsigned)H), dim3(RC<LG>::NWR * 64), 0, st, k, D, kspec, (int)H, kscale, pad, tab);
     return hipGetLastError();
 }
-template <int LG, class IO, bool DU>
-hipError_t rbwd_run(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
-                    const Problem& pr, const Plan& pl, const uint4* tab, hipStream_t st)
+template <int LG, class IO, bool DU, bool GATE>
+hipError_t rbwd_run(const BwdArgs<typename IO::T>& a, hipStream_t st)
 {
-    using T = typename IO::T;
     if constexpr (RC<LG>::NWR > 1) {
-        using Q = BwdCfg<LG>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rbwd_kernel<LG, IO, DU>),
+        using Q = BwdCfg<LG, GATE>;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rbwd_kernel<LG, IO, DU, GATE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q::lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((rbwd_kernel<LG, IO, DU>), dim3((unsigned)(pr.H * nsplit)), dim3(Q::NWV * 64), Q::lds, st, (const T*)dy,
-                           (const T*)u, kspec, (T*)du, dk, dD, (int)pr.B, (int)pr.H, nsplit, pl.dkscale, pr.pad, tab);
+        hipLaunchKernelGGL((rbwd_kernel<LG, IO, DU, GATE>), dim3((unsigned)(a.H * a.nsplit)), dim3(Q::NWV * 64), Q::lds, st, a);
     } else {
-        hipLaunchKernelGGL((rbwd1_kernel<LG, IO, DU>), dim3((unsigned)(pr.H * nsplit)), dim3(256), 0, st, (const T*)dy,
-                           (const T*)u, kspec, (T*)du, dk, dD, (int)pr.B, (int)pr.H, nsplit, pl.dkscale, pr.pad, tab);
+        hipLaunchKernelGGL((rbwd1_kernel<LG, IO, DU, GATE>), dim3((unsigned)(a.H * a.nsplit)), dim3(256), 0, st, a);
     }
     return hipGetLastError();
 }
 template <int LG, class IO>
-hipError_t rbwd_go(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
-                   const Problem& pr, const Plan& pl, const uint4* tab, hipStream_t st)
+hipError_t rbwd_go(const BwdArgs<typename IO::T>& a, hipStream_t st)
 {
-    return du ? rbwd_run<LG, IO, true>(dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st)
-              : rbwd_run<LG, IO, false>(dy, u, nullptr, nullptr, dk, dD, nsplit, pr, pl, tab, st);
+    if (a.g) return a.du && a.dg ? rbwd_run<LG, IO, true, true>(a, st) : hipErrorInvalidValue;
+    return a.du ? rbwd_run<LG, IO, true, false>(a, st) : rbwd_run<LG, IO, false, false>(a, st);
 }
 
 #define ROWS_SWITCH(lg, FN, ...)                                  \
@@ -1409,19 +1580,22 @@ hipError_t rows_conv(const void* in, const float2* kspec, void* out, bool conj, 
     return hipErrorInvalidValue;
 }
 template <class IO>
-static hipError_t bwd_io(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+static hipError_t bwd_io(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, void* dg, int nsplit,
                          const Problem& pr, const Plan& pl, const uint4* tab, hipStream_t st)
 {
+    using T = typename IO::T;
+    const BwdArgs<T> a = {(const T*)dy, (const T*)u, (const T*)pr.gate, kspec, (T*)du, (T*)dg, dk, dD, (int)pr.B, (int)pr.H, nsplit,
+                          pl.dkscale, pr.pad, tab};
 #define RF(L) rbwd_go<L, IO>
-    ROWS_SWITCH(pl.order.wave_lg, RF, (dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st))
+    ROWS_SWITCH(pl.order.wave_lg, RF, (a, st))
 #undef RF
 }
-hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, void* dg, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     const uint4* tab = (const uint4*)tb.rtab;
-    if (pr.io == LONGCONV_F16) return bwd_io<IoF16>(dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st);
-    if (pr.io == LONGCONV_BF16) return bwd_io<IoBF16>(dy, u, kspec, du, dk, dD, nsplit, pr, pl, tab, st);
+    if (pr.io == LONGCONV_F16) return bwd_io<IoF16>(dy, u, kspec, du, dk, dD, dg, nsplit, pr, pl, tab, st);
+    if (pr.io == LONGCONV_BF16) return bwd_io<IoBF16>(dy, u, kspec, du, dk, dD, dg, nsplit, pr, pl, tab, st);
     return hipErrorInvalidValue;
 }
 

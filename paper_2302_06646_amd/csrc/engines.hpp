@@ -148,7 +148,8 @@ hipError_t rows_conv(const void* in, const float2* kspec, void* out, bool conj, 
 // rows of a head are dealt to nsplit workgroups, dk and dD then point to partial buffers [nsplit][H][N] and [nsplit][H]
 // that sum_partials() adds up in share order.
 int rows_bwd_nsplit(int64_t B, int64_t H, int lg);
-hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+// With Problem::gate: the gated layer's backward pass (du and dg both given), dg = dy (ungated output).
+hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, void* dg, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 
 // ---- cooperative chained matrix-core kernels for 2^13 <= L2 <= 2^15 (engine_coop.hip) --------
