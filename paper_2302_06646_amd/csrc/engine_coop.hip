@@ -902,6 +902,255 @@ __device__ __forceinline__ int chunk_run_n(int r)
     return (da << (C::cb + 4)) + (db << C::cb) + 4 * q;
 }
 
+// -------------------------------------------------------------------------------------
+// Single rows of N = L = 32768 samples, forward and du: one N-point transform of the twisted row
+//     X[f] = sum_n x[n] exp(-2 pi i n (4 f + 1) / 4N),
+// whose products are convolutions modulo z^N - i; the real part, untwisted, is the causal convolution truncated to N
+// samples (see engine_rows.hip).  The row's transform fits one compute unit, so rows go from memory to memory in one
+// kernel.  (As row pairs in two chunks of a 65536-point transform the same matrix work needs a complex fp16 workspace
+// of twice the rows' bytes written, and read back by a pass C kernel, and has two chunks where an odd last row needs one.)
+// B=32, H=128, N=32768 fp16: 670 us as pairs in two chunks, 311 us here (1.7 TB/s); what is left is matrix and vector issue.
+// The twist W^n, W = exp(-2 pi i / 4N), n = d_a 16 TC + d_b TC + t, takes no instructions: its d_a factor sits in the
+// matrices over d_a of both directions, its d_b factor in the lanes' w_256 constants and its t factor in the w_L table,
+// which phases 1 and 3 (conjugated) share.  Staging, prefetch and the band test are those of coop_conv_real_kernel.
+// -------------------------------------------------------------------------------------
+template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
+__global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
+coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec,
+                     typename IO::T* __restrict__ out, const typename IO::T* __restrict__ gate, int64_t B, int64_t H,
+                     int per, const float2* __restrict__ tw, const unsigned char* __restrict__ ctab)
+{
+    using C = CC<LG>;
+    constexpr int NT = NWV * 64;
+    constexpr int RPL = (C::L / 8) / NT;             // 16-byte runs (8 samples) of the row per lane
+    static_assert(RPL * NT * 8 == C::L, "runs must tile the row");
+    extern __shared__ uint4 lds4[];
+    uint32_t* xb = reinterpret_cast<uint32_t*>(lds4);
+    uint4* t1f = lds4 + C::XWORDS / 4;
+    uint4* t1i = t1f + C::TC * 4;
+    uint32_t* vt = reinterpret_cast<uint32_t*>(t1i + C::TC * 4);      // [TC][16]: w_L^(k_a t) W^t
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, g = lane >> 4;
+    const unsigned G = gridDim.x;
+    const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
+    // work items (head, row), `per` consecutive ones per workgroup (a head's rows share its spectrum)
+    const int nrow = (int)B, total = (int)H * nrow;
+    const int it0 = (int)vid * per, it1 = it0 + per < total ? it0 + per : total;
+    const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
+
+    auto run_n = [&](int i) { return staged_run_n<LG>(i * NT + tid); };
+    uint4 pa[RPL];
+    auto fetch = [&](int it) {
+        const size_t o = row_off(it % nrow, it / nrow, H, C::L);
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) pa[i] = *reinterpret_cast<const uint4*>(in + o + run_n(i));
+    };
+    if (it0 < it1) fetch(it0);       // first row on its way while the constants are built
+
+    Consts<LG> K;
+    make_consts<LG>(K, tw, lane);
+    const Mats F1 = phase_mats(1, C::cb + 4, LG + 2, tw, lane);
+    h8 I3;                           // conjugate of the same entries, real part of the product only; d_a on the lanes
+    h2 c1[4], c3[4];                 // w_256^(k_a d_b) W^(d_b TC): d_b = 4g+j in phase 1, d_b = c in phase 3
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t y = (uint32_t)(4 * g + j);
+        const float2 a = tw_full(tw, ((((c * y) & 15u) << (TW_LOG2 - 4)) + ((uint32_t)c << (TW_LOG2 - 6))) & (TW_L - 1));
+        I3[2 * j] = (_Float16)(a.x * 0.25f);
+        I3[2 * j + 1] = (_Float16)(a.y * 0.25f);
+        const uint32_t b = ((c * y) & 255u) << (TW_LOG2 - 8);
+        const float2 w1 = tw_full(tw, (b + (y << (TW_LOG2 - 10))) & (TW_L - 1));
+        const float2 w3 = tw_full(tw, (b + ((uint32_t)c << (TW_LOG2 - 10))) & (TW_L - 1));
+        c1[j] = h2{(_Float16)w1.x, (_Float16)w1.y};
+        c3[j] = h2{(_Float16)w3.x, (_Float16)w3.y};
+    }
+    int ng = C::TC / (8 * NWV);
+    asm volatile("" : "+s"(ng));
+    const int w1 = (c * C::PITCH + g * C::TC) * 4;
+
+    // bf16 rows outside the band are scaled by a power of two, as in coop_conv_real_kernel
+    __shared__ uint32_t dr_mx[NWV];
+    auto measure = [&]() {
+        uint32_t m[1] = {0u};
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+            m[0] = absmax_acc(absmax_acc(absmax_acc(absmax_acc(m[0], pa[i].x), pa[i].y), pa[i].z), pa[i].w);
+        band_or_exact<1>(m);
+        if (lane == 0) dr_mx[wave] = m[0];
+    };
+    auto stage = [&](int ea) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            uint32_t wa[4] = {pa[i].x, pa[i].y, pa[i].z, pa[i].w};
+            if (IsBf<IO>::v) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) wa[m] = __builtin_expect(ea != 0, 0) ? bf2_to_h2_scaled(wa[m], ea) : bf2_to_h2(wa[m]);
+            }
+            const int a0 = staged_slot<LG>(run_n(i));
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                xb[a0 + 8 * m] = wa[m] & 0xffffu;
+                xb[a0 + 8 * m + 4] = wa[m] >> 16;
+            }
+        }
+    };
+    auto drain = [&](int it, int ea) {
+        const size_t o = row_off(it % nrow, it / nrow, H, C::L);
+        uint4 ga[GATE ? RPL : 1];
+        if constexpr (GATE) {
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) ga[i] = *reinterpret_cast<const uint4*>(gate + o + run_n(i));
+        }
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            const int n = run_n(i), a0 = staged_slot<LG>(n);
+            uint32_t wa[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                wa[m] = __builtin_amdgcn_perm(xb[a0 + 8 * m + 4], xb[a0 + 8 * m], 0x05040100u);
+                uint32_t gw = 0u;
+                if constexpr (GATE) gw = m == 0 ? ga[i].x : (m == 1 ? ga[i].y : (m == 2 ? ga[i].z : ga[i].w));
+                union { uint32_t u; h2 h; } a, q;
+                a.u = wa[m];
+                if (IsBf<IO>::v) {
+                    float x0 = (float)a.h[0], x1 = (float)a.h[1];
+                    if constexpr (GATE) {
+                        x0 *= __uint_as_float(gw << 16);
+                        x1 *= __uint_as_float(gw & 0xffff0000u);
+                    }
+                    wa[m] = pack_bf2(x0, x1);
+                } else if constexpr (GATE) {
+                    q.u = gw;
+                    a.h = a.h * q.h;
+                    wa[m] = a.u;
+                }
+            }
+            if (__builtin_expect(ea != 0, 0)) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
+            }
+            store_words<4>(out + o + n, wa);
+        }
+    };
+
+    staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
+    for (int i = tid; i < C::TC * 16; i += NT) {         // (a lane rewrites the entries it wrote itself)
+        const uint32_t t = (uint32_t)i >> 4;
+        const float2 w = tw_full(tw, (((((uint32_t)i & 15u) * t) << (TW_LOG2 - LG)) + (t << (TW_LOG2 - LG - 2))) & (TW_L - 1));
+        vt[i] = pack_h2(w.x, w.y);
+    }
+    __syncthreads();
+    if (it0 < it1) {
+        if constexpr (IsBf<IO>::v) measure();
+        stage(0);
+    }
+    for (int it = it0; it < it1; ++it) {
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) +
+                                                         (size_t)(it / nrow) * C::L);
+        asm volatile("" : "+s"(ks));
+        __syncthreads();             // staged row visible
+        int ea = 0;
+        if constexpr (IsBf<IO>::v) {
+            uint32_t ma = 0u;
+#pragma unroll
+            for (int w = 0; w < NWV; ++w) ma = max(ma, dr_mx[w]);
+            ma = (uint32_t)__builtin_amdgcn_readfirstlane((int)ma);
+            if (__builtin_expect(!rows_in_band(ma, ma), 0)) {
+                int eb = 0;
+                pair_exponents(ma, 0u, ea, eb);
+                if (ea != 0) {
+                    stage(ea);
+                    __syncthreads();
+                }
+            }
+        }
+        const bool more = it + 1 < it1;
+        if (more) fetch(it + 1);     // phases 1 to 3 cover the transfer
+
+        // ---- phase 1, in place
+#pragma unroll 1
+        for (int gi = 0; gi < ng; ++gi)
+            phase1_inplace<LG, NB>(xb, t1f, vt, F1, K.F16, c1, (gi * NWV + wave) * 8, lane);
+        __syncthreads();
+        asm volatile("" : "+s"(ks));
+
+        // ---- phase 2
+#pragma unroll 1
+        for (int gi = 0; gi < ng; ++gi)
+#pragma unroll
+        for (int tb = 0; tb < 8; tb += NB) {
+            const int t0 = (gi * NWV + wave) * 8;
+            int base[NB];
+            f4 zr[NB], zi[NB];
+            H8U kk[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const int t2 = t0 + tb + k;
+                base[k] = phase2_base<LG>(t2, lane);
+                kk[k].u = ks[t2 * 64 + lane];
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) phase2_fwd<LG>(xb, base[k], K, zr[k], zi[k]);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                H8U m;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)      // correlation (du): the conjugate spectrum
+                    m.w[j] = CONJ ? cmul_pack_conj(zr[k][j], zi[k][j], kk[k].c[j])
+                                  : cmul_pack(zr[k][j], zi[k][j], kk[k].c[j]);
+                phase2_inv<LG>(xb, base[k], K, m);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+
+        // ---- phase 3, in place, real part only: samples (d_a, d_b) = (4g+j, c) of each tile
+#pragma unroll 1
+        for (int gi = 0; gi < ng; ++gi) {
+            const int t0 = (gi * NWV + wave) * 8;
+            const f4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int tb = 0; tb < 8; tb += 2) {
+                H8U tw1[2], x[2], vv[2];
+                f4 yr[2], yi[2], r[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int t = t0 + tb + k;
+                    tw1[k].u = t1i[t * 4 + g];
+                    x[k].u = *reinterpret_cast<const uint4*>(&xb[w1 + 4 * t]);
+                    vv[k].u = *reinterpret_cast<const uint4*>(&vt[t * 16 + 4 * g]);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[k].w[j] = cmul_h2(x[k].w[j], tw1[k].c[j]);
+                    yr[k] = MFMA(x[k].v, K.I16.re, zero);
+                    yi[k] = MFMA(x[k].v, K.I16.im, zero);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    H8U u;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) u.w[j] = cmul_pack_conj(yr[k][j], yi[k][j], cmul_hh(c3[j], vv[k].c[j]));
+                    r[k] = MFMA(I3, u.v, zero);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) =
+                        make_uint4(pack_h2(r[k][0], 0.f), pack_h2(r[k][1], 0.f), pack_h2(r[k][2], 0.f), pack_h2(r[k][3], 0.f));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+        const int es = __builtin_amdgcn_readfirstlane(spec_exp_of(kspec, H, 2 * (int64_t)C::L)[it / nrow]);
+        drain(it, ea + es);          // (the lane that drains a slot stages the next row's sample there)
+        if (more) {
+            if constexpr (IsBf<IO>::v) measure();
+            stage(0);
+        }
+    }
+}
+
 template <int LG, class IO, int NWV, int NB, bool CONJ, int FUSEA>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, __half2* __restrict__ ws,
@@ -1881,6 +2130,8 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
                        const float2* __restrict__ tw, const unsigned char* __restrict__ ctab)
 {
     using C = CC<LG>;
+    // LR = 1: the row's single transform of coop_conv_row_kernel, which is chunk 1 of a split four wide (twist w_{4N}^n)
+    constexpr int LT = LR == 1 ? 2 : LR, LCH = LR == 1 ? 0 : LR;      // outer radix of the twist, chunks per head (log2)
     constexpr int NT = C::NW * 64, RH = LR ? (1 << LR) / 2 : 1;
     constexpr int NROW = LR ? RH * C::L : C::L / 2;      // samples of a row
     constexpr int RPA = (C::L / 8) / NT;                 // runs of eight samples per lane
@@ -1894,7 +2145,7 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     const int c = lane & 15, g = lane >> 4;
     const unsigned G = gridDim.x;
     const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
-    const int h = (int)(vid >> LR), k1 = (int)(vid & ((1u << LR) - 1u));
+    const int h = (int)(vid >> LCH), k1 = LR == 1 ? 1 : (int)(vid & ((1u << LR) - 1u));
     const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
     const float* kr = k + (size_t)h * NROW;
 
@@ -1967,8 +2218,8 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
             const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
             cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
         }
-        F1 = LR ? phase_mats(k1, C::cb + 4, LG + LR, tw, lane) : K.F16;
-        F2 = LR ? phase_mats(k1, C::cb, LG + LR, tw, lane) : K.F16;
+        F1 = LR ? phase_mats(k1, C::cb + 4, LG + LT, tw, lane) : K.F16;
+        F2 = LR ? phase_mats(k1, C::cb, LG + LT, tw, lane) : K.F16;
     };
 
     float r;
@@ -1979,7 +2230,7 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
 #pragma unroll
         for (int i = 0; i < RPA; ++i) load_run(v[i], i);
         staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-        if (LR) twisted_t1f<LG, LR, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
+        if (LR) twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
         make_operands();
         float m = 0.f;
 #pragma unroll
@@ -2010,7 +2261,7 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
             a = rs[Hh + h];
             mp = rs[2 * Hh + h];
         }
-        twisted_t1f<LG, LR, NT>(t1f, gtab, k1, tw, tid);
+        twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);
 #pragma unroll
         for (int i0 = 0; i0 < RPA; i0 += 2) {
             float4 v[2][RH][2];
@@ -2026,9 +2277,9 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     for (int gi = 0; gi < C::NG; ++gi) phase1_inplace<LG, 2>(xb, t1f, vt, F1, F2, cF, (gi * C::NW + wave) * 8, lane);
     __syncthreads();
     const int es = spec_exponent(kscale * a, kscale * mp);
-    if (k1 == 0 && tid == 0) spec_exp_of(kspec, G >> LR, (int64_t)C::L << LR)[h] = es;
+    if (k1 == (LR == 1) && tid == 0) spec_exp_of(kspec, G >> LCH, (int64_t)C::L << LR)[h] = es;
     const float alpha = ldexpf(kscale_over_c / r, -es), beta = ldexpf(Dh * kscale, -es);
-    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (((size_t)h << LR) + k1) * C::L);
+    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (((size_t)h << LCH) + (LR == 1 ? 0 : k1)) * C::L);
 #pragma unroll 1
     for (int gi = 0; gi < C::NG; ++gi)
 #pragma unroll
@@ -2069,6 +2320,23 @@ hipError_t coop_conv_real_go(const void* in, const float2* kspec, void* out, con
     return hipGetLastError();
 }
 
+template <int LG, class IO, bool CONJ, bool GATE>
+hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, const Problem& pr, const Tables& tb,
+                            hipStream_t st)
+{
+    using T = typename IO::T;
+    constexpr int NWV = CC<LG>::NW;
+    const auto kern = coop_conv_row_kernel<LG, IO, NWV, NTB, CONJ, GATE>;
+    const size_t lds = coop_real_lds_bytes<LG>();
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const long total = pr.H * pr.B;                      // (head, row) items; the row fills a compute unit's LDS
+    const int cus = compute_units(), per = (int)((total + cus - 1) / cus);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + per - 1) / per)), dim3(NWV * 64), lds, st, (const T*)in, kspec, (T*)out,
+                       (const T*)pr.gate, pr.B, pr.H, per, tb.tw, (const unsigned char*)tb.ctab);
+    return hipGetLastError();
+}
+
 template <int LG, class IO>
 hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
                         const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
@@ -2080,6 +2348,14 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2*
                         : coop_conv_real_go<LG, IO, NWV, NB, false, true>(in, kspec, out, pr, tb, st);
         return conj ? coop_conv_real_go<LG, IO, NWV, NB, true, false>(in, kspec, out, pr, tb, st)
                     : coop_conv_real_go<LG, IO, NWV, NB, false, false>(in, kspec, out, pr, tb, st);
+    }
+    if constexpr (LG == COOP_MAX_LOG2) {
+        if (pl.row1) {
+            if (pr.gate)
+                return conj ? hipErrorInvalidValue : coop_conv_row_go<LG, IO, false, true>(in, kspec, out, pr, tb, st);
+            return conj ? coop_conv_row_go<LG, IO, true, false>(in, kspec, out, pr, tb, st)
+                        : coop_conv_row_go<LG, IO, false, false>(in, kspec, out, pr, tb, st);
+        }
     }
     // multi-pass: the inner convolution on pass A's workspace, or (fuse_a) on the rows themselves
     using T = typename IO::T;
@@ -2104,11 +2380,8 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2*
                            (const unsigned char*)tb.ctab, fuse_a ? pr.max_a : nullptr);
         return hipGetLastError();
     };
-    static int res[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    static int res[6] = {0, 0, 0, 0, 0, 0};
     if constexpr (LG == COOP_MAX_LOG2) {
-        if (fuse_a && pl.log2R == 1)
-            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 1>, res[6])
-                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 1>, res[7]);
         if (fuse_a && pl.log2R == 2)
             return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 2>, res[2])
                         : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 2>, res[3]);
@@ -2196,13 +2469,13 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(H << pl.log2R)), dim3(C::NW * 64), lds_rows, st, k, D,
+        hipLaunchKernelGGL(kern, dim3((unsigned)(pl.row1 ? H : H << pl.log2R)), dim3(C::NW * 64), lds_rows, st, k, D,
                            pl.log2R == 3 ? rs : nullptr, kspec, koc, pl.kscale, tb.tw, (const unsigned char*)tb.ctab);
         return hipGetLastError();
     };
     if (pl.log2R == 0) return launch_rows(coop_kspec_rows_kernel<LG, 0>);
     if constexpr (LG == COOP_MAX_LOG2) {      // pass A inside
-        if (pl.fuse_a && pl.log2R == 1) return launch_rows(coop_kspec_rows_kernel<LG, 1>);
+        if (pl.row1) return launch_rows(coop_kspec_rows_kernel<LG, 1>);
         if (pl.fuse_a && pl.log2R == 2) return launch_rows(coop_kspec_rows_kernel<LG, 2>);
         if (pl.fuse_a && pl.log2R == 3) return launch_rows(coop_kspec_rows_kernel<LG, 3>);
     }

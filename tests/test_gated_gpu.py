@@ -58,6 +58,12 @@ def test_gated_layer_against_the_oracle(N, io):
     assert errs
 
 
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+def test_gated_rows_of_32768_samples(io):
+    # the gate in the store of the single-row kernel (forward, and dg as the forward pass gated by dy)
+    test_gated_layer_against_the_oracle(32768, io)
+
+
 def test_optional_outputs_and_error_codes():
     inp, g_s, g_v = _inputs(1024, wl.BF16, 2, 2)
     y, du, dk, dD, dg = _run(inp, g_s, want_du=False, want_dk=False, want_dD=False)

@@ -227,3 +227,28 @@ def test_fp32_engine_every_length(N, B, H):
     dk1, dD1 = g.bwd(du=False)[1:]
     assert np.array_equal(dk1, dk) and np.array_equal(dD1, dD)
     assert wl.rel_l2(g.bwd(dk=False, dD=False)[0], du) < 1e-6
+
+
+@pytest.mark.parametrize("io,B,H", [(wl.F16, 1, 1), (wl.BF16, 3, 2), (wl.BF16, 5, 61)])
+def test_single_rows_of_32768_samples(io, B, H):
+    # one twisted transform per row: the only row of the call; an odd count with rows outside the bf16 band (each row is
+    # scaled by itself, so each meets the tolerance by itself); more rows than compute units, where a workgroup takes
+    # several, of two heads, and the last workgroup is short
+    import oracle
+    from gpu_harness import TOL, GpuRun, _compare, check_full, check_sampled
+    inp = wl.generate(wl.Workload(6, B, H, 32768, io, "decay_alpha_squash"))
+    if B == 3:
+        s = 2.0 ** np.array([-40, 0, 12])[:, None, None]        # powers of two: exact in bf16
+        for name in ("u", "dy"):
+            x = getattr(inp, name) * s
+            st, x = wl.quantize(x.astype(np.float32), io)
+            setattr(inp, name, x), setattr(inp, name + "_store", st)
+    if B == 3:
+        check_full(inp, backward=False, label="single rows")
+        du = GpuRun(inp).bwd(dk=False, dD=False)[0]
+        want = oracle.longconv_bwd(inp.dy, inp.u, inp.k.astype(np.float64), inp.D.astype(np.float64))[0]
+        _compare({"du": du}, {"du": want}, TOL[io], "single rows, du alone")
+    elif H <= 2:
+        check_full(inp, label="single rows")
+    else:
+        check_sampled(inp, [0, 31, H - 1], label="single rows")
