@@ -291,6 +291,7 @@ static hipError_t run_conv(const void* in, const float2* kspec, void* out, void*
     if (pl.log2R && !pl.row_lg) {
         Problem pc = pr;     // pass C gives the output the power of two that the stored spectrum left out
         pc.spec_exp = spec_exp_ptr(kspec, pr.H, size_t(1) << pl.log2L, pl);
+        if (fuse_a && rows_split(pl)) return outer_inv_rows(ws1, out, pc, pl.log2L2, tw, st);
         e = outer_inv(ws1, out, pc, pl.log2R, pl.log2L2, 1.0f, f16ws, tw, st,
                       fuse_a && coop_conv_chunks(pr, pl, fuse_a) < (1 << pl.log2R));
     }

@@ -494,13 +494,13 @@ __device__ __forceinline__ void twisted_t1f(uint4* t1f, const uint4* gtab, int k
 // s[n2] = sum_{n1 < R/2} w_R^(n1 k1) z[n1 L + n2], z = a + i b, R = 2^LR, into the exchange slots.  The twist
 // is not applied here (it sits in the phase-1 operands).  One packed fp16 complex multiply-add per term.
 // HASB = false: the pair has no row b (odd batch); twice as many runs are then in flight per round trip.
-template <int LG, class IO, int LR, int NT, bool HASB>
+// RH: terms of the sum (rows of RH L samples; half the outer radix for zero-padded ones).
+template <int LG, class IO, int LR, int NT, bool HASB, int RH = (1 << LR) / 2>
 __device__ __forceinline__ void stage_rows_pass_a_impl(uint32_t* xb, const typename IO::T* ra, const typename IO::T* rb,
                                                        int k1, const float2* __restrict__ tw, int tid, int ex)
 {
     // ex != 0 (bf16 rows of a head whose largest sample lies outside the band 2^-2 .. 2^4): every sample times 2^-ex
     using C = CC<LG>;
-    constexpr int RH = (1 << LR) / 2;
     h2 cr[RH], crs[RH];                              // w_R^(n1 k1) and i times it
 #pragma unroll
     for (int n1 = 1; n1 < RH; ++n1) {
@@ -900,7 +900,12 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
     }
 }
 
-template <int LG, class IO, int NWV, int NB, bool CONJ, int FUSEA>
+// ROWS (outer radix 4): items are single rows of N = 2 L samples, in two chunks of the N-point twisted transform instead
+// of four of a zero-padded one per pair (npairs = B, log2R = 1 as the count of chunks).  Pass C is outer_inv_rows.  Equal work for
+// an even batch and half the spectrum; a single row takes two chunks instead of three, 256 items instead of 384 at
+// H = 128: one round of the device instead of two.
+// B=1, H=128, N=65536 fp16 step: 271 us with pairs, 207 us with rows.
+template <int LG, class IO, int NWV, int NB, bool CONJ, int FUSEA, bool ROWS>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, __half2* __restrict__ ws,
                  int64_t B, int64_t H, int64_t N, int npairs, int log2R, int nch, int total, int per,
@@ -968,15 +973,22 @@ coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict
     // FUSEA: rows of the item -> pass-A sum -> slots; phase-1 operands of the item
     Mats F1 = K.F16, F2 = K.F16;
     auto stage_rows = [&](int it) __attribute__((always_inline)) {
-        constexpr int LR = FUSEA > 0 ? FUSEA : 2;
+        // ROWS: chunk kc of a row is chunk 4 kc + 1 of a split twice as wide (see coop_conv_row_kernel)
+        constexpr int LR = ROWS ? FUSEA + 1 : (FUSEA > 0 ? FUSEA : 2);
         const int hk = it / npairs, p = it - hk * npairs;
-        const int h = hk / nch, k1 = hk - h * nch;
+        const int h = hk / nch, kc = hk - h * nch, k1 = ROWS ? 4 * kc + 1 : kc;
         F1 = phase_mats(k1, C::cb + 4, LG + LR, tw, lane);
         F2 = phase_mats(k1, C::cb, LG + LR, tw, lane);
         twisted_t1f<LG, LR, NT>(t1f, gtab, k1, tw, tid);
-        const bool has_b = (2 * p + 1) < B;
-        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-        stage_rows_pass_a<LG, IO, LR, NT>(xb, in + oa, in + ob, has_b, k1, tw, tid, head_rows_exponent(rows_max, h));
+        const int ex = head_rows_exponent(rows_max, h);
+        if constexpr (ROWS) {
+            const size_t o = row_off(p, h, H, N);
+            stage_rows_pass_a_impl<LG, IO, LR, NT, false, (1 << FUSEA) / 2>(xb, in + o, in + o, k1, tw, tid, ex);
+        } else {
+            const bool has_b = (2 * p + 1) < B;
+            const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
+            stage_rows_pass_a<LG, IO, LR, NT>(xb, in + oa, in + ob, has_b, k1, tw, tid, ex);
+        }
     };
     auto stage_item = [&](int it) __attribute__((always_inline)) {
         if (FUSEA) stage_rows(it);
@@ -1872,15 +1884,16 @@ coop_kspec_kernel(const __half2* __restrict__ ws, const float* __restrict__ D, c
 // and the conversion, one round trip to memory; R = 8: the maximum comes from the caller (rs).
 // Then s[n2] = sum_{n1 < R/2} w_R^(n1 k1) k[n1 L + n2] goes to the exchange slots as fp16 complex, phase 1 runs
 // in place with the twist in its operands, the forward half of phase 2 writes kscale (FFT + D[h]).
-template <int LG, int LR>
+template <int LG, int LR, bool ROWS>
 __global__ void __launch_bounds__(CC<LG>::NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D, const float* __restrict__ rs,
                        float2* __restrict__ kspec, float kscale_over_c, float kscale,
                        const float2* __restrict__ tw, const unsigned char* __restrict__ ctab)
 {
     using C = CC<LG>;
-    // LR = 1: the row's single transform of coop_conv_row_kernel, which is chunk 1 of a split four wide (twist w_{4N}^n)
-    constexpr int LT = LR == 1 ? 2 : LR, LCH = LR == 1 ? 0 : LR;      // outer radix of the twist, chunks per head (log2)
+    // ROWS: the N-point twisted transform of single rows (coop_conv_row_kernel), 2^(LR-1) chunks of which number kc is
+    // chunk 4 kc + 1 of a split twice as wide
+    constexpr int LT = ROWS ? LR + 1 : LR, LCH = ROWS ? LR - 1 : LR;      // outer radix of the twist, chunks per head (log2)
     constexpr int NT = C::NW * 64, RH = (1 << LR) / 2;
     constexpr int NROW = RH * C::L;                      // samples of a row
     constexpr int RPA = (C::L / 8) / NT;                 // runs of eight samples per lane
@@ -1894,14 +1907,14 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     const int c = lane & 15, g = lane >> 4;
     const unsigned G = gridDim.x;
     const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
-    const int h = (int)(vid >> LCH), k1 = LR == 1 ? 1 : (int)(vid & ((1u << LR) - 1u));
+    const int h = (int)(vid >> LCH), kc = (int)(vid & ((1u << LCH) - 1u)), k1 = ROWS ? 4 * kc + 1 : kc;
     const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
     const float* kr = k + (size_t)h * NROW;
 
     float2 cr[RH];
 #pragma unroll
     for (int n1 = 0; n1 < RH; ++n1)
-        cr[n1] = tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LR) - 1)) << (TW_LOG2 - LR));
+        cr[n1] = tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LT) - 1)) << (TW_LOG2 - LT));
     auto load_run = [&](float4 (&v)[RH][2], int i) __attribute__((always_inline)) {
         const int n = staged_run_n<LG>(i * NT + tid);
 #pragma unroll
@@ -2005,7 +2018,7 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
         m = head_max(m);                                 // (the barrier also covers the tables)
         r = head_scale_of(rs ? rs[h] : m);
         if (rs) {                                        // [H, 2H) and [2H, 3H) of the caller's statistics
-            const unsigned Hh = G >> LR;
+            const unsigned Hh = G >> LCH;
             a = rs[Hh + h];
             mp = rs[2 * Hh + h];
         }
@@ -2025,9 +2038,9 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     for (int gi = 0; gi < C::NG; ++gi) phase1_inplace<LG, 2>(xb, t1f, vt, F1, F2, cF, (gi * C::NW + wave) * 8, lane);
     __syncthreads();
     const int es = spec_exponent(kscale * a, kscale * mp);
-    if (k1 == (LR == 1) && tid == 0) spec_exp_of(kspec, G >> LCH, (int64_t)C::L << LR)[h] = es;
+    if (kc == 0 && tid == 0) spec_exp_of(kspec, G >> LCH, (int64_t)C::L << LR)[h] = es;
     const float alpha = ldexpf(kscale_over_c / r, -es), beta = ldexpf(Dh * kscale, -es);
-    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (((size_t)h << LCH) + (LR == 1 ? 0 : k1)) * C::L);
+    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (((size_t)h << LCH) + kc) * C::L);
 #pragma unroll 1
     for (int gi = 0; gi < C::NG; ++gi)
 #pragma unroll
@@ -2079,8 +2092,9 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, __half2* ws, bool c
     const size_t lds = coop_real_lds_bytes<LG>();
     // (head, chunk, pair) items; a batch of one row (every pair a single real row) with pass A inside needs only
     // the chunks up to R/2 (conv_chunks)
-    const int nch = coop_conv_chunks(pr, pl, fuse_a);
-    const long total = pr.H * nch * pr.npairs;
+    const bool rows = fuse_a && rows_split(pl);
+    const int nch = rows ? 2 : coop_conv_chunks(pr, pl, fuse_a), nrow = rows ? (int)pr.B : pr.npairs;
+    const long total = pr.H * nch * nrow;
     auto launch = [&](auto kern, int& resident) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -2093,22 +2107,22 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, __half2* ws, bool c
         }
         const int per = (int)((total + resident - 1) / resident);
         hipLaunchKernelGGL(kern, dim3((unsigned)((total + per - 1) / per)), dim3(NWV * 64), lds, st, (const T*)in, kspec,
-                           ws, pr.B, pr.H, pr.N, pr.npairs, pl.log2R, nch, (int)total, per, tb.tw,
+                           ws, pr.B, pr.H, pr.N, nrow, rows ? 1 : pl.log2R, nch, (int)total, per, tb.tw,
                            (const unsigned char*)tb.ctab, fuse_a ? pr.max_a : nullptr);
         return hipGetLastError();
     };
     static int res[6] = {0, 0, 0, 0, 0, 0};
     if constexpr (LG == COOP_MAX_LOG2) {
-        if (fuse_a && pl.log2R == 2)
-            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 2>, res[2])
-                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 2>, res[3]);
+        if (rows)
+            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 2, true>, res[2])
+                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 2, true>, res[3]);
         if (fuse_a && pl.log2R == 3)
-            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 3>, res[4])
-                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 3>, res[5]);
+            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 3, false>, res[4])
+                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 3, false>, res[5]);
     }
     if (fuse_a) return hipErrorInvalidValue;
-    return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 0>, res[1])
-                : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 0>, res[0]);
+    return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 0, false>, res[1])
+                : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 0, false>, res[0]);
 }
 
 // multi-pass dk: chunks of pass A's outputs in, chunks for pass C and partial dD sums out
@@ -2186,14 +2200,14 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(pl.row_lg ? H : H << pl.log2R)), dim3(C::NW * 64), lds_rows, st, k, D,
+        hipLaunchKernelGGL(kern, dim3((unsigned)(pl.row_lg ? H : H << (pl.log2R - (rows_split(pl) ? 1 : 0)))), dim3(C::NW * 64), lds_rows, st, k, D,
                            pl.log2R == 3 ? rs : nullptr, kspec, koc, pl.kscale, tb.tw, (const unsigned char*)tb.ctab);
         return hipGetLastError();
     };
-    if (pl.row_lg) return launch_rows(coop_kspec_rows_kernel<LG, 1>);
+    if (pl.row_lg) return launch_rows(coop_kspec_rows_kernel<LG, 1, true>);
     if constexpr (LG == COOP_MAX_LOG2) {      // pass A inside
-        if (pl.fuse_a && pl.log2R == 2) return launch_rows(coop_kspec_rows_kernel<LG, 2>);
-        if (pl.fuse_a && pl.log2R == 3) return launch_rows(coop_kspec_rows_kernel<LG, 3>);
+        if (rows_split(pl)) return launch_rows(coop_kspec_rows_kernel<LG, 2, true>);
+        if (pl.fuse_a && pl.log2R == 3) return launch_rows(coop_kspec_rows_kernel<LG, 3, false>);
     }
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_kspec_kernel<LG>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

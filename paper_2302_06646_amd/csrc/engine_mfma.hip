@@ -555,6 +555,7 @@ void mfma_fill_plan(Plan& pl)
         const float cr = 1.0f / (float)(1 << total_shift(pl.row_lg));
         pl.kscale = 1.0f / (0.5f * L * cr * cr);
     }
+    if (rows_split(pl)) pl.kscale *= 2.0f;        // N points instead of 2N
     // one backward kernel where a wave group holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
     pl.fuse_bwd = pl.order.wave_lg && opt.fuse_bwd;
 }

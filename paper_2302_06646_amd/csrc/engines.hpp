@@ -60,6 +60,8 @@ int outer_fwd_blocks_per_head(const Problem& pr, int log2L2);
 // (truncation to the first N samples); re -> row 2p, im -> row 2p+1.
 // herm: every row is a single real row whose chunks above R/2 were not computed; they are taken as the complex
 // conjugates of chunks R - k1 (Hermitian spectrum of real data).
+// Pass C of rows_split plans: ws holds two chunks of L2 values per row.
+hipError_t outer_inv_rows(const void* ws, void* out, const Problem& pr, int log2L2, const float2* tw, hipStream_t st);
 hipError_t outer_inv(const void* ws, void* out, const Problem& pr, int log2R, int log2L2, float scale,
                      bool ws_f16, const float2* tw, hipStream_t st, bool herm = false);
 // dD[h] = sum_b sum_t dy[b,h,t] u[b,h,t], plain fp32 dot product (one workgroup per head).
@@ -159,6 +161,9 @@ hipError_t coop_fill_tables(const void** tab_out, hipStream_t st);
 // Chunks of the multi-pass split that the inner convolution computes: all R, or, for a batch of one row with pass
 // A inside the kernel, only k1 <= R/2: a real row has a Hermitian spectrum, chunk R - k1 of pass C's input is the
 // complex conjugate of chunk k1, and pass C (outer_inv with herm = true) takes it from there.
+// N = 65536: spectrum and convolutions take two chunks of each row's N-point twisted transform (4N is the twiddle table's
+// length, so N = 131072 keeps the zero-padded pairs)
+inline bool rows_split(const Plan& pl) { return pl.fuse_a && pl.log2R == 2; }
 inline int coop_conv_chunks(const Problem& pr, const Plan& pl, bool fuse_a)
 {
     const int R = 1 << pl.log2R;

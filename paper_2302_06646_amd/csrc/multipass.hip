@@ -421,6 +421,47 @@ hipError_t fwd_launch(const void* in, const void* in2, void* ws, void* ws2, floa
     return hipGetLastError();
 }
 
+// Pass C of single rows in two chunks (N = 2 L2 = 65536, W = exp(-2 pi i / 4N)): chunk kc carries the frequencies
+// kc + 2 f2 of the twisted row, so with a = W^-n2 v_0 and b = W^-5n2 v_1 sample n2 is Re(a + b) and sample L2 + n2
+// Re(exp(2 pi i / 8) (a - b)).  Four columns per thread as in outer_inv4_kernel; bound by the chunks' reads.
+template <class IO>
+__global__ void __launch_bounds__(OB) outer_inv_rows_kernel(const __half2* __restrict__ ws, typename IO::T* __restrict__ out,
+                                                            int nrow, int64_t H, int log2L2, const float2* __restrict__ tw,
+                                                            const typename IO::T* __restrict__ gate,
+                                                            const uint32_t* __restrict__ max_a, const int* __restrict__ spec_exp)
+{
+    constexpr int VEC = 4;
+    const int L2 = 1 << log2L2, nbx = L2 / (VEC * OB);
+    const int n2 = ((blockIdx.x % nbx) * OB + threadIdx.x) * VEC;
+    const int item = blockIdx.x / nbx, h = item / nrow;
+    const size_t o = row_off(item - h * nrow, h, H, 2 * (int64_t)L2) + n2;
+    const float scale = ldexpf(1.0f, spec_exp[h] + (max_a ? mu::row_exponent(max_a[h]) : 0));
+    const __half2* src = ws + ((size_t)item << (log2L2 + 1)) + n2;
+    uint32_t q0[VEC], q1[VEC];
+    mu::load_words<VEC>(src, q0);
+    mu::load_words<VEC>(src + L2, q1);
+    float x[VEC], y[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        const float2 w = tw_full(tw, (uint32_t)(n2 + j) << (TW_LOG2 - log2L2 - 3));
+        const float2 w2 = cmul(w, w), w5 = cmul(cmul(w2, w2), w);
+        union { uint32_t u; __half2 hh; } c0, c1;
+        c0.u = q0[j]; c1.u = q1[j];
+        const float2 a = cmulc(__half22float2(c0.hh), w), b = cmulc(__half22float2(c1.hh), w5);
+        x[j] = (a.x + b.x) * scale;
+        y[j] = ((a.x - b.x) - (a.y - b.y)) * (0.70710678118654752f * scale);
+    }
+    if (gate) {
+        float g0[VEC], g1[VEC];
+        load_cols<IO, VEC>(gate + o, g0);
+        load_cols<IO, VEC>(gate + o + L2, g1);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) { x[j] *= g0[j]; y[j] *= g1[j]; }
+    }
+    store_cols<IO, VEC>(out + o, x);
+    store_cols<IO, VEC>(out + o + L2, y);
+}
+
 template <class IO, class CW, int LOG2R>
 hipError_t inv_launch(const void* ws, void* out, const Problem& pr, int log2L2, float scale, const float2* tw,
                       hipStream_t st, int herm)
@@ -502,6 +543,19 @@ hipError_t outer_inv(const void* ws, void* out, const Problem& pr, int log2R, in
         GO(IoBF16, CwF32);
     }
 #undef GO
+}
+
+hipError_t outer_inv_rows(const void* ws, void* out, const Problem& pr, int log2L2, const float2* tw, hipStream_t st)
+{
+    if (log2L2 + 3 > TW_LOG2 || (1 << log2L2) < 4 * OB) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(((size_t)1 << log2L2) / (4 * OB) * (size_t)pr.B * (size_t)pr.H));
+#define GO(IO) hipLaunchKernelGGL(outer_inv_rows_kernel<IO>, grid, dim3(OB), 0, st, (const __half2*)ws, (IO::T*)out, (int)pr.B, \
+                                  pr.H, log2L2, tw, (const IO::T*)pr.gate, pr.max_a, pr.spec_exp)
+    if (pr.io == LONGCONV_F16) GO(IoF16);
+    else if (pr.io == LONGCONV_BF16) GO(IoBF16);
+    else return hipErrorInvalidValue;
+#undef GO
+    return hipGetLastError();
 }
 
 size_t head_stats_floats(int64_t H, int64_t N) { return (size_t)3 * H * (1 + (size_t)((N + STAT_BLOCK - 1) / STAT_BLOCK)); }

@@ -254,3 +254,14 @@ def test_single_rows_of_8192_to_32768_samples(N, io, B, H):
         check_full(inp, label="single rows")
     else:
         check_sampled(inp, [0, 31, H - 1], label="single rows")
+
+
+@pytest.mark.parametrize("io,B,H", [(wl.F16, 3, 2), (wl.BF16, 2, 65)])
+def test_rows_of_65536_samples_in_two_chunks(io, B, H):
+    # an odd batch; as many chunks as compute units and a few more (a workgroup takes two of different rows)
+    from gpu_harness import check_full, check_sampled
+    inp = wl.generate(wl.Workload(6, B, H, 65536, io, "decay4"))
+    if H <= 2:
+        check_full(inp, label="rows in two chunks")
+    else:
+        check_sampled(inp, [0, 33, H - 1], label="rows in two chunks")
