@@ -87,24 +87,29 @@ def group_bytes(w: wl.Workload):
 
 def executed_mfma_flops(w: wl.Workload):
     """Matrix-core flops the kernels issue for one step (model of the factorisation, dense 16x16x32 blocks,
-    two instructions per 16x16 complex tile and stage, 16384 flop each): per 256-point tile a forward or an
-    inverse half transform costs 8 instructions on the cooperative kernels (four stages), 6 on the
-    wave-autonomous ones (three stages).  Half transforms per row pair: forward 2, backward 3 where one kernel
-    serves du, dk and dD (up to 4096 points) else 4; per head: spectrum 1, dk's inverse 1."""
+    two instructions per 16x16 complex tile and stage, 16384 flop each): per 256-point tile a forward or an inverse half
+    transform costs 8 instructions at four digits, 6 at three, 4 at two.  The convolutions and the spectrum transform N
+    twisted points per row up to N = 65536 (2N points per row pair, N per head), the whole backward pass too up to
+    N = 4096; dk beyond that works on pairs.  Half transforms: forward 2, du 2, dk 2 per row or pair (3 for both where
+    one kernel serves them); per head: spectrum 1, dk's inverse 1."""
     if w.dtype == wl.F32:
         return 0.0
-    L = 2 * w.N
+    L, N = 2 * w.N, w.N
     npairs = (w.B + 1) // 2
-    per_half = (6 if L <= 4096 else 8) * 16384 * (L / 256)
-    bwd_halves = 3 if L <= 4096 else 4
-    fwd_halves, head_halves = 2.0, 2.0
-    if L > 32768 and w.B == 1:
-        # a batch of one row: the multi-pass kernels compute the chunks 0 .. R/2 of R only (Hermitian spectrum);
-        # the convolutions split into R = L / 32768 chunks, dk into 2R chunks of 16384 points
-        R = L // 32768
-        fc, fd = (R / 2 + 1) / R, (R + 1) / (2 * R)
-        fwd_halves, bwd_halves, head_halves = 2 * fc, 2 * fc + 2 * fd, 1 + fd
-    return w.H * (npairs * (fwd_halves + bwd_halves) + head_halves) * per_half
+    half = lambda points, digits: 2 * digits * 16384 * (points / 256)
+    if N <= 4096:
+        return w.H * (5 * w.B + 2) * half(N, 2 if N == 256 else 3)
+    pairs = half(L, 4)
+    dk = 2 * npairs + 1
+    if N >= 32768 and w.B == 1:
+        # a batch of one row: dk splits into R chunks of 16384 points and computes 0 .. R/2 of them (Hermitian spectrum)
+        R = L // 16384
+        dk *= (R / 2 + 1) / R
+    if N <= 65536:
+        return w.H * ((4 * w.B + 1) * half(N, 4) + dk * pairs)
+    R = L // 32768
+    fc = (R / 2 + 1) / R if w.B == 1 else 1.0
+    return w.H * ((4 * npairs * fc + 1 + dk) * pairs)
 
 
 class Sets:

@@ -423,7 +423,8 @@ hipError_t fwd_launch(const void* in, const void* in2, void* ws, void* ws2, floa
 
 // Pass C of single rows in two chunks (N = 2 L2 = 65536, W = exp(-2 pi i / 4N)): chunk kc carries the frequencies
 // kc + 2 f2 of the twisted row, so with a = W^-n2 v_0 and b = W^-5n2 v_1 sample n2 is Re(a + b) and sample L2 + n2
-// Re(exp(2 pi i / 8) (a - b)).  Four columns per thread as in outer_inv4_kernel; bound by the chunks' reads.
+// Re(exp(2 pi i / 8) (a - b)).  Four columns per thread as in outer_inv4_kernel; bound by
+// the chunks' reads: B=1, H=128 9.8 us, 50.7 MB (5.2 TB/s; four chunks of a pair: 12 us).
 template <class IO>
 __global__ void __launch_bounds__(OB) outer_inv_rows_kernel(const __half2* __restrict__ ws, typename IO::T* __restrict__ out,
                                                             int nrow, int64_t H, int log2L2, const float2* __restrict__ tw,
