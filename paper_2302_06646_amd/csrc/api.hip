@@ -288,7 +288,7 @@ static hipError_t run_conv(const void* in, const float2* kspec, void* out, void*
     else
         e = mfma_conv(in, kspec, out, (__half2*)ws1, conj, fuse_a, pr, pl, tb, st);
     if (e != hipSuccess) return e;
-    if (pl.log2R && !pl.row_lg) {
+    if (pl.log2R && !pl.row1) {
         Problem pc = pr;     // pass C gives the output the power of two that the stored spectrum left out
         pc.spec_exp = spec_exp_ptr(kspec, pr.H, size_t(1) << pl.log2L, pl);
         if (fuse_a && rows_split(pl)) return outer_inv_rows(ws1, out, pc, pl.log2L2, tw, st);
@@ -377,7 +377,7 @@ static int fwd_impl(const void* u, const float* k, const float* D, const void* k
     }
     Problem pr{B, H, N, io, (int)((B + 1) / 2)};
     pr.pad = pad;
-    if (rows_rescaled(pl, io) && !pl.row_lg) {      // (row_lg: the kernel measures the rows itself)
+    if (rows_rescaled(pl, io) && !pl.row1) {      // (row1: the kernel measures the rows itself)
         uint32_t* mx = (uint32_t*)(base + w.rowmx);
         if (note(rows_absmax(u, mx, pr, st), "rows max") != hipSuccess) return LONGCONV_ERR_HIP;
         pr.max_a = mx;
@@ -483,7 +483,7 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
     bool dy_ready = false;   // multi-pass: pass A of dy already in ws1
     uint32_t* mx_u = nullptr;      // bf16 rows of these multi-pass plans: per-head maxima of u and dy
     uint32_t* mx_dy = nullptr;
-    if (rows_rescaled(pl, io) && (want_dkD || !pl.row_lg)) {
+    if (rows_rescaled(pl, io) && (want_dkD || !pl.row1)) {
         mx_u = (uint32_t*)(base + w.rowmx);
         mx_dy = mx_u + H;
         hipError_t e = hipSuccess;

@@ -178,7 +178,7 @@ struct Plan {
     float kscale;    // factor folded into the stored spectrum (includes 1/L)
     float dkscale;   // factor applied to the inverse transform of the dk accumulator
     int fuse_a;      // multi-pass convolutions take pass A inside the inner kernel (outer radix 2, 4 or 8, matrix cores)
-    int row_lg;      // != 0 (N = 8192 .. 32768, matrix cores): spectrum and convolutions run one transform of N = 2^row_lg twisted points per row
+    int row1;        // fuse_a at outer radix 2: the convolutions run one transform of N twisted points per row instead
     int fuse_bwd;    // du, dk and dD of one call come from one kernel (single pass up to 4096 points, matrix cores)
 };
 

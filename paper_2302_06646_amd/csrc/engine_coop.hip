@@ -19,7 +19,7 @@
 // in the tile's lane order, w_L twiddles from a lane-ordered global table (16 bytes per lane and tile).
 // Staged (convolutions, single-pass dk): the whole workgroup moves the pair between global memory and
 // LDS in unit-stride runs, phases 1 and 3 run in place on LDS, and the w_L twiddle is a per-lane
-// constant times an LDS table; see coop_conv_row_kernel.
+// constant times an LDS table; see coop_conv_real_kernel.
 #include "engines.hpp"
 #include "mfma_util.hpp"
 
@@ -296,13 +296,15 @@ __device__ __forceinline__ void phase3_two(const uint32_t* xb, const uint4* gtab
 }
 
 // -------------------------------------------------------------------------------------
-// The staged layout.  The phase-1 tile of a wave takes samples a tile count apart, so loading its operands straight
-// from global memory touches 16 bytes of every 256; here the whole workgroup moves rows
+// Fused convolution of zero-padded real row pairs (single-pass plan), rows staged through LDS.
+// The phase-1 tile of a wave takes samples a tile count apart, so loading its operands straight
+// from global memory touches 16 bytes of every 256; here the whole workgroup moves the pair
 // between global memory and LDS in unit-stride 16-byte runs instead, into the very slots that
-// phase 1 reads and phase 3 writes: sample n = d_a 16 TC + d_b TC + t, an fp16 complex word,
-// lives in word (d_b PITCH + (d_a / 4) TC + t) 4 + d_a % 4 -- the
+// phase 1 reads and phase 3 writes: sample n = d_a 16 TC + d_b TC + t of the pair, packed as the
+// fp16 complex word (row a, row b), lives in word (d_b PITCH + (d_a / 4) TC + t) 4 + d_a % 4 -- the
 // slot phase 1 fills with output (k_a, k_b) = (d_b, d_a) of tile t, and phase 3 the other way round,
-// each lane reading and writing only its own 16 bytes.  The next rows are fetched into registers
+// each lane reading and writing only its own 16 bytes.  Slots of the zero padding (d_a >= 8) are
+// cleared at the start and again by phase 3.  The next pair's runs are fetched into registers
 // before phase 1 and stored to LDS by the lane that has just drained the same slots, so global
 // latency is covered by the three phases and no phase but the second (spectrum) issues global loads:
 // the w_L twiddle of phases 1 and 3 is the product of a per-lane constant w_256^(k_a d_b) and an
@@ -442,6 +444,262 @@ __device__ __forceinline__ int staged_slot(int n)
 
 template <int LG>
 __host__ __device__ constexpr size_t coop_real_lds_bytes() { return (size_t)CC<LG>::XWORDS * 4 + (size_t)CC<LG>::TC * 8 * 16 + (size_t)CC<LG>::TC * 16 * 4; }
+
+// GATE: the output is multiplied element by element by a second tensor of the same shape on its way out (the
+// gated layer: y = g * z).
+template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
+__global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
+coop_conv_real_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec,
+                      typename IO::T* __restrict__ out, const typename IO::T* __restrict__ gate, int64_t B, int64_t H,
+                      int64_t N, int npairs, int per, const float2* __restrict__ tw,
+                      const unsigned char* __restrict__ ctab)
+{
+    using C = CC<LG>;
+    constexpr int NT = NWV * 64;
+    constexpr int RPL = (C::L / 16) / NT;            // 16-byte runs (8 samples) of one row per lane
+    static_assert(RPL * NT * 16 == C::L, "runs must tile the row");
+    extern __shared__ uint4 lds4[];
+    uint32_t* xb = reinterpret_cast<uint32_t*>(lds4);
+    uint4* t1f = lds4 + C::XWORDS / 4;
+    uint4* t1i = t1f + C::TC * 4;
+    uint32_t* vt = reinterpret_cast<uint32_t*>(t1i + C::TC * 4);      // [TC][16]: w_L^(k_a t)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, g = lane >> 4;
+    const unsigned G = gridDim.x;
+    const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
+    // work items (head, pair), `per` consecutive ones per workgroup (a head's pairs share its spectrum)
+    const int total = (int)H * npairs;
+    const int it0 = (int)vid * per, it1 = it0 + per < total ? it0 + per : total;
+    const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
+    Consts<LG> K;
+    make_consts<LG>(K, tw, lane);
+    h2 cF[4];                                            // w_256^(x (4g+j)), the same in both directions
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
+        cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
+    }
+    int ng = C::TC / (8 * NWV);
+    asm volatile("" : "+s"(ng));
+    const int w1 = (c * C::PITCH + g * C::TC) * 4;
+
+    auto run_n = [&](int i) { return staged_run_n<LG>(i * NT + tid); };
+    auto slot = [&](int i) { return staged_slot<LG>(run_n(i)); };
+    uint4 pa[RPL], pb[RPL];
+    auto fetch = [&](int it) {
+        const int h = it / npairs, p = it - h * npairs;
+        const bool has_b = (2 * p + 1) < B;
+        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            const int n = run_n(i);
+            pa[i] = *reinterpret_cast<const uint4*>(in + oa + n);
+            pb[i] = *reinterpret_cast<const uint4*>(in + ob + n);
+            if (!has_b) pb[i] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    };
+    // bf16 rows of a pair that are not both of order one (see band_or_exact, pair_exponents) are scaled by powers
+    // of two on the way in and back on the way out.  The pair is staged unscaled first; every wave publishes the
+    // band test of the words it fetched (two patterns and a flag byte), and after the barrier that makes the staged
+    // pair visible one LDS read tells all waves whether any of them saw a row outside the band.  Only then the
+    // maxima are combined and, if the pair needs it, staged again from the registers, with its scales.
+    __shared__ uint32_t dr_mx[2 * NWV + 2];          // [NWV][2] patterns, then NWV flag bytes
+    auto measure = [&]() {
+        uint32_t m[2] = {0u, 0u};
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            m[0] = absmax_acc(absmax_acc(absmax_acc(absmax_acc(m[0], pa[i].x), pa[i].y), pa[i].z), pa[i].w);
+            m[1] = absmax_acc(absmax_acc(absmax_acc(absmax_acc(m[1], pb[i].x), pb[i].y), pb[i].z), pb[i].w);
+        }
+        band_or_exact<2>(m);
+        if (lane == 0) {
+            dr_mx[2 * wave] = m[0];
+            dr_mx[2 * wave + 1] = m[1];
+            reinterpret_cast<unsigned char*>(dr_mx + 2 * NWV)[wave] = rows_in_band(m[0], m[1]) ? 0 : 1;
+        }
+    };
+    auto stage = [&](int ea, int eb) {
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            uint32_t wa[4] = {pa[i].x, pa[i].y, pa[i].z, pa[i].w}, wb[4] = {pb[i].x, pb[i].y, pb[i].z, pb[i].w};
+            if (IsBf<IO>::v) {
+                if (__builtin_expect((ea | eb) != 0, 0)) {
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) { wa[m] = bf2_to_h2_scaled(wa[m], ea); wb[m] = bf2_to_h2_scaled(wb[m], eb); }
+                } else {
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) { wa[m] = bf2_to_h2(wa[m]); wb[m] = bf2_to_h2(wb[m]); }
+                }
+            }
+            const int a0 = slot(i);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                xb[a0 + 8 * m] = __builtin_amdgcn_perm(wb[m], wa[m], 0x05040100u);
+                xb[a0 + 8 * m + 4] = __builtin_amdgcn_perm(wb[m], wa[m], 0x07060302u);
+            }
+        }
+    };
+    auto drain = [&](int it, int ea, int eb) {
+        const int h = it / npairs, p = it - h * npairs;
+        const bool has_b = (2 * p + 1) < B;
+        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(2 * p + 1, h, H, N);
+        uint4 ga[GATE ? RPL : 1], gb[GATE ? RPL : 1];        // gate values of the runs this lane stores
+        if constexpr (GATE) {
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                const int n = run_n(i);
+                ga[i] = *reinterpret_cast<const uint4*>(gate + oa + n);
+                gb[i] = *reinterpret_cast<const uint4*>(gate + (has_b ? ob : oa) + n);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            const int a0 = slot(i), n = run_n(i);
+            uint32_t x[8], wa[4], wb[4];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = xb[a0 + 4 * e];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                wa[m] = __builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x05040100u);
+                wb[m] = __builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x07060302u);
+                uint32_t gwa = 0u, gwb = 0u;
+                if constexpr (GATE) {
+                    gwa = m == 0 ? ga[i].x : (m == 1 ? ga[i].y : (m == 2 ? ga[i].z : ga[i].w));
+                    gwb = m == 0 ? gb[i].x : (m == 1 ? gb[i].y : (m == 2 ? gb[i].z : gb[i].w));
+                }
+                if (IsBf<IO>::v) {
+                    union { uint32_t u; h2 h; } a, b;
+                    a.u = wa[m]; b.u = wb[m];
+                    float a0f = (float)a.h[0], a1f = (float)a.h[1], b0f = (float)b.h[0], b1f = (float)b.h[1];
+                    if constexpr (GATE) {
+                        a0f *= __uint_as_float(gwa << 16); a1f *= __uint_as_float(gwa & 0xffff0000u);
+                        b0f *= __uint_as_float(gwb << 16); b1f *= __uint_as_float(gwb & 0xffff0000u);
+                    }
+                    wa[m] = pack_bf2(a0f, a1f);
+                    wb[m] = pack_bf2(b0f, b1f);
+                } else if constexpr (GATE) {
+                    union { uint32_t u; h2 h; } a, b, qa, qb;
+                    a.u = wa[m]; b.u = wb[m]; qa.u = gwa; qb.u = gwb;
+                    a.h = a.h * qa.h; b.h = b.h * qb.h;
+                    wa[m] = a.u; wb[m] = b.u;
+                }
+            }
+            if (__builtin_expect((ea | eb) != 0, 0)) {      // exponents of the output rows (drain's arguments)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
+                    wb[m] = out_rescaled<IsBf<IO>::v>(wb[m], eb);
+                }
+            }
+            store_words<4>(out + oa + n, wa);
+            if (has_b) store_words<4>(out + ob + n, wb);
+        }
+    };
+
+    if (it0 < it1) fetch(it0);       // first pair on its way while the tables are built
+    staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
+    __syncthreads();                 // tables and cleared slots in place
+    if (it0 < it1) {
+        if constexpr (IsBf<IO>::v) measure();
+        stage(0, 0);
+    }
+    for (int it = it0; it < it1; ++it) {
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) +
+                                                         (size_t)(it / npairs) * C::L);
+        asm volatile("" : "+s"(ks));
+        __syncthreads();             // staged pair visible
+        int ea = 0, eb = 0;          // exponents of the two rows of this pair
+        if constexpr (IsBf<IO>::v) {
+            static_assert(NWV == 4 || NWV == 8, "flag bytes are read as one or two words");
+            uint32_t f = dr_mx[2 * NWV];
+            if constexpr (NWV == 8) f |= dr_mx[2 * NWV + 1];
+            if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)f) != 0, 0)) {
+                uint32_t ma = 0u, mb = 0u;
+#pragma unroll
+                for (int w = 0; w < NWV; ++w) { ma = max(ma, dr_mx[2 * w]); mb = max(mb, dr_mx[2 * w + 1]); }
+                ma = (uint32_t)__builtin_amdgcn_readfirstlane((int)ma);
+                mb = (uint32_t)__builtin_amdgcn_readfirstlane((int)mb);
+                if (!rows_in_band(ma, mb)) pair_exponents(ma, mb, ea, eb);
+                if ((ea | eb) != 0) {
+                    stage(ea, eb);
+                    __syncthreads();
+                }
+            }
+        }
+
+        // the next pair's runs start travelling now: they have phases 1 to 3 to land (issued in front of phase 3
+        // only, they arrive in a burst from all compute units at once and part of the transfer is exposed)
+        const bool more = it + 1 < it1;
+        if (more) fetch(it + 1);
+
+        // ---- phase 1, in place
+#pragma unroll 1
+        for (int gi = 0; gi < ng; ++gi)
+            phase1_inplace<LG, NB>(xb, t1f, vt, K.F16, K.F16, cF, (gi * NWV + wave) * 8, lane);
+        __syncthreads();
+        asm volatile("" : "+s"(ks));
+
+        // ---- phase 2
+#pragma unroll 1
+        for (int gi = 0; gi < ng; ++gi)
+#pragma unroll
+        for (int tb = 0; tb < 8; tb += NB) {
+            const int t0 = (gi * NWV + wave) * 8;
+            int base[NB];
+            f4 zr[NB], zi[NB];
+            H8U kk[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const int t2 = t0 + tb + k;
+                base[k] = phase2_base<LG>(t2, lane);
+                kk[k].u = ks[t2 * 64 + lane];
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) phase2_fwd<LG>(xb, base[k], K, zr[k], zi[k]);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                H8U m;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    // correlation (du): the conjugate spectrum, a sign inside the multiply
+                    m.w[j] = CONJ ? cmul_pack_conj(zr[k][j], zi[k][j], kk[k].c[j])
+                                  : cmul_pack(zr[k][j], zi[k][j], kk[k].c[j]);
+                }
+                phase2_inv<LG>(xb, base[k], K, m);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+
+        // ---- phase 3, in place: word = (row a sample, row b sample); padding slots cleared
+#pragma unroll 1
+        for (int gi = 0; gi < ng; ++gi) {
+            const int t0 = (gi * NWV + wave) * 8;
+#pragma unroll
+            for (int tb = 0; tb < 8; tb += 2) {
+                f4 r[2], s[2];
+                phase3_two_lds<LG>(xb, t1i, vt, K, cF, t0 + tb, lane, r, s);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    uint4 o = make_uint4(0u, 0u, 0u, 0u);
+                    if (g < 2) o = make_uint4(pack_h2(r[k][0], s[k][0]), pack_h2(r[k][1], s[k][1]),
+                                              pack_h2(r[k][2], s[k][2]), pack_h2(r[k][3], s[k][3]));
+                    *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) = o;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+        {   // output rows: the input rows' powers of two back, and the one the head's stored spectrum left out
+            const int es = __builtin_amdgcn_readfirstlane(spec_exp_of(kspec, H, C::L)[it / npairs]);
+            drain(it, ea + es, eb + es);
+        }
+        if (more) {
+            if constexpr (IsBf<IO>::v) measure();
+            stage(0, 0);
+        }
+    }
+}
 
 // -------------------------------------------------------------------------------------
 // Inner convolution of the multi-pass split on the staged layout: chunk k1 (L fp16 complex values of pass
@@ -645,20 +903,16 @@ __device__ __forceinline__ int chunk_run_n(int r)
 }
 
 // -------------------------------------------------------------------------------------
-// Single rows of N = L = 8192 .. 32768 samples, forward and du: one N-point transform of the twisted row
+// Single rows of N = L = 32768 samples, forward and du: one N-point transform of the twisted row
 //     X[f] = sum_n x[n] exp(-2 pi i n (4 f + 1) / 4N),
 // whose products are convolutions modulo z^N - i; the real part, untwisted, is the causal convolution truncated to N
 // samples (see engine_rows.hip).  The row's transform fits one compute unit, so rows go from memory to memory in one
 // kernel.  (As row pairs in two chunks of a 65536-point transform the same matrix work needs a complex fp16 workspace
 // of twice the rows' bytes written, and read back by a pass C kernel, and has two chunks where an odd last row needs one.)
 // B=32, H=128, N=32768 fp16: 670 us as pairs in two chunks, 311 us here (1.7 TB/s); what is left is matrix and vector issue.
-// B=8, H=256, N=16384 fp16 step: 298 us with row pairs, 285 us with rows (half the spectrum, two workgroups of four waves per
-// compute unit, whose transfers and arithmetic overlap).
 // The twist W^n, W = exp(-2 pi i / 4N), n = d_a 16 TC + d_b TC + t, takes no instructions: its d_a factor sits in the
 // matrices over d_a of both directions, its d_b factor in the lanes' w_256 constants and its t factor in the w_L table,
-// which phases 1 and 3 (conjugated) share.
-// GATE: the output is multiplied element by element by a second tensor of the same shape on its way out (the gated
-// layer: y = g * z).
+// which phases 1 and 3 (conjugated) share.  Staging, prefetch and the band test are those of coop_conv_real_kernel.
 // -------------------------------------------------------------------------------------
 template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -714,10 +968,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
     asm volatile("" : "+s"(ng));
     const int w1 = (c * C::PITCH + g * C::TC) * 4;
 
-    // a bf16 row that is not of order one (see band_or_exact, pair_exponents) is scaled by a power of two on the way in and
-    // back on the way out.  The row is staged unscaled first; every wave publishes the band test of the words it fetched,
-    // and after the barrier that makes the staged row visible all waves combine them and, if the row needs it, stage it
-    // again from the registers, with its scale.
+    // bf16 rows outside the band are scaled by a power of two, as in coop_conv_real_kernel
     __shared__ uint32_t dr_mx[NWV];
     auto measure = [&]() {
         uint32_t m[1] = {0u};
@@ -1894,8 +2145,8 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     // ROWS: the N-point twisted transform of single rows (coop_conv_row_kernel), 2^(LR-1) chunks of which number kc is
     // chunk 4 kc + 1 of a split twice as wide
     constexpr int LT = ROWS ? LR + 1 : LR, LCH = ROWS ? LR - 1 : LR;      // outer radix of the twist, chunks per head (log2)
-    constexpr int NT = C::NW * 64, RH = (1 << LR) / 2;
-    constexpr int NROW = RH * C::L;                      // samples of a row
+    constexpr int NT = C::NW * 64, RH = LR ? (1 << LR) / 2 : 1;
+    constexpr int NROW = LR ? RH * C::L : C::L / 2;      // samples of a row
     constexpr int RPA = (C::L / 8) / NT;                 // runs of eight samples per lane
     extern __shared__ uint4 lds4[];
     __shared__ float mred[3][C::NW];
@@ -1914,14 +2165,15 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     float2 cr[RH];
 #pragma unroll
     for (int n1 = 0; n1 < RH; ++n1)
-        cr[n1] = tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LT) - 1)) << (TW_LOG2 - LT));
+        cr[n1] = LR ? tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LT) - 1)) << (TW_LOG2 - LT)) : make_float2(1.f, 0.f);
     auto load_run = [&](float4 (&v)[RH][2], int i) __attribute__((always_inline)) {
         const int n = staged_run_n<LG>(i * NT + tid);
 #pragma unroll
         for (int n1 = 0; n1 < RH; ++n1) {
             const float4* src = reinterpret_cast<const float4*>(kr + (size_t)n1 * C::L + n);
-            v[n1][0] = src[0];
-            v[n1][1] = src[1];
+            const bool pad = LR == 0 && n >= NROW;       // the zero half of a single-pass transform
+            v[n1][0] = pad ? make_float4(0.f, 0.f, 0.f, 0.f) : src[0];
+            v[n1][1] = pad ? make_float4(0.f, 0.f, 0.f, 0.f) : src[1];
         }
     };
     // a, mp: sum and maximum of the magnitudes with the skip term counted in the lag-0 tap (`first`: v[0][0].x is
@@ -1979,8 +2231,8 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
             const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
             cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
         }
-        F1 = phase_mats(k1, C::cb + 4, LG + LT, tw, lane);
-        F2 = phase_mats(k1, C::cb, LG + LT, tw, lane);
+        F1 = LR ? phase_mats(k1, C::cb + 4, LG + LT, tw, lane) : K.F16;
+        F2 = LR ? phase_mats(k1, C::cb, LG + LT, tw, lane) : K.F16;
     };
 
     float r;
@@ -1991,7 +2243,7 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
 #pragma unroll
         for (int i = 0; i < RPA; ++i) load_run(v[i], i);
         staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-        twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
+        if (LR) twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
         make_operands();
         float m = 0.f;
 #pragma unroll
@@ -2056,37 +2308,68 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
 template <int LG>
 size_t coop_lds_bytes() { return (size_t)CC<LG>::XWORDS * 4 + (size_t)CC<LG>::TC * 8 * 16; }
 
+// work split of the staged convolution kernel: as many workgroups as the device holds at once
+template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
+hipError_t coop_conv_real_go(const void* in, const float2* kspec, void* out, const Problem& pr,
+                             const Tables& tb, hipStream_t st)
+{
+    using T = typename IO::T;
+    const size_t lds = coop_real_lds_bytes<LG>();
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_conv_real_kernel<LG, IO, NWV, NB, CONJ, GATE>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    static int resident = 0;
+    if (resident == 0) {
+        int nb = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, coop_conv_real_kernel<LG, IO, NWV, NB, CONJ, GATE>, NWV * 64, lds);
+        if (e != hipSuccess) return e;
+        resident = (nb > 0 ? nb : 1) * compute_units();
+    }
+    const long total = pr.H * pr.npairs;                 // (head, pair) items, a run of `per` per workgroup
+    const int per = (int)((total + resident - 1) / resident);
+    hipLaunchKernelGGL((coop_conv_real_kernel<LG, IO, NWV, NB, CONJ, GATE>), dim3((unsigned)((total + per - 1) / per)),
+                       dim3(NWV * 64), lds, st, (const T*)in, kspec, (T*)out, (const T*)pr.gate, pr.B, pr.H, pr.N,
+                       pr.npairs, per, tb.tw, (const unsigned char*)tb.ctab);
+    return hipGetLastError();
+}
+
 template <int LG, class IO, bool CONJ, bool GATE>
 hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, const Problem& pr, const Tables& tb,
                             hipStream_t st)
 {
     using T = typename IO::T;
-    // four waves per workgroup where two workgroups share a compute unit (N <= 16384)
-    constexpr int NWV = LG < COOP_MAX_LOG2 ? 4 : 8;
+    constexpr int NWV = CC<LG>::NW;
     const auto kern = coop_conv_row_kernel<LG, IO, NWV, NTB, CONJ, GATE>;
     const size_t lds = coop_real_lds_bytes<LG>();
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const long total = pr.H * pr.B;                      // (head, row) items, a run of `per` per resident workgroup
-    const int resident = (LG < COOP_MAX_LOG2 ? 2 : 1) * compute_units(), per = (int)((total + resident - 1) / resident);
+    const long total = pr.H * pr.B;                      // (head, row) items; the row fills a compute unit's LDS
+    const int cus = compute_units(), per = (int)((total + cus - 1) / cus);
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + per - 1) / per)), dim3(NWV * 64), lds, st, (const T*)in, kspec, (T*)out,
                        (const T*)pr.gate, pr.B, pr.H, per, tb.tw, (const unsigned char*)tb.ctab);
     return hipGetLastError();
 }
-template <int LG, class IO>
-hipError_t coop_conv_rows(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr, const Tables& tb,
-                          hipStream_t st)
-{
-    if (pr.gate) return conj ? hipErrorInvalidValue : coop_conv_row_go<LG, IO, false, true>(in, kspec, out, pr, tb, st);
-    return conj ? coop_conv_row_go<LG, IO, true, false>(in, kspec, out, pr, tb, st)
-                : coop_conv_row_go<LG, IO, false, false>(in, kspec, out, pr, tb, st);
-}
 
 template <int LG, class IO>
-hipError_t coop_conv_go(const void* in, const float2* kspec, __half2* ws, bool conj, bool fuse_a,
+hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
                         const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     constexpr int NWV = CC<LG>::NW, NB = NTB;
+    if (pl.log2R == 0) {
+        if (pr.gate)
+            return conj ? hipErrorInvalidValue
+                        : coop_conv_real_go<LG, IO, NWV, NB, false, true>(in, kspec, out, pr, tb, st);
+        return conj ? coop_conv_real_go<LG, IO, NWV, NB, true, false>(in, kspec, out, pr, tb, st)
+                    : coop_conv_real_go<LG, IO, NWV, NB, false, false>(in, kspec, out, pr, tb, st);
+    }
+    if constexpr (LG == COOP_MAX_LOG2) {
+        if (pl.row1) {
+            if (pr.gate)
+                return conj ? hipErrorInvalidValue : coop_conv_row_go<LG, IO, false, true>(in, kspec, out, pr, tb, st);
+            return conj ? coop_conv_row_go<LG, IO, true, false>(in, kspec, out, pr, tb, st)
+                        : coop_conv_row_go<LG, IO, false, false>(in, kspec, out, pr, tb, st);
+        }
+    }
     // multi-pass: the inner convolution on pass A's workspace, or (fuse_a) on the rows themselves
     using T = typename IO::T;
     const size_t lds = coop_real_lds_bytes<LG>();
@@ -2200,12 +2483,14 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(pl.row_lg ? H : H << (pl.log2R - (rows_split(pl) ? 1 : 0)))), dim3(C::NW * 64), lds_rows, st, k, D,
+        const int lch = pl.log2R - (pl.row1 || rows_split(pl) ? 1 : 0);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(H << lch)), dim3(C::NW * 64), lds_rows, st, k, D,
                            pl.log2R == 3 ? rs : nullptr, kspec, koc, pl.kscale, tb.tw, (const unsigned char*)tb.ctab);
         return hipGetLastError();
     };
-    if (pl.row_lg) return launch_rows(coop_kspec_rows_kernel<LG, 1, true>);
+    if (pl.log2R == 0) return launch_rows(coop_kspec_rows_kernel<LG, 0, false>);
     if constexpr (LG == COOP_MAX_LOG2) {      // pass A inside
+        if (pl.row1) return launch_rows(coop_kspec_rows_kernel<LG, 1, true>);
         if (rows_split(pl)) return launch_rows(coop_kspec_rows_kernel<LG, 2, true>);
         if (pl.fuse_a && pl.log2R == 3) return launch_rows(coop_kspec_rows_kernel<LG, 3, false>);
     }
@@ -2222,16 +2507,15 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
 hipError_t coop_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
-    const int lg = pl.row_lg ? pl.row_lg : pl.log2L2;
-#define GO(LG, IO) return pl.row_lg ? coop_conv_rows<LG, IO>(in, kspec, out, conj, pr, tb, st) : coop_conv_go<LG, IO>(in, kspec, ws, conj, fuse_a, pr, pl, tb, st)
+#define GO(LG, IO) return coop_conv_go<LG, IO>(in, kspec, out, ws, conj, fuse_a, pr, pl, tb, st)
     if (pr.io == LONGCONV_F16) {
-        if (lg == 13) GO(13, IoF16);
-        if (lg == 14) GO(14, IoF16);
-        if (lg == 15) GO(15, IoF16);
+        if (pl.log2L2 == 13) GO(13, IoF16);
+        if (pl.log2L2 == 14) GO(14, IoF16);
+        if (pl.log2L2 == 15) GO(15, IoF16);
     } else if (pr.io == LONGCONV_BF16) {
-        if (lg == 13) GO(13, IoBF16);
-        if (lg == 14) GO(14, IoBF16);
-        if (lg == 15) GO(15, IoBF16);
+        if (pl.log2L2 == 13) GO(13, IoBF16);
+        if (pl.log2L2 == 14) GO(14, IoBF16);
+        if (pl.log2L2 == 15) GO(15, IoBF16);
     }
 #undef GO
     return hipErrorInvalidValue;
@@ -2240,10 +2524,9 @@ hipError_t coop_conv(const void* in, const float2* kspec, void* out, __half2* ws
 hipError_t coop_kspec(const float* k, const __half2* ws, const float* D, const float* rs, float2* kspec, int64_t H,
                       int64_t N, const Plan& pl, const Tables& tb, hipStream_t st)
 {
-    const int lg = pl.row_lg ? pl.row_lg : pl.log2L2;
-    if (lg == 13) return coop_kspec_go<13>(k, ws, D, rs, kspec, H, N, pl, tb, st);
-    if (lg == 14) return coop_kspec_go<14>(k, ws, D, rs, kspec, H, N, pl, tb, st);
-    if (lg == 15) return coop_kspec_go<15>(k, ws, D, rs, kspec, H, N, pl, tb, st);
+    if (pl.log2L2 == 13) return coop_kspec_go<13>(k, ws, D, rs, kspec, H, N, pl, tb, st);
+    if (pl.log2L2 == 14) return coop_kspec_go<14>(k, ws, D, rs, kspec, H, N, pl, tb, st);
+    if (pl.log2L2 == 15) return coop_kspec_go<15>(k, ws, D, rs, kspec, H, N, pl, tb, st);
     return hipErrorInvalidValue;
 }
 

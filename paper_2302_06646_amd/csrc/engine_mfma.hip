@@ -548,13 +548,9 @@ void mfma_fill_plan(Plan& pl)
     // outer radix 4 or 8 around the 32768-point cooperative kernels: the convolutions take pass A in their
     // staging (switch fuse_pass_a = 0 keeps the separate pass, for comparison)
     pl.fuse_a = pl.order.coop_lg == COOP_MAX_LOG2 && pl.log2R >= 1 && pl.log2R <= 3 && opt.fuse_pass_a;
-    // the N twisted points of one row fit one compute unit up to N = 32768: spectrum, forward and du run on them (dk keeps
-    // the pairs)
-    if (pl.order.coop_lg && (pl.log2R == 0 || (pl.log2R == 1 && pl.fuse_a))) {
-        pl.row_lg = pl.log2L - 1;
-        const float cr = 1.0f / (float)(1 << total_shift(pl.row_lg));
-        pl.kscale = 1.0f / (0.5f * L * cr * cr);
-    }
+    // ... and at outer radix 2 a row's N twisted points fit one compute unit (spectrum, forward, du; dk keeps the split)
+    pl.row1 = pl.fuse_a && pl.log2R == 1;
+    if (pl.row1) pl.kscale *= 2.0f;               // 1/N instead of 1/2N
     if (rows_split(pl)) pl.kscale *= 2.0f;        // N points instead of 2N
     // one backward kernel where a wave group holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
     pl.fuse_bwd = pl.order.wave_lg && opt.fuse_bwd;

@@ -229,16 +229,14 @@ def test_fp32_engine_every_length(N, B, H):
     assert wl.rel_l2(g.bwd(dk=False, dD=False)[0], du) < 1e-6
 
 
-@pytest.mark.parametrize("N,io,B,H", [(32768, wl.F16, 1, 1), (32768, wl.BF16, 3, 2), (32768, wl.BF16, 5, 61),
-                                      (16384, wl.F16, 1, 1), (16384, wl.BF16, 3, 2), (16384, wl.F16, 7, 81),
-                                      (8192, wl.F16, 1, 1), (8192, wl.BF16, 3, 2), (8192, wl.BF16, 7, 81)])
-def test_single_rows_of_8192_to_32768_samples(N, io, B, H):
+@pytest.mark.parametrize("io,B,H", [(wl.F16, 1, 1), (wl.BF16, 3, 2), (wl.BF16, 5, 61)])
+def test_single_rows_of_32768_samples(io, B, H):
     # one twisted transform per row: the only row of the call; an odd count with rows outside the bf16 band (each row is
-    # scaled by itself, so each meets the tolerance by itself); more rows than workgroups fit the device, where a workgroup takes
+    # scaled by itself, so each meets the tolerance by itself); more rows than compute units, where a workgroup takes
     # several, of two heads, and the last workgroup is short
     import oracle
     from gpu_harness import TOL, GpuRun, _compare, check_full, check_sampled
-    inp = wl.generate(wl.Workload(6, B, H, N, io, "decay_alpha_squash"))
+    inp = wl.generate(wl.Workload(6, B, H, 32768, io, "decay_alpha_squash"))
     if B == 3:
         s = 2.0 ** np.array([-40, 0, 12])[:, None, None]        # powers of two: exact in bf16
         for name in ("u", "dy"):
