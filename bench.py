@@ -89,8 +89,8 @@ def executed_mfma_flops(w: wl.Workload):
     """Matrix-core flops the kernels issue for one step (model of the factorisation, dense 16x16x32 blocks,
     two instructions per 16x16 complex tile and stage, 16384 flop each): per 256-point tile a forward or an inverse half
     transform costs 8 instructions at four digits, 6 at three, 4 at two.  The convolutions and the spectrum transform N
-    twisted points per row up to N = 65536 (2N points per row pair, N per head), the whole backward pass too up to
-    N = 4096; dk beyond that works on pairs.  Half transforms: forward 2, du 2, dk 2 per row or pair (3 for both where
+    twisted points per row at N <= 4096, 32768 and 65536 (2N points per row pair, N per head), the whole backward pass too
+    up to N = 4096; dk beyond that, and everything at the other lengths, works on zero-padded pairs.  Half transforms: forward 2, du 2, dk 2 per row or pair (3 for both where
     one kernel serves them); per head: spectrum 1, dk's inverse 1."""
     if w.dtype == wl.F32:
         return 0.0
@@ -105,10 +105,10 @@ def executed_mfma_flops(w: wl.Workload):
         # a batch of one row: dk splits into R chunks of 16384 points and computes 0 .. R/2 of them (Hermitian spectrum)
         R = L // 16384
         dk *= (R / 2 + 1) / R
-    if N <= 65536:
+    if N in (32768, 65536):
         return w.H * ((4 * w.B + 1) * half(N, 4) + dk * pairs)
     R = L // 32768
-    fc = (R / 2 + 1) / R if w.B == 1 else 1.0
+    fc = (R / 2 + 1) / R if w.B == 1 and R > 1 else 1.0
     return w.H * ((4 * npairs * fc + 1 + dk) * pairs)
 
 

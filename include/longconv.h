@@ -36,13 +36,13 @@
  *     bf16 rows (u, dy) may have any magnitude: rows are multiplied by a power of two on
  *     their way into the transform and by its inverse on the way out where they need it, so
  *     gradients of order 1e-10 or activations of order 1e6 keep the accuracy of data of
- *     order one.  For y and du up to N = 32768, and for dk and dD up to N = 4096, this is
- *     decided row by row: a row whose largest sample lies in 2^-2 .. 2^4 runs unscaled, any
- *     other row is scaled on its own, so every row meets the bound of data of order one
- *     whatever its neighbours' sizes.  dk and dD up to N = 16384 go pair by pair (two batch
- *     rows of a head share one complex transform), each row of a pair outside that band or
- *     more than a factor of four apart with its own scale.  Beyond these lengths all rows of
- *     a head share one power of
+ *     order one.  Up to N = 4096, and for y and du at N = 32768, this is decided row by row:
+ *     a row whose largest sample lies in 2^-2 .. 2^4 runs unscaled, any other row is scaled on
+ *     its own.  At N = 8192 and 16384 it is decided pair by pair (two batch rows of a head
+ *     share one complex transform): a pair whose rows both lie in that band and within a
+ *     factor of four of each other runs unscaled, in any other pair every row is scaled on
+ *     its own.  Either way every row meets the bound of data of order one whatever its
+ *     neighbours' sizes.  Beyond these lengths all rows of a head share one power of
  *     two, found by a pass over the tensor in front, so rows of one head that differ by many
  *     orders of magnitude lose the small ones.  The kernel k and the skip term D may have any
  *     magnitude as well: a head is scaled by a power of two on its way into the spectrum's
