@@ -934,6 +934,24 @@ __device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2
     return etop;
 }
 
+// The accumulator goes into dk's inverse transform as fp16, and as a sum over rows it has no bound of its own (rows with a
+// mean add up in the first bins: 0.8 N^2 / 4^SHIFT times the product of the means per row, 3300 at N = 4096).  So its
+// largest component is brought to 2^7 .. 2^8 by a power of two, which dk gets back in fp32: the inverse grows a
+// component by at most sqrt(2) N / 2^SHIFT <= 91, which stays below fp16's 65504.  This wave's largest component:
+template <int NA>
+__device__ __forceinline__ float acc_peak(const float2 (&acc)[NA][4])
+{
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < NA; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m = fmaxf(m, fmaxf(fabsf(acc[k][j].x), fabsf(acc[k][j].y)));
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    return m;
+}
+// exponent of the power of two an accumulator whose largest component is m is divided by
+__device__ __forceinline__ int acc_exponent(float m) { return (int)(__float_as_uint(m) >> 23) - (127 + 7); }
+
 // -------------------------------------------------------------------------------------
 // Whole backward pass of a head (or of a share of its rows) per workgroup, rows shared by NWR waves (N >= 1024): du, dk
 // and dD from one read of dy and u.  Per row: W = transform of dy, U = transform of u, du = inverse of W conj(K),
@@ -1197,17 +1215,25 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
     if (lane == 0) dred[wave] = dsum;
-    const int etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
+    int etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
-    if (NGRP > 1 || !q.dk) __syncthreads();              // (the reduction's words lie in the buffers that follow)
+    float* peaks = reinterpret_cast<float*>(mxs);        // [NWR] (the rows' patterns are done with)
+    const float peak = acc_peak<2>(acc);
+    if (lane == 0 && grp == 0) peaks[wave] = peak;
+    __syncthreads();                                     // (the reduction's words lie in the buffers that follow, too)
     if (q.dk) {
+        float m = peaks[0];
+#pragma unroll
+        for (int w = 1; w < NWR; ++w) m = fmaxf(m, peaks[w]);
+        const int ea = __builtin_amdgcn_readfirstlane(acc_exponent(m));
+        etop += ea;
         float* fs = reinterpret_cast<float*>(lds + 2 * C::XW);        // the row of dk in the u buffers of the first group
         if (grp == 0) {
             H8U mm[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) mm[k].w[r] = pack_h2(acc[k][r].y, acc[k][r].x);
+                for (int r = 0; r < 4; ++r) mm[k].w[r] = pack_h2(ldexpf(acc[k][r].y, -ea), ldexpf(acc[k][r].x, -ea));
             phase2_inv<LG>(lds + xpo, K, mm);
         }
         __syncthreads();
@@ -1412,11 +1438,17 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
     if (lane == 0) dred[wave] = dsum;
-    const int etop = acc_reduce<NS, 1, NWV, BF>(acc, eref, red, erefs, wave, lane);
+    int etop = acc_reduce<NS, 1, NWV, BF>(acc, eref, red, erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
     if (wave != 0) return;
     if (lane == 0 && q.dD) q.dD[ho] = ((dred[0] + dred[1]) + dred[2]) + dred[3];
     if (!q.dk) return;
+    const int ea = __builtin_amdgcn_readfirstlane(acc_exponent(acc_peak<NS>(acc)));
+    etop += ea;
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { acc[k][r].x = ldexpf(acc[k][r].x, -ea); acc[k][r].y = ldexpf(acc[k][r].y, -ea); }
     H8U m[2];
     f4 v[2];
 #pragma unroll

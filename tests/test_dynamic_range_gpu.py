@@ -127,3 +127,27 @@ def test_random_magnitudes(N, B, H, seed, kernels):
     ks = 2.0 ** rng.integers(-24, 20, size=H) if kernels else None
     Ds = 2.0 ** rng.integers(-24, 20, size=H) if kernels else None
     check_full(scaled_inputs(N, B, H, us, ds, k_scale=ks, D_scale=Ds, seed=seed), label=f"random magnitudes, N={N}", dd_tol=1e-4)
+
+
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("N", [256, 512, 1024, 2048, 4096])
+def test_dk_of_rows_with_a_mean(N, io):
+    # Rows with a mean add up in the first bins of dk's accumulator: rows of constant 4 reach 4 * 4 * 24 * 207 = 79000
+    # at N = 256 and 512, and more beyond (fp16 ends at 65504), while dk itself is an ordinary fp32 number.  Heads enough
+    # that one workgroup has all rows of a head; every other head's rows carry noise around the mean, one head's dy
+    # is small.
+    from gpu_harness import GpuRun, TOL, _compare
+    import oracle
+    B, H = 24, 129 if N == 4096 else 257
+    inp = wl.generate(wl.Workload(2, B, H, N, io, "squash_pool"))
+    u, dy = inp.u + 4.0, inp.dy + 4.0
+    u[:, ::2] = dy[:, ::2] = 4.0
+    dy[:, 3] = 2.0 ** -10
+    (u_s, u_v), (dy_s, dy_v) = wl.quantize(u.astype(np.float32), io), wl.quantize(dy.astype(np.float32), io)
+    g = GpuRun(dataclasses.replace(inp, u_store=u_s, dy_store=dy_s, u=u_v, dy=dy_v))
+    heads = [0, 1, 2, 3, H - 1]
+    want = oracle.longconv_bwd(dy_v[:, heads], u_v[:, heads], inp.k[heads].astype(np.float64), inp.D[heads].astype(np.float64))[1]
+    for du in (True, False):                 # du, dk and dD from one kernel, and dk by itself
+        dk = g.bwd(du=du)[1]
+        assert np.all(np.isfinite(dk))
+        _compare({"dk": dk[heads]}, {"dk": want}, TOL[io], f"rows with a mean, N={N} io={wl.DTYPE_NAMES[io]} du={du}")
