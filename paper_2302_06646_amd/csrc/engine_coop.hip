@@ -1005,29 +1005,35 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
         for (int i = 0; i < RPL; ++i) {
             const int n = run_n(i), a0 = staged_slot<LG>(n);
             uint32_t wa[4];
+            if constexpr (GATE) {                        // fp32 samples: gate and power of two, then one rounding
+                float x[8];
+                const uint32_t gw[4] = {ga[i].x, ga[i].y, ga[i].z, ga[i].w};
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                wa[m] = __builtin_amdgcn_perm(xb[a0 + 8 * m + 4], xb[a0 + 8 * m], 0x05040100u);
-                uint32_t gw = 0u;
-                if constexpr (GATE) gw = m == 0 ? ga[i].x : (m == 1 ? ga[i].y : (m == 2 ? ga[i].z : ga[i].w));
-                union { uint32_t u; h2 h; } a, q;
-                a.u = wa[m];
-                if (IsBf<IO>::v) {
-                    float x0 = (float)a.h[0], x1 = (float)a.h[1];
-                    if constexpr (GATE) {
-                        x0 *= __uint_as_float(gw << 16);
-                        x1 *= __uint_as_float(gw & 0xffff0000u);
-                    }
-                    wa[m] = pack_bf2(x0, x1);
-                } else if constexpr (GATE) {
-                    q.u = gw;
-                    a.h = a.h * q.h;
-                    wa[m] = a.u;
+                for (int m = 0; m < 4; ++m) {
+                    union { uint32_t u; h2 h; } q;
+                    q.u = gw[m];
+                    x[2 * m] = __uint_as_float(xb[a0 + 8 * m]) * (IsBf<IO>::v ? __uint_as_float(gw[m] << 16) : (float)q.h[0]);
+                    x[2 * m + 1] = __uint_as_float(xb[a0 + 8 * m + 4]) *
+                                   (IsBf<IO>::v ? __uint_as_float(gw[m] & 0xffff0000u) : (float)q.h[1]);
                 }
-            }
-            if (__builtin_expect(ea != 0, 0)) {
+                if (__builtin_expect(ea != 0, 0)) {
 #pragma unroll
-                for (int m = 0; m < 4; ++m) wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
+                    for (int e = 0; e < 8; ++e) x[e] = ldexpf(x[e], ea);
+                }
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    wa[m] = IsBf<IO>::v ? pack_bf2(x[2 * m], x[2 * m + 1]) : pack_h2(x[2 * m], x[2 * m + 1]);
+            } else {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    union { uint32_t u; h2 h; } a;
+                    a.u = __builtin_amdgcn_perm(xb[a0 + 8 * m + 4], xb[a0 + 8 * m], 0x05040100u);
+                    wa[m] = IsBf<IO>::v ? pack_bf2((float)a.h[0], (float)a.h[1]) : a.u;
+                }
+                if (__builtin_expect(ea != 0, 0)) {
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
+                }
             }
             store_words<4>(out + o + n, wa);
         }
@@ -1104,7 +1110,8 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
         }
         __syncthreads();
 
-        // ---- phase 3, in place, real part only: samples (d_a, d_b) = (4g+j, c) of each tile
+        // ---- phase 3, in place, real part only: samples (d_a, d_b) = (4g+j, c) of each tile.  Samples that
+        // meet a gate fill their slots in fp32: gate and power of two come before the one rounding, to the I/O dtype.
 #pragma unroll 1
         for (int gi = 0; gi < ng; ++gi) {
             const int t0 = (gi * NWV + wave) * 8;
@@ -1136,8 +1143,11 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
                 }
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
-                    *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) =
-                        make_uint4(pack_h2(r[k][0], 0.f), pack_h2(r[k][1], 0.f), pack_h2(r[k][2], 0.f), pack_h2(r[k][3], 0.f));
+                    if constexpr (GATE)
+                        *reinterpret_cast<f4*>(&xb[w1 + 4 * (t0 + tb + k)]) = r[k];
+                    else
+                        *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) = make_uint4(
+                            pack_h2(r[k][0], 0.f), pack_h2(r[k][1], 0.f), pack_h2(r[k][2], 0.f), pack_h2(r[k][3], 0.f));
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

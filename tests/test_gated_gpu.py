@@ -1,5 +1,7 @@
 """Gated long convolution (output times a second sequence) and its backward through the C ABI against the float64
 oracle: every plan family, all three I/O dtypes, optional outputs."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -62,6 +64,32 @@ def test_gated_layer_against_the_oracle(N, io):
 def test_gated_rows_of_32768_samples(io):
     # the gate in the store of the single-row kernel (forward, and dg as the forward pass gated by dy)
     test_gated_layer_against_the_oracle(32768, io)
+
+
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("N", [32768])
+def test_gate_meets_heads_of_other_magnitudes(N, io):
+    # A head with a small concentrated kernel is stored with a power of two taken out (2^-22 for 1e-4 at one tap), so its
+    # outputs are large numbers until they get it back; the gate (y) or dy (dg), of order 64 here, must not meet them
+    # before that: fp16 ends at 65504, and y and dg themselves are of order 1e-2 there.  Next to it an ordinary head and a
+    # large one.  dz = dy g stays of order one.
+    B, H = 2 if N <= 16384 else 1, 3
+    inp, _, g_v = _inputs(N, io, B, H, seed=5)
+    k, D = inp.k.copy(), inp.D.copy()
+    k[0] = 0.0; k[0, 0] = 1e-4; D[0] = 0.0
+    k[2] *= 2.0 ** 9; D[2] *= 2.0 ** 9
+    k64, D64 = k.astype(np.float64), D.astype(np.float64)
+    for big in ("y", "dg"):
+        s = np.array([64.0, 64.0, 1.0 / 64.0])[None, :, None] ** (1 if big == "y" else -1)
+        g_s, g = wl.quantize((s * g_v).astype(np.float32), io)
+        dy_s, dy = wl.quantize((inp.dy / s).astype(np.float32), io)
+        y, du, dk, dD, dg = _run(dataclasses.replace(inp, k=k, D=D, dy_store=dy_s, dy=dy), g_s)
+        rdu, rdk, rdD, rdg = gated.gated_bwd(dy, g, inp.u, k64, D64)
+        got = {"du": du, "dk": dk, big: y if big == "y" else dg}
+        want = {"du": rdu, "dk": rdk, big: gated.gated_fwd(inp.u, k64, D64, g) if big == "y" else rdg}
+        heads = slice(None) if big == "y" else slice(0, 2)      # (the large head's dg lies below fp16's normal range)
+        got[big], want[big] = got[big][:, heads], want[big][:, heads]
+        _compare(got, want, TOL[io], f"gate and heads of other magnitudes, {big}, N={N} io={wl.DTYPE_NAMES[io]}")
 
 
 def test_optional_outputs_and_error_codes():
