@@ -587,8 +587,15 @@ coop_conv_real_kernel(const typename IO::T* __restrict__ in, const float2* __res
             if (__builtin_expect((ea | eb) != 0, 0)) {      // exponents of the output rows (drain's arguments)
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
-                    wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
-                    wb[m] = out_rescaled<IsBf<IO>::v>(wb[m], eb);
+                    if constexpr (GATE && !IsBf<IO>::v) {   // (gate and power of two before the rounding)
+                        const uint32_t gwa = m == 0 ? ga[i].x : (m == 1 ? ga[i].y : (m == 2 ? ga[i].z : ga[i].w));
+                        const uint32_t gwb = m == 0 ? gb[i].x : (m == 1 ? gb[i].y : (m == 2 ? gb[i].z : gb[i].w));
+                        wa[m] = h2_gated(__builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x05040100u), gwa, ea);
+                        wb[m] = h2_gated(__builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x07060302u), gwb, eb);
+                    } else {
+                        wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
+                        wb[m] = out_rescaled<IsBf<IO>::v>(wb[m], eb);
+                    }
                 }
             }
             store_words<4>(out + oa + n, wa);

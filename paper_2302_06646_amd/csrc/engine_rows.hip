@@ -487,12 +487,12 @@ struct RowPtr {
 };
 // Which code an iteration runs.  Whole: every phase has a row (no conditions).  Scaled: some power of two is not one.
 template <bool W, bool S> struct Mode { static constexpr bool whole = W, scaled = S; };
-// words of samples -> I/O dtype, times 2^ex
+// samples times 2^ex -> word of the I/O dtype.  The power of two comes before the rounding: samples of a head whose stored
+// spectrum left one out may lie outside fp16's range until they have it back, gated ones in particular.
 template <class IO, bool SCALED>
 __device__ __forceinline__ uint32_t out_word(float a, float b, int ex)
 {
-    const uint32_t w = pack_io<IO>(a, b);
-    return SCALED ? out_rescaled<IsBf<IO>::v>(w, ex) : w;
+    return SCALED ? pack_io<IO>(ldexpf(a, ex), ldexpf(b, ex)) : pack_io<IO>(a, b);
 }
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));

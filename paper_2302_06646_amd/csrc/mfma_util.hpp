@@ -146,6 +146,13 @@ __device__ __forceinline__ uint32_t h2_rescaled(uint32_t w, int e)
     cv.u = w;
     return pack_h2(ldexpf((float)cv.h[0], e), ldexpf((float)cv.h[1], e));
 }
+// words of two fp16 values each: z g 2^e, rounded once (z g alone may leave fp16's range where the result does not)
+__device__ __forceinline__ uint32_t h2_gated(uint32_t z, uint32_t g, int e)
+{
+    union { uint32_t u; h2 h; } a, b;
+    a.u = z; b.u = g;
+    return pack_h2(ldexpf((float)a.h[0] * (float)b.h[0], e), ldexpf((float)a.h[1] * (float)b.h[1], e));
+}
 // packed output word of either half dtype times 2^e
 template <bool BF>
 __device__ __forceinline__ uint32_t out_rescaled(uint32_t w, int e)

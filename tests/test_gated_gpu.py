@@ -67,7 +67,7 @@ def test_gated_rows_of_32768_samples(io):
 
 
 @pytest.mark.parametrize("io", [wl.F16, wl.BF16])
-@pytest.mark.parametrize("N", [32768])
+@pytest.mark.parametrize("N", [256, 512, 1024, 2048, 4096, 8192, 16384, 32768, 65536])
 def test_gate_meets_heads_of_other_magnitudes(N, io):
     # A head with a small concentrated kernel is stored with a power of two taken out (2^-22 for 1e-4 at one tap), so its
     # outputs are large numbers until they get it back; the gate (y) or dy (dg), of order 64 here, must not meet them
