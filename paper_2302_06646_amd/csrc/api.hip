@@ -863,13 +863,27 @@ const char* longconv_plan_string(int64_t N, int io)
     static thread_local char buf[256];
     if (check_shape(1, 1, N, io) != LONGCONV_OK) { snprintf(buf, sizeof(buf), "invalid"); return buf; }
     const Plan pl = make_plan(N, io);
-    int n = snprintf(buf, sizeof(buf), "engine=%s L=2^%d outer_radix=%d inner=2^%d passes=%d digits=",
-                     pl.engine == ENGINE_VALU ? "valu-fp32" : "mfma-fp16", pl.log2L, 1 << pl.log2R, pl.log2L2,
-                     pl.log2R ? 3 : 1);
-    for (int i = 0; i < pl.order.ndig && n < (int)sizeof(buf) - 4; ++i)
-        n += snprintf(buf + n, sizeof(buf) - n, "%s%d", i ? "x" : "", 1 << pl.order.bits[i]);
-    if (pl.order.wave_lg) snprintf(buf + n, sizeof(buf) - n, " kernel=wave");
-    if (pl.order.coop_lg) snprintf(buf + n, sizeof(buf) - n, " kernel=chained");
+    // what the convolutions transform: N twisted points of each row, or 2N zero-padded points of a row pair
+    const bool wave = pl.engine == ENGINE_MFMA && pl.order.wave_lg;
+    const bool rows = wave || pl.row1 || rows_split(pl);
+    const int lgL = pl.log2L - rows, lgL2 = wave ? lgL : pl.log2L2, lgR = lgL - lgL2;
+    int bits[20], nd = 0;
+    if (lgR) bits[nd++] = lgR;
+    if (wave) {
+        bits[nd++] = 4; bits[nd++] = 4;
+        if (lgL > 8) bits[nd++] = lgL - 8;
+    } else {
+        for (int i = pl.log2R != 0; i < pl.order.ndig; ++i) bits[nd++] = pl.order.bits[i];
+    }
+    int n = snprintf(buf, sizeof(buf), "engine=%s L=2^%d of %s outer_radix=%d inner=2^%d passes=%d digits=",
+                     pl.engine == ENGINE_VALU ? "valu-fp32" : "mfma-fp16", lgL, rows ? "rows" : "pairs", 1 << lgR, lgL2,
+                     lgR ? 3 : 1);
+    for (int i = 0; i < nd; ++i) n += snprintf(buf + n, sizeof(buf) - n, "%s%d", i ? "x" : "", 1 << bits[i]);
+    if (wave) n += snprintf(buf + n, sizeof(buf) - n, " kernel=wave");
+    if (pl.order.coop_lg) n += snprintf(buf + n, sizeof(buf) - n, " kernel=chained");
+    if (pl.engine == ENGINE_VALU || pl.fuse_bwd) snprintf(buf + n, sizeof(buf) - n, " backward=one");
+    else if (coop_dk_rows_ok(pl)) snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,%dx2^%d),du", 2 << pl.log2R, pl.log2L2 - 1);
+    else snprintf(buf + n, sizeof(buf) - n, " backward=dk,du");
     return buf;
 }
 

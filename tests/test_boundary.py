@@ -53,6 +53,36 @@ def test_spectrum_size_is_exact_per_dtype():
         assert lc.longconv_kspec_bytes(8, 1024, io) == 8 * 2048 * 4 + 32
 
 
+def test_plan_string_names_what_runs():
+    # rows of N twisted points at N <= 4096, 32768 and 65536, pairs of 2N zero-padded ones elsewhere; fields a program may
+    # look for stay in front
+    want = {
+        (256, lc.F16): ("L=2^8 of rows", "outer_radix=1", "passes=1", "digits=16x16 ", "kernel=wave", "backward=one"),
+        (1024, lc.BF16): ("L=2^10 of rows", "inner=2^10", "passes=1", "digits=16x16x4 ", "kernel=wave", "backward=one"),
+        (4096, lc.F16): ("L=2^12 of rows", "digits=16x16x16 ", "passes=1", "kernel=wave", "backward=one"),
+        (16384, lc.F16): ("L=2^15 of pairs", "passes=1", "digits=16x16x16x8 ", "kernel=chained", "backward=dk,du"),
+        (32768, lc.BF16): ("L=2^15 of rows", "outer_radix=1", "passes=1", "digits=16x16x16x8 ", "backward=dk(pairs,4x2^14),du"),
+        (65536, lc.F16): ("L=2^16 of rows", "outer_radix=2", "inner=2^15", "passes=3", "digits=2x16x16x16x8 ",
+                          "backward=dk(pairs,8x2^14),du"),
+        (131072, lc.F16): ("L=2^18 of pairs", "outer_radix=8", "inner=2^15", "passes=3", "digits=8x16x16x16x8 ",
+                           "backward=dk(pairs,16x2^14),du"),
+        (1024, lc.F32): ("L=2^11 of pairs", "passes=1", "digits=8x8x8x4 ", "backward=one"),
+        (32768, lc.F32): ("L=2^16 of pairs", "outer_radix=4", "inner=2^14", "passes=3", "backward=one"),
+    }
+    try:
+        for (N, io), parts in want.items():
+            s = lc.longconv_plan_string(N, io)
+            for part in parts:
+                assert part in s, (N, io, part, s)
+        lc.longconv_set_option("fuse_pass_a", 0)         # pass A as a kernel of its own: pairs again
+        assert "L=2^16 of pairs outer_radix=2" in lc.longconv_plan_string(32768, lc.F16)
+        lc.longconv_set_option("fuse_bwd", 0)
+        assert "backward=dk,du" in lc.longconv_plan_string(1024, lc.F16)
+    finally:
+        for name, value in lc.OPTION_DEFAULTS.items():
+            lc.longconv_set_option(name, value)
+
+
 def test_options_switch_plans_and_reject_bad_input():
     try:
         assert "kernel=wave" in lc.longconv_plan_string(1024, lc.F16)
