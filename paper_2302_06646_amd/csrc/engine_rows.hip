@@ -888,14 +888,6 @@ __device__ __forceinline__ void acc_tile(float2 (&acc)[4], const f4& ur, const f
     for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(acc[j].x), "+v"(acc[j].y));
 }
 
-// U of the dk-only kernels as packed fp16 (dot products without du keep one operand packed; the fused kernel keeps both
-// in fp32)
-__device__ __forceinline__ void round_h2(f4& a, f4& b)
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { a[j] = (float)(_Float16)a[j]; b[j] = (float)(_Float16)b[j]; }
-}
-
 // The waves' partial accumulators through LDS (red: NWV * NA * 4 * 64 float2) and added in group order by the first
 // group's waves; returns the exponent of the sum's unit.  The caller puts a barrier in front if red is in use.
 template <int NA, int NWR, int NGRP, bool BF>
@@ -1172,10 +1164,7 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
                 phase2_inv<LG>(xu + xpo + bs, K, mm);
             }
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                if (!DU) round_h2(yr[k], yi[k]);
-                acc_tile<BF && M::scaled>(acc[k], yr[k], yi[k], wr[k], wi[k], down);
-            }
+            for (int k = 0; k < 2; ++k) acc_tile<BF && M::scaled>(acc[k], yr[k], yi[k], wr[k], wi[k], down);
         }
         ed2 = ed1; ed1 = ed0;
         eu2 = eu1; eu1 = eu0;
@@ -1392,7 +1381,6 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            if (!DU) round_h2(yr[k], yi[k]);
             // N = 256: tile k is row k and both add to the same bins
             const int epk = C::TC == 1 && k == 1 ? epb : epa;
             acc_tile<BF && M::scaled>(acc[k % NS], yr[k], yi[k], wr[k], wi[k], min(epk - eref, 0));
