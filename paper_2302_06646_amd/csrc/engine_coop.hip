@@ -963,8 +963,8 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
     for (int j = 0; j < 4; ++j) {
         const uint32_t y = (uint32_t)(4 * g + j);
         const float2 a = tw_full(tw, ((((c * y) & 15u) << (TW_LOG2 - 4)) + ((uint32_t)c << (TW_LOG2 - 6))) & (TW_L - 1));
-        I3[2 * j] = (_Float16)(a.x * 0.25f);
-        I3[2 * j + 1] = (_Float16)(a.y * 0.25f);
+        I3[2 * j] = (_Float16)(a.x * 0.5f);          // 2/4: N points where the spectrum's scale has 1/2N
+        I3[2 * j + 1] = (_Float16)(a.y * 0.5f);
         const uint32_t b = ((c * y) & 255u) << (TW_LOG2 - 8);
         const float2 w1 = tw_full(tw, (b + (y << (TW_LOG2 - 10))) & (TW_L - 1));
         const float2 w3 = tw_full(tw, (b + ((uint32_t)c << (TW_LOG2 - 10))) & (TW_L - 1));

@@ -541,17 +541,17 @@ void mfma_fill_plan(Plan& pl)
     pl.kscale = 1.0f / (L * c * c);
     pl.dkscale = 1.0f / (L * c * c * c);
     if (pl.order.wave_lg) {
-        const float n = 0.5f * L, cr = rows_chain_scale(pl.order.wave_lg);
-        pl.kscale = 1.0f / (n * cr * cr);
-        pl.dkscale = 1.0f / (n * cr * cr * cr);
+        const float cr = rows_chain_scale(pl.order.wave_lg);     // (N points, the inverse at twice the scale)
+        pl.kscale = 1.0f / (L * cr * cr);
+        pl.dkscale = 1.0f / (L * cr * cr * cr);
     }
     // outer radix 4 or 8 around the 32768-point cooperative kernels: the convolutions take pass A in their
     // staging (switch fuse_pass_a = 0 keeps the separate pass, for comparison)
     pl.fuse_a = pl.order.coop_lg == COOP_MAX_LOG2 && pl.log2R >= 1 && pl.log2R <= 3 && opt.fuse_pass_a;
     // ... and at outer radix 2 a row's N twisted points fit one compute unit (spectrum, forward, du; dk keeps the split)
+    // (N points instead of 2N: the factor of two comes behind the last fp16 value, in the row kernel's last block and, at
+    // outer radix 4, in pass C, so that the products with the spectrum are no larger than a pair's)
     pl.row1 = pl.fuse_a && pl.log2R == 1;
-    if (pl.row1) pl.kscale *= 2.0f;               // 1/N instead of 1/2N
-    if (rows_split(pl)) pl.kscale *= 2.0f;        // N points instead of 2N
     // one backward kernel where a wave group holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
     pl.fuse_bwd = pl.order.wave_lg && opt.fuse_bwd;
 }

@@ -49,7 +49,10 @@ struct RC {
     static constexpr int XW = TC == 1 ? 0 : TC * P;       // words of one exchange buffer
     static constexpr int SW = N / 2 + (TC == 4 ? 128 : 0);   // words of a staged row (see stage_word)
     static constexpr int COLS = 256 / TC;                 // columns of a phase-2 tile
-    static constexpr int SHIFT = 4 + (cb >= 3 ? 2 : (cb >= 1 ? 1 : 0));     // log2 of a chain's scale
+    // A forward chain scales by 2^-SHIFT, an inverse one by twice that, in its last block, whose result stays fp32.  N bins
+    // of N points are all the energy there is where a pair's transform had 2N, so at equal scales the products with the
+    // spectrum, in fp16, were 1.8 times as large as a pair's and rows of a mean A overflowed from A sum k = 1137 at N = 4096.
+    static constexpr int SHIFT = 4 + (cb >= 3 ? 2 : (cb >= 1 ? 1 : 0));
 };
 
 // ---- constant tables: lane-ordered 16-byte units, per length 6 units per tile and 4 common ones ---------------------
@@ -103,7 +106,8 @@ __global__ void fill_rows_tab_kernel(uint4* tab, int lg)
                 // conjugates, other index on the lanes
                 case 3: fb(yr, db_of(lg, x)); o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)im; break;
                 case 4: fb(yr, db_of(lg, x)); o.h[2 * q] = (_Float16)(-im); o.h[2 * q + 1] = (_Float16)re; break;
-                default: fa(yr, x); o.h[2 * q] = (_Float16)re; o.h[2 * q + 1] = (_Float16)im; break;
+                // twice as large: see SHIFT
+                default: fa(yr, x); o.h[2 * q] = (_Float16)(2.0 * re); o.h[2 * q + 1] = (_Float16)(2.0 * im); break;
             }
         }
     } else {

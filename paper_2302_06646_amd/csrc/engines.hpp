@@ -140,7 +140,7 @@ hipError_t sum_partials(const float* dk_part, float* dk, size_t n_dk, const floa
 // ---- single rows of N = 256 .. 4096 samples on the matrix cores (engine_rows.hip) -----------
 constexpr int ROWS_MIN_LOG2 = 8, ROWS_MAX_LOG2 = 12;
 hipError_t rows_fill_tables(const void** tab_out, hipStream_t st);
-float rows_chain_scale(int lg);      // scale of one transform of N = 2^lg samples
+float rows_chain_scale(int lg);      // scale of a forward transform of N = 2^lg samples; an inverse one has twice that
 // Spectrum (finds each head's pre-scale itself).  pad: see Problem::pad.
 hipError_t rows_kspec(const float* k, const float* D, float2* kspec, int64_t H, const Plan& pl, uint32_t pad, const Tables& tb,
                       hipStream_t st);

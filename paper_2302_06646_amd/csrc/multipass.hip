@@ -436,7 +436,8 @@ __global__ void __launch_bounds__(OB) outer_inv_rows_kernel(const __half2* __res
     const int n2 = ((blockIdx.x % nbx) * OB + threadIdx.x) * VEC;
     const int item = blockIdx.x / nbx, h = item / nrow;
     const size_t o = row_off(item - h * nrow, h, H, 2 * (int64_t)L2) + n2;
-    const float scale = ldexpf(1.0f, spec_exp[h] + (max_a ? mu::row_exponent(max_a[h]) : 0));
+    // (2: N points where the spectrum's scale has 1/2N)
+    const float scale = ldexpf(2.0f, spec_exp[h] + (max_a ? mu::row_exponent(max_a[h]) : 0));
     const __half2* src = ws + ((size_t)item << (log2L2 + 1)) + n2;
     uint32_t q0[VEC], q1[VEC];
     mu::load_words<VEC>(src, q0);

@@ -151,3 +151,26 @@ def test_dk_of_rows_with_a_mean(N, io):
         dk = g.bwd(du=du)[1]
         assert np.all(np.isfinite(dk))
         _compare({"dk": dk[heads]}, {"dk": want}, TOL[io], f"rows with a mean, N={N} io={wl.DTYPE_NAMES[io]} du={du}")
+
+
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("N", [256, 512, 1024, 2048, 4096, 32768, 65536])
+def test_outputs_of_rows_with_a_mean(N, io):
+    # A row of mean A meets sum k in the first bin: as 2N zero-padded points A sum k 2^(s-1), s the log2 of the transform's
+    # scale, which may come up to 0.9 of fp16's 65504; the N twisted points of single rows must leave as much room.
+    s = {256: 4, 512: 5, 1024: 5, 2048: 6, 4096: 6}.get(N, 7)
+    A, B, H = 8.0, 3, 2
+    K = 0.9 * 65504 / 2 ** (s - 1) / A
+    inp = wl.generate(wl.Workload(2, B, H, N, io, "squash_pool"))
+    (u_s, u_v), (dy_s, dy_v) = (wl.quantize((A + x).astype(np.float32), io) for x in (0.1 * inp.u, 0.1 * inp.dy))
+    k, D = inp.k.copy(), inp.D.copy()
+    k -= k.mean(axis=1, keepdims=True)           # (sum k is K: the taps' noise has no mean of its own)
+    k[:, 0] += K / 2
+    D[:] = K / 2
+    from gpu_harness import GpuRun, TOL, _compare
+    import oracle
+    g = GpuRun(dataclasses.replace(inp, u_store=u_s, dy_store=dy_s, u=u_v, dy=dy_v, k=k, D=D))
+    k64, D64 = k.astype(np.float64), D.astype(np.float64)
+    _compare({"y": g.fwd(), "du": g.bwd(dk=False, dD=False)[0]},
+             {"y": oracle.longconv_fwd(u_v, k64, D64), "du": oracle.longconv_bwd(dy_v, u_v, k64, D64)[0]}, TOL[io],
+             f"outputs of rows with a mean, N={N} io={wl.DTYPE_NAMES[io]}")
