@@ -170,11 +170,12 @@ int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float
  * [B,H,N1,N2] in the I/O dtype, N2 fastest; k, dk are [H,N1,N2] float32; D, dD are [H] float32.  N1 and N2 are
  * powers of two, N2 >= 8, and N = 2 N1 N2 meets the limits of N above (so images up to 256 x 256, or 128 x 512
  * and so on); B and H as above with that N.  Inside, every row of image and filter is zero padded to 2 N2 columns
- * in the workspace and the row-major sequence of N samples goes through longconv_fwd / longconv_bwd, which is
+ * (while it is loaded for fp16/bf16 I/O up to N = 4096, in the workspace otherwise) and the row-major sequence of N samples goes through longconv_fwd / longconv_bwd, which is
  * exact for this sum and as large as a 2-D transform of the padded image would be; accuracy, dtype rules and
  * stream behaviour are those of the 1-D call at that N.  The spectrum is always computed on the fly.
- * longconv2d_workspace_bytes (backward = 0 or 1) includes the padded copies: about 2 (forward) or 3 (backward)
- * tensors of twice the image's size, plus the 1-D call's own workspace; 0 on bad arguments. */
+ * longconv2d_workspace_bytes (backward = 0 or 1): the 1-D call's own workspace and, for the calls that pad in the
+ * workspace, the padded copies, about 2 (forward) or 3 (backward) tensors of twice the image's size; 0 on bad
+ * arguments. */
 size_t longconv2d_workspace_bytes(int64_t B, int64_t H, int64_t N1, int64_t N2, int io, int backward);
 int longconv2d_fwd(const void* u, const float* k, const float* D, void* y,
                    int64_t B, int64_t H, int64_t N1, int64_t N2, int io,

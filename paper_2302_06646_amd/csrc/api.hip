@@ -206,16 +206,18 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     const bool kscr = mc && pl.log2R && !pl.fuse_a;
     w.kscratch = off; if (kscr) off += up256((size_t)H * L * sizeof(float2));
     w.hscale = off; off += up256(head_stats_floats(H, N) * sizeof(float));
-    w.ws1 = off; if (pl.log2R) off += up256((size_t)H * npairs * L * cw_bytes(pl));
-    // (the fp32 engine takes pass A inside its kernels)
-    w.ws2 = off; if (pl.log2R && backward && pl.engine == ENGINE_MFMA) off += up256((size_t)H * npairs * L * cw_bytes(pl));
+    // rows that go from memory to memory (row1) have no chunks; pass A's outputs for dk, and what goes with them, belong to
+    // plans that run it as a kernel of its own (not the fp32 engine, and not where dk comes straight from the rows)
+    const bool outer_a = pl.engine == ENGINE_MFMA && !coop_dk_rows_ok(pl);
+    w.ws1 = off; if (pl.log2R && !pl.row1) off += up256((size_t)H * npairs * L * cw_bytes(pl));
+    w.ws2 = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npairs * L * cw_bytes(pl));
     w.wsA = off; if (pl.log2R && backward) off += up256((size_t)H * L * cw_bytes(pl));
     w.nblk = (int)(npairs * ((size_t(1) << pl.log2L2) / 256));
     const size_t npart = (size_t)w.nblk > (size_t(1) << pl.log2R) ? (size_t)w.nblk : (size_t(1) << pl.log2R);
-    w.dpart = off; if (pl.log2R && backward) off += up256((size_t)H * npart * sizeof(float));
+    w.dpart = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npart * sizeof(float));
     w.nsplit = backward ? dk_nsplit(B, H, pl) : 1;
     w.zbuf = off;
-    if (backward && pl.order.coop_lg) off += up256((size_t)H * L * sizeof(__half2));
+    if (backward && pl.order.coop_lg && outer_a) off += up256((size_t)H * L * sizeof(__half2));
     if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(H, w.nsplit, pl));
     // partial dk rows, or (fp32 engine, multi-pass) partial sets of pass C's complex chunks
     w.dkpart = off; if (w.nsplit > 1) off += up256((size_t)w.nsplit * H * (pl.log2R ? 2 * L : L / 2) * sizeof(float));
@@ -621,6 +623,8 @@ static Ws2d carve2d(int64_t B, int64_t H, int64_t N, int io, bool backward)
     const size_t rows = up256((size_t)B * H * N * io_bytes(io)), heads = up256((size_t)H * N * sizeof(float));
     size_t off = up256(longconv_workspace_bytes(B, H, N, io, backward ? 1 : 0));
     w.base = off;
+    w.total = off + (backward ? 256 : 0);          // (a backward size is above the forward one of its shape at every length)
+    if (pads_itself(make_plan(N, io))) return w;   // no copies
     w.kp = off;  off += heads;
     w.up = off;  off += rows;
     w.yp = off;  off += rows;                      // y of the forward pass, dy of the backward pass

@@ -53,6 +53,26 @@ def test_spectrum_size_is_exact_per_dtype():
         assert lc.longconv_kspec_bytes(8, 1024, io) == 8 * 2048 * 4 + 32
 
 
+def test_workspace_holds_nothing_that_no_kernel_touches():
+    # N = 32768 goes from rows to rows: an on-the-fly spectrum and per-head statistics, whatever the batch; dk adds its fp16
+    # chunks.  At 65536 and 131072 the pairs' (rows') chunks for pass C come on top, once, for forward and du.
+    H = 128
+    for io in (lc.F16, lc.BF16):
+        ks = lc.longconv_kspec_bytes(H, 32768, io)
+        one = lc.longconv_workspace_bytes(1, H, 32768, io, False)
+        assert ks <= one <= ks + (1 << 20)
+        assert lc.longconv_workspace_bytes(32, H, 32768, io, False) == one <= lc.STATIC_SCRATCH_BYTES
+        assert lc.longconv_workspace_bytes(32, H, 32768, io, True) <= one + H * 65536 * 4 + (1 << 16)
+        for N in (65536, 131072):
+            f, b = (lc.longconv_workspace_bytes(32, 8, N, io, bwd) for bwd in (False, True))
+            assert f >= 32 * 8 * N * 4 and b <= f + 8 * 2 * N * 4 + (1 << 16)
+        # images up to N = 4096 padded samples are padded on their way in, larger ones in the workspace
+        for bwd in (False, True):
+            assert lc.longconv2d_workspace_bytes(64, 256, 32, 32, io, bwd) <= lc.longconv_workspace_bytes(64, 256, 2048, io, bwd) + 256
+            assert lc.longconv2d_workspace_bytes(4, 8, 64, 64, io, bwd) >= 2 * 4 * 8 * 8192 * 2
+    assert lc.longconv2d_workspace_bytes(4, 8, 32, 32, lc.F32, False) >= 2 * 4 * 8 * 2048 * 4
+
+
 def test_plan_string_names_what_runs():
     # rows of N twisted points at N <= 4096, 32768 and 65536, pairs of 2N zero-padded ones elsewhere; fields a program may
     # look for stay in front

@@ -52,6 +52,11 @@ def test_no_alloc_forward_matches_longconv_fwd_twice_in_a_row(cached):
     _both(wl.generate(wl.WORKLOADS["1"], B=1, H=2), cached)
 
 
+def test_no_alloc_forward_of_32768_samples_whatever_the_batch():
+    # (rows go from memory to memory there: the array holds the spectrum alone)
+    _both(wl.generate(wl.Workload(3, 20, 25, 32768, wl.F16, "decay_alpha_squash")), True)
+
+
 def test_no_alloc_forward_refuses_what_does_not_fit():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
