@@ -933,20 +933,32 @@ __device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2
 // The accumulator goes into dk's inverse transform as fp16, and as a sum over rows it has no bound of its own (rows with a
 // mean add up in the first bins: 0.8 N^2 / 4^SHIFT times the product of the means per row, 3300 at N = 4096).  So its
 // largest component is brought to 2^7 .. 2^8 by a power of two, which dk gets back in fp32: the inverse grows a
-// component by at most sqrt(2) N / 2^SHIFT <= 91, which stays below fp16's 65504.  This wave's largest component:
-template <int NA>
-__device__ __forceinline__ float acc_peak(const float2 (&acc)[NA][4])
+// component by at most sqrt(2) N / 2^SHIFT <= 91, which stays below fp16's 65504.  This wave's largest component, as
+// the pattern of its magnitude, without a trip through LDS (a butterfly of __shfl_xor cost calls of one row 0.2 us):
+__device__ __forceinline__ uint32_t wave_umax(uint32_t q)
 {
-    float m = 0.f;
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0xB1, 0xf, 0xf, true));       // quad_perm: lanes ^ 1
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x4E, 0xf, 0xf, true));       // lanes ^ 2
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x141, 0xf, 0xf, true));      // row_half_mirror
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x140, 0xf, 0xf, true));      // row_mirror
+    uint32_t s = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s = max(s, (uint32_t)__builtin_amdgcn_readlane((int)q, 16 * j));
+    return s;
+}
+template <int NA>
+__device__ __forceinline__ uint32_t acc_peak(const float2 (&acc)[NA][4])
+{
+    uint32_t m = 0u;
 #pragma unroll
     for (int k = 0; k < NA; ++k)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) m = fmaxf(m, fmaxf(fabsf(acc[k][j].x), fabsf(acc[k][j].y)));
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    return m;
+        for (int j = 0; j < 4; ++j)
+            m = max(m, max(__float_as_uint(acc[k][j].x) & 0x7fffffffu, __float_as_uint(acc[k][j].y) & 0x7fffffffu));
+    return wave_umax(m);
 }
 // exponent of the power of two an accumulator whose largest component is m is divided by
-__device__ __forceinline__ int acc_exponent(float m) { return (int)(__float_as_uint(m) >> 23) - (127 + 7); }
+__device__ __forceinline__ int acc_exponent(uint32_t m) { return (int)(m >> 23) - (127 + 7); }
 
 // -------------------------------------------------------------------------------------
 // Whole backward pass of a head (or of a share of its rows) per workgroup, rows shared by NWR waves (N >= 1024): du, dk
@@ -1210,14 +1222,14 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
     if (lane == 0) dred[wave] = dsum;
     int etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
-    float* peaks = reinterpret_cast<float*>(mxs);        // [NWR] (the rows' patterns are done with)
-    const float peak = acc_peak<2>(acc);
+    uint32_t* peaks = mxs;                               // [NWR] (the rows' patterns are done with)
+    const uint32_t peak = acc_peak<2>(acc);
     if (lane == 0 && grp == 0) peaks[wave] = peak;
     __syncthreads();                                     // (the reduction's words lie in the buffers that follow, too)
     if (q.dk) {
-        float m = peaks[0];
+        uint32_t m = peaks[0];
 #pragma unroll
-        for (int w = 1; w < NWR; ++w) m = fmaxf(m, peaks[w]);
+        for (int w = 1; w < NWR; ++w) m = max(m, peaks[w]);
         const int ea = __builtin_amdgcn_readfirstlane(acc_exponent(m));
         etop += ea;
         float* fs = reinterpret_cast<float*>(lds + 2 * C::XW);        // the row of dk in the u buffers of the first group
@@ -1435,7 +1447,7 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
     if (wave != 0) return;
     if (lane == 0 && q.dD) q.dD[ho] = ((dred[0] + dred[1]) + dred[2]) + dred[3];
     if (!q.dk) return;
-    const int ea = __builtin_amdgcn_readfirstlane(acc_exponent(acc_peak<NS>(acc)));
+    const int ea = acc_exponent(acc_peak<NS>(acc));
     etop += ea;
 #pragma unroll
     for (int k = 0; k < NS; ++k)
