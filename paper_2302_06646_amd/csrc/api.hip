@@ -176,10 +176,10 @@ struct WsLayout {
 
 // Single-pass matrix-core plans: the dk kernels run one workgroup per head; with few heads the pairs of a head are
 // dealt to `nsplit` workgroups (about 384 in all), whose partial dk and dD are then summed in a fixed order.
-static int dk_nsplit(int64_t B, int64_t H, const Plan& pl)
+static int dk_nsplit(int64_t B, int64_t H, const Plan& pl, bool gated)
 {
     if (pl.engine == ENGINE_VALU) return valu_bwd_nsplit(H, (int)((B + 1) / 2), pl);
-    if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_nsplit(B, H, pl.order.wave_lg);
+    if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_nsplit(B, H, pl.order.wave_lg, gated);
     if (pl.engine != ENGINE_MFMA || pl.log2R || !pl.order.coop_lg) return 1;
     const int64_t npairs = (B + 1) / 2;
     int64_t s = 384 / H;
@@ -215,7 +215,7 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     w.nblk = (int)(npairs * ((size_t(1) << pl.log2L2) / 256));
     const size_t npart = (size_t)w.nblk > (size_t(1) << pl.log2R) ? (size_t)w.nblk : (size_t(1) << pl.log2R);
     w.dpart = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npart * sizeof(float));
-    w.nsplit = backward ? dk_nsplit(B, H, pl) : 1;
+    w.nsplit = backward ? dk_nsplit(B, H, pl, true) : 1;      // (room for the gated pass, which never has fewer shares)
     w.zbuf = off;
     if (backward && pl.order.coop_lg && outer_a) off += up256((size_t)H * L * sizeof(__half2));
     if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(H, w.nsplit, pl));
@@ -503,7 +503,7 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
                 return LONGCONV_ERR_HIP;
             ks = (const float2*)(base + w.kspec);
         }
-        const int ns = w.nsplit;
+        const int ns = dk_nsplit(B, H, pl, gate != nullptr);
         float* dkp = (float*)(base + w.dkpart);
         float* ddp = (float*)(base + w.ddpart);
         hipError_t e = rows_bwd(dy, u, ks, du, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD ? ddp : nullptr) : dD, dg, ns,
@@ -558,7 +558,7 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
                 if (e == hipSuccess && dD) e = reduce_dD(dpart, dD, H, w.nblk, st);
             }
             if (e == hipSuccess && (dk || !pl.log2R)) {
-                const int ns = w.nsplit;
+                const int ns = dk_nsplit(B, H, pl, false);
                 float* dkp = (float*)(base + w.dkpart);
                 float* ddp = (float*)(base + w.ddpart);
                 float* dD1 = pl.log2R ? nullptr : dD;

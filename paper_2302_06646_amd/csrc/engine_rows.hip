@@ -22,8 +22,9 @@
 //   phase 3 (tile d_c):   X = k_a, Y = k_b -[F16^-1 over k_b]-> X = d_b, Y = k_a * conj(w_256^(k_a d_b))
 //                         -[F16^-1 over k_a, real part only]-> X = d_b, Y = d_a: samples
 // The twist w^-n and all factors that depend on d_c are folded into the matrices of the tile's two 16-point blocks,
-// so one twiddle table (four words per lane) serves every tile and both directions.  A wave owns tiles 2w, 2w+1 of
-// all three phases and keeps their constants in registers; TC/2 waves share a row.
+// so one twiddle table (four words per lane) serves every tile and both directions.  Constants stay in registers.
+// From N = 2048 on a wave owns tiles 2w, 2w+1 of all three phases and TC/2 waves share a row; up to N = 1024 a wave owns
+// whole rows, at N = 1024 with four tiles (the gated backward pass, which has no registers for them, shares it between two).
 #include "engines.hpp"
 #include "mfma_util.hpp"
 
@@ -42,7 +43,9 @@ struct RC {
     static constexpr int N = 1 << LG, cb = LG - 8, TC = 1 << cb;
     static constexpr int NWR = TC >= 4 ? TC / 2 : 1;      // waves that share a row
     static constexpr int RPI = TC == 1 ? 2 : 1;           // rows a group of waves takes at a time
-    static constexpr int NS = TC == 1 ? 1 : 2;            // tiles of a wave with constants and bins of their own
+    static constexpr int NS = TC == 1 ? 1 : 2;            // of a pair of tiles: those with constants and bins of their own
+    // kernels whose waves own whole rows: pairs of tiles of a wave (one row's up to N = 1024), and tiles with their own constants
+    static constexpr int NP = TC == 4 ? 2 : 1, NT = NP * NS;
     // words between the planes of two d_c in the exchange buffer: phase 2 reads four planes at once, and these
     // strides put its 64 lanes on 64 banks
     static constexpr int P = TC == 16 ? 260 : (TC == 8 ? 264 : 256);
@@ -136,24 +139,24 @@ __global__ void fill_rows_tab_kernel(uint4* tab, int lg)
     tab[(size_t)unit * 64 + lane] = o.u;
 }
 
-template <int LG>
+template <int LG, int NT = RC<LG>::NS>
 struct RK {
-    h4 fa_re[RC<LG>::NS], fa_im[RC<LG>::NS];      // [F16 over d_a]: B operand of a 16x16x16 product
-    h8 b_re[RC<LG>::NS], b_im[RC<LG>::NS];        // [F16 over d_b]: A operand
-    h8 bi_re[RC<LG>::NS], bi_im[RC<LG>::NS];      // its adjoint: B operand
-    h8 ai[RC<LG>::NS];                            // adjoint of [F16 over d_a], real rows of the product only
+    h4 fa_re[NT], fa_im[NT];      // [F16 over d_a]: B operand of a 16x16x16 product
+    h8 b_re[NT], b_im[NT];        // [F16 over d_b]: A operand
+    h8 bi_re[NT], bi_im[NT];      // its adjoint: B operand
+    h8 ai[NT];                            // adjoint of [F16 over d_a], real rows of the product only
     H8U t1, t1i;                                  // w_256^(k_a d_b), k_a (t1) or d_b (t1i) on the lanes
     h8 c_re, c_im;                                // I (x) F_TC
 };
-template <int LG>
-__device__ __forceinline__ void load_consts(RK<LG>& K, const uint4* __restrict__ tab, int t0, int lane)
+template <int LG, int NT>
+__device__ __forceinline__ void load_consts(RK<LG, NT>& K, const uint4* __restrict__ tab, int t0, int lane)
 {
     using C = RC<LG>;
     const uint4* p = tab + (size_t)tab_offset(LG) * 64 + lane;
     union { uint4 u; struct { h4 a, b; } h; } v;
     H8U x;
 #pragma unroll
-    for (int k = 0; k < C::NS; ++k) {
+    for (int k = 0; k < NT; ++k) {
         const uint4* q = p + (size_t)(t0 + k) * 6 * 64;
         v.u = q[0]; K.fa_re[k] = v.h.a; K.fa_im[k] = v.h.b;
         x.u = q[64]; K.b_re[k] = x.v;
@@ -174,11 +177,11 @@ __device__ __forceinline__ void load_consts(RK<LG>& K, const uint4* __restrict__
 // for since.
 __device__ __forceinline__ void arrived(h8& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void arrived(h4& v) { asm volatile("" : "+v"(v)); }
-template <int LG>
-__device__ __forceinline__ void arrived(RK<LG>& K)
+template <int LG, int NT>
+__device__ __forceinline__ void arrived(RK<LG, NT>& K)
 {
 #pragma unroll
-    for (int k = 0; k < RC<LG>::NS; ++k) {
+    for (int k = 0; k < NT; ++k) {
         arrived(K.fa_re[k]); arrived(K.fa_im[k]); arrived(K.ai[k]);
         arrived(K.b_re[k]); arrived(K.b_im[k]); arrived(K.bi_re[k]); arrived(K.bi_im[k]);
     }
@@ -229,12 +232,14 @@ __device__ __forceinline__ void word_offsets(uint32_t (&off)[4], int t0, int lan
 // ---- bf16 rows: exponent of the power of two a row is divided by -----------------------------------------------------
 // Largest-magnitude pattern over the words of one wave: the stand-in BAND_LOW if the cheap test shows that they lie in
 // 2 .. 8, otherwise measured.  At N = 256 lanes 0-7 and 8-15 of every 16 hold different rows: m[0], m[1].
-template <int RPI>
-__device__ __forceinline__ void words_max(const uint32_t (&w)[4], uint32_t (&m)[RPI])
+template <int RPI, int NP>
+__device__ __forceinline__ void words_max(const uint32_t (&w)[NP][4], uint32_t (&m)[RPI])
 {
     uint32_t a = 0u;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a = absmax_acc(a, w[r]);
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a = absmax_acc(a, w[p][r]);
     if constexpr (RPI == 1) {
         m[0] = a;
         band_or_exact<1>(m);
@@ -295,7 +300,7 @@ __device__ __forceinline__ uint32_t cmul_swap(float yr, float yi, h2 w)
     return cv.u;
 }
 
-// Phase 1 of the wave's two tiles.  w: raw words of the row(s); e: exponents (bf16 rows only).  The result goes to the
+// Phase 1 of a pair of the wave's tiles (pair p: 2p, 2p + 1 of them).  w: raw words of the row(s); e: exponents (bf16 rows only).  The result goes to the
 // exchange buffer at xw (this lane's place in plane t0), at N = 256 it stays in registers: z[row][k_b % 4] complex.
 template <int LG, class IO, bool SCALED>
 __device__ __forceinline__ void phase1_ops(const uint32_t (&w)[4], int e0, int e1, int lane, h4 (&op)[2])
@@ -317,17 +322,18 @@ __device__ __forceinline__ void phase1_ops(const uint32_t (&w)[4], int e0, int e
         op[1] = h4_of(__builtin_amdgcn_perm(w[1], w[0], 0x07060302u), __builtin_amdgcn_perm(w[3], w[2], 0x07060302u));
     }
 }
-template <int LG>
-__device__ __forceinline__ void phase1(const h4 (&op)[2], const RK<LG>& K, uint32_t* xw, f4 (&zr)[2], f4 (&zi)[2])
+template <int LG, int NT>
+__device__ __forceinline__ void phase1(const h4 (&op)[2], const RK<LG, NT>& K, uint32_t* xw, f4 (&zr)[2], f4 (&zi)[2], int p = 0)
 {
     using C = RC<LG>;
+    xw += 2 * p * C::P;
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 r[2], s[2];
     H8U m[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        r[k] = MFMA16(op[k], K.fa_re[k % C::NS], zero);
-        s[k] = MFMA16(op[k], K.fa_im[k % C::NS], zero);
+        r[k] = MFMA16(op[k], K.fa_re[2 * p + k % C::NS], zero);
+        s[k] = MFMA16(op[k], K.fa_im[2 * p + k % C::NS], zero);
     }
     if constexpr (C::TC == 1) {
         // tile k holds d_b = 2j + k of row 0 in its first 32 lanes and of row 1 in the others: exchanged to tile = row
@@ -345,8 +351,8 @@ __device__ __forceinline__ void phase1(const h4 (&op)[2], const RK<LG>& K, uint3
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        zr[k] = MFMA(K.b_re[k % C::NS], m[k].v, zero);
-        zi[k] = MFMA(K.b_im[k % C::NS], m[k].v, zero);
+        zr[k] = MFMA(K.b_re[2 * p + k % C::NS], m[k].v, zero);
+        zi[k] = MFMA(K.b_im[2 * p + k % C::NS], m[k].v, zero);
     }
     if constexpr (C::TC > 1) {
 #pragma unroll
@@ -387,8 +393,8 @@ __device__ __forceinline__ void phase2_read(const uint32_t* xp, H8U (&m)[2])
 #pragma unroll
     for (int r = 0; r < 4; ++r) m[1].w[r] = xq[p2_off<LG>(r)];
 }
-template <int LG>
-__device__ __forceinline__ void phase2_fwd(const H8U (&m)[2], const RK<LG>& K, f4 (&yr)[2], f4 (&yi)[2])
+template <int LG, int NT>
+__device__ __forceinline__ void phase2_fwd(const H8U (&m)[2], const RK<LG, NT>& K, f4 (&yr)[2], f4 (&yi)[2])
 {
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -396,8 +402,8 @@ __device__ __forceinline__ void phase2_fwd(const H8U (&m)[2], const RK<LG>& K, f
 }
 // inverse half, in place; m: words with real and imaginary part exchanged (the forward blocks then give the
 // adjoint's result, exchanged again)
-template <int LG>
-__device__ __forceinline__ void phase2_inv(uint32_t* xp, const RK<LG>& K, const H8U (&m)[2])
+template <int LG, int NT>
+__device__ __forceinline__ void phase2_inv(uint32_t* xp, const RK<LG, NT>& K, const H8U (&m)[2])
 {
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 zr[2], zi[2];
@@ -417,16 +423,16 @@ __device__ __forceinline__ void phase3_read(const uint32_t* xw, H8U (&m)[2])
 #pragma unroll
     for (int k = 0; k < 2; ++k) m[k].u = *reinterpret_cast<const uint4*>(xw + k * RC<LG>::P);
 }
-template <int LG>
-__device__ __forceinline__ void phase3(H8U (&m)[2], const RK<LG>& K, f4 (&v)[2])
+template <int LG, int NT>
+__device__ __forceinline__ void phase3(H8U (&m)[2], const RK<LG, NT>& K, f4 (&v)[2], int p = 0)
 {
     using C = RC<LG>;
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 r[2], s[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        r[k] = MFMA(m[k].v, K.bi_re[k % C::NS], zero);
-        s[k] = MFMA(m[k].v, K.bi_im[k % C::NS], zero);
+        r[k] = MFMA(m[k].v, K.bi_re[2 * p + k % C::NS], zero);
+        s[k] = MFMA(m[k].v, K.bi_im[2 * p + k % C::NS], zero);
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k)
@@ -442,7 +448,7 @@ __device__ __forceinline__ void phase3(H8U (&m)[2], const RK<LG>& K, f4 (&v)[2])
         }
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) v[k] = MFMA(K.ai[k % C::NS], m[k].v, zero);
+    for (int k = 0; k < 2; ++k) v[k] = MFMA(K.ai[2 * p + k % C::NS], m[k].v, zero);
 }
 template <class IO>
 __device__ __forceinline__ uint32_t pack_io(float a, float b) { return IsBf<IO>::v ? pack_bf2(a, b) : pack_h2(a, b); }
@@ -500,18 +506,19 @@ __device__ __forceinline__ uint32_t out_word(float a, float b, int ex)
 }
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u4v buf_load4(rsrc_t r, uint32_t off)
 {
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
 }
 // -------------------------------------------------------------------------------------
-// Convolution of all rows, rows shared by NWR waves (N >= 1024).  Persistent workgroups, each with a run of consecutive
+// Convolution of all rows, rows shared by NWR waves (N >= 2048).  Persistent workgroups, each with a run of consecutive
 // rows (head by head).  Software pipeline over rows, one barrier per row: iteration t stores row t - 3, runs phase 3 of
 // row t - 2, phase 2 of row t - 1 and phase 1 of row t, puts row t + 1 into LDS and asks for row t + 2.  Phase 3 reads
 // the planes that the same wave's phase 1 then writes, so two exchange buffers serve all three phases.
 // Loads and stores are issued in every iteration, with an empty descriptor where there is no row: conditional ones
 // would make the compiler wait for younger requests than it has to.
-// Bound by matrix and vector issue, which add up.  B=16, H=768, N=1024 bf16: 23.7 us, 54.6 MB moved (2.3 TB/s).
+// Bound by matrix and vector issue, which add up.
 // Whole steps, row pairs in 2N points against rows: B=64, H=1024, N=4096 1556 -> 838 us; N=256 85 -> 67 us.
 // -------------------------------------------------------------------------------------
 template <int LG, class IO, bool CONJ, bool GATE>
@@ -560,8 +567,8 @@ rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
     auto arrive = [&](int t) {
         if constexpr (BF) {
             uint32_t m[1];
-            const uint32_t w[4] = {rr[0], rr[1], rr[2], rr[3]};
-            words_max<1>(w, m);
+            const uint32_t w[1][4] = {{rr[0], rr[1], rr[2], rr[3]}};
+            words_max(w, m);
             if (lane == 0) mxs[(t & 1) * 8 + wave] = m[0];
         }
         *reinterpret_cast<u4v*>(raw + (t & 1) * C::SW + sf) = rr;
@@ -653,17 +660,47 @@ rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
     }
 }
 
-// The same for rows that one wave owns (N = 256: two rows at a time; N = 512): no barrier, no staging (a wave's words
-// already cover 32 or 64 contiguous bytes).
+// Words of pass rows at the lane's offsets: one load of 8 bytes where the wave owns two pairs of tiles.
+template <int NP>
+__device__ __forceinline__ void load_words(rsrc_t d, const uint32_t (&off)[4], uint32_t (&w)[NP][4])
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (NP == 2) {
+            const u2v v = __builtin_amdgcn_raw_buffer_load_b64(d, (int)off[r], 0, 0);
+            w[0][r] = v[0]; w[1][r] = v[1];
+        } else {
+            w[0][r] = buf_load(d, off[r]);
+        }
+    }
+}
+template <int NP>
+__device__ __forceinline__ void store_words(rsrc_t d, const uint32_t (&off)[4], const uint32_t (&w)[NP][4])
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (NP == 2) {
+            const u2v v = {w[0][r], w[1][r]};
+            __builtin_amdgcn_raw_buffer_store_b64(v, d, (int)off[r], 0, 0);
+        } else {
+            buf_store(d, off[r], w[0][r]);
+        }
+    }
+}
+
+// The same for rows that one wave owns (N = 256: two rows at a time; N = 512; N = 1024: four tiles): no barrier, no
+// staging (a wave's words already cover 32 to 128 contiguous bytes), and nothing to fill and drain for a wave's few rows.
+// N = 1024 as a row pipeline of two waves (rconv_kernel's), kernel time in us, there -> here, bf16: B=1, H=768
+// 6.7 -> 4.8; B=16, H=256 12.2 -> 8.6; B=16, H=768 21.3 -> 17.1; B=64, H=1024 75.7 -> 68.9 (3.9 TB/s).
 template <int LG, class IO, bool CONJ, bool GATE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RC<LG>::NP == 2 ? 2 : 4)))
 rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
               const typename IO::T* __restrict__ gate, int B, int H, int bpi, int items, uint32_t pad,
               const uint4* __restrict__ tab)
 {
     using C = RC<LG>;
     constexpr bool BF = IsBf<IO>::v;
-    constexpr int NSP = C::NS;
+    constexpr int NP = C::NP, NT = C::NT;
     __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : 4 * C::XW];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ng = gridDim.x * 4, g = xcd_swizzle(blockIdx.x, gridDim.x) * 4 + wave;
@@ -682,39 +719,48 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
     auto rsrc = [&](const RowPtr& q) { return make_rsrc(q.p, C::RPI == 2 && q.b != odd ? row_bytes + row_step : row_bytes); };
     uint32_t off[4];
     word_offsets<LG>(off, 0, lane, pad, row_step);
-    uint32_t w[4], gn[4] = {0u, 0u, 0u, 0u};
-    auto load = [&](RowPtr& q, uint32_t (&v)[4], bool any) {      // (an empty descriptor where there is no row)
-        const rsrc_t d = any ? rsrc(q) : make_rsrc(q.p, 0u);
+    uint32_t w[NP][4], gn[NP][4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = buf_load(d, off[r]);
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) gn[p][r] = 0u;
+    auto load = [&](RowPtr& q, uint32_t (&v)[NP][4], bool any) {  // (an empty descriptor where there is no row)
+        load_words<NP>(any ? rsrc(q) : make_rsrc(q.p, 0u), off, v);
         q.next(bpi, step, wrap);
     };
     load(pi, w, true);
     if (GATE) load(pg, gn, true);
-    RK<LG> K;
+    RK<LG, NT> K;
     load_consts<LG>(K, tab, 0, lane);
     uint32_t* xb = xbuf + (C::TC == 1 ? 0 : wave * C::XW);
     uint32_t* xw = xb + 4 * lane;
     uint32_t* xp = xb + p2_base<LG>(0, lane);
-    H8U kk[NSP];
+    H8U kk[NT];
     arrived(K);
     int es = 0;
     int ea = 0, eb = 0;                                           // exponents (bf16) of the pass's row(s)
     auto iter = [&](auto mode, int i) {
         using M = decltype(mode);
-        h4 op[2];
+        h4 op[NP][2];
         f4 zr[2], zi[2], v[2];
         H8U m[2];
-        uint32_t ga[4];
-        phase1_ops<LG, IO, M::scaled>(w, ea, eb, lane, op);
+        uint32_t ga[NP][4], o[NP][4];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) phase1_ops<LG, IO, M::scaled>(w[p], ea, eb, lane, op[p]);
         if (GATE) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ga[r] = gn[r];
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) ga[p][r] = gn[p][r];
         }
         load(pi, w, i + 1 < i1);
         if (GATE) load(pg, gn, i + 1 < i1);
         SCHED_FENCE();                                  // (the loads go out here)
-        phase1<LG>(op, K, xw, zr, zi);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            phase1<LG>(op[p], K, xw, zr, zi, p);
+            if (NP > 1) SCHED_FENCE();
+        }
         if constexpr (C::TC == 1) {
 #pragma unroll
             for (int k = 0; k < 2; ++k)
@@ -723,24 +769,32 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
                     m[k].w[r] = CONJ ? cmul_pack_conj(zr[k][r], zi[k][r], kk[0].c[r]) : cmul_pack(zr[k][r], zi[k][r], kk[0].c[r]);
         } else {
             wave_lds_fence();
-            f4 yr[2], yi[2];
-            phase2_read<LG>(xp, m);
-            phase2_fwd<LG>(m, K, yr, yi);
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int p = 0; p < NP; ++p) {
+                f4 yr[2], yi[2];
+                phase2_read<LG>(xp + 2 * p * C::COLS, m);
+                phase2_fwd<LG>(m, K, yr, yi);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_swap<CONJ>(yr[k][r], yi[k][r], kk[k % NSP].c[r]);
-            phase2_inv<LG>(xp, K, m);
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m[k].w[r] = cmul_swap<CONJ>(yr[k][r], yi[k][r], kk[2 * p + k % C::NS].c[r]);
+                phase2_inv<LG>(xp + 2 * p * C::COLS, K, m);
+                if (NP > 1) SCHED_FENCE();
+            }
             wave_lds_fence();
-            phase3_read<LG>(xw, m);
         }
-        phase3<LG>(m, K, v);
         const int ex = es + (C::TC == 1 && (lane & 8) ? eb : ea);
-        const rsrc_t d = rsrc(po);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            buf_store(d, off[r], GATE ? out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(ga[r]), v[1][r] * hi_of<IO>(ga[r]), ex)
-                                      : out_word<IO, M::scaled>(v[0][r], v[1][r], ex));
+        for (int p = 0; p < NP; ++p) {
+            if constexpr (C::TC > 1) phase3_read<LG>(xw + 2 * p * C::P, m);
+            phase3<LG>(m, K, v, p);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                o[p][r] = GATE ? out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(ga[p][r]), v[1][r] * hi_of<IO>(ga[p][r]), ex)
+                               : out_word<IO, M::scaled>(v[0][r], v[1][r], ex);
+            if (NP > 1) SCHED_FENCE();
+        }
+        store_words<NP>(rsrc(po), off, o);
         po.next(bpi, step, wrap);
         h += po.b == 0;
     };
@@ -749,14 +803,14 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
         if (i == i0 || po.b == 0) {
             const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
 #pragma unroll
-            for (int k = 0; k < NSP; ++k) kk[k].u = ks[k * 64 + lane];
+            for (int k = 0; k < NT; ++k) kk[k].u = ks[k * 64 + lane];
             es = spec_exp_of(kspec, H, 2 * C::N)[h];
 #pragma unroll
-            for (int k = 0; k < NSP; ++k) arrived(kk[k].v);
+            for (int k = 0; k < NT; ++k) arrived(kk[k].v);
         }
         if constexpr (BF) {
             uint32_t m[C::RPI];
-            words_max<C::RPI>(w, m);
+            words_max(w, m);
             ea = row_exponent(m[0]);
             if (C::RPI == 2) eb = row_exponent(m[C::RPI - 1]);
         }
@@ -961,7 +1015,8 @@ __device__ __forceinline__ uint32_t acc_peak(const float2 (&acc)[NA][4])
 __device__ __forceinline__ int acc_exponent(uint32_t m) { return (int)(m >> 23) - (127 + 7); }
 
 // -------------------------------------------------------------------------------------
-// Whole backward pass of a head (or of a share of its rows) per workgroup, rows shared by NWR waves (N >= 1024): du, dk
+// Whole backward pass of a head (or of a share of its rows) per workgroup, rows shared by NWR waves (N >= 2048, gated
+// N >= 1024): du, dk
 // and dD from one read of dy and u.  Per row: W = transform of dy, U = transform of u, du = inverse of W conj(K),
 // A += conj(U) W in fp32 registers; dk is one inverse transform of A at the end.  Software pipeline as in rconv_kernel:
 // phase 1 of both rows t, phase 2 of rows t - 1, phase 3 of du's row t - 2, row t - 3 stored, one barrier per row.
@@ -1003,8 +1058,8 @@ __device__ __forceinline__ float gate_words(uint32_t (&d)[4], const uint32_t (&g
     return s;
 }
 
-// Three transforms per row against the convolution's two, at half its waves per SIMD (accumulators).  B=16, H=768, N=1024 bf16:
-// 42.3 us, 82.5 MB moved (row pairs: 48 us); gated step B=7, H=193, N=2048: five kernels 93 us, this one 41 us.
+// Three transforms per row against the convolution's two, at half its waves per SIMD (accumulators).
+// Gated step B=7, H=193, N=2048: five kernels 93 us, this one 41 us.
 template <int LG, class IO, bool DU, bool GATE>
 __global__ void __launch_bounds__((BwdCfg<LG, GATE>::NWV * 64)) __attribute__((amdgpu_waves_per_eu(2)))
 rbwd_kernel(const BwdArgs<typename IO::T> q)
@@ -1086,8 +1141,9 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
         }
         if constexpr (BF) {
             uint32_t m1[1], m2[1];
-            words_max<1>(d, m1);
-            words_max<1>(v, m2);
+            const uint32_t d1[1][4] = {{d[0], d[1], d[2], d[3]}}, v1[1][4] = {{v[0], v[1], v[2], v[3]}};
+            words_max(d1, m1);
+            words_max(v1, m2);
             if (lane == 0) *reinterpret_cast<uint2*>(mxs + ((t & 1) * 8 + wave) * 2) = make_uint2(m1[0], m2[0]);
         }
         *reinterpret_cast<uint4*>(raw + (t & 1) * C::SW + sf) = make_uint4(d[0], d[1], d[2], d[3]);
@@ -1268,17 +1324,23 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
     }
 }
 
-// The same for rows that one wave owns (N = 256: two rows at a time; N = 512): four independent waves per workgroup.
-template <int LG, class IO, bool DU, bool GATE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+// The same for rows that one wave owns (N = 256: two rows at a time; N = 512; N = 1024: four tiles), NWV independent waves
+// per workgroup.  N = 1024 as a row pipeline (rbwd_kernel, two groups of two waves), kernel time in us, there -> here,
+// bf16: B=1, H=768 16.5 -> 8.1; B=5, H=64 12.0 -> 9.7; B=16, H=256 20.3 -> 14.4; B=16, H=768 37.4 -> 30.2; B=64, H=1024
+// 137 -> 110.  (Gated it spills 50 registers and more, and is 1.5 times as slow as the pipeline.)
+template <int LG, class IO, bool DU, bool GATE, int NWV>
+__global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 rbwd1_kernel(const BwdArgs<typename IO::T> q)
 {
     using C = RC<LG>;
     static_assert(DU || !GATE, "the gated form comes with du");
     constexpr bool BF = IsBf<IO>::v;
-    constexpr int NS = C::NS, NWV = 4;
+    constexpr int NP = C::NP, NS = C::NS, NT = C::NT;
+    // the reduction's words: at N = 1024 in the exchange buffers, which are as large (two workgroups per compute unit)
     __shared__ __align__(16) uint32_t xbuf[C::TC == 1 ? 4 : NWV * 2 * C::XW];
-    __shared__ float2 red[NWV * NS * 4 * 64];
+    __shared__ float2 own[NP > 1 ? 1 : NWV * NT * 4 * 64];
+    static_assert(NP == 1 || 2 * C::XW == NT * 4 * 64 * 2, "the accumulators of a wave fill its exchange buffers");
+    float2* red = NP > 1 ? reinterpret_cast<float2*>(xbuf) : own;
     __shared__ float dred[NWV];
     __shared__ int erefs[NWV];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1296,14 +1358,10 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
     char* pdg = reinterpret_cast<char*>(q.dg) + o0;
     uint32_t off[4];
     word_offsets<LG>(off, 0, lane, pad, row_step);
-    uint32_t wd[4], wu[4], gn[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) wd[r] = wu[r] = gn[r] = 0u;
+    uint32_t wd[NP][4], wu[NP][4], gn[NP][4];
     auto bytes_of = [&](int p) { return C::RPI == 2 && p != odd ? row_bytes + row_step : row_bytes; };
-    auto load = [&](const char*& ptr, int p, uint32_t (&w)[4]) {
-        const rsrc_t d = make_rsrc(ptr, p < npass ? bytes_of(p) : 0u);      // (an empty descriptor where there is no row)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = buf_load(d, off[r]);
+    auto load = [&](const char*& ptr, int p, uint32_t (&w)[NP][4]) {
+        load_words<NP>(make_rsrc(ptr, p < npass ? bytes_of(p) : 0u), off, w);      // (an empty descriptor where there is no row)
         ptr += step;
     };
     auto load_all = [&](int p) {
@@ -1312,110 +1370,135 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
         if (GATE) load(pg, p, gn);
     };
     load_all(p0);
-    RK<LG> K;
+    RK<LG, NT> K;
     load_consts<LG>(K, q.tab, 0, lane);
-    H8U kk[NS];
+    H8U kk[NT];
     int es = 0;
     if (DU) {
         const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(q.kspec) + (size_t)h * 2 * C::N);
 #pragma unroll
-        for (int k = 0; k < NS; ++k) kk[k].u = ks[k * 64 + lane];
+        for (int k = 0; k < NT; ++k) kk[k].u = ks[k * 64 + lane];
         es = spec_exp_of(q.kspec, H, 2 * C::N)[h];
     }
     uint32_t* xd = xbuf + (C::TC == 1 ? 0 : wave * 2 * C::XW);
     uint32_t* xu = xd + C::XW;
     const int xwo = C::TC == 1 ? 0 : 4 * lane, xpo = C::TC == 1 ? 0 : p2_base<LG>(0, lane);
-    float2 acc[NS][4];
+    float2 acc[NT][4];
 #pragma unroll
-    for (int k = 0; k < NS; ++k)
+    for (int k = 0; k < NT; ++k)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[k][j] = make_float2(0.f, 0.f);
     arrived(K);
     if (DU) {
 #pragma unroll
-        for (int k = 0; k < NS; ++k) arrived(kk[k].v);
+        for (int k = 0; k < NT; ++k) arrived(kk[k].v);
     }
     float dsum = 0.f;
     int eref = EXP_NONE;
     int eda = 0, edb = 0, eua = 0, eub = 0, epa = 0, epb = 0;      // exponents (bf16) of the pass's row(s), and of their products
-    uint32_t gy[4] = {0u, 0u, 0u, 0u};                   // dy's own words (gated layer)
+    uint32_t gy[NP][4];                                  // dy's own words (gated layer)
     auto iter = [&](auto mode, int p) {
         using M = decltype(mode);
-        h4 od[2], ou[2];
+        h4 od[NP][2], ou[NP][2];
         f4 wr[2], wi[2], yr[2], yi[2], v[2];
         H8U m[2], n[2];
-        uint32_t wy[4];
-        phase1_ops<LG, IO, M::scaled>(wd, eda, edb, lane, od);
-        phase1_ops<LG, IO, M::scaled>(wu, eua, eub, lane, ou);
-        if (GATE) {
+        uint32_t wy[NP][4], o[NP][4], og[NP][4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) wy[r] = gy[r];
+        for (int c = 0; c < NP; ++c) {
+            phase1_ops<LG, IO, M::scaled>(wd[c], eda, edb, lane, od[c]);
+            phase1_ops<LG, IO, M::scaled>(wu[c], eua, eub, lane, ou[c]);
+            if (GATE) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) wy[c][r] = gy[c][r];
+            }
         }
         load_all(p + pstep);
         SCHED_FENCE();                                  // (the loads go out here)
-        if constexpr (BF && M::scaled) acc_align<NS>(acc, eref, C::TC == 1 ? max(epa, epb) : epa);
-        phase1<LG>(od, K, xd + xwo, wr, wi);
-        phase1<LG>(ou, K, xu + xwo, yr, yi);
-        if constexpr (C::TC > 1) {
-            wave_lds_fence();
-            phase2_read<LG>(xd + xpo, m);
-            phase2_read<LG>(xu + xpo, n);
-            phase2_fwd<LG>(m, K, wr, wi);
-            phase2_fwd<LG>(n, K, yr, yi);
+        if constexpr (BF && M::scaled) acc_align<NT>(acc, eref, C::TC == 1 ? max(epa, epb) : epa);
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+            phase1<LG>(od[c], K, xd + xwo, wr, wi, c);
+            phase1<LG>(ou[c], K, xu + xwo, yr, yi, c);
+        }
+        if constexpr (C::TC > 1) wave_lds_fence();
+        auto accumulate = [&](int c) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                // N = 256: tile k is row k and both add to the same bins
+                const int epk = C::TC == 1 && k == 1 ? epb : epa;
+                acc_tile<BF && M::scaled>(acc[2 * c + k % NS], yr[k], yi[k], wr[k], wi[k], min(epk - eref, 0));
+            }
+        };
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+            if constexpr (C::TC > 1) {
+                phase2_read<LG>(xd + xpo + 2 * c * C::COLS, m);
+                phase2_read<LG>(xu + xpo + 2 * c * C::COLS, n);
+                phase2_fwd<LG>(m, K, wr, wi);
+                phase2_fwd<LG>(n, K, yr, yi);
+            }
+            if (DU) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const h2 kw = kk[2 * c + k % NS].c[r];
+                        m[k].w[r] = C::TC == 1 ? cmul_pack_conj(wr[k][r], wi[k][r], kw) : cmul_swap<true>(wr[k][r], wi[k][r], kw);
+                        if (GATE) n[k].w[r] = C::TC == 1 ? cmul_pack(yr[k][r], yi[k][r], kw) : cmul_swap<false>(yr[k][r], yi[k][r], kw);
+                    }
+                if constexpr (C::TC > 1) {
+                    phase2_inv<LG>(xd + xpo + 2 * c * C::COLS, K, m);
+                    if (GATE) phase2_inv<LG>(xu + xpo + 2 * c * C::COLS, K, n);
+                }
+            }
+            if constexpr (NP > 1) accumulate(c);
         }
         if (DU) {
+            if constexpr (C::TC > 1) wave_lds_fence();
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const h2 kw = kk[k % NS].c[r];
-                    m[k].w[r] = C::TC == 1 ? cmul_pack_conj(wr[k][r], wi[k][r], kw) : cmul_swap<true>(wr[k][r], wi[k][r], kw);
-                    if (GATE) n[k].w[r] = C::TC == 1 ? cmul_pack(yr[k][r], yi[k][r], kw) : cmul_swap<false>(yr[k][r], yi[k][r], kw);
+            for (int c = 0; c < NP; ++c) {
+                if constexpr (C::TC > 1) {
+                    phase3_read<LG>(xd + xwo + 2 * c * C::P, m);
+                    if (GATE) phase3_read<LG>(xu + xwo + 2 * c * C::P, n);
                 }
-            if constexpr (C::TC > 1) {
-                phase2_inv<LG>(xd + xpo, K, m);
-                if (GATE) phase2_inv<LG>(xu + xpo, K, n);
-                wave_lds_fence();
-                phase3_read<LG>(xd + xwo, m);
-                if (GATE) phase3_read<LG>(xu + xwo, n);
-            }
-            phase3<LG>(m, K, v);
-            rsrc_t d = make_rsrc(pdu, bytes_of(p));
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                buf_store(d, off[r], out_word<IO, M::scaled>(v[0][r], v[1][r], es + (C::TC == 1 && (lane & 8) ? edb : eda)));
-            pdu += step;
-            if (GATE) {
-                phase3<LG>(n, K, v);
-                d = make_rsrc(pdg, bytes_of(p));
+                phase3<LG>(m, K, v, c);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    buf_store(d, off[r], out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(wy[r]), v[1][r] * hi_of<IO>(wy[r]),
-                                                                 es + (C::TC == 1 && (lane & 8) ? eub : eua)));
+                    o[c][r] = out_word<IO, M::scaled>(v[0][r], v[1][r], es + (C::TC == 1 && (lane & 8) ? edb : eda));
+                if (GATE) {
+                    phase3<LG>(n, K, v, c);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        og[c][r] = out_word<IO, M::scaled>(v[0][r] * lo_of<IO>(wy[c][r]), v[1][r] * hi_of<IO>(wy[c][r]),
+                                                           es + (C::TC == 1 && (lane & 8) ? eub : eua));
+                }
+            }
+            store_words<NP>(make_rsrc(pdu, bytes_of(p)), off, o);
+            pdu += step;
+            if (GATE) {
+                store_words<NP>(make_rsrc(pdg, bytes_of(p)), off, og);
                 pdg += step;
             }
         }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            // N = 256: tile k is row k and both add to the same bins
-            const int epk = C::TC == 1 && k == 1 ? epb : epa;
-            acc_tile<BF && M::scaled>(acc[k % NS], yr[k], yi[k], wr[k], wi[k], min(epk - eref, 0));
-        }
+        if constexpr (NP == 1) accumulate(0);           // (behind the stores: the products' registers are there)
     };
     // the pass has arrived: gate, dot product, exponents; is anything scaled?
     auto prep = [&]() {
-        if (GATE) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) gy[r] = wd[r];
-            dsum = gate_words<IO>(wd, gn, wu, dsum);
-        } else {
+        for (int c = 0; c < NP; ++c) {
+            if (GATE) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(wd[r], wu[r], dsum);
+                for (int r = 0; r < 4; ++r) gy[c][r] = wd[c][r];
+                dsum = gate_words<IO>(wd[c], gn[c], wu[c], dsum);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(wd[c][r], wu[c][r], dsum);
+            }
         }
         if constexpr (BF) {
             uint32_t md[C::RPI], mu_[C::RPI];
-            words_max<C::RPI>(wd, md);
-            words_max<C::RPI>(wu, mu_);
+            words_max(wd, md);
+            words_max(wu, mu_);
             eda = row_exponent(md[0]);
             eua = row_exponent(mu_[0]);
             epa = md[0] && mu_[0] ? eda + eua : EXP_NONE;
@@ -1442,40 +1525,55 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
     if (lane == 0) dred[wave] = dsum;
-    int etop = acc_reduce<NS, 1, NWV, BF>(acc, eref, red, erefs, wave, lane);
+    if (NP > 1 && NWV > 1) __syncthreads();              // (the exchange buffers become the reduction's)
+    int etop = acc_reduce<NT, 1, NWV, BF>(acc, eref, red, erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
     if (wave != 0) return;
-    if (lane == 0 && q.dD) q.dD[ho] = ((dred[0] + dred[1]) + dred[2]) + dred[3];
+    if (lane == 0 && q.dD) {
+        float t = dred[0];
+        for (int w = 1; w < NWV; ++w) t += dred[w];
+        q.dD[ho] = t;
+    }
     if (!q.dk) return;
-    const int ea = acc_exponent(acc_peak<NS>(acc));
+    const int ea = acc_exponent(acc_peak<NT>(acc));
     etop += ea;
 #pragma unroll
-    for (int k = 0; k < NS; ++k)
+    for (int k = 0; k < NT; ++k)
 #pragma unroll
         for (int r = 0; r < 4; ++r) { acc[k][r].x = ldexpf(acc[k][r].x, -ea); acc[k][r].y = ldexpf(acc[k][r].y, -ea); }
     H8U m[2];
-    f4 v[2];
+    f4 v[NP][2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+    for (int c = 0; c < NP; ++c) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (C::TC == 1) m[k].w[r] = k == 0 ? pack_h2(acc[0][r].x, acc[0][r].y) : 0u;
-            else m[k].w[r] = pack_h2(acc[k % NS][r].y, acc[k % NS][r].x);
-        }
-    if constexpr (C::TC > 1) {
-        phase2_inv<LG>(xd + xpo, K, m);
-        wave_lds_fence();
-        phase3_read<LG>(xd + xwo, m);
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (C::TC == 1) m[k].w[r] = k == 0 ? pack_h2(acc[0][r].x, acc[0][r].y) : 0u;
+                else m[k].w[r] = pack_h2(acc[2 * c + k % NS][r].y, acc[2 * c + k % NS][r].x);
+            }
+        if constexpr (C::TC > 1) phase2_inv<LG>(xd + xpo + 2 * c * C::COLS, K, m);
     }
-    phase3<LG>(m, K, v);
+    if constexpr (C::TC > 1) wave_lds_fence();
+#pragma unroll
+    for (int c = 0; c < NP; ++c) {
+        if constexpr (C::TC > 1) phase3_read<LG>(xd + xwo + 2 * c * C::P, m);
+        phase3<LG>(m, K, v[c], c);
+    }
     const uint32_t kb = (pad ? C::N / 2 : C::N) * 4u;
     const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(q.dk) + ho * kb, kb);
     word_offsets<LG>(off, 0, lane, pad, NOWHERE);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-        const u2v o = {__float_as_uint(ldexpf(v[0][r] * q.dkscale, etop)), __float_as_uint(ldexpf(v[1][r] * q.dkscale, etop))};
-        __builtin_amdgcn_raw_buffer_store_b64(o, d, (int)((off[r] & NOWHERE) ? NOWHERE : 2u * off[r]), 0, 0);
+        const int at = (int)((off[r] & NOWHERE) ? NOWHERE : 2u * off[r]);
+        auto bits = [&](int c, int k) { return __float_as_uint(ldexpf(v[c][k][r] * q.dkscale, etop)); };
+        if constexpr (NP == 2) {
+            const u4v o = {bits(0, 0), bits(0, 1), bits(1, 0), bits(1, 1)};
+            __builtin_amdgcn_raw_buffer_store_b128(o, d, at, 0, 0);
+        } else {
+            const u2v o = {bits(0, 0), bits(0, 1)};
+            __builtin_amdgcn_raw_buffer_store_b64(o, d, at, 0, 0);
+        }
     }
 }
 
@@ -1499,7 +1597,7 @@ hipError_t rconv_run(const void* in, const float2* kspec, void* out, const Probl
     using C = RC<LG>;
     static int cap = 0;
     hipError_t e;
-    if constexpr (C::NWR > 1) {
+    if constexpr (LG > 10) {
         const int items = (int)(pr.B * pr.H);
         e = resident(rconv_kernel<LG, IO, CONJ, GATE>, C::NWR * 64, 0, cap);
         if (e != hipSuccess) return e;
@@ -1529,19 +1627,31 @@ hipError_t rkspec_go(const float* k, const float* D, float2* kspec, int64_t H, f
     hipLaunchKernelGGL((rkspec_kernel<LG>), dim3((unsigned)H), dim3(RC<LG>::NWR * 64), 0, st, k, D, kspec, (int)H, kscale, pad, tab);
     return hipGetLastError();
 }
+template <int LG, class IO, bool DU, bool GATE, int NWV>
+hipError_t rbwd1_run(const BwdArgs<typename IO::T>& a, hipStream_t st)
+{
+    hipLaunchKernelGGL((rbwd1_kernel<LG, IO, DU, GATE, NWV>), dim3((unsigned)(a.H * a.nsplit)), dim3(64 * NWV), 0, st, a);
+    return hipGetLastError();
+}
 template <int LG, class IO, bool DU, bool GATE>
 hipError_t rbwd_run(const BwdArgs<typename IO::T>& a, hipStream_t st)
 {
-    if constexpr (RC<LG>::NWR > 1) {
+    if constexpr (LG < 10) {
+        return rbwd1_run<LG, IO, DU, GATE, 4>(a, st);
+    } else if constexpr (LG == 10 && !GATE) {
+        // no more waves than the share has rows (B=1, H=768: four of them, three idle, 11.6 us, one 8.1)
+        const int each = (a.B + a.nsplit - 1) / a.nsplit;
+        if (each == 1) return rbwd1_run<LG, IO, DU, GATE, 1>(a, st);
+        if (each == 2) return rbwd1_run<LG, IO, DU, GATE, 2>(a, st);
+        return rbwd1_run<LG, IO, DU, GATE, 4>(a, st);
+    } else {
         using Q = BwdCfg<LG, GATE>;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rbwd_kernel<LG, IO, DU, GATE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q::lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((rbwd_kernel<LG, IO, DU, GATE>), dim3((unsigned)(a.H * a.nsplit)), dim3(Q::NWV * 64), Q::lds, st, a);
-    } else {
-        hipLaunchKernelGGL((rbwd1_kernel<LG, IO, DU, GATE>), dim3((unsigned)(a.H * a.nsplit)), dim3(256), 0, st, a);
+        return hipGetLastError();
     }
-    return hipGetLastError();
 }
 template <int LG, class IO>
 hipError_t rbwd_go(const BwdArgs<typename IO::T>& a, hipStream_t st)
@@ -1573,14 +1683,23 @@ hipError_t rows_fill_tables(const void** tab_out, hipStream_t st)
     return hipGetLastError();
 }
 
-// Shares of a head's rows in the backward kernel: about as many workgroups as the device holds at once when heads are
-// few, and at least two rows (passes of two rows at N = 256) for every group of waves.
-int rows_bwd_nsplit(int64_t B, int64_t H, int lg)
+// Shares of a head's rows in the backward kernel: about as many workgroups as the device holds at once when heads are few
+// (half of it at N = 1024 ungated, a row a wave), and at least two rows (passes of two rows at N = 256) for every group of
+// waves.  More than one share costs a second launch, about 3.5 us, so where the heads alone fill a quarter of the device a
+// share has at least eight rows a group (fp16, kernel time of one share against two: B=16, H=256, N=512 8.4 and 10.5 us;
+// B=3, H=256, N=2048 10.1 and 13.2); gated rows of 4096 samples are worth it (B=4, H=128 bf16 21.5 and 19.8).  N = 1024
+// ungated, few heads: the root of the rows, where the rows a wave is spared and the partial results that come with them
+// balance (fp16: B=16, H=16 2 shares 10.4 us, 4 9.3; B=64, H=32 4 shares 14.3, 8 12.9, 16 17.3).
+int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated)
 {
-    const int ngrp = lg == 12 || lg == 11 ? 1 : (lg == 10 ? 2 : 4);
+    const bool wave_rows = lg == 10 && !gated;
+    const int ngrp = lg >= 11 ? 1 : lg == 10 && gated ? 2 : 4;
     const int64_t units = lg == 8 ? (B + 1) / 2 : B;
-    const int64_t most = (units + 2 * ngrp - 1) / (2 * ngrp);
-    int64_t s = (lg == 12 ? 256 : 512) / H;
+    int64_t s = (lg == 12 || wave_rows ? 256 : 512) / H;
+    const int64_t least = ngrp * (s < 4 && !(gated && lg == 12) ? 8 : 2);
+    int64_t most = (units + least - 1) / least;
+    if (wave_rows && s >= 4)
+        for (most = units / 4; most > 1 && most * most > units;) --most;
     if (s > most) s = most;
     if (s > 64) s = 64;
     return s < 1 ? 1 : (int)s;

@@ -149,7 +149,7 @@ hipError_t rows_conv(const void* in, const float2* kspec, void* out, bool conj, 
 // du, dk and dD in one kernel, from one read of dy and u; du (and with it kspec), dk and dD may be null.  nsplit > 1: the
 // rows of a head are dealt to nsplit workgroups, dk and dD then point to partial buffers [nsplit][H][N] and [nsplit][H]
 // that sum_partials() adds up in share order.
-int rows_bwd_nsplit(int64_t B, int64_t H, int lg);
+int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated);
 // With Problem::gate: the gated layer's backward pass (du and dg both given), dg = dy (ungated output).
 hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, void* dg, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);

@@ -263,3 +263,21 @@ def test_rows_of_65536_samples_in_two_chunks(io, B, H):
         check_full(inp, label="rows in two chunks")
     else:
         check_sampled(inp, [0, 33, H - 1], label="rows in two chunks")
+
+
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("B,H", [(1, 3), (2, 5), (3, 2), (5, 64), (9, 3), (17, 2), (16, 129), (33, 257)])
+def test_rows_of_1024_samples_one_wave_each(B, H, io):
+    # one, two and four waves in the backward kernel; one share of the rows and several, even and ragged, more rows than
+    # waves on the device; dk and dD by themselves equal those of the call with du
+    from gpu_harness import GpuRun, check_full, check_sampled
+    inp = wl.generate(wl.Workload(6, B, H, 1024, io, "squash_pool"))
+    if B * H <= 64:
+        check_full(inp, label="one wave a row")
+    else:
+        check_sampled(inp, [0, H // 2, H - 1], label="one wave a row")
+    g = GpuRun(inp)
+    dk, dD = g.bwd()[1:]
+    g.dk.fill_(float("nan")), g.dD.fill_(float("nan"))
+    dk1, dD1 = g.bwd(du=False)[1:]
+    assert np.array_equal(dk, dk1) and np.array_equal(dD, dD1)
