@@ -174,3 +174,42 @@ def test_outputs_of_rows_with_a_mean(N, io):
     _compare({"y": g.fwd(), "du": g.bwd(dk=False, dD=False)[0]},
              {"y": oracle.longconv_fwd(u_v, k64, D64), "du": oracle.longconv_bwd(dy_v, u_v, k64, D64)[0]}, TOL[io],
              f"outputs of rows with a mean, N={N} io={wl.DTYPE_NAMES[io]}")
+
+
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("N,B,H", [(256, 18, 1200), (512, 9, 1200), (1024, 9, 1100), (2048, 7, 800), (4096, 7, 400)])
+def test_long_runs_of_rows_and_heads_of_other_magnitudes(N, B, H, io):
+    # Workgroups with many rows: the kernels have code of their own for the middle of a run, with and without powers of
+    # two, which shapes of a few rows do not reach.  More rows than four times what the device holds at once, heads whose
+    # spectrum has a power of two taken out next to ordinary ones, and (bf16) rows out of band or zero anywhere.
+    from gpu_harness import GpuRun, TOL, _compare
+    import oracle
+    rng = np.random.default_rng(31 + N)
+    ks = np.where(rng.random(H) < 0.3, 2.0 ** rng.integers(-9, 9, size=H), 1.0)
+    us = ds = np.ones((B, H))
+    if io == wl.BF16:
+        us = np.where(rng.random((B, H)) < 0.3, 10.0 ** rng.uniform(-6, 6, size=(B, H)), 1.0)
+        ds = np.where(rng.random((B, H)) < 0.3, 10.0 ** rng.uniform(-9, 3, size=(B, H)), 1.0)
+        us[rng.random((B, H)) < 0.05] = 0.0
+        ds[rng.random((B, H)) < 0.05] = 0.0
+    inp = scaled_inputs(N, B, H, us, ds, k_scale=ks, D_scale=ks, seed=8, dtype=io)
+    heads = sorted({0, 1, H // 3, H // 3 + 1, H // 2, H - 1, int(np.argmin(ks)), int(np.argmax(ks))})
+    g = GpuRun(inp)
+    got = dict(zip(("y", "du", "dk", "dD"), (g.fwd(), *g.bwd())))
+    assert all(np.all(np.isfinite(v)) for v in got.values())
+    k64, D64 = inp.k[heads].astype(np.float64), inp.D[heads].astype(np.float64)
+    want = dict(zip(("y", "du", "dk", "dD"), (oracle.longconv_fwd(inp.u[:, heads], k64, D64),
+                                              *oracle.longconv_bwd(inp.dy[:, heads], inp.u[:, heads], k64, D64))))
+    got = {n: v[:, heads] if v.ndim == 3 else v[heads] for n, v in got.items()}
+    # (dD: rows of wildly different size meet in one fp32 dot product, see test_random_magnitudes)
+    _compare(got, want, TOL[io], f"long runs, N={N} B={B} H={H} io={wl.DTYPE_NAMES[io]}", dd_tol=1e-4)
+
+
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+def test_rows_of_one_head_apart_at_32768(io):
+    # y and du are scaled row by row there, dk head by head: rows far apart in size, the largest u with the largest dy (a
+    # head's dk is then that row's, and the others' share of it lies far below the bound)
+    us, ds = np.array([[1.0], [1e3], [1e-4]]), np.array([[1.0], [1e2], [1e-5]])
+    if io == wl.F16:
+        us, ds = np.array([[1.0], [8.0], [0.25]]), np.array([[0.5], [4.0], [1.0]])
+    check_full(scaled_inputs(32768, 3, 2, us, ds, seed=9, dtype=io), label="rows of one head apart", dd_tol=1e-4)

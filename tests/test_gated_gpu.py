@@ -92,6 +92,37 @@ def test_gate_meets_heads_of_other_magnitudes(N, io):
         _compare(got, want, TOL[io], f"gate and heads of other magnitudes, {big}, N={N} io={wl.DTYPE_NAMES[io]}")
 
 
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("N,B,H", [(256, 18, 520), (512, 9, 520), (1024, 9, 1100), (2048, 7, 780), (4096, 7, 400)])
+def test_gated_long_runs_of_rows(N, B, H, io):
+    # workgroups with many rows, which run the middle of the kernels' row pipelines: gradients as small as a mean loss
+    # makes them (bf16), rows of other magnitudes and zero rows among them, heads with a power of two taken out
+    inp, g_s, g_v = _inputs(N, io, B, H, seed=7)
+    rng = np.random.default_rng(57 + N)
+    ks = np.where(rng.random(H) < 0.3, 2.0 ** rng.integers(-9, 9, size=H), 1.0)
+    k, D = (inp.k * ks[:, None]).astype(np.float32), (inp.D * ks).astype(np.float32)
+    us = ds = np.ones((B, H, 1))
+    if io == wl.BF16:
+        us = np.where(rng.random((B, H, 1)) < 0.3, 10.0 ** rng.uniform(-6, 6, size=(B, H, 1)), 1.0)
+        ds = np.where(rng.random((B, H, 1)) < 0.3, 10.0 ** rng.uniform(-9, 3, size=(B, H, 1)), 1e-4)
+        us[rng.random((B, H, 1)) < 0.05] = 0.0
+        ds[rng.random((B, H, 1)) < 0.05] = 0.0
+    u_s, u = wl.quantize((inp.u * us).astype(np.float32), io)
+    dy_s, dy = wl.quantize((inp.dy * ds).astype(np.float32), io)
+    out = _run(dataclasses.replace(inp, k=k, D=D, u_store=u_s, u=u, dy_store=dy_s, dy=dy), g_s)
+    assert all(np.all(np.isfinite(v)) for v in out)
+    hs = sorted({0, 1, H // 3, H // 3 + 1, H // 2, H - 1, int(np.argmin(ks)), int(np.argmax(ks))})
+    y, du, dk, dD, dg = (v[:, hs] if v.ndim == 3 else v[hs] for v in out)
+    k64, D64 = k[hs].astype(np.float64), D[hs].astype(np.float64)
+    rdu, rdk, rdD, rdg = gated.gated_bwd(dy[:, hs], g_v[:, hs], u[:, hs], k64, D64)
+    label = f"gated long runs, N={N} B={B} H={H} io={wl.DTYPE_NAMES[io]}"
+    # (dD: rows of wildly different size meet in one fp32 dot product, a few 1e-5)
+    _compare({"y": y, "dk": dk, "dg": dg, "dD": dD}, {"y": gated.gated_fwd(u[:, hs], k64, D64, g_v[:, hs]), "dk": rdk, "dg": rdg, "dD": rdD},
+             TOL[io], label, dd_tol=1e-4)
+    # du is rounded twice in bf16, dz on the way in and du on the way out, by 2^-9 at most each; the transforms add 1e-3
+    _compare({"du": du}, {"du": rdu}, 2 * 2.0 ** -9 + 1e-3 if io == wl.BF16 else TOL[io], label)
+
+
 def test_optional_outputs_and_error_codes():
     inp, g_s, g_v = _inputs(1024, wl.BF16, 2, 2)
     y, du, dk, dD, dg = _run(inp, g_s, want_du=False, want_dk=False, want_dD=False)
