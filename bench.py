@@ -88,17 +88,19 @@ def group_bytes(w: wl.Workload):
 def executed_mfma_flops(w: wl.Workload):
     """Matrix-core flops the kernels issue for one step (model of the factorisation, dense 16x16x32 blocks,
     two instructions per 16x16 complex tile and stage, 16384 flop each): per 256-point tile a forward or an inverse half
-    transform costs 8 instructions at four digits, 6 at three, 4 at two.  The convolutions and the spectrum transform N
-    twisted points per row at N <= 4096, 32768 and 65536 (2N points per row pair, N per head), the whole backward pass too
-    up to N = 4096; dk beyond that, and everything at the other lengths, works on zero-padded pairs.  Half transforms: forward 2, du 2, dk 2 per row or pair (3 for both where
-    one kernel serves them); per head: spectrum 1, dk's inverse 1."""
+    transform costs 8 instructions at four digits, and one less than 6 at three or 4 at two digits (rows up to N = 4096: the
+    first block of real samples is two 16x16x16 instructions, the last computes real parts only, as the inverse at
+    N = 32768 does).  The convolutions and the spectrum transform N twisted points per row at N <= 4096, 32768 and 65536 (2N
+    points per row pair, N per head), the whole backward pass too up to N = 4096; dk beyond that, and everything at the other
+    lengths, works on zero-padded pairs.  Half transforms: forward 2, du 2, dk 2 per row or pair (3 for both where one kernel
+    serves them); per head: spectrum 1, dk's inverse 1."""
     if w.dtype == wl.F32:
         return 0.0
     L, N = 2 * w.N, w.N
     npairs = (w.B + 1) // 2
-    half = lambda points, digits: 2 * digits * 16384 * (points / 256)
+    half = lambda points, digits, less=0: (2 * digits - less) * 16384 * (points / 256)
     if N <= 4096:
-        return w.H * (5 * w.B + 2) * half(N, 2 if N == 256 else 3)
+        return w.H * (5 * w.B + 2) * half(N, 2 if N == 256 else 3, 1)
     pairs = half(L, 4)
     dk = 2 * npairs + 1
     if N >= 32768 and w.B == 1:
@@ -106,7 +108,8 @@ def executed_mfma_flops(w: wl.Workload):
         R = L // 16384
         dk *= (R / 2 + 1) / R
     if N in (32768, 65536):
-        return w.H * ((4 * w.B + 1) * half(N, 4) + dk * pairs)
+        inverse = half(N, 4, 1 if N == 32768 else 0)
+        return w.H * ((2 * w.B + 1) * half(N, 4) + 2 * w.B * inverse + dk * pairs)
     R = L // 32768
     fc = (R / 2 + 1) / R if w.B == 1 and R > 1 else 1.0
     return w.H * ((4 * npairs * fc + 1 + dk) * pairs)
