@@ -50,10 +50,10 @@
  *     with a further power of two taken out, which the convolutions give back where they
  *     pack their output (heads of order one take neither path).  Not rescaled, and therefore
  *     to be kept inside fp16's normal range by the caller: fp16 rows (order one is fine up
- *     to N = 131072; the transform grows them by at most sqrt(2N); batch rows 2p and 2p+1
- *     of a head share one complex transform, so the error of an fp16 row is relative to the
- *     larger of the two: rows of similar size, as a normalised layer produces them, meet the
- *     bound), and of course the outputs have to fit the I/O dtype.  fp32 I/O computes in fp32.
+ *     to N = 131072; the transform grows them by at most sqrt(2N); at N = 8192, 16384 and
+ *     131072, and for dk from 32768 on, batch rows 2p and 2p+1 of a head share one complex
+ *     transform, so the error of an fp16 row is relative to the larger of the two: rows of
+ *     similar size, as a normalised layer produces them, meet the bound), and of course the outputs have to fit the I/O dtype.  fp32 I/O computes in fp32.
  */
 #ifndef LONGCONV_H
 #define LONGCONV_H
@@ -83,7 +83,9 @@ typedef enum {
 int longconv_init(void);
 
 /* Size in bytes of the spectrum cache for H heads of length N (0 on bad args).
- * The cache holds, per head, the 2N-point spectrum of [k[h,:], 0_N] plus D[h]
+ * The cache holds, per head, the spectrum of [k[h,:], 0_N] plus D[h]: 2N points, or the
+ * N points of the twisted row where fp16/bf16 rows are transformed one by one (N <= 4096,
+ * 32768 and 65536; the room is that of 2N points at every length)
  * (the skip term is a delta kernel of height D[h]), pre-scaled and stored in the
  * permuted order the fused transform produces (Algorithm 2 lines 1-2: the
  * spectrum is computed once and stored already permuted, so no permutation ever
@@ -131,8 +133,9 @@ int longconv_fwd_noalloc(const void* u, const float* k, const float* D, const vo
 /* Backward: du, dk, dD as defined above.  Any of the three output pointers may be
  * NULL to skip that gradient.  dk and dD are overwritten (not accumulated) and are
  * summed over b in a fixed order (bitwise repeatable call to call).  Which kernels
- * run depends on which outputs are asked for (for N <= 2048 with fp16/bf16 I/O, du
- * together with dk or dD comes from one kernel, otherwise from separate ones), so a
+ * run depends on which outputs are asked for (for N <= 4096 with fp16/bf16 I/O, and at
+ * every length with fp32 I/O, du together with dk or dD comes from one kernel, otherwise
+ * from separate ones), so a
  * gradient may differ in its last bits between a call for all three and a call for
  * itself alone; both meet the stated accuracy.  kspec as in longconv_fwd (only
  * needed for du). */
