@@ -519,7 +519,7 @@ __device__ __forceinline__ u4v buf_load4(rsrc_t r, uint32_t off)
 // Loads and stores are issued in every iteration, with an empty descriptor where there is no row: conditional ones
 // would make the compiler wait for younger requests than it has to.
 // Bound by matrix and vector issue, which add up.
-// Whole steps, row pairs in 2N points against rows: B=64, H=1024, N=4096 1556 -> 838 us; N=256 85 -> 67 us.
+// Whole steps, row pairs in 2N points against rows: B=64, H=1024, N=4096 1564 -> 837 us; N=256 85 -> 67 us.
 // -------------------------------------------------------------------------------------
 template <int LG, class IO, bool CONJ, bool GATE>
 __global__ void __launch_bounds__(RC<LG>::NWR * 64) __attribute__((amdgpu_waves_per_eu(4)))
