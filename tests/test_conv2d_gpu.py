@@ -58,6 +58,14 @@ def test_conv2d_against_the_oracle(N1, N2, io, B, H):
              f"conv2d {N1}x{N2} io={wl.DTYPE_NAMES[io]}")
 
 
+@pytest.mark.parametrize("io,B", [(wl.F16, 1), (wl.BF16, 5)])
+@pytest.mark.parametrize("N1,N2", [(16, 8), (32, 8), (64, 8), (16, 32), (1, 512), (128, 8), (256, 8), (2, 1024)])
+def test_images_padded_while_they_are_loaded(N1, N2, io, B):
+    # the narrowest image there is (8 samples: the widest piece that a lane loads or stores at once), a square-like one and
+    # the widest, at every length of the kernels that pad by themselves
+    test_conv2d_against_the_oracle(N1, N2, io, B, 3)
+
+
 def test_full_size_image_batch_on_sampled_heads():
     """B=64, H=256, 32x32 bf16 images (the shape timed in the design notes), all of it through the library; eight heads
     (first, last, seeded ones) in full against the oracle."""
