@@ -731,8 +731,8 @@ int longconv_lbfly_spectrum(const float* k, const float* D, float* shat, int64_t
     hipStream_t st = (hipStream_t)stream;
     Tables tb;
     if (get_tables(&tb, st, false) != hipSuccess) return LONGCONV_ERR_HIP;
-    return note(lbfly_spectrum(k, D, shat, H, N, tb, st), "lbfly spectrum") == hipSuccess ? LONGCONV_OK
-                                                                                          : LONGCONV_ERR_HIP;
+    return note(spectrum_natural(k, D, shat, H, N, tb, st), "lbfly spectrum") == hipSuccess ? LONGCONV_OK
+                                                                                            : LONGCONV_ERR_HIP;
 }
 
 int longconv_lbfly_spectrum_bwd(const float* dshat, float* dk, float* dD, int64_t H, int64_t N, void* stream)
@@ -745,7 +745,7 @@ int longconv_lbfly_spectrum_bwd(const float* dshat, float* dk, float* dD, int64_
     hipStream_t st = (hipStream_t)stream;
     Tables tb;
     if (get_tables(&tb, st, false) != hipSuccess) return LONGCONV_ERR_HIP;
-    return note(lbfly_spectrum_bwd(dshat, dk, dD, H, N, tb, st), "lbfly spectrum bwd") == hipSuccess
+    return note(spectrum_natural_bwd(dshat, dk, dD, H, N, tb, st), "lbfly spectrum bwd") == hipSuccess
                ? LONGCONV_OK
                : LONGCONV_ERR_HIP;
 }

@@ -88,10 +88,6 @@ hipError_t lbfly_fwd(const void* u, const float* shat, const float* Af, const fl
 hipError_t lbfly_bwd(const void* dy, const void* u, const float* shat, const float* Af, const float* Ai, void* du,
                      float* dshat, float* dAf, float* dAi, void* partials, int64_t B, int64_t H, int64_t N, int io,
                      const Tables& tb, hipStream_t st);
-hipError_t lbfly_spectrum(const float* k, const float* D, float* shat, int64_t H, int64_t N, const Tables& tb,
-                          hipStream_t st);
-hipError_t lbfly_spectrum_bwd(const float* dshat, float* dk, float* dD, int64_t H, int64_t N, const Tables& tb,
-                              hipStream_t st);
 
 // ---- block-size study (bsize.hip): forward convolution of fp16 rows with DFT blocks of 2^log2r points, N = 1024, 4096
 hipError_t blocksize_fwd(const void* u, const float* shat, void* y, int64_t B, int64_t H, int64_t N, int log2r,
@@ -112,6 +108,11 @@ void valu_fill_plan(Plan& pl);
 // the order of the engine's own kernels, or scattered to `consumer`'s order if that is given.
 hipError_t valu_kspec(const float* k, const float* D, float2* kspec, int64_t H, int64_t N, const SpecOrder* consumer,
                       float scale, const Tables& tb, int log2R, int log2L2, hipStream_t st);
+// Spectrum of [k, 0] plus D in natural frequency order, fp32, and its adjoint (dk and dD may be null); N = 256 .. 4096.
+hipError_t spectrum_natural(const float* k, const float* D, float* shat, int64_t H, int64_t N, const Tables& tb,
+                            hipStream_t st);
+hipError_t spectrum_natural_bwd(const float* dshat, float* dk, float* dD, int64_t H, int64_t N, const Tables& tb,
+                                hipStream_t st);
 // Multi-pass plans: pass A is taken inside the kernels, ws receives pass C's input.
 hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
                      const Plan& pl, const Tables& tb, hipStream_t st);

@@ -20,8 +20,6 @@
 // complex fp16), then the gradient walks the stages in reverse; the gradient of a block is the 16 x 16 complex
 // matrix sum over columns of (gradient at the block's output) x conj(the block's input), two more MFMAs per 16
 // columns with the columns as the K dimension, accumulated in fp32 registers over the rows a workgroup owns.
-// Also here: the plain radix-2 fp32 FFT per head that makes Shat from (k, D) in natural frequency order, and its
-// adjoint from dShat back to (dk, dD).
 #include "engines.hpp"
 
 namespace lc {
@@ -549,52 +547,6 @@ lb_reduce_kernel(const float2* __restrict__ part_shat, const float2* __restrict_
     }
 }
 
-// -------------------------------------------------------------------------------------------------------------------
-// Spectrum of the head's filter in natural frequency order, fp32: Shat[h,f] = sum_{s<N} k[h,s] exp(-2 pi i f s / L)
-// + D[h] (MODE 0), and the adjoint dk[h,s] = Re sum_f exp(+2 pi i f s / L) dShat[h,f], dD[h] = Re sum_f dShat[h,f]
-// (MODE 1).  One workgroup per head, radix-2 decimation in time on bit-reversed input, L complex fp32 in LDS.
-// -------------------------------------------------------------------------------------------------------------------
-template <int MODE>
-__global__ void __launch_bounds__(256)
-lb_fft_kernel(const float* __restrict__ in, const float* __restrict__ D, float* __restrict__ out,
-              float* __restrict__ dD, int LG, const float2* __restrict__ tw)
-{
-    extern __shared__ uint4 smem_raw[];
-    float2* z = reinterpret_cast<float2*>(smem_raw);
-    const int L = 1 << LG, N = L / 2, h = blockIdx.x, tid = threadIdx.x;
-    for (int i = tid; i < L; i += 256) {
-        const int j = (int)(__brev((unsigned)i) >> (32 - LG));
-        float2 v;
-        if (MODE == 0)
-            v = make_float2(i < N ? in[(size_t)h * N + i] : 0.f, 0.f);
-        else
-            v = reinterpret_cast<const float2*>(in)[(size_t)h * L + i];
-        z[j] = v;
-    }
-    __syncthreads();
-    for (int s = 1; s <= LG; ++s) {
-        const int half = 1 << (s - 1);
-        for (int i = tid; i < L / 2; i += 256) {
-            const int pos = i & (half - 1), a = ((i >> (s - 1)) << s) + pos, b = a + half;
-            float2 w = tw_full(tw, (uint32_t)pos << (TW_LOG2 - s));
-            if (MODE == 1) w.y = -w.y;
-            const float2 t = cmul(z[b], w), za = z[a];
-            z[b] = csub(za, t);
-            z[a] = cadd(za, t);
-        }
-        __syncthreads();
-    }
-    if (MODE == 0) {
-        const float d = D[h];
-        for (int f = tid; f < L; f += 256)
-            reinterpret_cast<float2*>(out)[(size_t)h * L + f] = make_float2(z[f].x + d, z[f].y);
-    } else {
-        if (out)
-            for (int s = tid; s < N; s += 256) out[(size_t)h * N + s] = z[s].x;
-        if (dD && tid == 0) dD[h] = z[0].x;
-    }
-}
-
 template <class F>
 hipError_t set_lds(F* f, size_t bytes)
 {
@@ -694,31 +646,6 @@ hipError_t lbfly_bwd(const void* dy, const void* u, const float* shat, const flo
     while ((1 << lg) < 2 * N) ++lg;
     hipLaunchKernelGGL(lb_reduce_kernel, dim3((unsigned)H), dim3(256), 0, st, part_shat, part_q, (float2*)dshat,
                        (float2*)dAf, (float2*)dAi, H, (int)(2 * N), lg - 8, nsplit);
-    return hipGetLastError();
-}
-
-hipError_t lbfly_spectrum(const float* k, const float* D, float* shat, int64_t H, int64_t N, const Tables& tb,
-                          hipStream_t st)
-{
-    int lg = 0;
-    while ((1 << lg) < 2 * N) ++lg;
-    const size_t lds = (size_t)(2 * N) * sizeof(float2);
-    hipError_t e = set_lds(lb_fft_kernel<0>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lb_fft_kernel<0>, dim3((unsigned)H), dim3(256), lds, st, k, D, shat, (float*)nullptr, lg, tb.tw);
-    return hipGetLastError();
-}
-
-hipError_t lbfly_spectrum_bwd(const float* dshat, float* dk, float* dD, int64_t H, int64_t N, const Tables& tb,
-                              hipStream_t st)
-{
-    int lg = 0;
-    while ((1 << lg) < 2 * N) ++lg;
-    const size_t lds = (size_t)(2 * N) * sizeof(float2);
-    hipError_t e = set_lds(lb_fft_kernel<1>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lb_fft_kernel<1>, dim3((unsigned)H), dim3(256), lds, st, dshat, (const float*)nullptr, dk, dD, lg,
-                       tb.tw);
     return hipGetLastError();
 }
 
