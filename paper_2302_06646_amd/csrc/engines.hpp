@@ -81,7 +81,7 @@ hipError_t unpad_rows(const void* src, void* dst, size_t rows, size_t row_bytes,
 
 // ---- learned Butterfly extension (lbfly.hip): N = 256 .. 2048, fp16 / bf16 rows -----------------------------------
 // rows are split over this many workgroups per head in the backward pass; their partial sums need lbfly_partial_bytes
-int lbfly_nsplit(int64_t B, int64_t H);
+int lbfly_nsplit(int64_t B, int64_t H, int64_t N);
 size_t lbfly_partial_bytes(int64_t B, int64_t H, int64_t N);
 hipError_t lbfly_fwd(const void* u, const float* shat, const float* Af, const float* Ai, void* y, int64_t B, int64_t H,
                      int64_t N, int io, const Tables& tb, hipStream_t st);

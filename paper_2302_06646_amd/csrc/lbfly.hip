@@ -14,12 +14,13 @@
 //   T_B: the mirror image, s = 2, 1, 0: (s < 2) conj(w_s), then block B_s[h] along digit s; 1/L at the end.
 //
 // Every block product is one pair of v_mfma_f32_16x16x32_f16 per 16 columns (real form of the complex product, K =
-// 16 slots x (re, im)), data as fp16 complex in LDS between stages, fp32 accumulation; every stage carries a fixed
+// 16 slots x (re, im)), data as fp16 complex between stages, fp32 accumulation; every stage carries a fixed
 // power of two (1/4 per 16-point block) so that DFT-like blocks keep the data at unit magnitude, undone in fp32 at
-// the end.  Backward: the forward chain is run again with the input of every stage kept in LDS (seven buffers of L
-// complex fp16), then the gradient walks the stages in reverse; the gradient of a block is the 16 x 16 complex
-// matrix sum over columns of (gradient at the block's output) x conj(the block's input), two more MFMAs per 16
+// the end.  Backward: the forward chain is run again next to the gradient's, and the gradient of a block is the 16 x 16
+// complex matrix sum over columns of (gradient at the block's output) x conj(the block's input), two more MFMAs per 16
 // columns with the columns as the K dimension, accumulated in fp32 registers over the rows a workgroup owns.
+#include <type_traits>
+
 #include "engines.hpp"
 
 namespace lc {
@@ -34,8 +35,7 @@ typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 constexpr int NBLK = 256;                       // entries of one 16 x 16 block
 __host__ __device__ constexpr int stage_shift(int b) { return b == 4 ? 2 : (b >= 2 ? 1 : 0); }
 __host__ __device__ constexpr int total_shift(int lg) { return 4 + stage_shift(lg - 8); }
-__host__ __device__ constexpr int lb_waves(int lg) { return lg == 9 ? 2 : 4; }          // forward kernel
-__host__ __device__ constexpr int lbb_waves(int lg) { return lg == 9 ? 2 : lg == 10 ? 4 : 8; }   // backward kernel
+constexpr int LBB_WAVES = 8;                     // backward kernel of N = 2048
 
 struct Mats {
     h8 re, im;   // A operands producing the real / imaginary part of the output
@@ -253,95 +253,685 @@ __device__ __forceinline__ void store_row(const h2* s, typename IO::T* row, int 
     }
 }
 
-// -------------------------------------------------------------------------------------------------------------------
-// Forward.  grid = (row groups, H); a workgroup keeps its head's six blocks as MFMA operands in registers and walks
-// its rows; one buffer of L complex fp16, every stage in place.
-// -------------------------------------------------------------------------------------------------------------------
-template <int LG, class IO>
-__global__ void __launch_bounds__(lb_waves(LG) * 64)
-lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ shat, const float2* __restrict__ Af,
-              const float2* __restrict__ Ai, typename IO::T* __restrict__ y, int64_t B, int64_t H, int rows_per_wg,
-              const float2* __restrict__ stw)
+// ---- the register-chained form ------------------------------------------------------------------------------------------
+// With T = L / 256 = the last radix, tile t = (all d_0, d_1 at d_2 = t) is one 16 x 16 matrix of points that two blocks
+// contract one after the other: a matrix instruction leaves its result as (X = lane % 16, Y = 4 (lane / 16) + register)
+// and takes an operand in the same form with Y the contracted index, and which of its two operands the data is decides
+// whether X stays (data second) or the new index takes the lanes and X the registers (data first).  So both 16-point
+// blocks of a direction run in registers, and only d_2 crosses LDS.
+//   * Twiddles: w_0 = w_256^(k_0 d_1) w_L^(k_0 t), w_1 = w_16T^(k_1 t).  Everything that depends on t is a row or column
+//     scale of the tile's own matrices; what is left, w_256^(lane (4g + r)), is four numbers per lane, the same for all
+//     tiles and both directions, multiplied in fp32.
+//   * Data between stages is planar: a lane's four real parts, then its four imaginary parts (the matrices' K index runs in
+//     that order), so LDS holds planes of 16-bit numbers, written as runs of four, and read either the same way or
+//     transposed (ds_read_b64_tr_b16): each of the two index orders of a tile costs one 8-byte LDS access per plane.
+//   * Exchange buffer: [d_2][plane][k_0][k_1], 8 words of padding per d_2.  LDS serves an 8-byte access 16 lanes at a time;
+//     where these lanes sit in 16 different rows of 16 numbers they all want the same quarter of their rows, so a row's
+//     quarters are stored XORed with a hash of (d_2, k_0) that makes 16 rows of one d_2, and 16 slots of a middle tile,
+//     fill all banks.
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+
+struct Cx {
+    h8 re, im;      // complex in: operands giving the real and imaginary part of the result
+};
+struct Rl {
+    h4 re, im;      // real in
+};
+union H8P {
+    h8 v;
+    h4 p[2];        // planes
+    uint2 u[2];
+};
+
+template <int LG>
+struct Geo {
+    static constexpr int L = 1 << LG, N = L / 2, LB = LG - 8, T = 1 << LB;
+    static constexpr int XS = 512 + 16;                       // numbers of a tile in the exchange buffer
+    static constexpr int IS = 264, OS = 136;                  // and of a tile of rows coming in (16 x 16, 8 zero) and going out
+    static constexpr float yscale() { return (float)(1 << 2 * total_shift(LG)) / (float)L; }
+    // quarter q of row (d_2, k_0) of the exchange buffer
+    static __device__ __forceinline__ int at(int d2, int k0, int q)
+    {
+        const int f = T == 16 ? d2 >> 2 : T == 8 ? (d2 >> 2) | ((d2 & 1) << 1) : T == 4 ? d2 : 2 * d2;
+        return d2 * XS + k0 * 16 + 4 * ((q ^ (k0 >> 2) ^ f) & 3);
+    }
+    // the row that is slot s of middle tile m: d_2 = s mod T, k_0 = ...
+    static __device__ __forceinline__ int slot_at(int m, int s, int q) { return at(s & (T - 1), m * (16 / T) + (s >> LB), q); }
+};
+
+__device__ __forceinline__ f4 mm(const h8& a, const h8& b)
 {
-    extern __shared__ uint4 smem_raw[];
-    constexpr int NW = lb_waves(LG), L = 1 << LG, N = L / 2, T = L / 256, LB = LG - 8, TPW = T / NW;
-    float2* sS = reinterpret_cast<float2*>(smem_raw);                 // the spectrum in position order
-    h2* s = reinterpret_cast<h2*>(sS + L);
-    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float2* af = Af + (size_t)h * 3 * NBLK;
-    const float2* ai = Ai + (size_t)h * 3 * NBLK;
-    const Mats A0 = load_mats(af, 4, false, lane), A1 = load_mats(af + NBLK, 4, false, lane);
-    const Mats A2 = load_mats(af + 2 * NBLK, LB, false, lane);
-    const Mats B0 = load_mats(ai, 4, false, lane), B1 = load_mats(ai + NBLK, 4, false, lane);
-    const Mats B2 = load_mats(ai + 2 * NBLK, LB, false, lane);
-    stage_spectrum<LG>(sS, shat + (size_t)h * L, tid, NW * 64);
-    const float yscale = exp2f((float)(2 * total_shift(LG) - LG));
-    const int64_t b0 = (int64_t)blockIdx.x * rows_per_wg;
-    const int64_t b1 = b0 + rows_per_wg < B ? b0 + rows_per_wg : B;
-    for (int64_t b = b0; b < b1; ++b) {
-        load_row<IO>(s, u + row_off(b, h, H, N), N, tid, NW * 64);
-        __syncthreads();
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, z, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mm(const h4& a, const h4& b)
+{
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, z, 0, 0, 0);
+}
+// four 16-bit numbers a lane: lane i of 16 gives the address of numbers 4 (i % 4) .. + 3 of row i / 4 and receives column i of
+// the four rows (all lanes active)
+__device__ __forceinline__ h4 tr_read(const _Float16* s)
+{
+    typedef __fp16 t4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) t4 lds_t4;
+    union { t4 t; h4 h; } cv;
+    cv.t = __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_t4*)(s));
+    return cv.h;
+}
+__device__ __forceinline__ h4 rd4(const _Float16* s) { return *reinterpret_cast<const h4*>(s); }
+__device__ __forceinline__ void wr4(_Float16* s, const h4& v) { *reinterpret_cast<h4*>(s) = v; }
+__device__ __forceinline__ h4 cvt4(const f4& v) { return __builtin_convertvector(v, h4); }
+__device__ __forceinline__ H8P planes(const f4& re, const f4& im)
+{
+    H8P x;
+    x.p[0] = cvt4(re);
+    x.p[1] = cvt4(im);
+    return x;
+}
+// (re + i im) * w, or * conj(w), four numbers, fp32
+template <bool CONJ>
+__device__ __forceinline__ void cmul4(f4& re, f4& im, const f4& wr, const f4& wi)
+{
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<1>(s, s, wave + tt * NW, LG - 4, LG - 4, A0, stw, lane);
-        __syncthreads();
+    for (int r = 0; r < 4; ++r) {
+        const float2 v = make_float2(re[r], im[r]), w = make_float2(wr[r], wi[r]);
+        const float2 p = CONJ ? cmulc(v, w) : cmul(v, w);
+        re[r] = p.x;
+        im[r] = p.y;
+    }
+}
+// matrix operands: lane = (o = lane % 16 the result's index, g), entries in order of the input's index i = 4g .. 4g+3
+template <class F>
+__device__ __forceinline__ Cx make_cx(F&& entry, int lane)
+{
+    Cx M;
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<1>(s, s, wave + tt * NW, LG - 8, LG - 8, A1, stw, lane);
-        __syncthreads();
-        // last forward block -> product with the spectrum -> first inverse block, in registers
+    for (int e = 0; e < 4; ++e) {
+        const float2 w = entry(lane & 15, 4 * (lane >> 4) + e);
+        M.re[e] = (_Float16)w.x;
+        M.re[4 + e] = (_Float16)(-w.y);
+        M.im[e] = (_Float16)w.y;
+        M.im[4 + e] = (_Float16)w.x;
+    }
+    return M;
+}
+template <class F>
+__device__ __forceinline__ Rl make_rl(F&& entry, int lane)
+{
+    Rl M;
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            const int pb = (16 * t + (lane & 15)) * 16 + 4 * (lane >> 4), ab = phys(pb);
-            H8U x;
-            x.u = *reinterpret_cast<const uint4*>(&s[ab]);
-            f4 yr, yi;
-            blk16(A2, x.v, yr, yi);
-            const float4 s01 = *reinterpret_cast<const float4*>(&sS[ab]);
-            const float4 s23 = *reinterpret_cast<const float4*>(&sS[ab + 2]);
-            const float2 sv[4] = {make_float2(s01.x, s01.y), make_float2(s01.z, s01.w), make_float2(s23.x, s23.y),
-                                  make_float2(s23.z, s23.w)};
-            H8U m;
+    for (int e = 0; e < 4; ++e) {
+        const float2 w = entry(lane & 15, 4 * (lane >> 4) + e);
+        M.re[e] = (_Float16)w.x;
+        M.im[e] = (_Float16)w.y;
+    }
+    return M;
+}
+__device__ __forceinline__ float2 scaled(float2 w, float s) { return make_float2(w.x * s, w.y * s); }
+__device__ __forceinline__ float2 conj2(float2 w) { return make_float2(w.x, -w.y); }
+
+constexpr int ROW = 17;        // stride of 16 complex numbers in LDS: lanes that read down a column meet 16 different banks
+// entries of the matrices of tile t, from the head's blocks in LDS (forward, then inverse)
+template <int LG>
+struct Entries {
+    using G = Geo<LG>;
+    const float2 *A, *B, *stw;
+    int t;
+    __device__ __forceinline__ float2 w0(int k0) const { return stw[stw_offset(LG) + (k0 << (LG - 4)) + t]; }
+    __device__ __forceinline__ float2 w1(int k1) const { return stw[stw_offset(4 + G::LB) + (k1 << G::LB) + t]; }
+    __device__ __forceinline__ float2 a0(int k0, int d0) const { return scaled(cmul(A[k0 * ROW + d0], w0(k0)), 0.25f); }
+    __device__ __forceinline__ float2 a1(int k1, int d1) const { return scaled(cmul(A[(16 + k1) * ROW + d1], w1(k1)), 0.25f); }
+    __device__ __forceinline__ float2 b1(int d1, int k1) const { return scaled(cmulc(B[(16 + d1) * ROW + k1], w1(k1)), 0.25f); }
+    __device__ __forceinline__ float2 b0(int d0, int k0) const { return scaled(cmulc(B[d0 * ROW + k0], w0(k0)), 0.25f); }
+    // the last block, block diagonal over the k_0's that share a middle tile
+    __device__ __forceinline__ float2 last(const float2* M, int o, int i) const
+    {
+        const float2 v = M[(32 + (o & (G::T - 1))) * ROW + (i & (G::T - 1))];
+        return (o >> G::LB) == (i >> G::LB) ? scaled(v, 1.0f / (float)(1 << stage_shift(G::LB))) : make_float2(0.f, 0.f);
+    }
+};
+// w_256^(c d), d = 4g .. 4g+3
+__device__ __forceinline__ void inner_twiddles(f4& wr, f4& wi, const float2* __restrict__ stw, int lane)
+{
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float2 r = cmul(make_float2(yr[j], yi[j]), sv[j]);
-                m.c[j] = pack(r.x, r.y);
-            }
-            blk16(B2, m.v, yr, yi);
-            H8U o;
+    for (int r = 0; r < 4; ++r) {
+        const float2 v = stw[stw_offset(8) + 16 * (4 * (lane >> 4) + r) + (lane & 15)];
+        wr[r] = v.x;
+        wi[r] = v.y;
+    }
+}
+// What a workgroup of T waves needs of its head travels in whole lines, through LDS: the six blocks (1536 numbers) and the
+// spectrum in natural order (L numbers).  Gathered straight from memory, lane by lane, the
+// constants of a workgroup cost more than eight rows of work.
+template <int LG>
+struct HeadData {
+    using G = Geo<LG>;
+    static constexpr int NT = 64 * G::T, HALF = 3 * NBLK / 2, NB = (2 * HALF + NT - 1) / NT;     // 16-byte pieces of the blocks
+    static constexpr int BLK = 96 * ROW;                                // the spectrum's place behind the blocks
+    static constexpr size_t bytes = sizeof(float2) * (BLK + G::L / 16 * ROW);
+    f4 blk[NB], sp[2];
+    __device__ __forceinline__ void load(const float2* Af, const float2* Ai, const float2* shat, int h, int tid)
+    {
+        const f4* a = reinterpret_cast<const f4*>(Af + (size_t)h * 3 * NBLK);
+        const f4* b = reinterpret_cast<const f4*>(Ai + (size_t)h * 3 * NBLK) - HALF;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float2 r = cmulc(make_float2(yr[j], yi[j]), stage_twiddle(stw, pb + j, LB));
-                o.c[j] = pack(r.x, r.y);
-            }
-            *reinterpret_cast<uint4*>(&s[ab]) = o.u;
+        for (int i = 0; i < NB; ++i) {
+            const int e = min(tid + i * NT, 2 * HALF - 1);
+            blk[i] = (e < HALF ? a : b)[e];
         }
-        __syncthreads();
+        const f4* s = reinterpret_cast<const f4*>(shat + (size_t)h * G::L);
+        sp[0] = s[tid];
+        sp[1] = s[tid + NT];
+    }
+    static __device__ __forceinline__ void put2(float2* sm, int e, const f4& v)      // numbers 2e, 2e + 1
+    {
+        float2* p = sm + (e >> 3) * ROW + 2 * (e & 7);
+        p[0] = make_float2(v[0], v[1]);
+        p[1] = make_float2(v[2], v[3]);
+    }
+    __device__ __forceinline__ void put(float2* sm, int tid) const
+    {
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<2>(s, s, wave + tt * NW, LG - 8, LG - 4, B1, stw, lane);
-        __syncthreads();
-#pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<0>(s, s, wave + tt * NW, LG - 4, 0, B0, stw, lane);
-        __syncthreads();
-        store_row<IO>(s, y + row_off(b, h, H, N), N, yscale, tid, NW * 64);
-        __syncthreads();
+        for (int i = 0; i < NB; ++i)
+            if (NB * NT == 2 * HALF || tid + i * NT < 2 * HALF) put2(sm, tid + i * NT, blk[i]);
+        put2(sm + BLK, tid, sp[0]);
+        put2(sm + BLK, tid + NT, sp[1]);
+    }
+};
+
+// frequency in slot s of middle tile m at k_1 (row: stride of 16 numbers)
+template <int LG>
+__device__ __forceinline__ int freq_at(int m, int s, int k1, int row = 16)
+{
+    using G = Geo<LG>;
+    return m * (16 / G::T) + (s >> G::LB) + row * (k1 + 16 * (s & (G::T - 1)));
+}
+
+template <class IO>
+__device__ __forceinline__ uint32_t to_h2(uint32_t w)
+{
+    if constexpr (std::is_same<IO, IoBF16>::value) {
+        const h2 h = pack(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+        return __builtin_bit_cast(uint32_t, h);
+    }
+    return w;
+}
+// Samples 2 tid, 2 tid + 1 of a row into the tiles [t][d_0][d_1] of the workgroup's T waves, and back
+template <int LG>
+__device__ __forceinline__ void row_in(_Float16* s, uint32_t w, int tid)
+{
+    using G = Geo<LG>;
+    const h2 v = __builtin_bit_cast(h2, w);
+    const int e = (2 * tid) >> G::LB;          // d_0, d_1; a row's quarters are XORed with d_0 / 4
+    _Float16* p = s + ((2 * tid) & (G::T - 1)) * G::IS + (e ^ ((e >> 6) << 2));
+    p[0] = v[0];
+    p[G::IS] = v[1];
+}
+template <int LG>
+__device__ __forceinline__ uint32_t row_out(const _Float16* s, int tid)
+{
+    using G = Geo<LG>;
+    const int e = (2 * tid) >> G::LB;
+    const uint16_t* p = reinterpret_cast<const uint16_t*>(s) + ((2 * tid) & (G::T - 1)) * G::OS + (e ^ ((e >> 6) << 2));
+    return (uint32_t)p[0] | ((uint32_t)p[G::OS] << 16);
+}
+// four results of a row's tile (lane d_0 < 8, d_1 = 4g ..) as I/O numbers
+template <class IO>
+__device__ __forceinline__ void put_out(_Float16* tile, const f4& v, int lane)
+{
+    if ((lane & 15) >= 8) return;
+    _Float16* p = tile + (lane & 15) * 16 + 4 * ((lane >> 4) ^ ((lane & 15) >> 2));
+    if constexpr (std::is_same<IO, IoBF16>::value) {
+        typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<b4*>(p) = __builtin_convertvector(v, b4);
+    } else {
+        wr4(p, cvt4(v));
     }
 }
 
 // -------------------------------------------------------------------------------------------------------------------
-// Backward.  grid = (nsplit, H): workgroup (sp, h) owns rows b = sp, sp + nsplit, ... of head h, accumulates the
+// Forward.  One wave per tile: wave t owns tile t of the 16-point blocks and middle tile t.  The grid is what the device holds
+// at once; a workgroup takes `per` consecutive rows of the (head, batch row) list, head by head, as a pipeline with two
+// barriers per row:
+//     [inverse blocks of row b-1, forward blocks of row b]  barrier  [last blocks and spectrum of row b, rows in and out]
+// (a wave's tile of the exchange buffer is its own in the first part, so the two rows need one buffer).  Bound by issue: 11
+// matrix and 83 vector instructions per 256 points and row; two rows per barrier were no faster.  The form it replaced took
+// every block through LDS with its own addresses, twiddle loads and barrier: B=16, H=768, N=1024 bf16 77 us, this one 36
+// (53 before the quarters were hashed, 41 with a workgroup per 8 rows of one head).
+// -------------------------------------------------------------------------------------------------------------------
+template <int LG, class IO>
+__global__ void __launch_bounds__(64 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(4)))
+lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ shat, const float2* __restrict__ Af,
+              const float2* __restrict__ Ai, typename IO::T* __restrict__ y, int B, int H, int64_t per,
+              const float2* __restrict__ stw)
+{
+    using G = Geo<LG>;
+    constexpr int T = G::T, N = G::N;
+    constexpr size_t work = sizeof(_Float16) * T * (G::XS + G::IS + G::OS);
+    __shared__ f4 smem[(work > HeadData<LG>::bytes ? work : HeadData<LG>::bytes) / 16];
+    _Float16 *ex = reinterpret_cast<_Float16*>(smem), *in = ex + T * G::XS, *outb = in + T * G::IS;
+    float2* sm2 = reinterpret_cast<float2*>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, t = tid >> 6, c = lane & 15, g = lane >> 4;
+    _Float16* mine = ex + G::at(t, c, g);                                            // (k_0 = c, k_1 = 4g ..) of tile t
+    const _Float16* tin = in + t * G::IS + 16 * (c >> 2) + 64 * g + 4 * ((c & 3) ^ g);   // transposed: lane d_1, d_0 = 4g ..
+    const _Float16* mid_in = ex + G::slot_at(t, 4 * g + (c >> 2), c & 3);            // transposed: lane k_1, slots 4g ..
+    _Float16* mid_out = ex + G::slot_at(t, c, g);                                    // lane slot, k_1 = 4g ..
+    f4 cr, ci;
+    inner_twiddles(cr, ci, stw, lane);
+
+    int64_t item = (int64_t)blockIdx.x * per;
+    const int64_t end = item + per < (int64_t)B * H ? item + per : (int64_t)B * H;
+    while (item < end) {
+        const int h = (int)(item / B), b0 = (int)(item - (int64_t)h * B);
+        const int n = (int)(end - item < B - b0 ? end - item : B - b0);              // rows b0 .. b0 + n of this head
+        item += n;
+        HeadData<LG> hd;
+        hd.load(Af, Ai, shat, h, tid);
+        const uint32_t* up = reinterpret_cast<const uint32_t*>(u + row_off(b0, h, H, N)) + tid;
+        uint32_t* yp = reinterpret_cast<uint32_t*>(y + row_off(b0, h, H, N)) + tid;
+        const size_t step = (size_t)H * (N / 2);
+        uint32_t w = *up, wn = n > 1 ? up[step] : 0u;
+        up += 2 * step;
+        hd.put(sm2, tid);
+        __syncthreads();
+        const Entries<LG> E{sm2, sm2 + 48 * ROW, stw, t};
+        const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i); }, lane);
+        const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i); }, lane);
+        const Cx A2 = make_cx([&](int o, int i) { return E.last(E.A, o, i); }, lane);
+        const Cx B2 = make_cx([&](int o, int i) { return E.last(E.B, o, i); }, lane);
+        const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i); }, lane);
+        const h8 B0 = make_cx([&](int o, int i) { return scaled(E.b0(o, i), G::yscale()); }, lane).re;
+        f4 sr, si;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float2 s = sm2[HeadData<LG>::BLK + freq_at<LG>(t, 4 * g + r, c, ROW)];
+            sr[r] = s.x;
+            si[r] = s.y;
+        }
+        __syncthreads();
+        for (int i = tid; i < T * G::IS / 2; i += 64 * T) reinterpret_cast<uint32_t*>(in)[i] = 0;
+        __syncthreads();
+        row_in<LG>(in, to_h2<IO>(w), tid);
+        __syncthreads();
+
+        const auto forward = [&]() {
+            const h4 x = tr_read(tin);
+            f4 yr = mm(x, A0.re), yi = mm(x, A0.im);                    // lane k_0, d_1 = 4g ..
+            cmul4<false>(yr, yi, cr, ci);
+            const H8P x1 = planes(yr, yi);
+            const H8P x2 = planes(mm(A1.re, x1.v), mm(A1.im, x1.v));    // lane k_0, k_1 = 4g ..
+            wr4(mine, x2.p[0]);
+            wr4(mine + 256, x2.p[1]);
+        };
+        const auto middle = [&]() {
+            H8P x;
+            x.p[0] = tr_read(mid_in);
+            x.p[1] = tr_read(mid_in + 256);
+            f4 zr = mm(A2.re, x.v), zi = mm(A2.im, x.v);                // lane k_1, slots 4g ..
+            cmul4<false>(zr, zi, sr, si);
+            const H8P m = planes(zr, zi);
+            const H8P v = planes(mm(m.v, B2.re), mm(m.v, B2.im));       // lane slot, k_1 = 4g ..
+            wr4(mid_out, v.p[0]);
+            wr4(mid_out + 256, v.p[1]);
+        };
+        const auto inverse = [&]() {
+            H8P x;
+            x.p[0] = rd4(mine);
+            x.p[1] = rd4(mine + 256);
+            f4 yr = mm(x.v, B1.re), yi = mm(x.v, B1.im);                // lane d_1, k_0 = 4g ..
+            cmul4<true>(yr, yi, cr, ci);
+            put_out<IO>(outb + t * G::OS, mm(planes(yr, yi).v, B0), lane);
+        };
+        const auto next_row_in = [&](int b) {                           // row b + 1; row b + 2 asked for
+            row_in<LG>(in, to_h2<IO>(wn), tid);
+            if (b + 2 < n) {
+                wn = *up;
+                up += step;
+            }
+        };
+        forward();
+        __syncthreads();
+        middle();
+        next_row_in(0);
+        __syncthreads();
+        for (int b = 1; b < n; ++b) {
+            inverse();
+            forward();
+            __syncthreads();
+            *yp = row_out<LG>(outb, tid);
+            yp += step;
+            middle();
+            next_row_in(b);
+            __syncthreads();
+        }
+        inverse();
+        __syncthreads();
+        *yp = row_out<LG>(outb, tid);
+        __syncthreads();                                                // (the next head's constants go where the rows were)
+    }
+}
+
+// -------------------------------------------------------------------------------------------------------------------
+// Backward, register-chained.  grid = (nsplit, H): workgroup (sp, h) owns rows b = sp, sp + nsplit, ... of head h, one wave per
+// tile.  dy goes through the adjoint of the inverse blocks exactly as u goes through the forward blocks, so the pipeline is the
+// forward kernel's with two rows in flight side by side, and the same two barriers:
+//     [row b-1: the input of B_0 from that of B_1; gradients through A_1, A_0; du.  row b: u through A_0, A_1, dy through
+//      B_0^H, B_1^H]  barrier  [row b: last blocks, spectrum, and their adjoints]
+// The gradient of a block is the 16 x 16 sum over columns of (gradient at its output) x conj(its input): two more matrix
+// products per tile with the columns as K, on operands whose lanes are the slots.  Both index orders of a tile are needed
+// for that; those that pass the exchange buffers are read from there either way, the others take a wave's own 1 KB of LDS.
+// The twiddle factors that were folded into a tile's matrices scale rows or columns of its 16 x 16 sums: applied once, at
+// the end, where the waves' sums meet in wave order.  Per 256 points and row 33 matrix and 187 vector instructions; 240
+// registers (matrices 76, sums 48).  B=16, H=768, N=1024 bf16: 105 us; the form it replaced (every block a trip through LDS
+// with its own barrier, seven buffers) 292 and 9.3 to add its partial sums.
+// -------------------------------------------------------------------------------------------------------------------
+struct LbGrads {            // where the sums go: of share sp and head h at index sp * H + h
+    float2 *shat, *qf, *qi;
+    int q_stride;
+};
+
+template <int LG>
+constexpr int lbb_numbers() { return Geo<LG>::T * (2 * Geo<LG>::XS + 2 * Geo<LG>::IS + Geo<LG>::OS + 512); }
+template <int LG>
+constexpr size_t lbb_lds()
+{
+    const size_t work = sizeof(_Float16) * lbb_numbers<LG>(), red = sizeof(float2) * 2 * NBLK * Geo<LG>::T;
+    const size_t a = work > red ? work : red;
+    return a > HeadData<LG>::bytes ? a : HeadData<LG>::bytes;
+}
+
+__device__ __forceinline__ void outer(const H8P& G, const H8P& X, f4& qr, f4& qi)
+{
+    H8P s;
+    s.u[0] = make_uint2(X.u[1].x ^ 0x80008000u, X.u[1].y ^ 0x80008000u);
+    s.u[1] = X.u[0];
+    qr = __builtin_amdgcn_mfma_f32_16x16x32_f16(G.v, X.v, qr, 0, 0, 0);      // Gr Xr + Gi Xi
+    qi = __builtin_amdgcn_mfma_f32_16x16x32_f16(G.v, s.v, qi, 0, 0, 0);      // Gi Xr - Gr Xi
+}
+
+template <int LG, class IO>
+__global__ void __launch_bounds__(64 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(2)))
+lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
+              const float2* __restrict__ shat, const float2* __restrict__ Af, const float2* __restrict__ Ai,
+              typename IO::T* __restrict__ du, LbGrads out, int B, int H, const float2* __restrict__ stw)
+{
+    using G = Geo<LG>;
+    constexpr int T = G::T, N = G::N, LB = G::LB;
+    __shared__ f4 smem[lbb_lds<LG>() / 16];
+    _Float16 *exu = reinterpret_cast<_Float16*>(smem), *exg = exu + T * G::XS, *inu = exg + T * G::XS;
+    _Float16 *ing = inu + T * G::IS, *outb = ing + T * G::IS, *priv = outb + T * G::OS;
+    float2* sm2 = reinterpret_cast<float2*>(smem);
+    const int sp = blockIdx.x, nsplit = gridDim.x, h = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, t = tid >> 6, c = lane & 15, g = lane >> 4;
+    const size_t step = (size_t)nsplit * H * (N / 2);
+    const uint32_t* up = reinterpret_cast<const uint32_t*>(u + row_off(sp, h, H, N)) + tid;
+    const uint32_t* gp = reinterpret_cast<const uint32_t*>(dy + row_off(sp, h, H, N)) + tid;
+    uint32_t* dp = reinterpret_cast<uint32_t*>(du ? du + row_off(sp, h, H, N) : nullptr) + tid;
+    const int n = (B - sp + nsplit - 1) / nsplit;                       // rows of this workgroup
+    HeadData<LG> hd;
+    hd.load(Af, Ai, shat, h, tid);
+    uint32_t wu = *up, wg = *gp, nu = 0, ng = 0;
+    if (n > 1) { nu = up[step]; ng = gp[step]; }
+    up += 2 * step;
+    gp += 2 * step;
+    f4 cr, ci;
+    inner_twiddles(cr, ci, stw, lane);
+    hd.put(sm2, tid);
+    __syncthreads();
+    const Entries<LG> E{sm2, sm2 + 48 * ROW, stw, t};
+    const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i); }, lane);
+    const Rl B0H = make_rl([&](int o, int i) { return conj2(E.b0(i, o)); }, lane);
+    const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i); }, lane);
+    const Cx A1H = make_cx([&](int o, int i) { return conj2(E.a1(i, o)); }, lane);
+    const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i); }, lane);
+    const Cx B1H = make_cx([&](int o, int i) { return conj2(E.b1(i, o)); }, lane);
+    const Cx A2 = make_cx([&](int o, int i) { return E.last(E.A, o, i); }, lane);
+    const Cx A2H = make_cx([&](int o, int i) { return conj2(E.last(E.A, i, o)); }, lane);
+    const Cx B2 = make_cx([&](int o, int i) { return E.last(E.B, o, i); }, lane);
+    const Cx B2H = make_cx([&](int o, int i) { return conj2(E.last(E.B, i, o)); }, lane);
+    const h8 A0H = make_cx([&](int o, int i) { return scaled(conj2(E.a0(i, o)), G::yscale()); }, lane).re;
+    f4 sr, si;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float2 s = sm2[HeadData<LG>::BLK + freq_at<LG>(t, 4 * g + r, c, ROW)];
+        sr[r] = s.x;
+        si[r] = s.y;
+    }
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 a0r = zero, a0i = zero, a1r = zero, a1i = zero, a2r = zero, a2i = zero;      // sums of the blocks' gradients
+    f4 b0r = zero, b0i = zero, b1r = zero, b1i = zero, b2r = zero, b2i = zero;
+    f4 dsr = zero, dsi = zero;
+
+    const int own = G::at(t, c, g), own_tr = G::at(t, 4 * g + (c >> 2), c & 3);      // tile t: row c, or transposed
+    const int mid = G::slot_at(t, c, g), mid_tr = G::slot_at(t, 4 * g + (c >> 2), c & 3);
+    const int trow = 16 * (4 * g + (c >> 2)) + 4 * ((c & 3) ^ g), row = 16 * c + 4 * (g ^ (c >> 2));   // a plain 16 x 16 tile
+    const _Float16 *tu = inu + t * G::IS, *tg = ing + t * G::IS;
+    _Float16* pv = priv + t * 512;
+    const auto transposed = [&](const H8P& x) {
+        H8P y;
+        wr4(pv + row, x.p[0]);
+        wr4(pv + row + 256, x.p[1]);
+        y.p[0] = tr_read(pv + trow);
+        y.p[1] = tr_read(pv + trow + 256);
+        return y;
+    };
+    __syncthreads();
+    for (int i = tid; i < T * G::IS; i += 64 * T) reinterpret_cast<uint32_t*>(inu)[i] = 0;       // both rows' tiles
+    __syncthreads();
+    row_in<LG>(inu, to_h2<IO>(wu), tid);
+    row_in<LG>(ing, to_h2<IO>(wg), tid);
+    __syncthreads();
+
+    H8P x1t, g1t;           // kept from a row's first part to its last
+    h4 uo, go;
+    const auto first = [&]() {
+        {
+            const h4 x = tr_read(tu + trow);
+            uo = rd4(tu + row);                                         // lane d_0, d_1 = 4g ..
+            f4 yr = mm(x, A0.re), yi = mm(x, A0.im);                    // lane k_0, d_1 = 4g ..
+            cmul4<false>(yr, yi, cr, ci);
+            const H8P x1 = planes(yr, yi);
+            x1t = transposed(x1);                                       // lane d_1, k_0 = 4g ..
+            const H8P x2 = planes(mm(A1.re, x1.v), mm(A1.im, x1.v));    // lane k_0, k_1 = 4g ..
+            wr4(exu + own, x2.p[0]);
+            wr4(exu + own + 256, x2.p[1]);
+        }
+        {
+            const h4 x = tr_read(tg + trow);
+            go = rd4(tg + row);
+            f4 yr = mm(x, B0H.re), yi = mm(x, B0H.im);
+            cmul4<false>(yr, yi, cr, ci);
+            const H8P g1 = planes(yr, yi);
+            g1t = transposed(g1);
+            const H8P g2 = planes(mm(B1H.re, g1.v), mm(B1H.im, g1.v));
+            wr4(exg + own, g2.p[0]);
+            wr4(exg + own + 256, g2.p[1]);
+        }
+    };
+    const auto middle = [&]() {
+        H8P x, xt, y, yt;
+        x.p[0] = tr_read(exu + mid_tr);                                 // lane k_1, slots 4g ..
+        x.p[1] = tr_read(exu + mid_tr + 256);
+        xt.p[0] = rd4(exu + mid);                                       // lane slot, k_1 = 4g ..
+        xt.p[1] = rd4(exu + mid + 256);
+        y.p[0] = tr_read(exg + mid_tr);
+        y.p[1] = tr_read(exg + mid_tr + 256);
+        yt.p[0] = rd4(exg + mid);
+        yt.p[1] = rd4(exg + mid + 256);
+        const f4 zr = mm(A2.re, x.v), zi = mm(A2.im, x.v);              // the transform of u: lane k_1, slots 4g ..
+        f4 wr = zr, wi = zi;
+        cmul4<false>(wr, wi, sr, si);
+        const H8P w = planes(wr, wi);
+        const H8P wt = transposed(w);
+        const H8P v = planes(mm(w.v, B2.re), mm(w.v, B2.im));           // lane slot, k_1 = 4g ..
+        wr4(exu + mid, v.p[0]);
+        wr4(exu + mid + 256, v.p[1]);
+        outer(yt, wt, b2r, b2i);
+        f4 hr = mm(B2H.re, y.v), hi = mm(B2H.im, y.v);                  // gradient at the product with the spectrum
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            dsr[r] += hr[r] * zr[r] + hi[r] * zi[r];
+            dsi[r] += hi[r] * zr[r] - hr[r] * zi[r];
+        }
+        cmul4<true>(hr, hi, sr, si);
+        const H8P q = planes(hr, hi);
+        const H8P qt = transposed(q);
+        const H8P p = planes(mm(q.v, A2H.re), mm(q.v, A2H.im));
+        wr4(exg + mid, p.p[0]);
+        wr4(exg + mid + 256, p.p[1]);
+        outer(qt, xt, a2r, a2i);
+    };
+    const auto last = [&]() {
+        {
+            H8P v, vt;
+            v.p[0] = rd4(exu + own);                                    // lane k_0, k_1 = 4g ..
+            v.p[1] = rd4(exu + own + 256);
+            vt.p[0] = tr_read(exu + own_tr);                            // lane k_1, k_0 = 4g ..
+            vt.p[1] = tr_read(exu + own_tr + 256);
+            f4 yr = mm(B1.re, v.v), yi = mm(B1.im, v.v);                // lane k_0, d_1 = 4g ..
+            cmul4<true>(yr, yi, cr, ci);
+            const H8P w0 = planes(yr, yi);
+            outer(g1t, vt, b1r, b1i);
+            b0r = __builtin_amdgcn_mfma_f32_16x16x16f16(go, w0.p[0], b0r, 0, 0, 0);
+            b0i = __builtin_amdgcn_mfma_f32_16x16x16f16(go, w0.p[1], b0i, 0, 0, 0);     // (minus the imaginary part)
+        }
+        {
+            H8P v, vt;
+            v.p[0] = rd4(exg + own);
+            v.p[1] = rd4(exg + own + 256);
+            vt.p[0] = tr_read(exg + own_tr);
+            vt.p[1] = tr_read(exg + own_tr + 256);
+            f4 yr = mm(v.v, A1H.re), yi = mm(v.v, A1H.im);              // lane d_1, k_0 = 4g ..
+            cmul4<true>(yr, yi, cr, ci);
+            const H8P g6 = planes(yr, yi);
+            outer(vt, x1t, a1r, a1i);
+            const H8P g6t = transposed(g6);                             // lane k_0, d_1 = 4g ..
+            a0r = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[0], uo, a0r, 0, 0, 0);
+            a0i = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[1], uo, a0i, 0, 0, 0);
+            put_out<IO>(outb + t * G::OS, mm(g6.v, A0H), lane);
+        }
+    };
+    const auto rows_in = [&](int b) {                                   // row b + 1; row b + 2 asked for
+        row_in<LG>(inu, to_h2<IO>(nu), tid);
+        row_in<LG>(ing, to_h2<IO>(ng), tid);
+        if (b + 2 < n) {
+            nu = *up;
+            ng = *gp;
+            up += step;
+            gp += step;
+        }
+    };
+    first();
+    __syncthreads();
+    middle();
+    rows_in(0);
+    __syncthreads();
+    for (int b = 1; b < n; ++b) {
+        last();
+        first();
+        __syncthreads();
+        if (du) {
+            *dp = row_out<LG>(outb, tid);
+            dp += step;
+        }
+        middle();
+        rows_in(b);
+        __syncthreads();
+    }
+    last();
+    __syncthreads();
+    if (du) *dp = row_out<LG>(outb, tid);
+
+    const size_t at = (size_t)sp * H + h;
+    if (out.shat) {
+        float2* ps = out.shat + at * G::L;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ps[freq_at<LG>(t, 4 * g + r, c)] = make_float2(dsr[r] * G::yscale(), dsi[r] * G::yscale());
+    }
+    // the waves' sums of one block of either chain, [chain][wave][entry]; then entry by entry in wave order
+    const float2 w0c = E.w0(c), w1c = E.w1(c);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 4 * g + r, e = i * 16 + c;
+            float2 f, q;
+            if (s == 0) {
+                f = cmulc(make_float2(a0r[r], a0i[r]), E.w0(i));
+                q = cmul(make_float2(b0r[r], -b0i[r]), w0c);
+            } else if (s == 1) {
+                f = cmulc(make_float2(a1r[r], a1i[r]), E.w1(i));
+                q = cmul(make_float2(b1r[r], b1i[r]), w1c);
+            } else {
+                f = make_float2(a2r[r], a2i[r]);
+                q = make_float2(b2r[r], b2i[r]);
+            }
+            sm2[t * NBLK + e] = f;
+            sm2[(T + t) * NBLK + e] = q;
+        }
+        __syncthreads();
+        const float sc = G::yscale() / (float)(1 << stage_shift(s == 2 ? LB : 4));
+        for (int e2 = tid; e2 < 2 * NBLK; e2 += 64 * T) {
+            const int chain = e2 / NBLK, e = e2 % NBLK, i = e / 16, j = e % 16;
+            float2* q = chain ? out.qi : out.qf;
+            if (!q) continue;
+            float2 a = make_float2(0.f, 0.f);
+            const float2* p = sm2 + chain * T * NBLK;
+            if (s < 2) {
+                for (int w = 0; w < T; ++w) a = cadd(a, p[w * NBLK + e]);
+            } else if (i < T && j < T) {             // the diagonal blocks of I (x) A_2 all carry the same parameters
+                for (int w = 0; w < T; ++w)
+                    for (int d = 0; d < 16; d += T) a = cadd(a, p[w * NBLK + (d + i) * 16 + d + j]);
+            }
+            q[at * out.q_stride + s * NBLK + e] = make_float2(a.x * sc, a.y * sc);
+        }
+    }
+}
+
+// Sums the partial results over the shares (fixed order): grid (pieces of a head's results, H)
+__global__ void __launch_bounds__(256)
+lb_reduce_kernel(const float2* __restrict__ part_shat, const float2* __restrict__ part_q, float2* __restrict__ dshat,
+                 float2* __restrict__ dAf, float2* __restrict__ dAi, int64_t H, int L, int nsplit)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x, h = blockIdx.y;
+    const float2* p;
+    size_t stride;
+    float2* out;
+    if (e < L) {
+        p = part_shat + (size_t)h * L + e;
+        stride = (size_t)H * L;
+        out = dshat ? dshat + (size_t)h * L + e : nullptr;
+    } else {
+        const int q = e - L;
+        if (q >= 6 * NBLK) return;
+        p = part_q + (size_t)h * 6 * NBLK + q;
+        stride = (size_t)H * 6 * NBLK;
+        float2* d = q < 3 * NBLK ? dAf : dAi;
+        out = d ? d + (size_t)h * 3 * NBLK + q % (3 * NBLK) : nullptr;
+    }
+    if (!out) return;
+    float2 a = make_float2(0.f, 0.f);
+    for (int sp = 0; sp < nsplit; ++sp) a = cadd(a, p[sp * stride]);
+    *out = a;
+}
+
+// -------------------------------------------------------------------------------------------------------------------
+// Backward of N = 2048 (sixteen tiles would be two per wave, whose matrices and sums do not fit the registers), with every
+// block a trip through LDS.  grid = (nsplit, H): workgroup (sp, h) owns rows b = sp, sp + nsplit, ... of head h, accumulates the
 // gradients of the head's six blocks and of its spectrum in registers over those rows and writes them as partial
 // results, which lb_reduce_kernel sums in a fixed order.  LDS: the spectrum, X0, X1, X2 (inputs of the forward
 // blocks), W2, W1, W0 (inputs of the inverse blocks), G (the gradient, in place).
 // -------------------------------------------------------------------------------------------------------------------
 template <int LG, class IO>
-__global__ void __launch_bounds__(lbb_waves(LG) * 64) __attribute__((amdgpu_waves_per_eu(2)))
-lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
+__global__ void __launch_bounds__(LBB_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
+lb_bwd_lds_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
               const float2* __restrict__ shat, const float2* __restrict__ Af, const float2* __restrict__ Ai,
-              typename IO::T* __restrict__ du, float2* __restrict__ part_shat, float2* __restrict__ part_q, int64_t B,
-              int64_t H, const float2* __restrict__ stw)
+              typename IO::T* __restrict__ du, LbGrads out, int64_t B, int64_t H, const float2* __restrict__ stw)
 {
     extern __shared__ uint4 smem_raw[];
-    constexpr int NW = lbb_waves(LG), L = 1 << LG, N = L / 2, T = L / 256, LB = LG - 8, TPW = T / NW;
+    constexpr int NW = LBB_WAVES, L = 1 << LG, N = L / 2, T = L / 256, LB = LG - 8, TPW = T / NW;
     float2* sS = reinterpret_cast<float2*>(smem_raw);                 // the spectrum in position order
     h2* bX0 = reinterpret_cast<h2*>(sS + L);
     h2 *bX1 = bX0 + L, *bX2 = bX1 + L, *bW2 = bX2 + L, *bW1 = bW2 + L, *bW0 = bW1 + L, *bG = bW0 + L;
@@ -479,14 +1069,15 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
     }
 
     // gradient of the spectrum: every position is owned by one lane
-    float2* ps = part_shat + ((size_t)sp * H + h) * L;
+    const size_t at = (size_t)sp * H + h;
+    float2* ps = out.shat + at * L;
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) {
         const int t = wave + tt * NW;
         const int pb = (16 * t + (lane & 15)) * 16 + 4 * (lane >> 4);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            ps[freq_of<LG>(pb + j)] = make_float2(acc_s[tt][j].x * yscale, acc_s[tt][j].y * yscale);
+            if (out.shat) ps[freq_of<LG>(pb + j)] = make_float2(acc_s[tt][j].x * yscale, acc_s[tt][j].y * yscale);
     }
     // gradients of the blocks: the waves add their 16 x 16 sums into one LDS copy, one wave after the other
     float2* red = reinterpret_cast<float2*>(smem_raw);          // [6][256]
@@ -508,42 +1099,11 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
         }
         __syncthreads();
     }
-    float2* pq = part_q + ((size_t)sp * H + h) * 6 * NBLK;
     for (int e = tid; e < 6 * NBLK; e += NW * 64) {
         const int s = (e / NBLK) % 3;
         const float sc = yscale / (float)(1 << stage_shift(s == 2 ? LB : 4));
-        pq[e] = make_float2(red[e].x * sc, red[e].y * sc);
-    }
-}
-
-// Sums the partial results over the splits (fixed order).  Blocks: the last stage's 16 x 16 sum is folded onto its
-// r x r corner (the diagonal blocks of I (x) A_2 all carry the same parameters); entries outside the corner are zero.
-__global__ void __launch_bounds__(256)
-lb_reduce_kernel(const float2* __restrict__ part_shat, const float2* __restrict__ part_q, float2* __restrict__ dshat,
-                 float2* __restrict__ dAf, float2* __restrict__ dAi, int64_t H, int L, int LB, int nsplit)
-{
-    const int h = blockIdx.x, tid = threadIdx.x;
-    if (dshat)
-        for (int f = tid; f < L; f += 256) {
-            float2 a = make_float2(0.f, 0.f);
-            for (int sp = 0; sp < nsplit; ++sp) a = cadd(a, part_shat[((size_t)sp * H + h) * L + f]);
-            dshat[(size_t)h * L + f] = a;
-        }
-    const int r = 1 << LB;
-    for (int e = tid; e < 6 * NBLK; e += 256) {
-        const int which = e / (3 * NBLK), s = (e / NBLK) % 3, i = (e % NBLK) / 16, j = e % 16;
-        float2* out = which ? dAi : dAf;
-        if (!out) continue;
-        float2 a = make_float2(0.f, 0.f);
-        if (s < 2) {
-            for (int sp = 0; sp < nsplit; ++sp) a = cadd(a, part_q[((size_t)sp * H + h) * 6 * NBLK + e]);
-        } else if (i < r && j < r) {
-            for (int sp = 0; sp < nsplit; ++sp)
-                for (int blk = 0; blk < 16 / r; ++blk)
-                    a = cadd(a, part_q[((size_t)sp * H + h) * 6 * NBLK + (which * 3 + 2) * NBLK +
-                                       (blk * r + i) * 16 + blk * r + j]);
-        }
-        out[((size_t)h * 3 + s) * NBLK + i * 16 + j] = a;
+        float2* q = e < 3 * NBLK ? out.qf : out.qi;
+        if (q) q[at * out.q_stride + e % (3 * NBLK)] = make_float2(red[e].x * sc, red[e].y * sc);
     }
 }
 
@@ -558,50 +1118,59 @@ hipError_t fwd_go(const void* u, const float* shat, const float* Af, const float
                   const Tables& tb, hipStream_t st)
 {
     using T = typename IO::T;
-    constexpr int NW = lb_waves(LG);
-    const size_t lds = (size_t)(1 << LG) * (sizeof(h2) + sizeof(float2));
-    // enough workgroups to fill the device several times over, each keeping its head's blocks for all its rows
-    const int64_t want = (int64_t)compute_units() * 16;
-    int64_t rows = (B * H + want - 1) / want;
-    if (rows < 4) rows = 4;            // the spectrum is staged once per workgroup: not for fewer rows than this
-    if (rows > B) rows = B;
-    const unsigned groups = (unsigned)((B + rows - 1) / rows);
-    hipError_t e = set_lds(lb_fwd_kernel<LG, IO>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((lb_fwd_kernel<LG, IO>), dim3(groups, (unsigned)H), dim3(NW * 64), lds, st, (const T*)u,
-                       (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)y, B, H, (int)rows, tb.stw);
+    static int resident = 0;       // workgroups the device holds at once
+    if (resident == 0) {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, lb_fwd_kernel<LG, IO>, 64 << (LG - 8), 0) != hipSuccess) nb = 1;
+        resident = (nb > 0 ? nb : 1) * compute_units();
+    }
+    const int64_t rows = B * H, per = (rows + resident - 1) / resident;      // even shares of the device
+    hipLaunchKernelGGL((lb_fwd_kernel<LG, IO>), dim3((unsigned)((rows + per - 1) / per)), dim3(64 << (LG - 8)), 0, st,
+                       (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)y, (int)B, (int)H, per, tb.stw);
     return hipGetLastError();
 }
 
 template <int LG, class IO>
 hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float* Af, const float* Ai, void* du,
-                  float2* part_shat, float2* part_q, int64_t B, int64_t H, int nsplit, const Tables& tb, hipStream_t st)
+                  const LbGrads& out, int64_t B, int64_t H, int nsplit, const Tables& tb, hipStream_t st)
 {
     using T = typename IO::T;
-    constexpr int NW = lbb_waves(LG);
-    size_t lds = (size_t)(1 << LG) * (7 * sizeof(h2) + sizeof(float2));
-    const size_t red = (size_t)6 * NBLK * sizeof(float2);
-    if (lds < red) lds = red;
-    hipError_t e = set_lds(lb_bwd_kernel<LG, IO>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((lb_bwd_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(NW * 64), lds, st,
-                       (const T*)dy, (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du,
-                       part_shat, part_q, B, H, tb.stw);
+    if constexpr (LG == 12) {
+        const size_t lds = (size_t)(1 << LG) * (7 * sizeof(h2) + sizeof(float2));
+        hipError_t e = set_lds(lb_bwd_lds_kernel<LG, IO>, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((lb_bwd_lds_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(LBB_WAVES * 64), lds, st,
+                           (const T*)dy, (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du,
+                           out, B, H, tb.stw);
+    } else {
+        hipLaunchKernelGGL((lb_bwd_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(64 << (LG - 8)), 0, st,
+                           (const T*)dy, (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du, out,
+                           (int)B, (int)H, tb.stw);
+    }
     return hipGetLastError();
 }
 
 }  // namespace
 
-int lbfly_nsplit(int64_t B, int64_t H)
+// Shares of a head's rows: the number that ends first, ceil(512 / H) at most, where 8 / T workgroups of T waves run on each of
+// 256 compute units.  A share's matrices and sums take as long as about six rows (8.5 us at N = 1024, a row 1.6), two of the
+// slower rows of N = 2048; more than one share is a second launch.
+int lbfly_nsplit(int64_t B, int64_t H, int64_t N)
 {
-    int64_t n = (512 + H - 1) / H;
-    if (n > B) n = B;
-    return (int)(n < 1 ? 1 : n);
+    const int64_t most = (512 + H - 1) / H < B ? (512 + H - 1) / H : B;
+    const int64_t resident = N == 2048 ? 256 : 256 * (1024 / N);
+    const int64_t setup = N == 2048 ? 2 : 6, launch = N == 2048 ? 1 : 3;
+    int64_t best = 1, best_t = -1;
+    for (int64_t n = 1; n <= most; ++n) {
+        const int64_t t = (n * H + resident - 1) / resident * ((B + n - 1) / n + setup) + (n > 1 ? launch : 0);
+        if (best_t < 0 || t < best_t) { best = n; best_t = t; }
+    }
+    return (int)best;
 }
 
 size_t lbfly_partial_bytes(int64_t B, int64_t H, int64_t N)
 {
-    return (size_t)lbfly_nsplit(B, H) * (size_t)H * ((size_t)(2 * N) + 6 * NBLK) * sizeof(float2);
+    return (size_t)lbfly_nsplit(B, H, N) * (size_t)H * ((size_t)(2 * N) + 6 * NBLK) * sizeof(float2);
 }
 
 hipError_t lbfly_fwd(const void* u, const float* shat, const float* Af, const float* Ai, void* y, int64_t B, int64_t H,
@@ -624,13 +1193,15 @@ hipError_t lbfly_bwd(const void* dy, const void* u, const float* shat, const flo
                      float* dshat, float* dAf, float* dAi, void* partials, int64_t B, int64_t H, int64_t N, int io,
                      const Tables& tb, hipStream_t st)
 {
-    const int nsplit = lbfly_nsplit(B, H);
+    const int nsplit = lbfly_nsplit(B, H, N);
     float2* part_shat = (float2*)partials;
     float2* part_q = part_shat + (size_t)nsplit * H * 2 * N;
+    const LbGrads out = nsplit == 1 ? LbGrads{(float2*)dshat, (float2*)dAf, (float2*)dAi, 3 * NBLK}
+                                    : LbGrads{part_shat, part_q, part_q + 3 * NBLK, 6 * NBLK};
     hipError_t e;
 #define LB_BWD(LGV)                                                                                                   \
-    e = io == LONGCONV_F16 ? bwd_go<LGV, IoF16>(dy, u, shat, Af, Ai, du, part_shat, part_q, B, H, nsplit, tb, st)     \
-                           : bwd_go<LGV, IoBF16>(dy, u, shat, Af, Ai, du, part_shat, part_q, B, H, nsplit, tb, st);   \
+    e = io == LONGCONV_F16 ? bwd_go<LGV, IoF16>(dy, u, shat, Af, Ai, du, out, B, H, nsplit, tb, st)     \
+                           : bwd_go<LGV, IoBF16>(dy, u, shat, Af, Ai, du, out, B, H, nsplit, tb, st);   \
     break
     switch (N) {
         case 256: LB_BWD(9);
@@ -641,11 +1212,9 @@ hipError_t lbfly_bwd(const void* dy, const void* u, const float* shat, const flo
     }
 #undef LB_BWD
     if (e != hipSuccess) return e;
-    if (!dshat && !dAf && !dAi) return hipSuccess;
-    int lg = 0;
-    while ((1 << lg) < 2 * N) ++lg;
-    hipLaunchKernelGGL(lb_reduce_kernel, dim3((unsigned)H), dim3(256), 0, st, part_shat, part_q, (float2*)dshat,
-                       (float2*)dAf, (float2*)dAi, H, (int)(2 * N), lg - 8, nsplit);
+    if (nsplit == 1 || (!dshat && !dAf && !dAi)) return hipSuccess;
+    hipLaunchKernelGGL(lb_reduce_kernel, dim3((unsigned)((2 * N + 6 * NBLK) / 256), (unsigned)H), dim3(256), 0, st, part_shat,
+                       part_q, (float2*)dshat, (float2*)dAf, (float2*)dAi, H, (int)(2 * N), nsplit);
     return hipGetLastError();
 }
 
