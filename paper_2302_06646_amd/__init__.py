@@ -6,6 +6,9 @@ inverse, truncation, skip term, gradients — runs inside the HIP kernels of
 the stream.  There is no CPU fallback: if the library is missing, importing
 the functions raises.
 
+The usual call (plain contiguous device tensors) is marshalled by ``_native`` (csrc/binding.cpp); what that does not
+know it hands back, and the Python code behind it checks, refuses or serves the call.  Same checks, same results.
+
 Functions mirror the C ABI of ``include/longconv.h``:
     longconv_init, longconv_kspec_bytes, longconv_workspace_bytes,
     longconv_kspec_compute, longconv_fwd, longconv_bwd, longconv_plan_string,
@@ -28,6 +31,7 @@ _CODE = {v: k for k, v in _TORCH_DTYPE.items()}
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblongconv.so")
 _lib = None
+_bound = None
 
 EXPORTS = ("longconv_init", "longconv_kspec_bytes", "longconv_workspace_bytes",
            "longconv_kspec_compute", "longconv_fwd", "longconv_bwd", "longconv_status_string",
@@ -102,12 +106,36 @@ def lib():
     return _lib
 
 
+def _fast():
+    """The native marshalling module, bound to the entry points of lib()."""
+    global _bound
+    if _bound is None:
+        L = lib()
+        try:
+            from . import _native as n
+        except ImportError as e:
+            raise LongconvError("the binding's native part cannot be loaded: build it with "
+                                "`python -m paper_2302_06646_amd.build`") from e
+        n.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS})
+        _bound = n
+    return _bound
+
+
 def _check(status: int, what: str):
     if status != 0:
         L = lib()
         msg = L.longconv_status_string(status).decode()
         hip = L.longconv_last_hip_error().decode()
         raise LongconvError(f"{what}: {msg}" + (f" [{hip}]" if status == 6 and hip else ""))
+
+
+def _done(status, what: str) -> bool:
+    """Whether the native part made the call (raising if the library refused it)."""
+    if status is None:
+        return False
+    if status:
+        _check(status, what)
+    return True
 
 
 def _ptr(t):
@@ -159,6 +187,8 @@ def longconv_set_option(name: str, value: int) -> None:
 
 def longconv_kreg_fwd(k, drop_mask, kbar, p: int, lam: float, stream=None) -> None:
     """kbar <- Squash(Smooth(dropout(k))) (Algorithm 1 lines 1-3); drop_mask may be None."""
+    if _done((_bound or _fast()).kreg_fwd(k, drop_mask, kbar, p, lam, stream), "longconv_kreg_fwd"):
+        return
     H, N = k.shape
     _need(k, "k", torch.float32, (H, N)); _need(drop_mask, "drop_mask", torch.float32, (H, N))
     _need(kbar, "kbar", torch.float32, (H, N))
@@ -168,6 +198,8 @@ def longconv_kreg_fwd(k, drop_mask, kbar, p: int, lam: float, stream=None) -> No
 
 def longconv_kreg_bwd(k, drop_mask, dkbar, dk, p: int, lam: float, stream=None) -> None:
     """dk <- chain rule through dropout, Smooth and Squash applied to dkbar."""
+    if _done((_bound or _fast()).kreg_bwd(k, drop_mask, dkbar, dk, p, lam, stream), "longconv_kreg_bwd"):
+        return
     H, N = k.shape
     _need(k, "k", torch.float32, (H, N)); _need(drop_mask, "drop_mask", torch.float32, (H, N))
     _need(dkbar, "dkbar", torch.float32, (H, N)); _need(dk, "dk", torch.float32, (H, N))
@@ -191,6 +223,8 @@ def new_kspec(H, N, io, device="cuda"):
 
 
 def longconv_kspec_compute(k, D, kspec, io: int, workspace, stream=None) -> None:
+    if _done((_bound or _fast()).kspec_compute(k, D, kspec, io, workspace, stream), "longconv_kspec_compute"):
+        return
     H, N = k.shape
     _need(k, "k", torch.float32, (H, N)); _need(D, "D", torch.float32, (H,))
     _check(lib().longconv_kspec_compute(_ptr(k), _ptr(D), _ptr(kspec), H, N, io, _ptr(workspace),
@@ -200,6 +234,8 @@ def longconv_kspec_compute(k, D, kspec, io: int, workspace, stream=None) -> None
 
 def longconv_fwd(u, k, D, y, workspace, kspec=None, stream=None) -> None:
     """y <- (u * k)[:N] + D u.  All tensors caller-allocated on the device."""
+    if _done((_bound or _fast()).fwd(u, k, D, y, workspace, kspec, stream), "longconv_fwd"):
+        return
     B, H, N = u.shape
     io = dtype_code(u)
     _need(u, "u", _TORCH_DTYPE[io], (B, H, N)); _need(y, "y", _TORCH_DTYPE[io], (B, H, N))
@@ -210,6 +246,8 @@ def longconv_fwd(u, k, D, y, workspace, kspec=None, stream=None) -> None:
 
 def longconv_fwd_gated(u, k, D, g, y, workspace, kspec=None, stream=None) -> None:
     """y <- g * ((u * k)[:N] + D u)."""
+    if _done((_bound or _fast()).fwd_gated(u, k, D, g, y, workspace, kspec, stream), "longconv_fwd_gated"):
+        return
     B, H, N = u.shape
     io = dtype_code(u)
     _need(u, "u", _TORCH_DTYPE[io], (B, H, N)); _need(y, "y", _TORCH_DTYPE[io], (B, H, N))
@@ -222,6 +260,9 @@ def longconv_fwd_gated(u, k, D, g, y, workspace, kspec=None, stream=None) -> Non
 def longconv_bwd_gated(dy, g, u, k, D, du, dk, dD, dg, workspace, kspec=None, stream=None) -> None:
     """du, dk, dD, dg <- gradients of the gated layer (any may be None).  The workspace must hold
     longconv_workspace_bytes(B, H, N, io, 2) bytes."""
+    if _done((_bound or _fast()).bwd_gated(dy, g, u, k, D, du,
+                                           dk, dD, dg, workspace, kspec, stream), "longconv_bwd_gated"):
+        return
     B, H, N = dy.shape
     io = dtype_code(dy)
     for t, name in ((dy, "dy"), (g, "g"), (u, "u"), (du, "du"), (dg, "dg")):
@@ -246,6 +287,8 @@ def new_workspace2d(B, H, N1, N2, io, backward, device="cuda"):
 
 def longconv2d_fwd(u, k, D, y, workspace, stream=None) -> None:
     """y[b,h] <- the 2-D linear convolution of u[b,h] with k[h], truncated to the image, + D[h] u[b,h]."""
+    if _done((_bound or _fast()).fwd2d(u, k, D, y, workspace, stream), "longconv2d_fwd"):
+        return
     B, H, N1, N2 = u.shape
     io = dtype_code(u)
     _need(u, "u", _TORCH_DTYPE[io], (B, H, N1, N2)); _need(y, "y", _TORCH_DTYPE[io], (B, H, N1, N2))
@@ -256,6 +299,8 @@ def longconv2d_fwd(u, k, D, y, workspace, stream=None) -> None:
 
 def longconv2d_bwd(dy, u, k, D, du, dk, dD, workspace, stream=None) -> None:
     """du, dk, dD <- adjoints of longconv2d_fwd (any of the three may be None)."""
+    if _done((_bound or _fast()).bwd2d(dy, u, k, D, du, dk, dD, workspace, stream), "longconv2d_bwd"):
+        return
     B, H, N1, N2 = dy.shape
     io = dtype_code(dy)
     for t, name in ((dy, "dy"), (u, "u"), (du, "du")):
@@ -272,6 +317,8 @@ def longconv_lbfly_workspace_bytes(B: int, H: int, N: int, io: int) -> int:
 
 def longconv_lbfly_spectrum(k, D, shat, stream=None) -> None:
     """shat [H, 2N, 2] <- FFT([k, 0]) + D in natural frequency order (re, im)."""
+    if _done((_bound or _fast()).lbfly_spectrum(k, D, shat, stream), "longconv_lbfly_spectrum"):
+        return
     H, N = k.shape
     _need(k, "k", torch.float32, (H, N)); _need(D, "D", torch.float32, (H,))
     _need(shat, "shat", torch.float32, (H, 2 * N, 2))
@@ -280,6 +327,8 @@ def longconv_lbfly_spectrum(k, D, shat, stream=None) -> None:
 
 def longconv_lbfly_spectrum_bwd(dshat, dk, dD, stream=None) -> None:
     """dk [H, N], dD [H] <- the adjoint of longconv_lbfly_spectrum applied to dshat (either may be None)."""
+    if _done((_bound or _fast()).lbfly_spectrum_bwd(dshat, dk, dD, stream), "longconv_lbfly_spectrum_bwd"):
+        return
     H, L, _ = dshat.shape
     _need(dshat, "dshat", torch.float32, (H, L, 2)); _need(dk, "dk", torch.float32, (H, L // 2))
     _need(dD, "dD", torch.float32, (H,))
@@ -289,6 +338,8 @@ def longconv_lbfly_spectrum_bwd(dshat, dk, dD, stream=None) -> None:
 
 def longconv_lbfly_fwd(u, shat, Af, Ai, y, stream=None) -> None:
     """y <- Re(T_B(shat . T_A([u, 0])))[:N] with the per-head blocks Af, Ai [H, 3, 16, 16, 2]."""
+    if _done((_bound or _fast()).lbfly_fwd(u, shat, Af, Ai, y, stream), "longconv_lbfly_fwd"):
+        return
     B, H, N = u.shape
     io = dtype_code(u)
     _need(u, "u", _TORCH_DTYPE[io], (B, H, N)); _need(y, "y", _TORCH_DTYPE[io], (B, H, N))
@@ -300,6 +351,9 @@ def longconv_lbfly_fwd(u, shat, Af, Ai, y, stream=None) -> None:
 
 def longconv_lbfly_bwd(dy, u, shat, Af, Ai, du, dshat, dAf, dAi, workspace, stream=None) -> None:
     """du, dshat, dAf, dAi <- gradients of longconv_lbfly_fwd (any may be None)."""
+    if _done((_bound or _fast()).lbfly_bwd(dy, u, shat, Af, Ai, du,
+                                           dshat, dAf, dAi, workspace, stream), "longconv_lbfly_bwd"):
+        return
     B, H, N = dy.shape
     io = dtype_code(dy)
     for t, name in ((dy, "dy"), (u, "u"), (du, "du")):
@@ -337,6 +391,8 @@ def longconv_fwd_noalloc(u, k, D, y, kspec=None, stream=None) -> None:
 
 def longconv_bwd(dy, u, k, D, du, dk, dD, workspace, kspec=None, stream=None) -> None:
     """du, dk, dD <- adjoints (any of the three may be None to skip it)."""
+    if _done((_bound or _fast()).bwd(dy, u, k, D, du, dk, dD, workspace, kspec, stream), "longconv_bwd"):
+        return
     B, H, N = dy.shape
     io = dtype_code(dy)
     _need(dy, "dy", _TORCH_DTYPE[io], (B, H, N)); _need(u, "u", _TORCH_DTYPE[io], (B, H, N))

@@ -9,6 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblongconv.so")
+NATIVE = os.path.join(HERE, "_native.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -31,8 +32,23 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed:\n" + out)
 
 
+def build_binding(verbose: bool = True) -> str:
+    """Compile the host-side marshalling of the Python binding against torch's headers (no device code in it)."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+          "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          "-I" + sysconfig.get_paths()["include"], f"-I{t}/include", f"-I{t}/include/torch/csrc/api/include",
+          f"-I{rocm}/include", os.path.join(CSRC, "binding.cpp"), "-o", NATIVE, f"-L{t}/lib", "-lc10", "-lc10_hip",
+          "-ltorch_cpu", "-ltorch_python"], verbose)
+    return NATIVE
+
+
 def build(verbose: bool = True) -> str:
-    """Compile every csrc/*.hip (in parallel) and link liblongconv.so next to this file."""
+    """Compile every csrc/*.hip (in parallel) and link liblongconv.so next to this file; then the binding."""
     from concurrent.futures import ThreadPoolExecutor
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     objdir = os.path.join(HERE, "_build")
@@ -45,6 +61,7 @@ def build(verbose: bool = True) -> str:
                     zip(srcs, objs)))
     check_assembly(objdir, srcs, verbose)
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
+    build_binding(verbose)
     return LIB
 
 
