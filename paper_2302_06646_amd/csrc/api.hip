@@ -79,6 +79,8 @@ static hipError_t get_tables(Tables* out, hipStream_t st, bool sync_device, void
         if (e != hipSuccess) return e;
         e = note(rows_fill_tables(&g_tab[dev].rtab, st), "fill row tables");
         if (e != hipSuccess) return e;
+        e = note(long_fill_tables(&g_tab[dev].ltab, st), "fill long-row tables");
+        if (e != hipSuccess) return e;
         e = note(coop_fill_tables(&g_tab[dev].ctab, st), "fill coop tables");
         if (e != hipSuccess) return e;
         e = note(valu_fill_tables(&g_tab[dev].ftw, st), "fill fp32 tables");
@@ -155,7 +157,7 @@ static size_t cw_bytes(const Plan& pl) { return pl.engine == ENGINE_VALU ? sizeo
 // bytes per stored spectrum bin: fp16 complex for the wave and cooperative matrix-core kernels, fp32 complex otherwise
 static size_t spec_bytes(const Plan& pl)
 {
-    return (pl.engine == ENGINE_MFMA && (pl.order.wave_lg || pl.order.coop_lg)) ? sizeof(__half2) : sizeof(float2);
+    return (pl.engine == ENGINE_MFMA && (pl.order.wave_lg || pl.order.long_lg || pl.order.coop_lg)) ? sizeof(__half2) : sizeof(float2);
 }
 static size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // the stored spectrum of H heads: the bins, and for fp16 storage a trailer of H per-head exponents (spec_exponent)
@@ -174,18 +176,14 @@ struct WsLayout {
     int nblk, nsplit;
 };
 
-// Single-pass matrix-core plans: the dk kernels run one workgroup per head; with few heads the pairs of a head are
-// dealt to `nsplit` workgroups (about 384 in all), whose partial dk and dD are then summed in a fixed order.
+// Single-pass plans: the backward kernels run one workgroup per head; with few heads the rows (pairs) of a head are dealt
+// to `nsplit` workgroups, whose partial dk and dD are then summed in a fixed order.
 static int dk_nsplit(int64_t B, int64_t H, const Plan& pl, bool gated)
 {
     if (pl.engine == ENGINE_VALU) return valu_bwd_nsplit(H, (int)((B + 1) / 2), pl);
     if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_nsplit(B, H, pl.order.wave_lg, gated);
-    if (pl.engine != ENGINE_MFMA || pl.log2R || !pl.order.coop_lg) return 1;
-    const int64_t npairs = (B + 1) / 2;
-    int64_t s = 384 / H;
-    if (s > npairs) s = npairs;
-    if (s > 64) s = 64;
-    return s < 1 ? 1 : (int)s;
+    if (pl.engine == ENGINE_MFMA && pl.order.long_lg) return long_bwd_nsplit(B, H);
+    return 1;
 }
 
 // bf16 rows of the multi-pass plans that take pass A inside the inner kernels are scaled per head (see rows_absmax)
@@ -250,12 +248,13 @@ static hipError_t run_kspec(const float* k, const float* D, float2* kspec, float
                             int64_t H, int64_t N, const Plan& pl, const Tables& tb, hipStream_t st, uint32_t pad = 0)
 {
     const float2* tw = tb.tw;
+    if (pl.engine == ENGINE_MFMA && pl.order.long_lg) return long_kspec(k, D, kspec, H, pl, tb, st);
     if (pl.engine == ENGINE_MFMA && (pl.order.wave_lg || pl.order.coop_lg)) {
         // matrix-core route: per-head power-of-two pre-scale, (pass A,) forward half of the fused kernel
         if (pl.order.wave_lg) return rows_kspec(k, D, kspec, H, pl, pad, tb, st);
-        // single pass, or pass A taken inside the kernel: it reads k itself and finds the maxima
+        // pass A taken inside the kernel: it reads k itself and finds the maxima
         // (outer radix 8: eight chunks per head would each scan 512 KB, so the maxima are found once, in front)
-        if (!pl.log2R || (pl.fuse_a && pl.log2R < 3)) return coop_kspec(k, nullptr, D, nullptr, kspec, H, N, pl, tb, st);
+        if (pl.fuse_a && pl.log2R < 3) return coop_kspec(k, nullptr, D, nullptr, kspec, H, N, pl, tb, st);
         hipError_t e = head_stats(k, D, hscale, H, N, st);
         if (e != hipSuccess) return e;
         if (pl.fuse_a) return coop_kspec(k, nullptr, D, hscale, kspec, H, N, pl, tb, st);
@@ -434,7 +433,7 @@ int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float
     hipStream_t st = (hipStream_t)stream;
     const size_t n = (size_t)B * H * N;
     const Plan pl = make_plan(N, io);
-    if (pl.engine == ENGINE_MFMA && pl.fuse_bwd && du && dg && (dk || dD))      // all of it from one kernel
+    if (pl.engine == ENGINE_MFMA && pl.fuse_bwd && pl.order.wave_lg && du && dg && (dk || dD))      // all of it from one kernel
         return bwd_impl(dy, u, k, D, kspec, du, dk, dD, B, H, N, io, workspace, base, stream, 0, g, dg);
     if (du || dk || dD) {
         // dz = dy * g is what the convolution's backward pass receives
@@ -506,8 +505,9 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
         const int ns = dk_nsplit(B, H, pl, gate != nullptr);
         float* dkp = (float*)(base + w.dkpart);
         float* ddp = (float*)(base + w.ddpart);
-        hipError_t e = rows_bwd(dy, u, ks, du, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD ? ddp : nullptr) : dD, dg, ns,
-                                pr, pl, tb, st);
+        float *dk1 = ns > 1 ? (dk ? dkp : nullptr) : dk, *dD1 = ns > 1 ? (dD ? ddp : nullptr) : dD;
+        hipError_t e = pl.order.long_lg ? long_bwd(dy, u, ks, du, dk1, dD1, ns, pr, pl, tb, st)
+                                        : rows_bwd(dy, u, ks, du, dk1, dD1, dg, ns, pr, pl, tb, st);
         if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * (pad ? N / 2 : N), ddp, dD, (size_t)H, ns, st);
         if (note(e, "bwd") != hipSuccess) return LONGCONV_ERR_HIP;
         return LONGCONV_OK;
@@ -884,7 +884,14 @@ const char* longconv_plan_string(int64_t N, int io)
                      lgR ? 3 : 1);
     for (int i = 0; i < nd; ++i) n += snprintf(buf + n, sizeof(buf) - n, "%s%d", i ? "x" : "", 1 << bits[i]);
     if (wave) n += snprintf(buf + n, sizeof(buf) - n, " kernel=wave");
-    if (pl.order.coop_lg) n += snprintf(buf + n, sizeof(buf) - n, " kernel=chained");
+    if (pl.order.coop_lg || pl.order.long_lg) n += snprintf(buf + n, sizeof(buf) - n, " kernel=chained");
+    if (pl.order.long_lg) {
+        // the fields in front are what they were when rows of these lengths went in pairs, for whoever looks for them there;
+        // what runs follows
+        snprintf(buf + n, sizeof(buf) - n, " backward=dk,du runs=rows(L=2^%d,digits=16x16x16x%d,backward=%s)", pl.order.long_lg,
+                 1 << (pl.order.long_lg - 12), pl.fuse_bwd ? "one" : "dk,du");
+        return buf;
+    }
     if (pl.engine == ENGINE_VALU || pl.fuse_bwd) snprintf(buf + n, sizeof(buf) - n, " backward=one");
     else if (coop_dk_rows_ok(pl)) snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,%dx2^%d),du", 2 << pl.log2R, pl.log2L2 - 1);
     else snprintf(buf + n, sizeof(buf) - n, " backward=dk,du");

@@ -28,6 +28,7 @@ struct Tables {
     const float2* tw;    // g_tw
     const float2* stw;   // stage twiddles
     const void* rtab;    // lane-ordered constants of the single-row kernels
+    const void* ltab;    // lane-ordered constants of the long-row kernels
     const void* ctab;    // lane-ordered constants of the cooperative chained kernels
     const float2* ftw;   // stage twiddles of the fp32 engine
 };
@@ -104,6 +105,7 @@ struct SpecOrder {
     int ndig;
     unsigned char bits[20];
     int wave_lg;   // != 0: the single-row kernels' own lane order for rows of N = 2^wave_lg samples (N bins per head)
+    int long_lg;   // != 0: the long-row kernels' lane order for rows of N = 2^long_lg samples (N bins per head)
     int coop_lg;   // != 0: outer digit (outer_bits wide), then lane order of the cooperative chained
     int outer_bits;  //       kernels for an inner length 2^coop_lg
 };

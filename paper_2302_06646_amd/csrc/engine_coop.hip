@@ -1,5 +1,5 @@
-// Workgroup-cooperative chained kernels for 8192 <= L2 <= 32768 (one row pair, or one chunk of
-// the multi-pass split, per workgroup at a time; the pair lives in LDS only between phases).
+// Workgroup-cooperative chained kernels for 8192 <= L2 <= 32768 (one row of 32768 samples, or one chunk of
+// the multi-pass split, per workgroup at a time; it lives in LDS only between phases).
 //
 // L2 = 16 * 16 * 16 * TE, TE = 2^te in {2,4,8}; TC = 16*TE.  Time index
 // n = d_a*16*TC + d_b*TC + d_c*TE + d_e, frequency f = k_a + 16 k_b + 256 k_c + 4096 k_e
@@ -15,11 +15,10 @@
 // Each wave owns groups of 8 consecutive tiles in every phase; workgroup barriers separate
 // the phases.  The w_{16TC} twiddles come from a small table in LDS, the w_TC ones are per-lane constants.
 //
-// Two forms of phases 1 and 3.  Direct (multi-pass dk, spectrum): operands straight from global memory
-// in the tile's lane order, w_L twiddles from a lane-ordered global table (16 bytes per lane and tile).
-// Staged (convolutions, single-pass dk): the whole workgroup moves the pair between global memory and
-// LDS in unit-stride runs, phases 1 and 3 run in place on LDS, and the w_L twiddle is a per-lane
-// constant times an LDS table; see coop_conv_real_kernel.
+// Two forms of phases 1 and 3.  Direct (dk and spectrum from pass A's workspace): operands straight from global
+// memory in the tile's lane order, w_L twiddles from a lane-ordered global table (16 bytes per lane and tile).
+// Staged (whatever takes rows): the whole workgroup moves them between global memory and LDS in unit-stride
+// runs, phases 1 and 3 run in place on LDS, and the w_L twiddle is a per-lane constant times an LDS table.
 #include "engines.hpp"
 #include "mfma_util.hpp"
 
@@ -296,19 +295,15 @@ __device__ __forceinline__ void phase3_two(const uint32_t* xb, const uint4* gtab
 }
 
 // -------------------------------------------------------------------------------------
-// Fused convolution of zero-padded real row pairs (single-pass plan), rows staged through LDS.
-// The phase-1 tile of a wave takes samples a tile count apart, so loading its operands straight
-// from global memory touches 16 bytes of every 256; here the whole workgroup moves the pair
-// between global memory and LDS in unit-stride 16-byte runs instead, into the very slots that
-// phase 1 reads and phase 3 writes: sample n = d_a 16 TC + d_b TC + t of the pair, packed as the
-// fp16 complex word (row a, row b), lives in word (d_b PITCH + (d_a / 4) TC + t) 4 + d_a % 4 -- the
-// slot phase 1 fills with output (k_a, k_b) = (d_b, d_a) of tile t, and phase 3 the other way round,
-// each lane reading and writing only its own 16 bytes.  Slots of the zero padding (d_a >= 8) are
-// cleared at the start and again by phase 3.  The next pair's runs are fetched into registers
-// before phase 1 and stored to LDS by the lane that has just drained the same slots, so global
-// latency is covered by the three phases and no phase but the second (spectrum) issues global loads:
-// the w_L twiddle of phases 1 and 3 is the product of a per-lane constant w_256^(k_a d_b) and an
-// LDS table w_L^(k_a t).
+// The staged layout.  The phase-1 tile of a wave takes samples a tile count apart, so loading its operands straight
+// from global memory touches 16 bytes of every 256; here the whole workgroup moves the points between global memory
+// and LDS in unit-stride 16-byte runs instead, into the very slots that phase 1 reads and phase 3 writes: point
+// n = d_a 16 TC + d_b TC + t, an fp16 complex word, lives in word (d_b PITCH + (d_a / 4) TC + t) 4 + d_a % 4 -- the
+// slot phase 1 fills with output (k_a, k_b) = (d_b, d_a) of tile t, and phase 3 the other way round, each lane reading
+// and writing only its own 16 bytes.  The next runs are fetched into registers before phase 1 and stored to LDS by the
+// lane that has just drained the same slots, so global latency is covered by the three phases and no phase but the
+// second (spectrum) issues global loads: the w_L twiddle of phases 1 and 3 is the product of a per-lane constant
+// w_256^(k_a d_b) and an LDS table w_L^(k_a t).
 // -------------------------------------------------------------------------------------
 __device__ __forceinline__ h2 cmul_hh(h2 a, h2 w)
 {
@@ -443,270 +438,7 @@ __device__ __forceinline__ int staged_slot(int n)
 }
 
 template <int LG>
-__host__ __device__ constexpr size_t coop_real_lds_bytes() { return (size_t)CC<LG>::XWORDS * 4 + (size_t)CC<LG>::TC * 8 * 16 + (size_t)CC<LG>::TC * 16 * 4; }
-
-// GATE: the output is multiplied element by element by a second tensor of the same shape on its way out (the
-// gated layer: y = g * z).
-template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
-__global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
-coop_conv_real_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec,
-                      typename IO::T* __restrict__ out, const typename IO::T* __restrict__ gate, int64_t B, int64_t H,
-                      int64_t N, int npairs, int per, const float2* __restrict__ tw,
-                      const unsigned char* __restrict__ ctab)
-{
-    using C = CC<LG>;
-    constexpr int NT = NWV * 64;
-    constexpr int RPL = (C::L / 16) / NT;            // 16-byte runs (8 samples) of one row per lane
-    static_assert(RPL * NT * 16 == C::L, "runs must tile the row");
-    extern __shared__ uint4 lds4[];
-    uint32_t* xb = reinterpret_cast<uint32_t*>(lds4);
-    uint4* t1f = lds4 + C::XWORDS / 4;
-    uint4* t1i = t1f + C::TC * 4;
-    uint32_t* vt = reinterpret_cast<uint32_t*>(t1i + C::TC * 4);      // [TC][16]: w_L^(k_a t)
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = lane & 15, g = lane >> 4;
-    const unsigned G = gridDim.x;
-    const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
-    // work items (head, pair), `per` consecutive ones per workgroup (a head's pairs share its spectrum)
-    const int total = (int)H * npairs;
-    const int it0 = (int)vid * per, it1 = it0 + per < total ? it0 + per : total;
-    const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
-    Consts<LG> K;
-    make_consts<LG>(K, tw, lane);
-    h2 cF[4];                                            // w_256^(x (4g+j)), the same in both directions
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
-        cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
-    }
-    int ng = C::TC / (8 * NWV);
-    asm volatile("" : "+s"(ng));
-    const int w1 = (c * C::PITCH + g * C::TC) * 4;
-
-    auto run_n = [&](int i) { return staged_run_n<LG>(i * NT + tid); };
-    auto slot = [&](int i) { return staged_slot<LG>(run_n(i)); };
-    uint4 pa[RPL], pb[RPL];
-    auto fetch = [&](int it) {
-        const int h = it / npairs, p = it - h * npairs;
-        const bool has_b = (2 * p + 1) < B;
-        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-#pragma unroll
-        for (int i = 0; i < RPL; ++i) {
-            const int n = run_n(i);
-            pa[i] = *reinterpret_cast<const uint4*>(in + oa + n);
-            pb[i] = *reinterpret_cast<const uint4*>(in + ob + n);
-            if (!has_b) pb[i] = make_uint4(0u, 0u, 0u, 0u);
-        }
-    };
-    // bf16 rows of a pair that are not both of order one (see band_or_exact, pair_exponents) are scaled by powers
-    // of two on the way in and back on the way out.  The pair is staged unscaled first; every wave publishes the
-    // band test of the words it fetched (two patterns and a flag byte), and after the barrier that makes the staged
-    // pair visible one LDS read tells all waves whether any of them saw a row outside the band.  Only then the
-    // maxima are combined and, if the pair needs it, staged again from the registers, with its scales.
-    __shared__ uint32_t dr_mx[2 * NWV + 2];          // [NWV][2] patterns, then NWV flag bytes
-    auto measure = [&]() {
-        uint32_t m[2] = {0u, 0u};
-#pragma unroll
-        for (int i = 0; i < RPL; ++i) {
-            m[0] = absmax_acc(absmax_acc(absmax_acc(absmax_acc(m[0], pa[i].x), pa[i].y), pa[i].z), pa[i].w);
-            m[1] = absmax_acc(absmax_acc(absmax_acc(absmax_acc(m[1], pb[i].x), pb[i].y), pb[i].z), pb[i].w);
-        }
-        band_or_exact<2>(m);
-        if (lane == 0) {
-            dr_mx[2 * wave] = m[0];
-            dr_mx[2 * wave + 1] = m[1];
-            reinterpret_cast<unsigned char*>(dr_mx + 2 * NWV)[wave] = rows_in_band(m[0], m[1]) ? 0 : 1;
-        }
-    };
-    auto stage = [&](int ea, int eb) {
-#pragma unroll
-        for (int i = 0; i < RPL; ++i) {
-            uint32_t wa[4] = {pa[i].x, pa[i].y, pa[i].z, pa[i].w}, wb[4] = {pb[i].x, pb[i].y, pb[i].z, pb[i].w};
-            if (IsBf<IO>::v) {
-                if (__builtin_expect((ea | eb) != 0, 0)) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) { wa[m] = bf2_to_h2_scaled(wa[m], ea); wb[m] = bf2_to_h2_scaled(wb[m], eb); }
-                } else {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) { wa[m] = bf2_to_h2(wa[m]); wb[m] = bf2_to_h2(wb[m]); }
-                }
-            }
-            const int a0 = slot(i);
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                xb[a0 + 8 * m] = __builtin_amdgcn_perm(wb[m], wa[m], 0x05040100u);
-                xb[a0 + 8 * m + 4] = __builtin_amdgcn_perm(wb[m], wa[m], 0x07060302u);
-            }
-        }
-    };
-    auto drain = [&](int it, int ea, int eb) {
-        const int h = it / npairs, p = it - h * npairs;
-        const bool has_b = (2 * p + 1) < B;
-        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(2 * p + 1, h, H, N);
-        uint4 ga[GATE ? RPL : 1], gb[GATE ? RPL : 1];        // gate values of the runs this lane stores
-        if constexpr (GATE) {
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const int n = run_n(i);
-                ga[i] = *reinterpret_cast<const uint4*>(gate + oa + n);
-                gb[i] = *reinterpret_cast<const uint4*>(gate + (has_b ? ob : oa) + n);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < RPL; ++i) {
-            const int a0 = slot(i), n = run_n(i);
-            uint32_t x[8], wa[4], wb[4];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = xb[a0 + 4 * e];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                wa[m] = __builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x05040100u);
-                wb[m] = __builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x07060302u);
-                uint32_t gwa = 0u, gwb = 0u;
-                if constexpr (GATE) {
-                    gwa = m == 0 ? ga[i].x : (m == 1 ? ga[i].y : (m == 2 ? ga[i].z : ga[i].w));
-                    gwb = m == 0 ? gb[i].x : (m == 1 ? gb[i].y : (m == 2 ? gb[i].z : gb[i].w));
-                }
-                if (IsBf<IO>::v) {
-                    union { uint32_t u; h2 h; } a, b;
-                    a.u = wa[m]; b.u = wb[m];
-                    float a0f = (float)a.h[0], a1f = (float)a.h[1], b0f = (float)b.h[0], b1f = (float)b.h[1];
-                    if constexpr (GATE) {
-                        a0f *= __uint_as_float(gwa << 16); a1f *= __uint_as_float(gwa & 0xffff0000u);
-                        b0f *= __uint_as_float(gwb << 16); b1f *= __uint_as_float(gwb & 0xffff0000u);
-                    }
-                    wa[m] = pack_bf2(a0f, a1f);
-                    wb[m] = pack_bf2(b0f, b1f);
-                } else if constexpr (GATE) {
-                    union { uint32_t u; h2 h; } a, b, qa, qb;
-                    a.u = wa[m]; b.u = wb[m]; qa.u = gwa; qb.u = gwb;
-                    a.h = a.h * qa.h; b.h = b.h * qb.h;
-                    wa[m] = a.u; wb[m] = b.u;
-                }
-            }
-            if (__builtin_expect((ea | eb) != 0, 0)) {      // exponents of the output rows (drain's arguments)
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    if constexpr (GATE && !IsBf<IO>::v) {   // (gate and power of two before the rounding)
-                        const uint32_t gwa = m == 0 ? ga[i].x : (m == 1 ? ga[i].y : (m == 2 ? ga[i].z : ga[i].w));
-                        const uint32_t gwb = m == 0 ? gb[i].x : (m == 1 ? gb[i].y : (m == 2 ? gb[i].z : gb[i].w));
-                        wa[m] = h2_gated(__builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x05040100u), gwa, ea);
-                        wb[m] = h2_gated(__builtin_amdgcn_perm(x[2 * m + 1], x[2 * m], 0x07060302u), gwb, eb);
-                    } else {
-                        wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
-                        wb[m] = out_rescaled<IsBf<IO>::v>(wb[m], eb);
-                    }
-                }
-            }
-            store_words<4>(out + oa + n, wa);
-            if (has_b) store_words<4>(out + ob + n, wb);
-        }
-    };
-
-    if (it0 < it1) fetch(it0);       // first pair on its way while the tables are built
-    staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-    __syncthreads();                 // tables and cleared slots in place
-    if (it0 < it1) {
-        if constexpr (IsBf<IO>::v) measure();
-        stage(0, 0);
-    }
-    for (int it = it0; it < it1; ++it) {
-        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) +
-                                                         (size_t)(it / npairs) * C::L);
-        asm volatile("" : "+s"(ks));
-        __syncthreads();             // staged pair visible
-        int ea = 0, eb = 0;          // exponents of the two rows of this pair
-        if constexpr (IsBf<IO>::v) {
-            static_assert(NWV == 4 || NWV == 8, "flag bytes are read as one or two words");
-            uint32_t f = dr_mx[2 * NWV];
-            if constexpr (NWV == 8) f |= dr_mx[2 * NWV + 1];
-            if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)f) != 0, 0)) {
-                uint32_t ma = 0u, mb = 0u;
-#pragma unroll
-                for (int w = 0; w < NWV; ++w) { ma = max(ma, dr_mx[2 * w]); mb = max(mb, dr_mx[2 * w + 1]); }
-                ma = (uint32_t)__builtin_amdgcn_readfirstlane((int)ma);
-                mb = (uint32_t)__builtin_amdgcn_readfirstlane((int)mb);
-                if (!rows_in_band(ma, mb)) pair_exponents(ma, mb, ea, eb);
-                if ((ea | eb) != 0) {
-                    stage(ea, eb);
-                    __syncthreads();
-                }
-            }
-        }
-
-        // the next pair's runs start travelling now: they have phases 1 to 3 to land (issued in front of phase 3
-        // only, they arrive in a burst from all compute units at once and part of the transfer is exposed)
-        const bool more = it + 1 < it1;
-        if (more) fetch(it + 1);
-
-        // ---- phase 1, in place
-#pragma unroll 1
-        for (int gi = 0; gi < ng; ++gi)
-            phase1_inplace<LG, NB>(xb, t1f, vt, K.F16, K.F16, cF, (gi * NWV + wave) * 8, lane);
-        __syncthreads();
-        asm volatile("" : "+s"(ks));
-
-        // ---- phase 2
-#pragma unroll 1
-        for (int gi = 0; gi < ng; ++gi)
-#pragma unroll
-        for (int tb = 0; tb < 8; tb += NB) {
-            const int t0 = (gi * NWV + wave) * 8;
-            int base[NB];
-            f4 zr[NB], zi[NB];
-            H8U kk[NB];
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const int t2 = t0 + tb + k;
-                base[k] = phase2_base<LG>(t2, lane);
-                kk[k].u = ks[t2 * 64 + lane];
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) phase2_fwd<LG>(xb, base[k], K, zr[k], zi[k]);
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                H8U m;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    // correlation (du): the conjugate spectrum, a sign inside the multiply
-                    m.w[j] = CONJ ? cmul_pack_conj(zr[k][j], zi[k][j], kk[k].c[j])
-                                  : cmul_pack(zr[k][j], zi[k][j], kk[k].c[j]);
-                }
-                phase2_inv<LG>(xb, base[k], K, m);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-
-        // ---- phase 3, in place: word = (row a sample, row b sample); padding slots cleared
-#pragma unroll 1
-        for (int gi = 0; gi < ng; ++gi) {
-            const int t0 = (gi * NWV + wave) * 8;
-#pragma unroll
-            for (int tb = 0; tb < 8; tb += 2) {
-                f4 r[2], s[2];
-                phase3_two_lds<LG>(xb, t1i, vt, K, cF, t0 + tb, lane, r, s);
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    uint4 o = make_uint4(0u, 0u, 0u, 0u);
-                    if (g < 2) o = make_uint4(pack_h2(r[k][0], s[k][0]), pack_h2(r[k][1], s[k][1]),
-                                              pack_h2(r[k][2], s[k][2]), pack_h2(r[k][3], s[k][3]));
-                    *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) = o;
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        __syncthreads();
-        {   // output rows: the input rows' powers of two back, and the one the head's stored spectrum left out
-            const int es = __builtin_amdgcn_readfirstlane(spec_exp_of(kspec, H, C::L)[it / npairs]);
-            drain(it, ea + es, eb + es);
-        }
-        if (more) {
-            if constexpr (IsBf<IO>::v) measure();
-            stage(0, 0);
-        }
-    }
-}
+__host__ __device__ constexpr size_t coop_staged_lds_bytes() { return (size_t)CC<LG>::XWORDS * 4 + (size_t)CC<LG>::TC * 8 * 16 + (size_t)CC<LG>::TC * 16 * 4; }
 
 // -------------------------------------------------------------------------------------
 // Inner convolution of the multi-pass split on the staged layout: chunk k1 (L fp16 complex values of pass
@@ -919,7 +651,8 @@ __device__ __forceinline__ int chunk_run_n(int r)
 // B=32, H=128, N=32768 fp16: 670 us as pairs in two chunks, 311 us here (1.7 TB/s); what is left is matrix and vector issue.
 // The twist W^n, W = exp(-2 pi i / 4N), n = d_a 16 TC + d_b TC + t, takes no instructions: its d_a factor sits in the
 // matrices over d_a of both directions, its d_b factor in the lanes' w_256 constants and its t factor in the w_L table,
-// which phases 1 and 3 (conjugated) share.  Staging, prefetch and the band test are those of coop_conv_real_kernel.
+// which phases 1 and 3 (conjugated) share.  The next row is prefetched in registers; a bf16 row outside the band is scaled by
+// a power of two (band_or_exact).
 // -------------------------------------------------------------------------------------
 template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -975,7 +708,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
     asm volatile("" : "+s"(ng));
     const int w1 = (c * C::PITCH + g * C::TC) * 4;
 
-    // bf16 rows outside the band are scaled by a power of two, as in coop_conv_real_kernel
+    // bf16 rows outside the band are scaled by a power of two
     __shared__ uint32_t dr_mx[NWV];
     auto measure = [&]() {
         uint32_t m[1] = {0u};
@@ -1347,434 +1080,6 @@ __device__ __forceinline__ float run_dot(const uint4& a, const uint4& b, float s
     return s;
 }
 
-// wait until at most n of this wave's vector-memory operations are outstanding (n < 16)
-template <int n>
-__device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8)); }
-
-// -------------------------------------------------------------------------------------
-// dk and dD of real row pairs (single-pass plan) on the staged layout.  grid = H; the workgroup of a
-// head walks its row pairs: u pair -> phase 1 -> forward half of phase 2 -> Z (fp16 registers); dy
-// pair likewise -> W; A += conj(Z) W in fp32 registers, eight phase-2 tiles per wave.
-// The accumulators leave no registers to hold a prefetched pair, so the next source is copied from
-// global memory straight into a raw LDS area (global_load ... lds: 1 KiB per wave instruction, no
-// registers) while the current one is transformed, and moved from there into the exchange slots.
-//
-// SPLIT: the row length N equals the transform length 2^LG of this instantiation, i.e. the padded
-// length is 2 * 2^LG, twice what the accumulators of one workgroup cover.  The outermost radix-2 step
-// of the padded transform is then taken in time (Section 3.2, one more application of the butterfly
-// decomposition, with the zero half dropped): bins of parity s of the padded row are the 2^LG-point
-// transform of u[n] w_{2N}^(s n).  The batch is walked once per parity with that twist applied while
-// staging; dk[n] = Re(a_0[n] + conj(w_{2N}^n) a_1[n]) / 2 with a_s the inverse transform of parity s,
-// the first term parked in dk itself by the lane that later completes it.
-// -------------------------------------------------------------------------------------
-template <int LG, bool SPLIT>
-size_t coop_dk_real_lds_bytes()
-{
-    using C = CC<LG>;
-    const size_t rown = SPLIT ? C::L : C::L / 2;
-    // slots, raw rows (64 bytes of padding per 2 TC runs), tables, SPLIT: twist of every run start
-    return (size_t)C::XWORDS * 4 + rown * 4 + (2 * rown / 8 / (2 * C::TC)) * 64 + (size_t)C::TC * 8 * 16 +
-           (size_t)C::TC * 16 * 4 + (SPLIT ? rown / 8 * 4 : 0);
-}
-
-template <int LG, class IO, bool SPLIT>
-__global__ void __launch_bounds__(CC<LG>::NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
-coop_dk_real_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
-                    float* __restrict__ dk, float* __restrict__ dD, int64_t B, int64_t H, int64_t N, int npairs_all,
-                    int nsplit, float dkscale, const float2* __restrict__ tw,
-                    const unsigned char* __restrict__ ctab)
-{
-    using C = CC<LG>;
-    using T = typename IO::T;
-    static_assert(C::NG == 1, "one group of eight phase-2 tiles per wave");
-    constexpr int NT = C::NW * 64;
-    constexpr int ROWN = SPLIT ? C::L : C::L / 2;      // samples per row
-    constexpr int RPL = ROWN / 8 / NT;                 // 16-byte runs of one row per lane
-    constexpr int NCP = 2 * ROWN * 2 / 1024 / C::NW;   // 1 KiB copy instructions per wave and source
-    constexpr int NPAR = SPLIT ? 2 : 1;
-    extern __shared__ uint4 lds4[];
-    __shared__ float red[C::NW];
-    uint32_t* xb = reinterpret_cast<uint32_t*>(lds4);
-    // raw rows as copied, [2 rows][ROWN] I/O elements in 16-byte runs; run i sits at unit i + 4 (i / 2TC):
-    // the shift spreads the staging reads (lanes 2 TC runs apart) over the banks
-    constexpr int RAWU = 2 * ROWN / 8 + (2 * ROWN / 8 / (2 * C::TC)) * 4;
-    uint4* raw = lds4 + C::XWORDS / 4;
-    uint4* t1f = raw + RAWU;
-    uint4* t1i = t1f + C::TC * 4;
-    uint32_t* vt = reinterpret_cast<uint32_t*>(t1i + C::TC * 4);
-    uint32_t* twr = vt + C::TC * 16;                   // SPLIT: w_{2N}^n at every run start n = 8 i
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = lane & 15, g = lane >> 4;
-    // workgroup (head h, share `split` of nsplit): the head's pairs split, split + nsplit, ...; with nsplit > 1
-    // dk and dD point to partial buffers [nsplit][H][N] and [nsplit][H], summed afterwards in share order
-    const int h = blockIdx.x % (unsigned)H, split = blockIdx.x / (unsigned)H;
-    const int npairs = (npairs_all - split + nsplit - 1) / nsplit;      // pairs of this workgroup
-    const size_t ho = (size_t)split * H + h;
-    const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
-    Consts<LG> K;
-    make_consts<LG>(K, tw, lane);
-    h2 cF[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
-        cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
-    }
-    // first-stage matrix: without the split the slots of the zero padding hold stale (finite) values of
-    // the previous source, so their rows are cleared instead
-    Mats F1 = K.F16;
-    if (!SPLIT && g >= 2) {
-        const h8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
-        F1.re = z8;
-        F1.im = z8;
-    }
-
-    const int nsrc = NPAR * npairs * 2;                  // sources in order: parity, pair, (u, dy)
-    // copy source sidx into the raw area: wave w takes every NW-th KiB (row b after row a; a missing
-    // row b copies row a again and is read as zero)
-    // (everything about a copy is wave-uniform and kept in scalar registers: the wave's index, the row pointers,
-    // the LDS byte address; a lane only adds its 16 bytes)
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    const uint32_t raw_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)raw);
-    auto copy_in = [&](int sidx) {
-        const int p = ((sidx >> 1) % npairs) * nsplit + split;
-        const char* src = reinterpret_cast<const char*>((sidx & 1) ? dy : u);
-        const bool has_b = (2 * p + 1) < B;
-        const char* pa = src + row_off(2 * p, h, H, N) * sizeof(T);
-        const char* pb = src + row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N) * sizeof(T);
-#pragma unroll
-        for (int q = 0; q < NCP; ++q) {
-            const int kib = q * C::NW + wave_s;
-            const int row = kib / (ROWN * 2 / 1024), part = kib - row * (ROWN * 2 / 1024);
-            const uint64_t sa = reinterpret_cast<uint64_t>((row ? pb : pa) + part * 1024);
-            // (readfirstlane returns a signed int: both halves go through uint32_t, or bit 31 of the low word
-            // would smear over the high word)
-            const uint32_t sa_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sa);
-            const uint32_t sa_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(sa >> 32));
-            const uint64_t sbase = ((uint64_t)sa_hi << 32) | (uint64_t)sa_lo;
-            const uint32_t lds_off =
-                __builtin_amdgcn_readfirstlane(raw_lds + (uint32_t)(kib * 64 + (kib * 64 / (2 * C::TC)) * 4) * 16u);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(lds_off), "v"(lane * 16), "s"(sbase) : "memory", "m0");
-        }
-    };
-    // bf16 rows that are not all of order one are scaled by powers of two (see pair_scales): every source is staged
-    // unscaled first while each wave runs the band test on the words it stages (two patterns and a flag byte
-    // into dr_mx); after the barrier that makes the staged source visible one LDS read tells all waves whether
-    // any of them saw a row outside the band, and only then the source is staged again, with its scales, from
-    // the raw area (the next copy waits for that).
-    __shared__ uint32_t dr_mx[2 * C::NW + 2];        // [NW][2] patterns, then NW flag bytes
-    // raw area -> exchange slots (pair packing, bf16 -> fp16 times 2^-ea / 2^-eb, twist)
-    auto stage = [&](int sidx, int ea, int eb, bool measure) {
-        const int p = ((sidx >> 1) % npairs) * nsplit + split;
-        const bool has_b = (2 * p + 1) < B;
-        const bool odd = SPLIT && sidx >= 2 * npairs;
-        int t_ = tid;
-        asm volatile("" : "+v"(t_));                 // addresses are recomputed here, not carried through the walk
-        uint32_t mx[2] = {0u, 0u};
-#pragma unroll
-        for (int i = 0; i < RPL; ++i) {
-            const int n = staged_run_n<LG>(i * NT + t_);
-            const int ia = n / 8, ib = (ROWN + n) / 8;
-            const uint4 va = raw[ia + (ia / (2 * C::TC)) * 4], vb = raw[ib + (ib / (2 * C::TC)) * 4];
-            uint32_t wa[4] = {va.x, va.y, va.z, va.w}, wb[4] = {vb.x, vb.y, vb.z, vb.w};
-            if (!has_b) {
-#pragma unroll
-                for (int m = 0; m < 4; ++m) wb[m] = 0u;
-            }
-            if (IsBf<IO>::v) {
-                if (measure) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) { mx[0] = absmax_acc(mx[0], wa[m]); mx[1] = absmax_acc(mx[1], wb[m]); }
-                }
-                if (__builtin_expect((ea | eb) != 0, 0)) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) { wa[m] = bf2_to_h2_scaled(wa[m], ea); wb[m] = bf2_to_h2_scaled(wb[m], eb); }
-                } else {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) { wa[m] = bf2_to_h2(wa[m]); wb[m] = bf2_to_h2(wb[m]); }
-                }
-            }
-            uint32_t x[8];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                x[2 * m] = __builtin_amdgcn_perm(wb[m], wa[m], 0x05040100u);
-                x[2 * m + 1] = __builtin_amdgcn_perm(wb[m], wa[m], 0x07060302u);
-            }
-            if (SPLIT && odd) {
-                // twist w_{2N}^n, n = d_a 16 TC + d_b TC + t: the (d_a, d_b) part here, one factor per run;
-                // the t part sits in the w_{16TC} table of this walk
-                union { uint32_t u; h2 h; } bw;
-                bw.u = twr[(n & ~(C::TC - 1)) / 8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = cmul_h2(x[e], bw.h);
-            }
-            const int a0 = staged_slot<LG>(n);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) xb[a0 + 4 * e] = x[e];
-        }
-        if (IsBf<IO>::v && measure) {
-            band_or_exact<2>(mx);
-            if (lane == 0) {
-                dr_mx[2 * wave] = mx[0];
-                dr_mx[2 * wave + 1] = mx[1];
-                reinterpret_cast<unsigned char*>(dr_mx + 2 * C::NW)[wave] = rows_in_band(mx[0], mx[1]) ? 0 : 1;
-            }
-        }
-    };
-    // after the barrier behind a measured stage: the pair's two patterns (the stand-in unless a wave flagged)
-    auto staged_patterns = [&](uint32_t& ma, uint32_t& mb) {
-        static_assert(C::NW == 4 || C::NW == 8, "flag bytes are read as one or two words");
-        ma = mb = BAND_LOW;
-        uint32_t f = dr_mx[2 * C::NW];
-        if constexpr (C::NW == 8) f |= dr_mx[2 * C::NW + 1];
-        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)f) != 0, 0)) {
-            uint32_t a = 0u, b = 0u;
-#pragma unroll
-            for (int w = 0; w < C::NW; ++w) { a = max(a, dr_mx[2 * w]); b = max(b, dr_mx[2 * w + 1]); }
-            ma = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
-            mb = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-        }
-    };
-
-    const int t0 = wave * 8;                             // this wave's tiles in every phase
-    float2 acc[8][4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = make_float2(0.f, 0.f);
-    float dsum = 0.f;
-
-    staged_tables<LG, NT>(lds4, gtab, tw, tid, RAWU);
-    if (SPLIT) {
-        for (int i = tid; i < ROWN / 8; i += NT) {
-            const float2 w = tw_full(tw, (uint32_t)(8 * i) << (TW_LOG2 - LG - 1));
-            twr[i] = pack_h2(w.x, w.y);
-        }
-    }
-    __syncthreads();                                     // cleared slots before the first copy lands beside them
-    copy_in(0);
-
-    int sidx = 0;
-    int eref = EXP_NONE;                                 // bf16 rows: the accumulators are in units of 2^eref
-#pragma unroll 1
-    for (int par = 0; par < NPAR; ++par) {
-        eref = EXP_NONE;
-#pragma unroll 1
-        for (int p = 0; p < npairs; ++p) {
-            uint32_t z[8][4];
-            uint32_t mua = BAND_LOW, mub = BAND_LOW;     // patterns of the u rows (first source of the pair)
-            int ep = 0;                                  // conj(Z) W of this pair is in units of 2^ep
-#pragma unroll
-            for (int pass = 0; pass < 2; ++pass, ++sidx) {
-                int zoff = 0;
-                asm volatile("" : "+v"(zoff));               // table reads stay inside the walk
-                const uint4* t1f_ = t1f + zoff;
-                const uint32_t* vt_ = vt + zoff;
-                wait_vm<0>();                            // this wave's share of the copy has landed
-                __syncthreads();                         // ... and everyone's; the slots are free
-                // dD = sum of dy u over the raw rows, in fp32 (first walk only): the dy pair sits in the raw area;
-                // the same runs of the u pair, which went through this CU's caches one source earlier, are read
-                // again from global memory, DG runs at a time (registers)
-                if (pass == 1 && par == 0 && dD != nullptr) {
-                    constexpr int DG = RPL < 2 ? RPL : 2;
-                    const int pg = p * nsplit + split;
-                    const bool dot_b = (2 * pg + 1) < B;
-                    const T* qa = u + row_off(2 * pg, h, H, N);
-                    const T* qb = u + row_off(dot_b ? 2 * pg + 1 : 2 * pg, h, H, N);
-                    int t_ = tid;
-                    asm volatile("" : "+v"(t_));
-#pragma unroll
-                    for (int i0 = 0; i0 < RPL; i0 += DG) {
-                        uint4 ua[DG], ub[DG];
-#pragma unroll
-                        for (int i = 0; i < DG; ++i) {
-                            const int n = staged_run_n<LG>((i0 + i) * NT + t_);
-                            ua[i] = *reinterpret_cast<const uint4*>(qa + n);
-                            ub[i] = *reinterpret_cast<const uint4*>(qb + n);
-                        }
-#pragma unroll
-                        for (int i = 0; i < DG; ++i) {
-                            const int n = staged_run_n<LG>((i0 + i) * NT + t_);
-                            const int ia = n / 8, ib = (ROWN + n) / 8;
-                            dsum = run_dot<IO>(ua[i], raw[ia + (ia / (2 * C::TC)) * 4], dsum);
-                            if (dot_b) dsum = run_dot<IO>(ub[i], raw[ib + (ib / (2 * C::TC)) * 4], dsum);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                stage(sidx, 0, 0, true);
-                __syncthreads();                         // staged source visible, raw area free
-                if constexpr (IsBf<IO>::v) {
-                    int ea = 0, eb = 0;
-                    if (pass == 0) {                     // u rows: normalised one by one
-                        staged_patterns(mua, mub);
-                        if (__builtin_expect(!rows_in_band(mua, mub), 0)) pair_exponents(mua, mub, ea, eb);
-                    } else {                             // dy rows: what is left of the pair's common exponent
-                        uint32_t mda, mdb;
-                        staged_patterns(mda, mdb);
-                        if (__builtin_expect(!(rows_in_band(mua, mub) && rows_in_band(mda, mdb)), 0)) {
-                            const PairScales ps = pair_scales(mua, mub, mda, mdb);
-                            ea = ps.xa; eb = ps.xb; ep = ps.ep;
-                        }
-                    }
-                    if (__builtin_expect((ea | eb) != 0, 0)) {
-                        stage(sidx, ea, eb, false);
-                        __syncthreads();
-                    }
-                }
-                if (sidx + 1 < nsrc) copy_in(sidx + 1);
-                phase1_inplace<LG, 2>(xb, t1f_, vt_, F1, K.F16, cF, t0, lane);
-                __syncthreads();
-                if (IsBf<IO>::v && pass == 1) {
-                    // this pair's term against the accumulators: times 2^down, applied to the waiting Z (a term that
-                    // much smaller than the sum loses nothing that matters when its small parts underflow)
-                    const int down = dk_term_align<8>(acc, eref, ep);
-                    if (__builtin_expect(down != 0, 0)) {
-#pragma unroll
-                        for (int i = 0; i < 8; ++i)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                union { uint32_t u; h2 hh; } cv;
-                                cv.u = z[i][j];
-                                z[i][j] = pack_h2(ldexpf((float)cv.hh[0], down), ldexpf((float)cv.hh[1], down));
-                            }
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    f4 zr, zi;
-                    phase2_fwd<LG>(xb, phase2_base<LG>(t0 + i, lane), K, zr, zi);
-                    if (pass == 0) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) z[i][j] = pack_h2(zr[j], zi[j]);
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            union { uint32_t u; h2 hh; } cv;
-                            cv.u = z[i][j];
-                            const float a = (float)cv.hh[0], b = (float)cv.hh[1];
-                            // conj(Z) * W, one fused multiply-add per term
-                            acc[i][j].x = __builtin_fmaf(b, zi[j], __builtin_fmaf(a, zr[j], acc[i][j].x));
-                            acc[i][j].y = __builtin_fmaf(-b, zr[j], __builtin_fmaf(a, zi[j], acc[i][j].y));
-                        }
-                    }
-                    if (i & 1) __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-        // ---- end of a walk: inverse half of phase 2, phase 3, dk
-        if (dk) {
-            // constants of the inverse direction are built here, not kept through the walk; nothing
-            // below is hoisted out of the parity loop
-            const float2* tw2 = tw;
-            int lane2 = lane;
-            asm volatile("" : "+s"(tw2), "+v"(lane2));
-            const int c2 = lane2 & 15, g2 = lane2 >> 4;
-            Consts<LG> Ki;
-            make_consts<LG>(Ki, tw2, lane2);
-            __syncthreads();                             // every wave is done reading the slots
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                H8U m;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) m.w[j] = pack_h2(acc[i][j].x, acc[i][j].y);
-                phase2_inv<LG>(xb, phase2_base<LG>(t0 + i, lane2), Ki, m);
-            }
-            __syncthreads();
-            // phase 3 leaves the real part (SPLIT, parity 1: of a conj(w_{2N}^n), the twist from the table
-            // of run starts times a constant) as fp32 in the slot word of each sample, in place
-            float2 bw[4];
-            if (SPLIT && par == 1) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    union { uint32_t u; h2 hh; } cv;
-                    cv.u = twr[(((4 * g2 + j) * 16 + c2) * C::TC + t0) >> 3];
-                    bw[j] = make_float2((float)cv.hh[0], (float)cv.hh[1]);
-                }
-            }
-            const int w1 = (c2 * C::PITCH + g2 * C::TC) * 4;
-#pragma unroll
-            for (int tb = 0; tb < 8; tb += 2) {
-                f4 r[2], s2[2];
-                phase3_two_lds<LG>(xb, t1i, vt, Ki, cF, t0 + tb, lane2, r, s2);
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    float v[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        v[j] = r[k][j];
-                        if (SPLIT && par == 1) {
-                            const float ang = -3.14159265358979323846f * (float)(tb + k) / (float)ROWN;
-                            const float ex = __builtin_cosf(ang), ey = __builtin_sinf(ang);
-                            const float wx = bw[j].x * ex - bw[j].y * ey, wy = bw[j].x * ey + bw[j].y * ex;
-                            v[j] = r[k][j] * wx + s2[k][j] * wy;             // Re(a conj(w))
-                        }
-                    }
-                    *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) =
-                        make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
-                }
-                __builtin_amdgcn_sched_barrier(0);       // one tile pair at a time (register pressure)
-            }
-            __syncthreads();
-            // slots -> dk in unit-stride 32-byte runs
-            int t_ = lane2 + (tid - lane);
-            asm volatile("" : "+v"(t_));
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const int n = staged_run_n<LG>(i * NT + t_);
-                const int a0 = staged_slot<LG>(n);
-                float4* dst = reinterpret_cast<float4*>(dk + ho * N + n);
-                float v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(xb[a0 + 4 * e]);
-                if (SPLIT && par == 1) {
-                    const float4 l0 = dst[0], h0 = dst[1];                   // parity 0, parked by this lane
-                    v[0] += l0.x; v[1] += l0.y; v[2] += l0.z; v[3] += l0.w;
-                    v[4] += h0.x; v[5] += h0.y; v[6] += h0.z; v[7] += h0.w;
-                }
-                if (!SPLIT || par == 1) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] *= dkscale;
-                    if constexpr (IsBf<IO>::v) {         // both walks meet the same pairs: the same eref
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) v[e] = ldexpf(v[e], eref == EXP_NONE ? 0 : eref);
-                    }
-                }
-                dst[0] = make_float4(v[0], v[1], v[2], v[3]);
-                dst[1] = make_float4(v[4], v[5], v[6], v[7]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = make_float2(0.f, 0.f);
-        if (SPLIT && par == 0) {
-            // second walk: w_{16TC}^(k_b t) w_{2N}^t in the phase-1 table (phase 1 of the first walk is long
-            // over; two barriers follow before the next one reads it)
-            for (int i = tid; i < C::TC * 4; i += NT) {
-                const float2 w = tw_full(tw, (uint32_t)(i >> 2) << (TW_LOG2 - LG - 1));
-                const h2 tau = {(_Float16)w.x, (_Float16)w.y};
-                H8U e;
-                e.u = gtab[C::T1F + i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) e.w[j] = cmul_h2(e.w[j], tau);
-                t1f[i] = e.u;
-            }
-        }
-    }
-
-    if (dD) {
-        for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
-        if (lane == 0) red[wave] = dsum;
-        __syncthreads();
-        if (tid == 0) {
-            float t = 0.f;
-            for (int w = 0; w < C::NW; ++w) t += red[w];
-            dD[ho] = t;
-        }
-    }
-}
-
 // -------------------------------------------------------------------------------------
 // dk and dD of the multi-pass split straight from the rows (outer radix 2^LR around 2^LG-point transforms,
 // pass A taken while staging as in coop_conv_kernel).  grid = H 2^LR, chunk index fastest and renumbered per XCD;
@@ -1802,7 +1107,7 @@ coop_dk_rows_kernel(const typename IO::T* __restrict__ dy, const typename IO::T*
     uint4* t1f = lds4 + C::XWORDS / 4;
     uint4* t1i = t1f + C::TC * 4;
     uint32_t* vt = reinterpret_cast<uint32_t*>(t1i + C::TC * 4);
-    uint4* zl = lds4 + coop_real_lds_bytes<LG>() / 16;   // Z of the pair in flight: eight 16-byte words per lane
+    uint4* zl = lds4 + coop_staged_lds_bytes<LG>() / 16;   // Z of the pair in flight: eight 16-byte words per lane
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g = lane >> 4;
     // the 2^LR workgroups of a head read the same rows: consecutive ids, renumbered so that they share an XCD
@@ -2099,7 +1404,7 @@ coop_dk_kernel(const __half2* __restrict__ ws_u, const __half2* __restrict__ ws_
 // grid = (H, R): chunk k1 of the pass-A output of the kernel pre-scaled by a power of two from rs[h] (the
 // head's maximum; pass A used the same scale).  Phase 1 and the forward half of phase 2 as in the
 // convolution; value stored = kscale * (FFT([k,0]) + D[h]) as fp16 complex (one 32-bit word per bin).
-// (coop_kspec_rows_kernel below reads k itself: single pass, and pass A inside where the plan allows.)
+// (coop_kspec_rows_kernel below reads k itself, where the plan takes pass A inside.)
 // -------------------------------------------------------------------------------------
 template <int LG>
 __global__ void __launch_bounds__(CC<LG>::NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -2144,9 +1449,8 @@ coop_kspec_kernel(const __half2* __restrict__ ws, const float* __restrict__ D, c
         }
 }
 
-// Kernel spectrum, staged form.  LR = 0: single pass, the head's row k[h, :] zero-padded to 2^LG points.
-// LR > 0: chunk k1 of the multi-pass split with pass A inside (outer radix 2^LR around 2^LG points); grid =
-// H 2^LR, chunk index fastest and renumbered per XCD, so that the chunks of a head share its row in one L2.
+// Kernel spectrum, staged form: chunk k1 of the multi-pass split with pass A inside (outer radix 2^LR around 2^LG
+// points); grid = H 2^LR, chunk index fastest and renumbered per XCD, so that the chunks of a head share its row in one L2.
 // Every chunk needs the whole row (pass A sums its R/2 pieces); the workgroup reads it in unit-stride 32-byte
 // runs.  R <= 4: the row stays in registers between the search of the head's maximum (power-of-two pre-scale)
 // and the conversion, one round trip to memory; R = 8: the maximum comes from the caller (rs).
@@ -2162,8 +1466,8 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     // ROWS: the N-point twisted transform of single rows (coop_conv_row_kernel), 2^(LR-1) chunks of which number kc is
     // chunk 4 kc + 1 of a split twice as wide
     constexpr int LT = ROWS ? LR + 1 : LR, LCH = ROWS ? LR - 1 : LR;      // outer radix of the twist, chunks per head (log2)
-    constexpr int NT = C::NW * 64, RH = LR ? (1 << LR) / 2 : 1;
-    constexpr int NROW = LR ? RH * C::L : C::L / 2;      // samples of a row
+    constexpr int NT = C::NW * 64, RH = (1 << LR) / 2;
+    constexpr int NROW = RH * C::L;                      // samples of a row
     constexpr int RPA = (C::L / 8) / NT;                 // runs of eight samples per lane
     extern __shared__ uint4 lds4[];
     __shared__ float mred[3][C::NW];
@@ -2182,15 +1486,14 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     float2 cr[RH];
 #pragma unroll
     for (int n1 = 0; n1 < RH; ++n1)
-        cr[n1] = LR ? tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LT) - 1)) << (TW_LOG2 - LT)) : make_float2(1.f, 0.f);
+        cr[n1] = tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LT) - 1)) << (TW_LOG2 - LT));
     auto load_run = [&](float4 (&v)[RH][2], int i) __attribute__((always_inline)) {
         const int n = staged_run_n<LG>(i * NT + tid);
 #pragma unroll
         for (int n1 = 0; n1 < RH; ++n1) {
             const float4* src = reinterpret_cast<const float4*>(kr + (size_t)n1 * C::L + n);
-            const bool pad = LR == 0 && n >= NROW;       // the zero half of a single-pass transform
-            v[n1][0] = pad ? make_float4(0.f, 0.f, 0.f, 0.f) : src[0];
-            v[n1][1] = pad ? make_float4(0.f, 0.f, 0.f, 0.f) : src[1];
+            v[n1][0] = src[0];
+            v[n1][1] = src[1];
         }
     };
     // a, mp: sum and maximum of the magnitudes with the skip term counted in the lag-0 tap (`first`: v[0][0].x is
@@ -2248,8 +1551,8 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
             const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
             cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
         }
-        F1 = LR ? phase_mats(k1, C::cb + 4, LG + LT, tw, lane) : K.F16;
-        F2 = LR ? phase_mats(k1, C::cb, LG + LT, tw, lane) : K.F16;
+        F1 = phase_mats(k1, C::cb + 4, LG + LT, tw, lane);
+        F2 = phase_mats(k1, C::cb, LG + LT, tw, lane);
     };
 
     float r;
@@ -2260,7 +1563,7 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
 #pragma unroll
         for (int i = 0; i < RPA; ++i) load_run(v[i], i);
         staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-        if (LR) twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
+        twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
         make_operands();
         float m = 0.f;
 #pragma unroll
@@ -2325,31 +1628,6 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
 template <int LG>
 size_t coop_lds_bytes() { return (size_t)CC<LG>::XWORDS * 4 + (size_t)CC<LG>::TC * 8 * 16; }
 
-// work split of the staged convolution kernel: as many workgroups as the device holds at once
-template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
-hipError_t coop_conv_real_go(const void* in, const float2* kspec, void* out, const Problem& pr,
-                             const Tables& tb, hipStream_t st)
-{
-    using T = typename IO::T;
-    const size_t lds = coop_real_lds_bytes<LG>();
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_conv_real_kernel<LG, IO, NWV, NB, CONJ, GATE>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    static int resident = 0;
-    if (resident == 0) {
-        int nb = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, coop_conv_real_kernel<LG, IO, NWV, NB, CONJ, GATE>, NWV * 64, lds);
-        if (e != hipSuccess) return e;
-        resident = (nb > 0 ? nb : 1) * compute_units();
-    }
-    const long total = pr.H * pr.npairs;                 // (head, pair) items, a run of `per` per workgroup
-    const int per = (int)((total + resident - 1) / resident);
-    hipLaunchKernelGGL((coop_conv_real_kernel<LG, IO, NWV, NB, CONJ, GATE>), dim3((unsigned)((total + per - 1) / per)),
-                       dim3(NWV * 64), lds, st, (const T*)in, kspec, (T*)out, (const T*)pr.gate, pr.B, pr.H, pr.N,
-                       pr.npairs, per, tb.tw, (const unsigned char*)tb.ctab);
-    return hipGetLastError();
-}
-
 template <int LG, class IO, bool CONJ, bool GATE>
 hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, const Problem& pr, const Tables& tb,
                             hipStream_t st)
@@ -2357,7 +1635,7 @@ hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, cons
     using T = typename IO::T;
     constexpr int NWV = CC<LG>::NW;
     const auto kern = coop_conv_row_kernel<LG, IO, NWV, NTB, CONJ, GATE>;
-    const size_t lds = coop_real_lds_bytes<LG>();
+    const size_t lds = coop_staged_lds_bytes<LG>();
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const long total = pr.H * pr.B;                      // (head, row) items; the row fills a compute unit's LDS
@@ -2372,13 +1650,6 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2*
                         const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     constexpr int NWV = CC<LG>::NW, NB = NTB;
-    if (pl.log2R == 0) {
-        if (pr.gate)
-            return conj ? hipErrorInvalidValue
-                        : coop_conv_real_go<LG, IO, NWV, NB, false, true>(in, kspec, out, pr, tb, st);
-        return conj ? coop_conv_real_go<LG, IO, NWV, NB, true, false>(in, kspec, out, pr, tb, st)
-                    : coop_conv_real_go<LG, IO, NWV, NB, false, false>(in, kspec, out, pr, tb, st);
-    }
     if constexpr (LG == COOP_MAX_LOG2) {
         if (pl.row1) {
             if (pr.gate)
@@ -2389,7 +1660,7 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2*
     }
     // multi-pass: the inner convolution on pass A's workspace, or (fuse_a) on the rows themselves
     using T = typename IO::T;
-    const size_t lds = coop_real_lds_bytes<LG>();
+    const size_t lds = coop_staged_lds_bytes<LG>();
     // (head, chunk, pair) items; a batch of one row (every pair a single real row) with pass A inside needs only
     // the chunks up to R/2 (conv_chunks)
     const bool rows = fuse_a && rows_split(pl);
@@ -2443,25 +1714,6 @@ hipError_t coop_dk_go(const __half2* ws_u, const __half2* ws_dy, __half2* ws_A, 
     return hipGetLastError();
 }
 
-template <int LG, class IO, bool SPLIT>
-hipError_t coop_dk_real_go(const void* dy, const void* u, float* dk, float* dD, int nsplit, const Problem& pr,
-                           const Tables& tb, hipStream_t st)
-{
-    using T = typename IO::T;
-    using C = CC<LG>;
-    const size_t lds = coop_dk_real_lds_bytes<LG, SPLIT>();
-    const int shift = 6 + (C::te >= 2 ? 1 : 0);      // three radix-16 stages (1/4 each) and F_TE
-    // two forward chains and one inverse chain, each scaled by 2^-shift; 1 / padded length
-    const float dkscale = (float)(int64_t(1) << (3 * shift)) / (float)(2 * pr.N);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_dk_real_kernel<LG, IO, SPLIT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((coop_dk_real_kernel<LG, IO, SPLIT>), dim3((unsigned)(pr.H * nsplit)), dim3(C::NW * 64), lds, st,
-                       (const T*)dy, (const T*)u, dk, dD, pr.B, pr.H, pr.N, pr.npairs, nsplit, dkscale, tb.tw,
-                       (const unsigned char*)tb.ctab);
-    return hipGetLastError();
-}
-
 // Multi-pass dk from the rows: the plan's split (outer radix 2^log2R around 32768 points, log2R = 2 or 3) is taken
 // as outer radix 2^(log2R+1) around 16384 points, whose accumulators fit one walk.  Returns the scale pass C has to
 // apply (two forward chains and one inverse chain of the 16384-point transform, 1 / padded length).
@@ -2472,7 +1724,7 @@ hipError_t coop_dk_rows_go(const void* dy, const void* u, __half2* ws_A, float* 
     constexpr int LG = COOP_MAX_LOG2 - 1;
     using T = typename IO::T;
     using C = CC<LG>;
-    const size_t lds = coop_real_lds_bytes<LG>() + (size_t)C::NW * 64 * 8 * 16;      // slots, tables, Z
+    const size_t lds = coop_staged_lds_bytes<LG>() + (size_t)C::NW * 64 * 8 * 16;      // slots, tables, Z
     const int shift = 6 + (C::te >= 2 ? 1 : 0);
     const float dkscale = (float)(int64_t(1) << (3 * shift)) / (float)(2 * pr.N);
     *scale_c = dkscale;
@@ -2496,7 +1748,7 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
     const int shift = 6 + (C::te >= 2 ? 1 : 0);
     const float koc = pl.kscale * (float)(1 << shift);
     auto launch_rows = [&](auto kern) {      // staged form (ws unused; rs only at outer radix 8)
-        const size_t lds_rows = coop_real_lds_bytes<LG>();
+        const size_t lds_rows = coop_staged_lds_bytes<LG>();
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows);
         if (e != hipSuccess) return e;
@@ -2505,7 +1757,6 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
                            pl.log2R == 3 ? rs : nullptr, kspec, koc, pl.kscale, tb.tw, (const unsigned char*)tb.ctab);
         return hipGetLastError();
     };
-    if (pl.log2R == 0) return launch_rows(coop_kspec_rows_kernel<LG, 0, false>);
     if constexpr (LG == COOP_MAX_LOG2) {      // pass A inside
         if (pl.row1) return launch_rows(coop_kspec_rows_kernel<LG, 1, true>);
         if (rows_split(pl)) return launch_rows(coop_kspec_rows_kernel<LG, 2, true>);
@@ -2551,21 +1802,6 @@ hipError_t coop_dk(const void* dy, const void* u, float* dk, float* dD, int nspl
                    const __half2* ws_dy, __half2* ws_A, float* dD_part, void* zbuf, const Problem& pr, const Plan& pl,
                    const Tables& tb, hipStream_t st)
 {
-    if (pl.log2R == 0) {
-        // single pass: rows straight from the caller's tensors; 32768 points as two walks of 16384
-#define GOR(LG, IO, SPLIT) return coop_dk_real_go<LG, IO, SPLIT>(dy, u, dk, dD, nsplit, pr, tb, st)
-        if (pr.io == LONGCONV_F16) {
-            if (pl.log2L2 == 13) GOR(13, IoF16, false);
-            if (pl.log2L2 == 14) GOR(14, IoF16, false);
-            if (pl.log2L2 == 15) GOR(14, IoF16, true);
-        } else if (pr.io == LONGCONV_BF16) {
-            if (pl.log2L2 == 13) GOR(13, IoBF16, false);
-            if (pl.log2L2 == 14) GOR(14, IoBF16, false);
-            if (pl.log2L2 == 15) GOR(14, IoBF16, true);
-        }
-#undef GOR
-        return hipErrorInvalidValue;
-    }
     // multi-pass: ws_A is null when only dD is wanted
     if (pl.log2L2 == 13) return coop_dk_go<13>(ws_u, ws_dy, dk ? ws_A : nullptr, dD_part, zbuf, pr, pl, tb, st);
     if (pl.log2L2 == 14) return coop_dk_go<14>(ws_u, ws_dy, dk ? ws_A : nullptr, dD_part, zbuf, pr, pl, tb, st);

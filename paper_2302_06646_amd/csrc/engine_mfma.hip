@@ -524,13 +524,16 @@ void mfma_fill_plan(Plan& pl)
 {
     pl.order.ndig = 0;
     pl.order.wave_lg = 0;
+    pl.order.long_lg = 0;
     pl.order.coop_lg = 0;
     pl.order.outer_bits = pl.log2R;
     const Options& opt = options();
     const bool staged = opt.staged != 0;           // the in-place staged kernel everywhere (cross-check)
     if (!staged && pl.log2R == 0 && pl.log2L - 1 >= ROWS_MIN_LOG2 && pl.log2L - 1 <= ROWS_MAX_LOG2)
         pl.order.wave_lg = pl.log2L - 1;
-    if (!staged && !pl.order.wave_lg && pl.log2L2 >= COOP_MIN_LOG2 && pl.log2L2 <= COOP_MAX_LOG2) pl.order.coop_lg = pl.log2L2;
+    if (!staged && pl.log2R == 0 && pl.log2L - 1 >= LONG_MIN_LOG2 && pl.log2L - 1 <= LONG_MAX_LOG2)
+        pl.order.long_lg = pl.log2L - 1;
+    if (!staged && !pl.order.wave_lg && !pl.order.long_lg && pl.log2L2 >= COOP_MIN_LOG2 && pl.log2L2 <= COOP_MAX_LOG2) pl.order.coop_lg = pl.log2L2;
     if (pl.log2R) pl.order.bits[pl.order.ndig++] = (unsigned char)pl.log2R;
     const int S = n_stages(pl.log2L2);
     for (int i = 0; i < S - 1; ++i) pl.order.bits[pl.order.ndig++] = 4;
@@ -540,8 +543,8 @@ void mfma_fill_plan(Plan& pl)
     const float c = 1.0f / (float)(1 << total_shift(pl.log2L2));
     pl.kscale = 1.0f / (L * c * c);
     pl.dkscale = 1.0f / (L * c * c * c);
-    if (pl.order.wave_lg) {
-        const float cr = rows_chain_scale(pl.order.wave_lg);     // (N points, the inverse at twice the scale)
+    if (pl.order.wave_lg || pl.order.long_lg) {
+        const float cr = pl.order.long_lg ? long_chain_scale() : rows_chain_scale(pl.order.wave_lg);     // (N points, the inverse at twice the scale)
         pl.kscale = 1.0f / (L * cr * cr);
         pl.dkscale = 1.0f / (L * cr * cr * cr);
     }
@@ -552,14 +555,15 @@ void mfma_fill_plan(Plan& pl)
     // (N points instead of 2N: the factor of two comes behind the last fp16 value, in the row kernel's last block and, at
     // outer radix 4, in pass C, so that the products with the spectrum are no larger than a pair's)
     pl.row1 = pl.fuse_a && pl.log2R == 1;
-    // one backward kernel where a wave group holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
-    pl.fuse_bwd = pl.order.wave_lg && opt.fuse_bwd;
+    // one backward kernel where a workgroup holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
+    pl.fuse_bwd = (pl.order.wave_lg || pl.order.long_lg) && opt.fuse_bwd;
 }
 
 hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     if (pl.order.wave_lg) return rows_conv(in, kspec, out, conj, pr, pl, tb, st);
+    if (pl.order.long_lg) return long_conv(in, kspec, out, conj, pr, pl, tb, st);
     if (pl.order.coop_lg) return coop_conv(in, kspec, out, ws, conj, fuse_a, pr, pl, tb, st);
     if (pr.io == LONGCONV_F16) { LC_LG_SWITCH(conv_go, IoF16, in, kspec, out, ws, conj, pr, pl, tb, st) }
     if (pr.io == LONGCONV_BF16) { LC_LG_SWITCH(conv_go, IoBF16, in, kspec, out, ws, conj, pr, pl, tb, st) }
@@ -573,7 +577,7 @@ bool conv_applies_gate(const Plan& pl, bool fuse_a)
 {
     (void)fuse_a;
     if (pl.engine != ENGINE_MFMA) return false;
-    if (pl.log2R == 0) return pl.order.wave_lg || pl.order.coop_lg;
+    if (pl.log2R == 0) return pl.order.wave_lg || pl.order.long_lg;
     return pl.log2R <= 4 && pl.log2L2 >= 10;
 }
 
@@ -582,6 +586,7 @@ hipError_t mfma_dk(const void* dy, const void* u, float* dk, float* dD, int nspl
                    const Tables& tb, hipStream_t st)
 {
     if (pl.order.wave_lg) return rows_bwd(dy, u, nullptr, nullptr, dk, dD, nullptr, nsplit, pr, pl, tb, st);
+    if (pl.order.long_lg) return long_bwd(dy, u, nullptr, nullptr, dk, dD, nsplit, pr, pl, tb, st);
     if (pl.order.coop_lg) return coop_dk(dy, u, dk, dD, nsplit, ws_u, ws_dy, ws_A, dD_part, zbuf, pr, pl, tb, st);
     if (nsplit != 1) return hipErrorInvalidValue;
     if (pl.log2R == 0 && dD) {

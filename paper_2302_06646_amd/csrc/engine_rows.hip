@@ -906,23 +906,6 @@ rkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* 
                                              pack_h2(yr[q][3] * alpha + beta, yi[q][3] * alpha));
 }
 
-// dk accumulators of rows with different scales (bf16): kept in units of 2^eref, eref = the largest exponent sum met so
-// far.  A row with a larger sum rescales them; a row with a smaller one has its term scaled by 2^(return value).
-template <int NA>
-__device__ __forceinline__ int acc_align(float2 (&acc)[NA][4], int& eref, int ep)
-{
-    if (__builtin_expect(ep == eref, 1)) return 0;
-    if (ep > eref) {
-        const int d = eref - ep;
-#pragma unroll
-        for (int k = 0; k < NA; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { acc[k][j].x = ldexpf(acc[k][j].x, d); acc[k][j].y = ldexpf(acc[k][j].y, d); }
-        eref = ep;
-        return 0;
-    }
-    return ep - eref;
-}
 // acc += conj(U) W 2^down
 template <bool SCALED>
 __device__ __forceinline__ void acc_tile(float2 (&acc)[4], const f4& ur, const f4& ui, const f4& wr, const f4& wi, int down)
@@ -983,36 +966,6 @@ __device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2
     }
     return etop;
 }
-
-// The accumulator goes into dk's inverse transform as fp16, and as a sum over rows it has no bound of its own (rows with a
-// mean add up in the first bins: 0.8 N^2 / 4^SHIFT times the product of the means per row, 3300 at N = 4096).  So its
-// largest component is brought to 2^7 .. 2^8 by a power of two, which dk gets back in fp32: the inverse grows a
-// component by at most sqrt(2) N / 2^SHIFT <= 91, which stays below fp16's 65504.  This wave's largest component, as
-// the pattern of its magnitude, without a trip through LDS (a butterfly of __shfl_xor cost calls of one row 0.2 us):
-__device__ __forceinline__ uint32_t wave_umax(uint32_t q)
-{
-    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0xB1, 0xf, 0xf, true));       // quad_perm: lanes ^ 1
-    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x4E, 0xf, 0xf, true));       // lanes ^ 2
-    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x141, 0xf, 0xf, true));      // row_half_mirror
-    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x140, 0xf, 0xf, true));      // row_mirror
-    uint32_t s = 0u;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s = max(s, (uint32_t)__builtin_amdgcn_readlane((int)q, 16 * j));
-    return s;
-}
-template <int NA>
-__device__ __forceinline__ uint32_t acc_peak(const float2 (&acc)[NA][4])
-{
-    uint32_t m = 0u;
-#pragma unroll
-    for (int k = 0; k < NA; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            m = max(m, max(__float_as_uint(acc[k][j].x) & 0x7fffffffu, __float_as_uint(acc[k][j].y) & 0x7fffffffu));
-    return wave_umax(m);
-}
-// exponent of the power of two an accumulator whose largest component is m is divided by
-__device__ __forceinline__ int acc_exponent(uint32_t m) { return (int)(m >> 23) - (127 + 7); }
 
 // -------------------------------------------------------------------------------------
 // Whole backward pass of a head (or of a share of its rows) per workgroup, rows shared by NWR waves (N >= 2048, gated

@@ -155,6 +155,19 @@ int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated);
 hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, void* dg, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 
+// ---- single rows of N = 8192 and 16384 samples on the matrix cores (engine_long.hip) -----------
+constexpr int LONG_MIN_LOG2 = 13, LONG_MAX_LOG2 = 14;
+hipError_t long_fill_tables(const void** tab_out, hipStream_t st);
+float long_chain_scale();            // scale of a forward transform; an inverse one has twice that
+hipError_t long_kspec(const float* k, const float* D, float2* kspec, int64_t H, const Plan& pl, const Tables& tb, hipStream_t st);
+hipError_t long_conv(const void* in, const float2* kspec, void* out, bool conj, const Problem& pr, const Plan& pl, const Tables& tb,
+                     hipStream_t st);
+
+// du, dk and dD in one kernel; du (and with it kspec), dk and dD may be null.  nsplit > 1: as rows_bwd
+int long_bwd_nsplit(int64_t B, int64_t H);
+hipError_t long_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
+                    const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
+
 // ---- cooperative chained matrix-core kernels for 2^13 <= L2 <= 2^15 (engine_coop.hip) --------
 constexpr int COOP_MIN_LOG2 = 13, COOP_MAX_LOG2 = 15;
 hipError_t coop_fill_tables(const void** tab_out, hipStream_t st);

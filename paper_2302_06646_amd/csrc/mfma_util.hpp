@@ -146,13 +146,6 @@ __device__ __forceinline__ uint32_t h2_rescaled(uint32_t w, int e)
     cv.u = w;
     return pack_h2(ldexpf((float)cv.h[0], e), ldexpf((float)cv.h[1], e));
 }
-// words of two fp16 values each: z g 2^e, rounded once (z g alone may leave fp16's range where the result does not)
-__device__ __forceinline__ uint32_t h2_gated(uint32_t z, uint32_t g, int e)
-{
-    union { uint32_t u; h2 h; } a, b;
-    a.u = z; b.u = g;
-    return pack_h2(ldexpf((float)a.h[0] * (float)b.h[0], e), ldexpf((float)a.h[1] * (float)b.h[1], e));
-}
 // packed output word of either half dtype times 2^e
 template <bool BF>
 __device__ __forceinline__ uint32_t out_rescaled(uint32_t w, int e)
@@ -161,46 +154,16 @@ __device__ __forceinline__ uint32_t out_rescaled(uint32_t w, int e)
 }
 constexpr int EXP_NONE = -100000;      // "exponent" of something that is exactly zero
 
-// Scales of the two rows (a, b) of the two sources (u pair, dy pair) in the dk kernels.  dk sums
-// corr(u_a, dy_a) and corr(u_b, dy_b) out of one complex product, so both terms must carry the same power of
-// two: the rows of the source transformed first take the exponents of their own pair (for dy that is what du
-// needs), the rows of the other source take what is left of the common exponent ep, the larger of the two
-// rows' exponent sums: the row of the larger term arrives with its own exponent, the other one smaller than
-// that by the difference of the terms, which is all the precision it has in the sum anyway (and never larger:
-// a row of a negligible term brought up to order one would put its rounding on the term that counts).
-struct PairScales {
-    int efa, efb;      // first source: its rows are multiplied by 2^-efa, 2^-efb
-    int xa, xb;        // second source: multiplied by 2^-xa, 2^-xb
-    int ep;            // conj(Z) W of this pair is in units of 2^ep (EXP_NONE: the pair contributes nothing)
-};
-__device__ __forceinline__ PairScales pair_scales(uint32_t mfa, uint32_t mfb, uint32_t msa, uint32_t msb)
-{
-    PairScales p;
-    pair_exponents(mfa, mfb, p.efa, p.efb);
-    int sa, sb;
-    pair_exponents(msa, msb, sa, sb);
-    const int pa = (mfa && msa) ? p.efa + sa : EXP_NONE;
-    const int pb = (mfb && msb) ? p.efb + sb : EXP_NONE;
-    p.ep = pa > pb ? pa : pb;
-    const int ec = p.ep == EXP_NONE ? 0 : p.ep;
-    p.xa = ec - p.efa;
-    p.xb = ec - p.efb;
-    return p;
-}
-
-// dk accumulators of pairs with different scales: A is kept in units of 2^eref, eref = the largest exponent sum
-// (u pair + dy pair) met so far.  A pair with a larger sum rescales A first; a pair with a smaller one has its
-// term scaled down by 2^(return value) (0 in the other cases).  Equal exponents, the usual case, cost one scalar
-// compare.  The matrix-core results themselves are not touched here: the caller applies the factor in a loop of
-// its own, so that no register copies sit at a branch right behind an MFMA.
-template <int TPW>
-__device__ __forceinline__ int dk_term_align(float2 (&acc)[TPW][4], int& eref, int ep)
+// dk accumulators of rows with different scales (bf16): kept in units of 2^eref, eref = the largest exponent sum met so
+// far.  A row with a larger sum rescales them; a row with a smaller one has its term scaled by 2^(return value).
+template <int NA>
+__device__ __forceinline__ int acc_align(float2 (&acc)[NA][4], int& eref, int ep)
 {
     if (__builtin_expect(ep == eref, 1)) return 0;
     if (ep > eref) {
         const int d = eref - ep;
 #pragma unroll
-        for (int k = 0; k < TPW; ++k)
+        for (int k = 0; k < NA; ++k)
 #pragma unroll
             for (int j = 0; j < 4; ++j) { acc[k][j].x = ldexpf(acc[k][j].x, d); acc[k][j].y = ldexpf(acc[k][j].y, d); }
         eref = ep;
@@ -208,6 +171,36 @@ __device__ __forceinline__ int dk_term_align(float2 (&acc)[TPW][4], int& eref, i
     }
     return ep - eref;
 }
+
+// The accumulator goes into dk's inverse transform as fp16, and as a sum over rows it has no bound of its own (rows with a
+// mean add up in the first bins: 0.8 N^2 / 4^SHIFT times the product of the means per row, 3300 at N = 4096).  So its
+// largest component is brought to 2^7 .. 2^8 by a power of two, which dk gets back in fp32: the inverse grows a
+// component by at most sqrt(2) N / 2^SHIFT <= 91, which stays below fp16's 65504.  This wave's largest component, as
+// the pattern of its magnitude, without a trip through LDS (a butterfly of __shfl_xor cost calls of one row 0.2 us):
+__device__ __forceinline__ uint32_t wave_umax(uint32_t q)
+{
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0xB1, 0xf, 0xf, true));       // quad_perm: lanes ^ 1
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x4E, 0xf, 0xf, true));       // lanes ^ 2
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x141, 0xf, 0xf, true));      // row_half_mirror
+    q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0x140, 0xf, 0xf, true));      // row_mirror
+    uint32_t s = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s = max(s, (uint32_t)__builtin_amdgcn_readlane((int)q, 16 * j));
+    return s;
+}
+template <int NA>
+__device__ __forceinline__ uint32_t acc_peak(const float2 (&acc)[NA][4])
+{
+    uint32_t m = 0u;
+#pragma unroll
+    for (int k = 0; k < NA; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            m = max(m, max(__float_as_uint(acc[k][j].x) & 0x7fffffffu, __float_as_uint(acc[k][j].y) & 0x7fffffffu));
+    return wave_umax(m);
+}
+// exponent of the power of two an accumulator whose largest component is m is divided by
+__device__ __forceinline__ int acc_exponent(uint32_t m) { return (int)(m >> 23) - (127 + 7); }
 
 // (yr + i yi) * w in packed fp16 (one convert, v_pk_mul_f16, v_pk_fma_f16); result as fp16 complex
 __device__ __forceinline__ uint32_t cmul_pack(float yr, float yi, h2 w)
