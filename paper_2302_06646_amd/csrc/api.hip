@@ -1,10 +1,10 @@
 // C-ABI layer of liblongconv: argument validation, planning, workspace carving, dispatch.
-// Every step of the path runs in the kernels of engine_rows.hip (rows of 256..4096 samples), engine_coop.hip
-// (8192..32768 points, and the inner transforms of longer ones), multipass.hip (outer passes), engine_valu.hip
-// (fp32 I/O), engine_mfma.hip (first-generation in-place kernel, kept as a cross-check behind a switch and
-// for 256-point inner transforms), kreg.hip (kernel regularisers), gate.hip (the gate's streaming pass) and
-// conv2d.hip (row padding of the 2-D convolution), lbfly.hip (learned Butterfly extension), bsize.hip (block-size study); nothing here
-// computes on the host.
+// Every step of the path runs in the kernels of engine_rows.hip (rows of 256..4096 samples), engine_long.hip (8192 and 16384),
+// engine_coop.hip (32768, and the inner transforms of the forced multi-pass split), engine_chunk.hip (65536 and 131072),
+// multipass.hip (outer passes), engine_valu.hip (fp32 I/O), engine_mfma.hip (first-generation in-place kernel, kept as a
+// cross-check behind a switch and for 256-point inner transforms), kreg.hip (kernel regularisers), gate.hip (the gate's streaming
+// pass) and conv2d.hip (row padding of the 2-D convolution), lbfly.hip (learned Butterfly extension), bsize.hip (block-size
+// study); nothing here computes on the host.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -80,6 +80,8 @@ static hipError_t get_tables(Tables* out, hipStream_t st, bool sync_device, void
         e = note(rows_fill_tables(&g_tab[dev].rtab, st), "fill row tables");
         if (e != hipSuccess) return e;
         e = note(long_fill_tables(&g_tab[dev].ltab, st), "fill long-row tables");
+        if (e != hipSuccess) return e;
+        e = note(chunk_fill_tables(&g_tab[dev].chtab, st), "fill chunk tables");
         if (e != hipSuccess) return e;
         e = note(coop_fill_tables(&g_tab[dev].ctab, st), "fill coop tables");
         if (e != hipSuccess) return e;
@@ -172,7 +174,7 @@ static const int* spec_exp_ptr(const float2* kspec, int64_t H, size_t L, const P
 }
 
 struct WsLayout {
-    size_t kspec, kscratch, hscale, ws1, ws2, wsA, dpart, zbuf, dkpart, ddpart, rowmx, total;
+    size_t kspec, kscratch, hscale, ws1, ws2, wsA, dpart, chunk, zbuf, dkpart, ddpart, rowmx, total;
     int nblk, nsplit;
 };
 
@@ -204,15 +206,17 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     const bool kscr = mc && pl.log2R && !pl.fuse_a;
     w.kscratch = off; if (kscr) off += up256((size_t)H * L * sizeof(float2));
     w.hscale = off; off += up256(head_stats_floats(H, N) * sizeof(float));
-    // rows that go from memory to memory (row1) have no chunks; pass A's outputs for dk, and what goes with them, belong to
-    // plans that run it as a kernel of its own (not the fp32 engine, and not where dk comes straight from the rows)
-    const bool outer_a = pl.engine == ENGINE_MFMA && !coop_dk_rows_ok(pl);
+    // rows that go from memory to memory (row1) have no chunks to keep; pass A's outputs for dk, and what goes with them,
+    // belong to plans that run it as a kernel of its own (not the fp32 engine, and not where dk comes straight from the rows)
+    const bool chunks = pl.engine == ENGINE_MFMA && chunk_dk_plan(pl);
+    const bool outer_a = pl.engine == ENGINE_MFMA && !chunks;
     w.ws1 = off; if (pl.log2R && !pl.row1) off += up256((size_t)H * npairs * L * cw_bytes(pl));
     w.ws2 = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npairs * L * cw_bytes(pl));
     w.wsA = off; if (pl.log2R && backward) off += up256((size_t)H * L * cw_bytes(pl));
     w.nblk = (int)(npairs * ((size_t(1) << pl.log2L2) / 256));
     const size_t npart = (size_t)w.nblk > (size_t(1) << pl.log2R) ? (size_t)w.nblk : (size_t(1) << pl.log2R);
     w.dpart = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npart * sizeof(float));
+    w.chunk = off; if (backward && chunks) off += up256((size_t)chunk_bwd_shares(B, H, pl.log2R) * (H << pl.log2R) * 2 * sizeof(float));
     w.nsplit = backward ? dk_nsplit(B, H, pl, true) : 1;      // (room for the gated pass, which never has fewer shares)
     w.zbuf = off;
     if (backward && pl.order.coop_lg && outer_a) off += up256((size_t)H * L * sizeof(__half2));
@@ -252,12 +256,13 @@ static hipError_t run_kspec(const float* k, const float* D, float2* kspec, float
     if (pl.engine == ENGINE_MFMA && (pl.order.wave_lg || pl.order.coop_lg)) {
         // matrix-core route: per-head power-of-two pre-scale, (pass A,) forward half of the fused kernel
         if (pl.order.wave_lg) return rows_kspec(k, D, kspec, H, pl, pad, tb, st);
-        // pass A taken inside the kernel: it reads k itself and finds the maxima
-        // (outer radix 8: eight chunks per head would each scan 512 KB, so the maxima are found once, in front)
-        if (pl.fuse_a && pl.log2R < 3) return coop_kspec(k, nullptr, D, nullptr, kspec, H, N, pl, tb, st);
+        // the kernel reads k itself and finds the maxima
+        // (N = 131072: eight chunks per head would each scan 512 KB, so the maxima are found once, in front)
+        if (pl.row1) return coop_kspec(k, nullptr, D, nullptr, kspec, H, N, pl, tb, st);
+        if (chunk_plan(pl) && pl.log2R == 2) return chunk_kspec(k, D, nullptr, kspec, H, pl, tb, st);
         hipError_t e = head_stats(k, D, hscale, H, N, st);
         if (e != hipSuccess) return e;
-        if (pl.fuse_a) return coop_kspec(k, nullptr, D, hscale, kspec, H, N, pl, tb, st);
+        if (chunk_plan(pl)) return chunk_kspec(k, D, hscale, kspec, H, pl, tb, st);
         if (pl.log2R) {
             Problem pk{1, H, N, LONGCONV_F32, 1};
             e = outer_fwd(k, nullptr, kscratch, nullptr, nullptr, pk, pl.log2R, pl.log2L2, 1.0f, tw, st, hscale);
@@ -279,22 +284,24 @@ static hipError_t run_conv(const void* in, const float2* kspec, void* out, void*
     hipError_t e;
     const float2* tw = tb.tw;
     const bool f16ws = pl.engine == ENGINE_MFMA;
-    const bool fuse_a = pl.engine == ENGINE_MFMA && pl.fuse_a && !ws1_ready;   // pass A inside the inner kernel
-    if (pl.engine == ENGINE_MFMA && pl.log2R && !ws1_ready && !fuse_a) {
+    if (pl.engine == ENGINE_MFMA && chunk_plan(pl)) {
+        Problem pc = pr;
+        pc.spec_exp = spec_exp_ptr(kspec, pr.H, size_t(1) << pl.log2L, pl);
+        return chunk_conv(in, kspec, out, ws1, conj, pc, pl, tb, st);
+    }
+    if (pl.engine == ENGINE_MFMA && pl.log2R && !ws1_ready && !pl.row1) {
         e = outer_fwd(in, nullptr, ws1, nullptr, nullptr, pr, pl.log2R, pl.log2L2, 1.0f, tw, st);
         if (e != hipSuccess) return e;
     }
     if (pl.engine == ENGINE_VALU)
         e = valu_conv(in, kspec, out, (float2*)ws1, conj, pr, pl, tb, st);
     else
-        e = mfma_conv(in, kspec, out, (__half2*)ws1, conj, fuse_a, pr, pl, tb, st);
+        e = mfma_conv(in, kspec, out, (__half2*)ws1, conj, pr, pl, tb, st);
     if (e != hipSuccess) return e;
     if (pl.log2R && !pl.row1) {
         Problem pc = pr;     // pass C gives the output the power of two that the stored spectrum left out
         pc.spec_exp = spec_exp_ptr(kspec, pr.H, size_t(1) << pl.log2L, pl);
-        if (fuse_a && rows_split(pl)) return outer_inv_rows(ws1, out, pc, pl.log2L2, tw, st);
-        e = outer_inv(ws1, out, pc, pl.log2R, pl.log2L2, 1.0f, f16ws, tw, st,
-                      fuse_a && coop_conv_chunks(pr, pl, fuse_a) < (1 << pl.log2R));
+        e = outer_inv(ws1, out, pc, pl.log2R, pl.log2L2, 1.0f, f16ws, tw, st);
     }
     return e;
 }
@@ -385,7 +392,7 @@ static int fwd_impl(const void* u, const float* k, const float* D, const void* k
     }
     // output gate (y = g * z): inside the convolution's store where the plan's kernel has that form, otherwise a
     // pass of its own over y
-    const bool fused_gate = gate && conv_applies_gate(pl, pl.fuse_a);
+    const bool fused_gate = gate && conv_applies_gate(pl);
     if (fused_gate) pr.gate = gate;
     if (note(run_conv(u, ks, y, base + w.ws1, false, pr, pl, tb, st, false), "fwd") != hipSuccess)
         return LONGCONV_ERR_HIP;
@@ -536,48 +543,46 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
         if (e == hipSuccess && multi && du) e = outer_inv(base + w.ws1, du, pr, pl.log2R, pl.log2L2, 1.0f, false, tw, st);
         return note(e, "bwd") == hipSuccess ? LONGCONV_OK : LONGCONV_ERR_HIP;
     }
-    if (want_dkD) {
+    if (want_dkD && pl.engine == ENGINE_MFMA && chunk_dk_plan(pl)) {
+        // one walk over the rows for all that is asked for (switch fuse_bwd = 0, and N = 32768: du by itself, below)
+        void* du1 = chunk_plan(pl) && options().fuse_bwd ? du : nullptr;
+        const float2* ks = (const float2*)kspec;
+        if (du1 && !ks) {
+            if (note(run_kspec(k, D, (float2*)(base + w.kspec), nullptr, (float*)(base + w.hscale), H, N, pl, tb, st), "kspec") !=
+                hipSuccess)
+                return LONGCONV_ERR_HIP;
+            ks = (const float2*)(base + w.kspec);
+        }
+        Problem prc = pr;
+        prc.max_a = mx_u;
+        prc.max_b = mx_dy;
+        prc.spec_exp = du1 ? spec_exp_ptr(ks, H, size_t(1) << pl.log2L, pl) : nullptr;
+        int* exps = (int*)(base + w.chunk);
+        float* dD_part = (float*)exps + (size_t)chunk_bwd_shares(B, H, pl.log2R) * (H << pl.log2R);
+        if (note(chunk_bwd(dy, u, ks, du1, base + w.ws1, dk, dD, base + w.wsA, exps, dD_part, prc, pl, tb, st), "bwd") != hipSuccess)
+            return LONGCONV_ERR_HIP;
+        if (du1) return LONGCONV_OK;
+    } else if (want_dkD) {
         hipError_t e = hipSuccess;
         float* dpart = (float*)(base + w.dpart);
-        int cR = pl.log2R, cL2 = pl.log2L2;        // the split and scale pass C of dk works with
-        float cscale = pl.dkscale;
-        if (coop_dk_rows_ok(pl)) {
-            // straight from the rows, as outer radix 8 or 16 around 16384-point transforms (no pass A kernel);
-            // dD is the rows' dot product, taken by the workgroup of each head's first chunk
-            cR += 1; cL2 -= 1;
-            Problem prs = pr;
-            prs.max_a = mx_u;
-            prs.max_b = mx_dy;
-            e = coop_dk_rows(dy, u, dk ? (__half2*)(base + w.wsA) : nullptr, dD, prs, pl, tb, st, &cscale);
-        } else {
-            if (pl.log2R) {
-                // pass A for u and dy in one launch; its blocks also leave dD's partial dot products
-                e = outer_fwd(dy, u, base + w.ws1, base + w.ws2, dD ? dpart : nullptr, pr, pl.log2R, pl.log2L2, 1.0f, tw,
-                              st);
-                dy_ready = true;
-                if (e == hipSuccess && dD) e = reduce_dD(dpart, dD, H, w.nblk, st);
-            }
-            if (e == hipSuccess && (dk || !pl.log2R)) {
-                const int ns = dk_nsplit(B, H, pl, false);
-                float* dkp = (float*)(base + w.dkpart);
-                float* ddp = (float*)(base + w.ddpart);
-                float* dD1 = pl.log2R ? nullptr : dD;
-                e = mfma_dk(dy, u, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD1 ? ddp : nullptr) : dD1, ns,
-                            (const __half2*)(base + w.ws2), (const __half2*)(base + w.ws1), (__half2*)(base + w.wsA),
-                            nullptr, base + w.zbuf, pr, pl, tb, st);
-                if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * (pad ? N / 2 : N), ddp, dD1, (size_t)H, ns, st);
-            }
+        if (pl.log2R) {
+            // pass A for u and dy in one launch; its blocks also leave dD's partial dot products
+            e = outer_fwd(dy, u, base + w.ws1, base + w.ws2, dD ? dpart : nullptr, pr, pl.log2R, pl.log2L2, 1.0f, tw, st);
+            dy_ready = true;
+            if (e == hipSuccess && dD) e = reduce_dD(dpart, dD, H, w.nblk, st);
         }
-        if (e == hipSuccess && pl.log2R && dk) {
-            Problem pk{1, H, N, LONGCONV_F32, 1};   // heads as single rows, real part only
-            if (pl.engine == ENGINE_MFMA && coop_dk_rows_ok(pl)) {
-                pk.max_a = mx_u;                     // the powers of two the rows of each head went in with
-                pk.max_b = mx_dy;
-            }
-            // (dk from the rows of a batch of one: only the chunks up to R/2 were computed)
-            e = outer_inv(base + w.wsA, dk, pk, cR, cL2, cscale, f16ws, tw, st,
-                          pl.engine == ENGINE_MFMA && coop_dk_rows_ok(pl) && B == 1);
+        if (e == hipSuccess && (dk || !pl.log2R)) {
+            const int ns = dk_nsplit(B, H, pl, false);
+            float* dkp = (float*)(base + w.dkpart);
+            float* ddp = (float*)(base + w.ddpart);
+            float* dD1 = pl.log2R ? nullptr : dD;
+            e = mfma_dk(dy, u, ns > 1 ? (dk ? dkp : nullptr) : dk, ns > 1 ? (dD1 ? ddp : nullptr) : dD1, ns,
+                        (const __half2*)(base + w.ws2), (const __half2*)(base + w.ws1), (__half2*)(base + w.wsA), nullptr,
+                        base + w.zbuf, pr, pl, tb, st);
+            if (e == hipSuccess && ns > 1) e = sum_partials(dkp, dk, (size_t)H * (pad ? N / 2 : N), ddp, dD1, (size_t)H, ns, st);
         }
+        if (e == hipSuccess && pl.log2R && dk)           // heads as single rows, real part only
+            e = outer_inv(base + w.wsA, dk, Problem{1, H, N, LONGCONV_F32, 1}, pl.log2R, pl.log2L2, pl.dkscale, f16ws, tw, st);
         if (note(e, "bwd dk/dD") != hipSuccess) return LONGCONV_ERR_HIP;
     }
     if (du) {
@@ -869,7 +874,8 @@ const char* longconv_plan_string(int64_t N, int io)
     const Plan pl = make_plan(N, io);
     // what the convolutions transform: N twisted points of each row, or 2N zero-padded points of a row pair
     const bool wave = pl.engine == ENGINE_MFMA && pl.order.wave_lg;
-    const bool rows = wave || pl.row1 || rows_split(pl);
+    const bool chunks = pl.engine == ENGINE_MFMA && chunk_plan(pl);
+    const bool rows = wave || pl.row1 || (chunks && pl.log2R == 2);
     const int lgL = pl.log2L - rows, lgL2 = wave ? lgL : pl.log2L2, lgR = lgL - lgL2;
     int bits[20], nd = 0;
     if (lgR) bits[nd++] = lgR;
@@ -893,7 +899,10 @@ const char* longconv_plan_string(int64_t N, int io)
         return buf;
     }
     if (pl.engine == ENGINE_VALU || pl.fuse_bwd) snprintf(buf + n, sizeof(buf) - n, " backward=one");
-    else if (coop_dk_rows_ok(pl)) snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,%dx2^%d),du", 2 << pl.log2R, pl.log2L2 - 1);
+    else if (chunks)                                      // (the fields in front as above)
+        snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,%dx2^14),du runs=rows(L=2^%d,digits=%dx16x16x16x4,backward=%s)",
+                 2 << pl.log2R, pl.log2L - 1, 1 << pl.log2R, options().fuse_bwd ? "one" : "dk,du");
+    else if (pl.row1) snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,4x2^14),du runs=rows(dk=2x2^14)");
     else snprintf(buf + n, sizeof(buf) - n, " backward=dk,du");
     return buf;
 }

@@ -29,6 +29,7 @@ struct Tables {
     const float2* stw;   // stage twiddles
     const void* rtab;    // lane-ordered constants of the single-row kernels
     const void* ltab;    // lane-ordered constants of the long-row kernels
+    const void* chtab;   // and of the chunks of longer rows
     const void* ctab;    // lane-ordered constants of the cooperative chained kernels
     const float2* ftw;   // stage twiddles of the fp32 engine
 };
@@ -179,9 +180,9 @@ struct Plan {
     SpecOrder order; // storage order of the spectrum: outer digit first, then inner digits
     float kscale;    // factor folded into the stored spectrum (includes 1/L)
     float dkscale;   // factor applied to the inverse transform of the dk accumulator
-    int fuse_a;      // multi-pass convolutions take pass A inside the inner kernel (outer radix 2, 4 or 8, matrix cores)
-    int row1;        // fuse_a at outer radix 2: the convolutions run one transform of N twisted points per row instead
-    int fuse_bwd;    // du, dk and dD of one call come from one kernel (single pass up to 4096 points, matrix cores)
+    int fuse_a;      // rows of 32768 and more samples go without a pass A kernel: row1, or in chunks (engine_chunk.hip)
+    int row1;        // fuse_a at N = 32768: spectrum and convolutions run one transform of N twisted points per row
+    int fuse_bwd;    // du, dk and dD of one call come from one kernel (single pass, matrix cores)
 };
 
 Plan make_plan(int64_t N, int io);
@@ -194,7 +195,7 @@ struct Options {
     int engine;       // 0: by dtype (default), 1: fp32 vector-ALU engine, 2: fp16 matrix-core engine (half I/O only)
     int inner_log2;   // 0: default; otherwise cap the on-chip transform length at 2^n (forces the multi-pass split)
     int staged;       // 1: the in-place staged matrix-core kernel instead of the wave / cooperative kernels
-    int fuse_pass_a;  // 1 (default): pass A of outer radix 4 and 8 inside the inner kernels
+    int fuse_pass_a;  // 1 (default): rows of 32768 and more samples without a pass A kernel (Plan::fuse_a)
     int fuse_bwd;     // 1 (default): du, dk, dD of one call from one kernel where a plan has one
 };
 const Options& options();

@@ -446,12 +446,6 @@ __host__ __device__ constexpr size_t coop_staged_lds_bytes() { return (size_t)CC
 // ones (same spectrum slice) per workgroup; a chunk moves between the workspace and the slots in
 // unit-stride 16-byte runs of four values.  Lane bits of a run: two for the position in a 64-byte
 // segment, then d_a % 4 and d_b % 4 (the 4-byte LDS accesses of a wave then hit 64 different banks).
-//
-// FUSEA > 0 (= log2 of the outer radix R, 4 or 8): pass A is taken here instead of in a kernel of its own.
-// With the padded half dropped its sum has R/2 terms, s[n2] = sum_{n1 < R/2} w_R^(n1 k1) z[n1 L + n2]
-// (z = row a + i row b), formed while staging straight from the caller's rows; its twist w_{RL}^(k1 n2),
-// n2 = d_a 16 TC + d_b TC + t, costs nothing: the d_a and d_b factors scale the columns of the two
-// phase-1 matrices and the t factor goes into the w_{16TC} table, all three rebuilt per item.
 // -------------------------------------------------------------------------------------
 // (1/4) F16[m][sig] w_{2^lt}^(k1 sig 2^wl) as MFMA operand: the contraction index sig carries the phase
 __device__ __forceinline__ Mats phase_mats(int k1, int wl, int lt, const float2* __restrict__ tw, int lane)
@@ -485,147 +479,6 @@ __device__ __forceinline__ void twisted_t1f(uint4* t1f, const uint4* gtab, int k
         for (int j = 0; j < 4; ++j) e.w[j] = cmul_h2(e.w[j], tau);
         t1f[i] = e.u;
     }
-}
-
-// Pass A of chunk k1 while staging: rows a, b of one pair (N = 2^(LR-1) L samples each) ->
-// s[n2] = sum_{n1 < R/2} w_R^(n1 k1) z[n1 L + n2], z = a + i b, R = 2^LR, into the exchange slots.  The twist
-// is not applied here (it sits in the phase-1 operands).  One packed fp16 complex multiply-add per term.
-// HASB = false: the pair has no row b (odd batch); twice as many runs are then in flight per round trip.
-// RH: terms of the sum (rows of RH L samples; half the outer radix for zero-padded ones).
-template <int LG, class IO, int LR, int NT, bool HASB, int RH = (1 << LR) / 2>
-__device__ __forceinline__ void stage_rows_pass_a_impl(uint32_t* xb, const typename IO::T* ra, const typename IO::T* rb,
-                                                       int k1, const float2* __restrict__ tw, int tid, int ex)
-{
-    // ex != 0 (bf16 rows of a head whose largest sample lies outside the band 2^-2 .. 2^4): every sample times 2^-ex
-    using C = CC<LG>;
-    h2 cr[RH], crs[RH];                              // w_R^(n1 k1) and i times it
-#pragma unroll
-    for (int n1 = 1; n1 < RH; ++n1) {
-        const float2 w = tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LR) - 1)) << (TW_LOG2 - LR));
-        cr[n1] = h2{(_Float16)w.x, (_Float16)w.y};
-        crs[n1] = h2{(_Float16)(-w.y), (_Float16)w.x};
-    }
-    constexpr int RPA = (C::L / 8) / NT;             // runs of eight samples per lane
-    constexpr int RB = RH > 4 ? 1 : (RH <= 2 ? 2 : 1) * (HASB ? 1 : 2);      // runs in flight
-    constexpr int NV = HASB ? 2 : 1;
-    static_assert(RPA % RB == 0, "runs in flight divide the runs of a lane");
-    if constexpr (RH > 4) {
-        // outer radix 16: the eight pieces of a run come in two halves of four (registers), the sums of the first
-        // half wait as packed fp16
-        constexpr int PH = 4;
-#pragma unroll
-        for (int i0 = 0; i0 < RPA; i0 += RB) {
-            uint32_t sum[RB][8];
-#pragma unroll
-            for (int half = 0; half < RH / PH; ++half) {
-                uint4 v[RB][NV][PH];
-#pragma unroll
-                for (int i = 0; i < RB; ++i) {
-                    const int n = staged_run_n<LG>((i0 + i) * NT + tid);
-#pragma unroll
-                    for (int q = 0; q < PH; ++q) {
-                        v[i][0][q] = *reinterpret_cast<const uint4*>(ra + (size_t)(half * PH + q) * C::L + n);
-                        if (HASB) v[i][NV - 1][q] = *reinterpret_cast<const uint4*>(rb + (size_t)(half * PH + q) * C::L + n);
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < RB; ++i) {
-                    uint32_t wa[PH][4], wb[PH][4];
-#pragma unroll
-                    for (int q = 0; q < PH; ++q) {
-                        const uint4 a4 = v[i][0][q], b4 = HASB ? v[i][NV - 1][q] : make_uint4(0u, 0u, 0u, 0u);
-                        wa[q][0] = a4.x; wa[q][1] = a4.y; wa[q][2] = a4.z; wa[q][3] = a4.w;
-                        wb[q][0] = b4.x; wb[q][1] = b4.y; wb[q][2] = b4.z; wb[q][3] = b4.w;
-                        if (IsBf<IO>::v) {
-#pragma unroll
-                            for (int m = 0; m < 4; ++m) {
-                                wa[q][m] = ex ? bf2_to_h2_scaled(wa[q][m], ex) : bf2_to_h2(wa[q][m]);
-                                if (HASB) wb[q][m] = ex ? bf2_to_h2_scaled(wb[q][m], ex) : bf2_to_h2(wb[q][m]);
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-                        union { uint32_t u; h2 h; } acc, z;
-                        acc.u = half ? sum[i][e] : __builtin_amdgcn_perm(wb[0][e >> 1], wa[0][e >> 1], sel);
-#pragma unroll
-                        for (int q = half ? 0 : 1; q < PH; ++q) {
-                            const int n1 = half * PH + q;
-                            z.u = __builtin_amdgcn_perm(wb[q][e >> 1], wa[q][e >> 1], sel);
-                            const h2 x = {z.h[0], z.h[0]}, y = {z.h[1], z.h[1]};
-                            acc.h = __builtin_elementwise_fma(y, crs[n1], __builtin_elementwise_fma(x, cr[n1], acc.h));
-                        }
-                        sum[i][e] = acc.u;
-                    }
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const int a0 = staged_slot<LG>(staged_run_n<LG>((i0 + i) * NT + tid));
-#pragma unroll
-                for (int e = 0; e < 8; ++e) xb[a0 + 4 * e] = sum[i][e];
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i0 = 0; i0 < RPA; i0 += RB) {
-        uint4 v[RB][NV][RH];
-#pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            const int n = staged_run_n<LG>((i0 + i) * NT + tid);
-#pragma unroll
-            for (int n1 = 0; n1 < RH; ++n1) {
-                v[i][0][n1] = *reinterpret_cast<const uint4*>(ra + (size_t)n1 * C::L + n);
-                if (HASB) v[i][NV - 1][n1] = *reinterpret_cast<const uint4*>(rb + (size_t)n1 * C::L + n);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            uint32_t wa[RH][4], wb[RH][4];
-#pragma unroll
-            for (int n1 = 0; n1 < RH; ++n1) {
-                const uint4 a4 = v[i][0][n1], b4 = HASB ? v[i][NV - 1][n1] : make_uint4(0u, 0u, 0u, 0u);
-                wa[n1][0] = a4.x; wa[n1][1] = a4.y; wa[n1][2] = a4.z; wa[n1][3] = a4.w;
-                wb[n1][0] = b4.x; wb[n1][1] = b4.y; wb[n1][2] = b4.z; wb[n1][3] = b4.w;
-                if (IsBf<IO>::v) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        wa[n1][m] = ex ? bf2_to_h2_scaled(wa[n1][m], ex) : bf2_to_h2(wa[n1][m]);
-                        if (HASB) wb[n1][m] = ex ? bf2_to_h2_scaled(wb[n1][m], ex) : bf2_to_h2(wb[n1][m]);
-                    }
-                }
-            }
-            const int a0 = staged_slot<LG>(staged_run_n<LG>((i0 + i) * NT + tid));
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-                union { uint32_t u; h2 h; } acc, z;
-                acc.u = __builtin_amdgcn_perm(wb[0][e >> 1], wa[0][e >> 1], sel);
-#pragma unroll
-                for (int n1 = 1; n1 < RH; ++n1) {
-                    z.u = __builtin_amdgcn_perm(wb[n1][e >> 1], wa[n1][e >> 1], sel);
-                    const h2 x = {z.h[0], z.h[0]}, y = {z.h[1], z.h[1]};
-                    acc.h = __builtin_elementwise_fma(y, crs[n1], __builtin_elementwise_fma(x, cr[n1], acc.h));
-                }
-                xb[a0 + 4 * e] = acc.u;
-            }
-        }
-    }
-}
-
-template <int LG, class IO, int LR, int NT>
-__device__ __forceinline__ void stage_rows_pass_a(uint32_t* xb, const typename IO::T* ra, const typename IO::T* rb,
-                                                  bool has_b, int k1, const float2* __restrict__ tw, int tid, int ex = 0)
-{
-    if (has_b) stage_rows_pass_a_impl<LG, IO, LR, NT, true>(xb, ra, rb, k1, tw, tid, ex);
-    else stage_rows_pass_a_impl<LG, IO, LR, NT, false>(xb, ra, rb, k1, tw, tid, ex);
-}
-// exponent of a head's rows from the pattern of their largest magnitude (NULL: rows are taken as they are)
-__device__ __forceinline__ int head_rows_exponent(const uint32_t* __restrict__ mx, int h)
-{
-    return mx ? __builtin_amdgcn_readfirstlane(row_exponent(mx[h])) : 0;
 }
 
 // run r of a chunk of complex values (16-byte runs of four) -> first value n; lane bits as for the rows:
@@ -901,17 +754,10 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
     }
 }
 
-// ROWS (outer radix 4): items are single rows of N = 2 L samples, in two chunks of the N-point twisted transform instead
-// of four of a zero-padded one per pair (npairs = B, log2R = 1 as the count of chunks).  Pass C is outer_inv_rows.  Equal work for
-// an even batch and half the spectrum; a single row takes two chunks instead of three, 256 items instead of 384 at
-// H = 128: one round of the device instead of two.
-// B=1, H=128, N=65536 fp16 step: 271 us with pairs, 207 us with rows.
-template <int LG, class IO, int NWV, int NB, bool CONJ, int FUSEA, bool ROWS>
+template <int LG, int NWV, int NB, bool CONJ>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
-coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, __half2* __restrict__ ws,
-                 int64_t B, int64_t H, int64_t N, int npairs, int log2R, int nch, int total, int per,
-                 const float2* __restrict__ tw, const unsigned char* __restrict__ ctab,
-                 const uint32_t* __restrict__ rows_max)
+coop_conv_kernel(const float2* __restrict__ kspec, __half2* __restrict__ ws, int npairs, int log2R, int total, int per,
+                 const float2* __restrict__ tw, const unsigned char* __restrict__ ctab)
 {
     using C = CC<LG>;
     constexpr int NT = NWV * 64;
@@ -941,8 +787,8 @@ coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict
     const int w1 = (c * C::PITCH + g * C::TC) * 4;
 
     auto run_n = [&](int i) { return chunk_run_n<LG>(i * NT + tid); };
-    // items (head, chunk k1 < nch, pair); nch = R, or R/2 + 1 where every pair is a single real row: the chunks
-    // above R/2 are then the complex conjugates of those below (Hermitian spectrum) and pass C fills them in
+    // items (head, chunk k1, pair)
+    const int nch = 1 << log2R;
     auto chunk_of = [&](int it) {
         const int hk = it / npairs, p = it - hk * npairs;
         const int h = hk / nch, k1 = hk - h * nch;
@@ -971,34 +817,9 @@ coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict
         }
     };
 
-    // FUSEA: rows of the item -> pass-A sum -> slots; phase-1 operands of the item
-    Mats F1 = K.F16, F2 = K.F16;
-    auto stage_rows = [&](int it) __attribute__((always_inline)) {
-        // ROWS: chunk kc of a row is chunk 4 kc + 1 of a split twice as wide (see coop_conv_row_kernel)
-        constexpr int LR = ROWS ? FUSEA + 1 : (FUSEA > 0 ? FUSEA : 2);
-        const int hk = it / npairs, p = it - hk * npairs;
-        const int h = hk / nch, kc = hk - h * nch, k1 = ROWS ? 4 * kc + 1 : kc;
-        F1 = phase_mats(k1, C::cb + 4, LG + LR, tw, lane);
-        F2 = phase_mats(k1, C::cb, LG + LR, tw, lane);
-        twisted_t1f<LG, LR, NT>(t1f, gtab, k1, tw, tid);
-        const int ex = head_rows_exponent(rows_max, h);
-        if constexpr (ROWS) {
-            const size_t o = row_off(p, h, H, N);
-            stage_rows_pass_a_impl<LG, IO, LR, NT, false, (1 << FUSEA) / 2>(xb, in + o, in + o, k1, tw, tid, ex);
-        } else {
-            const bool has_b = (2 * p + 1) < B;
-            const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-            stage_rows_pass_a<LG, IO, LR, NT>(xb, in + oa, in + ob, has_b, k1, tw, tid, ex);
-        }
-    };
-    auto stage_item = [&](int it) __attribute__((always_inline)) {
-        if (FUSEA) stage_rows(it);
-        else stage(it);
-    };
-
     staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
     __syncthreads();
-    if (it0 < it1) stage_item(it0);
+    if (it0 < it1) stage(it0);
     for (int it = it0; it < it1; ++it) {
         const int hk = it / npairs, hh = hk / nch;
         const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) +
@@ -1008,7 +829,7 @@ coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict
         // ---- phase 1, in place
 #pragma unroll 1
         for (int gi = 0; gi < ng; ++gi)
-            phase1_inplace<LG, NB>(xb, t1f, vt, F1, F2, cF, (gi * NWV + wave) * 8, lane);
+            phase1_inplace<LG, NB>(xb, t1f, vt, K.F16, K.F16, cF, (gi * NWV + wave) * 8, lane);
         __syncthreads();
 
         // ---- phase 2
@@ -1059,187 +880,7 @@ coop_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict
         }
         __syncthreads();
         drain(it);
-        if (it + 1 < it1) {
-            if (FUSEA) __syncthreads();      // rows are staged by other lanes than those that drained the slots
-            stage_item(it + 1);
-        }
-    }
-}
-
-// s + dot product of two runs of eight raw samples (I/O dtype, two per word): exact products, fp32 sum
-template <class IO>
-__device__ __forceinline__ float run_dot(const uint4& a, const uint4& b, float s)
-{
-    const uint32_t wa[4] = {a.x, a.y, a.z, a.w}, wb[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        union { uint32_t u; h2 h; bf2 b; } x, y;
-        x.u = wa[m]; y.u = wb[m];
-        s = IsBf<IO>::v ? __builtin_amdgcn_fdot2_f32_bf16(x.b, y.b, s, false) : __builtin_amdgcn_fdot2(x.h, y.h, s, false);
-    }
-    return s;
-}
-
-// -------------------------------------------------------------------------------------
-// dk and dD of the multi-pass split straight from the rows (outer radix 2^LR around 2^LG-point transforms,
-// pass A taken while staging as in coop_conv_kernel).  grid = H 2^LR, chunk index fastest and renumbered per XCD;
-// the workgroup of (head, chunk k1) walks the head's row pairs: u pair -> pass A, phase 1, forward half of
-// phase 2 -> Z (fp16, parked in LDS beside the slots); dy pair likewise -> W; A += conj(Z) W in fp32
-// registers, eight phase-2 tiles per wave.  Then the inverse half of phase 2 and phase 3 give chunk k1 of pass
-// C's input (fp16 complex, unit-stride runs).  dD is the plain fp32 dot product of the rows (chunk 0's workgroup).
-// Every chunk's workgroup reads the whole rows: 2^LR reads of u and dy through L2 (LR = 4: 1 GB per launch at
-// N = 131072, B = 1, which is what bounds that case).
-// -------------------------------------------------------------------------------------
-template <int LG, class IO, int LR>
-__global__ void __launch_bounds__(CC<LG>::NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
-coop_dk_rows_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
-                    __half2* __restrict__ ws_A, float* __restrict__ dD, int64_t B, int64_t H, int64_t N,
-                    int npairs, int nch, const float2* __restrict__ tw, const unsigned char* __restrict__ ctab,
-                    const uint32_t* __restrict__ u_max, const uint32_t* __restrict__ dy_max)
-{
-    using C = CC<LG>;
-    using T = typename IO::T;
-    static_assert(C::NG == 1, "one group of eight phase-2 tiles per wave");
-    constexpr int NT = C::NW * 64;
-    extern __shared__ uint4 lds4[];
-    __shared__ float red[C::NW];
-    uint32_t* xb = reinterpret_cast<uint32_t*>(lds4);
-    uint4* t1f = lds4 + C::XWORDS / 4;
-    uint4* t1i = t1f + C::TC * 4;
-    uint32_t* vt = reinterpret_cast<uint32_t*>(t1i + C::TC * 4);
-    uint4* zl = lds4 + coop_staged_lds_bytes<LG>() / 16;   // Z of the pair in flight: eight 16-byte words per lane
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = lane & 15, g = lane >> 4;
-    // the 2^LR workgroups of a head read the same rows: consecutive ids, renumbered so that they share an XCD
-    // (one L2), fetch them from HBM once
-    const unsigned G = gridDim.x;
-    const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
-    // nch chunks per head: all 2^LR, or only k1 <= 2^LR / 2 for a batch of one row (the accumulated spectrum of
-    // real rows is Hermitian, pass C takes the other chunks as conjugates)
-    const int h = (int)(vid / (unsigned)nch), k1 = (int)(vid - (unsigned)h * (unsigned)nch);
-    const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
-    Consts<LG> K;
-    make_consts<LG>(K, tw, lane);
-    h2 cF[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
-        cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
-    }
-    // phase-1 operands of this chunk: pass A's twist in the matrix columns and the w_{16TC} table
-    const Mats F1 = phase_mats(k1, C::cb + 4, LG + LR, tw, lane), F2 = phase_mats(k1, C::cb, LG + LR, tw, lane);
-    staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-    __syncthreads();
-    twisted_t1f<LG, LR, NT>(t1f, gtab, k1, tw, tid);
-
-    // dD[h] = sum over the head's rows of dy u, in fp32, by the workgroup of chunk 0 (its siblings pull the same
-    // rows through this XCD's L2): unit-stride runs of eight samples, exact products, fixed summation order
-    if (dD && k1 == 0) {
-        float dsum = 0.f;
-        const int64_t nrun = N / 8;
-        for (int64_t b = 0; b < B; ++b) {
-            const uint4* qu = reinterpret_cast<const uint4*>(u + row_off(b, h, H, N));
-            const uint4* qd = reinterpret_cast<const uint4*>(dy + row_off(b, h, H, N));
-            for (int64_t i0 = tid; i0 < nrun; i0 += 4 * NT) {
-                uint4 a[4], d[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int64_t i = i0 + q * NT;
-                    if (i < nrun) { a[q] = qu[i]; d[q] = qd[i]; }
-                    else { a[q] = make_uint4(0u, 0u, 0u, 0u); d[q] = a[q]; }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) dsum = run_dot<IO>(a[q], d[q], dsum);
-            }
-        }
-        for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
-        if (lane == 0) red[wave] = dsum;
-        __syncthreads();
-        if (tid == 0) {
-            float t = 0.f;
-            for (int w = 0; w < C::NW; ++w) t += red[w];
-            dD[h] = t;
-        }
-    }
-
-    const int t0 = wave * 8;                             // this wave's tiles in every phase
-    float2 acc[8][4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = make_float2(0.f, 0.f);
-
-#pragma unroll 1
-    for (int p = 0; p < npairs; ++p) {
-        const bool has_b = (2 * p + 1) < B;
-        const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            int zoff = 0;
-            asm volatile("" : "+v"(zoff));               // table reads stay inside the walk
-            const uint4* t1f_ = t1f + zoff;
-            const uint32_t* vt_ = vt + zoff;
-            const T* src = pass ? dy : u;
-            __syncthreads();                             // the slots are free (and the tables written)
-            stage_rows_pass_a<LG, IO, LR, NT>(xb, src + oa, src + ob, has_b, k1, tw, tid,
-                                              head_rows_exponent(pass ? dy_max : u_max, h));
-            __syncthreads();
-            phase1_inplace<LG, 2>(xb, t1f_, vt_, F1, F2, cF, t0, lane);
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                f4 zr, zi;
-                phase2_fwd<LG>(xb, phase2_base<LG>(t0 + i, lane), K, zr, zi);
-                if (pass == 0) {
-                    zl[i * NT + tid] = make_uint4(pack_h2(zr[0], zi[0]), pack_h2(zr[1], zi[1]), pack_h2(zr[2], zi[2]),
-                                                  pack_h2(zr[3], zi[3]));
-                } else {
-                    const uint4 zq = zl[i * NT + tid];   // (written by this lane: no barrier)
-                    const uint32_t z[4] = {zq.x, zq.y, zq.z, zq.w};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        union { uint32_t u; h2 hh; } cv;
-                        cv.u = z[j];
-                        const float a = (float)cv.hh[0], b = (float)cv.hh[1];
-                        // conj(Z) * W, one fused multiply-add per term
-                        acc[i][j].x = __builtin_fmaf(b, zi[j], __builtin_fmaf(a, zr[j], acc[i][j].x));
-                        acc[i][j].y = __builtin_fmaf(-b, zr[j], __builtin_fmaf(a, zi[j], acc[i][j].y));
-                    }
-                }
-                if (i & 1) __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-
-    __syncthreads();                                     // every wave is done reading the slots
-    if (!ws_A) return;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        H8U m;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) m.w[j] = pack_h2(acc[i][j].x, acc[i][j].y);
-        phase2_inv<LG>(xb, phase2_base<LG>(t0 + i, lane), K, m);
-    }
-    __syncthreads();
-    const int w1 = (c * C::PITCH + g * C::TC) * 4;
-#pragma unroll
-    for (int tb = 0; tb < 8; tb += 2) {
-        f4 r[2], s2[2];
-        phase3_two_lds<LG>(xb, t1i, vt, K, cF, t0 + tb, lane, r, s2);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) =
-                make_uint4(pack_h2(r[k][0], s2[k][0]), pack_h2(r[k][1], s2[k][1]), pack_h2(r[k][2], s2[k][2]),
-                           pack_h2(r[k][3], s2[k][3]));
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
-    uint4* dst = reinterpret_cast<uint4*>(ws_A + ((size_t)h << (LG + LR)) + (size_t)k1 * C::L);
-    constexpr int RPL = (C::L / 4) / NT;
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-        const int n = chunk_run_n<LG>(i * NT + tid), a0 = staged_slot<LG>(n);
-        dst[n / 4] = make_uint4(xb[a0], xb[a0 + 4], xb[a0 + 8], xb[a0 + 12]);
+        if (it + 1 < it1) stage(it + 1);
     }
 }
 
@@ -1449,25 +1090,17 @@ coop_kspec_kernel(const __half2* __restrict__ ws, const float* __restrict__ D, c
         }
 }
 
-// Kernel spectrum, staged form: chunk k1 of the multi-pass split with pass A inside (outer radix 2^LR around 2^LG
-// points); grid = H 2^LR, chunk index fastest and renumbered per XCD, so that the chunks of a head share its row in one L2.
-// Every chunk needs the whole row (pass A sums its R/2 pieces); the workgroup reads it in unit-stride 32-byte
-// runs.  R <= 4: the row stays in registers between the search of the head's maximum (power-of-two pre-scale)
-// and the conversion, one round trip to memory; R = 8: the maximum comes from the caller (rs).
-// Then s[n2] = sum_{n1 < R/2} w_R^(n1 k1) k[n1 L + n2] goes to the exchange slots as fp16 complex, phase 1 runs
-// in place with the twist in its operands, the forward half of phase 2 writes kscale (FFT + D[h]).
-template <int LG, int LR, bool ROWS>
+// Kernel spectrum of rows of N = 2^LG samples (coop_conv_row_kernel), staged form, one workgroup per head: the row stays in
+// registers between the search of the head's maximum (power-of-two pre-scale) and the conversion, one round trip to memory;
+// phase 1 runs in place with the twist in its operands, the forward half of phase 2 writes kscale (FFT + D[h]).
+template <int LG>
 __global__ void __launch_bounds__(CC<LG>::NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
-coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D, const float* __restrict__ rs,
-                       float2* __restrict__ kspec, float kscale_over_c, float kscale,
+coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* __restrict__ kspec, float kscale_over_c,
+                       float kscale,
                        const float2* __restrict__ tw, const unsigned char* __restrict__ ctab)
 {
     using C = CC<LG>;
-    // ROWS: the N-point twisted transform of single rows (coop_conv_row_kernel), 2^(LR-1) chunks of which number kc is
-    // chunk 4 kc + 1 of a split twice as wide
-    constexpr int LT = ROWS ? LR + 1 : LR, LCH = ROWS ? LR - 1 : LR;      // outer radix of the twist, chunks per head (log2)
-    constexpr int NT = C::NW * 64, RH = (1 << LR) / 2;
-    constexpr int NROW = RH * C::L;                      // samples of a row
+    constexpr int NT = C::NW * 64;
     constexpr int RPA = (C::L / 8) / NT;                 // runs of eight samples per lane
     extern __shared__ uint4 lds4[];
     __shared__ float mred[3][C::NW];
@@ -1478,130 +1111,63 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g = lane >> 4;
     const unsigned G = gridDim.x;
-    const unsigned vid = (G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3);
-    const int h = (int)(vid >> LCH), kc = (int)(vid & ((1u << LCH) - 1u)), k1 = ROWS ? 4 * kc + 1 : kc;
+    const int h = (int)((G & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (G >> 3) + (blockIdx.x >> 3));
     const uint4* gtab = reinterpret_cast<const uint4*>(ctab + coop_tab_offset(LG));
-    const float* kr = k + (size_t)h * NROW;
+    const float* kr = k + (size_t)h * C::L;
 
-    float2 cr[RH];
+    // the row starts travelling first; tables and operands are built behind it (their loads return after
+    // the row's, so one round trip to memory covers everything)
+    float4 v[RPA][2];
 #pragma unroll
-    for (int n1 = 0; n1 < RH; ++n1)
-        cr[n1] = tw_full(tw, (uint32_t)((n1 * k1) & ((1 << LT) - 1)) << (TW_LOG2 - LT));
-    auto load_run = [&](float4 (&v)[RH][2], int i) __attribute__((always_inline)) {
-        const int n = staged_run_n<LG>(i * NT + tid);
-#pragma unroll
-        for (int n1 = 0; n1 < RH; ++n1) {
-            const float4* src = reinterpret_cast<const float4*>(kr + (size_t)n1 * C::L + n);
-            v[n1][0] = src[0];
-            v[n1][1] = src[1];
-        }
-    };
-    // a, mp: sum and maximum of the magnitudes with the skip term counted in the lag-0 tap (`first`: v[0][0].x is
-    // k_0), the two bounds on the head's largest spectrum bin (spec_exponent)
+    for (int i = 0; i < RPA; ++i) {
+        const float4* src = reinterpret_cast<const float4*>(kr + staged_run_n<LG>(i * NT + tid));
+        v[i][0] = src[0];
+        v[i][1] = src[1];
+    }
     const float Dh = D[h];
-    float a = 0.f, mp = 0.f;
-    auto max_run = [&](const float4 (&v)[RH][2], float m, bool first) __attribute__((always_inline)) {
+    staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
+    twisted_t1f<LG, 2, NT>(t1f, gtab, 1, tw, tid);       // (a lane rewrites the entries it wrote itself)
+    // constants of the transform (table look-ups in global memory)
+    Consts<LG> K;
+    make_consts<LG>(K, tw, lane);
+    h2 cF[4];
 #pragma unroll
-        for (int n1 = 0; n1 < RH; ++n1)
+    for (int j = 0; j < 4; ++j) {
+        const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
+        cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
+    }
+    const Mats F1 = phase_mats(1, C::cb + 4, LG + 2, tw, lane), F2 = phase_mats(1, C::cb, LG + 2, tw, lane);
+    // the head's largest magnitude; a, mp: sum and maximum of the magnitudes with the skip term counted in the lag-0 tap
+    // (run 0 of lane 0 starts at k_0), the two bounds on the head's largest spectrum bin (spec_exponent)
+    float m = 0.f, a = 0.f, mp = 0.f;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(v[n1][q].x), fabsf(v[n1][q].y)), fmaxf(fabsf(v[n1][q].z), fabsf(v[n1][q].w))));
-                const float x0 = fabsf(v[n1][q].x + ((first && n1 == 0 && q == 0) ? Dh : 0.f));
-                a += (x0 + fabsf(v[n1][q].y)) + (fabsf(v[n1][q].z) + fabsf(v[n1][q].w));
-                mp = fmaxf(mp, fmaxf(fmaxf(x0, fabsf(v[n1][q].y)), fmaxf(fabsf(v[n1][q].z), fabsf(v[n1][q].w))));
-            }
-        return m;
-    };
-    auto head_max = [&](float m) __attribute__((always_inline)) {     // over the workgroup; ends behind a barrier
-        for (int o = 32; o > 0; o >>= 1) {
-            m = fmaxf(m, __shfl_xor(m, o, 64));
-            mp = fmaxf(mp, __shfl_xor(mp, o, 64));
-            a += __shfl_xor(a, o, 64);
+    for (int i = 0; i < RPA; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float4 x = v[i][q];
+            m = fmaxf(m, fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))));
+            const float x0 = fabsf(x.x + (i == 0 && q == 0 && tid == 0 ? Dh : 0.f));
+            a += (x0 + fabsf(x.y)) + (fabsf(x.z) + fabsf(x.w));
+            mp = fmaxf(mp, fmaxf(fmaxf(x0, fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))));
         }
-        if (lane == 0) { mred[0][wave] = m; mred[1][wave] = a; mred[2][wave] = mp; }
-        __syncthreads();
-        m = mred[0][0]; a = mred[1][0]; mp = mred[2][0];
-        for (int w = 1; w < C::NW; ++w) { m = fmaxf(m, mred[0][w]); a += mred[1][w]; mp = fmaxf(mp, mred[2][w]); }
-        return m;
-    };
-    auto put_run = [&](const float4 (&v)[RH][2], int i, float r) __attribute__((always_inline)) {
+    for (int o = 32; o > 0; o >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, o, 64));
+        mp = fmaxf(mp, __shfl_xor(mp, o, 64));
+        a += __shfl_xor(a, o, 64);
+    }
+    if (lane == 0) { mred[0][wave] = m; mred[1][wave] = a; mred[2][wave] = mp; }
+    __syncthreads();                                     // (also covers the cleared slots)
+    m = mred[0][0]; a = mred[1][0]; mp = mred[2][0];
+    for (int w = 1; w < C::NW; ++w) { m = fmaxf(m, mred[0][w]); a += mred[1][w]; mp = fmaxf(mp, mred[2][w]); }
+    const float r = head_scale_of(m);
+#pragma unroll
+    for (int i = 0; i < RPA; ++i) {
         const int a0 = staged_slot<LG>(staged_run_n<LG>(i * NT + tid));
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            float sr = 0.f, si = 0.f;
-#pragma unroll
-            for (int n1 = 0; n1 < RH; ++n1) {
-                const float4 q = v[n1][e >> 2];
-                const float x = ((e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w) * r;
-                sr = __builtin_fmaf(cr[n1].x, x, sr);
-                si = __builtin_fmaf(cr[n1].y, x, si);
-            }
-            xb[a0 + 4 * e] = pack_h2(sr, si);
-        }
-    };
-
-    // constants of the transform (table look-ups in global memory)
-    Consts<LG> K;
-    h2 cF[4];
-    Mats F1, F2;
-    auto make_operands = [&]() __attribute__((always_inline)) {
-        make_consts<LG>(K, tw, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float2 w = tw_full(tw, (uint32_t)((c * (4 * g + j)) & 255) << (TW_LOG2 - 8));
-            cF[j] = h2{(_Float16)w.x, (_Float16)w.y};
-        }
-        F1 = phase_mats(k1, C::cb + 4, LG + LT, tw, lane);
-        F2 = phase_mats(k1, C::cb, LG + LT, tw, lane);
-    };
-
-    float r;
-    if constexpr (RH <= 2) {
-        // the row starts travelling first; tables and operands are built behind it (their loads return after
-        // the row's, so one round trip to memory covers everything)
-        float4 v[RPA][RH][2];
-#pragma unroll
-        for (int i = 0; i < RPA; ++i) load_run(v[i], i);
-        staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-        twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);     // (a lane rewrites the entries it wrote itself)
-        make_operands();
-        float m = 0.f;
-#pragma unroll
-        for (int i = 0; i < RPA; ++i) m = max_run(v[i], m, i == 0 && tid == 0);     // run 0 of lane 0 starts at k_0
-        r = head_scale_of(head_max(m));                  // (the barrier also covers the cleared slots)
-#pragma unroll
-        for (int i = 0; i < RPA; ++i) put_run(v[i], i, r);
-    } else {
-        staged_tables<LG, NT>(lds4, gtab, tw, tid, 0);
-        make_operands();
-        // the head's maximum comes from the caller (rs, found by a kernel in front: one read of the row instead
-        // of one per chunk), else from a scan of the whole row here
-        float m = 0.f;
-        if (!rs) {
-            const float4* k4 = reinterpret_cast<const float4*>(kr);
-            for (int i = tid; i < RH * (C::L / 4); i += NT) {
-                const float4 q = k4[i];
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(q.x), fabsf(q.y)), fmaxf(fabsf(q.z), fabsf(q.w))));
-                const float x0 = fabsf(q.x + (i == 0 ? Dh : 0.f));
-                a += (x0 + fabsf(q.y)) + (fabsf(q.z) + fabsf(q.w));
-                mp = fmaxf(mp, fmaxf(fmaxf(x0, fabsf(q.y)), fmaxf(fabsf(q.z), fabsf(q.w))));
-            }
-        }
-        m = head_max(m);                                 // (the barrier also covers the tables)
-        r = head_scale_of(rs ? rs[h] : m);
-        if (rs) {                                        // [H, 2H) and [2H, 3H) of the caller's statistics
-            const unsigned Hh = G >> LCH;
-            a = rs[Hh + h];
-            mp = rs[2 * Hh + h];
-        }
-        twisted_t1f<LG, LT, NT>(t1f, gtab, k1, tw, tid);
-#pragma unroll
-        for (int i0 = 0; i0 < RPA; i0 += 2) {
-            float4 v[2][RH][2];
-            load_run(v[0], i0);
-            load_run(v[1], i0 + 1);
-            put_run(v[0], i0, r);
-            put_run(v[1], i0 + 1, r);
+            const float4 q = v[i][e >> 2];
+            const float x = ((e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w) * r;
+            xb[a0 + 4 * e] = pack_h2(x, 0.f);
         }
     }
 
@@ -1610,9 +1176,9 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
     for (int gi = 0; gi < C::NG; ++gi) phase1_inplace<LG, 2>(xb, t1f, vt, F1, F2, cF, (gi * C::NW + wave) * 8, lane);
     __syncthreads();
     const int es = spec_exponent(kscale * a, kscale * mp);
-    if (kc == 0 && tid == 0) spec_exp_of(kspec, G >> LCH, (int64_t)C::L << LR)[h] = es;
+    if (tid == 0) spec_exp_of(kspec, G, (int64_t)C::L * 2)[h] = es;
     const float alpha = ldexpf(kscale_over_c / r, -es), beta = ldexpf(Dh * kscale, -es);
-    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (((size_t)h << LCH) + kc) * C::L);
+    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(kspec) + (size_t)h * C::L);
 #pragma unroll 1
     for (int gi = 0; gi < C::NG; ++gi)
 #pragma unroll
@@ -1645,9 +1211,10 @@ hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, cons
     return hipGetLastError();
 }
 
+// rows, or the inner convolution of the multi-pass split in the workspace
 template <int LG, class IO>
-hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
-                        const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
+hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, const Problem& pr, const Plan& pl,
+                        const Tables& tb, hipStream_t st)
 {
     constexpr int NWV = CC<LG>::NW, NB = NTB;
     if constexpr (LG == COOP_MAX_LOG2) {
@@ -1658,14 +1225,8 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2*
                         : coop_conv_row_go<LG, IO, false, false>(in, kspec, out, pr, tb, st);
         }
     }
-    // multi-pass: the inner convolution on pass A's workspace, or (fuse_a) on the rows themselves
-    using T = typename IO::T;
     const size_t lds = coop_staged_lds_bytes<LG>();
-    // (head, chunk, pair) items; a batch of one row (every pair a single real row) with pass A inside needs only
-    // the chunks up to R/2 (conv_chunks)
-    const bool rows = fuse_a && rows_split(pl);
-    const int nch = rows ? 2 : coop_conv_chunks(pr, pl, fuse_a), nrow = rows ? (int)pr.B : pr.npairs;
-    const long total = pr.H * nch * nrow;
+    const long total = pr.H * ((long)pr.npairs << pl.log2R);          // (head, chunk, pair) items
     auto launch = [&](auto kern, int& resident) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1677,23 +1238,12 @@ hipError_t coop_conv_go(const void* in, const float2* kspec, void* out, __half2*
             resident = (nb > 0 ? nb : 1) * compute_units();
         }
         const int per = (int)((total + resident - 1) / resident);
-        hipLaunchKernelGGL(kern, dim3((unsigned)((total + per - 1) / per)), dim3(NWV * 64), lds, st, (const T*)in, kspec,
-                           ws, pr.B, pr.H, pr.N, nrow, rows ? 1 : pl.log2R, nch, (int)total, per, tb.tw,
-                           (const unsigned char*)tb.ctab, fuse_a ? pr.max_a : nullptr);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((total + per - 1) / per)), dim3(NWV * 64), lds, st, kspec, ws, pr.npairs, pl.log2R,
+                           (int)total, per, tb.tw, (const unsigned char*)tb.ctab);
         return hipGetLastError();
     };
-    static int res[6] = {0, 0, 0, 0, 0, 0};
-    if constexpr (LG == COOP_MAX_LOG2) {
-        if (rows)
-            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 2, true>, res[2])
-                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 2, true>, res[3]);
-        if (fuse_a && pl.log2R == 3)
-            return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 3, false>, res[4])
-                        : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 3, false>, res[5]);
-    }
-    if (fuse_a) return hipErrorInvalidValue;
-    return conj ? launch(coop_conv_kernel<LG, IO, NWV, NB, true, 0, false>, res[1])
-                : launch(coop_conv_kernel<LG, IO, NWV, NB, false, 0, false>, res[0]);
+    static int res[2] = {0, 0};
+    return conj ? launch(coop_conv_kernel<LG, NWV, NB, true>, res[1]) : launch(coop_conv_kernel<LG, NWV, NB, false>, res[0]);
 }
 
 // multi-pass dk: chunks of pass A's outputs in, chunks for pass C and partial dD sums out
@@ -1714,30 +1264,6 @@ hipError_t coop_dk_go(const __half2* ws_u, const __half2* ws_dy, __half2* ws_A, 
     return hipGetLastError();
 }
 
-// Multi-pass dk from the rows: the plan's split (outer radix 2^log2R around 32768 points, log2R = 2 or 3) is taken
-// as outer radix 2^(log2R+1) around 16384 points, whose accumulators fit one walk.  Returns the scale pass C has to
-// apply (two forward chains and one inverse chain of the 16384-point transform, 1 / padded length).
-template <class IO, int LR>
-hipError_t coop_dk_rows_go(const void* dy, const void* u, __half2* ws_A, float* dD, const Problem& pr,
-                           const Tables& tb, hipStream_t st, float* scale_c)
-{
-    constexpr int LG = COOP_MAX_LOG2 - 1;
-    using T = typename IO::T;
-    using C = CC<LG>;
-    const size_t lds = coop_staged_lds_bytes<LG>() + (size_t)C::NW * 64 * 8 * 16;      // slots, tables, Z
-    const int shift = 6 + (C::te >= 2 ? 1 : 0);
-    const float dkscale = (float)(int64_t(1) << (3 * shift)) / (float)(2 * pr.N);
-    *scale_c = dkscale;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_dk_rows_kernel<LG, IO, LR>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    const int nch = pr.B == 1 ? (1 << LR) / 2 + 1 : (1 << LR);
-    hipLaunchKernelGGL((coop_dk_rows_kernel<LG, IO, LR>), dim3((unsigned)(pr.H * nch)), dim3(C::NW * 64), lds, st,
-                       (const T*)dy, (const T*)u, ws_A, dD, pr.B, pr.H, pr.N, pr.npairs, nch, tb.tw,
-                       (const unsigned char*)tb.ctab, pr.max_a, pr.max_b);
-    return hipGetLastError();
-}
-
 template <int LG>
 hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, const float* rs, float2* kspec,
                          int64_t H, int64_t N, const Plan& pl, const Tables& tb, hipStream_t st)
@@ -1747,20 +1273,16 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
     dim3 grid((unsigned)H, 1u << pl.log2R);
     const int shift = 6 + (C::te >= 2 ? 1 : 0);
     const float koc = pl.kscale * (float)(1 << shift);
-    auto launch_rows = [&](auto kern) {      // staged form (ws unused; rs only at outer radix 8)
-        const size_t lds_rows = coop_staged_lds_bytes<LG>();
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows);
-        if (e != hipSuccess) return e;
-        const int lch = pl.log2R - (pl.row1 || rows_split(pl) ? 1 : 0);
-        hipLaunchKernelGGL(kern, dim3((unsigned)(H << lch)), dim3(C::NW * 64), lds_rows, st, k, D,
-                           pl.log2R == 3 ? rs : nullptr, kspec, koc, pl.kscale, tb.tw, (const unsigned char*)tb.ctab);
-        return hipGetLastError();
-    };
-    if constexpr (LG == COOP_MAX_LOG2) {      // pass A inside
-        if (pl.row1) return launch_rows(coop_kspec_rows_kernel<LG, 1, true>);
-        if (rows_split(pl)) return launch_rows(coop_kspec_rows_kernel<LG, 2, true>);
-        if (pl.fuse_a && pl.log2R == 3) return launch_rows(coop_kspec_rows_kernel<LG, 3, false>);
+    if constexpr (LG == COOP_MAX_LOG2) {
+        if (pl.row1) {                               // (ws and rs unused)
+            const size_t lds_rows = coop_staged_lds_bytes<LG>();
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_kspec_rows_kernel<LG>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(coop_kspec_rows_kernel<LG>, dim3((unsigned)H), dim3(C::NW * 64), lds_rows, st, k, D, kspec, koc,
+                               pl.kscale, tb.tw, (const unsigned char*)tb.ctab);
+            return hipGetLastError();
+        }
     }
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(coop_kspec_kernel<LG>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1772,10 +1294,10 @@ hipError_t coop_kspec_go(const float* k, const __half2* ws, const float* D, cons
 
 }  // namespace
 
-hipError_t coop_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
+hipError_t coop_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
-#define GO(LG, IO) return coop_conv_go<LG, IO>(in, kspec, out, ws, conj, fuse_a, pr, pl, tb, st)
+#define GO(LG, IO) return coop_conv_go<LG, IO>(in, kspec, out, ws, conj, pr, pl, tb, st)
     if (pr.io == LONGCONV_F16) {
         if (pl.log2L2 == 13) GO(13, IoF16);
         if (pl.log2L2 == 14) GO(14, IoF16);
@@ -1806,23 +1328,6 @@ hipError_t coop_dk(const void* dy, const void* u, float* dk, float* dD, int nspl
     if (pl.log2L2 == 13) return coop_dk_go<13>(ws_u, ws_dy, dk ? ws_A : nullptr, dD_part, zbuf, pr, pl, tb, st);
     if (pl.log2L2 == 14) return coop_dk_go<14>(ws_u, ws_dy, dk ? ws_A : nullptr, dD_part, zbuf, pr, pl, tb, st);
     if (pl.log2L2 == 15) return coop_dk_go<15>(ws_u, ws_dy, dk ? ws_A : nullptr, dD_part, zbuf, pr, pl, tb, st);
-    return hipErrorInvalidValue;
-}
-
-hipError_t coop_dk_rows(const void* dy, const void* u, __half2* ws_A, float* dD, const Problem& pr, const Plan& pl,
-                        const Tables& tb, hipStream_t st, float* scale_c)
-{
-    if (!coop_dk_rows_ok(pl)) return hipErrorInvalidValue;
-    if (pl.log2R == 1) {
-        if (pr.io == LONGCONV_F16) return coop_dk_rows_go<IoF16, 2>(dy, u, ws_A, dD, pr, tb, st, scale_c);
-        if (pr.io == LONGCONV_BF16) return coop_dk_rows_go<IoBF16, 2>(dy, u, ws_A, dD, pr, tb, st, scale_c);
-    } else if (pl.log2R == 2) {
-        if (pr.io == LONGCONV_F16) return coop_dk_rows_go<IoF16, 3>(dy, u, ws_A, dD, pr, tb, st, scale_c);
-        if (pr.io == LONGCONV_BF16) return coop_dk_rows_go<IoBF16, 3>(dy, u, ws_A, dD, pr, tb, st, scale_c);
-    } else {
-        if (pr.io == LONGCONV_F16) return coop_dk_rows_go<IoF16, 4>(dy, u, ws_A, dD, pr, tb, st, scale_c);
-        if (pr.io == LONGCONV_BF16) return coop_dk_rows_go<IoBF16, 4>(dy, u, ws_A, dD, pr, tb, st, scale_c);
-    }
     return hipErrorInvalidValue;
 }
 

@@ -548,23 +548,26 @@ void mfma_fill_plan(Plan& pl)
         pl.kscale = 1.0f / (L * cr * cr);
         pl.dkscale = 1.0f / (L * cr * cr * cr);
     }
-    // outer radix 4 or 8 around the 32768-point cooperative kernels: the convolutions take pass A in their
-    // staging (switch fuse_pass_a = 0 keeps the separate pass, for comparison)
+    // rows of 32768 and more samples: N twisted points per row, in one kernel at 32768 (a row fits one compute unit), in chunks of
+    // 16384 points above it, without a pass A kernel (switch fuse_pass_a = 0: pairs and pass A, for comparison)
+    // (N points instead of 2N: the factor of two comes behind the last fp16 value)
     pl.fuse_a = pl.order.coop_lg == COOP_MAX_LOG2 && pl.log2R >= 1 && pl.log2R <= 3 && opt.fuse_pass_a;
-    // ... and at outer radix 2 a row's N twisted points fit one compute unit (spectrum, forward, du; dk keeps the split)
-    // (N points instead of 2N: the factor of two comes behind the last fp16 value, in the row kernel's last block and, at
-    // outer radix 4, in pass C, so that the products with the spectrum are no larger than a pair's)
     pl.row1 = pl.fuse_a && pl.log2R == 1;
+    if (chunk_plan(pl)) {
+        const float cr = long_chain_scale();
+        pl.kscale = 1.0f / (L * cr * cr);
+        pl.dkscale = 1.0f / (L * cr * cr * cr);
+    }
     // one backward kernel where a workgroup holds a head's accumulators (switch fuse_bwd = 0: two calls of it)
     pl.fuse_bwd = (pl.order.wave_lg || pl.order.long_lg) && opt.fuse_bwd;
 }
 
-hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
+hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     if (pl.order.wave_lg) return rows_conv(in, kspec, out, conj, pr, pl, tb, st);
     if (pl.order.long_lg) return long_conv(in, kspec, out, conj, pr, pl, tb, st);
-    if (pl.order.coop_lg) return coop_conv(in, kspec, out, ws, conj, fuse_a, pr, pl, tb, st);
+    if (pl.order.coop_lg) return coop_conv(in, kspec, out, ws, conj, pr, pl, tb, st);
     if (pr.io == LONGCONV_F16) { LC_LG_SWITCH(conv_go, IoF16, in, kspec, out, ws, conj, pr, pl, tb, st) }
     if (pr.io == LONGCONV_BF16) { LC_LG_SWITCH(conv_go, IoBF16, in, kspec, out, ws, conj, pr, pl, tb, st) }
     return hipErrorInvalidValue;
@@ -573,9 +576,8 @@ hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws
 // The single-pass wave and cooperative convolutions multiply Problem::gate into their own store; of the multi-pass
 // plans those whose pass C is the vectorised kernel (fp16 workspace, outer radix up to 16, inner length >= 1024)
 // apply it there.
-bool conv_applies_gate(const Plan& pl, bool fuse_a)
+bool conv_applies_gate(const Plan& pl)
 {
-    (void)fuse_a;
     if (pl.engine != ENGINE_MFMA) return false;
     if (pl.log2R == 0) return pl.order.wave_lg || pl.order.long_lg;
     return pl.log2R <= 4 && pl.log2L2 >= 10;

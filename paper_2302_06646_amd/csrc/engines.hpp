@@ -25,9 +25,9 @@ struct Problem {
     int io;          // longconv_dtype_t of u, y, dy, du
     int npairs;      // ceil(B/2): two batch rows of one head are transformed as re + i*im
     const void* gate = nullptr;   // convolutions only: [B,H,N] I/O dtype, multiplied into the output before the store
-    // bf16 rows of the multi-pass plans: per head, the bf16 pattern of the largest magnitude of the input rows
-    // (max_a: the convolution's input, or u for dk; max_b: dy for dk).  Heads outside the band are scaled by a
-    // power of two where the rows are converted (pass A inside the inner kernels) and back in pass C.
+    // bf16 rows that go through chunks (engine_chunk.hip): per head, the bf16 pattern of the largest magnitude of the input
+    // rows (max_a: the convolution's input, or u for dk; max_b: dy for dk).  Heads outside the band are scaled by a power of
+    // two where the rows are converted, and back in the last step.
     const uint32_t* max_a = nullptr;
     const uint32_t* max_b = nullptr;
     // convolutions of the multi-pass plans with an fp16 spectrum: the per-head exponents of the stored spectrum
@@ -40,7 +40,7 @@ struct Problem {
 // mx[h] = bf16 pattern of max |in[b,h,:]| over b (zeroed first); rows of 16-bit floats only
 hipError_t rows_absmax(const void* in, uint32_t* mx, const Problem& pr, hipStream_t st);
 // which plans apply Problem::gate inside their own store (the others leave it to a pass of its own)
-bool conv_applies_gate(const Plan& pl, bool fuse_a);
+bool conv_applies_gate(const Plan& pl);
 
 // ---- outer passes of the multi-pass split (multipass.hip) ------------------------
 // Pass A (matrix-core engine, fp16 workspace): ws[(h*npairs+p)*L + k1*L2 + n2] = scale * w_L^(n2*k1) * sum_{n1<R/2} w_R^(n1*k1) z[n1*L2+n2],
@@ -58,12 +58,8 @@ hipError_t head_stats(const float* k, const float* D, float* stats, int64_t H, i
 int outer_fwd_blocks_per_head(const Problem& pr, int log2L2);
 // Pass C: rows of `out` <- scale * sum_{k1} conj(w_R^(n1*k1) w_L^(n2*k1)) ws[...], n1 < R/2 only
 // (truncation to the first N samples); re -> row 2p, im -> row 2p+1.
-// herm: every row is a single real row whose chunks above R/2 were not computed; they are taken as the complex
-// conjugates of chunks R - k1 (Hermitian spectrum of real data).
-// Pass C of rows_split plans: ws holds two chunks of L2 values per row.
-hipError_t outer_inv_rows(const void* ws, void* out, const Problem& pr, int log2L2, const float2* tw, hipStream_t st);
 hipError_t outer_inv(const void* ws, void* out, const Problem& pr, int log2R, int log2L2, float scale,
-                     bool ws_f16, const float2* tw, hipStream_t st, bool herm = false);
+                     bool ws_f16, const float2* tw, hipStream_t st);
 // dD[h] = sum_b sum_t dy[b,h,t] u[b,h,t], plain fp32 dot product (one workgroup per head).
 hipError_t head_dot(const void* dy, const void* u, float* dD, const Problem& pr, hipStream_t st);
 // dD[h] = sum of the per-block partials written by outer_fwd.
@@ -127,8 +123,7 @@ hipError_t valu_bwd(const void* dy, const void* u, const float2* kspec, void* du
 // ---- fp16 MFMA engine (engine_mfma.hip) ---------------------------------------------
 constexpr int MFMA_INNER_MAX_LOG2 = 15;
 void mfma_fill_plan(Plan& pl);
-// fuse_a (only when pl.fuse_a): pass A has not been run; the inner kernel reads the rows `in` itself.
-hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
+hipError_t mfma_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 // Multi-pass: dD_part[h*R + k1] receives chunk k1's share of dD[h] (sum them with reduce_dD).
 hipError_t mfma_dk(const void* dy, const void* u, float* dk, float* dD, int nsplit, const __half2* ws_u,
@@ -168,32 +163,29 @@ int long_bwd_nsplit(int64_t B, int64_t H);
 hipError_t long_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 
+// ---- rows of N = 65536 and 131072 samples, N / 16384 chunks of their N-point transforms (engine_chunk.hip) ----
+// (and dk and dD of rows of 32768 samples, whose convolutions fit a compute unit: row1)
+inline bool chunk_plan(const Plan& pl) { return pl.fuse_a && pl.log2R >= 2; }
+inline bool chunk_dk_plan(const Plan& pl) { return pl.fuse_a; }
+hipError_t chunk_fill_tables(const void** tab_out, hipStream_t st);
+// rs: head_stats of k (N = 131072 only)
+hipError_t chunk_kspec(const float* k, const float* D, const float* rs, float2* kspec, int64_t H, const Plan& pl, const Tables& tb,
+                       hipStream_t st);
+// ws: 4 B H N bytes; pr.spec_exp, pr.gate and pr.max_a (powers of two the rows go in with) go into the output
+hipError_t chunk_conv(const void* in, const float2* kspec, void* out, void* ws, bool conj, const Problem& pr, const Plan& pl,
+                      const Tables& tb, hipStream_t st);
+hipError_t chunk_rows(const void* ws, void* out, const Problem& pr, int R, hipStream_t st);
+// du (with ws_du as ws above and pr.spec_exp; may be null), dk and dD (may be null).  Each share of a head's rows leaves
+// 4 H N bytes in ws_A and H N / 16384 numbers in exps and dD_part.  pr.max_a, pr.max_b: of u and dy
+int chunk_bwd_shares(int64_t B, int64_t H, int log2R);
+hipError_t chunk_bwd(const void* dy, const void* u, const float2* kspec, void* du, void* ws_du, float* dk, float* dD, void* ws_A,
+                     int* exps, float* dD_part, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
+
 // ---- cooperative chained matrix-core kernels for 2^13 <= L2 <= 2^15 (engine_coop.hip) --------
 constexpr int COOP_MIN_LOG2 = 13, COOP_MAX_LOG2 = 15;
 hipError_t coop_fill_tables(const void** tab_out, hipStream_t st);
-// fuse_a (plans with pl.fuse_a only): the kernel reads the rows `in` and takes pass A itself.
-// Chunks of the multi-pass split that the inner convolution computes: all R, or, for a batch of one row with pass
-// A inside the kernel, only k1 <= R/2: a real row has a Hermitian spectrum, chunk R - k1 of pass C's input is the
-// complex conjugate of chunk k1, and pass C (outer_inv with herm = true) takes it from there.
-// N = 65536: spectrum and convolutions take two chunks of each row's N-point twisted transform (4N is the twiddle table's
-// length, so N = 131072 keeps the zero-padded pairs)
-inline bool rows_split(const Plan& pl) { return pl.fuse_a && pl.log2R == 2; }
-inline int coop_conv_chunks(const Problem& pr, const Plan& pl, bool fuse_a)
-{
-    const int R = 1 << pl.log2R;
-    return (fuse_a && pr.B == 1 && pl.log2R >= 2) ? R / 2 + 1 : R;
-}
-hipError_t coop_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj, bool fuse_a,
+hipError_t coop_conv(const void* in, const float2* kspec, void* out, __half2* ws, bool conj,
                      const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
-// Multi-pass dk straight from the rows, for plans of outer radix 4 or 8 around 32768 points with pl.fuse_a: run as
-// outer radix 8 or 16 around 16384 points.  ws_A (null: dD only) receives pass C's input for that split (log2R + 1,
-// log2L2 - 1), dD (may be null) the heads' dot products, *scale_c the factor pass C applies.
-inline bool coop_dk_rows_ok(const Plan& pl)
-{
-    return pl.fuse_a && pl.log2R >= 1 && pl.log2R <= 3 && pl.log2L2 == COOP_MAX_LOG2;
-}
-hipError_t coop_dk_rows(const void* dy, const void* u, __half2* ws_A, float* dD, const Problem& pr, const Plan& pl,
-                        const Tables& tb, hipStream_t st, float* scale_c);
 // ws: pass-A output of the pre-scaled kernel (multi-pass plans only).
 hipError_t coop_kspec(const float* k, const __half2* ws, const float* D, const float* rs, float2* kspec, int64_t H,
                       int64_t N, const Plan& pl, const Tables& tb, hipStream_t st);

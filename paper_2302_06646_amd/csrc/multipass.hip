@@ -84,7 +84,7 @@ __global__ void outer_fwd_kernel(const typename IO::T* __restrict__ in, const ty
 template <class IO, class CW, int LOG2R>
 __global__ void outer_inv_kernel(const typename CW::T* __restrict__ ws, typename IO::T* __restrict__ out,
                                  int64_t B, int64_t H, int64_t N, int npairs, int log2L2, float scale,
-                                 const float2* __restrict__ tw, int herm, const int* __restrict__ spec_exp)
+                                 const float2* __restrict__ tw, const int* __restrict__ spec_exp)
 {
     constexpr int R = 1 << LOG2R, RH = R / 2;
     const int L2 = 1 << log2L2;
@@ -101,9 +101,7 @@ __global__ void outer_inv_kernel(const typename CW::T* __restrict__ ws, typename
 #pragma unroll
     for (int k1 = 0; k1 < R; ++k1) {
         const float2 wl = tw_full(tw, ((uint32_t)n2 * (uint32_t)k1) << (TW_LOG2 - log2L));
-        // herm: chunks above R/2 were not computed; untwisted, they are the conjugates of their mirror chunks
-        if (herm && k1 > RH) v[k1] = make_float2(v[R - k1].x, -v[R - k1].y);
-        else v[k1] = cmulc(CW::ld(ws, base + (size_t)k1 * L2 + n2), wl);
+        v[k1] = cmulc(CW::ld(ws, base + (size_t)k1 * L2 + n2), wl);
     }
 #pragma unroll 1
     for (int n1 = 0; n1 < RH; ++n1) {
@@ -186,14 +184,10 @@ template <class IO, int LOG2R>
 __global__ void __launch_bounds__(OB) outer_inv4_kernel(const __half2* __restrict__ ws,
                                                         typename IO::T* __restrict__ out, int64_t B, int64_t H,
                                                         int64_t N, int npairs, int log2L2, float scale,
-                                                        const float2* __restrict__ tw, int herm,
+                                                        const float2* __restrict__ tw,
                                                         const typename IO::T* __restrict__ gate,
-                                                        const uint32_t* __restrict__ max_a,
-                                                        const uint32_t* __restrict__ max_b,
                                                         const int* __restrict__ spec_exp)
 {
-    // max_a / max_b != NULL: the rows that went into this head were scaled by powers of two on the way in (bf16
-    // rows outside the band); the output gets the product of those powers back
     // gate != NULL: the rows are multiplied element by element by that tensor before the store (gated layer)
     static_assert(LOG2R >= 1 && LOG2R <= 4, "the roots of unity of rot16");
     constexpr int R = 1 << LOG2R, RH = R / 2;
@@ -207,20 +201,12 @@ __global__ void __launch_bounds__(OB) outer_inv4_kernel(const __half2* __restric
     const bool has_b = (2 * p + 1) < B;
     const size_t oa = row_off(2 * p, h, H, N), ob = row_off(has_b ? 2 * p + 1 : 2 * p, h, H, N);
     const __half2* src = ws + ((size_t)pairidx << log2L) + n2;
-    if (max_a) scale = ldexpf(scale, mu::row_exponent(max_a[h]) + (max_b ? mu::row_exponent(max_b[h]) : 0));
     if (spec_exp) scale = ldexpf(scale, spec_exp[h]);      // the stored spectrum's per-head power of two
     float2 w1[VEC], pw[VEC], v[R][VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) w1[j] = tw_full(tw, (uint32_t)(n2 + j) << (TW_LOG2 - log2L));
 #pragma unroll
     for (int k1 = 0; k1 < R; ++k1) {
-        // herm (single real rows): chunks above R/2 were not computed; untwisted, chunk k1 is the complex
-        // conjugate of chunk R - k1 (Hermitian spectrum of real data)
-        if (k1 > RH && herm) {
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) v[k1][j] = make_float2(v[R - k1][j].x, -v[R - k1][j].y);
-            continue;
-        }
         uint32_t qw[4];
         mu::load_words<VEC>(src + (size_t)k1 * L2, qw);
 #pragma unroll
@@ -421,52 +407,9 @@ hipError_t fwd_launch(const void* in, const void* in2, void* ws, void* ws2, floa
     return hipGetLastError();
 }
 
-// Pass C of single rows in two chunks (N = 2 L2 = 65536, W = exp(-2 pi i / 4N)): chunk kc carries the frequencies
-// kc + 2 f2 of the twisted row, so with a = W^-n2 v_0 and b = W^-5n2 v_1 sample n2 is Re(a + b) and sample L2 + n2
-// Re(exp(2 pi i / 8) (a - b)).  Four columns per thread as in outer_inv4_kernel; bound by
-// the chunks' reads: B=1, H=128 9.8 us, 50.7 MB (5.2 TB/s; four chunks of a pair: 12 us).
-template <class IO>
-__global__ void __launch_bounds__(OB) outer_inv_rows_kernel(const __half2* __restrict__ ws, typename IO::T* __restrict__ out,
-                                                            int nrow, int64_t H, int log2L2, const float2* __restrict__ tw,
-                                                            const typename IO::T* __restrict__ gate,
-                                                            const uint32_t* __restrict__ max_a, const int* __restrict__ spec_exp)
-{
-    constexpr int VEC = 4;
-    const int L2 = 1 << log2L2, nbx = L2 / (VEC * OB);
-    const int n2 = ((blockIdx.x % nbx) * OB + threadIdx.x) * VEC;
-    const int item = blockIdx.x / nbx, h = item / nrow;
-    const size_t o = row_off(item - h * nrow, h, H, 2 * (int64_t)L2) + n2;
-    // (2: N points where the spectrum's scale has 1/2N)
-    const float scale = ldexpf(2.0f, spec_exp[h] + (max_a ? mu::row_exponent(max_a[h]) : 0));
-    const __half2* src = ws + ((size_t)item << (log2L2 + 1)) + n2;
-    uint32_t q0[VEC], q1[VEC];
-    mu::load_words<VEC>(src, q0);
-    mu::load_words<VEC>(src + L2, q1);
-    float x[VEC], y[VEC];
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        const float2 w = tw_full(tw, (uint32_t)(n2 + j) << (TW_LOG2 - log2L2 - 3));
-        const float2 w2 = cmul(w, w), w5 = cmul(cmul(w2, w2), w);
-        union { uint32_t u; __half2 hh; } c0, c1;
-        c0.u = q0[j]; c1.u = q1[j];
-        const float2 a = cmulc(__half22float2(c0.hh), w), b = cmulc(__half22float2(c1.hh), w5);
-        x[j] = (a.x + b.x) * scale;
-        y[j] = ((a.x - b.x) - (a.y - b.y)) * (0.70710678118654752f * scale);
-    }
-    if (gate) {
-        float g0[VEC], g1[VEC];
-        load_cols<IO, VEC>(gate + o, g0);
-        load_cols<IO, VEC>(gate + o + L2, g1);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) { x[j] *= g0[j]; y[j] *= g1[j]; }
-    }
-    store_cols<IO, VEC>(out + o, x);
-    store_cols<IO, VEC>(out + o + L2, y);
-}
-
 template <class IO, class CW, int LOG2R>
 hipError_t inv_launch(const void* ws, void* out, const Problem& pr, int log2L2, float scale, const float2* tw,
-                      hipStream_t st, int herm)
+                      hipStream_t st)
 {
     using T = typename IO::T;
     using C = typename CW::T;
@@ -475,16 +418,15 @@ hipError_t inv_launch(const void* ws, void* out, const Problem& pr, int log2L2, 
         if ((1 << log2L2) >= VEC * OB) {
             dim3 grid4((unsigned)(((size_t)1 << log2L2) / (VEC * OB) * (size_t)pr.npairs * (size_t)pr.H));
             hipLaunchKernelGGL((outer_inv4_kernel<IO, LOG2R>), grid4, dim3(OB), 0, st, (const __half2*)ws, (T*)out,
-                               pr.B, pr.H, pr.N, pr.npairs, log2L2, scale, tw, herm, (const T*)pr.gate, pr.max_a,
-                               pr.max_b, pr.spec_exp);
+                               pr.B, pr.H, pr.N, pr.npairs, log2L2, scale, tw, (const T*)pr.gate, pr.spec_exp);
             return hipGetLastError();
         }
     }
-    // only the vectorised pass C applies a gate (see conv_applies_gate) or undoes row scales
-    if (pr.gate || pr.max_a || pr.max_b) return hipErrorInvalidValue;
+    // only the vectorised pass C applies a gate (see conv_applies_gate)
+    if (pr.gate) return hipErrorInvalidValue;
     dim3 grid((unsigned)(((size_t)1 << log2L2) / OB * (size_t)pr.npairs * (size_t)pr.H));
     hipLaunchKernelGGL((outer_inv_kernel<IO, CW, LOG2R>), grid, dim3(OB), 0, st, (const C*)ws, (T*)out, pr.B,
-                       pr.H, pr.N, pr.npairs, log2L2, scale, tw, herm, pr.spec_exp);
+                       pr.H, pr.N, pr.npairs, log2L2, scale, tw, pr.spec_exp);
     return hipGetLastError();
 }
 
@@ -508,9 +450,9 @@ hipError_t fwd_r(const void* in, const void* in2, void* ws, void* ws2, float* dD
 }
 template <class IO, class CW>
 hipError_t inv_r(const void* ws, void* out, const Problem& pr, int log2R, int log2L2, float scale,
-                 const float2* tw, hipStream_t st, int herm)
+                 const float2* tw, hipStream_t st)
 {
-#define CALL(LR) inv_launch<IO, CW, LR>(ws, out, pr, log2L2, scale, tw, st, herm)
+#define CALL(LR) inv_launch<IO, CW, LR>(ws, out, pr, log2L2, scale, tw, st)
     LC_R_SWITCH(CALL)
 #undef CALL
 }
@@ -531,10 +473,10 @@ hipError_t outer_fwd(const void* in, const void* in2, void* ws, void* ws2, float
 }
 
 hipError_t outer_inv(const void* ws, void* out, const Problem& pr, int log2R, int log2L2, float scale,
-                     bool ws_f16, const float2* tw, hipStream_t st, bool herm)
+                     bool ws_f16, const float2* tw, hipStream_t st)
 {
     if ((1 << log2L2) < OB) return hipErrorInvalidValue;
-#define GO(IO, CW) return inv_r<IO, CW>(ws, out, pr, log2R, log2L2, scale, tw, st, herm ? 1 : 0)
+#define GO(IO, CW) return inv_r<IO, CW>(ws, out, pr, log2R, log2L2, scale, tw, st)
     if (ws_f16) {
         if (pr.io == LONGCONV_F32) GO(IoF32, CwF16);
         if (pr.io == LONGCONV_F16) GO(IoF16, CwF16);
@@ -545,19 +487,6 @@ hipError_t outer_inv(const void* ws, void* out, const Problem& pr, int log2R, in
         GO(IoBF16, CwF32);
     }
 #undef GO
-}
-
-hipError_t outer_inv_rows(const void* ws, void* out, const Problem& pr, int log2L2, const float2* tw, hipStream_t st)
-{
-    if (log2L2 + 3 > TW_LOG2 || (1 << log2L2) < 4 * OB) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(((size_t)1 << log2L2) / (4 * OB) * (size_t)pr.B * (size_t)pr.H));
-#define GO(IO) hipLaunchKernelGGL(outer_inv_rows_kernel<IO>, grid, dim3(OB), 0, st, (const __half2*)ws, (IO::T*)out, (int)pr.B, \
-                                  pr.H, log2L2, tw, (const IO::T*)pr.gate, pr.max_a, pr.spec_exp)
-    if (pr.io == LONGCONV_F16) GO(IoF16);
-    else if (pr.io == LONGCONV_BF16) GO(IoBF16);
-    else return hipErrorInvalidValue;
-#undef GO
-    return hipGetLastError();
 }
 
 size_t head_stats_floats(int64_t H, int64_t N) { return (size_t)3 * H * (1 + (size_t)((N + STAT_BLOCK - 1) / STAT_BLOCK)); }
