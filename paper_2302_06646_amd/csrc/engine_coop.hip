@@ -214,15 +214,20 @@ __device__ __forceinline__ int phase2_base(int t2, int lane)
     return (ka * C::PITCH + (kb >> 2) * C::TC + t) * 4 + (kb & 3);
 }
 
-// forward half of phase 2 on one tile: LDS -> [A: F16 over d_c] * w_TC -> [B: F_TE over d_e]
+// tile t2 = t0 + k, t0 a multiple of TE = 8 tiles: words from t0's place
 template <int LG>
-__device__ __forceinline__ void phase2_fwd(const uint32_t* xb, int base, const Consts<LG>& K, f4& zr, f4& zi)
+__device__ __forceinline__ constexpr int phase2_step(int k)
 {
     using C = CC<LG>;
+    const int kb = (k & (C::TE - 1)) << (4 - C::te);
+    return ((k >> C::te) * C::PITCH + (kb >> 2) * C::TC) * 4 + (kb & 3);
+}
+
+// forward half of phase 2 on one tile: LDS -> [A: F16 over d_c] * w_TC -> [B: F_TE over d_e]
+template <int LG>
+__device__ __forceinline__ void phase2_fwd(const H8U& x, const Consts<LG>& K, f4& zr, f4& zi)
+{
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    H8U x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x.w[j] = xb[base + j * C::TE * 4];
     const f4 yr = MFMA(x.v, K.F16.re, zero), yi = MFMA(x.v, K.F16.im, zero);
     H8U u;
 #pragma unroll
@@ -230,23 +235,16 @@ __device__ __forceinline__ void phase2_fwd(const uint32_t* xb, int base, const C
     zr = MFMA(K.FL.re, u.v, zero);
     zi = MFMA(K.FL.im, u.v, zero);
 }
-
-// inverse half of phase 2 on one tile: (already multiplied) spectrum values m -> LDS
 template <int LG>
-__device__ __forceinline__ void phase2_inv(uint32_t* xb, int base, const Consts<LG>& K, const H8U& m)
+__device__ __forceinline__ void phase2_fwd(const uint32_t* xb, int base, const Consts<LG>& K, f4& zr, f4& zi)
 {
-    using C = CC<LG>;
-    const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    const f4 yr = MFMA(m.v, K.IL.re, zero), yi = MFMA(m.v, K.IL.im, zero);
-    H8U u;
+    H8U x;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) u.w[j] = cmul_pack(yr[j], yi[j], K.t2i[j]);
-    const f4 vr = MFMA(K.I16.re, u.v, zero), vi = MFMA(K.I16.im, u.v, zero);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) xb[base + j * C::TE * 4] = pack_h2(vr[j], vi[j]);
+    for (int j = 0; j < 4; ++j) x.w[j] = xb[base + j * CC<LG>::TE * 4];
+    phase2_fwd<LG>(x, K, zr, zi);
 }
 
-// the same, result kept in registers (4 fp16 complex words)
+// inverse half of phase 2 on one tile: (already multiplied) spectrum values m -> LDS
 template <int LG>
 __device__ __forceinline__ void phase2_inv_regs(const Consts<LG>& K, const H8U& m, H8U& out)
 {
@@ -258,6 +256,14 @@ __device__ __forceinline__ void phase2_inv_regs(const Consts<LG>& K, const H8U& 
     const f4 vr = MFMA(K.I16.re, u.v, zero), vi = MFMA(K.I16.im, u.v, zero);
 #pragma unroll
     for (int j = 0; j < 4; ++j) out.w[j] = pack_h2(vr[j], vi[j]);
+}
+template <int LG>
+__device__ __forceinline__ void phase2_inv(uint32_t* xb, int base, const Consts<LG>& K, const H8U& m)
+{
+    H8U o;
+    phase2_inv_regs<LG>(K, m, o);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xb[base + j * CC<LG>::TE * 4] = o.w[j];
 }
 
 // phase 3 on two tiles t, t+1: returns real parts r[k] and imaginary parts s[k] of the time samples
@@ -312,10 +318,19 @@ __device__ __forceinline__ h2 cmul_hh(h2 a, h2 w)
     return __builtin_elementwise_fma(ay, ws, ax * w);
 }
 
+// SW: the slots of eight consecutive t change places, in pairs, by XOR with the low bits of t / 8.  Four lanes of a row on its way
+// write (read) samples eight apart at a time, whose slots lie in the same banks otherwise (B=32, H=128, N=32768 fp16: 312
+// us, LDS busy 44% of the time and half of that in conflicts; 279 and 32%).
+template <int LG, bool SW>
+__device__ __forceinline__ void tile_places(int (&at)[4], int w1, int t0)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) at[j] = w1 + 4 * t0 + 8 * (SW ? j ^ ((t0 >> 3) & 3) : j);
+}
 // Phase 1 in place on the staged layout, 8 tiles t0..t0+7 of one wave: each lane reads its own 16 bytes
 // of a tile (samples d_a = 4g..4g+3 of column d_b = c) and writes outputs (k_a, k_b) = (c, 4g..4g+3) there.
 // F1 is the first-stage matrix (rows of the zero padding cleared when those slots hold stale data).
-template <int LG, int NB>
+template <int LG, int NB, bool SW = false>
 __device__ __forceinline__ void phase1_inplace(uint32_t* xb, const uint4* t1f, const uint32_t* vt, const Mats& F1,
                                                const Mats& F2, const h2 (&cF)[4], int t0, int lane)
 {
@@ -323,6 +338,8 @@ __device__ __forceinline__ void phase1_inplace(uint32_t* xb, const uint4* t1f, c
     const int c = lane & 15, g = lane >> 4;
     const int w1 = (c * C::PITCH + g * C::TC) * 4;
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    int at[4];                                           // places of tiles t0, t0 + 2, ..; the next tile is 4 words on
+    tile_places<LG, SW>(at, w1, t0);
 #pragma unroll
     for (int tb = 0; tb < 8; tb += NB) {
         H8U x[NB], tw1[NB];
@@ -331,7 +348,7 @@ __device__ __forceinline__ void phase1_inplace(uint32_t* xb, const uint4* t1f, c
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             const int t = t0 + tb + k;
-            x[k].u = *reinterpret_cast<const uint4*>(&xb[w1 + 4 * t]);
+            x[k].u = *reinterpret_cast<const uint4*>(&xb[at[(tb + k) >> 1] + ((tb + k) & 1) * 4]);
             tw1[k].u = t1f[t * 4 + g];
             union { uint32_t u; h2 h; } cv;
             cv.u = vt[t * 16 + c];
@@ -357,7 +374,7 @@ __device__ __forceinline__ void phase1_inplace(uint32_t* xb, const uint4* t1f, c
             o.y = cmul_pack(zr[k][1], zi[k][1], tw1[k].c[1]);
             o.z = cmul_pack(zr[k][2], zi[k][2], tw1[k].c[2]);
             o.w = cmul_pack(zr[k][3], zi[k][3], tw1[k].c[3]);
-            *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) = o;
+            *reinterpret_cast<uint4*>(&xb[at[(tb + k) >> 1] + ((tb + k) & 1) * 4]) = o;
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -419,7 +436,7 @@ __device__ __forceinline__ void staged_tables(uint4* lds4, const uint4* gtab, co
 // bits pick d_a % 4 and d_b % 4, so that a wave's 4-byte LDS accesses (word stride 4 along t) spread
 // over 32 banks while global accesses keep 64-byte segments
 template <int LG>
-__device__ __forceinline__ int staged_run_n(int r)
+__device__ __forceinline__ constexpr int staged_run_n(int r)
 {
     using C = CC<LG>;
     constexpr int QB = C::cb - 3;
@@ -428,9 +445,12 @@ __device__ __forceinline__ int staged_run_n(int r)
     const int db = ((r >> 4) & 3) | (((r >> (QB + 4)) & 3) << 2);
     return (da << (C::cb + 4)) + (db << C::cb) + 8 * q;
 }
+// what run i NT + r adds to run r, NT a multiple of the runs that share d_a / 4 and the high bit of d_b
+template <int LG>
+__device__ __forceinline__ constexpr int run_step(int r) { return staged_run_n<LG>(r); }
 // word of sample n of the pair in the exchange buffer (consecutive samples are 4 words apart)
 template <int LG>
-__device__ __forceinline__ int staged_slot(int n)
+__device__ __forceinline__ constexpr int staged_slot(int n)
 {
     using C = CC<LG>;
     const int t = n & (C::TC - 1), db = (n >> C::cb) & 15, da = n >> (C::cb + 4);
@@ -501,7 +521,7 @@ __device__ __forceinline__ int chunk_run_n(int r)
 // samples (see engine_rows.hip).  The row's transform fits one compute unit, so rows go from memory to memory in one
 // kernel.  (As row pairs in two chunks of a 65536-point transform the same matrix work needs a complex fp16 workspace
 // of twice the rows' bytes written, and read back by a pass C kernel, and has two chunks where an odd last row needs one.)
-// B=32, H=128, N=32768 fp16: 670 us as pairs in two chunks, 311 us here (1.7 TB/s); what is left is matrix and vector issue.
+// B=32, H=128, N=32768 fp16: 670 us as pairs in two chunks, 279 us here (1.9 TB/s); what is left is matrix and vector issue.
 // The twist W^n, W = exp(-2 pi i / 4N), n = d_a 16 TC + d_b TC + t, takes no instructions: its d_a factor sits in the
 // matrices over d_a of both directions, its d_b factor in the lanes' w_256 constants and its t factor in the w_L table,
 // which phases 1 and 3 (conjugated) share.  The next row is prefetched in registers; a bf16 row outside the band is scaled by
@@ -563,6 +583,11 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
 
     // bf16 rows outside the band are scaled by a power of two
     __shared__ uint32_t dr_mx[NWV];
+    // word of sample e of run i: pairs of samples change places by the low bits of the run's t / 8
+    int sl[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sl[e] = staged_slot<LG>(run_n(0)) + 8 * (e ^ ((run_n(0) >> 3) & 3));
+    auto slot = [&](int i, int e) { return sl[e >> 1] + (e & 1) * 4 + staged_slot<LG>(run_step<LG>(i * NT)); };
     auto measure = [&]() {
         uint32_t m[1] = {0u};
 #pragma unroll
@@ -579,11 +604,10 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
 #pragma unroll
                 for (int m = 0; m < 4; ++m) wa[m] = __builtin_expect(ea != 0, 0) ? bf2_to_h2_scaled(wa[m], ea) : bf2_to_h2(wa[m]);
             }
-            const int a0 = staged_slot<LG>(run_n(i));
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                xb[a0 + 8 * m] = wa[m] & 0xffffu;
-                xb[a0 + 8 * m + 4] = wa[m] >> 16;
+                xb[slot(i, 2 * m)] = wa[m] & 0xffffu;
+                xb[slot(i, 2 * m + 1)] = wa[m] >> 16;
             }
         }
     };
@@ -596,7 +620,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
         }
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
-            const int n = run_n(i), a0 = staged_slot<LG>(n);
+            const int n = run_n(i);
             uint32_t wa[4];
             if constexpr (GATE) {                        // fp32 samples: gate and power of two, then one rounding
                 float x[8];
@@ -605,8 +629,8 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
                 for (int m = 0; m < 4; ++m) {
                     union { uint32_t u; h2 h; } q;
                     q.u = gw[m];
-                    x[2 * m] = __uint_as_float(xb[a0 + 8 * m]) * (IsBf<IO>::v ? __uint_as_float(gw[m] << 16) : (float)q.h[0]);
-                    x[2 * m + 1] = __uint_as_float(xb[a0 + 8 * m + 4]) *
+                    x[2 * m] = __uint_as_float(xb[slot(i, 2 * m)]) * (IsBf<IO>::v ? __uint_as_float(gw[m] << 16) : (float)q.h[0]);
+                    x[2 * m + 1] = __uint_as_float(xb[slot(i, 2 * m + 1)]) *
                                    (IsBf<IO>::v ? __uint_as_float(gw[m] & 0xffff0000u) : (float)q.h[1]);
                 }
                 if (__builtin_expect(ea != 0, 0)) {
@@ -620,7 +644,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     union { uint32_t u; h2 h; } a;
-                    a.u = __builtin_amdgcn_perm(xb[a0 + 8 * m + 4], xb[a0 + 8 * m], 0x05040100u);
+                    a.u = __builtin_amdgcn_perm(xb[slot(i, 2 * m + 1)], xb[slot(i, 2 * m)], 0x05040100u);
                     wa[m] = IsBf<IO>::v ? pack_bf2((float)a.h[0], (float)a.h[1]) : a.u;
                 }
                 if (__builtin_expect(ea != 0, 0)) {
@@ -669,37 +693,44 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
         // ---- phase 1, in place
 #pragma unroll 1
         for (int gi = 0; gi < ng; ++gi)
-            phase1_inplace<LG, NB>(xb, t1f, vt, F1, K.F16, c1, (gi * NWV + wave) * 8, lane);
+            phase1_inplace<LG, NB, true>(xb, t1f, vt, F1, K.F16, c1, (gi * NWV + wave) * 8, lane);
         __syncthreads();
         asm volatile("" : "+s"(ks));
 
         // ---- phase 2
 #pragma unroll 1
-        for (int gi = 0; gi < ng; ++gi)
-#pragma unroll
-        for (int tb = 0; tb < 8; tb += NB) {
+        for (int gi = 0; gi < ng; ++gi) {
             const int t0 = (gi * NWV + wave) * 8;
-            int base[NB];
-            f4 zr[NB], zi[NB];
-            H8U kk[NB];
+            // this lane's words d_c = 4g + j of tile t0; tile t0 + k: phase2_step(k) on
+            int at[4];
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const int t2 = t0 + tb + k;
-                base[k] = phase2_base<LG>(t2, lane);
-                kk[k].u = ks[t2 * 64 + lane];
+            for (int j = 0; j < 4; ++j) at[j] = phase2_base<LG>(t0, lane) + j * C::TE * 4 + 4 * (((c & 7) ^ (2 * j)) - (c & 7));
+#pragma unroll
+            for (int tb = 0; tb < 8; tb += NB) {
+                f4 zr[NB], zi[NB];
+                H8U kk[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) kk[k].u = ks[(t0 + tb + k) * 64 + lane];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    H8U x;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x.w[j] = xb[at[j] + phase2_step<LG>(tb + k)];
+                    phase2_fwd<LG>(x, K, zr[k], zi[k]);
+                }
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    H8U m, o;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)      // correlation (du): the conjugate spectrum
+                        m.w[j] = CONJ ? cmul_pack_conj(zr[k][j], zi[k][j], kk[k].c[j])
+                                      : cmul_pack(zr[k][j], zi[k][j], kk[k].c[j]);
+                    phase2_inv_regs<LG>(K, m, o);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) xb[at[j] + phase2_step<LG>(tb + k)] = o.w[j];
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) phase2_fwd<LG>(xb, base[k], K, zr[k], zi[k]);
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                H8U m;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)      // correlation (du): the conjugate spectrum
-                    m.w[j] = CONJ ? cmul_pack_conj(zr[k][j], zi[k][j], kk[k].c[j])
-                                  : cmul_pack(zr[k][j], zi[k][j], kk[k].c[j]);
-                phase2_inv<LG>(xb, base[k], K, m);
-            }
-            __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
 
@@ -709,6 +740,8 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
         for (int gi = 0; gi < ng; ++gi) {
             const int t0 = (gi * NWV + wave) * 8;
             const f4 zero = {0.f, 0.f, 0.f, 0.f};
+            int at[4];
+            tile_places<LG, true>(at, w1, t0);
 #pragma unroll
             for (int tb = 0; tb < 8; tb += 2) {
                 H8U tw1[2], x[2], vv[2];
@@ -717,7 +750,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
                 for (int k = 0; k < 2; ++k) {
                     const int t = t0 + tb + k;
                     tw1[k].u = t1i[t * 4 + g];
-                    x[k].u = *reinterpret_cast<const uint4*>(&xb[w1 + 4 * t]);
+                    x[k].u = *reinterpret_cast<const uint4*>(&xb[at[(tb + k) >> 1] + ((tb + k) & 1) * 4]);
                     vv[k].u = *reinterpret_cast<const uint4*>(&vt[t * 16 + 4 * g]);
                 }
 #pragma unroll
@@ -737,9 +770,9 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
                     if constexpr (GATE)
-                        *reinterpret_cast<f4*>(&xb[w1 + 4 * (t0 + tb + k)]) = r[k];
+                        *reinterpret_cast<f4*>(&xb[at[(tb + k) >> 1] + ((tb + k) & 1) * 4]) = r[k];
                     else
-                        *reinterpret_cast<uint4*>(&xb[w1 + 4 * (t0 + tb + k)]) = make_uint4(
+                        *reinterpret_cast<uint4*>(&xb[at[(tb + k) >> 1] + ((tb + k) & 1) * 4]) = make_uint4(
                             pack_h2(r[k][0], 0.f), pack_h2(r[k][1], 0.f), pack_h2(r[k][2], 0.f), pack_h2(r[k][3], 0.f));
                 __builtin_amdgcn_sched_barrier(0);
             }
