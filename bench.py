@@ -88,31 +88,21 @@ def group_bytes(w: wl.Workload):
 def executed_mfma_flops(w: wl.Workload):
     """Matrix-core flops the kernels issue for one step (model of the factorisation, dense 16x16x32 blocks,
     two instructions per 16x16 complex tile and stage, 16384 flop each): per 256-point tile a forward or an inverse half
-    transform costs 8 instructions at four digits, and one less than 6 at three or 4 at two digits (rows up to N = 4096: the
-    first block of real samples is two 16x16x16 instructions, the last computes real parts only, as the inverse at
-    N = 32768 does).  The convolutions and the spectrum transform N twisted points per row at N <= 4096, 32768 and 65536 (2N
-    points per row pair, N per head), the whole backward pass too up to N = 4096; dk beyond that, and everything at the other
-    lengths, works on zero-padded pairs.  Half transforms: forward 2, du 2, dk 2 per row or pair (3 for both where one kernel
-    serves them); per head: spectrum 1, dk's inverse 1."""
+    transform costs 8 instructions at four digits, 6 at three and 4 at two, and one less where the first block takes real
+    samples (two 16x16x16 instructions) and the last computes real parts only: rows up to N = 16384, and the inverse of the
+    convolutions at N = 32768.  Everything transforms N points per row and per head.  Half transforms per row: forward 2,
+    backward 3 (4 at N = 32768, where du and dk are separate); per head: spectrum 1, dk's inverse 1."""
     if w.dtype == wl.F32:
         return 0.0
-    L, N = 2 * w.N, w.N
-    npairs = (w.B + 1) // 2
-    half = lambda points, digits, less=0: (2 * digits - less) * 16384 * (points / 256)
+    N = w.N
+    half = lambda digits, less=0: (2 * digits - less) * 16384 * (N / 256)
     if N <= 4096:
-        return w.H * (5 * w.B + 2) * half(N, 2 if N == 256 else 3, 1)
-    pairs = half(L, 4)
-    dk = 2 * npairs + 1
-    if N >= 32768 and w.B == 1:
-        # a batch of one row: dk splits into R chunks of 16384 points and computes 0 .. R/2 of them (Hermitian spectrum)
-        R = L // 16384
-        dk *= (R / 2 + 1) / R
-    if N in (32768, 65536):
-        inverse = half(N, 4, 1 if N == 32768 else 0)
-        return w.H * ((2 * w.B + 1) * half(N, 4) + 2 * w.B * inverse + dk * pairs)
-    R = L // 32768
-    fc = (R / 2 + 1) / R if w.B == 1 and R > 1 else 1.0
-    return w.H * ((4 * npairs * fc + 1 + dk) * pairs)
+        return w.H * (5 * w.B + 2) * half(2 if N == 256 else 3, 1)
+    if N <= 16384:
+        return w.H * (5 * w.B + 2) * half(4, 1)
+    if N == 32768:
+        return w.H * ((4 * w.B + 2) * half(4) + 2 * w.B * half(4, 1))
+    return w.H * (5 * w.B + 2) * half(4)
 
 
 class Sets:
@@ -155,7 +145,8 @@ def run_workload(key, steps, warmup, lc, torch):
     w = wl.WORKLOADS[key]
     S = Sets(w, lc, torch)
     plan = lc.longconv_plan_string(w.N, w.dtype)
-    one_kernel_bwd = "kernel=wave" in plan            # du, dk, dD of a call come from one kernel
+    # du, dk, dD of a call come from one kernel
+    one_kernel_bwd = "kernel=wave" in plan or ("runs=rows(" in plan and "backward=one" in plan)
     gb = group_bytes(w)
     groups = ["kspec", "fwd"] + (["bwd"] if one_kernel_bwd else ["bwd_dk", "bwd_du"])
 

@@ -36,24 +36,18 @@
  *     bf16 rows (u, dy) may have any magnitude: rows are multiplied by a power of two on
  *     their way into the transform and by its inverse on the way out where they need it, so
  *     gradients of order 1e-10 or activations of order 1e6 keep the accuracy of data of
- *     order one.  Up to N = 4096, and for y and du at N = 32768, this is decided row by row:
+ *     order one.  Up to N = 16384, and for y and du at N = 32768, this is decided row by row:
  *     a row whose largest sample lies in 2^-2 .. 2^4 runs unscaled, any other row is scaled on
- *     its own.  At N = 8192 and 16384 it is decided pair by pair (two batch rows of a head
- *     share one complex transform): a pair whose rows both lie in that band and within a
- *     factor of four of each other runs unscaled, in any other pair every row is scaled on
- *     its own.  Either way every row meets the bound of data of order one whatever its
- *     neighbours' sizes.  Beyond these lengths all rows of a head share one power of
- *     two, found by a pass over the tensor in front, so rows of one head that differ by many
+ *     its own, so every row meets the bound of data of order one whatever its neighbours'
+ *     sizes.  Beyond these lengths all rows of a head share one power of two, found by a pass over the tensor in front, so rows of one head that differ by many
  *     orders of magnitude lose the small ones.  The kernel k and the skip term D may have any
  *     magnitude as well: a head is scaled by a power of two on its way into the spectrum's
  *     transform, and a head whose spectrum lies outside fp16's comfortable range is stored
  *     with a further power of two taken out, which the convolutions give back where they
  *     pack their output (heads of order one take neither path).  Not rescaled, and therefore
  *     to be kept inside fp16's normal range by the caller: fp16 rows (order one is fine up
- *     to N = 131072; the transform grows them by at most sqrt(2N); at N = 8192, 16384 and
- *     131072, and for dk from 32768 on, batch rows 2p and 2p+1 of a head share one complex
- *     transform, so the error of an fp16 row is relative to the larger of the two: rows of
- *     similar size, as a normalised layer produces them, meet the bound), and of course the outputs have to fit the I/O dtype.  fp32 I/O computes in fp32.
+ *     to N = 131072; the transform grows them by at most sqrt(2N)), and of course the outputs
+ *     have to fit the I/O dtype.  fp32 I/O computes in fp32.
  */
 #ifndef LONGCONV_H
 #define LONGCONV_H
@@ -84,8 +78,7 @@ int longconv_init(void);
 
 /* Size in bytes of the spectrum cache for H heads of length N (0 on bad args).
  * The cache holds, per head, the spectrum of [k[h,:], 0_N] plus D[h]: 2N points, or the
- * N points of the twisted row where fp16/bf16 rows are transformed one by one (N <= 4096,
- * 32768 and 65536; the room is that of 2N points at every length)
+ * N points of the twisted row for fp16/bf16 I/O (the room is that of 2N points)
  * (the skip term is a delta kernel of height D[h]), pre-scaled and stored in the
  * permuted order the fused transform produces (Algorithm 2 lines 1-2: the
  * spectrum is computed once and stored already permuted, so no permutation ever
