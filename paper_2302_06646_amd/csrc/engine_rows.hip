@@ -1653,8 +1653,30 @@ hipError_t rows_fill_tables(const void** tab_out, hipStream_t st)
 // B=3, H=256, N=2048 10.1 and 13.2); gated rows of 4096 samples are worth it (B=4, H=128 bf16 21.5 and 19.8).  N = 1024
 // ungated, few heads: the root of the rows, where the rows a wave is spared and the partial results that come with them
 // balance (fp16: B=16, H=16 2 shares 10.4 us, 4 9.3; B=64, H=32 4 shares 14.3, 8 12.9, 16 17.3).
+// N >= 2048 with more than half as many heads as the device has compute units, up to twice as many: what a compute unit has to
+// do depends on how H * s workgroups fall on the 256 of them, so the estimate below picks s.  A share's rows and the ends of
+// its pipeline count once per workgroup on the fullest unit; two resident workgroups (N = 2048) take 1.32 times one's time; the
+// shares' sum is a launch and its bytes.  bf16, a call before and now: N=2048 H=130 B=16 26.7 -> 23.1 us, gated 33.6 -> 27.8 (3
+// shares, not 2); H=340 B=32 65 -> 58, gated 90 -> 75 (3, not 1); N=4096 H=340 B=32 135 -> 123, gated 179 -> 159 (2, not 1).
+// Its sum does not depend on the gate and grows with s, so a gated call never has fewer shares than an ungated one.
+static int rows_bwd_nsplit_many(int64_t B, int64_t H, int lg, bool gated)
+{
+    const float row_us = lg == 11 ? (gated ? 1.7f : 1.33f) : (gated ? 2.3f : 1.65f);
+    const float ends = lg == 11 ? 4.f : 5.f;
+    int best = 1;
+    float least = 0.f;
+    for (int s = 1; s <= 3 && s <= B; ++s) {
+        const int on_cu = (int)((H * s + 255) / 256);
+        const float load = lg == 11 ? 1.32f * (on_cu / 2) + (on_cu & 1) : (float)on_cu;
+        const float sum = s > 1 ? 3.5f + (float)s * (float)H * (float)(8 << lg) * 2e-7f : 0.f;
+        const float us = row_us * load * ((float)((B + s - 1) / s) + ends) + sum;
+        if (s == 1 || us < least) { best = s; least = us; }
+    }
+    return best;
+}
 int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated)
 {
+    if (lg >= 11 && H > 128 && H <= 512) return rows_bwd_nsplit_many(B, H, lg, gated);
     const bool wave_rows = lg == 10 && !gated;
     const int ngrp = lg >= 11 ? 1 : lg == 10 && gated ? 2 : 4;
     const int64_t units = lg == 8 ? (B + 1) / 2 : B;

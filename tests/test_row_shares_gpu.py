@@ -1,0 +1,42 @@
+"""Backward pass of rows of 2048 and 4096 samples whose heads alone fill half the device: two or three shares of a head's rows,
+uneven ones among them, and one share next to the rule's edges (128 and 512 heads)."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+import test_gated_gpu as tg
+from gpu_harness import DD_TOL, TOL, GpuRun, _compare, sample_heads
+from oracle import gated
+
+pytestmark = pytest.mark.gpu
+
+
+# three shares of 5 and 6 rows, three of 11 and 10; three shares of more than one turn; two shares; none (few rows; the edges)
+@pytest.mark.parametrize("B,H,N,io", [(16, 130, 2048, wl.BF16), (32, 130, 4096, wl.F16), (25, 340, 2048, wl.F16),
+                                      (25, 260, 4096, wl.BF16), (1, 129, 2048, wl.BF16), (2, 512, 2048, wl.F16),
+                                      (2, 513, 4096, wl.F16), (17, 128, 2048, wl.F16)])
+def test_shares_of_many_heads(B, H, N, io):
+    inp = wl.generate(dataclasses.replace(wl.WORKLOADS["2"], N=N, dtype=io), B=B, H=H)
+    g = GpuRun(inp)
+    hs = sample_heads(H, B, seed=N + H)
+    k64, D64 = inp.k.astype(np.float64)[hs], inp.D.astype(np.float64)[hs]
+    du, dk, dD = g.bwd()
+    for x in (du, dk, dD):
+        assert np.all(np.isfinite(x))
+    rdu, rdk, rdD = oracle.longconv_bwd(inp.dy[:, hs], inp.u[:, hs], k64, D64)
+    _compare({"du": du[:, hs], "dk": dk[hs], "dD": dD[hs]}, {"du": rdu, "dk": rdk, "dD": rdD}, TOL[io], f"shares N{N}", DD_TOL)
+
+
+def test_shares_of_gated_rows():
+    B, H, N, io = 16, 130, 2048, wl.BF16
+    inp, g_s, g_v = tg._inputs(N, io, B, H, 5)
+    _, du, dk, dD, dg = tg._run(inp, g_s)
+    hs = sample_heads(H, B, seed=5)
+    k64, D64 = inp.k.astype(np.float64)[hs], inp.D.astype(np.float64)[hs]
+    rdu, rdk, rdD, rdg = gated.gated_bwd(inp.dy[:, hs], g_v[:, hs], inp.u[:, hs], k64, D64)
+    for name, a, b in (("du", du[:, hs], rdu), ("dk", dk[hs], rdk), ("dg", dg[:, hs], rdg), ("dD", dD[hs], rdD)):
+        e = wl.rel_l2(a, b)
+        assert np.isfinite(e) and e <= (1e-5 if name == "dD" else 3e-3), (name, e)
