@@ -92,7 +92,8 @@ size_t longconv_kspec_bytes(int64_t H, int64_t N, int io);
 
 /* Scratch bytes a call needs (0 on bad args).  `backward` = 0 for longconv_fwd and
  * longconv_fwd_gated, 1 for longconv_bwd, 2 for longconv_bwd_gated.  The figure includes room for an on-the-fly spectrum, so it
- * is valid whether or not a cached spectrum is passed. */
+ * is valid whether or not a cached spectrum is passed.  It never falls as B grows (nor do the 2-D and the learned layer's figures
+ * below): a workspace for a batch of B serves every smaller batch of the same H, N and io. */
 size_t longconv_workspace_bytes(int64_t B, int64_t H, int64_t N, int io, int backward);
 
 /* Kernel-spectrum precompute (Algorithm 2 lines 1-2; Appendix D.1: the spectrum is

@@ -175,7 +175,7 @@ static const int* spec_exp_ptr(const float2* kspec, int64_t H, size_t L, const P
 
 struct WsLayout {
     size_t kspec, kscratch, hscale, ws1, ws2, wsA, dpart, chunk, zbuf, dkpart, ddpart, rowmx, total;
-    int nblk, nsplit;
+    int nblk;
 };
 
 // Single-pass plans: the backward kernels run one workgroup per head; with few heads the rows (pairs) of a head are dealt
@@ -186,6 +186,13 @@ static int dk_nsplit(int64_t B, int64_t H, const Plan& pl, bool gated)
     if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_nsplit(B, H, pl.order.wave_lg, gated);
     if (pl.engine == ENGINE_MFMA && pl.order.long_lg) return long_bwd_nsplit(B, H);
     return 1;
+}
+// the most of them that a call of up to B rows takes (the numbers above need not grow with B, the workspace has to)
+static int dk_room(int64_t B, int64_t H, const Plan& pl)
+{
+    if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_room(B, H, pl.order.wave_lg);
+    if (pl.engine == ENGINE_MFMA && pl.order.long_lg) return long_bwd_room(B, H);
+    return dk_nsplit(B, H, pl, true);
 }
 
 // bf16 rows of the multi-pass plans that take pass A inside the inner kernels are scaled per head (see rows_absmax)
@@ -217,13 +224,13 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     const size_t npart = (size_t)w.nblk > (size_t(1) << pl.log2R) ? (size_t)w.nblk : (size_t(1) << pl.log2R);
     w.dpart = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npart * sizeof(float));
     w.chunk = off; if (backward && chunks) off += up256((size_t)chunk_bwd_shares(B, H, pl.log2R) * (H << pl.log2R) * 2 * sizeof(float));
-    w.nsplit = backward ? dk_nsplit(B, H, pl, true) : 1;      // (room for the gated pass, which never has fewer shares)
+    const size_t shares = backward ? dk_room(B, H, pl) : 1;
     w.zbuf = off;
     if (backward && pl.order.coop_lg && outer_a) off += up256((size_t)H * L * sizeof(__half2));
-    if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(H, w.nsplit, pl));
+    if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(H, (int)shares, pl));
     // partial dk rows, or (fp32 engine, multi-pass) partial sets of pass C's complex chunks
-    w.dkpart = off; if (w.nsplit > 1) off += up256((size_t)w.nsplit * H * (pl.log2R ? 2 * L : L / 2) * sizeof(float));
-    w.ddpart = off; if (w.nsplit > 1) off += up256((size_t)w.nsplit * H * sizeof(float));
+    w.dkpart = off; if (shares > 1) off += up256(shares * H * (pl.log2R ? 2 * L : L / 2) * sizeof(float));
+    w.ddpart = off; if (shares > 1) off += up256(shares * H * sizeof(float));
     // bf16 rows of the multi-pass plans with pass A inside the inner kernels: per-head maxima of u and dy
     w.rowmx = off; if (rows_rescaled(pl, io)) off += up256((size_t)2 * H * sizeof(uint32_t));
     w.total = off;
@@ -527,7 +534,7 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
                 return LONGCONV_ERR_HIP;
             ks = (const float2*)(base + w.kspec);
         }
-        const int ns = w.nsplit;
+        const int ns = dk_nsplit(B, H, pl, gate != nullptr);
         const bool multi = pl.log2R != 0;
         float* dkp = (float*)(base + w.dkpart);
         float* ddp = (float*)(base + w.ddpart);

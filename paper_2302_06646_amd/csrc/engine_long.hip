@@ -747,23 +747,35 @@ hipError_t long_bwd(const void* dy, const void* u, const float2* kspec, void* du
     return hipErrorInvalidValue;
 }
 
-// Shares of a head's rows: the number that ends first where each compute unit holds one workgroup (N = 16384) or two, and a
-// workgroup's constants and its inverse transform cost as much as about a row and a half, a second launch as half a row.
-int long_bwd_nsplit(int64_t B, int64_t H)
+// Shares of a head's rows: the number that ends first where each compute unit holds one workgroup (eight waves of more than 200
+// registers at either length), and a workgroup's constants and its inverse transform cost as much as about a row and a half, a
+// second launch as half a row.  How many are tried at most bounds the workspace.
+static int64_t most_shares(int64_t B, int64_t H)
 {
-    const int64_t resident = 256;
-    // (at most two more than when rows went in pairs and workgroups were a third more: a workspace of that time still serves)
     int64_t most = 384 / H;
     if (most > (B + 1) / 2) most = (B + 1) / 2;
     if (most > 64) most = 64;
     most = most > 1 ? most + 2 : 2;
-    if (most > B) most = B;
+    return most < B ? most : B;
+}
+static int64_t turns(int64_t workgroups) { return (workgroups + 255) / 256; }
+int long_bwd_nsplit(int64_t B, int64_t H)
+{
+    const int64_t most = most_shares(B, H);
     int64_t best = 1, best_t = -1;
     for (int64_t s = 1; s <= most; ++s) {
-        const int64_t t = (s * H + resident - 1) / resident * (2 * ((B + s - 1) / s) + 3) + (s > 1 ? 1 : 0);
+        const int64_t t = turns(s * H) * (2 * ((B + s - 1) / s) + 3) + (s > 1 ? 1 : 0);
         if (best_t < 0 || t < best_t) { best = s; best_t = t; }
     }
     return (int)best;
+}
+// (one share ends before s shares of s times its turns, whatever B)
+int long_bwd_room(int64_t B, int64_t H)
+{
+    int64_t room = 1;
+    for (int64_t s = 2; s <= most_shares(B, H); ++s)
+        if (turns(s * H) < s * turns(H)) room = s;
+    return (int)room;
 }
 
 }  // namespace lc

@@ -1659,6 +1659,12 @@ hipError_t rows_fill_tables(const void** tab_out, hipStream_t st)
 // shares' sum is a launch and its bytes.  bf16, a call before and now: N=2048 H=130 B=16 26.7 -> 23.1 us, gated 33.6 -> 27.8 (3
 // shares, not 2); H=340 B=32 65 -> 58, gated 90 -> 75 (3, not 1); N=4096 H=340 B=32 135 -> 123, gated 179 -> 159 (2, not 1).
 // Its sum does not depend on the gate and grows with s, so a gated call never has fewer shares than an ungated one.
+static bool many_heads(int64_t H, int lg) { return lg >= 11 && H > 128 && H <= 512; }
+static float many_load(int64_t H, int lg, int s)      // of the fullest unit, in workgroups that run alone
+{
+    const int on_cu = (int)((H * s + 255) / 256);
+    return lg == 11 ? 1.32f * (on_cu / 2) + (on_cu & 1) : (float)on_cu;
+}
 static int rows_bwd_nsplit_many(int64_t B, int64_t H, int lg, bool gated)
 {
     const float row_us = lg == 11 ? (gated ? 1.7f : 1.33f) : (gated ? 2.3f : 1.65f);
@@ -1666,17 +1672,15 @@ static int rows_bwd_nsplit_many(int64_t B, int64_t H, int lg, bool gated)
     int best = 1;
     float least = 0.f;
     for (int s = 1; s <= 3 && s <= B; ++s) {
-        const int on_cu = (int)((H * s + 255) / 256);
-        const float load = lg == 11 ? 1.32f * (on_cu / 2) + (on_cu & 1) : (float)on_cu;
         const float sum = s > 1 ? 3.5f + (float)s * (float)H * (float)(8 << lg) * 2e-7f : 0.f;
-        const float us = row_us * load * ((float)((B + s - 1) / s) + ends) + sum;
+        const float us = row_us * many_load(H, lg, s) * ((float)((B + s - 1) / s) + ends) + sum;
         if (s == 1 || us < least) { best = s; least = us; }
     }
     return best;
 }
 int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated)
 {
-    if (lg >= 11 && H > 128 && H <= 512) return rows_bwd_nsplit_many(B, H, lg, gated);
+    if (many_heads(H, lg)) return rows_bwd_nsplit_many(B, H, lg, gated);
     const bool wave_rows = lg == 10 && !gated;
     const int ngrp = lg >= 11 ? 1 : lg == 10 && gated ? 2 : 4;
     const int64_t units = lg == 8 ? (B + 1) / 2 : B;
@@ -1688,6 +1692,15 @@ int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated)
     if (s > most) s = most;
     if (s > 64) s = 64;
     return s < 1 ? 1 : (int)s;
+}
+// The other rule grows with B; of the estimate's choices s = 1 is faster at any B than an s that loads the fullest unit s times.
+int rows_bwd_room(int64_t B, int64_t H, int lg)
+{
+    if (!many_heads(H, lg)) return rows_bwd_nsplit(B, H, lg, true);
+    int room = 1;
+    for (int s = 2; s <= 3 && s <= B; ++s)
+        if (many_load(H, lg, s) < s * many_load(H, lg, 1)) room = s;
+    return room;
 }
 float rows_chain_scale(int lg)
 {

@@ -76,7 +76,8 @@ hipError_t pad_rows(const void* src, void* dst, size_t rows, size_t row_bytes, h
 hipError_t unpad_rows(const void* src, void* dst, size_t rows, size_t row_bytes, hipStream_t st);
 
 // ---- learned Butterfly extension (lbfly.hip): N = 256 .. 2048, fp16 / bf16 rows -----------------------------------
-// rows are split over this many workgroups per head in the backward pass; their partial sums need lbfly_partial_bytes
+// rows are split over this many workgroups per head in the backward pass; the partial sums of up to B rows need
+// lbfly_partial_bytes
 int lbfly_nsplit(int64_t B, int64_t H, int64_t N);
 size_t lbfly_partial_bytes(int64_t B, int64_t H, int64_t N);
 hipError_t lbfly_fwd(const void* u, const float* shat, const float* Af, const float* Ai, void* y, int64_t B, int64_t H,
@@ -146,6 +147,8 @@ hipError_t rows_conv(const void* in, const float2* kspec, void* out, bool conj, 
 // rows of a head are dealt to nsplit workgroups, dk and dD then point to partial buffers [nsplit][H][N] and [nsplit][H]
 // that sum_partials() adds up in share order.
 int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated);
+// the most shares that any call of up to B rows takes, gated or not: a workspace for B rows serves a smaller batch
+int rows_bwd_room(int64_t B, int64_t H, int lg);
 // With Problem::gate: the gated layer's backward pass (du and dg both given), dg = dy (ungated output).
 hipError_t rows_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, void* dg, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
@@ -160,6 +163,7 @@ hipError_t long_conv(const void* in, const float2* kspec, void* out, bool conj, 
 
 // du, dk and dD in one kernel; du (and with it kspec), dk and dD may be null.  nsplit > 1: as rows_bwd
 int long_bwd_nsplit(int64_t B, int64_t H);
+int long_bwd_room(int64_t B, int64_t H);         // as rows_bwd_room
 hipError_t long_bwd(const void* dy, const void* u, const float2* kspec, void* du, float* dk, float* dD, int nsplit,
                     const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 

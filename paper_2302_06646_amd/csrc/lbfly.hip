@@ -1061,22 +1061,31 @@ hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float*
 // Shares of a head's rows: the number that ends first, ceil(512 / H) at most, where 8 / T workgroups of T waves run on each of
 // 256 compute units.  A share's matrices and sums take as long as about six rows (8.5 us at N = 1024, a row 1.6), two of the
 // slower rows of N = 2048; more than one share is a second launch.
+static int64_t most_shares(int64_t B, int64_t H) { return (512 + H - 1) / H < B ? (512 + H - 1) / H : B; }
+static int64_t turns(int64_t workgroups, int64_t N)
+{
+    const int64_t resident = N == 2048 ? 256 : 256 * (1024 / N);
+    return (workgroups + resident - 1) / resident;
+}
 int lbfly_nsplit(int64_t B, int64_t H, int64_t N)
 {
-    const int64_t most = (512 + H - 1) / H < B ? (512 + H - 1) / H : B;
-    const int64_t resident = N == 2048 ? 256 : 256 * (1024 / N);
     const int64_t setup = N == 2048 ? 2 : 6, launch = N == 2048 ? 1 : 3;
     int64_t best = 1, best_t = -1;
-    for (int64_t n = 1; n <= most; ++n) {
-        const int64_t t = (n * H + resident - 1) / resident * ((B + n - 1) / n + setup) + (n > 1 ? launch : 0);
+    for (int64_t n = 1; n <= most_shares(B, H); ++n) {
+        const int64_t t = turns(n * H, N) * ((B + n - 1) / n + setup) + (n > 1 ? launch : 0);
         if (best_t < 0 || t < best_t) { best = n; best_t = t; }
     }
     return (int)best;
 }
 
+// For the most shares that any call of up to B rows takes: the number above need not grow with B, but a workspace for B rows
+// serves a smaller batch.  (One share ends before n shares of n times its turns, whatever B.)
 size_t lbfly_partial_bytes(int64_t B, int64_t H, int64_t N)
 {
-    return (size_t)lbfly_nsplit(B, H, N) * (size_t)H * ((size_t)(2 * N) + 6 * NBLK) * sizeof(float2);
+    int64_t room = 1;
+    for (int64_t n = 2; n <= most_shares(B, H); ++n)
+        if (turns(n * H, N) < n * turns(H, N)) room = n;
+    return (size_t)room * (size_t)H * ((size_t)(2 * N) + 6 * NBLK) * sizeof(float2);
 }
 
 hipError_t lbfly_fwd(const void* u, const float* shat, const float* Af, const float* Ai, void* y, int64_t B, int64_t H,

@@ -73,6 +73,27 @@ def test_workspace_holds_nothing_that_no_kernel_touches():
     assert lc.longconv2d_workspace_bytes(4, 8, 32, 32, lc.F32, False) >= 2 * 4 * 8 * 2048 * 4
 
 
+def test_a_workspace_for_a_batch_serves_every_smaller_one():
+    # a program keeps one workspace for its full batch and uses it for the last, smaller one too: no size falls as B grows.
+    # Head counts on both sides of the lines where the number of shares of a head's rows changes its rule.
+    heads = (1, 4, 16, 43, 64, 65, 96, 128, 129, 130, 160, 171, 172, 255, 256, 257, 340, 511, 512, 513, 1024)
+    batches = list(range(1, 40)) + [64, 69, 100, 128, 200, 333]
+
+    def grows(size, what):
+        sizes = [size(B) for B in batches]
+        assert min(sizes) > 0 and sizes == sorted(sizes), (what, sizes)
+
+    for H in heads:
+        for N in [1 << i for i in range(8, 18)]:
+            for io in (lc.F32, lc.F16):
+                for kind in (0, 1, 2):
+                    grows(lambda B: lc.longconv_workspace_bytes(B, H, N, io, kind), (N, H, io, kind))
+        for N1, N2 in ((16, 8), (32, 32), (32, 64), (64, 64), (64, 128)):
+            grows(lambda B: lc.longconv2d_workspace_bytes(B, H, N1, N2, lc.BF16, True), (N1, N2, H))
+        for N in (256, 512, 1024, 2048):
+            grows(lambda B: lc.longconv_lbfly_workspace_bytes(B, H, N, lc.BF16), ("learned", N, H))
+
+
 def test_plan_string_names_what_runs():
     # rows of N twisted points at N <= 4096, 32768 and 65536, pairs of 2N zero-padded ones elsewhere; fields a program may
     # look for stay in front
