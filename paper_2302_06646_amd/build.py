@@ -32,18 +32,22 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed:\n" + out)
 
 
-def build_binding(verbose: bool = True) -> str:
-    """Compile the host-side marshalling of the Python binding against torch's headers (no device code in it)."""
+def host_command(src: str, out: str) -> list:
+    """The host compiler's command for a Python extension against torch's headers (no device code in it)."""
     import sysconfig
 
     import torch
     t = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
-          "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-          "-I" + sysconfig.get_paths()["include"], f"-I{t}/include", f"-I{t}/include/torch/csrc/api/include",
-          f"-I{rocm}/include", os.path.join(CSRC, "binding.cpp"), "-o", NATIVE, f"-L{t}/lib", "-lc10", "-lc10_hip",
-          "-ltorch_cpu", "-ltorch_python"], verbose)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+            "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I" + sysconfig.get_paths()["include"], f"-I{t}/include", f"-I{t}/include/torch/csrc/api/include",
+            f"-I{rocm}/include", src, "-o", out, f"-L{t}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
+def build_binding(verbose: bool = True) -> str:
+    """Compile the host-side marshalling of the Python binding."""
+    _run(host_command(os.path.join(CSRC, "binding.cpp"), NATIVE), verbose)
     return NATIVE
 
 

@@ -10,6 +10,9 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <exception>
+#include <new>
+
 #include "../../include/longconv.h"
 
 namespace {
@@ -102,23 +105,36 @@ int io_code(c10::ScalarType dt)
     return dt == at::kFloat ? LONGCONV_F32 : dt == at::kHalf ? LONGCONV_F16 : dt == at::kBFloat16 ? LONGCONV_BF16 : -1;
 }
 
-// `body` fills the call in and returns its status through `call`; nothing that Python could see happens before `ok` is known
+struct WithoutGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
+// `body` fills the call in and returns its status through `call`; nothing that Python could see happens before `ok` is known.
+// What is thrown before the library is entered leaves the call to Python; what the library throws is a Python error, since work
+// may have been launched.
 template <class F>
 PyObject* guarded(PyObject* const* a, Py_ssize_t n, Py_ssize_t want, bool bound, F&& body)
 {
     if (n != want || !bound) Py_RETURN_NONE;
+    bool entered = false;
     try {
         Args A{a};
         int status = 0;
         const auto call = [&](auto&& f) {
             if (!A.ok) return;
-            PyThreadState* ts = PyEval_SaveThread();
+            entered = true;
+            const WithoutGil scope;
             status = f();
-            PyEval_RestoreThread(ts);
         };
         body(A, call);
         if (A.ok) return PyLong_FromLong(status);
+    } catch (const std::bad_alloc&) {
+        if (entered) return PyErr_NoMemory();
+    } catch (const std::exception& e) {
+        if (entered) return PyErr_Format(PyExc_RuntimeError, "longconv: %s", e.what());
     } catch (...) {
+        if (entered) return PyErr_Format(PyExc_RuntimeError, "longconv: unknown C++ exception");
     }
     PyErr_Clear();
     Py_RETURN_NONE;
