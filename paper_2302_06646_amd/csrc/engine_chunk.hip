@@ -516,7 +516,8 @@ chunk_bwd_kernel(const CBwdArgs<typename IO::T> q)
         uint32_t m = peaks[0];
 #pragma unroll
         for (int w = 1; w < L::NW; ++w) m = max(m, peaks[w]);
-        const int ea = __builtin_amdgcn_readfirstlane(mu::acc_exponent(m));
+        // (the inverse gains 2^8 on the way to z, which is fp16: A's largest component goes to 2^6 .. 2^7, so that z stays below 46342)
+        const int ea = __builtin_amdgcn_readfirstlane(mu::acc_exponent(m)) + 1;
         if (tid == 0) q.exps[at] = ea;
 #pragma unroll
         for (int j = 0; j < L::KB; ++j) {

@@ -174,9 +174,12 @@ __device__ __forceinline__ int acc_align(float2 (&acc)[NA][4], int& eref, int ep
 
 // The accumulator goes into dk's inverse transform as fp16, and as a sum over rows it has no bound of its own (rows with a
 // mean add up in the first bins: 0.8 N^2 / 4^SHIFT times the product of the means per row, 3300 at N = 4096).  So its
-// largest component is brought to 2^7 .. 2^8 by a power of two, which dk gets back in fp32: the inverse grows a
-// component by at most sqrt(2) N / 2^SHIFT <= 91, which stays below fp16's 65504.  This wave's largest component, as
-// the pattern of its magnitude, without a trip through LDS (a butterfly of __shfl_xor cost calls of one row 0.2 us):
+// largest component is brought to 2^7 .. 2^8 by a power of two, which dk gets back in fp32.  A value of the inverse is at most
+// sqrt(2) 2^8 times the product of its blocks' gains so far, and has to stay below 65504 as long as it is fp16: up to N = 4096
+// the whole inverse gains N / 2^(SHIFT - 1) <= 64 (23170); at 8192 and 16384 (SHIFT 7) the last block's sums stay fp32, and in
+// front of it there are N / 2^9 <= 32 (11586).  Chunks of 16384 points are rounded behind it, at 256 (92682): their kernel takes
+// one power of two more.  This wave's largest component, as the pattern of its magnitude, without a trip through LDS (a
+// butterfly of __shfl_xor cost calls of one row 0.2 us):
 __device__ __forceinline__ uint32_t wave_umax(uint32_t q)
 {
     q = max(q, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, 0xB1, 0xf, 0xf, true));       // quad_perm: lanes ^ 1

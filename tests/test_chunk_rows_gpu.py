@@ -63,6 +63,27 @@ def test_outputs_left_out(N, io, fuse):
                 assert np.all(np.isnan(got[other])), f"{other} was written"
 
 
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("N", [32768, 65536, 131072])
+def test_dk_of_one_tap(N, io):
+    # rows of one sample each: the spectrum's product is flat and dk a single tap, the largest number that a chunk's inverse
+    # transform can make of a spectrum of that size.  Magnitudes on both sides of a power of two, and
+    # lags that are odd and even multiples of a chunk's shares; the other taps hold nothing but rounding
+    lags = [0, 1, N // 32, N // 16, N // 8, N // 4, 3 * N // 8, N // 2, N - 1]
+    for size in (1.0, 1.1, 1.5, 1.999):
+        inp = wl.generate(_w(N=N, dtype=io), B=1, H=len(lags))
+        g = GpuRun(inp)
+        g.u.zero_()
+        g.dy.zero_()
+        g.u[0, :, 0] = 1.0
+        for h, lag in enumerate(lags):
+            g.dy[0, h, lag] = size
+        want = np.zeros(g.dk.shape)
+        want[range(len(lags)), lags] = float(g.dy[0, 0, 0])
+        _, dk, _ = g.bwd(du=False)
+        _compare({"dk": dk}, {"dk": want}, TOL[io], f"one tap N{N} {size}")
+
+
 @pytest.mark.parametrize("N", [32768, 65536])
 def test_dk_of_rows_with_a_mean(N):
     # the sums over rows grow as N^2 in the first bins, beyond fp16: each chunk's inverse transform has its own power of two.
