@@ -25,6 +25,12 @@ static __device__ uint4 g_chunk_tab[14 * C_UNITS * 64];             // R = 2, 4,
 template <int R>
 __host__ __device__ constexpr int chunk_tab() { return (R - 2) * C_UNITS * 64; }
 
+// s is rounded to fp16 divided by this, and the matrices over d_a give it back.  R equal samples N / R apart, all that there is of a
+// row, then stay finite up to 38370, 43470 and 23490 (R = 2, 4, 8); undivided R = 4 and 8 ended at 21730 and 11740.  More would
+// cost rows close to fp16's smallest normal number: with rows of 1e-4 (and kernels of 300) the error of y at N = 131072 is
+// 7.6e-4 either way, and 8.9e-4 divided by R.
+__host__ __device__ constexpr float staged_down(int R) { return R > 2 ? 2.f : 1.f; }
+
 template <int R>
 __global__ void fill_chunk_tab_kernel(uint4* tab)
 {
@@ -49,8 +55,8 @@ __global__ void fill_chunk_tab_kernel(uint4* tab)
         const int i = 4 * g + x;
         if (unit < C_B) {
             a(o, i, unit);
-            v.h[x] = (_Float16)re;
-            v.h[4 + x] = (_Float16)im;
+            v.h[x] = (_Float16)(re * staged_down(R));
+            v.h[4 + x] = (_Float16)(im * staged_down(R));
         } else if (unit < C_AI) {
             const int m = unit - C_B, de = (m % (2 * TE)) >> 1;
             const bool inv = m >= 2 * TE;
@@ -144,7 +150,7 @@ struct Run {
         i1 = i0 + each + (s < more);
     }
 };
-// exp(-2 pi i n (4 k1 + 1) / 4R) s
+// exp(-2 pi i n (4 k1 + 1) / 4R) s / staged_down
 template <int R>
 __device__ __forceinline__ void outer_factors(float2 (&f)[R], const float2* __restrict__ tw, int k1, float s)
 {
@@ -152,7 +158,7 @@ __device__ __forceinline__ void outer_factors(float2 (&f)[R], const float2* __re
 #pragma unroll
     for (int n = 0; n < R; ++n) {
         const float2 w = tw_full(tw, (uint32_t)((n * (4 * k1 + 1)) & (4 * R - 1)) << (TW_LOG2 - lg));
-        f[n] = make_float2(w.x * s, w.y * s);
+        f[n] = make_float2(w.x * s * (1.f / staged_down(R)), w.y * s * (1.f / staged_down(R)));
     }
 }
 // s of eight samples (words of two fp16 or bf16 numbers), as planes

@@ -63,6 +63,30 @@ def test_outputs_left_out(N, io, fuse):
                 assert np.all(np.isnan(got[other])), f"{other} was written"
 
 
+@pytest.mark.parametrize("N,amp", [(32768, 38000.0), (65536, 43000.0), (131072, 23000.0)])
+def test_large_samples_a_chunk_apart(N, amp):
+    # R fp16 samples N / R apart: a component of a chunk's sum over them is at most sum_n max(cos, sin)(2 pi n / 4R) <= 1.71, 3.02
+    # and 5.6 of them, and half of that (R > 2) has to fit fp16.  y of N = 32768 goes another way
+    H = 3
+    inp = wl.generate(_w(N=N, dtype=wl.F16), B=1, H=H)
+    g = GpuRun(inp)
+    for t, at in ((g.u, 100), (g.dy, 7)):
+        t.zero_()
+        t[..., at::16384] = amp
+    g.dy *= 2.0 ** -15                                       # dk stays below 2^18, du below 1
+    g.k.zero_()
+    g.k[:, 3], g.D[:] = 0.25, 0.125
+    u, dy = (t.cpu().numpy().astype(np.float64) for t in (g.u, g.dy))
+    k64, D64 = g.k.cpu().numpy().astype(np.float64), g.D.cpu().numpy().astype(np.float64)
+    got, want = {}, {}
+    if N > 32768:
+        got["y"], want["y"] = g.fwd(), oracle.longconv_fwd(u, k64, D64)
+    du, got["dk"], got["dD"] = g.bwd()
+    want["du"], want["dk"], want["dD"] = oracle.longconv_bwd(dy, u, k64, D64)
+    got["du"] = du
+    _compare(got, want, TOL[wl.F16], f"large samples N{N}", DD_TOL)
+
+
 @pytest.mark.parametrize("io", [wl.F16, wl.BF16])
 @pytest.mark.parametrize("N", [32768, 65536, 131072])
 def test_dk_of_one_tap(N, io):
