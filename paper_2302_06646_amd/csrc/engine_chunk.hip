@@ -30,6 +30,12 @@ __host__ __device__ constexpr int chunk_tab() { return (R - 2) * C_UNITS * 64; }
 // cost rows close to fp16's smallest normal number: with rows of 1e-4 (and kernels of 300) the error of y at N = 131072 is
 // 7.6e-4 either way, and 8.9e-4 divided by R.
 __host__ __device__ constexpr float staged_down(int R) { return R > 2 ? 2.f : 1.f; }
+// N points where the spectrum's scale has 1/2N: the factor of two that is missing stands in the inverse transform's last block,
+// over k_a.  At R = 8 it stands in the first, over d_e: the products with the spectrum are a sixteenth of the rows there, and
+// every rounding behind them meets fp16's smallest normal number the sooner (rows of 1e-4, error of y: 3.1e-3 with the factor in
+// the last block, 2.1e-3 in the first).  At R = 4 there is nothing to gain, and a row of 16 equal outputs 1024 apart would leave
+// fp16 in front of the last block from 16400 on, not 32800.
+__host__ __device__ constexpr float inverse_up(int R) { return R == 8 ? 1.f : 2.f; }
 
 template <int R>
 __global__ void fill_chunk_tab_kernel(uint4* tab)
@@ -65,8 +71,8 @@ __global__ void fill_chunk_tab_kernel(uint4* tab)
             put(x, m & 1, inv);
         } else if (unit < C_S) {
             a(i, o, 0);
-            re *= 2.0;                               // N points where the spectrum's scale has 1/2N
-            im *= 2.0;
+            re *= inverse_up(R);
+            im *= inverse_up(R);
             put(x, unit - C_AI, true);
         } else {
             const int e = (unit - C_S) * 64 + lane, t = e >> 2;
@@ -126,10 +132,16 @@ struct CK {
     }
 };
 constexpr int SHARED = L::N_LDS * 64 + L::TC * 4;       // matrices over d_b and d_e, the tiles' factors
+template <int R>
 __device__ __forceinline__ void load_chunk_shared(uint4* sm, const uint4* __restrict__ ltab, const uint4* __restrict__ ctab, int tid)
 {
     const uint4* p = ltab + (size_t)(tab_offset<14>() + L::U_LDS) * 64;
-    for (int i = tid; i < L::N_LDS * 64; i += L::NT) sm[i] = i < 4 * TE * 64 ? ctab[C_B * 64 + i] : p[i];
+    for (int i = tid; i < L::N_LDS * 64; i += L::NT) {
+        H8P x;
+        x.w = i < 4 * TE * 64 ? ctab[C_B * 64 + i] : p[i];
+        if (inverse_up(R) != 2.f && i >= L::U_EI * 64) x.v *= (_Float16)(2.f / inverse_up(R));
+        sm[i] = x.w;
+    }
     for (int i = tid; i < L::TC * 4; i += L::NT) sm[L::N_LDS * 64 + i] = ctab[C_S * 64 + i];
 }
 constexpr size_t chunk_lds(int nal) { return sizeof(_Float16) * L::EX + 16 * SHARED + 1024 * nal * L::NW; }
@@ -339,7 +351,7 @@ chunk_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restric
     _Float16* mine = ex + piece_of<L>(tid);
     CK<true, 0> K;
     K.load(ltab, ctab, wave, lane, nullptr);
-    load_chunk_shared(shared, ltab, ctab, tid);
+    load_chunk_shared<R>(shared, ltab, ctab, tid);
     const uint4 *mats = shared + lane, *factors = shared + L::N_LDS * 64 + 8 * wave * 4 + g;
     Places<L> P;
     P.make(wave, lane);
@@ -421,7 +433,7 @@ chunk_bwd_kernel(const CBwdArgs<typename IO::T> q)
     _Float16* mine = ex + piece_of<L>(tid);
     CK<true, CNAL> K;
     K.load(q.ltab, ctab, wave, lane, shared + SHARED);
-    load_chunk_shared(shared, q.ltab, ctab, tid);
+    load_chunk_shared<R>(shared, q.ltab, ctab, tid);
     const uint4 *mats = shared + lane, *factors = shared + L::N_LDS * 64 + 8 * wave * 4 + g;
     Places<L> P;
     P.make(wave, lane);
@@ -581,7 +593,7 @@ chunk_kspec_kernel(const float* __restrict__ k, const float* __restrict__ D, con
     const uint4* ctab = chtab + chunk_tab<R>() + (size_t)me.k1 * C_UNITS * 64;
     CK<false, 0> K;
     K.load(ltab, ctab, wave, lane, nullptr);
-    load_chunk_shared(shared, ltab, ctab, tid);
+    load_chunk_shared<R>(shared, ltab, ctab, tid);
     const uint4* mats = shared + lane;
     Places<L> P;
     P.make(wave, lane);

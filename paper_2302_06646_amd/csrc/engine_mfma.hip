@@ -550,7 +550,7 @@ void mfma_fill_plan(Plan& pl)
     }
     // rows of 32768 and more samples: N twisted points per row, in one kernel at 32768 (a row fits one compute unit), in chunks of
     // 16384 points above it, without a pass A kernel (switch fuse_pass_a = 0: pairs and pass A, for comparison)
-    // (N points instead of 2N: the factor of two is in the last block of the inverse; a chunk's z is fp16 behind it)
+    // (N points instead of 2N: the factor of two is in a block of the inverse; a chunk's z is fp16 behind it)
     pl.fuse_a = pl.order.coop_lg == COOP_MAX_LOG2 && pl.log2R >= 1 && pl.log2R <= 3 && opt.fuse_pass_a;
     pl.row1 = pl.fuse_a && pl.log2R == 1;
     if (chunk_plan(pl)) {

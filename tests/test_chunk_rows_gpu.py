@@ -87,6 +87,22 @@ def test_large_samples_a_chunk_apart(N, amp):
     _compare(got, want, TOL[wl.F16], f"large samples N{N}", DD_TOL)
 
 
+@pytest.mark.parametrize("N", [65536, 131072])
+def test_small_fp16_rows(N):
+    # rows of a few times fp16's smallest normal number (6.1e-5), which fp16 rows may have: the usual bound
+    inp = wl.generate(_w(N=N, dtype=wl.F16), B=2, H=2)
+    g = GpuRun(inp)
+    g.u *= 1.5e-4
+    g.dy *= 1.5e-4
+    u, dy = (t.cpu().numpy().astype(np.float64) for t in (g.u, g.dy))
+    k64, D64 = inp.k.astype(np.float64), inp.D.astype(np.float64)
+    y = g.fwd()
+    du, dk, dD = g.bwd()
+    rdu, rdk, rdD = oracle.longconv_bwd(dy, u, k64, D64)
+    _compare({"y": y, "du": du, "dk": dk, "dD": dD}, {"y": oracle.longconv_fwd(u, k64, D64), "du": rdu, "dk": rdk, "dD": rdD},
+             TOL[wl.F16], f"small rows N{N}", DD_TOL)
+
+
 @pytest.mark.parametrize("io", [wl.F16, wl.BF16])
 @pytest.mark.parametrize("N", [32768, 65536, 131072])
 def test_dk_of_one_tap(N, io):
