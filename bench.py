@@ -145,8 +145,8 @@ def run_workload(key, steps, warmup, lc, torch):
     w = wl.WORKLOADS[key]
     S = Sets(w, lc, torch)
     plan = lc.longconv_plan_string(w.N, w.dtype)
-    # du, dk, dD of a call come from one kernel
-    one_kernel_bwd = "kernel=wave" in plan or ("runs=rows(" in plan and "backward=one" in plan)
+    # du, dk, dD of a call come from one kernel (fp32: timed as the two calls that a program may make all the same)
+    one_kernel_bwd = "engine=mfma" in plan and "backward=one" in plan
     gb = group_bytes(w)
     groups = ["kspec", "fwd"] + (["bwd"] if one_kernel_bwd else ["bwd_dk", "bwd_du"])
 

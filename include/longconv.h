@@ -268,8 +268,16 @@ const char* longconv_status_string(int status);
 /* Text of the last HIP error seen by the calling thread ("" if none). */
 const char* longconv_last_hip_error(void);
 
-/* Human-readable description of the plan chosen for (N, io): engine, factorisation
- * of 2N, number of passes.  Returns a pointer to a thread-local buffer. */
+/* Human-readable description of the plan that calls for (N, io) run with the present options, as fields "name=value"
+ * (thread-local buffer):
+ *   engine       mfma-fp16 or valu-fp32
+ *   L            points per transform: N "of rows" (one transform per row) or 2N "of pairs" (of two batch rows, zero padded)
+ *   outer_radix  R and inner = L / R: a transform runs as R pieces of `inner` points each; passes = 3 where R > 1 (the
+ *                outer digit, the pieces, the outer digit back), else 1
+ *   digits       the factors of L, outermost first
+ *   kernel       wave (a few waves per row) or chained (a workgroup per row or piece); absent for the other kernels
+ *   backward     one: du, dk and dD asked for in one call come from one kernel; dk,du: du and the others from two;
+ *                dk(rows,Rx2^14),du: the same, dk and dD from rows in R pieces of 2^14 points */
 const char* longconv_plan_string(int64_t N, int io);
 
 #ifdef __cplusplus

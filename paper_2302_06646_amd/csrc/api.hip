@@ -879,37 +879,26 @@ const char* longconv_plan_string(int64_t N, int io)
     static thread_local char buf[256];
     if (check_shape(1, 1, N, io) != LONGCONV_OK) { snprintf(buf, sizeof(buf), "invalid"); return buf; }
     const Plan pl = make_plan(N, io);
-    // what the convolutions transform: N twisted points of each row, or 2N zero-padded points of a row pair
-    const bool wave = pl.engine == ENGINE_MFMA && pl.order.wave_lg;
-    const bool chunks = pl.engine == ENGINE_MFMA && chunk_plan(pl);
-    const bool rows = wave || pl.row1 || (chunks && pl.log2R == 2);
-    const int lgL = pl.log2L - rows, lgL2 = wave ? lgL : pl.log2L2, lgR = lgL - lgL2;
+    const bool mfma = pl.engine == ENGINE_MFMA, wave = mfma && pl.order.wave_lg, lng = mfma && pl.order.long_lg;
+    const bool chunks = mfma && chunk_plan(pl);
+    // what the convolutions transform: N twisted points of each row, or 2N zero-padded points of a row pair; rows above 32768
+    // samples in chunks of 16384 points
+    const bool rows = wave || lng || chunks || (mfma && pl.row1);
+    const int lgL = pl.log2L - rows, lgL2 = chunks ? lgL - pl.log2R : rows ? lgL : pl.log2L2, lgR = lgL - lgL2;
     int bits[20], nd = 0;
     if (lgR) bits[nd++] = lgR;
-    if (wave) {
-        bits[nd++] = 4; bits[nd++] = 4;
-        if (lgL > 8) bits[nd++] = lgL - 8;
+    if (wave || lng || chunks) {
+        for (int left = lgL2; left > 0; left -= 4) bits[nd++] = left < 4 ? left : 4;
     } else {
         for (int i = pl.log2R != 0; i < pl.order.ndig; ++i) bits[nd++] = pl.order.bits[i];
     }
     int n = snprintf(buf, sizeof(buf), "engine=%s L=2^%d of %s outer_radix=%d inner=2^%d passes=%d digits=",
-                     pl.engine == ENGINE_VALU ? "valu-fp32" : "mfma-fp16", lgL, rows ? "rows" : "pairs", 1 << lgR, lgL2,
-                     lgR ? 3 : 1);
+                     mfma ? "mfma-fp16" : "valu-fp32", lgL, rows ? "rows" : "pairs", 1 << lgR, lgL2, lgR ? 3 : 1);
     for (int i = 0; i < nd; ++i) n += snprintf(buf + n, sizeof(buf) - n, "%s%d", i ? "x" : "", 1 << bits[i]);
     if (wave) n += snprintf(buf + n, sizeof(buf) - n, " kernel=wave");
-    if (pl.order.coop_lg || pl.order.long_lg) n += snprintf(buf + n, sizeof(buf) - n, " kernel=chained");
-    if (pl.order.long_lg) {
-        // the fields in front are what they were when rows of these lengths went in pairs, for whoever looks for them there;
-        // what runs follows
-        snprintf(buf + n, sizeof(buf) - n, " backward=dk,du runs=rows(L=2^%d,digits=16x16x16x%d,backward=%s)", pl.order.long_lg,
-                 1 << (pl.order.long_lg - 12), pl.fuse_bwd ? "one" : "dk,du");
-        return buf;
-    }
-    if (pl.engine == ENGINE_VALU || pl.fuse_bwd) snprintf(buf + n, sizeof(buf) - n, " backward=one");
-    else if (chunks)                                      // (the fields in front as above)
-        snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,%dx2^14),du runs=rows(L=2^%d,digits=%dx16x16x16x4,backward=%s)",
-                 2 << pl.log2R, pl.log2L - 1, 1 << pl.log2R, options().fuse_bwd ? "one" : "dk,du");
-    else if (pl.row1) snprintf(buf + n, sizeof(buf) - n, " backward=dk(pairs,4x2^14),du runs=rows(dk=2x2^14)");
+    if (mfma && !wave && (lng || pl.order.coop_lg)) n += snprintf(buf + n, sizeof(buf) - n, " kernel=chained");
+    if (!mfma || pl.fuse_bwd || (chunks && options().fuse_bwd)) snprintf(buf + n, sizeof(buf) - n, " backward=one");
+    else if (mfma && chunk_dk_plan(pl)) snprintf(buf + n, sizeof(buf) - n, " backward=dk(rows,%dx2^14),du", 1 << pl.log2R);
     else snprintf(buf + n, sizeof(buf) - n, " backward=dk,du");
     return buf;
 }

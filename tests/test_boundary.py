@@ -95,30 +95,35 @@ def test_a_workspace_for_a_batch_serves_every_smaller_one():
 
 
 def test_plan_string_names_what_runs():
-    # rows of N twisted points at N <= 4096, 32768 and 65536, pairs of 2N zero-padded ones elsewhere; fields a program may
-    # look for stay in front
-    want = {
-        (256, lc.F16): ("L=2^8 of rows", "outer_radix=1", "passes=1", "digits=16x16 ", "kernel=wave", "backward=one"),
-        (1024, lc.BF16): ("L=2^10 of rows", "inner=2^10", "passes=1", "digits=16x16x4 ", "kernel=wave", "backward=one"),
-        (4096, lc.F16): ("L=2^12 of rows", "digits=16x16x16 ", "passes=1", "kernel=wave", "backward=one"),
-        (16384, lc.F16): ("L=2^15 of pairs", "passes=1", "digits=16x16x16x8 ", "kernel=chained", "backward=dk,du"),
-        (32768, lc.BF16): ("L=2^15 of rows", "outer_radix=1", "passes=1", "digits=16x16x16x8 ", "backward=dk(pairs,4x2^14),du"),
-        (65536, lc.F16): ("L=2^16 of rows", "outer_radix=2", "inner=2^15", "passes=3", "digits=2x16x16x16x8 ",
-                          "backward=dk(pairs,8x2^14),du"),
-        (131072, lc.F16): ("L=2^18 of pairs", "outer_radix=8", "inner=2^15", "passes=3", "digits=8x16x16x16x8 ",
-                           "backward=dk(pairs,16x2^14),du"),
-        (1024, lc.F32): ("L=2^11 of pairs", "passes=1", "digits=8x8x8x4 ", "backward=one"),
-        (32768, lc.F32): ("L=2^16 of pairs", "outer_radix=4", "inner=2^14", "passes=3", "backward=one"),
-    }
+    # fp16 and bf16: rows of N twisted points at every length, in chunks of 2^14 above 32768 (dk of 32768 as well); fp32: pairs of
+    # 2N zero-padded points.  The whole string, so that no field of another plan can stand beside the right ones
+    def mfma(L, R, digits, kernel, backward):
+        return (f"engine=mfma-fp16 L=2^{L} of rows outer_radix={R} inner=2^{L - R.bit_length() + 1} passes={3 if R > 1 else 1} "
+                f"digits={digits} kernel={kernel} backward={backward}")
+
+    want = {256: mfma(8, 1, "16x16", "wave", "one"), 512: mfma(9, 1, "16x16x2", "wave", "one"),
+            1024: mfma(10, 1, "16x16x4", "wave", "one"), 2048: mfma(11, 1, "16x16x8", "wave", "one"),
+            4096: mfma(12, 1, "16x16x16", "wave", "one"), 8192: mfma(13, 1, "16x16x16x2", "chained", "one"),
+            16384: mfma(14, 1, "16x16x16x4", "chained", "one"),
+            32768: mfma(15, 1, "16x16x16x8", "chained", "dk(rows,2x2^14),du"),
+            65536: mfma(16, 4, "4x16x16x16x4", "chained", "one"), 131072: mfma(17, 8, "8x16x16x16x4", "chained", "one")}
+    apart = {16384: "dk,du", 32768: "dk(rows,2x2^14),du", 65536: "dk(rows,4x2^14),du", 131072: "dk(rows,8x2^14),du"}
     try:
-        for (N, io), parts in want.items():
-            s = lc.longconv_plan_string(N, io)
-            for part in parts:
-                assert part in s, (N, io, part, s)
-        lc.longconv_set_option("fuse_pass_a", 0)         # pass A as a kernel of its own: pairs again
-        assert "L=2^16 of pairs outer_radix=2" in lc.longconv_plan_string(32768, lc.F16)
-        lc.longconv_set_option("fuse_bwd", 0)
-        assert "backward=dk,du" in lc.longconv_plan_string(1024, lc.F16)
+        for N, s in want.items():
+            assert lc.longconv_plan_string(N, lc.F16) == lc.longconv_plan_string(N, lc.BF16) == s
+        for N, parts in {1024: ("L=2^11 of pairs", "passes=1", "digits=8x8x8x4 ", "backward=one"),
+                         32768: ("L=2^16 of pairs", "outer_radix=4", "inner=2^14", "passes=3", "backward=one")}.items():
+            s = lc.longconv_plan_string(N, lc.F32)
+            assert s.startswith("engine=valu-fp32 ") and all(part in s for part in parts), s
+        lc.longconv_set_option("fuse_bwd", 0)            # du by a kernel of its own
+        for N in want:
+            backward = lc.longconv_plan_string(N, lc.F16).split(" backward=")[1]
+            assert backward == apart.get(N, "dk,du"), (N, backward)
+        lc.longconv_set_option("fuse_pass_a", 0)         # pass A as a kernel of its own: pairs, in chunks of 2^15
+        for N, R in ((32768, 2), (65536, 4), (131072, 8)):
+            s = lc.longconv_plan_string(N, lc.F16)
+            assert f"L=2^{N.bit_length()} of pairs outer_radix={R} inner=2^15 passes=3 digits={R}x16x16x16x8 " in s
+            assert s.endswith("kernel=chained backward=dk,du")
     finally:
         for name, value in lc.OPTION_DEFAULTS.items():
             lc.longconv_set_option(name, value)
