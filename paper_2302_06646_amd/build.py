@@ -3,13 +3,15 @@ from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblongconv.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))      # this interpreter's ABI, and no other's
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -34,19 +36,30 @@ def _run(cmd, verbose):
 
 def host_command(src: str, out: str) -> list:
     """The host compiler's command for a Python extension against torch's headers (no device code in it)."""
-    import sysconfig
-
     import torch
     t = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
-    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+    return [*os.environ.get("CXX", "g++").split(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
             "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             "-I" + sysconfig.get_paths()["include"], f"-I{t}/include", f"-I{t}/include/torch/csrc/api/include",
             f"-I{rocm}/include", src, "-o", out, f"-L{t}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
-def build_binding(verbose: bool = True) -> str:
-    """Compile the host-side marshalling of the Python binding."""
+def build_binding(verbose: bool = True):
+    """Compile the host-side marshalling of the Python binding.  The library does not need it, nor does the package, which
+    marshals in Python without it: where there is nothing to build it with, None."""
+    cxx, python_h = os.environ.get("CXX", "g++").split()[0], os.path.join(sysconfig.get_paths()["include"], "Python.h")
+    try:
+        import torch
+        missing = [p for p in (python_h, os.path.join(os.path.dirname(torch.__file__), "include", "ATen", "core", "Tensor.h"))
+                   if not os.path.exists(p)]
+    except ImportError:
+        missing = ["torch"]
+    if not shutil.which(cxx):
+        missing.append(cxx)
+    if missing:
+        print("binding's native part not built, missing:", ", ".join(missing))
+        return None
     _run(host_command(os.path.join(CSRC, "binding.cpp"), NATIVE), verbose)
     return NATIVE
 

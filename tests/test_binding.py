@@ -4,7 +4,9 @@ import subprocess
 import sys
 
 import pytest
+import torch
 
+import paper_2302_06646_amd as lc
 from paper_2302_06646_amd import build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -47,3 +49,28 @@ print("alive", sum(range(10)))
 """)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.split() == ["MemoryError"] * 3 + ["alive", "45"], r.stdout
+
+
+def test_calls_are_served_without_the_native_part(monkeypatch):
+    # a library built by itself, or for another interpreter: the Python way looks at every call
+    monkeypatch.setattr(lc, "_bound", None)
+    monkeypatch.setitem(sys.modules, "paper_2302_06646_amd._native", None)
+    monkeypatch.delattr(lc, "_native", raising=False)
+    k = torch.zeros(2, 256)
+    with pytest.warns(RuntimeWarning, match="native part"):
+        with pytest.raises(lc.LongconvError, match="k must be a contiguous device tensor"):
+            lc.longconv_kreg_fwd(k, None, k, 1, 0.5)
+    with pytest.raises(lc.LongconvError, match="u must be a contiguous device tensor"):       # (and warns once)
+        lc.longconv_fwd(torch.zeros(1, 2, 256), k, torch.zeros(2), torch.zeros(1, 2, 256), torch.zeros(1))
+
+
+def test_the_library_builds_without_a_host_compiler(monkeypatch, tmp_path, capsys):
+    monkeypatch.setenv("CXX", "/nonexistent/c++")
+    monkeypatch.setattr(build, "NATIVE", str(tmp_path / "_native.so"))
+    assert build.build_binding() is None
+    assert "/nonexistent/c++" in capsys.readouterr().out
+
+
+def test_the_native_part_is_of_this_interpreter():
+    import importlib.machinery
+    assert build.NATIVE.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])
