@@ -145,6 +145,29 @@ def test_full_size_of_the_timed_shape():
     assert np.all(np.isfinite(g["y"])) and np.all(np.isfinite(g["dAf"])) and np.all(np.isfinite(g["dshat"]))
 
 
+# The forward kernel's pipeline: more rows than the device can hold workgroups (2048 threads a compute unit, 2N / 4 a workgroup),
+# so that each takes several, and batches that do not divide what one takes, so that runs cross from head to head.  Then few
+# heads, whose rows the backward kernel takes in uneven shares (6, 5, 4 and 2 of them).
+@pytest.mark.parametrize("N,io,B,H", [(256, wl.BF16, 7, 1400), (512, wl.F16, 5, 1100), (1024, wl.F16, 7, 500), (2048, wl.BF16, 5, 330),
+                                      (256, wl.F16, 11, 100), (512, wl.BF16, 9, 100), (1024, wl.BF16, 13, 60), (2048, wl.F16, 7, 100)])
+def test_runs_of_rows_and_uneven_shares(N, io, B, H):
+    if H > 100:
+        assert B * H > 256 * (2048 // (N // 2))
+    u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=4)
+    g = _run(u_s, dy_s, k, D, Af32, Ai32, io)
+    for name, x in g.items():
+        assert np.all(np.isfinite(x)), name
+    heads = sorted({0, H - 1, *np.random.default_rng(N + H).choice(H, size=14, replace=False).tolist()})
+    shat = lbfly.spectrum(k[heads], D[heads])
+    ry = lbfly.lbfly_fwd(u_v[:, heads], shat, Af[heads], Ai[heads])
+    rdu, rdshat, rdAf, rdAi = lbfly.lbfly_bwd(dy_v[:, heads], u_v[:, heads], shat, Af[heads], Ai[heads])
+    label = f"lbfly runs N={N} B={B} H={H}"
+    _compare({"y": g["y"][:, heads], "du": g["du"][:, heads], "dshat": _ri(g["dshat"][heads])},
+             {"y": ry, "du": rdu, "dshat": _ri(rdshat)}, TOL[io], label)
+    _check_blocks(g["dAf"][heads], rdAf, N, TOL[io], label + " dAf")
+    _check_blocks(g["dAi"][heads], rdAi, N, TOL[io], label + " dAi")
+
+
 def test_optional_outputs_repeatability_and_error_codes():
     N, io, B, H = 512, wl.F16, 4, 3
     u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=2)

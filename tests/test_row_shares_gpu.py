@@ -14,13 +14,25 @@ from oracle import gated
 pytestmark = pytest.mark.gpu
 
 
-# three shares of 5 and 6 rows, three of 11 and 10; three shares of more than one turn; two shares; none (few rows; the edges)
-@pytest.mark.parametrize("B,H,N,io", [(16, 130, 2048, wl.BF16), (32, 130, 4096, wl.F16), (25, 340, 2048, wl.F16),
-                                      (25, 260, 4096, wl.BF16), (1, 129, 2048, wl.BF16), (2, 512, 2048, wl.F16),
-                                      (2, 513, 4096, wl.F16), (17, 128, 2048, wl.F16)])
-def test_shares_of_many_heads(B, H, N, io):
+def _shares_taken(g):
+    """How many shares of a head's rows the backward call takes: with the spectrum at hand it writes nothing to its workspace but
+    the shares' dk and dD, [shares][H][N + 1] fp32 numbers (one share: nothing)."""
+    ks = g.kspec()
+    g.ws.fill_(0xFF)
+    g.bwd(kspec=ks)
+    blocks = int((g.ws.view(-1, 256) != 0xFF).any(dim=1).sum())
+    return max(1, round(blocks * 256 / (g.H * (g.N + 1) * 4)))
+
+
+# three shares of 5 and 6 rows, three of 11 and 10; three shares of more than one turn; two shares; one (few rows; the edges of
+# the rule, and on its other side four)
+@pytest.mark.parametrize("B,H,N,io,shares", [(16, 130, 2048, wl.BF16, 3), (32, 130, 4096, wl.F16, 3), (32, 340, 2048, wl.F16, 3),
+                                             (25, 260, 4096, wl.BF16, 2), (1, 129, 2048, wl.BF16, 1), (2, 512, 2048, wl.F16, 1),
+                                             (2, 513, 4096, wl.F16, 1), (17, 128, 2048, wl.F16, 4)])
+def test_shares_of_many_heads(B, H, N, io, shares):
     inp = wl.generate(dataclasses.replace(wl.WORKLOADS["2"], N=N, dtype=io), B=B, H=H)
     g = GpuRun(inp)
+    assert _shares_taken(g) == shares
     hs = sample_heads(H, B, seed=N + H)
     k64, D64 = inp.k.astype(np.float64)[hs], inp.D.astype(np.float64)[hs]
     du, dk, dD = g.bwd()
@@ -30,8 +42,10 @@ def test_shares_of_many_heads(B, H, N, io):
     _compare({"du": du[:, hs], "dk": dk[hs], "dD": dD[hs]}, {"du": rdu, "dk": rdk, "dD": rdD}, TOL[io], f"shares N{N}", DD_TOL)
 
 
-def test_shares_of_gated_rows():
-    B, H, N, io = 16, 130, 2048, wl.BF16
+# three shares of a head's rows: all at once, and in more than one turn
+@pytest.mark.parametrize("B,H", [(16, 130), (32, 340)])
+def test_shares_of_gated_rows(B, H):
+    N, io = 2048, wl.BF16
     inp, g_s, g_v = tg._inputs(N, io, B, H, 5)
     _, du, dk, dD, dg = tg._run(inp, g_s)
     hs = sample_heads(H, B, seed=5)
