@@ -326,10 +326,10 @@ __device__ __forceinline__ void store_planes(_Float16* dst, const _Float16* mine
 }
 
 // -------------------------------------------------------------------------------------------------------------------
-// Convolution (forward; CONJ: du) of a chunk of a head's rows share, share + nshare, ...: z planes of row b to
-// ws[((h B + b) R + k_1) 2 L].  Bound by issue and by the row's way in: about 9 us a row and
-// chunk against 6.7 for a row of 16384 samples.  B=8, H=128, N=65536 fp16, whole call: 257 us as two chunks of 32768 points with
-// the first digit summed in fp16, 250 here, 215 with the next row asked for ahead.
+// Convolution (forward; CONJ: du) of a chunk of a run of rows: z planes of row b to ws[((h B + b) R + k_1) 2 L].  Bound by issue
+// and by the row's way in: about 9 us a row and chunk against 6.7 for a row of 16384 samples.  B=8, H=128, N=65536 fp16, whole call:
+// 257 us as two chunks of 32768 points with the first digit summed in fp16, 250 here, 215 with the next row asked for ahead.
+// (Eight registers are spilled at R = 8.)
 // -------------------------------------------------------------------------------------------------------------------
 template <class IO, int R, bool CONJ>
 __global__ void __launch_bounds__(L::NT) __attribute__((amdgpu_waves_per_eu(2)))
@@ -396,7 +396,7 @@ chunk_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restric
 // (ws_du may be null), at the end those of the inverse transform of A 2^-e to ws_A[(share H + h) R + k_1] with e behind them
 // (exps), and the chunk's part of dD (piece n_1 = k_1 of the rows) to dD_part at the same index.  There are no
 // registers to ask for the next row ahead: with 32 of them, spills made B=8, H=128, N=65536 430 us instead of 386 (as eight chunks
-// per pair of rows for dk, and du by itself: 690).
+// per pair of rows for dk, and du by itself: 690).  As it is, 2 are spilled at R = 4 and 17 to 22 at R = 8.
 // -------------------------------------------------------------------------------------------------------------------
 template <class T>
 struct CBwdArgs {

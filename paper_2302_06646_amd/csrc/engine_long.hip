@@ -101,7 +101,8 @@ __global__ void fill_long_tab_kernel(uint4* tab)
 // -------------------------------------------------------------------------------------------------------------------
 // Convolution (forward; CONJ: du) of all rows.  Persistent workgroups with even runs of consecutive (head, row) items, two
 // barriers per row.  Bound by issue: about 75 instructions per 256 points and row at some six cycles each with two waves per SIMD.
-// B=8, H=256, N=16384 fp16: 83 us as pairs of rows in 32768-point transforms, 54 here; B=64, H=128, N=8192: 129, 91.
+// B=8, H=256, N=16384 fp16: 83 us as pairs of rows in 32768-point transforms, 54 here; B=64, H=128, N=8192: 129, 91.  (The gate's
+// pieces cost the kernel of N = 8192 spilled registers, 14 in bf16 and 26 in fp16.)
 // -------------------------------------------------------------------------------------------------------------------
 template <int LG, class IO, bool CONJ, bool GATE>
 __global__ void __launch_bounds__(LR<LG>::NT) __attribute__((amdgpu_waves_per_eu(2)))
@@ -262,10 +263,13 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
 //     [phase 3 of row t-1's du, phase 1 of u_t]  [phase 2 of u_t; du stored, dy_t in]  [phase 1 of dy_t]
 //     [phase 2 of dy_t, A, inverse half for du; u_(t+1) in]
 // dD needs both rows at once: u is read a second time, from cache, when dy arrives.  DU = false: dk and dD alone.
-// Bound by issue like the convolution, and by registers: the sums alone take a quarter of them.  With spills in the loop the
-// reloads wait behind the row in flight: B=8, H=256, N=16384 fp16 167 us, 112 with the matrices of three tiles per wave and their
-// factors in LDS, 107 with the rows' addresses kept scalar (as pairs, dk in two walks and du by itself: 197).  N = 8192 takes four
-// tiles per wave (LB): with eight, B=64, H=128 289 us, with four 167 (as pairs 325).
+// Bound by memory as much as by issue: B=8, H=256, N=16384 fp16 moves up to 510 MB in 111 us (4.6 TB/s; a large copy 5.1) for
+// 235 MB of rows and gradients, with vector instructions in half of the cycles and matrix instructions in a quarter.  What is read
+// beyond the rows is the spectrum for every row again (117 MB), u's second reading (67) and spilled registers: the sums alone take
+// a quarter of them, and 17 to 24 have no place.  With more of them in the loop the reloads wait behind the row in flight: 167 us,
+// 112 with the matrices of three tiles per wave and their factors in LDS, 107 with the rows' addresses kept scalar (as pairs, dk in
+// two walks and du by itself: 197).  N = 8192 takes four tiles per wave (LB) and spills nothing: with eight, B=64, H=128 289 us,
+// with four 167 (as pairs 325).
 // -------------------------------------------------------------------------------------------------------------------
 template <class T>
 struct LBwdArgs {

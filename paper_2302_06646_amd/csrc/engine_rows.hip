@@ -1280,7 +1280,7 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
 // The same for rows that one wave owns (N = 256: two rows at a time; N = 512; N = 1024: four tiles), NWV independent waves
 // per workgroup.  N = 1024 as a row pipeline (rbwd_kernel, two groups of two waves), kernel time in us, there -> here,
 // bf16: B=1, H=768 16.5 -> 8.1; B=5, H=64 12.0 -> 9.7; B=16, H=256 20.3 -> 14.4; B=16, H=768 37.4 -> 30.2; B=64, H=1024
-// 137 -> 110.  (Gated it spills 50 registers and more, and is 1.5 times as slow as the pipeline.)
+// 137 -> 110.  (N = 1024 spills 6 to 14 registers; gated it would be 50 and more, and 1.5 times as slow as the pipeline.)
 template <int LG, class IO, bool DU, bool GATE, int NWV>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 rbwd1_kernel(const BwdArgs<typename IO::T> q)

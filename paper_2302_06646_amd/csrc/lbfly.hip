@@ -402,9 +402,10 @@ __device__ __forceinline__ void put_out(_Float16* tile, const f4& v, int lane)
 // barriers per row:
 //     [inverse blocks of row b-1, forward blocks of row b]  barrier  [last blocks and spectrum of row b, rows in and out]
 // (a wave's tile of the exchange buffer is its own in the first part, so the two rows need one buffer).  Bound by issue: 11
-// matrix and 83 vector instructions per 256 points and row; two rows per barrier were no faster.  The form it replaced took
-// every block through LDS with its own addresses, twiddle loads and barrier: B=16, H=768, N=1024 bf16 77 us, this one 36
-// (53 before the quarters were hashed, 41 with a workgroup per 8 rows of one head).
+// matrix and 83 vector instructions per 256 points and row, 112 with what a workgroup spends on its matrices (B=16, H=768,
+// N=1024); two rows per barrier were no faster.  The form it replaced took every block through LDS with its own addresses,
+// twiddle loads and barrier: that shape in bf16 77 us, this one 36 (53 before the quarters were hashed, 41 with a workgroup per 8
+// rows of one head).  N = 256 spills 5 registers, N = 2048 7.
 // -------------------------------------------------------------------------------------------------------------------
 template <int LG, class IO>
 __global__ void __launch_bounds__(64 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(4)))

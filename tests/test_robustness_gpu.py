@@ -167,9 +167,8 @@ def test_persistent_workgroups_ragged_item_count(N, B, H, io):
 @pytest.mark.parametrize("io", [wl.F16, wl.BF16])
 @pytest.mark.parametrize("N", [65536, 131072])
 def test_pass_a_inside_the_inner_kernel(N, io):
-    """N = 65536, 131072 (outer radix 4, 8): the convolutions, the spectrum and (N = 65536) dk take pass A while
-    staging their rows.  Odd batch (the last pair has one row), both half dtypes, against the oracle and against
-    the separate pass A."""
+    """N = 65536, 131072 (4 and 8 chunks of 16384 points): every kernel sums the first digit while it stages its rows.
+    Odd batch, both half dtypes, against the oracle and against pairs of rows behind a separate pass A."""
     from gpu_harness import GpuRun, TOL, check_full
     inp = wl.generate(_w("4a", N=N, dtype=io), B=3, H=1 if N > 65536 else 2)
     check_full(inp, label=f"pass A fused, io={wl.DTYPE_NAMES[io]}")
@@ -185,7 +184,7 @@ def test_pass_a_inside_the_inner_kernel(N, io):
     assert wl.rel_l2(dk, dk2) <= tol and wl.rel_l2(dD, dD2) <= tol
     assert not np.array_equal(y, y2)          # the two paths round differently: the switch did take effect
     if N == 65536:
-        assert not np.array_equal(dk, dk2)    # dk: outer radix 8 from the rows against radix 4 from a workspace
+        assert not np.array_equal(dk, dk2)    # dk: chunks of 16384 points from the rows against 32768 from a workspace
 
 
 @pytest.mark.parametrize("io", [wl.F16, wl.BF16])
@@ -231,9 +230,10 @@ def test_few_heads_batch_dealt_to_several_workgroups(N, B, H, io):
 @pytest.mark.parametrize("io", [wl.F16, wl.BF16])
 @pytest.mark.parametrize("N", [32768, 65536, 131072])
 def test_single_row_batch_uses_the_hermitian_symmetry_of_its_chunks(N, io):
-    """B = 1 in the multi-pass split: the row is real, so chunk R - k1 of the outer split is the complex conjugate
-    of chunk k1; the inner kernels compute the chunks up to R/2 only and pass C fills in the rest.  Against the
-    oracle, and against the plan with the separate pass A, which computes every chunk."""
+    """B = 1 at the lengths whose dk (and, above 32768, whose convolutions) go in chunks.  A real row's spectrum is
+    Hermitian: its twisted transform has no second half to leave out, so all chunks are computed, and the row alone must
+    come out as it does in the plan with the separate pass A, which transforms 2N points of a pair with a row of zeros.
+    Against the oracle, and against that plan."""
     from gpu_harness import GpuRun, TOL, check_full
     inp = wl.generate(_w("4a", N=N, dtype=io), B=1, H=3 if N < 131072 else 2)
     check_full(inp, label=f"single row N={N} io={wl.DTYPE_NAMES[io]}")
