@@ -54,18 +54,35 @@ __device__ __forceinline__ float2 cmulc(float2 a, float2 b)
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 
+// Rows that a kernel writes and nothing on the device reads again soon (y, du, dg) are stored with the nt hint: they leave the
+// L2 first, so that rows still to be read, spectra and spilled registers stay, and the lines are written back while the kernel
+// runs, not at its end.  Loads with the hint were slower (several loads of a wave share a line).  Whole steps, plain stores
+// and nt: B=64, H=1024, N=256 bf16 67.9 -> 58.9 us, B=16, H=768, N=1024 68.0 -> 64.1, B=8, H=256, N=16384 fp16 173 -> 162;
+// the gradients in fp32, spectra and workspaces gained nothing and are stored plainly.
+constexpr int BUF_ONCE = 2;               // the hint as a buffer instruction's auxiliary operand
+template <class V>
+__device__ __forceinline__ void put_once(V* p, const V& v)
+{
+    static_assert(sizeof(V) == 16 || sizeof(V) == 4, "pieces of 4 or 16 bytes");
+    typedef uint32_t w4 __attribute__((ext_vector_type(4)));
+    if constexpr (sizeof(V) == 16) __builtin_nontemporal_store(__builtin_bit_cast(w4, v), reinterpret_cast<w4*>(p));
+    else __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, v), reinterpret_cast<uint32_t*>(p));
+}
+
 // ---------------------------------------------------------------------------------
-// I/O element types.  ld/st convert to/from float with round-to-nearest-even.
+// I/O element types.  ld/st convert to/from float with round-to-nearest-even; once: a row's sample, see put_once.
 // ---------------------------------------------------------------------------------
 struct IoF32 {
     using T = float;
     static __device__ __forceinline__ float ld(const T* p, size_t i) { return p[i]; }
     static __device__ __forceinline__ void st(T* p, size_t i, float v) { p[i] = v; }
+    static __device__ __forceinline__ void once(T* p, size_t i, float v) { put_once(p + i, v); }
 };
 struct IoF16 {
     using T = __half;
     static __device__ __forceinline__ float ld(const T* p, size_t i) { return __half2float(p[i]); }
     static __device__ __forceinline__ void st(T* p, size_t i, float v) { p[i] = __float2half_rn(v); }
+    static __device__ __forceinline__ void once(T* p, size_t i, float v) { st(p, i, v); }
 };
 struct IoBF16 {
     using T = uint16_t;
@@ -80,6 +97,7 @@ struct IoBF16 {
         b += 0x7fffu + ((b >> 16) & 1u);
         p[i] = (uint16_t)(b >> 16);
     }
+    static __device__ __forceinline__ void once(T* p, size_t i, float v) { st(p, i, v); }
 };
 
 // Complex workspace element types used between passes.

@@ -731,7 +731,7 @@ chunk_rows_kernel(const _Float16* __restrict__ ws, typename IO::T* __restrict__ 
             if (gate) { a *= io_half<IO>(gw[q], 0); b *= io_half<IO>(gw[q], 1); }
             w[q] = pack_io<IO>(ldexpf(a, e2), ldexpf(b, e2));
         }
-        *reinterpret_cast<u4w*>(out + o + (size_t)n * L::N) = w;
+        put_once(reinterpret_cast<u4w*>(out + o + (size_t)n * L::N), w);
     }
 }
 // the same for dk, fp32, over the shares of a head; the first thread of a head adds up dD

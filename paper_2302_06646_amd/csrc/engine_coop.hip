@@ -652,7 +652,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
                     for (int m = 0; m < 4; ++m) wa[m] = out_rescaled<IsBf<IO>::v>(wa[m], ea);
                 }
             }
-            store_words<4>(out + o + n, wa);
+            put_once(reinterpret_cast<uint4*>(out + o + n), make_uint4(wa[0], wa[1], wa[2], wa[3]));
         }
     };
 

@@ -223,7 +223,7 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
     const auto store = [&]() {
         u4w* p = reinterpret_cast<u4w*>(out + row_off(bo, ho, H, L::N)) + tid;
 #pragma unroll
-        for (int i = 0; i < PC; ++i) p[i * L::NT] = *reinterpret_cast<const u4w*>(mine + i * L::STEP);
+        for (int i = 0; i < PC; ++i) put_once(p + i * L::NT, *reinterpret_cast<const u4w*>(mine + i * L::STEP));
         if (++bo == B) { bo = 0; ++ho; }
     };
     const auto exponent = [&](int t) {
@@ -376,7 +376,7 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
     };
     const auto store = [&]() {
 #pragma unroll
-        for (int i = 0; i < PC; ++i) uniform(po, i * L::NT)[(unsigned)tid] = *reinterpret_cast<const u4w*>(mine + i * L::STEP);
+        for (int i = 0; i < PC; ++i) put_once(uniform(po, i * L::NT) + (unsigned)tid, *reinterpret_cast<const u4w*>(mine + i * L::STEP));
         po += step;
     };
     // the other three parts of row t

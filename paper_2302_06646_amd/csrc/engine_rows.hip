@@ -203,7 +203,7 @@ __device__ __forceinline__ uint32_t buf_load(rsrc_t r, uint32_t off)
 }
 __device__ __forceinline__ void buf_store(rsrc_t r, uint32_t off, uint32_t v)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, BUF_ONCE);
 }
 
 // Sample n of the row -> element of memory.  pad = 0: itself.  pad = N2 (2-D layer): rows of N2 elements stand for
@@ -599,7 +599,7 @@ rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
             phase1_ops<LG, IO, M::scaled>(w, e0, 0, lane, op);
             phase1<LG>(op, K, xw + bt, zr, zi);
         }
-        __builtin_amdgcn_raw_buffer_store_b128(q, make_rsrc(po.p, M::whole || t >= 3 ? row_bytes : 0u), (int)foff, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(q, make_rsrc(po.p, M::whole || t >= 3 ? row_bytes : 0u), (int)foff, 0, BUF_ONCE);
         if (M::whole || t >= 3) po.next(B, step, wrap);
         SCHED_FENCE();
         if (do2) phase2_read<LG>(xp + bs, m2);
@@ -681,7 +681,7 @@ __device__ __forceinline__ void store_words(rsrc_t d, const uint32_t (&off)[4], 
     for (int r = 0; r < 4; ++r) {
         if constexpr (NP == 2) {
             const u2v v = {w[0][r], w[1][r]};
-            __builtin_amdgcn_raw_buffer_store_b64(v, d, (int)off[r], 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(v, d, (int)off[r], 0, BUF_ONCE);
         } else {
             buf_store(d, off[r], w[0][r]);
         }
@@ -1134,11 +1134,11 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
         if (DU) {
             const uint32_t bytes = M::whole || (t >= 3 && t - 3 < nmine) ? row_bytes : 0u;
             u4v o = *reinterpret_cast<const u4v*>(stg + ((t - 1) & 1) * C::SW + sf);
-            __builtin_amdgcn_raw_buffer_store_b128(o, make_rsrc(pdu, bytes), (int)foff, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(o, make_rsrc(pdu, bytes), (int)foff, 0, BUF_ONCE);
             if (M::whole || t >= 3) pdu += step;
             if (GATE) {
                 o = *reinterpret_cast<const u4v*>(stg + (2 + ((t - 1) & 1)) * C::SW + sf);
-                __builtin_amdgcn_raw_buffer_store_b128(o, make_rsrc(pdg, bytes), (int)foff, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(o, make_rsrc(pdg, bytes), (int)foff, 0, BUF_ONCE);
                 if (M::whole || t >= 3) pdg += step;
             }
         }

@@ -532,10 +532,10 @@ __device__ __forceinline__ void store_pair(const float2 (&x)[Fft<LG>::P], typena
     constexpr int P = Fft<LG>::P, T = Fft<LG>::T;
     if constexpr (!CHUNK) {
 #pragma unroll
-        for (int d = 0; d < P / 2; ++d) IO::st(ra, tid + d * T, x[d].x);
+        for (int d = 0; d < P / 2; ++d) IO::once(ra, tid + d * T, x[d].x);
         if (has_b) {
 #pragma unroll
-            for (int d = 0; d < P / 2; ++d) IO::st(rb, tid + d * T, x[d].y);
+            for (int d = 0; d < P / 2; ++d) IO::once(rb, tid + d * T, x[d].y);
         }
     } else {
 #pragma unroll

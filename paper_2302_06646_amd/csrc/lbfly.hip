@@ -249,7 +249,7 @@ __device__ __forceinline__ void store_row(const h2* s, typename IO::T* row, int 
             v[q] = (float)lo.c[q][0] * scale;
             v[4 + q] = (float)hi.c[q][0] * scale;
         }
-        p[i] = Cv<IO>::out(v);
+        put_once(p + i, Cv<IO>::out(v));
     }
 }
 
@@ -506,7 +506,7 @@ lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ s
             inverse();
             forward();
             __syncthreads();
-            *yp = row_out<LG>(outb, tid);
+            put_once(yp, row_out<LG>(outb, tid));
             yp += step;
             middle();
             next_row_in(b);
@@ -514,7 +514,7 @@ lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ s
         }
         inverse();
         __syncthreads();
-        *yp = row_out<LG>(outb, tid);
+        put_once(yp, row_out<LG>(outb, tid));
         __syncthreads();                                                // (the next head's constants go where the rows were)
     }
 }
@@ -739,7 +739,7 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
         first();
         __syncthreads();
         if (du) {
-            *dp = row_out<LG>(outb, tid);
+            put_once(dp, row_out<LG>(outb, tid));
             dp += step;
         }
         middle();
@@ -748,7 +748,7 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
     }
     last();
     __syncthreads();
-    if (du) *dp = row_out<LG>(outb, tid);
+    if (du) put_once(dp, row_out<LG>(outb, tid));
 
     const size_t at = (size_t)sp * H + h;
     if (out.shat) {
