@@ -977,8 +977,10 @@ __device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2
 // GATE (gated layer): dy is replaced by dz = dy g (rounded to the I/O dtype) as the rows arrive, dD sums dy g u in fp32,
 // and U's own inverse of U K gives z for dg = dy z.
 // -------------------------------------------------------------------------------------
-template <int LG, bool GATE> struct BwdCfg {
-    static constexpr int NGRP = LG == 10 ? 2 : 1, NWV = NGRP * RC<LG>::NWR;
+template <int LG, bool GATE, bool WIDE> struct BwdCfg {
+    // WIDE: twice the groups, for launches that give a compute unit one workgroup; N = 4096 has no LDS for them
+    static constexpr bool can_widen = LG < 12;
+    static constexpr int NGRP = (LG == 10 ? 2 : 1) * (WIDE ? 2 : 1), NWV = NGRP * RC<LG>::NWR;
     // LDS words of a group: two exchange buffers, two rows on the way in and two on the way out for each tensor
     static constexpr int GW = 4 * RC<LG>::XW + (GATE ? 8 : 6) * RC<LG>::SW;
     static constexpr size_t lds = ((size_t)NGRP * GW + 2 * 8 * 2 + 8 + 8) * 4;
@@ -1013,12 +1015,12 @@ __device__ __forceinline__ float gate_words(uint32_t (&d)[4], const uint32_t (&g
 
 // Three transforms per row against the convolution's two, at half its waves per SIMD (accumulators).
 // Gated step B=7, H=193, N=2048: five kernels 93 us, this one 41 us.
-template <int LG, class IO, bool DU, bool GATE>
-__global__ void __launch_bounds__((BwdCfg<LG, GATE>::NWV * 64)) __attribute__((amdgpu_waves_per_eu(2)))
+template <int LG, class IO, bool DU, bool GATE, bool WIDE>
+__global__ void __launch_bounds__((BwdCfg<LG, GATE, WIDE>::NWV * 64)) __attribute__((amdgpu_waves_per_eu(2)))
 rbwd_kernel(const BwdArgs<typename IO::T> q)
 {
     using C = RC<LG>;
-    using Q = BwdCfg<LG, GATE>;
+    using Q = BwdCfg<LG, GATE, WIDE>;
     static_assert(DU || !GATE, "the gated form comes with du");
     constexpr bool BF = IsBf<IO>::v;
     constexpr int NGRP = Q::NGRP, NWR = C::NWR;
@@ -1596,6 +1598,21 @@ hipError_t rbwd1_run(const BwdArgs<typename IO::T>& a, hipStream_t st)
     hipLaunchKernelGGL((rbwd1_kernel<LG, IO, DU, GATE, NWV>), dim3((unsigned)(a.H * a.nsplit)), dim3(64 * NWV), 0, st, a);
     return hipGetLastError();
 }
+template <int LG, class IO, bool DU, bool GATE, bool WIDE>
+hipError_t rbwd_launch(const BwdArgs<typename IO::T>& a, hipStream_t st)
+{
+    using Q = BwdCfg<LG, GATE, WIDE>;
+    const auto kern = rbwd_kernel<LG, IO, DU, GATE, WIDE>;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q::lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.H * a.nsplit)), dim3(Q::NWV * 64), Q::lds, st, a);
+    return hipGetLastError();
+}
+// Whether the workgroups of a backward call (N = 2048, gated N = 1024) take twice the groups of waves: where each has a compute
+// unit to itself, with one wave per SIMD, which issues an instruction every 8 cycles (two: every 5.6).  Whole steps, bf16: N=2048
+// B=8, H=200 29.3 -> 28.0 us, B=7, H=193 gated 38.7 -> 37.2; N=1024 gated B=16, H=256 36.7 -> 34.2.  One row a group gives it
+// nothing to do but the longer ends (N=2048 B=2, H=200 21.7 -> 22.1).
+bool wide_bwd(int64_t workgroups, int64_t rows, int groups) { return workgroups <= compute_units() && rows > 2 * groups; }
 template <int LG, class IO, bool DU, bool GATE>
 hipError_t rbwd_run(const BwdArgs<typename IO::T>& a, hipStream_t st)
 {
@@ -1608,12 +1625,10 @@ hipError_t rbwd_run(const BwdArgs<typename IO::T>& a, hipStream_t st)
         if (each == 2) return rbwd1_run<LG, IO, DU, GATE, 2>(a, st);
         return rbwd1_run<LG, IO, DU, GATE, 4>(a, st);
     } else {
-        using Q = BwdCfg<LG, GATE>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rbwd_kernel<LG, IO, DU, GATE>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)Q::lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((rbwd_kernel<LG, IO, DU, GATE>), dim3((unsigned)(a.H * a.nsplit)), dim3(Q::NWV * 64), Q::lds, st, a);
-        return hipGetLastError();
+        using Q = BwdCfg<LG, GATE, false>;
+        if constexpr (Q::can_widen)
+            if (wide_bwd(a.H * a.nsplit, (a.B + a.nsplit - 1) / a.nsplit, Q::NGRP)) return rbwd_launch<LG, IO, DU, GATE, true>(a, st);
+        return rbwd_launch<LG, IO, DU, GATE, false>(a, st);
     }
 }
 template <int LG, class IO>
@@ -1680,7 +1695,12 @@ static int rows_bwd_nsplit_many(int64_t B, int64_t H, int lg, bool gated)
 }
 int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated)
 {
-    if (many_heads(H, lg)) return rows_bwd_nsplit_many(B, H, lg, gated);
+    if (many_heads(H, lg)) {
+        // N = 2048: instead of two shares on one compute unit, two groups of waves in one workgroup (wide_bwd) and no sum of
+        // partial results: B=24, H=256 bf16 step 60.5 -> 57.2 us, gated 78.9 -> 73.8; B=64 120.1 -> 118.4
+        const int s = rows_bwd_nsplit_many(B, H, lg, gated);
+        return lg == 11 && H <= compute_units() && s == 2 ? 1 : s;
+    }
     const bool wave_rows = lg == 10 && !gated;
     const int ngrp = lg >= 11 ? 1 : lg == 10 && gated ? 2 : 4;
     const int64_t units = lg == 8 ? (B + 1) / 2 : B;

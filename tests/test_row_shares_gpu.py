@@ -54,3 +54,22 @@ def test_shares_of_gated_rows(B, H):
     for name, a, b in (("du", du[:, hs], rdu), ("dk", dk[hs], rdk), ("dg", dg[:, hs], rdg), ("dD", dD[hs], rdD)):
         e = wl.rel_l2(a, b)
         assert np.isfinite(e) and e <= (1e-5 if name == "dD" else 3e-3), (name, e)
+
+
+# twice the groups of waves in workgroups that have a compute unit to themselves (N = 2048 and gated 1024): uneven and even shares
+# of a group, the fewest rows that take them and one less, one and more heads than half the device
+@pytest.mark.parametrize("N,B,H,io", [(2048, 2, 200, wl.BF16), (2048, 3, 200, wl.F16), (2048, 5, 256, wl.BF16), (2048, 24, 256, wl.F16),
+                                      (2048, 3, 1, wl.BF16), (2048, 5, 257, wl.BF16), (1024, 4, 200, wl.BF16), (1024, 5, 200, wl.F16),
+                                      (1024, 11, 256, wl.BF16), (1024, 11, 3, wl.F16)])
+def test_groups_of_waves(N, B, H, io):
+    inp, g_s, g_v = tg._inputs(N, io, B, H, 7)
+    _, du, dk, dD, dg = tg._run(inp, g_s)
+    hs = sample_heads(H, B, seed=7)
+    k64, D64 = inp.k.astype(np.float64)[hs], inp.D.astype(np.float64)[hs]
+    rdu, rdk, rdD, rdg = gated.gated_bwd(inp.dy[:, hs], g_v[:, hs], inp.u[:, hs], k64, D64)
+    for name, a, b in (("du", du[:, hs], rdu), ("dk", dk[hs], rdk), ("dg", dg[:, hs], rdg), ("dD", dD[hs], rdD)):
+        e = wl.rel_l2(a, b)
+        assert np.isfinite(e) and e <= (1e-5 if name == "dD" else 3e-3), (name, e)
+    du, dk, dD = GpuRun(inp).bwd()
+    rdu, rdk, rdD = oracle.longconv_bwd(inp.dy[:, hs], inp.u[:, hs], k64, D64)
+    _compare({"du": du[:, hs], "dk": dk[hs], "dD": dD[hs]}, {"du": rdu, "dk": rdk, "dD": rdD}, TOL[io], f"groups N{N}", DD_TOL)
