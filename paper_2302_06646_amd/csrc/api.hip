@@ -27,7 +27,7 @@ __global__ void fill_tw_kernel(float2* tw)
     tw[j] = make_float2((float)c, (float)s);
 }
 
-static __device__ float2 g_stw[STW_TOTAL];
+static __device__ float2 g_stw[STW_ALL];
 
 __global__ void fill_stw_kernel(float2* stw)
 {
@@ -84,6 +84,8 @@ static hipError_t get_tables(Tables* out, hipStream_t st, bool sync_device, void
         e = note(chunk_fill_tables(&g_tab[dev].chtab, st), "fill chunk tables");
         if (e != hipSuccess) return e;
         e = note(coop_fill_tables(&g_tab[dev].ctab, st), "fill coop tables");
+        if (e != hipSuccess) return e;
+        e = note(valu_fill_twist(q, st), "fill twists");
         if (e != hipSuccess) return e;
         e = note(valu_fill_tables(&g_tab[dev].ftw, st), "fill fp32 tables");
         if (e != hipSuccess) return e;
@@ -150,6 +152,14 @@ Plan make_plan(int64_t N, int io)
     pl.log2L2 = pl.log2L < cap ? pl.log2L : cap;
     pl.log2R = pl.log2L - pl.log2L2;
     if (pl.log2R > 5) { pl.log2R = 5; pl.log2L2 = pl.log2L - 5; }   // not reachable for supported N
+    // fp32 rows whose N points fit where a pair's 2N would (or, unless a split is forced, N = 16384: twice as fast as in chunks);
+    // N <= 1024 stays with pairs: a wave or two per row would leave them nothing to hide behind
+    if (pl.engine == ENGINE_VALU && io == LONGCONV_F32 && pl.log2L > VALU_ROWS_MIN_LOG2 &&
+        (pl.log2R == 0 || (cap == VALU_INNER_MAX_LOG2 && pl.log2L == VALU_ROWS_MAX_LOG2 + 1))) {
+        pl.vrow = pl.log2L - 1;
+        pl.log2R = 0;
+        pl.log2L2 = pl.log2L;
+    }
     if (pl.engine == ENGINE_VALU) valu_fill_plan(pl);
     else mfma_fill_plan(pl);
     return pl;
@@ -182,7 +192,7 @@ struct WsLayout {
 // to `nsplit` workgroups, whose partial dk and dD are then summed in a fixed order.
 static int dk_nsplit(int64_t B, int64_t H, const Plan& pl, bool gated)
 {
-    if (pl.engine == ENGINE_VALU) return valu_bwd_nsplit(H, (int)((B + 1) / 2), pl);
+    if (pl.engine == ENGINE_VALU) return valu_bwd_nsplit(B, H, pl);
     if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_nsplit(B, H, pl.order.wave_lg, gated);
     if (pl.engine == ENGINE_MFMA && pl.order.long_lg) return long_bwd_nsplit(B, H);
     return 1;
@@ -227,7 +237,7 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     const size_t shares = backward ? dk_room(B, H, pl) : 1;
     w.zbuf = off;
     if (backward && pl.order.coop_lg && outer_a) off += up256((size_t)H * L * sizeof(__half2));
-    if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(H, (int)shares, pl));
+    if (backward && pl.engine == ENGINE_VALU) off += up256(valu_zbuf_bytes(B, H, (int)shares, pl));
     // partial dk rows, or (fp32 engine, multi-pass) partial sets of pass C's complex chunks
     w.dkpart = off; if (shares > 1) off += up256(shares * H * (pl.log2R ? 2 * L : L / 2) * sizeof(float));
     w.ddpart = off; if (shares > 1) off += up256(shares * H * sizeof(float));
@@ -277,6 +287,7 @@ static hipError_t run_kspec(const float* k, const float* D, float2* kspec, float
         }
         return coop_kspec(k, (const __half2*)kscratch, D, hscale, kspec, H, N, pl, tb, st);
     }
+    if (pl.engine == ENGINE_VALU && pl.vrow) return valu_rows_kspec(k, D, kspec, H, pl, tb, st);
     if (pl.engine == ENGINE_VALU) return valu_kspec(k, D, kspec, H, N, nullptr, pl.kscale, tb, pl.log2R, pl.log2L2, st);
     // staged matrix-core kernel: fp32 spectrum in that kernel's digit-reversed order
     const int lg2 = pl.log2L < VALU_INNER_MAX_LOG2 ? pl.log2L : VALU_INNER_MAX_LOG2;
@@ -883,7 +894,7 @@ const char* longconv_plan_string(int64_t N, int io)
     const bool chunks = mfma && chunk_plan(pl);
     // what the convolutions transform: N twisted points of each row, or 2N zero-padded points of a row pair; rows above 32768
     // samples in chunks of 16384 points
-    const bool rows = wave || lng || chunks || (mfma && pl.row1);
+    const bool rows = wave || lng || chunks || (mfma && pl.row1) || pl.vrow;
     const int lgL = pl.log2L - rows, lgL2 = chunks ? lgL - pl.log2R : rows ? lgL : pl.log2L2, lgR = lgL - lgL2;
     int bits[20], nd = 0;
     if (lgR) bits[nd++] = lgR;

@@ -23,6 +23,11 @@ constexpr int TW_L = 1 << TW_LOG2;
 // entries, so a wave's loads are unit-stride runs.
 constexpr int STW_TOTAL = (1 << 16) - 32;
 __host__ __device__ constexpr int stw_offset(int lgLs) { return (1 << lgLs) - 32; }
+// Behind them, for single fp32 rows of N = 2^lg samples (lg = 11 .. 14) with P points per thread: w_4N^((4k + 1) q) at entry
+// k N / P + q, the first stage's twiddles and the twist in one (engine_valu.hip).
+constexpr int TWIST_MIN = 11, TWIST_MAX = 14;
+__host__ __device__ constexpr int twist_offset(int lg) { return STW_TOTAL + (1 << lg) - (1 << TWIST_MIN); }
+constexpr int STW_ALL = twist_offset(TWIST_MAX + 1);
 
 struct Tables {
     const float2* tw;    // g_tw
@@ -201,6 +206,7 @@ struct Plan {
     int fuse_a;      // rows of 32768 and more samples go without a pass A kernel: row1, or in chunks (engine_chunk.hip)
     int row1;        // fuse_a at N = 32768: spectrum and convolutions run one transform of N twisted points per row
     int fuse_bwd;    // du, dk and dD of one call come from one kernel (single pass, matrix cores)
+    int vrow;        // fp32 engine: log2 N of rows that run one transform of N twisted points each (0: pairs of rows)
 };
 
 Plan make_plan(int64_t N, int io);

@@ -1,5 +1,5 @@
-// fp32 engine: the whole FFT convolution of one row pair on the vector ALUs.  It serves fp32 I/O (where fp16
-// matrix-core operands cannot meet the accuracy bound) and, for every dtype, the spectrum of plans whose consumer is
+// fp32 engine: the whole FFT convolution of one row pair, or (N = 2048 .. 16384) of one row, on the vector ALUs.  It serves fp32
+// I/O (where fp16 matrix-core operands cannot meet the accuracy bound) and, for every dtype, the spectrum of plans whose consumer is
 // the staged matrix-core kernel.
 //
 // Transform convention (paper Eq. 2 with the sequence zero padded to L = 2N): mixed radix, in place.  A stage of
@@ -47,6 +47,7 @@ constexpr int span_log2(int LG, int s)
 __host__ __device__ constexpr int phys(int p) { return p + (p >> 3); }
 // whether the backward kernel parks the transform of u in memory (see fbwd_kernel)
 constexpr bool valu_parks(int LG) { return LG >= 14; }
+constexpr bool row_parks(int LG) { return points_log2(LG) == 4; }        // (frow_bwd_kernel)
 constexpr size_t lds_bytes(int LG) { return sizeof(float2) * ((size_t(1) << LG) * 9 / 8); }
 
 // ---- butterflies in registers -------------------------------------------------------------------------------------
@@ -133,6 +134,37 @@ __device__ __forceinline__ void dft_half_out(float2* x)
     for (int n = 0; n < R / 2; ++n) x[n] = cadd(e[n], rot32<true>(o[n], n * (32 / R)));
 }
 
+// exp(-2 pi i d / 4R), d < R: the twist's share of a butterfly of R points (single rows)
+template <int R>
+__device__ __forceinline__ float2 twist_unit(int d)
+{
+    static_assert(R == 8 || R == 16, "the points of a thread");
+    constexpr float C[17] = {1.f, 0.99518472667219689f, 0.98078528040323045f, 0.95694033573220887f, 0.92387953251128676f, 0.88192126434835503f,
+                             0.83146961230254524f, 0.77301045336273696f, 0.70710678118654752f, 0.63439328416364550f, 0.55557023301960222f,
+                             0.47139673682599764f, 0.38268343236508977f, 0.29028467725446237f, 0.19509032201612827f, 0.098017140329560602f, 0.f};
+    const int m = d * (16 / R);
+    return make_float2(C[m], -C[16 - m]);
+}
+
+// The compiler keeps what it can prove unchanged: without this it would hold every twiddle and spectrum value of a
+// transform in registers from one transform (and one turn of the pair loop) to the next, and spill.
+// (The pointer itself stays visible: hidden, its loads become flat ones, which every wait for LDS waits for as well.)
+template <class T>
+__device__ __forceinline__ T* fresh(T* p)
+{
+    size_t zero = 0;
+    asm volatile("" : "+s"(zero));
+    return p + zero;
+}
+// p[i + lane], i the same for all lanes
+template <class T>
+__device__ __forceinline__ T* at(T* p, size_t i, int lane) { return p + i + (unsigned)lane; }
+__device__ __forceinline__ int fresh(int v)      // the same for addresses derived from the thread's number
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // ---- stage twiddles -----------------------------------------------------------------------------------------------
 // The table holds w_{2^l}^q, q < 2^(l-1), at entry 2^(l-1) + q.  w_Ls^(k q) for a radix-r stage needs q < Ls / r: the
 // powers 1, 2, 4, 8 are unit-stride runs of the tables of l = lgs, lgs-1, lgs-2, lgs-3, the others products of them.
@@ -142,7 +174,7 @@ struct StageTw {
     __device__ __forceinline__ void load(const float2* __restrict__ ft, int lgs, int q)
     {
 #pragma unroll
-        for (int i = 0; i < BITS; ++i) w[i] = ft[(1 << (lgs - 1 - i)) + q];
+        for (int i = 0; i < BITS; ++i) w[i] = *at(ft, 1 << (lgs - 1 - i), q);
     }
     // x[k] *= w^k (INV: conj), as w^(k & ~3) and then w^(k & 3): as many multiplications as forming all the powers, and
     // only six of them live
@@ -180,7 +212,7 @@ struct StageTwAll {
     {
         const int lgM = lgs - BITS;
 #pragma unroll
-        for (int k = 1; k < (1 << BITS); ++k) w[k - 1] = stw[stw_offset(lgM + 4) + ((k << (4 - BITS)) << lgM) + q];
+        for (int k = 1; k < (1 << BITS); ++k) w[k - 1] = *at(stw, stw_offset(lgM + 4) + ((k << (4 - BITS)) << lgM), q);
     }
     template <bool INV>
     __device__ __forceinline__ void apply(float2* x) const
@@ -190,30 +222,70 @@ struct StageTwAll {
     }
 };
 
-// The compiler keeps what it can prove unchanged: without this it would hold every twiddle and spectrum value of a
-// transform in registers from one transform (and one turn of the pair loop) to the next, and spill.
-template <class T>
-__device__ __forceinline__ T* fresh(T* p)
-{
-    asm volatile("" : "+s"(p));
-    return p;
-}
-__device__ __forceinline__ int fresh(int v)      // the same for addresses derived from the thread's number
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
+// Single rows, with tables in two factors, x[k] *= w^(k & ~3) w^(k & 3), each from a table: half the loads and registers of one
+// factor for every power, 12 multiplications more at radix 16.  TWIST: stage 0 of N = 2^lgs samples, with the twist of its
+// points' q, w_4N^((4k + 1) q), which rides on the factors of the groups of four.
+template <int BITS, bool TWIST>
+struct StageTwPairs {
+    static constexpr int R = 1 << BITS, G0 = TWIST ? 0 : 1, NG = R / 4 > G0 ? R / 4 - G0 : 1;
+    float2 f[NG], w[3];
+    __device__ __forceinline__ void load(const float2* __restrict__ stw, int lgs, int q)
+    {
+        const int lgM = lgs - BITS;
+#pragma unroll
+        for (int g = G0; g < R / 4; ++g)
+            f[g - G0] = *at(stw, TWIST ? twist_offset(lgs) + ((4 * g) << lgM) : stw_offset(lgM + 4) + (((4 * g) << (4 - BITS)) << lgM), q);
+#pragma unroll
+        for (int k = 1; k < 4 && k < R; ++k) w[k - 1] = *at(stw, stw_offset(lgM + 4) + ((k << (4 - BITS)) << lgM), q);
+    }
+    template <bool INV>
+    __device__ __forceinline__ void apply(float2* x) const
+    {
+        const auto mul = [](float2 v, float2 t) { return INV ? cmulc(v, t) : cmul(v, t); };
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            if (k / 4 >= G0) x[k] = mul(x[k], f[k / 4 >= G0 ? k / 4 - G0 : 0]);
+            if (k & 3) x[k] = mul(x[k], w[(k & 3) - 1]);
+        }
+    }
+};
+// the twist's stage with every power from its table
+template <int BITS>
+struct StageTwTwist {
+    float2 w[1 << BITS];
+    __device__ __forceinline__ void load(const float2* __restrict__ stw, int lg, int q)
+    {
+#pragma unroll
+        for (int k = 0; k < (1 << BITS); ++k) w[k] = *at(stw, twist_offset(lg) + (k << (lg - BITS)), q);
+    }
+    template <bool INV>
+    __device__ __forceinline__ void apply(float2* x) const
+    {
+#pragma unroll
+        for (int k = 0; k < (1 << BITS); ++k) x[k] = INV ? cmulc(x[k], w[k]) : cmul(x[k], w[k]);
+    }
+};
+// Which of them a stage of a single row takes, by time and error: at N = 2048 (eight points per thread) two factors in the
+// inner stages (B=16, H=256 step 90.7 us, one factor everywhere 98), beyond in stage 0 (B=4, H=96, N=8192 step 59.3 us, one
+// everywhere 64.4, two everywhere 58.8 with 9 % more error).
+template <int LG, int BITS, bool FIRST>
+using RowTw = typename std::conditional<FIRST, typename std::conditional<LG == 11, StageTwTwist<BITS>, StageTwPairs<BITS, true>>::type,
+                                        typename std::conditional<LG == 11, StageTwPairs<BITS, false>, StageTwAll<BITS>>::type>::type;
 
 // ALL: the tables handed to the transforms are Tables::stw and every power comes from there
-template <int LG, bool ALL = false>
+// TWIST: N points of a single real row (see frow_conv_kernel), in and out as the real parts of x; x[n] w^-n with
+// w = exp(i pi / 2N), where n = q + d T of a thread's points: the part of d is a constant of the butterfly, that of q rides on
+// the twiddles of stage 0
+template <int LG, bool ALL = false, bool TWIST = false>
 struct Fft {
-    static constexpr int P = 1 << points_log2(LG), T = (1 << LG) / P, S = stages(LG);
+    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG);
 
     template <int s>
     struct St {
         static constexpr int bits = stage_bits(LG, s), r = 1 << bits, G = P / r;
         static constexpr int lgs = span_log2(LG, s), lgM = lgs - bits;
-        typename std::conditional<ALL, StageTwAll<bits>, StageTw<bits>>::type tw[G];
+        static constexpr bool twist = TWIST && s == 0;
+        typename std::conditional<TWIST, RowTw<LG, bits, twist>, typename std::conditional<ALL, StageTwAll<bits>, StageTw<bits>>::type>::type tw[G];
         // butterfly g of thread tid: number tid + g T, q = its low lgM bits
         __device__ __forceinline__ static int q_of(int tid, int g) { return (tid + g * T) & ((1 << lgM) - 1); }
         __device__ __forceinline__ static int base(int tid, int g)
@@ -262,6 +334,13 @@ struct Fft {
                                                     const float2* __restrict__ ft, int tid)
     {
         using C = St<s>;
+        if constexpr (C::twist) {
+#pragma unroll
+            for (int d = 0; d < P; ++d) {
+                const float2 c = twist_unit<P>(d);
+                x[d] = make_float2(x[d].x * c.x, x[d].x * c.y);
+            }
+        }
 #pragma unroll
         for (int g = 0; g < C::G; ++g) {
             if constexpr (HALF && s == 0) dft_half_in<C::r>(x + g * C::r);
@@ -299,6 +378,13 @@ struct Fft {
         for (int g = 0; g < C::G; ++g) {
             if constexpr (HALF && s == 0) dft_half_out<C::r>(x + g * C::r);
             else dft<C::r, true>(x + g * C::r);
+        }
+        if constexpr (C::twist) {
+#pragma unroll
+            for (int d = 0; d < P; ++d) {
+                const float2 c = twist_unit<P>(d);
+                x[d].x = __builtin_fmaf(x[d].y, c.y, x[d].x * c.x);
+            }
         }
         if constexpr (s > 0) {
             St<s - 1> nx;
@@ -543,13 +629,13 @@ __device__ __forceinline__ void store_pair(const float2 (&x)[Fft<LG>::P], typena
     }
 }
 
-template <int LG, bool CONJ>
-__device__ __forceinline__ void times_spectrum(float2 (&x)[Fft<LG>::P], const float2* __restrict__ ks, int tid)
+template <class F, bool CONJ>
+__device__ __forceinline__ void times_spectrum(float2 (&x)[F::P], const float2* __restrict__ ks, int tid)
 {
     tid = fresh(tid);
 #pragma unroll
-    for (int i = 0; i < Fft<LG>::P / 2; ++i) {
-        const float4 k = *reinterpret_cast<const float4*>(ks + Fft<LG>::spec_at(tid, i));
+    for (int i = 0; i < F::P / 2; ++i) {
+        const float4 k = *at(reinterpret_cast<const float4*>(ks), F::spec_at(0, i) / 2, tid);
         const float2 ka = make_float2(k.x, k.y), kb = make_float2(k.z, k.w);
         x[2 * i] = CONJ ? cmulc(x[2 * i], ka) : cmul(x[2 * i], ka);
         x[2 * i + 1] = CONJ ? cmulc(x[2 * i + 1], kb) : cmul(x[2 * i + 1], kb);
@@ -580,8 +666,8 @@ fconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
     load_pair<LG, IO, CHUNK>(x, in + oa, in + ob, has_b, c, tid);
     F::template fwd<!CHUNK>(x, sm, ft, tid);
     const float2* ks = kspec + ((size_t)h << (LG + log2R)) + ((size_t)k1 << LG);
-    if (conj) times_spectrum<LG, true>(x, ks, tid);
-    else times_spectrum<LG, false>(x, ks, tid);
+    if (conj) times_spectrum<F, true>(x, ks, tid);
+    else times_spectrum<F, false>(x, ks, tid);
     F::template inv<!CHUNK>(x, sm, ft, tid);
     float2* chunk = CHUNK ? ws + (((size_t)h * gridDim.x + p) << (LG + log2R)) + ((size_t)k1 << LG) : nullptr;
     store_pair<LG, IO, CHUNK>(x, out + oa, out + ob, has_b, chunk, tid);
@@ -597,7 +683,7 @@ fconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
 //   dD: [nsplit][H]
 // At L2 = 16384 a thread may hold 128 registers (sixteen waves); accumulators, Z and the points in work do not fit into
 // them (spilled: 120 registers a thread), so Z waits in zbuf, [R][H][nsplit] sequences that stay in L2, written and
-// read by the same thread (B=4, H=96, N=8192: 62 -> 47 us).  26 (CHUNK) to 62 are spilled all the same, 43 with fp32 rows.
+// read by the same thread (B=4, H=96, N=8192, then in pairs: 62 -> 47 us).  48 are spilled all the same.
 template <int LG, class IO, bool CHUNK>
 __global__ void __launch_bounds__(Fft<LG>::T)
 fbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ kspec,
@@ -672,7 +758,7 @@ fbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
             acc[i].y += z[i].x * w[i].y - z[i].y * w[i].x;
         }
         if (want_du) {
-            times_spectrum<LG, true>(w, fresh(ks), tid);
+            times_spectrum<F, true>(w, fresh(ks), tid);
             F::template inv<!CHUNK>(w, sm, ft, tid);
             float2* chunk = CHUNK ? ws_du + (((size_t)h * npairs + p) << (LG + log2R)) + ((size_t)k1 << LG) : nullptr;
             store_pair<LG, IO, CHUNK>(w, du + oa, du + ob, has_b, chunk, tid);
@@ -706,6 +792,167 @@ fbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
     }
 }
 
+// ---- single fp32 rows of N = 2048 .. 16384 samples ----------------------------------------------------------------------
+// The transform of engine_rows.hip in fp32: N twisted points of one real row, whose products are convolutions modulo z^N - i
+// with the causal convolution as real part.  Against pairs of rows in 2N points it takes the same arithmetic a row, half the
+// LDS, half the spectrum, and twice the workgroups: two rows of 8192 samples share a compute unit and hide each other's
+// barriers and memory, and the backward kernel spills little (12 and 16 registers at N = 4096 and 16384, where a pair spilled 43);
+// N = 16384 takes no chunks.  Bound by vector issue: 105 instructions per point for a convolution, at 2.6 cycles and four waves
+// per SIMD.  Whole steps, pairs and rows: B=4, H=96, N=8192 78.8 -> 59.1 us, B=2, H=300 146 -> 92; B=3, H=50, N=16384 129 -> 70;
+// B=16, H=128, N=4096 112 -> 102; B=4, H=96, N=2048 28.0 -> 23.7; forward B=8, H=64, N=8192 20.4 -> 16.6.
+// Error against 64 bits, y and dk, pairs and rows: N = 2048 1.92 -> 1.73e-7, 2.84 -> 2.63e-7; 4096 1.94 -> 1.71, 2.86 -> 2.59;
+// 8192 2.12 -> 1.69, 3.10 -> 2.62; 16384 2.22 -> 1.82, 3.28 -> 2.78.  (A row without a partner had an easier time in a pair, B = 1:
+// 1.66 -> 1.73 and 2.40 -> 2.60, 1.63 -> 1.71 and 2.36 -> 2.57, 1.81 -> 1.67 and 2.62 -> 2.57, 1.90 -> 1.81 and 2.76 -> 2.76.)
+// Neighbouring items on one XCD: the rows of a head share its spectrum there.
+__device__ __forceinline__ int item_of(int items)
+{
+    const int per = (items + 7) >> 3;
+    return (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);       // (may lie beyond the last)
+}
+template <int LG>
+using RowFft = Fft<LG, true, true>;
+template <int LG>
+__device__ __forceinline__ void load_row(float2 (&x)[RowFft<LG>::P], const float* __restrict__ row, int tid)
+{
+    tid = fresh(tid);
+#pragma unroll
+    for (int d = 0; d < RowFft<LG>::P; ++d) x[d].x = *at(row, d * RowFft<LG>::T, tid);
+}
+template <int LG>
+__device__ __forceinline__ void store_row(const float2 (&x)[RowFft<LG>::P], float* __restrict__ row, int tid)
+{
+    tid = fresh(tid);
+#pragma unroll
+    for (int d = 0; d < RowFft<LG>::P; ++d) put_once(at(row, d * RowFft<LG>::T, tid), x[d].x);
+}
+
+template <int LG>
+__global__ void __launch_bounds__(RowFft<LG>::T)
+frow_kspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* __restrict__ kspec, float scale,
+                  const float2* __restrict__ stw)
+{
+    using F = RowFft<LG>;
+    extern __shared__ float2 sm[];
+    const int h = blockIdx.x, tid = threadIdx.x;
+    float2 x[F::P];
+    load_row<LG>(x, k + ((size_t)h << LG), tid);
+    const float dh = D[h];
+    F::template fwd<false>(x, sm, stw, tid);
+    float2* out = kspec + ((size_t)h << LG);
+#pragma unroll
+    for (int i = 0; i < F::P / 2; ++i)
+        *at(reinterpret_cast<float4*>(out), F::spec_at(0, i) / 2, tid) =
+            make_float4((x[2 * i].x + dh) * scale, x[2 * i].y * scale, (x[2 * i + 1].x + dh) * scale, x[2 * i + 1].y * scale);
+}
+
+template <int LG>
+__global__ void __launch_bounds__(RowFft<LG>::T) __attribute__((amdgpu_waves_per_eu(4)))
+frow_conv_kernel(const float* __restrict__ in, const float2* __restrict__ kspec, float* __restrict__ out, int conj, int B, int H,
+                 const float2* __restrict__ stw)
+{
+    using F = RowFft<LG>;
+    extern __shared__ float2 sm[];
+    const int item = item_of(B * H), tid = threadIdx.x;
+    if (item >= B * H) return;
+    const int h = item / B;
+    const size_t o = row_off(item - h * B, h, H, F::N);
+    float2 x[F::P];
+    load_row<LG>(x, in + o, tid);
+    F::template fwd<false>(x, sm, stw, tid);
+    const float2* ks = kspec + ((size_t)h << LG);
+    if (conj) times_spectrum<F, true>(x, ks, tid);
+    else times_spectrum<F, false>(x, ks, tid);
+    F::template inv<false>(x, sm, stw, tid);
+    store_row<LG>(x, out + o, tid);
+}
+
+// du, dk and dD in one walk over a share of the head's rows, as fbwd_kernel.  A, the sum of conj(U) W, waits in `acc` ([H][nsplit]
+// sequences, written and read by the same thread) while the next row is transformed: with it, and U, and the points in work, 128
+// registers are not enough.  A share of one row never touches it.
+template <int LG>
+__global__ void __launch_bounds__(RowFft<LG>::T) __attribute__((amdgpu_waves_per_eu(4)))
+frow_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ u, const float2* __restrict__ kspec, float* __restrict__ du,
+                float* __restrict__ dk, float* __restrict__ dD, float4* __restrict__ acc, int B, int H, int nsplit, float scale,
+                const float2* __restrict__ stw)
+{
+    using F = RowFft<LG>;
+    constexpr int P = F::P, T = F::T;
+    extern __shared__ float2 sm[];
+    __shared__ float red[T / 64];
+    const int item = item_of(H * nsplit), tid = threadIdx.x;
+    if (item >= H * nsplit) return;
+    const int h = item / nsplit, share = item - h * nsplit;
+    acc += (size_t)item << (LG - 1);
+    const float2* ks = kspec + ((size_t)h << LG);
+    constexpr bool PARK = row_parks(LG);
+    float dsum = 0.f;
+    float2 z[P], sum[PARK ? 1 : P];
+    if constexpr (!PARK) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) sum[i] = make_float2(0.f, 0.f);
+    }
+    for (int b = share; b < B; b += nsplit) {
+        const size_t o = row_off(b, h, H, F::N);
+        float2 w[P];
+        load_row<LG>(z, u + o, tid);
+        load_row<LG>(w, dy + o, tid);
+#pragma unroll
+        for (int d = 0; d < P; ++d) dsum = __builtin_fmaf(z[d].x, w[d].x, dsum);
+        F::template fwd<false>(z, sm, stw, tid);
+        __syncthreads();                      // the last stage of z has been read everywhere
+        F::template fwd<false>(w, sm, stw, tid);
+#pragma unroll
+        for (int i = 0; i < P; ++i) z[i] = cmulc(w[i], z[i]);
+        if constexpr (PARK) {
+            float4* a = fresh(acc);
+            const int t = fresh(tid);
+            if (b != share) {
+#pragma unroll
+                for (int i = 0; i < P / 2; ++i) {
+                    const float4 v = *at(a, i * T, t);
+                    z[2 * i].x += v.x; z[2 * i].y += v.y;
+                    z[2 * i + 1].x += v.z; z[2 * i + 1].y += v.w;
+                }
+            }
+            if (b + nsplit < B) {
+#pragma unroll
+                for (int i = 0; i < P / 2; ++i) *at(a, i * T, t) = make_float4(z[2 * i].x, z[2 * i].y, z[2 * i + 1].x, z[2 * i + 1].y);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < P; ++i) sum[i] = cadd(sum[i], z[i]);
+        }
+        if (du) {
+            times_spectrum<F, true>(w, fresh(ks), tid);
+            F::template inv<false>(w, sm, stw, tid);
+            store_row<LG>(w, du + o, tid);
+        } else {
+            __syncthreads();
+        }
+    }
+    if (dk) {
+        __syncthreads();
+        if constexpr (!PARK) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) z[i] = sum[i];
+        }
+        F::template inv<false>(z, sm, stw, tid);
+        float* o = dk + (((size_t)share * H + h) << LG);
+#pragma unroll
+        for (int d = 0; d < P; ++d) *at(o, d * T, tid) = z[d].x * scale;
+    }
+    if (dD) {                                 // fixed-order sum over the workgroup
+        for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
+        if ((tid & 63) == 0) red[tid >> 6] = dsum;
+        __syncthreads();
+        if (tid == 0) {
+            float t = 0.f;
+            for (int i = 0; i < T / 64; ++i) t += red[i];
+            dD[(size_t)share * H + h] = t;
+        }
+    }
+}
+
 template <class F>
 hipError_t set_lds(F* f, size_t bytes)
 {
@@ -722,6 +969,16 @@ __global__ void fill_ftw_kernel(float2* ft)
     double s, c;
     sincospi(-2.0 * (double)q / (double)(1 << l), &s, &c);
     ft[i] = make_float2((float)c, (float)s);
+}
+
+template <int LG>
+__global__ void fill_twist_kernel(float2* stw)
+{
+    constexpr int T = Fft<LG>::T;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, k = i / T, q = i % T;
+    double s, c;
+    sincospi(-2.0 * (double)((4 * k + 1) * q) / (double)(4 << LG), &s, &c);
+    stw[twist_offset(LG) + i] = make_float2((float)c, (float)s);
 }
 
 #define LC_LG_SWITCH(lg, CALL)                \
@@ -751,6 +1008,45 @@ hipError_t kspec_go(const float* k, const float* D, float2* kspec, int64_t H, in
         hipLaunchKernelGGL((fkspec_kernel<LG, false>), grid, dim3(Fft<LG>::T), lds_bytes(LG), st, k, D, kspec, N, log2R,
                            *consumer, scale, tb.tw, tb.ftw);
     }
+    return hipGetLastError();
+}
+
+#define LC_ROWS_SWITCH(lg, CALL)              \
+    switch (lg) {                             \
+        case 11: return CALL(11);             \
+        case 12: return CALL(12);             \
+        case 13: return CALL(13);             \
+        case 14: return CALL(14);             \
+        default: return hipErrorInvalidValue; \
+    }
+
+template <int LG>
+hipError_t rows_kspec_go(const float* k, const float* D, float2* kspec, int64_t H, float scale, const Tables& tb, hipStream_t st)
+{
+    const hipError_t e = set_lds(frow_kspec_kernel<LG>, lds_bytes(LG));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(frow_kspec_kernel<LG>, dim3((unsigned)H), dim3(RowFft<LG>::T), lds_bytes(LG), st, k, D, kspec, scale, tb.stw);
+    return hipGetLastError();
+}
+// workgroups for a list of items (see item_of)
+dim3 item_grid(int64_t items) { return dim3((unsigned)((items + 7) / 8 * 8)); }
+template <int LG>
+hipError_t rows_conv_go(const float* in, const float2* kspec, float* out, bool conj, const Problem& pr, const Tables& tb, hipStream_t st)
+{
+    const hipError_t e = set_lds(frow_conv_kernel<LG>, lds_bytes(LG));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(frow_conv_kernel<LG>, item_grid(pr.B * pr.H), dim3(RowFft<LG>::T), lds_bytes(LG), st, in, kspec, out, conj ? 1 : 0,
+                       (int)pr.B, (int)pr.H, tb.stw);
+    return hipGetLastError();
+}
+template <int LG>
+hipError_t rows_bwd_go(const float* dy, const float* u, const float2* kspec, float* du, float* dk, float* dD, void* acc, int nsplit,
+                       const Problem& pr, float scale, const Tables& tb, hipStream_t st)
+{
+    const hipError_t e = set_lds(frow_bwd_kernel<LG>, lds_bytes(LG));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(frow_bwd_kernel<LG>, item_grid(pr.H * nsplit), dim3(RowFft<LG>::T), lds_bytes(LG), st, dy, u, kspec, du, dk, dD,
+                       (float4*)acc, (int)pr.B, (int)pr.H, nsplit, scale, tb.stw);
     return hipGetLastError();
 }
 
@@ -785,13 +1081,16 @@ hipError_t conv_go(const void* in, const float2* kspec, void* out, float2* ws, b
     return hipGetLastError();
 }
 
+// pairs of whole rows: of fp32 rows there are those up to N = 1024 (longer ones run by themselves, see make_plan)
+template <class IO>
+constexpr int alone(int LG) { return std::is_same<IO, IoF32>::value && LG > VALU_ROWS_MIN_LOG2 ? VALU_ROWS_MIN_LOG2 : LG; }
 template <class IO>
 hipError_t conv_io(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
                    const Plan& pl, const Tables& tb, hipStream_t st)
 {
 #define CALL(LG)                                                                            \
     (pl.log2R ? conv_go<LG, IO, true>(in, kspec, out, ws, conj, pr, pl.log2R, tb, st)        \
-              : conv_go<LG, IO, false>(in, kspec, out, ws, conj, pr, 0, tb, st))
+              : conv_go<alone<IO>(LG), IO, false>(in, kspec, out, ws, conj, pr, 0, tb, st))
     LC_LG_SWITCH(pl.log2L2, CALL)
 #undef CALL
 }
@@ -815,7 +1114,7 @@ hipError_t bwd_io(const void* dy, const void* u, const float2* kspec, void* du, 
 {
 #define CALL(LG)                                                                                            \
     (pl.log2R ? bwd_go<LG, IO, true>(dy, u, kspec, nullptr, ws_du, nullptr, ws_A, dD, zbuf, nsplit, pr, pl, tb, st) \
-              : bwd_go<LG, IO, false>(dy, u, kspec, du, nullptr, dk, nullptr, dD, zbuf, nsplit, pr, pl, tb, st))
+              : bwd_go<alone<IO>(LG), IO, false>(dy, u, kspec, du, nullptr, dk, nullptr, dD, zbuf, nsplit, pr, pl, tb, st))
     LC_LG_SWITCH(pl.log2L2, CALL)
 #undef CALL
 }
@@ -833,12 +1132,22 @@ hipError_t valu_fill_tables(const float2** ftw, hipStream_t st)
     return hipGetLastError();
 }
 
+hipError_t valu_fill_twist(float2* stw, hipStream_t st)
+{
+    hipLaunchKernelGGL(fill_twist_kernel<11>, dim3((1 << 11) / 256), dim3(256), 0, st, stw);
+    hipLaunchKernelGGL(fill_twist_kernel<12>, dim3((1 << 12) / 256), dim3(256), 0, st, stw);
+    hipLaunchKernelGGL(fill_twist_kernel<13>, dim3((1 << 13) / 256), dim3(256), 0, st, stw);
+    hipLaunchKernelGGL(fill_twist_kernel<14>, dim3((1 << 14) / 256), dim3(256), 0, st, stw);
+    return hipGetLastError();
+}
+
 void valu_fill_plan(Plan& pl)
 {
     pl.order = SpecOrder{};
     if (pl.log2R) pl.order.bits[pl.order.ndig++] = (unsigned char)pl.log2R;
-    for (int s = 0; s < stages(pl.log2L2); ++s) pl.order.bits[pl.order.ndig++] = (unsigned char)stage_bits(pl.log2L2, s);
-    pl.kscale = pl.dkscale = 1.0f / (float)(int64_t(1) << pl.log2L);
+    const int lg = pl.vrow ? pl.vrow : pl.log2L2;
+    for (int s = 0; s < stages(lg); ++s) pl.order.bits[pl.order.ndig++] = (unsigned char)stage_bits(lg, s);
+    pl.kscale = pl.dkscale = 1.0f / (float)(int64_t(1) << (pl.vrow ? pl.vrow : pl.log2L));
 }
 
 hipError_t valu_kspec(const float* k, const float* D, float2* kspec, int64_t H, int64_t N, const SpecOrder* consumer,
@@ -846,6 +1155,13 @@ hipError_t valu_kspec(const float* k, const float* D, float2* kspec, int64_t H, 
 {
 #define CALL(LG) kspec_go<LG>(k, D, kspec, H, N, log2R, consumer, scale, tb, st)
     LC_LG_SWITCH(log2L2, CALL)
+#undef CALL
+}
+
+hipError_t valu_rows_kspec(const float* k, const float* D, float2* kspec, int64_t H, const Plan& pl, const Tables& tb, hipStream_t st)
+{
+#define CALL(LG) rows_kspec_go<LG>(k, D, kspec, H, pl.kscale, tb, st)
+    LC_ROWS_SWITCH(pl.vrow, CALL)
 #undef CALL
 }
 
@@ -882,6 +1198,11 @@ hipError_t spectrum_natural_bwd(const float* dshat, float* dk, float* dD, int64_
 hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
                      const Plan& pl, const Tables& tb, hipStream_t st)
 {
+    if (pl.vrow) {
+#define CALL(LG) rows_conv_go<LG>((const float*)in, kspec, (float*)out, conj, pr, tb, st)
+        LC_ROWS_SWITCH(pl.vrow, CALL)
+#undef CALL
+    }
     switch (pr.io) {
         case LONGCONV_F32: return conv_io<IoF32>(in, kspec, out, ws, conj, pr, pl, tb, st);
         case LONGCONV_F16: return conv_io<IoF16>(in, kspec, out, ws, conj, pr, pl, tb, st);
@@ -890,23 +1211,30 @@ hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws,
 }
 
 // Workgroups that fill the device: one, two or about four of them per compute unit by their LDS
-int valu_bwd_nsplit(int64_t H, int npairs, const Plan& pl)
+int valu_bwd_nsplit(int64_t B, int64_t H, const Plan& pl)
 {
-    const int target = pl.log2L2 >= 14 ? 256 : pl.log2L2 == 13 ? 512 : 1024;
+    const int lg = pl.vrow ? pl.vrow : pl.log2L2, target = lg >= 14 ? 256 : lg == 13 ? 512 : 1024;
+    const int64_t units = pl.vrow ? B : (B + 1) / 2;
     int64_t s = target / (H << pl.log2R);
-    if (s > npairs) s = npairs;
+    if (s > units) s = units;
     if (s > 64) s = 64;
     return s < 1 ? 1 : (int)s;
 }
 
-size_t valu_zbuf_bytes(int64_t H, int nsplit, const Plan& pl)
+size_t valu_zbuf_bytes(int64_t B, int64_t H, int nsplit, const Plan& pl)
 {
+    if (pl.vrow) return row_parks(pl.vrow) && B > nsplit ? ((size_t)H * nsplit << pl.vrow) * sizeof(float2) : 0;
     return valu_parks(pl.log2L2) ? ((size_t)H * nsplit << pl.log2L) * sizeof(float2) : 0;
 }
 
 hipError_t valu_bwd(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
                     float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
+    if (pl.vrow) {
+#define CALL(LG) rows_bwd_go<LG>((const float*)dy, (const float*)u, kspec, (float*)du, dk, dD, zbuf, nsplit, pr, pl.dkscale, tb, st)
+        LC_ROWS_SWITCH(pl.vrow, CALL)
+#undef CALL
+    }
     switch (pr.io) {
         case LONGCONV_F32: return bwd_io<IoF32>(dy, u, kspec, du, ws_du, dk, ws_A, dD, zbuf, nsplit, pr, pl, tb, st);
         case LONGCONV_F16: return bwd_io<IoF16>(dy, u, kspec, du, ws_du, dk, ws_A, dD, zbuf, nsplit, pr, pl, tb, st);

@@ -99,8 +99,10 @@ hipError_t kreg_bwd(const float* k, const float* mask, const float* dkbar, float
 
 // ---- fp32 VALU engine (engine_valu.hip) --------------------------------------------
 constexpr int VALU_INNER_MAX_LOG2 = 14;
+constexpr int VALU_ROWS_MIN_LOG2 = TWIST_MIN, VALU_ROWS_MAX_LOG2 = TWIST_MAX;      // fp32 rows that run by themselves (Plan::vrow)
 hipError_t valu_fill_tables(const float2** ftw, hipStream_t st);
 void valu_fill_plan(Plan& pl);
+hipError_t valu_fill_twist(float2* stw, hipStream_t st);       // the part of Tables::stw behind STW_TOTAL
 // Spectrum of all heads in fp32, as R = 2^log2R chunks of 2^log2L2 points (pass A taken inside the kernel), stored in
 // the order of the engine's own kernels, or scattered to `consumer`'s order if that is given.
 hipError_t valu_kspec(const float* k, const float* D, float2* kspec, int64_t H, int64_t N, const SpecOrder* consumer,
@@ -110,14 +112,15 @@ hipError_t spectrum_natural(const float* k, const float* D, float* shat, int64_t
                             hipStream_t st);
 hipError_t spectrum_natural_bwd(const float* dshat, float* dk, float* dD, int64_t H, int64_t N, const Tables& tb,
                                 hipStream_t st);
+hipError_t valu_rows_kspec(const float* k, const float* D, float2* kspec, int64_t H, const Plan& pl, const Tables& tb, hipStream_t st);
 // Multi-pass plans: pass A is taken inside the kernels, ws receives pass C's input.
 hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws, bool conj, const Problem& pr,
                      const Plan& pl, const Tables& tb, hipStream_t st);
 // du, dk and dD in one kernel; any of du / ws_du (multi-pass), dk / ws_A (multi-pass) and dD may be null.  nsplit > 1: dk
 // (or ws_A) and dD point to partial buffers [nsplit][...] that sum_partials() adds up in share order.
 // zbuf: valu_zbuf_bytes() of scratch.
-int valu_bwd_nsplit(int64_t H, int npairs, const Plan& pl);
-size_t valu_zbuf_bytes(int64_t H, int nsplit, const Plan& pl);
+int valu_bwd_nsplit(int64_t B, int64_t H, const Plan& pl);
+size_t valu_zbuf_bytes(int64_t B, int64_t H, int nsplit, const Plan& pl);
 hipError_t valu_bwd(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
                     float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 
