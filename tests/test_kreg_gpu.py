@@ -111,3 +111,25 @@ def test_regularised_convolution_end_to_end(key, B, H, p, lam, q):
     print("[kreg end to end] " + " ".join(f"{a}={b:.2e}" for a, b in errs.items()), flush=True)
     for name, e in errs.items():
         assert e <= tol, f"{name}: {e:.3e}"
+
+
+# a wave takes 256 entries and their halo: the narrowest and widest windows with one and with several of them in a row
+@pytest.mark.parametrize("N", [256, 1024])
+@pytest.mark.parametrize("p", [1, 15, 16, 31, 32])
+def test_windows_across_waves(N, p):
+    test_regularisers_forward_and_chain_against_oracle(3, N, p, 0.002, 0.2)
+
+
+def test_closed_gate_drops_any_gradient():
+    import paper_2302_06646_amd as lc
+    k = torch.zeros(2, 512, device="cuda")
+    k[:, 300] = 1.0
+    g = torch.full_like(k, float("nan"))
+    g[:, 296:305] = 1.0
+    dk = torch.full_like(k, float("nan"))
+    lc.longconv_kreg_bwd(k, None, g, dk, 2, 0.1)
+    assert torch.isfinite(dk).all()
+    want = torch.zeros(2, 512)
+    for n in range(298, 303):                            # K2 = 1/5 > lambda there, zero elsewhere
+        want[:, n - 2:n + 3] += 0.2
+    assert torch.allclose(dk.cpu(), want, atol=1e-6)
