@@ -278,23 +278,40 @@ struct Geo {
 };
 
 constexpr int ROW = 17;        // stride of 16 complex numbers in LDS: lanes that read down a column meet 16 different banks
-// entries of the matrices of tile t, from the head's blocks in LDS (forward, then inverse)
+// entries of the matrices of a tile, from the head's blocks in LDS (forward, then inverse); w: w_0 of k_0 or w_1 of k_1 (LaneTw)
 template <int LG>
 struct Entries {
     using G = Geo<LG>;
-    const float2 *A, *B, *stw;
-    int t;
-    __device__ __forceinline__ float2 w0(int k0) const { return stw[stw_offset(LG) + (k0 << (LG - 4)) + t]; }
-    __device__ __forceinline__ float2 w1(int k1) const { return stw[stw_offset(4 + G::LB) + (k1 << G::LB) + t]; }
-    __device__ __forceinline__ float2 a0(int k0, int d0) const { return scaled(cmul(A[k0 * ROW + d0], w0(k0)), 0.25f); }
-    __device__ __forceinline__ float2 a1(int k1, int d1) const { return scaled(cmul(A[(16 + k1) * ROW + d1], w1(k1)), 0.25f); }
-    __device__ __forceinline__ float2 b1(int d1, int k1) const { return scaled(cmulc(B[(16 + d1) * ROW + k1], w1(k1)), 0.25f); }
-    __device__ __forceinline__ float2 b0(int d0, int k0) const { return scaled(cmulc(B[d0 * ROW + k0], w0(k0)), 0.25f); }
+    const float2 *A, *B;
+    __device__ __forceinline__ float2 a0(int k0, int d0, float2 w) const { return scaled(cmul(A[k0 * ROW + d0], w), 0.25f); }
+    __device__ __forceinline__ float2 a1(int k1, int d1, float2 w) const { return scaled(cmul(A[(16 + k1) * ROW + d1], w), 0.25f); }
+    __device__ __forceinline__ float2 b1(int d1, int k1, float2 w) const { return scaled(cmulc(B[(16 + d1) * ROW + k1], w), 0.25f); }
+    __device__ __forceinline__ float2 b0(int d0, int k0, float2 w) const { return scaled(cmulc(B[d0 * ROW + k0], w), 0.25f); }
     // the last block, block diagonal over the k_0's that share a middle tile
     __device__ __forceinline__ float2 last(const float2* M, int o, int i) const
     {
         const float2 v = M[(32 + (o & (G::T - 1))) * ROW + (i & (G::T - 1))];
         return (o >> G::LB) == (i >> G::LB) ? scaled(v, 1.0f / (float)(1 << stage_shift(G::LB))) : make_float2(0.f, 0.f);
+    }
+};
+// The twiddles of one lane's operands, o = lane % 16 and i = 4g .. 4g+3 as result's and input's index, either way round: w_0 =
+// w_L^(k_0 t) and w_1 = w_16T^(k_1 t) at o (w0c, w1c) and at i (w0q, w1q).  Asked for in front of the head's data, not one by one
+// where they are used.
+template <int LG>
+struct LaneTw {
+    using G = Geo<LG>;
+    float2 w0c, w1c, w0q[4], w1q[4];
+    __device__ __forceinline__ void load(const float2* __restrict__ stw, int t, int lane)
+    {
+        const int c = lane & 15, q = 4 * (lane >> 4);
+        const float2 *p0 = stw + stw_offset(LG) + t, *p1 = stw + stw_offset(4 + G::LB) + t;
+        w0c = p0[c << (LG - 4)];
+        w1c = p1[c << G::LB];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            w0q[r] = p0[(q + r) << (LG - 4)];
+            w1q[r] = p1[(q + r) << G::LB];
+        }
     }
 };
 // w_256^(c d), d = 4g .. 4g+3
@@ -440,15 +457,17 @@ lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ s
         const size_t step = (size_t)H * (N / 2);
         uint32_t w = *up, wn = n > 1 ? up[step] : 0u;
         up += 2 * step;
+        LaneTw<LG> W;
+        W.load(stw, t, lane);
         hd.put(sm2, tid);
         __syncthreads();
-        const Entries<LG> E{sm2, sm2 + 48 * ROW, stw, t};
-        const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i); }, lane);
-        const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i); }, lane);
+        const Entries<LG> E{sm2, sm2 + 48 * ROW};
+        const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i, W.w0c); }, lane);
+        const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i, W.w1c); }, lane);
         const Cx A2 = make_cx([&](int o, int i) { return E.last(E.A, o, i); }, lane);
         const Cx B2 = make_cx([&](int o, int i) { return E.last(E.B, o, i); }, lane);
-        const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i); }, lane);
-        const h8 B0 = make_cx([&](int o, int i) { return scaled(E.b0(o, i), G::yscale()); }, lane).re;
+        const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i, W.w1q[i & 3]); }, lane);
+        const h8 B0 = make_cx([&](int o, int i) { return scaled(E.b0(o, i, W.w0q[i & 3]), G::yscale()); }, lane).re;
         f4 sr, si;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -543,7 +562,7 @@ constexpr int lbb_numbers() { return Geo<LG>::T * (2 * Geo<LG>::XS + 2 * Geo<LG>
 template <int LG>
 constexpr size_t lbb_lds()
 {
-    const size_t work = sizeof(_Float16) * lbb_numbers<LG>(), red = sizeof(float2) * 2 * NBLK * Geo<LG>::T;
+    const size_t work = sizeof(_Float16) * lbb_numbers<LG>(), red = sizeof(float2) * 4 * NBLK * Geo<LG>::T;
     const size_t a = work > red ? work : red;
     return a > HeadData<LG>::bytes ? a : HeadData<LG>::bytes;
 }
@@ -584,20 +603,22 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
     gp += 2 * step;
     f4 cr, ci;
     inner_twiddles(cr, ci, stw, lane);
+    LaneTw<LG> W;
+    W.load(stw, t, lane);
     hd.put(sm2, tid);
     __syncthreads();
-    const Entries<LG> E{sm2, sm2 + 48 * ROW, stw, t};
-    const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i); }, lane);
-    const Rl B0H = make_rl([&](int o, int i) { return conj2(E.b0(i, o)); }, lane);
-    const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i); }, lane);
-    const Cx A1H = make_cx([&](int o, int i) { return conj2(E.a1(i, o)); }, lane);
-    const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i); }, lane);
-    const Cx B1H = make_cx([&](int o, int i) { return conj2(E.b1(i, o)); }, lane);
+    const Entries<LG> E{sm2, sm2 + 48 * ROW};
+    const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i, W.w0c); }, lane);          // (i & 3: of the lane's four)
+    const Rl B0H = make_rl([&](int o, int i) { return conj2(E.b0(i, o, W.w0c)); }, lane);
+    const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i, W.w1c); }, lane);
+    const Cx A1H = make_cx([&](int o, int i) { return conj2(E.a1(i, o, W.w1q[i & 3])); }, lane);
+    const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i, W.w1q[i & 3]); }, lane);
+    const Cx B1H = make_cx([&](int o, int i) { return conj2(E.b1(i, o, W.w1c)); }, lane);
     const Cx A2 = make_cx([&](int o, int i) { return E.last(E.A, o, i); }, lane);
     const Cx A2H = make_cx([&](int o, int i) { return conj2(E.last(E.A, i, o)); }, lane);
     const Cx B2 = make_cx([&](int o, int i) { return E.last(E.B, o, i); }, lane);
     const Cx B2H = make_cx([&](int o, int i) { return conj2(E.last(E.B, i, o)); }, lane);
-    const h8 A0H = make_cx([&](int o, int i) { return scaled(conj2(E.a0(i, o)), G::yscale()); }, lane).re;
+    const h8 A0H = make_cx([&](int o, int i) { return scaled(conj2(E.a0(i, o, W.w0q[i & 3])), G::yscale()); }, lane).re;
     f4 sr, si;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -624,8 +645,8 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
         return y;
     };
     __syncthreads();
-    for (int i = tid; i < T * G::IS; i += 64 * T) reinterpret_cast<uint32_t*>(inu)[i] = 0;       // both rows' tiles
-    __syncthreads();
+    // both rows' tiles: the padding, d_0 >= 8, stays zero; a row's samples are the other half
+    for (int i = tid; i < T * 128; i += 64 * T) reinterpret_cast<uint32_t*>(inu + (i >> 6) * G::IS + 128)[i & 63] = 0;
     row_in<LG>(inu, to_h2<IO>(wu), tid);
     row_in<LG>(ing, to_h2<IO>(wg), tid);
     __syncthreads();
@@ -746,6 +767,7 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
         rows_in(b);
         __syncthreads();
     }
+    W.load(stw, t, lane);                    // (for the sums below; no registers for them in the loop)
     last();
     __syncthreads();
     if (du) put_once(dp, row_out<LG>(outb, tid));
@@ -756,36 +778,42 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
 #pragma unroll
         for (int r = 0; r < 4; ++r) ps[freq_at<LG>(t, 4 * g + r, c)] = make_float2(dsr[r] * G::yscale(), dsi[r] * G::yscale());
     }
-    // the waves' sums of one block of either chain, [chain][wave][entry]; then entry by entry in wave order
-    const float2 w0c = E.w0(c), w1c = E.w1(c);
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        __syncthreads();
+    // the waves' sums of one block of either chain, [chain][wave][entry]; then entry by entry in wave order.  Two buffers take
+    // turns, so that one barrier per block does.
+    __syncthreads();
+    const auto put_sums = [&](int s) {
+        float2* buf = sm2 + (s & 1) * 2 * T * NBLK;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = 4 * g + r, e = i * 16 + c;
+            const int e = (4 * g + r) * 16 + c;
             float2 f, q;
             if (s == 0) {
-                f = cmulc(make_float2(a0r[r], a0i[r]), E.w0(i));
-                q = cmul(make_float2(b0r[r], -b0i[r]), w0c);
+                f = cmulc(make_float2(a0r[r], a0i[r]), W.w0q[r]);
+                q = cmul(make_float2(b0r[r], -b0i[r]), W.w0c);
             } else if (s == 1) {
-                f = cmulc(make_float2(a1r[r], a1i[r]), E.w1(i));
-                q = cmul(make_float2(b1r[r], b1i[r]), w1c);
+                f = cmulc(make_float2(a1r[r], a1i[r]), W.w1q[r]);
+                q = cmul(make_float2(b1r[r], b1i[r]), W.w1c);
             } else {
                 f = make_float2(a2r[r], a2i[r]);
                 q = make_float2(b2r[r], b2i[r]);
             }
-            sm2[t * NBLK + e] = f;
-            sm2[(T + t) * NBLK + e] = q;
+            buf[t * NBLK + e] = f;
+            buf[(T + t) * NBLK + e] = q;
         }
+    };
+    put_sums(0);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
         __syncthreads();
+        if (s < 2) put_sums(s + 1);
+        const float2* buf = sm2 + (s & 1) * 2 * T * NBLK;
         const float sc = G::yscale() / (float)(1 << stage_shift(s == 2 ? LB : 4));
         for (int e2 = tid; e2 < 2 * NBLK; e2 += 64 * T) {
             const int chain = e2 / NBLK, e = e2 % NBLK, i = e / 16, j = e % 16;
             float2* q = chain ? out.qi : out.qf;
             if (!q) continue;
             float2 a = make_float2(0.f, 0.f);
-            const float2* p = sm2 + chain * T * NBLK;
+            const float2* p = buf + chain * T * NBLK;
             if (s < 2) {
                 for (int w = 0; w < T; ++w) a = cadd(a, p[w * NBLK + e]);
             } else if (i < T && j < T) {             // the diagonal blocks of I (x) A_2 all carry the same parameters
