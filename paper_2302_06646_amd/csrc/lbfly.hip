@@ -35,222 +35,11 @@ typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 constexpr int NBLK = 256;                       // entries of one 16 x 16 block
 __host__ __device__ constexpr int stage_shift(int b) { return b == 4 ? 2 : (b >= 2 ? 1 : 0); }
 __host__ __device__ constexpr int total_shift(int lg) { return 4 + stage_shift(lg - 8); }
-constexpr int LBB_WAVES = 8;                     // backward kernel of N = 2048
-
-struct Mats {
-    h8 re, im;   // A operands producing the real / imaginary part of the output
-};
-union H8U {
-    h8 v;
-    h2 c[4];
-    uint4 u;
-};
-
-// A operands of the 16 x 16 complex matrix 2^-sh * I_{16/r} (x) M, M = the leading r x r corner of `blk` (row major,
-// 16 entries per row) or its conjugate transpose.  Lane (m = l%16, g = l/16) holds K entries e = 0..7: slot
-// 4g + e/2, part e%2 (0 = re, 1 = im).
-__device__ Mats load_mats(const float2* __restrict__ blk, int b, bool adjoint, int lane)
-{
-    const int r = 1 << b, m = lane & 15, g = lane >> 4;
-    const float sc = 1.0f / (float)(1 << stage_shift(b));
-    Mats A;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int sig = 4 * g + q;
-        float2 w = make_float2(0.f, 0.f);
-        if ((m >> b) == (sig >> b)) {
-            const int i = m & (r - 1), j = sig & (r - 1);
-            w = adjoint ? blk[j * 16 + i] : blk[i * 16 + j];
-            if (adjoint) w.y = -w.y;
-        }
-        A.re[2 * q] = (_Float16)(w.x * sc);
-        A.re[2 * q + 1] = (_Float16)(-w.y * sc);
-        A.im[2 * q] = (_Float16)(w.y * sc);
-        A.im[2 * q + 1] = (_Float16)(w.x * sc);
-    }
-    return A;
-}
-
-__device__ __forceinline__ void blk16(const Mats& A, const h8& x, f4& yr, f4& yi)
-{
-    const f4 z = {0.f, 0.f, 0.f, 0.f};
-    yr = __builtin_amdgcn_mfma_f32_16x16x32_f16(A.re, x, z, 0, 0, 0);
-    yi = __builtin_amdgcn_mfma_f32_16x16x32_f16(A.im, x, z, 0, 0, 0);
-}
 
 __device__ __forceinline__ h2 pack(float re, float im)
 {
     const f2 v = {re, im};
     return __builtin_convertvector(v, h2);
-}
-
-// w_s(p) of the stage whose stride is 2^lgM
-__device__ __forceinline__ float2 stage_twiddle(const float2* __restrict__ stw, int p, int lgM)
-{
-    return stw[stw_offset(lgM + 4) + (p & ((16 << lgM) - 1))];
-}
-
-// position of (column gamma, slot sigma) for a stage of stride 2^lgM
-__device__ __forceinline__ int tile_pos(int gamma, int sigma, int lgM)
-{
-    return ((gamma >> lgM) << (lgM + 4)) | (gamma & ((1 << lgM) - 1)) | (sigma << lgM);
-}
-
-// Physical LDS index of position p: bank bits 2..5 are XORed with position bits 4..7 and 7..10.  Stages read a tile
-// with one slot digit spread over the lanes (strides of 2, 16, 128 ... words), the block gradients read it with the
-// roles of slot and column swapped; unswizzled, that is a five- to six-fold bank conflict on average over the access
-// patterns of this file, with this map about two-fold (bits 0, 1 stay, so runs of four positions remain one aligned
-// 16-byte access).  The map is linear over XOR: phys(a | b) = phys(a) ^ phys(b) for disjoint a, b.
-__host__ __device__ constexpr int phys(int p) { return p ^ ((((p >> 4) ^ (p >> 7)) & 15) << 2); }
-
-// frequency held by position p after the forward chain
-template <int LG>
-__device__ __forceinline__ int freq_of(int p)
-{
-    return (p >> (LG - 4)) | (((p >> (LG - 8)) & 15) << 4) | ((p & ((1 << (LG - 8)) - 1)) << 8);
-}
-
-// position that holds frequency f after the forward chain (the inverse of freq_of)
-template <int LG>
-__device__ __forceinline__ int pos_of(int f)
-{
-    return ((f & 15) << (LG - 4)) | (((f >> 4) & 15) << (LG - 8)) | (f >> 8);
-}
-
-// the head's spectrum, natural order in memory, into LDS in position order: the lanes of the middle step then read
-// their four bins as one 32-byte run instead of gathering them from 64 different cache lines per instruction
-template <int LG>
-__device__ __forceinline__ void stage_spectrum(float2* sS, const float2* __restrict__ sh, int tid, int nt)
-{
-    for (int f = tid; f < (1 << LG); f += nt) sS[phys(pos_of<LG>(f))] = sh[f];
-}
-
-// out <- post . (M in) on tile t (16 columns x 16 slots) of the stage with stride 2^lgM.  TWM: 0 no twiddle, 1 the
-// twiddle of the stage with stride 2^lgT, 2 its conjugate.  in == out is allowed (a lane writes what it read).
-template <int TWM>
-__device__ __forceinline__ void stage_tile(const h2* in, h2* out, int t, int lgM, int lgT, const Mats& A,
-                                           const float2* __restrict__ stw, int lane)
-{
-    const int c = lane & 15, g = lane >> 4;
-    const int p0 = tile_pos(16 * t + c, 4 * g, lgM), a0 = phys(p0);
-    int a[4];
-    H8U x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        a[j] = a0 ^ phys(j << lgM);              // the bits of j are clear in p0
-        x.c[j] = in[a[j]];
-    }
-    f4 yr, yi;
-    blk16(A, x.v, yr, yi);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float2 v = make_float2(yr[j], yi[j]);
-        if (TWM != 0) {
-            const float2 w = stage_twiddle(stw, p0 | (j << lgM), lgT);
-            v = TWM == 2 ? cmulc(v, w) : cmul(v, w);
-        }
-        out[a[j]] = pack(v.x, v.y);
-    }
-}
-
-// Q += G (x) conj(X) over the 16 columns of tile t of the stage with stride 2^lgM: Q[i][j] = sum_col G[i,col]
-// conj(X[j,col]).  The columns are the K dimension: lane (i = l%16, g = l/16) holds columns 4g .. 4g+3 of slot i as
-// (re, im) pairs, which is how they lie in LDS.  Result lane (j = l%16, g): rows i = 4g .. 4g+3.
-__device__ __forceinline__ void outer_tile(const h2* G, const h2* X, int t, int lgM, f4& qr, f4& qi, int lane)
-{
-    const int i = lane & 15, g = lane >> 4;
-    const int a0 = phys(tile_pos(16 * t + 4 * g, i, lgM));
-    H8U a, b, bs;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int p = a0 ^ phys(tile_pos(q, 0, lgM));      // column bits of q are clear in the tile's base
-        a.c[q] = G[p];
-        b.c[q] = X[p];
-        bs.c[q] = h2{(_Float16)(-b.c[q][1]), b.c[q][0]};
-    }
-    qr = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.v, b.v, qr, 0, 0, 0);     // Gr Xr + Gi Xi
-    qi = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.v, bs.v, qi, 0, 0, 0);    // Gi Xr - Gr Xi
-}
-
-template <class IO> struct Cv;
-template <> struct Cv<IoF16> {
-    static __device__ __forceinline__ void in(uint4 raw, float (&v)[8])
-    {
-        H8U x; x.u = raw;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = (float)x.v[q];
-    }
-    static __device__ __forceinline__ uint4 out(const float (&v)[8])
-    {
-        H8U x;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x.c[q] = pack(v[2 * q], v[2 * q + 1]);
-        return x.u;
-    }
-};
-template <> struct Cv<IoBF16> {
-    static __device__ __forceinline__ void in(uint4 raw, float (&v)[8])
-    {
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[2 * q] = __uint_as_float(w[q] << 16);
-            v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
-        }
-    }
-    static __device__ __forceinline__ uint4 out(const float (&v)[8])
-    {
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f2 f = {v[2 * q], v[2 * q + 1]};
-            union { bf2 b; uint32_t u; } cv;
-            cv.b = __builtin_convertvector(f, bf2);
-            w[q] = cv.u;
-        }
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    }
-};
-
-// one real row of N I/O elements -> positions 0 .. N-1 as (x, 0); positions N .. 2N-1 zero
-template <class IO>
-__device__ __forceinline__ void load_row(h2* s, const typename IO::T* row, int N, int tid, int nt)
-{
-    const uint4* p = reinterpret_cast<const uint4*>(row);
-    for (int i = tid; i < N / 8; i += nt) {
-        float v[8];
-        Cv<IO>::in(p[i], v);
-        H8U lo, hi;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            lo.c[q] = pack(v[q], 0.f);
-            hi.c[q] = pack(v[4 + q], 0.f);
-        }
-        *reinterpret_cast<uint4*>(&s[phys(8 * i)]) = lo.u;
-        *reinterpret_cast<uint4*>(&s[phys(8 * i + 4)]) = hi.u;
-        const uint4 z = make_uint4(0, 0, 0, 0);
-        *reinterpret_cast<uint4*>(&s[phys(N + 8 * i)]) = z;
-        *reinterpret_cast<uint4*>(&s[phys(N + 8 * i + 4)]) = z;
-    }
-}
-
-// row[t] <- scale * Re s[t], t < N
-template <class IO>
-__device__ __forceinline__ void store_row(const h2* s, typename IO::T* row, int N, float scale, int tid, int nt)
-{
-    uint4* p = reinterpret_cast<uint4*>(row);
-    for (int i = tid; i < N / 8; i += nt) {
-        H8U lo, hi;
-        lo.u = *reinterpret_cast<const uint4*>(&s[phys(8 * i)]);
-        hi.u = *reinterpret_cast<const uint4*>(&s[phys(8 * i + 4)]);
-        float v[8];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[q] = (float)lo.c[q][0] * scale;
-            v[4 + q] = (float)hi.c[q][0] * scale;
-        }
-        put_once(p + i, Cv<IO>::out(v));
-    }
 }
 
 // ---- the register-chained form ------------------------------------------------------------------------------------------
@@ -853,192 +642,328 @@ lb_reduce_kernel(const float2* __restrict__ part_shat, const float2* __restrict_
 }
 
 // -------------------------------------------------------------------------------------------------------------------
-// Backward of N = 2048 (sixteen tiles would be two per wave, whose matrices and sums do not fit the registers), with every
-// block a trip through LDS.  grid = (nsplit, H): workgroup (sp, h) owns rows b = sp, sp + nsplit, ... of head h, accumulates the
-// gradients of the head's six blocks and of its spectrum in registers over those rows and writes them as partial
-// results, which lb_reduce_kernel sums in a fixed order.  LDS: the spectrum, X0, X1, X2 (inputs of the forward
-// blocks), W2, W1, W0 (inputs of the inverse blocks), G (the gradient, in place).
+// Backward of N = 2048: the same pipeline with sixteen tiles, two per wave (t = 2 wave and 2 wave + 1: one set of addresses).  Two tiles' matrices and sums
+// would be 220 registers, so
+//   * the twiddle that tile t adds to w_256^(k_0 d_1) is multiplied with it in fp32, w_L^(k_0 (16 d_1 + t)): the outer blocks and
+//     their sums are then the same for all tiles (the gradient of A_1's input comes out with k_0 on the lanes, like all the others);
+//   * the blocks in the middle, A_1 and B_1 of every tile and A_2 and B_2, wait in LDS as planes (34 KB), read as they are or
+//     transposed for their adjoints.
+// grid = (nsplit, H), as above.  Bound by issue at two waves per SIMD; 29 registers spilled, two reloaded in the row loop.  A row takes
+// 3.2 us, a workgroup's matrices and sums 15.  B=64, H=256 bf16: 842 -> 218 us against the form it replaced (every block a trip
+// through LDS with its own barrier, seven buffers); steps B=16, H=100 fp16 155.5 -> 71.4, B=2, H=300 116 -> 63, B=64, H=1024 3777 ->
+// 1256.  Errors of du, dshat and both blocks' gradients against 64 bits are 0 to 2 % lower.
 // -------------------------------------------------------------------------------------------------------------------
-template <int LG, class IO>
-__global__ void __launch_bounds__(LBB_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
-lb_bwd_lds_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
-              const float2* __restrict__ shat, const float2* __restrict__ Af, const float2* __restrict__ Ai,
-              typename IO::T* __restrict__ du, LbGrads out, int64_t B, int64_t H, const float2* __restrict__ stw)
+struct Lb2 {
+    using G = Geo<12>;
+    static constexpr int NW = 8, NT = 64 * NW, T = G::T;
+    static constexpr int WORK = T * (2 * G::XS + 2 * G::IS + G::OS) + NW * 512;       // 16-bit numbers
+    static constexpr int MATS = 512 * (2 * T + 2);
+    static constexpr size_t lds = sizeof(_Float16) * (WORK + MATS);
+    static_assert(HeadData<12>::bytes <= sizeof(_Float16) * WORK, "the head's data passes through where the rows are");
+    static_assert(sizeof(float2) * 4 * NBLK * NW <= lds, "and the sums leave");
+};
+
+template <class IO>
+__global__ void __launch_bounds__(Lb2::NT) __attribute__((amdgpu_waves_per_eu(2)))
+lb_bwd2_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u, const float2* __restrict__ shat,
+               const float2* __restrict__ Af, const float2* __restrict__ Ai, typename IO::T* __restrict__ du, LbGrads out, int B, int H,
+               const float2* __restrict__ stw)
 {
-    extern __shared__ uint4 smem_raw[];
-    constexpr int NW = LBB_WAVES, L = 1 << LG, N = L / 2, T = L / 256, LB = LG - 8, TPW = T / NW;
-    float2* sS = reinterpret_cast<float2*>(smem_raw);                 // the spectrum in position order
-    h2* bX0 = reinterpret_cast<h2*>(sS + L);
-    h2 *bX1 = bX0 + L, *bX2 = bX1 + L, *bW2 = bX2 + L, *bW1 = bW2 + L, *bW0 = bW1 + L, *bG = bW0 + L;
+    constexpr int LG = 12, NW = Lb2::NW, NT = Lb2::NT;
+    using G = Geo<LG>;
+    constexpr int T = G::T, N = G::N;
+    extern __shared__ f4 lb2_mem[];
+    _Float16 *exu = reinterpret_cast<_Float16*>(lb2_mem), *exg = exu + T * G::XS, *inu = exg + T * G::XS;
+    _Float16 *ing = inu + T * G::IS, *outb = ing + T * G::IS, *priv = outb + T * G::OS, *mats = priv + NW * 512;
+    float2* sm2 = reinterpret_cast<float2*>(lb2_mem);
     const int sp = blockIdx.x, nsplit = gridDim.x, h = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float2* af = Af + (size_t)h * 3 * NBLK;
-    const float2* ai = Ai + (size_t)h * 3 * NBLK;
-    const Mats A0 = load_mats(af, 4, false, lane), A1 = load_mats(af + NBLK, 4, false, lane);
-    const Mats A2 = load_mats(af + 2 * NBLK, LB, false, lane);
-    const Mats B1 = load_mats(ai + NBLK, 4, false, lane), B2 = load_mats(ai + 2 * NBLK, LB, false, lane);
-    const Mats A0H = load_mats(af, 4, true, lane), A1H = load_mats(af + NBLK, 4, true, lane);
-    const Mats A2H = load_mats(af + 2 * NBLK, LB, true, lane);
-    const Mats B0H = load_mats(ai, 4, true, lane), B1H = load_mats(ai + NBLK, 4, true, lane);
-    const Mats B2H = load_mats(ai + 2 * NBLK, LB, true, lane);
-    stage_spectrum<LG>(sS, shat + (size_t)h * L, tid, NW * 64);
-    const float yscale = exp2f((float)(2 * total_shift(LG) - LG));
-
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const size_t step = (size_t)nsplit * H * (N / 2);
+    const uint32_t* up = reinterpret_cast<const uint32_t*>(u + row_off(sp, h, H, N)) + tid;
+    const uint32_t* gp = reinterpret_cast<const uint32_t*>(dy + row_off(sp, h, H, N)) + tid;
+    uint32_t* dp = reinterpret_cast<uint32_t*>(du ? du + row_off(sp, h, H, N) : nullptr) + tid;
+    const int n = (B - sp + nsplit - 1) / nsplit;                       // rows of this workgroup
+    uint32_t nu[2], ng[2];                                              // words tid and tid + NT of the next row
+    const auto ask = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            nu[j] = up[j * NT];
+            ng[j] = gp[j * NT];
+        }
+        up += step;
+        gp += step;
+    };
+    const auto rows_put = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            row_in<LG>(inu, to_h2<IO>(nu[j]), tid + j * NT);
+            row_in<LG>(ing, to_h2<IO>(ng[j]), tid + j * NT);
+        }
+    };
+    {
+        HeadData<LG> hd[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) hd[j].load(Af, Ai, shat, h, tid + j * NT);
+        ask();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) hd[j].put(sm2, tid + j * NT);
+    }
+    const int trow = 16 * (4 * g + (c >> 2)) + 4 * ((c & 3) ^ g), row = 16 * c + 4 * (g ^ (c >> 2));   // a plain 16 x 16 tile
+    // complex matrices as planes of such tiles: A_1, B_1 of tile t at 2t, 2t + 1; A_2, B_2 behind them
+    const auto mat_put = [&](int m, const Cx& x) {
+        H8P v;
+        v.v = x.re;
+        wr4(mats + m * 512 + row, v.p[0]);
+        v.v = x.im;
+        wr4(mats + m * 512 + 256 + row, v.p[0]);
+    };
+    const auto mat = [&](int m) {                                       // (planes P, Q: P - Q and Q + P as K runs)
+        H8P re, im;
+        re.p[0] = im.p[1] = rd4(mats + m * 512 + row);
+        im.p[0] = rd4(mats + m * 512 + 256 + row);
+        re.u[1] = make_uint2(im.u[0].x ^ 0x80008000u, im.u[0].y ^ 0x80008000u);
+        return Cx{re.v, im.v};
+    };
+    const auto mat_adj = [&](int m) {
+        H8P re, im;
+        re.p[0] = im.p[1] = tr_read(mats + m * 512 + trow);
+        re.p[1] = tr_read(mats + m * 512 + 256 + trow);
+        im.u[0] = make_uint2(re.u[1].x ^ 0x80008000u, re.u[1].y ^ 0x80008000u);
+        return Cx{re.v, im.v};
+    };
+    f4 cr[2], ci[2];                                                    // w_L^(k_0 (16 d_1 + t)), lane k_0, d_1 = 4g ..
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float2 v = stw[stw_offset(LG) + (c << (LG - 4)) + T * (4 * g + r) + 2 * wave + j];
+            cr[j][r] = v.x;
+            ci[j][r] = v.y;
+        }
+    __syncthreads();
+    const Entries<LG> E{sm2, sm2 + 48 * ROW};
+    const float2 one = make_float2(1.f, 0.f);
+    const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i, one); }, lane);
+    const Rl B0H = make_rl([&](int o, int i) { return conj2(E.b0(i, o, one)); }, lane);
+    const h8 A0H = make_cx([&](int o, int i) { return scaled(conj2(E.a0(i, o, one)), G::yscale()); }, lane).re;
+    f4 sr[2], si[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int t = 2 * wave + j;
+        LaneTw<LG> W;
+        W.load(stw, t, lane);
+        mat_put(2 * t, make_cx([&](int o, int i) { return E.a1(o, i, W.w1c); }, lane));
+        mat_put(2 * t + 1, make_cx([&](int o, int i) { return E.b1(o, i, W.w1q[i & 3]); }, lane));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float2 s = sm2[HeadData<LG>::BLK + freq_at<LG>(t, 4 * g + r, c, ROW)];
+            sr[j][r] = s.x;
+            si[j][r] = s.y;
+        }
+    }
+    if (wave < 2) mat_put(2 * T + wave, make_cx([&](int o, int i) { return E.last(wave ? E.B : E.A, o, i); }, lane));
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    f4 qfr[3] = {zero, zero, zero}, qfi[3] = {zero, zero, zero};     // blocks of the forward chain
-    f4 qir[3] = {zero, zero, zero}, qii[3] = {zero, zero, zero};     // blocks of the inverse chain
-    float2 acc_s[TPW][4];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc_s[i][j] = make_float2(0.f, 0.f);
+    f4 a0r = zero, a0i = zero, a2r = zero, a2i = zero, b0r = zero, b0i = zero, b2r = zero, b2i = zero;      // sums of the blocks'
+    f4 a1r[2] = {zero, zero}, a1i[2] = {zero, zero}, b1r[2] = {zero, zero}, b1i[2] = {zero, zero};           // gradients
+    f4 dsr[2] = {zero, zero}, dsi[2] = {zero, zero};
+    _Float16* pv = priv + wave * 512;
+    const auto transposed = [&](const H8P& x) {
+        H8P y;
+        wr4(pv + row, x.p[0]);
+        wr4(pv + row + 256, x.p[1]);
+        y.p[0] = tr_read(pv + trow);
+        y.p[1] = tr_read(pv + trow + 256);
+        return y;
+    };
+    __syncthreads();
+    // both rows' tiles: the padding, d_0 >= 8, stays zero; a row's samples are the other half
+    for (int i = tid; i < T * 128; i += NT) reinterpret_cast<uint32_t*>(inu + (i >> 6) * G::IS + 128)[i & 63] = 0;
+    rows_put();
+    if (n > 1) ask();
+    __syncthreads();
 
-    // tile loops stay rolled here (one iteration up to 2048 points; at 4096 points unrolling them costs more in
-    // spilled registers than the hoisted address arithmetic saves)
-    for (int64_t b = sp; b < B; b += nsplit) {
-        load_row<IO>(bX0, u + row_off(b, h, H, N), N, tid, NW * 64);
-        load_row<IO>(bG, dy + row_off(b, h, H, N), N, tid, NW * 64);
-        __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<1>(bX0, bX1, wave + tt * NW, LG - 4, LG - 4, A0, stw, lane);
-        __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<1>(bX1, bX2, wave + tt * NW, LG - 8, LG - 8, A1, stw, lane);
-        __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            const int pb = (16 * t + (lane & 15)) * 16 + 4 * (lane >> 4), ab = phys(pb);
-            H8U x;
-            x.u = *reinterpret_cast<const uint4*>(&bX2[ab]);
-            f4 yr, yi;
-            blk16(A2, x.v, yr, yi);
-            const float4 s01 = *reinterpret_cast<const float4*>(&sS[ab]);
-            const float4 s23 = *reinterpret_cast<const float4*>(&sS[ab + 2]);
-            const float2 sv[4] = {make_float2(s01.x, s01.y), make_float2(s01.z, s01.w), make_float2(s23.x, s23.y),
-                                  make_float2(s23.z, s23.w)};
-            H8U m;
+    H8P x1t[2], g1t[2];     // kept from a row's first part to its last
+    h4 uo[2], go[2];
+    const auto first = [&]() {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float2 r = cmul(make_float2(yr[j], yi[j]), sv[j]);
-                m.c[j] = pack(r.x, r.y);
+        for (int j = 0; j < 2; ++j) {
+            const int t = 2 * wave + j, own = G::at(t, c, g);          // tile t: row c
+            {
+                const h4 x = tr_read(inu + t * G::IS + trow);
+                uo[j] = rd4(inu + t * G::IS + row);                     // lane d_0, d_1 = 4g ..
+                f4 yr = mm(x, A0.re), yi = mm(x, A0.im);                // lane k_0, d_1 = 4g ..
+                cmul4<false>(yr, yi, cr[j], ci[j]);
+                const H8P x1 = planes(yr, yi);
+                x1t[j] = transposed(x1);                                // lane d_1, k_0 = 4g ..
+                const Cx A1 = mat(2 * t);
+                const H8P x2 = planes(mm(A1.re, x1.v), mm(A1.im, x1.v));            // lane k_0, k_1 = 4g ..
+                wr4(exu + own, x2.p[0]);
+                wr4(exu + own + 256, x2.p[1]);
             }
-            *reinterpret_cast<uint4*>(&bW2[ab]) = m.u;
-            blk16(B2, m.v, yr, yi);
-            H8U o;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float2 r = cmulc(make_float2(yr[j], yi[j]), stage_twiddle(stw, pb + j, LB));
-                o.c[j] = pack(r.x, r.y);
+            {
+                const h4 x = tr_read(ing + t * G::IS + trow);
+                go[j] = rd4(ing + t * G::IS + row);
+                f4 yr = mm(x, B0H.re), yi = mm(x, B0H.im);
+                cmul4<false>(yr, yi, cr[j], ci[j]);
+                const H8P g1 = planes(yr, yi);
+                g1t[j] = transposed(g1);
+                const Cx B1H = mat_adj(2 * t + 1);
+                const H8P g2 = planes(mm(B1H.re, g1.v), mm(B1H.im, g1.v));
+                wr4(exg + own, g2.p[0]);
+                wr4(exg + own + 256, g2.p[1]);
             }
-            *reinterpret_cast<uint4*>(&bW1[ab]) = o.u;
         }
-        __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) stage_tile<2>(bW1, bW0, wave + tt * NW, LG - 8, LG - 4, B1, stw, lane);
-        __syncthreads();
-
-        // back through the inverse chain: G holds the gradient at the output of B_0 (dy, zero above N)
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            outer_tile(bG, bW0, t, LG - 4, qir[0], qii[0], lane);
-            stage_tile<1>(bG, bG, t, LG - 4, LG - 4, B0H, stw, lane);
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            outer_tile(bG, bW1, t, LG - 8, qir[1], qii[1], lane);
-            stage_tile<1>(bG, bG, t, LG - 8, LG - 8, B1H, stw, lane);
-        }
-        __syncthreads();
-        // last block of the inverse chain, the product with the spectrum, last block of the forward chain
+    };
+    const auto middle = [&]() {
+        const Cx A2 = mat(2 * T), B2 = mat(2 * T + 1), A2H = mat_adj(2 * T), B2H = mat_adj(2 * T + 1);
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            const int pb = (16 * t + (lane & 15)) * 16 + 4 * (lane >> 4), ab = phys(pb);
-            outer_tile(bG, bW2, t, 0, qir[2], qii[2], lane);
-            H8U x, x2;
-            x.u = *reinterpret_cast<const uint4*>(&bG[ab]);
-            x2.u = *reinterpret_cast<const uint4*>(&bX2[ab]);
-            f4 yr, yi, ur, ui;
-            blk16(B2H, x.v, yr, yi);
-            blk16(A2, x2.v, ur, ui);                 // the transform of this tile again, instead of a buffer for it
-            const float4 s01 = *reinterpret_cast<const float4*>(&sS[ab]);
-            const float4 s23 = *reinterpret_cast<const float4*>(&sS[ab + 2]);
-            const float2 sv[4] = {make_float2(s01.x, s01.y), make_float2(s01.z, s01.w), make_float2(s23.x, s23.y),
-                                  make_float2(s23.z, s23.w)};
-            H8U o;
+        for (int j = 0; j < 2; ++j) {
+            const int t = 2 * wave + j, mid = G::slot_at(t, c, g), mid_tr = G::slot_at(t, 4 * g + (c >> 2), c & 3);
+            H8P x, xt, y, yt;
+            x.p[0] = tr_read(exu + mid_tr);                             // lane k_1, slots 4g ..
+            x.p[1] = tr_read(exu + mid_tr + 256);
+            xt.p[0] = rd4(exu + mid);                                   // lane slot, k_1 = 4g ..
+            xt.p[1] = rd4(exu + mid + 256);
+            y.p[0] = tr_read(exg + mid_tr);
+            y.p[1] = tr_read(exg + mid_tr + 256);
+            yt.p[0] = rd4(exg + mid);
+            yt.p[1] = rd4(exg + mid + 256);
+            const f4 zr = mm(A2.re, x.v), zi = mm(A2.im, x.v);          // the transform of u: lane k_1, slots 4g ..
+            f4 wr = zr, wi = zi;
+            cmul4<false>(wr, wi, sr[j], si[j]);
+            const H8P w = planes(wr, wi);
+            const H8P wt = transposed(w);
+            const H8P v = planes(mm(w.v, B2.re), mm(w.v, B2.im));       // lane slot, k_1 = 4g ..
+            wr4(exu + mid, v.p[0]);
+            wr4(exu + mid + 256, v.p[1]);
+            outer(yt, wt, b2r, b2i);
+            f4 hr = mm(B2H.re, y.v), hi = mm(B2H.im, y.v);              // gradient at the product with the spectrum
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float2 gv = make_float2(yr[j], yi[j]);
-                const float2 d = cmulc(gv, make_float2(ur[j], ui[j]));
-                acc_s[tt][j].x += d.x;
-                acc_s[tt][j].y += d.y;
-                const float2 r = cmulc(gv, sv[j]);
-                o.c[j] = pack(r.x, r.y);
+            for (int r = 0; r < 4; ++r) {
+                dsr[j][r] += hr[r] * zr[r] + hi[r] * zi[r];
+                dsi[j][r] += hi[r] * zr[r] - hr[r] * zi[r];
             }
-            *reinterpret_cast<uint4*>(&bG[ab]) = o.u;
-            // the tile just written is read back with the columns as the K dimension: same wave, LDS keeps the order
-            outer_tile(bG, bX2, t, 0, qfr[2], qfi[2], lane);
-            stage_tile<2>(bG, bG, t, 0, LG - 8, A2H, stw, lane);
+            cmul4<true>(hr, hi, sr[j], si[j]);
+            const H8P q = planes(hr, hi);
+            const H8P qt = transposed(q);
+            const H8P p = planes(mm(q.v, A2H.re), mm(q.v, A2H.im));
+            wr4(exg + mid, p.p[0]);
+            wr4(exg + mid + 256, p.p[1]);
+            outer(qt, xt, a2r, a2i);
         }
-        __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            outer_tile(bG, bX1, t, LG - 8, qfr[1], qfi[1], lane);
-            stage_tile<2>(bG, bG, t, LG - 8, LG - 4, A1H, stw, lane);
+    };
+    const auto last = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int t = 2 * wave + j, own = G::at(t, c, g), own_tr = G::at(t, 4 * g + (c >> 2), c & 3);
+            {
+                H8P v, vt;
+                v.p[0] = rd4(exu + own);                                // lane k_0, k_1 = 4g ..
+                v.p[1] = rd4(exu + own + 256);
+                vt.p[0] = tr_read(exu + own_tr);                        // lane k_1, k_0 = 4g ..
+                vt.p[1] = tr_read(exu + own_tr + 256);
+                const Cx B1 = mat(2 * t + 1);
+                f4 yr = mm(B1.re, v.v), yi = mm(B1.im, v.v);            // lane k_0, d_1 = 4g ..
+                cmul4<true>(yr, yi, cr[j], ci[j]);
+                const H8P w0 = planes(yr, yi);
+                outer(g1t[j], vt, b1r[j], b1i[j]);
+                b0r = __builtin_amdgcn_mfma_f32_16x16x16f16(go[j], w0.p[0], b0r, 0, 0, 0);
+                b0i = __builtin_amdgcn_mfma_f32_16x16x16f16(go[j], w0.p[1], b0i, 0, 0, 0);     // (minus the imaginary part)
+            }
+            {
+                H8P v, vt;
+                v.p[0] = rd4(exg + own);
+                v.p[1] = rd4(exg + own + 256);
+                vt.p[0] = tr_read(exg + own_tr);
+                vt.p[1] = tr_read(exg + own_tr + 256);
+                const Cx A1H = mat_adj(2 * t);
+                f4 yr = mm(A1H.re, v.v), yi = mm(A1H.im, v.v);          // lane k_0, d_1 = 4g ..
+                cmul4<true>(yr, yi, cr[j], ci[j]);
+                const H8P g6t = planes(yr, yi);
+                outer(vt, x1t[j], a1r[j], a1i[j]);
+                a0r = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[0], uo[j], a0r, 0, 0, 0);
+                a0i = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[1], uo[j], a0i, 0, 0, 0);
+                put_out<IO>(outb + t * G::OS, mm(transposed(g6t).v, A0H), lane);       // (operand: lane d_1, k_0 = 4g ..)
+            }
         }
+    };
+    const auto row_done = [&]() {
+        if (!du) return;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) put_once(dp + j * NT, row_out<LG>(outb, tid + j * NT));
+        dp += step;
+    };
+    const auto rows_in = [&](int b) {                                   // row b + 1; row b + 2 asked for
+        if (b + 1 < n) rows_put();
+        if (b + 2 < n) ask();
+    };
+    first();
+    __syncthreads();
+    middle();
+    rows_in(0);
+    __syncthreads();
+    for (int b = 1; b < n; ++b) {
+        last();
+        first();
         __syncthreads();
-#pragma unroll 1
-        for (int tt = 0; tt < TPW; ++tt) {
-            const int t = wave + tt * NW;
-            outer_tile(bG, bX0, t, LG - 4, qfr[0], qfi[0], lane);
-            if (du) stage_tile<0>(bG, bG, t, LG - 4, 0, A0H, stw, lane);
-        }
-        __syncthreads();
-        if (du) store_row<IO>(bG, du + row_off(b, h, H, N), N, yscale, tid, NW * 64);
+        row_done();
+        middle();
+        rows_in(b);
         __syncthreads();
     }
+    last();
+    __builtin_amdgcn_sched_barrier(0);       // (no registers for the sums' twiddles in front of it)
+    LaneTw<LG> W[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) W[j].load(stw, 2 * wave + j, lane);
+    __syncthreads();
+    row_done();
 
-    // gradient of the spectrum: every position is owned by one lane
     const size_t at = (size_t)sp * H + h;
-    float2* ps = out.shat + at * L;
+    if (out.shat) {
+        float2* ps = out.shat + at * G::L;
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) {
-        const int t = wave + tt * NW;
-        const int pb = (16 * t + (lane & 15)) * 16 + 4 * (lane >> 4);
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (out.shat) ps[freq_of<LG>(pb + j)] = make_float2(acc_s[tt][j].x * yscale, acc_s[tt][j].y * yscale);
+            for (int r = 0; r < 4; ++r)
+                ps[freq_at<LG>(2 * wave + j, 4 * g + r, c)] = make_float2(dsr[j][r] * G::yscale(), dsi[j][r] * G::yscale());
     }
-    // gradients of the blocks: the waves add their 16 x 16 sums into one LDS copy, one wave after the other
-    float2* red = reinterpret_cast<float2*>(smem_raw);          // [6][256]
-    for (int w = 0; w < NW; ++w) {
-        if (wave == w) {
+    // the waves' sums of one block of either chain, [chain][wave][entry]; then entry by entry in wave order
+    __syncthreads();
+    const auto put_sums = [&](int s) {
+        float2* buf = sm2 + (s & 1) * 2 * NW * NBLK;
 #pragma unroll
-            for (int s = 0; s < 3; ++s)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int e = (4 * (lane >> 4) + jj) * 16 + (lane & 15);       // entry [i][j]
-                    float2 f = make_float2(qfr[s][jj], qfi[s][jj]), i2 = make_float2(qir[s][jj], qii[s][jj]);
-                    if (w > 0) {
-                        f = cadd(f, red[s * NBLK + e]);
-                        i2 = cadd(i2, red[(3 + s) * NBLK + e]);
-                    }
-                    red[s * NBLK + e] = f;
-                    red[(3 + s) * NBLK + e] = i2;
-                }
+        for (int r = 0; r < 4; ++r) {
+            const int e = (4 * g + r) * 16 + c;
+            float2 f, q;
+            if (s == 0) {
+                f = make_float2(a0r[r], a0i[r]);
+                q = make_float2(b0r[r], -b0i[r]);
+            } else if (s == 1) {
+                f = cadd(cmulc(make_float2(a1r[0][r], a1i[0][r]), W[0].w1q[r]), cmulc(make_float2(a1r[1][r], a1i[1][r]), W[1].w1q[r]));
+                q = cadd(cmul(make_float2(b1r[0][r], b1i[0][r]), W[0].w1c), cmul(make_float2(b1r[1][r], b1i[1][r]), W[1].w1c));
+            } else {
+                f = make_float2(a2r[r], a2i[r]);
+                q = make_float2(b2r[r], b2i[r]);
+            }
+            buf[wave * NBLK + e] = f;
+            buf[(NW + wave) * NBLK + e] = q;
         }
+    };
+    put_sums(0);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
         __syncthreads();
-    }
-    for (int e = tid; e < 6 * NBLK; e += NW * 64) {
-        const int s = (e / NBLK) % 3;
-        const float sc = yscale / (float)(1 << stage_shift(s == 2 ? LB : 4));
-        float2* q = e < 3 * NBLK ? out.qf : out.qi;
-        if (q) q[at * out.q_stride + e % (3 * NBLK)] = make_float2(red[e].x * sc, red[e].y * sc);
+        if (s < 2) put_sums(s + 1);
+        const float sc = G::yscale() / (float)(1 << stage_shift(4));
+        const int chain = tid / NBLK, e = tid % NBLK;                   // (as many threads as entries)
+        static_assert(NT == 2 * NBLK, "a thread takes one entry");
+        float2* q = chain ? out.qi : out.qf;
+        if (!q) continue;
+        const float2* p = sm2 + (s & 1) * 2 * NW * NBLK + chain * NW * NBLK + e;
+        float2 a = make_float2(0.f, 0.f);
+        for (int w = 0; w < NW; ++w) a = cadd(a, p[w * NBLK]);
+        q[at * out.q_stride + s * NBLK + e] = make_float2(a.x * sc, a.y * sc);
     }
 }
 
@@ -1071,12 +996,10 @@ hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float*
 {
     using T = typename IO::T;
     if constexpr (LG == 12) {
-        const size_t lds = (size_t)(1 << LG) * (7 * sizeof(h2) + sizeof(float2));
-        hipError_t e = set_lds(lb_bwd_lds_kernel<LG, IO>, lds);
+        const hipError_t e = set_lds(lb_bwd2_kernel<IO>, Lb2::lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((lb_bwd_lds_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(LBB_WAVES * 64), lds, st,
-                           (const T*)dy, (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du,
-                           out, B, H, tb.stw);
+        hipLaunchKernelGGL((lb_bwd2_kernel<IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(Lb2::NT), Lb2::lds, st, (const T*)dy,
+                           (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du, out, (int)B, (int)H, tb.stw);
     } else {
         hipLaunchKernelGGL((lb_bwd_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(64 << (LG - 8)), 0, st,
                            (const T*)dy, (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du, out,
@@ -1088,8 +1011,8 @@ hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float*
 }  // namespace
 
 // Shares of a head's rows: the number that ends first, ceil(512 / H) at most, where 8 / T workgroups of T waves run on each of
-// 256 compute units.  A share's matrices and sums take as long as about six rows (8.5 us at N = 1024, a row 1.6), two of the
-// slower rows of N = 2048; more than one share is a second launch.
+// 256 compute units.  A share's matrices and sums take as long as about six rows (8.5 us at N = 1024, a row 1.6), five at N = 2048
+// (15 us, a row 3.2); more than one share is a second launch, as long as three rows or two.
 static int64_t most_shares(int64_t B, int64_t H) { return (512 + H - 1) / H < B ? (512 + H - 1) / H : B; }
 static int64_t turns(int64_t workgroups, int64_t N)
 {
@@ -1098,7 +1021,7 @@ static int64_t turns(int64_t workgroups, int64_t N)
 }
 int lbfly_nsplit(int64_t B, int64_t H, int64_t N)
 {
-    const int64_t setup = N == 2048 ? 2 : 6, launch = N == 2048 ? 1 : 3;
+    const int64_t setup = N == 2048 ? 5 : 6, launch = N == 2048 ? 2 : 3;
     int64_t best = 1, best_t = -1;
     for (int64_t n = 1; n <= most_shares(B, H); ++n) {
         const int64_t t = turns(n * H, N) * ((B + n - 1) / n + setup) + (n > 1 ? launch : 0);

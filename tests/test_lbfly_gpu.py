@@ -213,3 +213,25 @@ def test_spectrum_and_its_adjoint_in_fp32(N):
         assert wl.rel_l2(shat.cpu().numpy().reshape(H, -1).astype(np.float64), np.stack([want.real, want.imag], -1).reshape(H, -1)) <= tol
         assert wl.rel_l2(dk.cpu().numpy().astype(np.float64), wdk) <= tol
         assert np.max(np.abs(dD.cpu().numpy() - wdD)) <= tol * np.sqrt(4 * N) * 4
+
+
+def test_two_tiles_a_wave():
+    """N = 2048, where a wave of the backward kernel has two tiles: workgroups of one, two and three rows (the pipeline's ends), with
+    and without the optional outputs."""
+    N = 2048
+    for io, B, H in ((wl.F16, 1, 1), (wl.BF16, 2, 600), (wl.F16, 3, 520)):
+        u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=6)
+        g = _run(u_s, dy_s, k, D, Af32, Ai32, io)
+        for name, x in g.items():
+            assert np.all(np.isfinite(x)), name
+        heads = sorted({0, H // 2, H - 1})
+        shat = lbfly.spectrum(k[heads], D[heads])
+        rdu, rdshat, rdAf, rdAi = lbfly.lbfly_bwd(dy_v[:, heads], u_v[:, heads], shat, Af[heads], Ai[heads])
+        label = f"lbfly two tiles B={B} H={H}"
+        _compare({"du": g["du"][:, heads], "dshat": _ri(g["dshat"][heads])}, {"du": rdu, "dshat": _ri(rdshat)}, TOL[io], label)
+        _check_blocks(g["dAf"][heads], rdAf, N, TOL[io], label + " dAf")
+        _check_blocks(g["dAi"][heads], rdAi, N, TOL[io], label + " dAi")
+    only_du = _run(u_s, dy_s, k, D, Af32, Ai32, io, want=(True, False, False, False))
+    assert np.array_equal(only_du["du"], g["du"]) and np.all(np.isnan(only_du["dshat"])) and np.all(np.isnan(only_du["dAi"]))
+    no_du = _run(u_s, dy_s, k, D, Af32, Ai32, io, want=(False, True, True, True))
+    assert np.all(np.isnan(no_du["du"])) and np.array_equal(no_du["dshat"], g["dshat"]) and np.array_equal(no_du["dAf"], g["dAf"])
