@@ -461,19 +461,22 @@ int longconv_bwd_gated(const void* dy, const void* g, const void* u, const float
     if (pl.engine == ENGINE_MFMA && pl.fuse_bwd && pl.order.wave_lg && du && dg && (dk || dD))      // all of it from one kernel
         return bwd_impl(dy, u, k, D, kspec, du, dk, dD, B, H, N, io, workspace, base, stream, 0, g, dg);
     if (du || dk || dD) {
-        // dz = dy * g is what the convolution's backward pass receives
-        void* dz = (char*)workspace + base;
-        if ((du || dk) && note(ew_mul(dy, g, dz, n, io, st), "gate") != hipSuccess) return LONGCONV_ERR_HIP;
-        if (du || dk) {
+        // dz = dy * g is what the convolution's backward pass receives.  dD = sum dy g u comes from the same reads, straight from
+        // the three tensors: the rounding of dz to the I/O dtype stays out of it.  Its partial sums lie where the backward pass
+        // puts its spectrum (2N numbers a head), if it has to make one, later.
+        void* dz = du || dk ? (char*)workspace + base : nullptr;
+        Problem pr{B, H, N, io, (int)((B + 1) / 2)};
+        static_assert(GATE_SHARES <= 2 * 256, "the partial sums fit the spectrum of the shortest rows");
+        if (dD && u) {
+            if (note(gate_bwd(dy, g, u, dz, dD, (float*)workspace, pr, st), "gate dD") != hipSuccess) return LONGCONV_ERR_HIP;
+        } else if (dz && note(ew_mul(dy, g, dz, n, io, st), "gate") != hipSuccess) {
+            return LONGCONV_ERR_HIP;
+        }
+        if (dz) {
             s = longconv_bwd(dz, u, k, D, kspec, du, dk, nullptr, B, H, N, io, workspace, base, stream);
             if (s != LONGCONV_OK) return s;
         }
-        if (dD) {
-            // dD = sum dy g u straight from the three tensors: the rounding of dz to the I/O dtype stays out of it
-            if (!u) return LONGCONV_ERR_NULL;
-            Problem pr{B, H, N, io, (int)((B + 1) / 2)};
-            if (note(head_dot3(dy, g, u, dD, pr, st), "gate dD") != hipSuccess) return LONGCONV_ERR_HIP;
-        }
+        if (dD && !u) return LONGCONV_ERR_NULL;
     }
     if (dg) {
         // dg = dy * z, z the ungated output recomputed: the gated forward with dy in the gate's place

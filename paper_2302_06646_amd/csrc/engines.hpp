@@ -65,8 +65,9 @@ hipError_t head_dot(const void* dy, const void* u, float* dD, const Problem& pr,
 // dD[h] = sum of the per-block partials written by outer_fwd.
 hipError_t reduce_dD(const float* part, float* dD, int64_t H, int nblk, hipStream_t st);
 
-// dD[h] = sum_b sum_t dy g u in fp32, one workgroup per head, fixed order (gated layer) (multipass.hip)
-hipError_t head_dot3(const void* dy, const void* g, const void* u, float* dD, const Problem& pr, hipStream_t st);
+// dz = dy g (not written if null) and dD[h] = sum_b sum_t dy g u in fp32, fixed order (gated layer); part: H * GATE_SHARES floats (gate.hip)
+constexpr int64_t GATE_SHARES = 256;
+hipError_t gate_bwd(const void* dy, const void* g, const void* u, void* dz, float* dD, float* part, const Problem& pr, hipStream_t st);
 
 // out = a * b, element by element, n elements of the I/O dtype (n a multiple of 8; out may alias a or b) (gate.hip)
 hipError_t ew_mul(const void* a, const void* b, void* out, size_t n, int io, hipStream_t st);

@@ -141,3 +141,41 @@ def test_optional_outputs_and_error_codes():
     with pytest.raises(lc.LongconvError, match="workspace"):
         lc.longconv_bwd_gated(dy, g, u, k, D, torch.empty_like(u), None, None, None, small)
     assert lc.longconv_workspace_bytes(B, H, N, io, 2) >= lc.longconv_workspace_bytes(B, H, N, io, 1) + B * H * N * 2
+
+
+# dD by shares of a head's samples, beside dz where the backward pass needs that: one share, several even and uneven ones, as many as
+# there may be; u at any address where dD alone is asked for
+@pytest.mark.parametrize("N,io,B,H", [(8192, wl.F16, 1, 1), (8192, wl.BF16, 3, 1), (16384, wl.F32, 5, 2), (32768, wl.F16, 7, 3),
+                                      (131072, wl.BF16, 2, 3), (65536, wl.F16, 40, 1)])
+def test_shares_of_dD(N, io, B, H):
+    gen = torch.Generator(device="cuda").manual_seed(N + B)
+    td = {wl.F32: torch.float32, wl.F16: torch.float16, wl.BF16: torch.bfloat16}[io]
+    rand = lambda *n: torch.randn(*n, generator=gen, device="cuda").to(td)
+    dy, g, u = rand(B, H, N), rand(B, H, N), rand(B, H, N)
+    k, D = torch.randn(H, N, generator=gen, device="cuda") / N, torch.randn(H, generator=gen, device="cuda")
+    want = torch.zeros(H, dtype=torch.float64, device="cuda")
+    size = torch.zeros(H, dtype=torch.float64, device="cuda")
+    for b in range(B):
+        p = dy[b].double() * g[b].double() * u[b].double()
+        want += p.sum(-1)
+        size += p.abs().sum(-1)
+    ws = lc.new_workspace(B, H, N, io, 2)
+    outs = []
+    for all_of_it in (True, False):
+        du, dk, dD = torch.empty_like(u), torch.empty_like(k), torch.full_like(D, float("nan"))
+        lc.longconv_bwd_gated(dy, g, u, k, D, du if all_of_it else None, dk if all_of_it else None, dD, None, ws)
+        if all_of_it:
+            # the same dz as the ungated pass gets from torch: products of two numbers of the I/O type, rounded once
+            du2, dk2 = torch.empty_like(u), torch.empty_like(k)
+            lc.longconv_bwd((dy.float() * g.float()).to(td), u, k, D, du2, dk2, None, lc.new_workspace(B, H, N, io, 1))
+            assert torch.equal(du, du2) and torch.equal(dk, dk2)
+        outs.append(dD)
+    odd = torch.empty(B * H * N + 1, dtype=td, device="cuda")[1:].view(B, H, N).copy_(u)
+    dD = torch.full_like(D, float("nan"))
+    lc.longconv_bwd_gated(dy, g, odd, k, D, None, None, dD, None, ws)
+    outs.append(dD)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    # a lane's chain of at most per / 256 pieces of 8 terms in fp32, then two short trees; errors of a sum of terms of either sign
+    # stay below eps / 2 times the chain's length times the sum of magnitudes, and are far below it
+    chain = 8 * (B * N // 8 // 256 // max(1, min(256, B * N // 8192)) + 2) + 16
+    assert torch.all((outs[0].double() - want).abs() <= 6e-8 * chain * size)
