@@ -233,7 +233,7 @@ static WsLayout carve(int64_t B, int64_t H, int64_t N, const Plan& pl, bool back
     w.nblk = (int)(npairs * ((size_t(1) << pl.log2L2) / 256));
     const size_t npart = (size_t)w.nblk > (size_t(1) << pl.log2R) ? (size_t)w.nblk : (size_t(1) << pl.log2R);
     w.dpart = off; if (pl.log2R && backward && outer_a) off += up256((size_t)H * npart * sizeof(float));
-    w.chunk = off; if (backward && chunks) off += up256((size_t)chunk_bwd_shares(B, H, pl.log2R) * (H << pl.log2R) * 2 * sizeof(float));
+    w.chunk = off; if (backward && chunks) off += up256((size_t)chunk_bwd_shares(B, H, pl.log2R, false) * (H << pl.log2R) * 2 * sizeof(float));
     const size_t shares = backward ? dk_room(B, H, pl) : 1;
     w.zbuf = off;
     if (backward && pl.order.coop_lg && outer_a) off += up256((size_t)H * L * sizeof(__half2));
@@ -578,9 +578,13 @@ static int bwd_impl(const void* dy, const void* u, const float* k, const float* 
         prc.max_a = mx_u;
         prc.max_b = mx_dy;
         prc.spec_exp = du1 ? spec_exp_ptr(ks, H, size_t(1) << pl.log2L, pl) : nullptr;
-        int* exps = (int*)(base + w.chunk);
-        float* dD_part = (float*)exps + (size_t)chunk_bwd_shares(B, H, pl.log2R) * (H << pl.log2R);
-        if (note(chunk_bwd(dy, u, ks, du1, base + w.ws1, dk, dD, base + w.wsA, exps, dD_part, prc, pl, tb, st), "bwd") != hipSuccess)
+        // The workspace has room for the results of two shares of a head's rows, 4 H N bytes each.  More of them, and the numbers that
+        // go with them (at most 2 KB), wait in the 2 B H N bytes of du, which is written behind them from start to end.
+        const int ns = chunk_bwd_shares(B, H, pl.log2R, du != nullptr);
+        char* parts = ns > 2 ? (char*)du : base + w.wsA;
+        int* exps = (int*)(ns > 2 ? parts + (size_t)ns * H * N * 4 : base + w.chunk);
+        float* dD_part = (float*)exps + (size_t)ns * (H << pl.log2R);
+        if (note(chunk_bwd(dy, u, ks, du1, base + w.ws1, dk, dD, parts, exps, dD_part, ns, prc, pl, tb, st), "bwd") != hipSuccess)
             return LONGCONV_ERR_HIP;
         if (du1) return LONGCONV_OK;
     } else if (want_dkD) {

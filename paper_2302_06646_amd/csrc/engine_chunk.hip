@@ -873,13 +873,27 @@ hipError_t chunk_conv(const void* in, const float2* kspec, void* out, void* ws, 
     return hipErrorInvalidValue;
 }
 
-// Two shares of a head's rows where one leaves half the device idle (more would want more workspace than pairs of rows did)
-int chunk_bwd_shares(int64_t B, int64_t H, int log2R) { return B > 1 && (H << log2R) <= 128 ? 2 : 1; }
+// Shares of a head's rows where one leaves at least half of the device idle (a compute unit holds one workgroup): two, or (more: where
+// their results find room) the number that ends first, a row 12 us and another share 2 in chunk_dk_kernel, which reads all of them.
+// Steps, two shares at most and now: B=64, H=4, N=65536 bf16 614 -> 267 us, B=31, H=12 fp16 355 -> 228; B=64, H=4, N=32768 354 -> 134,
+// B=10, H=21 137 -> 120; B=16, H=7, N=131072 bf16 359 -> 298; B=7, H=4, N=65536 101.6 -> 90.3.
+int chunk_bwd_shares(int64_t B, int64_t H, int log2R, bool more)
+{
+    int64_t most = 256 / (H << log2R);
+    if (most < 2 || B < 2) return 1;
+    if (!more || most > (B - 1) / 2) most = more && (B - 1) / 2 > 2 ? (B - 1) / 2 : 2;
+    int64_t best = 2, best_t = 6 * ((B + 1) / 2) + 2;
+    for (int64_t s = 3; s <= most; ++s) {
+        const int64_t t = 6 * ((B + s - 1) / s) + s;
+        if (t < best_t) { best = s; best_t = t; }
+    }
+    return (int)best;
+}
 
 hipError_t chunk_bwd(const void* dy, const void* u, const float2* kspec, void* du, void* ws_du, float* dk, float* dD, void* ws_A,
-                     int* exps, float* dD_part, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
+                     int* exps, float* dD_part, int ns, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
-    const int ns = chunk_bwd_shares(pr.B, pr.H, pl.log2R), R = 1 << pl.log2R;
+    const int R = 1 << pl.log2R;
     if (du && R == 2) return hipErrorInvalidValue;   // (rows of 32768 samples have their spectrum in another order)
     hipError_t e = hipErrorInvalidValue;
     void *wd = du ? ws_du : nullptr, *wa = dk ? ws_A : nullptr;

@@ -185,9 +185,10 @@ hipError_t chunk_conv(const void* in, const float2* kspec, void* out, void* ws, 
 hipError_t chunk_rows(const void* ws, void* out, const Problem& pr, int R, hipStream_t st);
 // du (with ws_du as ws above and pr.spec_exp; may be null), dk and dD (may be null).  Each share of a head's rows leaves
 // 4 H N bytes in ws_A and H N / 16384 numbers in exps and dD_part.  pr.max_a, pr.max_b: of u and dy
-int chunk_bwd_shares(int64_t B, int64_t H, int log2R);
+// more: for more than (B - 1) / 2 of them there is no room, otherwise for two
+int chunk_bwd_shares(int64_t B, int64_t H, int log2R, bool more);
 hipError_t chunk_bwd(const void* dy, const void* u, const float2* kspec, void* du, void* ws_du, float* dk, float* dD, void* ws_A,
-                     int* exps, float* dD_part, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
+                     int* exps, float* dD_part, int ns, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);
 
 // ---- cooperative chained matrix-core kernels for 2^13 <= L2 <= 2^15 (engine_coop.hip) --------
 constexpr int COOP_MIN_LOG2 = 13, COOP_MAX_LOG2 = 15;

@@ -136,3 +136,19 @@ def test_dk_of_rows_with_a_mean(N):
     _, rdk, rdD = oracle.longconv_bwd(dy, u, inp.k.astype(np.float64), inp.D.astype(np.float64))
     _, dk, dD = g.bwd(du=False)
     _compare({"dk": dk, "dD": dD}, {"dk": rdk, "dD": rdD}, TOL[wl.F16], f"mean N{N}", DD_TOL)
+
+
+# more than two shares of a head's rows, whose results wait in du: three of uneven rows, as many as half the batch, du by a kernel of its
+# own (N = 32768, and without fuse_bwd); without du there are two
+@pytest.mark.parametrize("B,H,N,io,fuse", [(7, 1, 65536, wl.F16, 1), (16, 2, 65536, wl.BF16, 1), (9, 3, 131072, wl.BF16, 1), (11, 2, 32768, wl.F16, 1),
+                                           (23, 1, 32768, wl.BF16, 1), (9, 1, 65536, wl.F16, 0)])
+def test_shares_that_wait_in_du(B, H, N, io, fuse):
+    lc.longconv_set_option("fuse_bwd", fuse)
+    inp = wl.generate(_w(N=N, dtype=io), B=B, H=H)
+    check_full(inp)
+    g = GpuRun(inp)
+    first, again = g.bwd(), g.bwd()
+    assert all(np.array_equal(a, b) for a, b in zip(first, again))
+    du, dk, dD = g.bwd(du=False)
+    rdu, rdk, rdD = oracle.longconv_bwd(inp.dy, inp.u, inp.k.astype(np.float64), inp.D.astype(np.float64))
+    _compare({"dk": dk, "dD": dD}, {"dk": rdk, "dD": rdD}, TOL[io], f"two shares N{N}", DD_TOL)
