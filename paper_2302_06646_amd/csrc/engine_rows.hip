@@ -991,13 +991,15 @@ __device__ __forceinline__ int acc_reduce(float2 (&acc)[NA][4], int eref, float2
 // and dD from one read of dy and u.  Per row: W = transform of dy, U = transform of u, du = inverse of W conj(K),
 // A += conj(U) W in fp32 registers; dk is one inverse transform of A at the end.  Software pipeline as in rconv_kernel:
 // phase 1 of both rows t, phase 2 of rows t - 1, phase 3 of du's row t - 2, row t - 3 stored, one barrier per row.
-// NGRP groups of waves take every NGRP-th row and add their A at the end in group order.
+// NGRP groups of waves take every NGRP-th row; at the end they add their A in group order or, as two shares in one workgroup (see
+// rows_bwd_nsplit), each turn their A into a row of dk, and these are added as those of two workgroups are.
 // GATE (gated layer): dy is replaced by dz = dy g (rounded to the I/O dtype) as the rows arrive, dD sums dy g u in fp32,
 // and U's own inverse of U K gives z for dg = dy z.
 // -------------------------------------------------------------------------------------
 template <int LG, bool GATE, bool WIDE> struct BwdCfg {
     // WIDE: twice the groups, for launches that give a compute unit one workgroup; N = 4096 has no LDS for them
     static constexpr bool can_widen = LG < 12;
+    static constexpr bool can_pair = LG == 11 && WIDE;      // two shares in one workgroup
     static constexpr int NGRP = (LG == 10 ? 2 : 1) * (WIDE ? 2 : 1), NWV = NGRP * RC<LG>::NWR;
     // LDS words of a group: two exchange buffers, two rows on the way in and two on the way out for each tensor
     static constexpr int GW = 4 * RC<LG>::XW + (GATE ? 8 : 6) * RC<LG>::SW;
@@ -1013,7 +1015,7 @@ struct BwdArgs {
     T* dg;
     float* dk;
     float* dD;
-    int B, H, nsplit;
+    int B, H, nsplit, paired;
     float dkscale;
     uint32_t pad;
     const uint4* tab;
@@ -1249,32 +1251,35 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
     if (lane == 0) dred[wave] = dsum;
-    int etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
+    const bool paired = Q::can_pair && q.paired;
+    const int nsum = paired ? NGRP : 1;                  // sums A that are turned into a row of dk, each by its group
+    int etop = BF ? eref : 0;
+    if (!paired) etop = acc_reduce<2, NWR, NGRP, BF>(acc, eref, reinterpret_cast<float2*>(lds), erefs, wave, lane);
     const size_t ho = (size_t)split * H + h;
-    uint32_t* peaks = mxs;                               // [NWR] (the rows' patterns are done with)
+    uint32_t* peaks = mxs;                               // [nsum * NWR] (the rows' patterns are done with)
     const uint32_t peak = acc_peak<2>(acc);
-    if (lane == 0 && grp == 0) peaks[wave] = peak;
+    if (lane == 0 && grp < nsum) peaks[wave] = peak;
     __syncthreads();                                     // (the reduction's words lie in the buffers that follow, too)
     if (q.dk) {
-        uint32_t m = peaks[0];
+        if (grp < nsum) {
+            uint32_t m = peaks[grp * NWR];
 #pragma unroll
-        for (int w = 1; w < NWR; ++w) m = max(m, peaks[w]);
-        const int ea = __builtin_amdgcn_readfirstlane(acc_exponent(m));
-        etop += ea;
-        float* fs = reinterpret_cast<float*>(lds + 2 * C::XW);        // the row of dk in the u buffers of the first group
-        if (grp == 0) {
+            for (int w = 1; w < NWR; ++w) m = max(m, peaks[grp * NWR + w]);
+            const int ea = __builtin_amdgcn_readfirstlane(acc_exponent(m));
+            etop += ea;
             H8U mm[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mm[k].w[r] = pack_h2(ldexpf(acc[k][r].y, -ea), ldexpf(acc[k][r].x, -ea));
-            phase2_inv<LG>(lds + xpo, K, mm);
+            phase2_inv<LG>(xd + xpo, K, mm);
         }
         __syncthreads();
-        if (grp == 0) {
+        float* fs = reinterpret_cast<float*>(xu);        // the row of dk in the group's u buffers
+        if (grp < nsum) {
             H8U m3[2];
             f4 v[2];
-            phase3_read<LG>(lds + xwo, m3);
+            phase3_read<LG>(xd + xwo, m3);
             phase3<LG>(m3, K, v);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -1284,15 +1289,21 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
         __syncthreads();
         const uint32_t kb = (pad ? C::N / 2 : C::N) * 4u;
         const rsrc_t d = make_rsrc(reinterpret_cast<const char*>(q.dk) + ho * kb, kb);
+        fs = reinterpret_cast<float*>(lds + 2 * C::XW);
         for (int i = threadIdx.x; i < C::N / 4; i += Q::NWV * 64) {
             const uint32_t e = elem_of(4u * i, pad);
-            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u4v*>(fs + 4 * i), d,
-                                                   (int)(e == NOWHERE ? NOWHERE : 4u * e), 0, 0);
+            f4 v = *reinterpret_cast<const f4*>(fs + 4 * i);
+            if (paired) v += *reinterpret_cast<const f4*>(fs + Q::GW + 4 * i);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, v), d, (int)(e == NOWHERE ? NOWHERE : 4u * e), 0, 0);
         }
     }
     if (threadIdx.x == 0 && q.dD) {
         float s = 0.f;
-        for (int w = 0; w < Q::NWV; ++w) s += dred[w];
+        for (int g = 0; g < nsum; ++g) {
+            float t = 0.f;
+            for (int w = 0; w < Q::NWV / nsum; ++w) t += dred[g * NWR + w];
+            s += t;
+        }
         q.dD[ho] = s;
     }
 }
@@ -1712,14 +1723,18 @@ static int rows_bwd_nsplit_many(int64_t B, int64_t H, int lg, bool gated)
     }
     return best;
 }
+// N = 2048: two shares that would meet on one compute unit are the two groups of waves of one workgroup instead (wide_bwd), without
+// a launch to add them up.  Each group takes its sum through an inverse transform (fp16 operands) of its own and the two rows of dk
+// are added in fp32, as two shares' are: the same dk and dD to the bit (one inverse of both sums moved dk by 6e-4, the size of that
+// rounding, neither nearer to nor farther from the exact one: 8.4e-4) in the same time, since the second group has nothing else to do.
+// Steps, two workgroups and one: B=24, H=256 bf16 62.8 -> 56.8 us, gated 74.4 -> 67.4; 32 x 32 images, B=64, H=200 fp16 94.9 -> 90.3.
+static bool rows_bwd_paired(int64_t B, int64_t H, int lg, bool gated)
+{
+    return lg == 11 && many_heads(H, lg) && H <= compute_units() && rows_bwd_nsplit_many(B, H, lg, gated) == 2;
+}
 int rows_bwd_nsplit(int64_t B, int64_t H, int lg, bool gated)
 {
-    if (many_heads(H, lg)) {
-        // N = 2048: instead of two shares on one compute unit, two groups of waves in one workgroup (wide_bwd) and no sum of
-        // partial results: B=24, H=256 bf16 step 60.5 -> 57.2 us, gated 78.9 -> 73.8; B=64 120.1 -> 118.4
-        const int s = rows_bwd_nsplit_many(B, H, lg, gated);
-        return lg == 11 && H <= compute_units() && s == 2 ? 1 : s;
-    }
+    if (many_heads(H, lg)) return rows_bwd_paired(B, H, lg, gated) ? 1 : rows_bwd_nsplit_many(B, H, lg, gated);
     const bool wave_rows = lg == 10 && !gated;
     const int ngrp = lg >= 11 ? 1 : lg == 10 && gated ? 2 : 4;
     const int64_t units = lg == 8 ? (B + 1) / 2 : B;
@@ -1782,7 +1797,7 @@ static hipError_t bwd_io(const void* dy, const void* u, const float2* kspec, voi
 {
     using T = typename IO::T;
     const BwdArgs<T> a = {(const T*)dy, (const T*)u, (const T*)pr.gate, kspec, (T*)du, (T*)dg, dk, dD, (int)pr.B, (int)pr.H, nsplit,
-                          pl.dkscale, pr.pad, tab};
+                          rows_bwd_paired(pr.B, pr.H, pl.order.wave_lg, pr.gate != nullptr) ? 1 : 0, pl.dkscale, pr.pad, tab};
 #define RF(L) rbwd_go<L, IO>
     ROWS_SWITCH(pl.order.wave_lg, RF, (a, st))
 #undef RF

@@ -4,11 +4,13 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import paper_2302_06646_amd as lc
 import workloads as wl
 import test_gated_gpu as tg
-from gpu_harness import DD_TOL, TOL, GpuRun, _compare, sample_heads
+from gpu_harness import _TD, DD_TOL, TOL, GpuRun, _compare, sample_heads
 from oracle import gated
 
 pytestmark = pytest.mark.gpu
@@ -73,3 +75,31 @@ def test_groups_of_waves(N, B, H, io):
     du, dk, dD = GpuRun(inp).bwd()
     rdu, rdk, rdD = oracle.longconv_bwd(inp.dy[:, hs], inp.u[:, hs], k64, D64)
     _compare({"du": du[:, hs], "dk": dk[hs], "dD": dD[hs]}, {"du": rdu, "dk": rdk, "dD": rdD}, TOL[io], f"groups N{N}", DD_TOL)
+
+
+# N = 2048, two shares as the groups of waves of one workgroup: dk is the sum of two rows, each from an inverse transform of its own
+# (in fp16), as with two workgroups.  Calls for the even and for the odd rows make the same two rows, up to the order of their fp32
+# sums in front of the same rounding (2e-5); one inverse of the whole sum would be 6e-4 off.
+@pytest.mark.parametrize("layer,B,H,io", [("plain", 24, 256, wl.BF16), ("plain", 19, 200, wl.F16), ("gated", 24, 200, wl.F16),
+                                          ("gated", 25, 256, wl.BF16), ("image", 24, 256, wl.BF16)])
+def test_two_shares_in_one_workgroup(layer, B, H, io):
+    gen = torch.Generator(device="cuda").manual_seed(B + H)
+    shape = (32, 32) if layer == "image" else (2048,)
+    u, dy, g = (torch.randn(B, H, *shape, generator=gen, device="cuda").to(_TD[io]) for _ in range(3))
+    k, D = torch.randn(H, *shape, generator=gen, device="cuda") / 32, torch.randn(H, generator=gen, device="cuda")
+
+    def grads(rows):
+        u_, dy_, g_ = (t[rows].contiguous() for t in (u, dy, g))
+        du, dk, dD, dg = torch.empty_like(u_), torch.empty_like(k), torch.empty_like(D), torch.empty_like(u_)
+        n = u_.shape[0]
+        if layer == "image":
+            lc.longconv2d_bwd(dy_, u_, k, D, du, dk, dD, lc.new_workspace2d(n, H, *shape, io, True))
+        elif layer == "gated":
+            lc.longconv_bwd_gated(dy_, g_, u_, k, D, du, dk, dD, dg, lc.new_workspace(n, H, 2048, io, 2))
+        else:
+            lc.longconv_bwd(dy_, u_, k, D, du, dk, dD, lc.new_workspace(n, H, 2048, io, True))
+        return dk.double().cpu().numpy(), dD.double().cpu().numpy()
+
+    (dk, dD), (dk0, dD0), (dk1, dD1) = grads(slice(None)), grads(slice(0, None, 2)), grads(slice(1, None, 2))
+    assert wl.rel_l2(dk, dk0 + dk1) <= 1e-4
+    assert wl.rel_l2(dD, dD0 + dD1) <= 1e-5
