@@ -43,16 +43,23 @@ constexpr int span_log2(int LG, int s)
     return l;
 }
 
-// LDS position of point p: one slot of padding in nine, conflict-free for the strides 1, 8, 16 and above of the stages
-__host__ __device__ constexpr int phys(int p) { return p + (p >> 3); }
+// LDS position of point p, with a slot of padding behind every 2^K: eight, or sixteen for single rows of 2048 and 4096 samples, whose
+// runs of sixteen neighbours it leaves whole (16 lanes are served at a time; B=32, H=1024, N=4096 step 1333 -> 1308 us)
+template <int K = 3>
+__host__ __device__ constexpr int phys(int p) { return p + (p >> K); }
+constexpr int row_pad(int LG) { return LG <= 12 ? 4 : 3; }
 // whether the backward kernel parks the transform of u in memory (see fbwd_kernel)
 constexpr bool valu_parks(int LG) { return LG >= 14; }
 constexpr bool row_parks(int LG) { return points_log2(LG) == 4; }        // (frow_bwd_kernel)
+// which single rows take the butterflies' constants (N = 2048: and the twist's, on the way in) in two parts; see frow_conv_kernel
+constexpr bool row_fine(int LG) { return LG <= 12; }
 constexpr size_t lds_bytes(int LG) { return sizeof(float2) * ((size_t(1) << LG) * 9 / 8); }
 
 // ---- butterflies in registers -------------------------------------------------------------------------------------
-// v * exp(-+ 2 pi i m / 32): m a compile-time constant after unrolling
-template <bool INV>
+// v * exp(-+ 2 pi i m / 32): m a compile-time constant after unrolling.  FINE (even m only, the butterflies' own): constants in two
+// fp32 parts, so that their rounding, the same for every point of every stage, is out of the result: at 4096 points, radix 16,
+// it is a third of a transform's squared error, for 8 and 8 instructions more per butterfly.
+template <bool INV, bool FINE = false>
 __device__ __forceinline__ float2 rot32(float2 v, int m)
 {
     constexpr float C[5] = {1.f, 0.98078528040323043f, 0.92387953251128674f, 0.83146961230254524f, 0.70710678118654752f};
@@ -60,7 +67,17 @@ __device__ __forceinline__ float2 rot32(float2 v, int m)
     m &= 31;
     const int q = m >> 3, r = m & 7;
     float2 t = v;
-    if (r == 4) {
+    if (FINE && r) {
+        // cos of an eighth and a sixteenth of a turn (high, low part); tan of a sixteenth
+        constexpr float H = 0.70710678118654752f, HL = (float)(0.70710678118654752440 - (double)H);
+        constexpr float Q = 0.92387953251128676f, QL = (float)(0.92387953251128675613 - (double)Q), TQ = 0.41421356237309505f;
+        const float sy = INV ? v.y : -v.y, sx = INV ? v.x : -v.x;      // (v.x, v.y) turned by a quarter: (-sy, sx)
+        const float2 w = r == 4 ? make_float2(v.x - sy, v.y + sx)
+                       : r == 2 ? make_float2(__builtin_fmaf(-sy, TQ, v.x), __builtin_fmaf(sx, TQ, v.y))
+                                : make_float2(__builtin_fmaf(v.x, TQ, -sy), __builtin_fmaf(v.y, TQ, sx));
+        t = r == 4 ? make_float2(__builtin_fmaf(w.x, H, w.x * HL), __builtin_fmaf(w.y, H, w.y * HL))
+                   : make_float2(__builtin_fmaf(w.x, Q, w.x * QL), __builtin_fmaf(w.y, Q, w.y * QL));
+    } else if (r == 4) {
         t = INV ? make_float2((v.x - v.y) * C[4], (v.x + v.y) * C[4]) : make_float2((v.x + v.y) * C[4], (v.y - v.x) * C[4]);
     } else if (r) {
         const float c = r < 4 ? C[r] : S[8 - r], s = (r < 4 ? S[r] : C[8 - r]) * (INV ? 1.f : -1.f);
@@ -72,7 +89,7 @@ __device__ __forceinline__ float2 rot32(float2 v, int m)
 }
 
 // natural order in and out, stride ST between the elements
-template <int R, bool INV, int ST = 1>
+template <int R, bool INV, bool FINE = false, int ST = 1>
 __device__ __forceinline__ void dft(float2* x)
 {
     if constexpr (R == 2) {
@@ -96,13 +113,13 @@ __device__ __forceinline__ void dft(float2* x)
             float2 y[B];
 #pragma unroll
             for (int n1 = 0; n1 < B; ++n1) y[n1] = x[(A * n1 + n2) * ST];
-            dft<B, INV>(y);
+            dft<B, INV, FINE>(y);
 #pragma unroll
-            for (int k1 = 0; k1 < B; ++k1) t[k1 * A + n2] = rot32<INV>(y[k1], n2 * k1 * (32 / R));
+            for (int k1 = 0; k1 < B; ++k1) t[k1 * A + n2] = rot32<INV, FINE>(y[k1], n2 * k1 * (32 / R));
         }
 #pragma unroll
         for (int k1 = 0; k1 < B; ++k1) {
-            dft<A, INV>(t + k1 * A);
+            dft<A, INV, FINE>(t + k1 * A);
 #pragma unroll
             for (int k2 = 0; k2 < A; ++k2) x[(k1 + B * k2) * ST] = t[k1 * A + k2];
         }
@@ -134,16 +151,17 @@ __device__ __forceinline__ void dft_half_out(float2* x)
     for (int n = 0; n < R / 2; ++n) x[n] = cadd(e[n], rot32<true>(o[n], n * (32 / R)));
 }
 
-// exp(-2 pi i d / 4R), d < R: the twist's share of a butterfly of R points (single rows)
-template <int R>
+// exp(-2 pi i d / 4R), d < R: the twist's share of a butterfly of R points (single rows); LOW: what fp32 leaves of it
+template <int R, bool LOW = false>
 __device__ __forceinline__ float2 twist_unit(int d)
 {
     static_assert(R == 8 || R == 16, "the points of a thread");
-    constexpr float C[17] = {1.f, 0.99518472667219689f, 0.98078528040323045f, 0.95694033573220887f, 0.92387953251128676f, 0.88192126434835503f,
-                             0.83146961230254524f, 0.77301045336273696f, 0.70710678118654752f, 0.63439328416364550f, 0.55557023301960222f,
-                             0.47139673682599764f, 0.38268343236508977f, 0.29028467725446237f, 0.19509032201612827f, 0.098017140329560602f, 0.f};
+    constexpr double C[17] = {1., 0.99518472667219689, 0.98078528040323045, 0.95694033573220887, 0.92387953251128676, 0.88192126434835503,
+                              0.83146961230254524, 0.77301045336273696, 0.70710678118654752, 0.63439328416364550, 0.55557023301960222,
+                              0.47139673682599764, 0.38268343236508977, 0.29028467725446237, 0.19509032201612827, 0.098017140329560602, 0.};
     const int m = d * (16 / R);
-    return make_float2(C[m], -C[16 - m]);
+    const double c = C[m], s = -C[16 - m];
+    return LOW ? make_float2((float)(c - (double)(float)c), (float)(s - (double)(float)s)) : make_float2((float)c, (float)s);
 }
 
 // The compiler keeps what it can prove unchanged: without this it would hold every twiddle and spectrum value of a
@@ -278,7 +296,8 @@ using RowTw = typename std::conditional<FIRST, typename std::conditional<LG == 1
 // the twiddles of stage 0
 template <int LG, bool ALL = false, bool TWIST = false>
 struct Fft {
-    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG);
+    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG), PAD = TWIST ? row_pad(LG) : 3;
+    static constexpr bool FINE = TWIST && row_fine(LG);
 
     template <int s>
     struct St {
@@ -312,18 +331,18 @@ struct Fft {
         {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                float2* b = sm + phys(base(tid, g));
+                float2* b = sm + phys<PAD>(base(tid, g));
 #pragma unroll
-                for (int d = 0; d < r; ++d) b[phys(d << lgM)] = x[g * r + d];
+                for (int d = 0; d < r; ++d) b[phys<PAD>(d << lgM)] = x[g * r + d];
             }
         }
         __device__ __forceinline__ static void read(float2 (&x)[P], const float2* sm, int tid)
         {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const float2* b = sm + phys(base(tid, g));
+                const float2* b = sm + phys<PAD>(base(tid, g));
 #pragma unroll
-                for (int d = 0; d < r; ++d) x[g * r + d] = b[phys(d << lgM)];
+                for (int d = 0; d < r; ++d) x[g * r + d] = b[phys<PAD>(d << lgM)];
             }
         }
     };
@@ -338,13 +357,18 @@ struct Fft {
 #pragma unroll
             for (int d = 0; d < P; ++d) {
                 const float2 c = twist_unit<P>(d);
-                x[d] = make_float2(x[d].x * c.x, x[d].x * c.y);
+                if (FINE && LG == 11 && d) {
+                    const float2 l = twist_unit<P, true>(d);
+                    x[d] = make_float2(__builtin_fmaf(x[d].x, c.x, x[d].x * l.x), __builtin_fmaf(x[d].x, c.y, x[d].x * l.y));
+                } else {
+                    x[d] = make_float2(x[d].x * c.x, x[d].x * c.y);
+                }
             }
         }
 #pragma unroll
         for (int g = 0; g < C::G; ++g) {
             if constexpr (HALF && s == 0) dft_half_in<C::r>(x + g * C::r);
-            else dft<C::r, false>(x + g * C::r);
+            else dft<C::r, false, FINE>(x + g * C::r);
         }
         st.template twiddle<false>(x);
         if constexpr (s + 1 < S) {
@@ -377,7 +401,7 @@ struct Fft {
 #pragma unroll
         for (int g = 0; g < C::G; ++g) {
             if constexpr (HALF && s == 0) dft_half_out<C::r>(x + g * C::r);
-            else dft<C::r, true>(x + g * C::r);
+            else dft<C::r, true, FINE>(x + g * C::r);
         }
         if constexpr (C::twist) {
 #pragma unroll
@@ -798,11 +822,16 @@ fbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
 // LDS, half the spectrum, and twice the workgroups: two rows of 8192 samples share a compute unit and hide each other's
 // barriers and memory, and the backward kernel spills little (12 and 16 registers at N = 4096 and 16384, where a pair spilled 43);
 // N = 16384 takes no chunks.  Bound by vector issue: 105 instructions per point for a convolution, at 2.6 cycles and four waves
-// per SIMD.  Whole steps, pairs and rows: B=4, H=96, N=8192 78.8 -> 59.1 us, B=2, H=300 146 -> 92; B=3, H=50, N=16384 129 -> 70;
-// B=16, H=128, N=4096 112 -> 102; B=4, H=96, N=2048 28.0 -> 23.7; forward B=8, H=64, N=8192 20.4 -> 16.6.
-// Error against 64 bits, y and dk, pairs and rows: N = 2048 1.92 -> 1.73e-7, 2.84 -> 2.63e-7; 4096 1.94 -> 1.71, 2.86 -> 2.59;
-// 8192 2.12 -> 1.69, 3.10 -> 2.62; 16384 2.22 -> 1.82, 3.28 -> 2.78.  (A row without a partner had an easier time in a pair, B = 1:
-// 1.66 -> 1.73 and 2.40 -> 2.60, 1.63 -> 1.71 and 2.36 -> 2.57, 1.81 -> 1.67 and 2.62 -> 2.57, 1.90 -> 1.81 and 2.76 -> 2.76.)
+// per SIMD.  Whole steps back to back, pairs and rows: B=4, H=96, N=8192 77.0 -> 58.4 us, B=2, H=300 138 -> 92; B=4, H=96, N=16384
+// 197 -> 126; N=4096 44.4 -> 36.1, B=32, H=1024 1336 -> 1326; N=2048 29.0 -> 23.8.  Slower than pairs were: N = 2048 with 16000 rows and
+// more (B=16, H=1024 287 -> 296, B=32, H=1024 541 -> 592): there the exchanges bind, three of them where 4096 points of a pair have
+// two; sixteen points a thread (two exchanges, forward 192 -> 187) leave the backward kernel too few waves (368 -> 440), a
+// prefetched next row loses more in waves than it hides (forward 215 -> 239).
+// Error against 64 bits, y and dk, B = 4 and (a row without a partner had an easier time in a pair) B = 1, pairs -> rows, 1e-7: N = 2048
+// 1.91 -> 1.48, 2.83 -> 2.28 and 1.65 -> 1.47, 2.38 -> 2.25; 4096 1.93 -> 1.42, 2.86 -> 2.23 and 1.62 -> 1.41, 2.36 -> 2.19; 8192 2.13 ->
+// 1.69, 3.13 -> 2.61 and 1.82 -> 1.69, 2.63 -> 2.58; 16384 2.22 -> 1.82, 3.29 -> 2.79 and 1.89 -> 1.81, 2.77 -> 2.76.  Up to 4096 this
+// takes the constants in two parts (row_fine): with one, B = 1 was at 1.72, 2.61 and 1.70, 2.57; time the same to 3 % more (B=1, H=1,
+// N=2048 15.6 -> 16.0 us; B=8, H=200 45.2 -> 45.1; N=4096 B=8, H=129 69.5 -> 68.5).
 // Neighbouring items on one XCD: the rows of a head share its spectrum there.
 __device__ __forceinline__ int item_of(int items)
 {
