@@ -494,32 +494,49 @@ hipError_t head_dot(const void* dy, const void* u, float* dD, const Problem& pr,
     return hipGetLastError();
 }
 
-__global__ void sum_partials_kernel(const float* __restrict__ dk_part, float* __restrict__ dk, size_t n_dk,
-                                    const float* __restrict__ dD_part, float* __restrict__ dD, size_t n_dD, int nsplit)
+// t + p[s n + i] + p[(s + 1) n + i] + ..., in this order, A shares asked for at once as long as there are so many
+template <int A, class V>
+__device__ __forceinline__ V sum_shares(V t, const V* __restrict__ p, size_t n, size_t i, int s, int nsplit)
+{
+    for (; s + A <= nsplit; s += A) {
+        V v[A];
+#pragma unroll
+        for (int j = 0; j < A; ++j) v[j] = p[(size_t)(s + j) * n + i];
+#pragma unroll
+        for (int j = 0; j < A; ++j) t += v[j];
+    }
+    if constexpr (A > 1) return sum_shares<A / 2>(t, p, n, i, s, nsplit);
+    return t;
+}
+// Bound by its launch and a round trip to memory for every eight shares (one by one they were 64 for 64 shares); V: one number of dk
+// a thread, or four where they are enough to fill the device (the rows are 16-byte aligned and of whole pieces).
+template <class V>
+__global__ void sum_partials_kernel(const V* __restrict__ dk_part, V* __restrict__ dk, size_t n_dk, const float* __restrict__ dD_part,
+                                    float* __restrict__ dD, size_t n_dD, int nsplit)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_dk) {
-        float t = dk_part[i];
-        for (int s = 1; s < nsplit; ++s) t += dk_part[(size_t)s * n_dk + i];
-        dk[i] = t;
-    } else if (i - n_dk < n_dD) {
-        const size_t j = i - n_dk;
-        float t = dD_part[j];
-        for (int s = 1; s < nsplit; ++s) t += dD_part[(size_t)s * n_dD + j];
-        dD[j] = t;
-    }
+    if (i < n_dk) dk[i] = sum_shares<8>(dk_part[i], dk_part, n_dk, i, 1, nsplit);
+    else if (i - n_dk < n_dD) dD[i - n_dk] = sum_shares<8>(dD_part[i - n_dk], dD_part, n_dD, i - n_dk, 1, nsplit);
 }
 
+template <class V>
+static hipError_t sum_partials_go(const float* dk_part, float* dk, size_t n_dk, const float* dD_part, float* dD, size_t n_dD, int nsplit,
+                                  hipStream_t st)
+{
+    n_dk /= sizeof(V) / 4;
+    hipLaunchKernelGGL(sum_partials_kernel<V>, dim3((unsigned)((n_dk + n_dD + 255) / 256)), dim3(256), 0, st, (const V*)dk_part, (V*)dk,
+                       n_dk, dD_part, dD, n_dD, nsplit);
+    return hipGetLastError();
+}
 hipError_t sum_partials(const float* dk_part, float* dk, size_t n_dk, const float* dD_part, float* dD, size_t n_dD,
                         int nsplit, hipStream_t st)
 {
+    typedef float f4v __attribute__((ext_vector_type(4)));
     if (!dk) n_dk = 0;
     if (!dD) n_dD = 0;
-    const size_t n = n_dk + n_dD;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, dk_part, dk, n_dk,
-                       dD_part, dD, n_dD, nsplit);
-    return hipGetLastError();
+    if (n_dk + n_dD == 0) return hipSuccess;
+    return n_dk >= 4 * 256 * (size_t)compute_units() ? sum_partials_go<f4v>(dk_part, dk, n_dk, dD_part, dD, n_dD, nsplit, st)
+                                                     : sum_partials_go<float>(dk_part, dk, n_dk, dD_part, dD, n_dD, nsplit, st);
 }
 
 hipError_t reduce_dD(const float* part, float* dD, int64_t H, int nblk, hipStream_t st)

@@ -88,3 +88,9 @@ def test_error_of_a_row_without_a_partner(N, tol_y, tol_dk):
     errs = {"y": wl.rel_l2(n(y), ry), "du": wl.rel_l2(n(du), rdu), "dk": wl.rel_l2(n(dk), rdk)}
     print(f"[fp32 rows] N{N} " + " ".join(f"{a}={b:.3e}" for a, b in errs.items()), flush=True)
     assert errs["y"] <= tol_y and errs["du"] <= tol_y and errs["dk"] <= tol_dk
+
+
+# results of 2 to 64 shares added up: eight, four, two and one at a time, one number a thread and (heads enough) four
+@pytest.mark.parametrize("N,B,H", [(4096, 2, 1), (4096, 6, 3), (2048, 15, 2), (4096, 16, 1), (4096, 64, 2), (4096, 8, 100), (16384, 16, 16)])
+def test_sums_of_many_shares(N, B, H):
+    check_full(_inputs(N, B, H))
