@@ -202,7 +202,8 @@ static int dk_room(int64_t B, int64_t H, const Plan& pl)
 {
     if (pl.engine == ENGINE_MFMA && pl.order.wave_lg) return rows_bwd_room(B, H, pl.order.wave_lg);
     if (pl.engine == ENGINE_MFMA && pl.order.long_lg) return long_bwd_room(B, H);
-    return dk_nsplit(B, H, pl, true);
+    if (pl.engine == ENGINE_VALU) return valu_bwd_room(B, H, pl);
+    return 1;
 }
 
 // bf16 rows of the multi-pass plans that take pass A inside the inner kernels are scaled per head (see rows_absmax)

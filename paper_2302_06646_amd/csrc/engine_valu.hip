@@ -1240,7 +1240,7 @@ hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws,
 }
 
 // Workgroups that fill the device: one, two or about four of them per compute unit by their LDS
-int valu_bwd_nsplit(int64_t B, int64_t H, const Plan& pl)
+int valu_bwd_room(int64_t B, int64_t H, const Plan& pl)
 {
     const int lg = pl.vrow ? pl.vrow : pl.log2L2, target = lg >= 14 ? 256 : lg == 13 ? 512 : 1024;
     const int64_t units = pl.vrow ? B : (B + 1) / 2;
@@ -1248,6 +1248,25 @@ int valu_bwd_nsplit(int64_t B, int64_t H, const Plan& pl)
     if (s > units) s = units;
     if (s > 64) s = 64;
     return s < 1 ? 1 : (int)s;
+}
+// Single rows of 2048 samples: fewer, where the rows that a share is spared do not make up for its company on a compute unit and for
+// the sum of partial results.  A row takes 4.9, 5.8, 7.6 and 9.1 us with one to four workgroups on the fullest unit; the sum 2 us and
+// its bytes.  Backward calls, as many as there is room for and by this: B=2, H=400 21.7 -> 17.8 us, B=2, H=300 18.4 -> 17.6, B=4,
+// H=400 30.7 -> 29.5, B=8, H=129 25.7 -> 24.3.  At N = 4096 and above more shares were faster wherever there is room for them.
+int valu_bwd_nsplit(int64_t B, int64_t H, const Plan& pl)
+{
+    const int room = valu_bwd_room(B, H, pl);
+    if (pl.vrow != 11) return room;
+    const float row_us[5] = {0.f, 4.9f, 5.8f, 7.6f, 9.1f};
+    int best = 1;
+    float least = 0.f;
+    for (int s = 1; s <= room; ++s) {
+        const int on_cu = (int)((H * s + compute_units() - 1) / compute_units());
+        const float us = ((float)(on_cu / 4) * row_us[4] + row_us[on_cu % 4]) * (float)((B + s - 1) / s) +
+                         (s > 1 ? 2.f + (float)s * (float)H * 2048.f * 2e-6f : 0.f);
+        if (s == 1 || us < least) { best = s; least = us; }
+    }
+    return best;
 }
 
 size_t valu_zbuf_bytes(int64_t B, int64_t H, int nsplit, const Plan& pl)

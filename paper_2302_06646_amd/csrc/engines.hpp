@@ -121,6 +121,7 @@ hipError_t valu_conv(const void* in, const float2* kspec, void* out, float2* ws,
 // (or ws_A) and dD point to partial buffers [nsplit][...] that sum_partials() adds up in share order.
 // zbuf: valu_zbuf_bytes() of scratch.
 int valu_bwd_nsplit(int64_t B, int64_t H, const Plan& pl);
+int valu_bwd_room(int64_t B, int64_t H, const Plan& pl);       // the most it takes for up to B rows; never falls as B grows
 size_t valu_zbuf_bytes(int64_t B, int64_t H, int nsplit, const Plan& pl);
 hipError_t valu_bwd(const void* dy, const void* u, const float2* kspec, void* du, float2* ws_du, float* dk, float2* ws_A,
                     float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st);

@@ -94,3 +94,10 @@ def test_error_of_a_row_without_a_partner(N, tol_y, tol_dk):
 @pytest.mark.parametrize("N,B,H", [(4096, 2, 1), (4096, 6, 3), (2048, 15, 2), (4096, 16, 1), (4096, 64, 2), (4096, 8, 100), (16384, 16, 16)])
 def test_sums_of_many_shares(N, B, H):
     check_full(_inputs(N, B, H))
+
+
+# N = 2048: two rows of many heads in one share, of fewer in two; in between, fewer shares than there is room for
+@pytest.mark.parametrize("B,H", [(2, 255), (2, 400), (4, 400), (8, 129)])
+def test_shares_of_short_rows(B, H):
+    assert lc.longconv_workspace_bytes(B, H, 2048, lc.F32, 1) >= lc.longconv_workspace_bytes(B - 1, H, 2048, lc.F32, 1)
+    check_sampled(_inputs(2048, B, H), sample_heads(H, B, seed=B + H))
