@@ -78,7 +78,8 @@ int longconv_init(void);
 
 /* Size in bytes of the spectrum cache for H heads of length N (0 on bad args).
  * The cache holds, per head, the spectrum of [k[h,:], 0_N] plus D[h]: 2N points, or the
- * N points of the twisted row for fp16/bf16 I/O (the room is that of 2N points)
+ * N points of the twisted row for fp16/bf16 I/O and for fp32 I/O of N = 2048 to 16384 (the
+ * room is that of 2N points)
  * (the skip term is a delta kernel of height D[h]), pre-scaled and stored in the
  * permuted order the fused transform produces (Algorithm 2 lines 1-2: the
  * spectrum is computed once and stored already permuted, so no permutation ever
@@ -127,11 +128,12 @@ int longconv_fwd_noalloc(const void* u, const float* k, const float* D, const vo
 /* Backward: du, dk, dD as defined above.  Any of the three output pointers may be
  * NULL to skip that gradient.  dk and dD are overwritten (not accumulated) and are
  * summed over b in a fixed order (bitwise repeatable call to call).  Which kernels
- * run depends on which outputs are asked for (for N <= 4096 with fp16/bf16 I/O, and at
- * every length with fp32 I/O, du together with dk or dD comes from one kernel, otherwise
- * from separate ones), so a
+ * run depends on which outputs are asked for (du together with dk or dD comes from one
+ * kernel, at N = 32768 with fp16/bf16 I/O from two), and so, for few heads at N >= 32768
+ * with fp16/bf16 I/O, does the order of the sums of dk and dD: a
  * gradient may differ in its last bits between a call for all three and a call for
- * itself alone; both meet the stated accuracy.  kspec as in longconv_fwd (only
+ * itself alone; both meet the stated accuracy.  Until the call's last kernel has run,
+ * du may hold other data (there, partial sums of dk and dD).  kspec as in longconv_fwd (only
  * needed for du). */
 int longconv_bwd(const void* dy, const void* u, const float* k, const float* D, const void* kspec,
                  void* du, float* dk, float* dD,

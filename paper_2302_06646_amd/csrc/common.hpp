@@ -59,11 +59,16 @@ __device__ __forceinline__ float2 cmulc(float2 a, float2 b)
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 
-// Rows that a kernel writes and nothing on the device reads again soon (y, du, dg) are stored with the nt hint: they leave the
-// L2 first, so that rows still to be read, spectra and spilled registers stay, and the lines are written back while the kernel
-// runs, not at its end.  Loads with the hint were slower (several loads of a wave share a line).  Whole steps, plain stores
-// and nt: B=64, H=1024, N=256 bf16 67.9 -> 58.9 us, B=16, H=768, N=1024 68.0 -> 64.1, B=8, H=256, N=16384 fp16 173 -> 162;
-// the gradients in fp32, spectra and workspaces gained nothing and are stored plainly.
+// Rows that a kernel writes and does not read (y, du, dg) are stored with the nt hint: their lines are written back while the kernel
+// runs, not at its end.  (What the kernels read from memory stays the same to a percent, FETCH_SIZE of lbwd_kernel<14>,
+// rbwd1_kernel<8> and rconv1_kernel<8>, on the same tensors and on others in turn: the hint keeps nothing in the L2 that plain stores
+// would push out.)  Loads with the hint were slower (several loads of a wave share a line).  Whole steps back to back, plain stores and
+// nt, on the same tensors and (behind the comma) on tensors in turn that exceed the last-level cache together: B=64, H=1024, N=256 bf16
+// 45.8 -> 44.2 us, 66.1 -> 63.2; B=16, H=768, N=1024 58.3 -> 57.9, 63.9 -> 61.7; gated B=7, H=193, N=2048 37.4 -> 35.8, 39.9 -> 37.8;
+// B=8, H=256, N=16384 fp16 161 -> 153, 167 -> 157; forward B=32, H=128, N=32768 264 -> 247, 269 -> 256.  Where the library reads the
+// rows next it is about even: 128 x 128 images bf16 B=16, H=256 1388 -> 1376, B=8, H=64 263.5 -> 264.9; fp32 64 x 64 B=16, H=64 153.6 ->
+// 154.8, in turn 163 -> 165; gated fp32 B=8, H=64, N=16384 245 -> 237.  The gradients in fp32, spectra and workspaces gained nothing and
+// are stored plainly.
 constexpr int BUF_ONCE = 2;               // the hint as a buffer instruction's auxiliary operand
 template <class V>
 __device__ __forceinline__ void put_once(V* p, const V& v)

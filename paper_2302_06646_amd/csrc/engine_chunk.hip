@@ -873,7 +873,7 @@ hipError_t chunk_conv(const void* in, const float2* kspec, void* out, void* ws, 
     return hipErrorInvalidValue;
 }
 
-// Shares of a head's rows where one leaves at least half of the device idle (a compute unit holds one workgroup): two, or (more: where
+// Shares of a head's rows where one leaves at least half of a whole device's 256 compute units idle (one holds one workgroup): two, or (more: where
 // their results find room) the number that ends first, a row 12 us and another share 2 in chunk_dk_kernel, which reads all of them.
 // Steps, two shares at most and now: B=64, H=4, N=65536 bf16 614 -> 267 us, B=31, H=12 fp16 355 -> 228; B=64, H=4, N=32768 354 -> 134,
 // B=10, H=21 137 -> 120; B=16, H=7, N=131072 bf16 359 -> 298; B=7, H=4, N=65536 101.6 -> 90.3.

@@ -508,10 +508,12 @@ __device__ __forceinline__ uint32_t out_word(float a, float b, int ex)
 // Waves of workgroups that share a compute unit issue in the order of their age where they compete, so that the older workgroup
 // runs at the speed it has alone and the younger one with what is left: of two at N = 4096 a row in 1.75 and 3.5 us, and when the
 // first is through with its rows the second runs the rest by itself.  So the issue priority rises with the number of the
-// workgroup, in steps of the compute units of a launch (LEVELS of them).  Set behind the constants' way in; at the kernel's start
-// it changed nothing.  bf16, forward calls: B=8, H=64, N=4096 9.5 -> 8.8 us, B=16, H=64, N=2048 9.1 -> 8.3, B=32, H=256, N=512
-// 7.3 -> 7.0; steps: B=64, H=1024, N=256 59.4 -> 57.0, B=7, H=193, N=2048 gated 37.0 -> 36.2.  (The backward kernels of 1024 samples
-// and more lose 1 % or nothing, those of one workgroup per compute unit have nobody to share with.)
+// workgroup, in steps of the 256 compute units of a whole device (LEVELS of them; with another number of units the results are the
+// same and the priorities fall elsewhere).  Set behind the constants' way in; at the kernel's start it changed nothing.  bf16, back to
+// back on the same tensors and (behind the comma) on tensors in turn that exceed the last-level cache: forward B=8, H=64, N=4096 9.7 ->
+// 8.9 us, 10.4 -> 9.7, B=16, H=64, N=2048 9.7 -> 8.9, 10.2 -> 9.3, B=32, H=256, N=512 7.6 -> 7.1, 8.3 -> 8.3; steps B=64, H=1024, N=256
+// 47.5 -> 46.0, 64.8 -> 63.3, gated B=7, H=193, N=2048 37.1 -> 36.2, 38.3 -> 37.7.  (The backward kernels of 1024 samples and more lose
+// 1 % or nothing, those of one workgroup per compute unit have nobody to share with.)
 template <int LEVELS>
 __device__ __forceinline__ void younger_first()
 {

@@ -825,8 +825,9 @@ fbwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restr
 // per SIMD.  Whole steps back to back, pairs and rows: B=4, H=96, N=8192 77.0 -> 58.4 us, B=2, H=300 138 -> 92; B=4, H=96, N=16384
 // 197 -> 126; N=4096 44.4 -> 36.1, B=32, H=1024 1336 -> 1326; N=2048 29.0 -> 23.8.  Slower than pairs were: N = 2048 with 16000 rows and
 // more (B=16, H=1024 287 -> 296, B=32, H=1024 541 -> 592): there the exchanges bind, three of them where 4096 points of a pair have
-// two; sixteen points a thread (two exchanges, forward 192 -> 187) leave the backward kernel too few waves (368 -> 440), a
-// prefetched next row loses more in waves than it hides (forward 215 -> 239).
+// two; with sixteen points a thread (two exchanges) the forward pass of the last is faster, 213 -> 182, but the backward kernel, whose
+// accumulator then waits in memory, slower by more (step 575 -> 640); workgroups that keep on, with the next row asked for ahead,
+// take 237 for 214.
 // Error against 64 bits, y and dk, B = 4 and (a row without a partner had an easier time in a pair) B = 1, pairs -> rows, 1e-7: N = 2048
 // 1.91 -> 1.48, 2.83 -> 2.28 and 1.65 -> 1.47, 2.38 -> 2.25; 4096 1.93 -> 1.42, 2.86 -> 2.23 and 1.62 -> 1.41, 2.36 -> 2.19; 8192 2.13 ->
 // 1.69, 3.13 -> 2.61 and 1.82 -> 1.69, 2.63 -> 2.58; 16384 2.22 -> 1.82, 3.29 -> 2.79 and 1.89 -> 1.81, 2.77 -> 2.76.  Up to 4096 this
