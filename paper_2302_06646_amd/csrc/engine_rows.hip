@@ -189,6 +189,20 @@ __device__ __forceinline__ void arrived(RK<LG, NT>& K)
     if (RC<LG>::TC > 1) { arrived(K.c_re); arrived(K.c_im); }
 }
 
+// The factors of the complex products are read anew in every iteration, as far as the compiler can see.  Otherwise it computes their
+// exchanged and negated halves in front of the loop, which the packed instructions have modifiers for, and keeps them: a register
+// for every word of twiddles and spectrum, 16 of rconv_kernel's 128.  With the gate that kernel spilled four and reloaded them in
+// every row: gated forward, bf16, B=16, H=300, N=4096 36.5 -> 32.5 us, B=7, H=193, N=2048 10.7 -> 9.8.
+template <int LG, int NT, int NK>
+__device__ __forceinline__ void keep_words(RK<LG, NT>& K, H8U (&kk)[NK])
+{
+    arrived(K.t1.v);
+    if (RC<LG>::TC == 1) arrived(K.t1i.v);
+    else K.t1i = K.t1;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) arrived(kk[k].v);
+}
+
 // ---- global memory: a row (two rows at N = 256) behind a buffer descriptor; lanes that must not touch memory carry
 // an offset beyond it (loads give zero, stores do nothing) ------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -604,6 +618,7 @@ rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
         const int bt = (t & 1) * C::XW, bs = C::XW - bt;
         H8U m3[2], m2[2];
         uint32_t w[4];
+        keep_words(K, kk);
         if (do1) {
             const uint32_t* rw = raw + (t & 1) * C::SW + sw;
 #pragma unroll
@@ -649,22 +664,32 @@ rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
         }
         es2 = es1; e2 = e1; e1 = e0;
         SCHED_FENCE();
-        arrive(t + 1);
+        // The spectrum before the row: requests are counted in their order, and phase 2 would have to wait for a row asked for
+        // in front of its spectrum, half an iteration early, in every iteration.  (No faster where the rows come from the
+        // last-level cache; large calls run at the clock that the power budget leaves, 1.8 to 2.1 GHz.)
         if (do1) {
             if (b == 0 && t > 0) load_spec();           // the next phase 2 is another head's
             if (++b == B) { b = 0; ++h; }
         }
+        SCHED_FENCE();
+        arrive(t + 1);
         __syncthreads();
     };
     // exponent of row t; what kind of iteration t is: 0 at the ends, 1 whole, 2 whole and nothing scaled
     auto prep = [&](int t) {
         if constexpr (BF) {
+            int e = e0;
             if (t < n) {
-                uint32_t mm = 0u;
+                const uint32_t* mw = mxs + (t & 1) * 8;
+                e = 0;                                   // every wave found its words in the band
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(mw[lane & (C::NWR - 1)] != BAND_LOW) != 0, 0)) {
+                    uint32_t mm = 0u;
 #pragma unroll
-                for (int w = 0; w < C::NWR; ++w) mm = max(mm, mxs[(t & 1) * 8 + w]);
-                e0 = row_exponent(__builtin_amdgcn_readfirstlane((int)mm));
+                    for (int w = 0; w < C::NWR; ++w) mm = max(mm, mw[w]);
+                    e = row_exponent(__builtin_amdgcn_readfirstlane((int)mm));
+                }
             }
+            e0 = e;
         }
         return t >= 3 && t < n ? ((e0 | e2 | es2) == 0 ? 2 : 1) : 0;
     };
@@ -1117,14 +1142,22 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
             for (int r = 0; r < 4; ++r) dsum = dot_words<IO>(d[r], v[r], dsum);
         }
         if constexpr (BF) {
-            uint32_t m1[1], m2[1];
-            const uint32_t d1[1][4] = {{d[0], d[1], d[2], d[3]}}, v1[1][4] = {{v[0], v[1], v[2], v[3]}};
-            words_max(d1, m1);
-            words_max(v1, m2);
-            if (lane == 0) *reinterpret_cast<uint2*>(mxs + ((t & 1) * 8 + wave) * 2) = make_uint2(m1[0], m2[0]);
+            uint32_t md = 0u, mu_ = 0u;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { md = absmax_acc(md, d[r]); mu_ = absmax_acc(mu_, v[r]); }
+            band_or_exact2(md, mu_);
+            if (lane == 0) *reinterpret_cast<uint2*>(mxs + ((t & 1) * 8 + wave) * 2) = make_uint2(md, mu_);
         }
         *reinterpret_cast<uint4*>(raw + (t & 1) * C::SW + sf) = make_uint4(d[0], d[1], d[2], d[3]);
         *reinterpret_cast<uint4*>(raw + (2 + (t & 1)) * C::SW + sf) = make_uint4(v[0], v[1], v[2], v[3]);
+        // All uses of rows t stand in front of the request for rows t + 1, which then takes their registers.  Otherwise the sum
+        // of products is moved behind it, the rows come into registers of their own, are copied at the end of the same iteration
+        // and so waited for there: bf16, B=64, H=1024, N=4096 521 -> 488 us, B=32, H=512, N=2048 71 -> 66.  (Rows in fp16 have no
+        // branch to be moved across; holding the scheduler back costs them 1 %.)
+        if constexpr (BF) {
+            asm volatile("" : "+v"(dsum));
+            SCHED_FENCE();
+        }
         ask(t + 1);
     };
     arrived(K);
@@ -1225,19 +1258,22 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
     // exponents of rows t; what kind of iteration t is: 0 at the ends, 1 whole, 2 whole and nothing scaled
     auto prep = [&](int t) {
         if constexpr (BF) {
+            int d = ed0, v = eu0, p = ep0;               // (assigned once: stores on either side of a branch were merged in memory)
             if (t < nmine) {
-                uint32_t md = 0u, mu_ = 0u;
+                const uint32_t* mw = mxs + ((t & 1) * 8 + grp * NWR) * 2;
+                d = v = p = 0;                           // every wave found its words in the band
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(mw[lane & (2 * NWR - 1)] != BAND_LOW) != 0, 0)) {
+                    uint32_t md = 0u, mu_ = 0u;
 #pragma unroll
-                for (int w = 0; w < NWR; ++w) {
-                    const uint2 v = *reinterpret_cast<const uint2*>(mxs + ((t & 1) * 8 + grp * NWR + w) * 2);
-                    md = max(md, v.x); mu_ = max(mu_, v.y);
+                    for (int w = 0; w < NWR; ++w) { md = max(md, mw[2 * w]); mu_ = max(mu_, mw[2 * w + 1]); }
+                    md = __builtin_amdgcn_readfirstlane((int)md);
+                    mu_ = __builtin_amdgcn_readfirstlane((int)mu_);
+                    d = row_exponent(md);
+                    v = row_exponent(mu_);
+                    p = md && mu_ ? d + v : EXP_NONE;
                 }
-                md = __builtin_amdgcn_readfirstlane((int)md);
-                mu_ = __builtin_amdgcn_readfirstlane((int)mu_);
-                ed0 = row_exponent(md);
-                eu0 = row_exponent(mu_);
-                ep0 = md && mu_ ? ed0 + eu0 : EXP_NONE;
             }
+            ed0 = d; eu0 = v; ep0 = p;
         }
         if (t < 3 || t >= nmin) return 0;
         return (ed0 | eu0 | ed2 | es | (GATE ? eu2 : 0)) == 0 && (!BF || ep1 == eref) ? 2 : 1;

@@ -105,6 +105,24 @@ __device__ __forceinline__ void band_or_exact(uint32_t (&m)[NR])
         for (int r = 0; r < NR; ++r) m[r] = BAND_LOW;
     }
 }
+// The same for two rows in two variables, measured both where either fails the test.
+__device__ __forceinline__ void band_or_exact2(uint32_t& ma, uint32_t& mb)
+{
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    union { uint32_t u; us2 v; } a, b, hi;
+    a.u = ma; b.u = mb;
+    hi.v = __builtin_elementwise_max(a.v, b.v);
+    // (magnitudes below 0x8000: the sum's top bit tells whether a half is at or above BAND_HIGH, bit 14 at or above BAND_LOW)
+    constexpr uint32_t UP = (0x8000u - BAND_HIGH) * 0x10001u, LOW = BAND_LOW * 0x10001u;
+    const uint64_t big = __builtin_amdgcn_ballot_w64(((hi.u + UP) & 0x80008000u) != 0u);
+    const uint64_t la = __builtin_amdgcn_ballot_w64((ma & LOW) != 0u), lb = __builtin_amdgcn_ballot_w64((mb & LOW) != 0u);
+    if (__builtin_expect(big != 0 || la == 0 || lb == 0, 0)) {
+        ma = absmax_wave(ma);
+        mb = absmax_wave(mb);
+    } else {
+        ma = mb = BAND_LOW;
+    }
+}
 // after the maxima of all waves holding the rows were combined: did every wave publish the stand-in for both?
 __device__ __forceinline__ bool rows_in_band(uint32_t ma, uint32_t mb) { return ((ma ^ BAND_LOW) | (mb ^ BAND_LOW)) == 0u; }
 // Exponent e of the power of two 2^-e that brings a row whose largest bf16 magnitude pattern is m into
