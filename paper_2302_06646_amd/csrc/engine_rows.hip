@@ -736,8 +736,10 @@ __device__ __forceinline__ void store_words(rsrc_t d, const uint32_t (&off)[4], 
 // staging (a wave's words already cover 32 to 128 contiguous bytes), and nothing to fill and drain for a wave's few rows.
 // N = 1024 as a row pipeline of two waves (rconv_kernel's), kernel time in us, there -> here, bf16: B=1, H=768
 // 6.7 -> 4.8; B=16, H=256 12.2 -> 8.6; B=16, H=768 21.3 -> 17.1; B=64, H=1024 75.7 -> 68.9 (3.9 TB/s).
+// Three waves per SIMD at N = 1024 (168 registers, without the gate; two before keep_words): B=16, H=768 16.9 -> 15.2, B=64,
+// H=1024 72 -> 67.
 template <int LG, class IO, bool CONJ, bool GATE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RC<LG>::NP == 2 ? 2 : 4)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RC<LG>::NP == 2 ? (GATE ? 2 : 3) : 4)))
 rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec, typename IO::T* __restrict__ out,
               const typename IO::T* __restrict__ gate, int B, int H, int bpi, int items, uint32_t pad,
               const uint4* __restrict__ tab)
@@ -781,13 +783,23 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
     uint32_t* xw = xb + 4 * lane;
     uint32_t* xp = xb + p2_base<LG>(0, lane);
     H8U kk[NT];
-    arrived(K);
     int es = 0;
+    auto load_spec = [&]() {
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
+#pragma unroll
+        for (int k = 0; k < NT; ++k) kk[k].u = ks[k * 64 + lane];
+        es = spec_exp_of(kspec, H, 2 * C::N)[h];
+    };
+    load_spec();                                                  // (on its way together with the row and the constants)
+    arrived(K);
+#pragma unroll
+    for (int k = 0; k < NT; ++k) arrived(kk[k].v);
     int ea = 0, eb = 0;                                           // exponents (bf16) of the pass's row(s)
     auto iter = [&](auto mode, int i) {
         using M = decltype(mode);
         h4 op[NP][2];
         f4 zr[2], zi[2], v[2];
+        keep_words(K, kk);
         H8U m[2];
         uint32_t ga[NP][4], o[NP][4];
 #pragma unroll
@@ -845,11 +857,8 @@ rconv1_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ 
     };
     // the pass has arrived: spectrum of a new head, exponents; is anything scaled?
     auto prep = [&](int i) {
-        if (i == i0 || po.b == 0) {
-            const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * 2 * C::N);
-#pragma unroll
-            for (int k = 0; k < NT; ++k) kk[k].u = ks[k * 64 + lane];
-            es = spec_exp_of(kspec, H, 2 * C::N)[h];
+        if (po.b == 0 && i != i0) {
+            load_spec();
 #pragma unroll
             for (int k = 0; k < NT; ++k) arrived(kk[k].v);
         }
@@ -1349,7 +1358,9 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
 // The same for rows that one wave owns (N = 256: two rows at a time; N = 512; N = 1024: four tiles), NWV independent waves
 // per workgroup.  N = 1024 as a row pipeline (rbwd_kernel, two groups of two waves), kernel time in us, there -> here,
 // bf16: B=1, H=768 16.5 -> 8.1; B=5, H=64 12.0 -> 9.7; B=16, H=256 20.3 -> 14.4; B=16, H=768 37.4 -> 30.2; B=64, H=1024
-// 137 -> 110.  (N = 1024 spills 6 to 14 registers; gated it would be 50 and more, and 1.5 times as slow as the pipeline.)
+// 137 -> 110.  (Gated N = 1024 spills 50 registers and more and is 1.5 times as slow as the pipeline.)  With the factors' words kept
+// once (keep_words) N = 1024 spills none, where it had 6 to 14, B=1, H=768 7.9 -> 6.8, B=16, H=768 31.1 -> 29.6, and N = 512 has
+// three waves per SIMD in place of two: B=64, H=1024 60.2 -> 54.7.
 template <int LG, class IO, bool DU, bool GATE, int NWV>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 rbwd1_kernel(const BwdArgs<typename IO::T> q)
@@ -1422,6 +1433,7 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
     auto iter = [&](auto mode, int p) {
         using M = decltype(mode);
         h4 od[NP][2], ou[NP][2];
+        keep_words(K, kk);
         f4 wr[2], wi[2], yr[2], yi[2], v[2];
         H8U m[2], n[2];
         uint32_t wy[NP][4], o[NP][4], og[NP][4];
