@@ -19,6 +19,8 @@
 // memory in the tile's lane order, w_L twiddles from a lane-ordered global table (16 bytes per lane and tile).
 // Staged (whatever takes rows): the whole workgroup moves them between global memory and LDS in unit-stride
 // runs, phases 1 and 3 run in place on LDS, and the w_L twiddle is a per-lane constant times an LDS table.
+#include <type_traits>
+
 #include "engines.hpp"
 #include "mfma_util.hpp"
 
@@ -330,9 +332,10 @@ __device__ __forceinline__ void tile_places(int (&at)[4], int w1, int t0)
 // Phase 1 in place on the staged layout, 8 tiles t0..t0+7 of one wave: each lane reads its own 16 bytes
 // of a tile (samples d_a = 4g..4g+3 of column d_b = c) and writes outputs (k_a, k_b) = (c, 4g..4g+3) there.
 // F1 is the first-stage matrix (rows of the zero padding cleared when those slots hold stale data).
-template <int LG, int NB, bool SW = false>
+struct NothingElse { __device__ __forceinline__ void operator()(int) const {} };
+template <int LG, int NB, bool SW = false, class Also = NothingElse>
 __device__ __forceinline__ void phase1_inplace(uint32_t* xb, const uint4* t1f, const uint32_t* vt, const Mats& F1,
-                                               const Mats& F2, const h2 (&cF)[4], int t0, int lane)
+                                               const Mats& F2, const h2 (&cF)[4], int t0, int lane, Also&& also = Also())
 {
     using C = CC<LG>;
     const int c = lane & 15, g = lane >> 4;
@@ -354,6 +357,7 @@ __device__ __forceinline__ void phase1_inplace(uint32_t* xb, const uint4* t1f, c
             cv.u = vt[t * 16 + c];
             v[k] = cv.h;
         }
+        also(tb / NB);
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             yr[k] = MFMA(x[k].v, F1.re, zero);
@@ -553,12 +557,24 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
 
     auto run_n = [&](int i) { return staged_run_n<LG>(i * NT + tid); };
     uint4 pa[RPL];
-    auto fetch = [&](int it) {
-        const size_t o = row_off(it % nrow, it / nrow, H, C::L);
+    // quarter Q of a row's runs; without a row (an empty descriptor) the requests go out all the same and ask for nothing, so that
+    // they are in one stream with the rest
+    auto fetch = [&](int it, bool any, auto q) __attribute__((always_inline)) {
+        constexpr int Q = decltype(q)::value;
+        const typename IO::T* p = in + row_off(it % nrow, it / nrow, H, C::L);
+        const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(const_cast<typename IO::T*>(p), 0, any ? C::L * 2 : 0, 0x00027000);
 #pragma unroll
-        for (int i = 0; i < RPL; ++i) pa[i] = *reinterpret_cast<const uint4*>(in + o + run_n(i));
+        for (int i = Q * RPL / 4; i < (Q + 1) * RPL / 4; ++i)
+            pa[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(d, 2 * run_n(i), 0, 0));
+        asm volatile("; %0" :: "n"(Q));         // (the quarters' code is not to be merged: their registers would be in memory)
     };
-    if (it0 < it1) fetch(it0);       // first row on its way while the constants are built
+    const std::integral_constant<int, 0> q0;
+    const std::integral_constant<int, 1> q1;
+    const std::integral_constant<int, 2> q2;
+    const std::integral_constant<int, 3> q3;
+    if (it0 < it1) {                 // the first row is on its way while the constants are built
+        fetch(it0, true, q0); fetch(it0, true, q1); fetch(it0, true, q2); fetch(it0, true, q3);
+    }
 
     Consts<LG> K;
     make_consts<LG>(K, tw, lane);
@@ -668,9 +684,10 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
         stage(0);
     }
     for (int it = it0; it < it1; ++it) {
-        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) +
-                                                         (size_t)(it / nrow) * C::L);
+        const int h = __builtin_amdgcn_readfirstlane(it / nrow);
+        const uint4* ks = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(kspec) + (size_t)h * C::L);
         asm volatile("" : "+s"(ks));
+        const int es = spec_exp_of(kspec, H, 2 * (int64_t)C::L)[h];
         __syncthreads();             // staged row visible
         int ea = 0;
         if constexpr (IsBf<IO>::v) {
@@ -688,12 +705,20 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
             }
         }
         const bool more = it + 1 < it1;
-        if (more) fetch(it + 1);     // phases 1 to 3 cover the transfer
 
-        // ---- phase 1, in place
-#pragma unroll 1
-        for (int gi = 0; gi < ng; ++gi)
-            phase1_inplace<LG, NB, true>(xb, t1f, vt, F1, K.F16, c1, (gi * NWV + wave) * 8, lane);
+        // ---- phase 1, in place.  The next row is asked for piece by piece: asked for at once, the requests of eight waves held the
+        // later four of them back by some 2500 cycles of 33000 per row, and the others at the barrier (forward, B=32, H=128 fp16
+        // 260 -> 251 us, B=7, H=100 bf16 62.6 -> 60.9; one row per workgroup, B=2, H=128, 0.5 us slower)
+        static_assert(C::TC == 16 * NWV && NB == 4 && RPL % 4 == 0, "two groups of two batches of tiles per wave");
+        const int next = more ? it + 1 : it;
+        phase1_inplace<LG, NB, true>(xb, t1f, vt, F1, K.F16, c1, wave * 8, lane, [&](int b) __attribute__((always_inline)) {
+            if (b == 0) fetch(next, more, q0);
+            else fetch(next, more, q1);
+        });
+        phase1_inplace<LG, NB, true>(xb, t1f, vt, F1, K.F16, c1, (NWV + wave) * 8, lane, [&](int b) __attribute__((always_inline)) {
+            if (b == 0) fetch(next, more, q2);
+            else fetch(next, more, q3);
+        });
         __syncthreads();
         asm volatile("" : "+s"(ks));
 
@@ -778,7 +803,6 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
             }
         }
         __syncthreads();
-        const int es = __builtin_amdgcn_readfirstlane(spec_exp_of(kspec, H, 2 * (int64_t)C::L)[it / nrow]);
         drain(it, ea + es);          // (the lane that drains a slot stages the next row's sample there)
         if (more) {
             if constexpr (IsBf<IO>::v) measure();
