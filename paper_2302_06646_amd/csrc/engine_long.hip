@@ -101,8 +101,9 @@ __global__ void fill_long_tab_kernel(uint4* tab)
 // -------------------------------------------------------------------------------------------------------------------
 // Convolution (forward; CONJ: du) of all rows.  Persistent workgroups with even runs of consecutive (head, row) items, two
 // barriers per row.  Bound by issue: about 75 instructions per 256 points and row at some six cycles each with two waves per SIMD.
-// B=8, H=256, N=16384 fp16: 83 us as pairs of rows in 32768-point transforms, 54 here; B=64, H=128, N=8192: 129, 91.  (The gate's
-// pieces cost the kernel of N = 8192 spilled registers, 14 in bf16 and 26 in fp16.)
+// B=8, H=256, N=16384 fp16: 83 us as pairs of rows in 32768-point transforms, 54 here; B=64, H=128, N=8192: 129, 91.  Four waves per
+// SIMD with four tiles each (128 registers) were tried: 2 to 4 % faster at 16384, slower at 8192 and for few rows, and only with eight
+// spilled registers or the tiles' factors rounded by themselves.
 // -------------------------------------------------------------------------------------------------------------------
 template <int LG, class IO, bool CONJ, bool GATE>
 __global__ void __launch_bounds__(LR<LG>::NT) __attribute__((amdgpu_waves_per_eu(2)))
@@ -125,11 +126,14 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
     int h = i0 / B, b = i0 - h * B;                  // row of phase 1
     int ho = h, bo = b;                              // row that is stored
     int hl = h, bl = b;                              // row that is asked for
+    // (With the gate memory is reached through descriptors: a lane's 64-bit addresses cost 14 to 26 spilled registers at N = 8192.
+    // Without it plain addresses are as fast, and 3 % faster where a workgroup has one row.)
     u4w pf[PC];
     const auto ask = [&]() {
-        const u4w* p = reinterpret_cast<const u4w*>(in + row_off(bl, hl, H, L::N)) + tid;
+        const typename IO::T* p = in + row_off(bl, hl, H, L::N);
 #pragma unroll
-        for (int i = 0; i < PC; ++i) pf[i] = p[i * L::NT];
+        for (int i = 0; i < PC; ++i)
+            pf[i] = GATE ? row_load(row_rsrc(p, L::N * 2), 16 * tid, i * 16 * L::NT) : reinterpret_cast<const u4w*>(p)[tid + i * L::NT];
         if (++bl == B) { bl = 0; ++hl; }
     };
     ask();
@@ -147,7 +151,10 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
 #pragma unroll
         for (int j = 0; j < L::KB; ++j)
 #pragma unroll
-            for (int ke = 0; ke < TE; ++ke) ks[j][ke].w = s[((wave * L::KB + j) * TE + ke) * 64 + lane];
+            for (int ke = 0; ke < TE; ++ke) {
+                const int u = ((wave * L::KB + j) * TE + ke) * 64;
+                ks[j][ke].w = GATE ? __builtin_bit_cast(uint4, row_load(row_rsrc(s, L::N * 4), 16 * lane, 16 * u)) : s[u + lane];
+            }
         es0 = spec_exp_of(kspec, H, 2 * (int64_t)L::N)[h];
     };
     load_spec();
@@ -221,9 +228,13 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
         if (++b == B) { b = 0; ++h; }
     };
     const auto store = [&]() {
-        u4w* p = reinterpret_cast<u4w*>(out + row_off(bo, ho, H, L::N)) + tid;
+        typename IO::T* p = out + row_off(bo, ho, H, L::N);
 #pragma unroll
-        for (int i = 0; i < PC; ++i) put_once(p + i * L::NT, *reinterpret_cast<const u4w*>(mine + i * L::STEP));
+        for (int i = 0; i < PC; ++i) {
+            const u4w v = *reinterpret_cast<const u4w*>(mine + i * L::STEP);
+            if (GATE) row_store(row_rsrc(p, L::N * 2), 16 * tid, i * 16 * L::NT, v);
+            else put_once(reinterpret_cast<u4w*>(p) + tid + i * L::NT, v);
+        }
         if (++bo == B) { bo = 0; ++ho; }
     };
     const auto exponent = [&](int t) {
@@ -284,7 +295,7 @@ struct LBwdArgs {
     const uint4* tab;
 };
 template <int LG>
-using LB = LR<LG, LG == 13 ? 4 : 8>;
+using LB = LR<LG, LG == 13 ? 4 : 8, LG == 14 ? 3 : 0>;
 template <int LG, class IO, bool DU>
 __global__ void __launch_bounds__(LB<LG>::NT) __attribute__((amdgpu_waves_per_eu(2)))
 lbwd_kernel(const LBwdArgs<typename IO::T> q)
@@ -307,11 +318,19 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
     const u4w* pd = reinterpret_cast<const u4w*>(q.dy + row_off(split, h, H, L::N));
     u4w* po = DU ? reinterpret_cast<u4w*>(q.du + row_off(split, h, H, L::N)) : nullptr;
     u4w pa[PC], pb[PC];
-    const auto ask = [&](u4w (&v)[PC], const u4w* p) {
+    // Rows are asked for half by half, between the tiles, and stored between the k_b's: all at once, the requests of eight waves held
+    // the later four back by some 1800 cycles of 21000 per row, and the others at the barrier.  Where there is no row an empty
+    // descriptor asks for nothing: in a condition the pieces would come into registers of their own, be copied and so waited for.
+    // Backward, fp16, N=16384: B=8, H=256 98.5 -> 95.7 us, B=32, H=128 183 -> 176, B=1, H=256 27.2 -> 25.2; bf16 within 2 %.
+    const auto ask = [&](u4w (&v)[PC], const u4w* p, bool any, auto from, auto to) __attribute__((always_inline)) {
+        const auto d = row_rsrc(p, any ? L::N * 2 : 0);
 #pragma unroll
-        for (int i = 0; i < PC; ++i) v[i] = uniform(p, i * L::NT)[(unsigned)tid];
+        for (int i = decltype(from)::value; i < decltype(to)::value; ++i) v[i] = row_load(d, 16 * tid, i * 16 * L::NT);
     };
-    ask(pa, pu);
+    const std::integral_constant<int, 0> none;
+    const std::integral_constant<int, PC / 2> half;
+    const std::integral_constant<int, PC> all;
+    ask(pa, pu, true, none, all);
     LK<L, true, TAI, L::NAL> K;
     K.load(q.tab, wave, lane, shared + L::N_LDS * 64 + L::TC * 4);
     load_shared<L>(shared, q.tab, tid, true);
@@ -348,7 +367,7 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
     H8P U[NA];
     int eref = mu::EXP_NONE, ed = 0, eu = 0;         // unit of A; exponents (bf16) of the rows of dy and u
     uint32_t mu_ = 0u, md = 0u;
-    const auto part_a = [&](auto do3_, auto do1_) __attribute__((always_inline)) {
+    const auto part_a = [&](auto do3_, auto do1_, bool any) __attribute__((always_inline)) {      // (any: rows pd and pu are asked for)
         constexpr bool do3 = DU && decltype(do3_)::value, do1 = decltype(do1_)::value;
         const int ex3 = es + ed;
 #pragma unroll
@@ -366,6 +385,13 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
                 if (do3) v[k] = phase3_tile<L, TAI, false>(ex + P.own_tr[kt / TE] + P.in_group(kt), K, kt, mats, factors + 4 * kt);
                 if (do1) phase1_tile<L, false>(op[k], K, kt, mats, ex + P.own[kt / TE] + P.in_group(kt));
             }
+            if (do1) {
+                constexpr int LASTP = L::TPW / 2 - 1;
+                if (p == 0) ask(pa, pd, any, none, half);
+                if (p == (LASTP > 1)) ask(pa, pd, any, half, all);
+                if (p == LASTP - (LASTP > 1)) ask(pb, pu, any, none, half);
+                if (p == LASTP) ask(pb, pu, any, half, all);
+            }
             if (do3) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
@@ -374,13 +400,21 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    const auto store = [&]() {
+    // pieces i0 .. i1 - 1 of a row of du
+    const auto store = [&](const u4w (&o)[PC], bool any, int i0, int i1) __attribute__((always_inline)) {
+        const auto d = row_rsrc(po, any ? L::N * 2 : 0);
 #pragma unroll
-        for (int i = 0; i < PC; ++i) put_once(uniform(po, i * L::NT) + (unsigned)tid, *reinterpret_cast<const u4w*>(mine + i * L::STEP));
-        po += step;
+        for (int i = 0; i < PC; ++i)
+            if (i >= i0 && i < i1) row_store(d, 16 * tid, i * 16 * L::NT, o[i]);
+    };
+    const auto done = [&](u4w (&o)[PC]) __attribute__((always_inline)) {      // the row that phase 3 left
+#pragma unroll
+        for (int i = 0; i < PC; ++i) o[i] = *reinterpret_cast<const u4w*>(mine + i * L::STEP);
     };
     // the other three parts of row t
     const auto rest = [&](int t) __attribute__((always_inline)) {
+        u4w o[PC];
+        if (DU) done(o);
 #pragma unroll
         for (int i = 0; i < PC; ++i)
 #pragma unroll
@@ -396,13 +430,12 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
             phase2_fwd<L>(ex + P.mid_tr[j], K, j, mats, [&](int m, const f4& yr, const f4& yi) __attribute__((always_inline)) {
                 U[j * TE + m] = planes(yr, yi);
             });
+            if (DU) store(o, t > 0, j * PC / L::KB, (j + 1) * PC / L::KB);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (DU && t > 0) po += step;
         __syncthreads();
-        if (t + 1 < n) {
-            pu += step;
-            ask(pb, pu);
-        }
+        if (t + 1 < n) pu += step;
         if constexpr (BF) {
             md = pattern(1, t);
             ed = mu::row_exponent(md);
@@ -432,6 +465,8 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
                     const int kt = 2 * p + k;
                     phase1_tile<L, LG == 13>(op[k], K, kt, mats, ex + P.own[kt / TE] + P.in_group(kt));
                 }
+                if (p == 0) ask(pb, pu, t + 1 < n, none, half);
+                if (p == 1) ask(pb, pu, t + 1 < n, half, all);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -474,25 +509,22 @@ lbwd_kernel(const LBwdArgs<typename IO::T> q)
         }
     };
     exponent(0);
-    ask(pa, pd);
-    ask(pb, pu);
-    part_a(no, yes);
+    part_a(no, yes, true);
     __syncthreads();
     rest(0);
     for (int t = 1; t < n; ++t) {
         exponent(t);
         pd += step;
-        ask(pa, pd);
-        ask(pb, pu);
-        part_a(yes, yes);
+        part_a(yes, yes, true);
         __syncthreads();
-        if (DU) store();
         rest(t);
     }
     if (DU) {
-        part_a(yes, no);
+        part_a(yes, no, false);
         __syncthreads();
-        store();
+        u4w o[PC];
+        done(o);
+        store(o, true, 0, PC);
     }
 
     for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);

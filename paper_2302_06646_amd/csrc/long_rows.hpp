@@ -10,9 +10,10 @@ namespace longrows {
 using namespace planar;
 using mu::IsBf;
 
-template <int LG, int TPW_ = 8>
+template <int LG, int TPW_ = 8, int NAL_ = 0>
 struct LR {
     static constexpr int lg = LG, TPW = TPW_;            // TPW: tiles of a wave
+    static constexpr int NAL = NAL_;                     // of them, last ones whose matrices over d_a wait in LDS
     static constexpr int N = 1 << LG, TC = N / 256, TE = TC / 16, te = LG - 12;
     static constexpr int NW = TC / TPW, NT = 64 * NW, KB = 16 / NW;       // waves, threads, k_b's of a wave in phase 2
     static constexpr int SHIFT = 7;                       // forward chain: 2^-7, inverse: 2^-6 (see RC::SHIFT in engine_rows.hip)
@@ -35,9 +36,8 @@ struct LR {
     static constexpr int U_A = 0, U_AI = TC, U_TW = 2 * TC, U_C = U_TW + 1, U_CI = U_C + 32, U_LDS = U_CI + 32;
     static constexpr int U_B = 0, U_BI = 2 * TE, U_E = 4 * TE, U_EI = 6 * TE, N_LDS = 8 * TE;       // from U_LDS
     static constexpr int U_AP = U_LDS + N_LDS, U_S = U_AP + 1, UNITS = U_S + TC / 16;
-    // the backward pass keeps the matrices over d_a of its waves' last tiles in LDS, as many as fit
-    static constexpr int NAL = LG == 14 ? 3 : 0;
-    static constexpr size_t lds(bool bwd) { return sizeof(_Float16) * (EX + RAW) + 1024 * N_LDS + (bwd ? 64 * TC + 1024 * NAL * NW : 0); }
+    // factors: the tiles' factors are there, too
+    static constexpr size_t lds(bool factors) { return sizeof(_Float16) * (EX + RAW) + 1024 * (N_LDS + NAL * NW) + (factors ? 64 * TC : 0); }
 };
 
 // the constants of both lengths, one behind the other
@@ -354,6 +354,20 @@ __device__ __forceinline__ T* uniform(T* p, size_t i)
 {
     asm volatile("" : "+s"(i));
     return p + i;
+}
+// Memory behind a descriptor: 16 bytes at a lane's offset and a uniform one, without 64-bit addresses per lane; outside of `bytes`
+// loads give zero and stores do nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ u4w row_load(__amdgpu_buffer_rsrc_t d, int lane_off, int off)
+{
+    return __builtin_bit_cast(u4w, __builtin_amdgcn_raw_buffer_load_b128(d, lane_off, off, 0));
+}
+__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t d, int lane_off, int off, const u4w& v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, d, lane_off, off, BUF_ONCE);
 }
 // pattern of the largest sample of a wave's pieces (bf16): see band_or_exact
 template <int PC>
