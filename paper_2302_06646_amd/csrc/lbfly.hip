@@ -328,31 +328,39 @@ lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ s
 }
 
 // -------------------------------------------------------------------------------------------------------------------
-// Backward, register-chained.  grid = (nsplit, H): workgroup (sp, h) owns rows b = sp, sp + nsplit, ... of head h, one wave per
-// tile.  dy goes through the adjoint of the inverse blocks exactly as u goes through the forward blocks, so the pipeline is the
-// forward kernel's with two rows in flight side by side, and the same two barriers:
-//     [row b-1: the input of B_0 from that of B_1; gradients through A_1, A_0; du.  row b: u through A_0, A_1, dy through
+// Backward, register-chained.  grid = (nsplit, H): workgroup (sp, h) owns rows b = sp, sp + nsplit, ... of head h.  dy goes through
+// the adjoint of the inverse blocks exactly as u goes through the forward blocks, so there are two chains of waves side by side, u's
+// and dy's, with a wave per tile each and the forward kernel's two barriers per row:
+//     [row b-1: the input of B_0 from that of B_1 | gradients through A_1, A_0; du.  row b: u through A_0, A_1 | dy through
 //      B_0^H, B_1^H]  barrier  [row b: last blocks, spectrum, and their adjoints]
 // The gradient of a block is the 16 x 16 sum over columns of (gradient at its output) x conj(its input): two more matrix
-// products per tile with the columns as K, on operands whose lanes are the slots.  Both index orders of a tile are needed
-// for that; those that pass the exchange buffers are read from there either way, the others take a wave's own 1 KB of LDS.
+// products per tile with the columns as K, on operands whose lanes are the slots.  u's waves keep the sums of the B's and of the
+// spectrum, dy's those of the A's; the operand that the other chain makes is read from LDS.  Both index orders of a tile are needed:
+// what passes the exchange buffers is read from there either way, the rest takes a wave's own 1 KB of LDS.  u's waves take
+// the gradient at the product with the spectrum a second time, rather than wait for dy's.
 // The twiddle factors that were folded into a tile's matrices scale rows or columns of its 16 x 16 sums: applied once, at
-// the end, where the waves' sums meet in wave order.  Per 256 points and row 33 matrix and 187 vector instructions; 240
-// registers (matrices 76, sums 48).  B=16, H=768, N=1024 bf16: 105 us; the form it replaced (every block a trip through LDS
-// with its own barrier, seven buffers) 292 and 9.3 to add its partial sums.
+// the end, where the waves' sums meet in wave order.
+// Per 256 points and row 35 matrix and 195 vector instructions, and 9 KB written to LDS and 27 read.  One wave for both chains had 33 and 187, but needed 240 registers, and its two waves per SIMD left the chip waiting for LDS and for results; now four
+// fit, without spills in the row loop, since the last stage's matrices (the same for all tiles) are read from LDS.  A row of N = 1024
+// takes 3280 cycles of a CU (3700 before), of which 2280 are issue and 2060 LDS; 8900 cycles of a head are its constants, 5000 its sums.
+// bf16, B=16, H=768: N = 256 33.0 -> 29.4 us, 512 55.6 -> 47.7, 1024 99.2 -> 91.6 (a lane's registers for the next head's
+// constants, so that they come in during the sums: 66 spills and 96 us).
 // -------------------------------------------------------------------------------------------------------------------
 struct LbGrads {            // where the sums go: of share sp and head h at index sp * H + h
     float2 *shat, *qf, *qi;
     int q_stride;
 };
 
+// numbers in LDS: what the first parts leave for the middle one, what the middle one leaves for the last, a row of both tensors on
+// its way in, du on its way out; then a first part's x_1 or g_1 for the other chain's last part, by the row's parity, a wave's own
+// 1 KB and the last stage's matrices, or in the end the sums
 template <int LG>
-constexpr int lbb_numbers() { return Geo<LG>::T * (2 * Geo<LG>::XS + 2 * Geo<LG>::IS + Geo<LG>::OS + 512); }
+constexpr int lbb_kept() { return Geo<LG>::T * (4 * Geo<LG>::XS + 2 * Geo<LG>::IS + Geo<LG>::OS); }
 template <int LG>
 constexpr size_t lbb_lds()
 {
-    const size_t work = sizeof(_Float16) * lbb_numbers<LG>(), red = sizeof(float2) * 4 * NBLK * Geo<LG>::T;
-    const size_t a = work > red ? work : red;
+    const size_t work = sizeof(_Float16) * (Geo<LG>::T * 6 * 512 + 4 * 1024), red = sizeof(float2) * 6 * NBLK * Geo<LG>::T;
+    const size_t a = sizeof(_Float16) * lbb_kept<LG>() + (work > red ? work : red);
     return a > HeadData<LG>::bytes ? a : HeadData<LG>::bytes;
 }
 
@@ -365,66 +373,81 @@ __device__ __forceinline__ void outer(const H8P& G, const H8P& X, f4& qr, f4& qi
     qi = __builtin_amdgcn_mfma_f32_16x16x32_f16(G.v, s.v, qi, 0, 0, 0);      // Gi Xr - Gr Xi
 }
 
-template <int LG, class IO>
-__global__ void __launch_bounds__(64 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(2)))
-lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
+template <int LG, class IO, int chain>
+__device__ __forceinline__ void
+lb_bwd_chain(f4* lds4, const int t, const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
               const float2* __restrict__ shat, const float2* __restrict__ Af, const float2* __restrict__ Ai,
               typename IO::T* __restrict__ du, LbGrads out, int B, int H, const float2* __restrict__ stw)
 {
     using G = Geo<LG>;
     constexpr int T = G::T, N = G::N, LB = G::LB;
-    __shared__ f4 smem[lbb_lds<LG>() / 16];
-    _Float16 *exu = reinterpret_cast<_Float16*>(smem), *exg = exu + T * G::XS, *inu = exg + T * G::XS;
-    _Float16 *ing = inu + T * G::IS, *outb = ing + T * G::IS, *priv = outb + T * G::OS;
-    float2* sm2 = reinterpret_cast<float2*>(smem);
     const int sp = blockIdx.x, nsplit = gridDim.x, h = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, t = tid >> 6, c = lane & 15, g = lane >> 4;
+    const int wave = chain * T + t, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4, tid = 64 * t + lane;
+    _Float16 *exs = reinterpret_cast<_Float16*>(lds4), *exo = exs + 2 * T * G::XS, *ins = exo + 2 * T * G::XS;
+    _Float16 *outb = ins + 2 * T * G::IS, *kept = exs + lbb_kept<LG>(), *priv = kept + 4 * T * 512;
+    h8* mats = reinterpret_cast<h8*>(priv + 2 * T * 512) + lane;          // [A_2, B_2, B_2^H, A_2^H][re, im][lane]
+    float2* sm2 = reinterpret_cast<float2*>(lds4);
     const size_t step = (size_t)nsplit * H * (N / 2);
-    const uint32_t* up = reinterpret_cast<const uint32_t*>(u + row_off(sp, h, H, N)) + tid;
-    const uint32_t* gp = reinterpret_cast<const uint32_t*>(dy + row_off(sp, h, H, N)) + tid;
+    const uint32_t* xp = reinterpret_cast<const uint32_t*>((chain ? dy : u) + row_off(sp, h, H, N)) + tid;
     uint32_t* dp = reinterpret_cast<uint32_t*>(du ? du + row_off(sp, h, H, N) : nullptr) + tid;
     const int n = (B - sp + nsplit - 1) / nsplit;                       // rows of this workgroup
     HeadData<LG> hd;
-    hd.load(Af, Ai, shat, h, tid);
-    uint32_t wu = *up, wg = *gp, nu = 0, ng = 0;
-    if (n > 1) { nu = up[step]; ng = gp[step]; }
-    up += 2 * step;
-    gp += 2 * step;
+    if (chain == 0) hd.load(Af, Ai, shat, h, tid);
+    uint32_t wx = *xp, nx = n > 1 ? xp[step] : 0u;
+    xp += 2 * step;
     f4 cr, ci;
     inner_twiddles(cr, ci, stw, lane);
     LaneTw<LG> W;
     W.load(stw, t, lane);
-    hd.put(sm2, tid);
+    if (chain == 0) hd.put(sm2, tid);
     __syncthreads();
+    // The chain's matrices of the first part and the last: u's A_0, A_1, B_1; dy's the adjoints of B_0, B_1, A_1, A_0
     const Entries<LG> E{sm2, sm2 + 48 * ROW};
-    const Rl A0 = make_rl([&](int o, int i) { return E.a0(o, i, W.w0c); }, lane);          // (i & 3: of the lane's four)
-    const Rl B0H = make_rl([&](int o, int i) { return conj2(E.b0(i, o, W.w0c)); }, lane);
-    const Cx A1 = make_cx([&](int o, int i) { return E.a1(o, i, W.w1c); }, lane);
-    const Cx A1H = make_cx([&](int o, int i) { return conj2(E.a1(i, o, W.w1q[i & 3])); }, lane);
-    const Cx B1 = make_cx([&](int o, int i) { return E.b1(o, i, W.w1q[i & 3]); }, lane);
-    const Cx B1H = make_cx([&](int o, int i) { return conj2(E.b1(i, o, W.w1c)); }, lane);
-    const Cx A2 = make_cx([&](int o, int i) { return E.last(E.A, o, i); }, lane);
-    const Cx A2H = make_cx([&](int o, int i) { return conj2(E.last(E.A, i, o)); }, lane);
-    const Cx B2 = make_cx([&](int o, int i) { return E.last(E.B, o, i); }, lane);
-    const Cx B2H = make_cx([&](int o, int i) { return conj2(E.last(E.B, i, o)); }, lane);
-    const h8 A0H = make_cx([&](int o, int i) { return scaled(conj2(E.a0(i, o, W.w0q[i & 3])), G::yscale()); }, lane).re;
+    Rl M0;
+    Cx M1, M4;
+    h8 M5;
+    if (chain == 0) {
+        M0 = make_rl([&](int o, int i) { return E.a0(o, i, W.w0c); }, lane);
+        M1 = make_cx([&](int o, int i) { return E.a1(o, i, W.w1c); }, lane);
+        M4 = make_cx([&](int o, int i) { return E.b1(o, i, W.w1q[i & 3]); }, lane);
+        M5 = M1.re;                                                     // (not used)
+    } else {
+        M0 = make_rl([&](int o, int i) { return conj2(E.b0(i, o, W.w0c)); }, lane);
+        M1 = make_cx([&](int o, int i) { return conj2(E.b1(i, o, W.w1c)); }, lane);
+        M4 = make_cx([&](int o, int i) { return conj2(E.a1(i, o, W.w1q[i & 3])); }, lane);
+        M5 = make_cx([&](int o, int i) { return scaled(conj2(E.a0(i, o, W.w0q[i & 3])), G::yscale()); }, lane).re;
+    }
+    // the last stage's do not depend on t: in LDS, A_2, B_2, and their adjoints in the other order
+    Cx L0, L1;
+    if (t == 0) {
+        if (chain == 0) {
+            L0 = make_cx([&](int o, int i) { return E.last(E.A, o, i); }, lane);
+            L1 = make_cx([&](int o, int i) { return E.last(E.B, o, i); }, lane);
+        } else {
+            L0 = make_cx([&](int o, int i) { return conj2(E.last(E.B, i, o)); }, lane);
+            L1 = make_cx([&](int o, int i) { return conj2(E.last(E.A, i, o)); }, lane);
+        }
+    }
     f4 sr, si;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const float2 s = sm2[HeadData<LG>::BLK + freq_at<LG>(t, 4 * g + r, c, ROW)];
         sr[r] = s.x;
-        si[r] = s.y;
+        si[r] = chain ? -s.y : s.y;                                     // (dy's chain multiplies by the conjugate)
     }
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    f4 a0r = zero, a0i = zero, a1r = zero, a1i = zero, a2r = zero, a2i = zero;      // sums of the blocks' gradients
-    f4 b0r = zero, b0i = zero, b1r = zero, b1i = zero, b2r = zero, b2i = zero;
-    f4 dsr = zero, dsi = zero;
+    f4 q0r = zero, q0i = zero, q1r = zero, q1i = zero, q2r = zero, q2i = zero;      // sums: u's waves B_0, B_1, B_2; dy's A_0, A_1, A_2
+    f4 dsr = zero, dsi = zero;                                                      // the spectrum's (u's waves)
 
     const int own = G::at(t, c, g), own_tr = G::at(t, 4 * g + (c >> 2), c & 3);      // tile t: row c, or transposed
     const int mid = G::slot_at(t, c, g), mid_tr = G::slot_at(t, 4 * g + (c >> 2), c & 3);
     const int trow = 16 * (4 * g + (c >> 2)) + 4 * ((c & 3) ^ g), row = 16 * c + 4 * (g ^ (c >> 2));   // a plain 16 x 16 tile
-    const _Float16 *tu = inu + t * G::IS, *tg = ing + t * G::IS;
-    _Float16* pv = priv + t * 512;
+    _Float16 *ex = exs + chain * T * G::XS, *eo = exo + chain * T * G::XS;
+    const _Float16* ey = exs + (1 - chain) * T * G::XS + mid;                        // the other chain's, as slots
+    const _Float16 *tin = ins + (chain * T + t) * G::IS + trow, *tother = ins + ((1 - chain) * T + t) * G::IS + row;
+    _Float16* pv = priv + wave * 512;
+    _Float16* kmine = kept + wave * 512 + row;                                       // + parity * 2 T * 512
+    const _Float16* kother = kept + ((1 - chain) * T + t) * 512 + trow;
     const auto transposed = [&](const H8P& x) {
         H8P y;
         wr4(pv + row, x.p[0]);
@@ -435,120 +458,103 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
     };
     __syncthreads();
     // both rows' tiles: the padding, d_0 >= 8, stays zero; a row's samples are the other half
-    for (int i = tid; i < T * 128; i += 64 * T) reinterpret_cast<uint32_t*>(inu + (i >> 6) * G::IS + 128)[i & 63] = 0;
-    row_in<LG>(inu, to_h2<IO>(wu), tid);
-    row_in<LG>(ing, to_h2<IO>(wg), tid);
+    if (t == 0) {
+        mats[chain * 256] = L0.re;
+        mats[chain * 256 + 64] = L0.im;
+        mats[chain * 256 + 128] = L1.re;
+        mats[chain * 256 + 192] = L1.im;
+    }
+    for (int i = threadIdx.x; i < T * 128; i += 128 * T) reinterpret_cast<uint32_t*>(ins + (i >> 6) * G::IS + 128)[i & 63] = 0;
+    row_in<LG>(ins + chain * T * G::IS, to_h2<IO>(wx), tid);
     __syncthreads();
 
-    H8P x1t, g1t;           // kept from a row's first part to its last
-    h4 uo, go;
-    const auto first = [&]() {
-        {
-            const h4 x = tr_read(tu + trow);
-            uo = rd4(tu + row);                                         // lane d_0, d_1 = 4g ..
-            f4 yr = mm(x, A0.re), yi = mm(x, A0.im);                    // lane k_0, d_1 = 4g ..
-            cmul4<false>(yr, yi, cr, ci);
-            const H8P x1 = planes(yr, yi);
-            x1t = transposed(x1);                                       // lane d_1, k_0 = 4g ..
-            const H8P x2 = planes(mm(A1.re, x1.v), mm(A1.im, x1.v));    // lane k_0, k_1 = 4g ..
-            wr4(exu + own, x2.p[0]);
-            wr4(exu + own + 256, x2.p[1]);
-        }
-        {
-            const h4 x = tr_read(tg + trow);
-            go = rd4(tg + row);
-            f4 yr = mm(x, B0H.re), yi = mm(x, B0H.im);
-            cmul4<false>(yr, yi, cr, ci);
-            const H8P g1 = planes(yr, yi);
-            g1t = transposed(g1);
-            const H8P g2 = planes(mm(B1H.re, g1.v), mm(B1H.im, g1.v));
-            wr4(exg + own, g2.p[0]);
-            wr4(exg + own + 256, g2.p[1]);
-        }
+    h4 other;               // the other tensor's samples, kept from a row's first part to its last
+    const auto first = [&](int b) __attribute__((always_inline)) {
+        const h4 x = tr_read(tin);
+        other = rd4(tother);                                            // lane d_0, d_1 = 4g ..
+        f4 yr = mm(x, M0.re), yi = mm(x, M0.im);                        // lane k_0, d_1 = 4g ..
+        cmul4<false>(yr, yi, cr, ci);
+        const H8P x1 = planes(yr, yi);
+        _Float16* k = kmine + (b & 1) * 2 * T * 512;                    // (read transposed by the other chain's wave t)
+        wr4(k, x1.p[0]);
+        wr4(k + 256, x1.p[1]);
+        const H8P x2 = planes(mm(M1.re, x1.v), mm(M1.im, x1.v));        // lane k_0, k_1 = 4g ..
+        wr4(ex + own, x2.p[0]);
+        wr4(ex + own + 256, x2.p[1]);
     };
-    const auto middle = [&]() {
-        H8P x, xt, y, yt;
-        x.p[0] = tr_read(exu + mid_tr);                                 // lane k_1, slots 4g ..
-        x.p[1] = tr_read(exu + mid_tr + 256);
-        xt.p[0] = rd4(exu + mid);                                       // lane slot, k_1 = 4g ..
-        xt.p[1] = rd4(exu + mid + 256);
-        y.p[0] = tr_read(exg + mid_tr);
-        y.p[1] = tr_read(exg + mid_tr + 256);
-        yt.p[0] = rd4(exg + mid);
-        yt.p[1] = rd4(exg + mid + 256);
-        const f4 zr = mm(A2.re, x.v), zi = mm(A2.im, x.v);              // the transform of u: lane k_1, slots 4g ..
-        f4 wr = zr, wi = zi;
-        cmul4<false>(wr, wi, sr, si);
-        const H8P w = planes(wr, wi);
-        const H8P wt = transposed(w);
-        const H8P v = planes(mm(w.v, B2.re), mm(w.v, B2.im));           // lane slot, k_1 = 4g ..
-        wr4(exu + mid, v.p[0]);
-        wr4(exu + mid + 256, v.p[1]);
-        outer(yt, wt, b2r, b2i);
-        f4 hr = mm(B2H.re, y.v), hi = mm(B2H.im, y.v);                  // gradient at the product with the spectrum
+    const auto middle = [&]() __attribute__((always_inline)) {
+        H8P x, yt;
+        x.p[0] = tr_read(ex + mid_tr);                                  // lane k_1, slots 4g ..
+        x.p[1] = tr_read(ex + mid_tr + 256);
+        yt.p[0] = rd4(ey);                                              // the other chain's: lane slot, k_1 = 4g ..
+        yt.p[1] = rd4(ey + 256);
+        const h8* m = mats + chain * 256;
+        f4 zr = mm(m[0], x.v), zi = mm(m[64], x.v);                    // lane k_1, slots 4g ..
+        if (chain == 0) {
+            H8P y;
+            const _Float16* e = exs + T * G::XS + mid_tr;
+            y.p[0] = tr_read(e);
+            y.p[1] = tr_read(e + 256);
+            const f4 hr = mm(mats[256], y.v), hi = mm(mats[320], y.v);          // gradient at the product with the spectrum
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            dsr[r] += hr[r] * zr[r] + hi[r] * zi[r];
-            dsi[r] += hi[r] * zr[r] - hr[r] * zi[r];
+            for (int r = 0; r < 4; ++r) {
+                dsr[r] += hr[r] * zr[r] + hi[r] * zi[r];
+                dsi[r] += hi[r] * zr[r] - hr[r] * zi[r];
+            }
         }
-        cmul4<true>(hr, hi, sr, si);
-        const H8P q = planes(hr, hi);
-        const H8P qt = transposed(q);
-        const H8P p = planes(mm(q.v, A2H.re), mm(q.v, A2H.im));
-        wr4(exg + mid, p.p[0]);
-        wr4(exg + mid + 256, p.p[1]);
-        outer(qt, xt, a2r, a2i);
+        cmul4<false>(zr, zi, sr, si);
+        const H8P w = planes(zr, zi);
+        const H8P wt = transposed(w);
+        const H8P v = planes(mm(w.v, m[128]), mm(w.v, m[192]));           // lane slot, k_1 = 4g ..
+        wr4(eo + mid, v.p[0]);
+        wr4(eo + mid + 256, v.p[1]);
+        if (chain == 0) outer(yt, wt, q2r, q2i);
+        else outer(wt, yt, q2r, q2i);
     };
-    const auto last = [&]() {
-        {
-            H8P v, vt;
-            v.p[0] = rd4(exu + own);                                    // lane k_0, k_1 = 4g ..
-            v.p[1] = rd4(exu + own + 256);
-            vt.p[0] = tr_read(exu + own_tr);                            // lane k_1, k_0 = 4g ..
-            vt.p[1] = tr_read(exu + own_tr + 256);
-            f4 yr = mm(B1.re, v.v), yi = mm(B1.im, v.v);                // lane k_0, d_1 = 4g ..
+    const auto last = [&](int b) __attribute__((always_inline)) {
+        H8P v, vt, kt;
+        v.p[0] = rd4(eo + own);                                         // lane k_0, k_1 = 4g ..
+        v.p[1] = rd4(eo + own + 256);
+        vt.p[0] = tr_read(eo + own_tr);                                 // lane k_1, k_0 = 4g ..
+        vt.p[1] = tr_read(eo + own_tr + 256);
+        const _Float16* k = kother + (b & 1) * 2 * T * 512;
+        kt.p[0] = tr_read(k);                                           // lane d_1, k_0 = 4g ..
+        kt.p[1] = tr_read(k + 256);
+        if (chain == 0) {
+            f4 yr = mm(M4.re, v.v), yi = mm(M4.im, v.v);                // lane k_0, d_1 = 4g ..
             cmul4<true>(yr, yi, cr, ci);
             const H8P w0 = planes(yr, yi);
-            outer(g1t, vt, b1r, b1i);
-            b0r = __builtin_amdgcn_mfma_f32_16x16x16f16(go, w0.p[0], b0r, 0, 0, 0);
-            b0i = __builtin_amdgcn_mfma_f32_16x16x16f16(go, w0.p[1], b0i, 0, 0, 0);     // (minus the imaginary part)
-        }
-        {
-            H8P v, vt;
-            v.p[0] = rd4(exg + own);
-            v.p[1] = rd4(exg + own + 256);
-            vt.p[0] = tr_read(exg + own_tr);
-            vt.p[1] = tr_read(exg + own_tr + 256);
-            f4 yr = mm(v.v, A1H.re), yi = mm(v.v, A1H.im);              // lane d_1, k_0 = 4g ..
+            outer(kt, vt, q1r, q1i);
+            q0r = __builtin_amdgcn_mfma_f32_16x16x16f16(other, w0.p[0], q0r, 0, 0, 0);
+            q0i = __builtin_amdgcn_mfma_f32_16x16x16f16(other, w0.p[1], q0i, 0, 0, 0);     // (minus the imaginary part)
+        } else {
+            f4 yr = mm(v.v, M4.re), yi = mm(v.v, M4.im);                // lane d_1, k_0 = 4g ..
             cmul4<true>(yr, yi, cr, ci);
             const H8P g6 = planes(yr, yi);
-            outer(vt, x1t, a1r, a1i);
+            outer(vt, kt, q1r, q1i);
             const H8P g6t = transposed(g6);                             // lane k_0, d_1 = 4g ..
-            a0r = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[0], uo, a0r, 0, 0, 0);
-            a0i = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[1], uo, a0i, 0, 0, 0);
-            put_out<IO>(outb + t * G::OS, mm(g6.v, A0H), lane);
+            q0r = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[0], other, q0r, 0, 0, 0);
+            q0i = __builtin_amdgcn_mfma_f32_16x16x16f16(g6t.p[1], other, q0i, 0, 0, 0);
+            put_out<IO>(outb + t * G::OS, mm(g6.v, M5), lane);
         }
     };
     const auto rows_in = [&](int b) {                                   // row b + 1; row b + 2 asked for
-        row_in<LG>(inu, to_h2<IO>(nu), tid);
-        row_in<LG>(ing, to_h2<IO>(ng), tid);
+        row_in<LG>(ins + chain * T * G::IS, to_h2<IO>(nx), tid);
         if (b + 2 < n) {
-            nu = *up;
-            ng = *gp;
-            up += step;
-            gp += step;
+            nx = *xp;
+            xp += step;
         }
     };
-    first();
+    first(0);
     __syncthreads();
     middle();
     rows_in(0);
     __syncthreads();
     for (int b = 1; b < n; ++b) {
-        last();
-        first();
+        last(b - 1);
+        first(b);
         __syncthreads();
-        if (du) {
+        if (du && chain == 0) {
             put_once(dp, row_out<LG>(outb, tid));
             dp += step;
         }
@@ -557,61 +563,54 @@ lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __res
         __syncthreads();
     }
     W.load(stw, t, lane);                    // (for the sums below; no registers for them in the loop)
-    last();
+    last(n - 1);
     __syncthreads();
-    if (du) put_once(dp, row_out<LG>(outb, tid));
+    if (du && chain == 0) put_once(dp, row_out<LG>(outb, tid));
 
     const size_t at = (size_t)sp * H + h;
-    if (out.shat) {
+    if (out.shat && chain == 0) {
         float2* ps = out.shat + at * G::L;
 #pragma unroll
         for (int r = 0; r < 4; ++r) ps[freq_at<LG>(t, 4 * g + r, c)] = make_float2(dsr[r] * G::yscale(), dsi[r] * G::yscale());
     }
-    // the waves' sums of one block of either chain, [chain][wave][entry]; then entry by entry in wave order.  Two buffers take
-    // turns, so that one barrier per block does.
-    __syncthreads();
-    const auto put_sums = [&](int s) {
-        float2* buf = sm2 + (s & 1) * 2 * T * NBLK;
+    // the waves' sums, [block][chain][wave][entry], behind du's last row; then entry by entry in wave order
+    float2* sums = reinterpret_cast<float2*>(kept);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int e = (4 * g + r) * 16 + c;
-            float2 f, q;
-            if (s == 0) {
-                f = cmulc(make_float2(a0r[r], a0i[r]), W.w0q[r]);
-                q = cmul(make_float2(b0r[r], -b0i[r]), W.w0c);
-            } else if (s == 1) {
-                f = cmulc(make_float2(a1r[r], a1i[r]), W.w1q[r]);
-                q = cmul(make_float2(b1r[r], b1i[r]), W.w1c);
-            } else {
-                f = make_float2(a2r[r], a2i[r]);
-                q = make_float2(b2r[r], b2i[r]);
-            }
-            buf[t * NBLK + e] = f;
-            buf[(T + t) * NBLK + e] = q;
-        }
-    };
-    put_sums(0);
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        __syncthreads();
-        if (s < 2) put_sums(s + 1);
-        const float2* buf = sm2 + (s & 1) * 2 * T * NBLK;
-        const float sc = G::yscale() / (float)(1 << stage_shift(s == 2 ? LB : 4));
-        for (int e2 = tid; e2 < 2 * NBLK; e2 += 64 * T) {
-            const int chain = e2 / NBLK, e = e2 % NBLK, i = e / 16, j = e % 16;
-            float2* q = chain ? out.qi : out.qf;
-            if (!q) continue;
-            float2 a = make_float2(0.f, 0.f);
-            const float2* p = buf + chain * T * NBLK;
-            if (s < 2) {
-                for (int w = 0; w < T; ++w) a = cadd(a, p[w * NBLK + e]);
-            } else if (i < T && j < T) {             // the diagonal blocks of I (x) A_2 all carry the same parameters
-                for (int w = 0; w < T; ++w)
-                    for (int d = 0; d < 16; d += T) a = cadd(a, p[w * NBLK + (d + i) * 16 + d + j]);
-            }
-            q[at * out.q_stride + s * NBLK + e] = make_float2(a.x * sc, a.y * sc);
-        }
+    for (int r = 0; r < 4; ++r) {
+        float2* p = sums + ((1 - chain) * T + t) * NBLK + (4 * g + r) * 16 + c;
+        p[0] = chain ? cmulc(make_float2(q0r[r], q0i[r]), W.w0q[r]) : cmul(make_float2(q0r[r], -q0i[r]), W.w0c);
+        p[2 * T * NBLK] = chain ? cmulc(make_float2(q1r[r], q1i[r]), W.w1q[r]) : cmul(make_float2(q1r[r], q1i[r]), W.w1c);
+        p[4 * T * NBLK] = make_float2(q2r[r], q2i[r]);
     }
+    __syncthreads();
+    for (int e3 = threadIdx.x; e3 < 6 * NBLK; e3 += 128 * T) {
+        const int which = (e3 / NBLK) & 1, s = e3 / (2 * NBLK), e = e3 % NBLK, i = e / 16, j = e % 16;
+        float2* q = which ? out.qi : out.qf;
+        if (!q) continue;
+        float2 a = make_float2(0.f, 0.f);
+        const float2* p = sums + (e3 / NBLK) * T * NBLK;
+        if (s < 2) {
+            for (int w = 0; w < T; ++w) a = cadd(a, p[w * NBLK + e]);
+        } else if (i < T && j < T) {             // the diagonal blocks of I (x) A_2 all carry the same parameters
+            for (int w = 0; w < T; ++w)
+                for (int d = 0; d < 16; d += T) a = cadd(a, p[w * NBLK + (d + i) * 16 + d + j]);
+        }
+        const float sc = G::yscale() / (float)(1 << stage_shift(s == 2 ? LB : 4));
+        q[at * out.q_stride + s * NBLK + e] = make_float2(a.x * sc, a.y * sc);
+    }
+}
+
+// Waves 0 .. T - 1 do u's chain, the others dy's; a workgroup's barriers are the same in number on both sides.
+template <int LG, class IO>
+__global__ void __launch_bounds__(128 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(4)))
+lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
+              const float2* __restrict__ shat, const float2* __restrict__ Af, const float2* __restrict__ Ai,
+              typename IO::T* __restrict__ du, LbGrads out, int B, int H, const float2* __restrict__ stw)
+{
+    extern __shared__ f4 lds4[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < Geo<LG>::T) lb_bwd_chain<LG, IO, 0>(lds4, wave, dy, u, shat, Af, Ai, du, out, B, H, stw);
+    else lb_bwd_chain<LG, IO, 1>(lds4, wave - Geo<LG>::T, dy, u, shat, Af, Ai, du, out, B, H, stw);
 }
 
 // Sums the partial results over the shares (fixed order): grid (pieces of a head's results, H)
@@ -1001,7 +1000,9 @@ hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float*
         hipLaunchKernelGGL((lb_bwd2_kernel<IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(Lb2::NT), Lb2::lds, st, (const T*)dy,
                            (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du, out, (int)B, (int)H, tb.stw);
     } else {
-        hipLaunchKernelGGL((lb_bwd_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(64 << (LG - 8)), 0, st,
+        const hipError_t e = set_lds(lb_bwd_kernel<LG, IO>, lbb_lds<LG>());
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((lb_bwd_kernel<LG, IO>), dim3((unsigned)nsplit, (unsigned)H), dim3(128 << (LG - 8)), lbb_lds<LG>(), st,
                            (const T*)dy, (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)du, out,
                            (int)B, (int)H, tb.stw);
     }

@@ -168,6 +168,21 @@ def test_runs_of_rows_and_uneven_shares(N, io, B, H):
     _check_blocks(g["dAi"][heads], rdAi, N, TOL[io], label + " dAi")
 
 
+# The ends of the backward pipeline of rows: with more heads than 512 a workgroup takes every row of its head, here 1 to 4 (first and
+# last row the same, no row asked for ahead, one, two: both places of what one chain of waves keeps for the other).
+@pytest.mark.parametrize("N", [256, 512, 1024])
+@pytest.mark.parametrize("B", [1, 2, 3, 4])
+def test_backward_of_few_rows_a_head(N, B):
+    io, H, heads = wl.F16, 513, [0, 255, 256, 512]
+    u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=5)
+    g = _run(u_s, dy_s, k, D, Af32, Ai32, io)
+    rdu, rdshat, rdAf, rdAi = lbfly.lbfly_bwd(dy_v[:, heads], u_v[:, heads], lbfly.spectrum(k[heads], D[heads]), Af[heads], Ai[heads])
+    label = f"lbfly few rows N={N} B={B}"
+    _compare({"du": g["du"][:, heads], "dshat": _ri(g["dshat"][heads])}, {"du": rdu, "dshat": _ri(rdshat)}, TOL[io], label)
+    _check_blocks(g["dAf"][heads], rdAf, N, TOL[io], label + " dAf")
+    _check_blocks(g["dAi"][heads], rdAi, N, TOL[io], label + " dAi")
+
+
 def test_optional_outputs_repeatability_and_error_codes():
     N, io, B, H = 512, wl.F16, 4, 3
     u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=2)
