@@ -396,7 +396,7 @@ chunk_conv_kernel(const typename IO::T* __restrict__ in, const float2* __restric
 // (ws_du may be null), at the end those of the inverse transform of A 2^-e to ws_A[(share H + h) R + k_1] with e behind them
 // (exps), and the chunk's part of dD (piece n_1 = k_1 of the rows) to dD_part at the same index.  There are no
 // registers to ask for the next row ahead: with 32 of them, spills made B=8, H=128, N=65536 430 us instead of 386 (as eight chunks
-// per pair of rows for dk, and du by itself: 690).  As it is, 2 are spilled at R = 4 and 17 to 22 at R = 8.
+// per pair of rows for dk, and du by itself: 690).  As it is, 2 are spilled at R = 4 and 14 to 21 at R = 8.
 // -------------------------------------------------------------------------------------------------------------------
 template <class T>
 struct CBwdArgs {
@@ -453,8 +453,11 @@ chunk_bwd_kernel(const CBwdArgs<typename IO::T> q)
             for (int j = 0; j < 4; ++j) acc[k][j] = make_float2(0.f, 0.f);
         float dsum = 0.f;
         for (int b = share; b < B; b += q.nshare) {
-            x.ask_first(pu, tid);
-            x.stage(mine, pu, fu, tid);
+            {
+                RowIn<IO, R, 8 / R, 2> xu;                  // (the registers of U are free: N = 131072, H=64 90.5 -> 88.8 us)
+                xu.ask_first(pu, tid);
+                xu.stage(mine, pu, fu, tid);
+            }
             __syncthreads();
             phase1_chunk<false>(K, mats, P, ex);
             __syncthreads();
@@ -576,6 +579,7 @@ chunk_kspec_kernel(const float* __restrict__ k, const float* __restrict__ D, con
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const Run<R> me(H);
     constexpr bool HOLD = R == 4;
+    static_assert(4 * L::N == 128 * L::NT, "a thread touches 128 bytes");
     f4 v[HOLD ? PC : 1][R][2];
     const auto piece = [&](int to, int n, int i, int h) __attribute__((always_inline)) {
         const f4* p = reinterpret_cast<const f4*>(k + (size_t)h * R * L::N) + (size_t)n * (L::N / 4) + 2 * (tid + i * L::NT);
@@ -660,6 +664,11 @@ chunk_kspec_kernel(const float* __restrict__ k, const float* __restrict__ D, con
             *reinterpret_cast<u4w*>(mine + i * L::STEP) = re;
             *reinterpret_cast<u4w*>(mine + L::N + i * L::STEP) = im;
         }
+        // One word of every 128 bytes of the next head, of a part each for the R workgroups that read it: no registers are free to ask
+        // for the head itself (32 spills, 31 us at B=1, H=128, N=65536), but this much has it in the XCD's L2 when they ask (25.9 -> 23.8;
+        // R = 8, which asks piece by piece, 35.7 -> 37.1 at H=64)
+        uint32_t near = 0;
+        if (HOLD) near = uniform(reinterpret_cast<const uint32_t*>(k), ((size_t)min(h + 1, H - 1) * R + me.k1) * L::N)[(unsigned)tid * 32];
         __syncthreads();
         phase1_chunk<true>(K, mats, P, ex);
         __syncthreads();
@@ -673,6 +682,7 @@ chunk_kspec_kernel(const float* __restrict__ k, const float* __restrict__ D, con
                 out[((wave * L::KB + j) * TE + m) * 64 + lane] = planes(yr * alpha + beta, yi * alpha).w;
             });
         }
+        if (HOLD) asm volatile("" ::"v"(near));
         __syncthreads();                             // (the buffer, and mred)
     }
 }
