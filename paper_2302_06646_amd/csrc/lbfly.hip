@@ -972,6 +972,40 @@ hipError_t set_lds(F* f, size_t bytes)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Rows of the (head, batch row) list that a forward workgroup takes: what spreads them evenly over the `resident` workgroups of the
+// device at once, or a few more where the runs then end with their heads (a divisor of B or a multiple), since every head that a run
+// touches is matrices to build.  Even shares stay unless the others end 4 % earlier by this: a compute unit's workgroups issue 0.07 T us
+// a row and three rows' time a head, a workgroup by itself waits 0.5 + 0.02 T us a row and four rows' time a head (fitted to 40 shapes,
+// N = 256 .. 2048), and neither hides the other: the root of the sum of their squares.  bf16, us, even shares and this: N = 256 B=16 H=768 19.5 (6 rows) and 16.1 (8),
+// B=4 H=1030 13.3 (3) and 9.3 (4); N = 512 B=16 H=768 22.3 (12) and 20.4 (16), B=8 H=300 11.9 (3) and 9.5 (4); N = 1024 B=7 H=193 11.6 (3)
+// and 10.0 (7); N = 2048 B=12 H=90 17.7 (5) and 14.9 (6).
+int64_t run_of_rows(int64_t B, int64_t rows, int64_t resident, int T)
+{
+    const int64_t even = (rows + resident - 1) / resident, units = compute_units();
+    const double a = 0.07 * T, b = 0.5 + 0.02 * T > a ? 0.5 + 0.02 * T : a;
+    const auto time = [&](int64_t per) {
+        const int64_t n = (rows + per - 1) / per, each = (n + units - 1) / units;
+        const bool ends = per % B == 0 || B % per == 0;
+        const double heads = ends ? (per > B ? per / B : 1) : 1. + (double)(per - 1) / B;
+        const int64_t most = ends ? (int64_t)heads : 1 + (per - 1 + B - 1) / B;
+        const double all = each * (per + 3 * heads) * a, one = (per + 4 * most) * b;
+        return all * all + one * one;
+    };
+    int64_t best = even;
+    double least = 0.92 * time(even);
+    const auto take = [&](int64_t per) {
+        if (per < even || time(per) >= least) return;
+        best = per;
+        least = time(per);
+    };
+    const int64_t turns = (even + B - 1) / B;
+    take(turns * B);
+    take((turns + 1) * B);
+    for (int64_t q = 2; q <= 64 && B / q >= even; ++q)
+        if (B % q == 0) take(B / q);
+    return best;
+}
+
 template <int LG, class IO>
 hipError_t fwd_go(const void* u, const float* shat, const float* Af, const float* Ai, void* y, int64_t B, int64_t H,
                   const Tables& tb, hipStream_t st)
@@ -983,7 +1017,7 @@ hipError_t fwd_go(const void* u, const float* shat, const float* Af, const float
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, lb_fwd_kernel<LG, IO>, 64 << (LG - 8), 0) != hipSuccess) nb = 1;
         resident = (nb > 0 ? nb : 1) * compute_units();
     }
-    const int64_t rows = B * H, per = (rows + resident - 1) / resident;      // even shares of the device
+    const int64_t rows = B * H, per = run_of_rows(B, rows, resident, 1 << (LG - 8));
     hipLaunchKernelGGL((lb_fwd_kernel<LG, IO>), dim3((unsigned)((rows + per - 1) / per)), dim3(64 << (LG - 8)), 0, st,
                        (const T*)u, (const float2*)shat, (const float2*)Af, (const float2*)Ai, (T*)y, (int)B, (int)H, per, tb.stw);
     return hipGetLastError();

@@ -183,6 +183,23 @@ def test_backward_of_few_rows_a_head(N, B):
     _check_blocks(g["dAi"][heads], rdAi, N, TOL[io], label + " dAi")
 
 
+# What a forward workgroup takes of the list of rows: parts of a head (64 rows in runs of 4), one head (7), two (3 rows each), and runs that
+# cross from head to head (9 rows of heads of 4, 3 of 13) or end with the list in the middle of one.
+@pytest.mark.parametrize("N,io,B,H", [(256, wl.F16, 64, 64), (1024, wl.BF16, 7, 193), (256, wl.BF16, 3, 3000), (1024, wl.F16, 4, 1030),
+                                      (256, wl.F16, 13, 330), (2048, wl.F16, 12, 90)])
+def test_forward_runs_of_rows(N, io, B, H):
+    u_s, u_v, _, _, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=6)
+    u, shat = to_dev(u_s, io), torch.empty(H, 2 * N, 2, device="cuda")
+    y = torch.full_like(u, float("nan"))
+    lc.longconv_lbfly_spectrum(torch.from_numpy(k).cuda(), torch.from_numpy(D).cuda(), shat)
+    lc.longconv_lbfly_fwd(u, shat, torch.from_numpy(Af32).cuda(), torch.from_numpy(Ai32).cuda(), y)
+    got = to_f64(y, io)
+    assert np.all(np.isfinite(got))
+    heads = sorted({0, 1, H - 2, H - 1, *np.random.default_rng(N + H).choice(H, size=8, replace=False).tolist()})
+    want = lbfly.lbfly_fwd(u_v[:, heads], lbfly.spectrum(k[heads], D[heads]), Af[heads], Ai[heads])
+    _compare({"y": got[:, heads]}, {"y": want}, TOL[io], f"lbfly forward runs N={N} B={B} H={H}")
+
+
 def test_optional_outputs_repeatability_and_error_codes():
     N, io, B, H = 512, wl.F16, 4, 3
     u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=2)
