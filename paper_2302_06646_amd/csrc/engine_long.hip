@@ -6,8 +6,8 @@
 //   phase 1 (tile t, wave t / 8):       samples -[F16 over d_a, real input]-> * w_256^(k_a d_b) -[F16 over d_b]-> LDS
 //   phase 2 (k_b, wave k_b NW / 16):    its TE tiles d_e: [F16 over d_c], [F_TE over d_e], * spectrum, and the mirror image -> LDS
 //   phase 3 (tile t):                   [F16^-1 over k_b] * conj(w_256^(k_a d_b)) -[F16^-1 over k_a, real part]-> samples
-// With two waves per SIMD these kernels run at about six cycles per instruction, whatever it is, so what counts is how many
-// there are.  All twiddles but one sit in the matrices: w_N^(k_a t) w_4N^t in the tile's own matrix over d_a (registers, eight
+// With two waves per SIMD these kernels run at about six cycles per instruction, whatever it is (the units could take one every 4.4, and
+// matrix instructions of one wave beside the other's; two waves do not fill the waits), so what counts is how many there are.  All twiddles but one sit in the matrices: w_N^(k_a t) w_4N^t in the tile's own matrix over d_a (registers, eight
 // tiles per wave), w_256^(k_b d_c) in the wave's matrices over d_c (registers), w_256TE^(d_e k_b) in the matrices over d_b and
 // w_16TE^(d_e k_c) in those over d_e (few, shared by all waves: LDS).  The step over d_e contracts between tiles: for one k_c of
 // every lane the TE tiles' numbers are a matrix operand as they lie, with K = (lane group, d_e) and a matrix that is block
@@ -277,9 +277,9 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
 // Bound by memory as much as by issue: B=8, H=256, N=16384 fp16 moves up to 510 MB in 111 us (4.6 TB/s; a large copy 5.1) for
 // 235 MB of rows and gradients, with vector instructions in half of the cycles and matrix instructions in a quarter.  What is read
 // beyond the rows is the spectrum for every row again (117 MB), u's second reading (67) and spilled registers: the sums alone take
-// a quarter of them, and 17 to 24 have no place.  With more of them in the loop the reloads wait behind the row in flight: 167 us,
-// 112 with the matrices of three tiles per wave and their factors in LDS, 107 with the rows' addresses kept scalar (as pairs, dk in
-// two walks and du by itself: 197).  N = 8192 takes four tiles per wave (LB) and spills nothing: with eight, B=64, H=128 289 us,
+// a quarter of them, and 20 to 22 have no place.  With more of them in the loop the reloads wait behind the row in flight: 167 us,
+// 112 with the matrices of three tiles per wave and their factors in LDS, 107 with the rows' addresses kept scalar, 104
+// with requests and stores spread over the tiles (as pairs, dk in two walks and du by itself: 197).  N = 8192 takes four tiles per wave (LB) and spills nothing: with eight, B=64, H=128 289 us,
 // with four 167 (as pairs 325).
 // -------------------------------------------------------------------------------------------------------------------
 template <class T>

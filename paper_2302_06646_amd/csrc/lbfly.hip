@@ -340,11 +340,12 @@ lb_fwd_kernel(const typename IO::T* __restrict__ u, const float2* __restrict__ s
 // the gradient at the product with the spectrum a second time, rather than wait for dy's.
 // The twiddle factors that were folded into a tile's matrices scale rows or columns of its 16 x 16 sums: applied once, at
 // the end, where the waves' sums meet in wave order.
-// Per 256 points and row 35 matrix and 195 vector instructions, and 9 KB written to LDS and 27 read.  One wave for both chains had 33 and 187, but needed 240 registers, and its two waves per SIMD left the chip waiting for LDS and for results; now four
-// fit, without spills in the row loop, since the last stage's matrices (the same for all tiles) are read from LDS.  A row of N = 1024
-// takes 3280 cycles of a CU (3700 before), of which 2280 are issue and 2060 LDS; 8900 cycles of a head are its constants, 5000 its sums.
-// bf16, B=16, H=768: N = 256 33.0 -> 29.4 us, 512 55.6 -> 47.7, 1024 99.2 -> 91.6 (a lane's registers for the next head's
-// constants, so that they come in during the sums: 66 spills and 96 us).
+// Per 256 points and row 35 matrix and 195 vector instructions, and 9 KB written to LDS and 27 read.  One wave for both chains had 33 and
+// 187, but needed 240 registers, and its two waves per SIMD left the chip waiting for LDS and for results; now four fit, without spills
+// in the row loop, since the last stage's matrices (the same for all tiles) are read from LDS.  Vector instructions are issued in 66 %
+// of the cycles (57 before), LDS is active in 44 (31).  N = 1024: a row takes 3280 cycles of a compute unit, a head's constants and
+// matrices 8900, its sums 4300.  bf16, B=16, H=768: N = 256 33.0 -> 29.4 us, 512 55.6 -> 47.7, 1024 99.2 -> 91.6.  Workgroups that stay
+// for the next head, with its constants asked for in front of the sums, spilled 66 registers: 96.
 // -------------------------------------------------------------------------------------------------------------------
 struct LbGrads {            // where the sums go: of share sp and head h at index sp * H + h
     float2 *shat, *qf, *qi;
@@ -1045,8 +1046,8 @@ hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float*
 
 }  // namespace
 
-// Shares of a head's rows: the number that ends first, ceil(512 / H) at most, where 8 / T workgroups of T waves run on each of
-// 256 compute units.  A share's matrices and sums take as long as about six rows (8.5 us at N = 1024, a row 1.6), five at N = 2048
+// Shares of a head's rows: the number that ends first, ceil(512 / H) at most, where 8 / T workgroups (two chains of T waves) run on each of
+// 256 compute units.  A share's matrices and sums take as long as about six rows (8.3 us at N = 1024, a row 1.45), five at N = 2048
 // (15 us, a row 3.2); more than one share is a second launch, as long as three rows or two.
 static int64_t most_shares(int64_t B, int64_t H) { return (512 + H - 1) / H < B ? (512 + H - 1) / H : B; }
 static int64_t turns(int64_t workgroups, int64_t N)
