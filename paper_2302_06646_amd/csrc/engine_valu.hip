@@ -43,11 +43,15 @@ constexpr int span_log2(int LG, int s)
     return l;
 }
 
-// LDS position of point p, with a slot of padding behind every 2^K: eight, or sixteen for single rows of 2048 and 4096 samples, whose
-// runs of sixteen neighbours it leaves whole (16 lanes are served at a time; B=32, H=1024, N=4096 step 1333 -> 1308 us)
+// LDS position of point p, with a slot of padding behind every 2^K.  16 lanes are served at a time, so sixteen leaves their runs of
+// neighbours whole, and eight spreads the lanes of a last stage of radix 8 or 4.  Cycles per access of the exchanges of a transform, summed
+// over them, for eight and sixteen: 2^8 points 12 and 12 (of 6), 2^9 5 and 6, 2^10 12 and 12, 2^11 10 and 8, 2^12 8 and 4, 2^13 and 2^14 9
+// and 8, 2^15 11 and 6.  Measured, fp32 us: backward N = 512 (2^10) B=16 H=256 18.8 and 20.3, N = 1024 (2^11) B=64 H=256 90.1 and 87.1,
+// N = 16384 (single rows of 2^14) B=4 H=64 49.0 and 46.7, N = 65536 (2^14) B=2 H=32 129.3 and 125.8; step N = 4096 (rows of 2^12) B=32
+// H=1024 1333 and 1308.
 template <int K = 3>
 __host__ __device__ constexpr int phys(int p) { return p + (p >> K); }
-constexpr int row_pad(int LG) { return LG <= 12 ? 4 : 3; }
+constexpr int fft_pad(int LG) { return LG >= 11 ? 4 : 3; }
 // whether the backward kernel parks the transform of u in memory (see fbwd_kernel)
 constexpr bool valu_parks(int LG) { return LG >= 14; }
 constexpr bool row_parks(int LG) { return points_log2(LG) == 4; }        // (frow_bwd_kernel)
@@ -296,7 +300,7 @@ using RowTw = typename std::conditional<FIRST, typename std::conditional<LG == 1
 // the twiddles of stage 0
 template <int LG, bool ALL = false, bool TWIST = false>
 struct Fft {
-    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG), PAD = TWIST ? row_pad(LG) : 3;
+    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG), PAD = fft_pad(LG);
     static constexpr bool FINE = TWIST && row_fine(LG);
 
     template <int s>
