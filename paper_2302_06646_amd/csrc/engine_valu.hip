@@ -538,6 +538,11 @@ fkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* 
 // block-size study).  One workgroup per head; the frequencies go through LDS once more, so that memory sees whole
 // lines.  Bound by memory latency and launch (12 MB at H = 768, N = 1024): a radix-2 transform with its L points in LDS
 // throughout took 22.6 and 20.8 us there, this one 8.0 and 7.4, at 2-10 % less rounding error.
+// The LDS place of frequency f XORs its low four bits with those from 4 and from 7 on: 16 neighbouring threads meet 16 banks
+// both with neighbouring pairs of frequencies and with those of their last stage (2^9 points: two cycles there; as padded as
+// the transform's own exchanges: two and two to eight).  H = 1030, N = 1024 9.35 -> 8.65 us and 7.2 -> 6.5, H = 768 7.6 -> 7.3 and
+// 5.95 -> 5.4; N = 512 4.9 either way and 4.15 -> 4.25, N = 2048 the same.
+__device__ __forceinline__ int natural_place(uint32_t f) { return (int)(f ^ (((f >> 4) ^ (f >> 7)) & 15u)); }
 template <int LG>
 __global__ void __launch_bounds__(Fft<LG>::T)
 spectrum_natural_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* __restrict__ shat,
@@ -555,13 +560,13 @@ spectrum_natural_kernel(const float* __restrict__ k, const float* __restrict__ D
     F::template fwd<true>(x, sm, stw, tid);
     __syncthreads();                    // the last stage's points have been read
 #pragma unroll
-    for (int j = 0; j < P; ++j) sm[phys(F::freq_of(tid, j))] = x[j];
+    for (int j = 0; j < P; ++j) sm[natural_place(F::freq_of(tid, j))] = x[j];
     __syncthreads();
     float4* out = reinterpret_cast<float4*>(shat + ((size_t)h << LG));
 #pragma unroll
     for (int i = 0; i < P / 2; ++i) {
         const int f = 2 * (tid + i * T);
-        const float2 a = sm[phys(f)], b = sm[phys(f + 1)];
+        const float2 a = sm[natural_place(f)], b = sm[natural_place(f + 1)];
         out[tid + i * T] = make_float4(a.x + dh, a.y, b.x + dh, b.y);
     }
 }
@@ -580,13 +585,13 @@ spectrum_natural_bwd_kernel(const float2* __restrict__ dshat, float* __restrict_
     for (int i = 0; i < P / 2; ++i) {
         const int f = 2 * (tid + i * T);
         const float4 v = in[tid + i * T];
-        sm[phys(f)] = make_float2(v.x, v.y);
-        sm[phys(f + 1)] = make_float2(v.z, v.w);
+        sm[natural_place(f)] = make_float2(v.x, v.y);
+        sm[natural_place(f + 1)] = make_float2(v.z, v.w);
     }
     __syncthreads();
     float2 x[P];
 #pragma unroll
-    for (int j = 0; j < P; ++j) x[j] = sm[phys(F::freq_of(tid, j))];
+    for (int j = 0; j < P; ++j) x[j] = sm[natural_place(F::freq_of(tid, j))];
     __syncthreads();
     F::template inv<true>(x, sm, stw, tid);
     if (dk) {
