@@ -49,6 +49,22 @@ def test_runs_of_rows_across_heads(B, H, N, io):
              {"y": oracle.longconv_fwd(inp.u[:, hs], k64, D64), "du": rdu, "dk": rdk, "dD": rdD}, TOL[io], f"runs N{N}", DD_TOL)
 
 
+# A workgroup asks for the next row while it works on one: runs of two and three rows and of one and two, where nothing follows the last.
+@pytest.mark.parametrize("B,H,N,io", [(3, 171, 32768, wl.F16), (1, 257, 32768, wl.BF16), (1, 257, 16384, wl.BF16)])
+def test_ends_of_runs_of_one_to_three_rows(B, H, N, io):
+    inp = wl.generate(_w("3", N=N, dtype=io), B=B, H=H)
+    g = GpuRun(inp)
+    hs = sample_heads(H, B, seed=N)
+    k64, D64 = inp.k.astype(np.float64)[hs], inp.D.astype(np.float64)[hs]
+    y = g.fwd()
+    du, dk, dD = g.bwd()
+    for x in (y, du, dk, dD):
+        assert np.all(np.isfinite(x))
+    rdu, rdk, rdD = oracle.longconv_bwd(inp.dy[:, hs], inp.u[:, hs], k64, D64)
+    _compare({"y": y[:, hs], "du": du[:, hs], "dk": dk[hs], "dD": dD[hs]},
+             {"y": oracle.longconv_fwd(inp.u[:, hs], k64, D64), "du": rdu, "dk": rdk, "dD": rdD}, TOL[io], f"runs N{N}", DD_TOL)
+
+
 @pytest.mark.parametrize("N,io", [(8192, wl.F16), (16384, wl.BF16)])
 @pytest.mark.parametrize("fuse", [1, 0])
 def test_outputs_left_out(N, io, fuse):
