@@ -213,3 +213,47 @@ def test_rows_of_one_head_apart_at_32768(io):
     if io == wl.F16:
         us, ds = np.array([[1.0], [8.0], [0.25]]), np.array([[0.5], [4.0], [1.0]])
     check_full(scaled_inputs(32768, 3, 2, us, ds, seed=9, dtype=io), label="rows of one head apart", dd_tol=1e-4)
+
+
+# One sample outside the band in a row that otherwise lies inside it: the waves that hold the row decide by themselves whether it
+# has to be scaled, each from its own words, and a single word has to be enough.  Of either sign (bf16 patterns from 2^121 on are NaN
+# when read as fp16, where the maximum of |x| is taken), in the first or the last wave's words, in u alone or in dy alone: head
+# 4 place + 2 sign + tensor, rows inside the band around it.
+# Outputs are cut from a linear convolution of 2N samples, and the rounding of a transform is relative to all of it: of a sample six
+# before a row's end six samples are kept.  Rows (dk: heads) are held to the usual bound, relative to what they were cut from.
+@pytest.mark.parametrize("power", [4, 100, 122])
+@pytest.mark.parametrize("N,gate", [(2048, False), (4096, False), (1024, True), (2048, True)])
+def test_one_sample_out_of_band(N, gate, power):
+    from gpu_harness import GpuRun, TOL
+    import oracle
+    from oracle import gated
+    from test_gated_gpu import _run
+    B, H, io = 3, 8, wl.BF16
+    inp = wl.generate(wl.Workload(2, B, H, N, io, "squash_pool"))
+    u, dy = inp.u.copy(), inp.dy.copy()
+    for h in range(H):
+        x, at = (u, dy)[h & 1], (5, N - 6)[h >> 2]
+        x[h % B, h, at] = (1.0, -1.0)[(h >> 1) & 1] * 2.0 ** power
+    (u_s, u_v), (dy_s, dy_v) = wl.quantize(u.astype(np.float32), io), wl.quantize(dy.astype(np.float32), io)
+    inp = dataclasses.replace(inp, u_store=u_s, dy_store=dy_s, u=u_v, dy=dy_v)
+    k64, D64 = inp.k.astype(np.float64), inp.D.astype(np.float64)
+    norm = lambda x: np.linalg.norm(x, axis=-1)
+    f = lambda x: np.fft.fft(x, 2 * N)
+    kd = k64.copy()
+    kd[:, 0] += D64
+    g_v = np.ones((B, H, N))
+    if gate:
+        g_s, g_v = wl.quantize(np.broadcast_to(np.where(np.arange(N) % 3 == 1, -1.0, 1.0), (B, H, N)).astype(np.float32), io)
+        got = dict(zip(("y", "du", "dk", "dD", "dg"), _run(inp, g_s)))
+    else:
+        g = GpuRun(inp)
+        got = dict(zip(("y", "du", "dk", "dD"), (g.fwd(), *g.bwd())))
+    want = dict(zip(("du", "dk", "dD", "dg"), gated.gated_bwd(dy_v, g_v, u_v, k64, D64)), y=gated.gated_fwd(u_v, k64, D64, g_v))
+    whole = {"y": norm(np.fft.ifft(f(u_v) * f(kd))), "du": norm(np.fft.ifft(f(dy_v * g_v) * f(kd).conj())),
+             "dk": norm(np.fft.ifft((f(dy_v * g_v) * f(u_v).conj()).sum(axis=0)))}
+    whole["dg"] = np.maximum(norm(want["dg"]), norm(dy_v) * whole["y"] / (2 * N) ** 0.5)
+    errs = {n: float(np.max(norm(got[n] - want[n]) / whole[n])) for n in got if n != "dD"}
+    errs["dD"] = float(np.max(np.abs(got["dD"] - want["dD"]) / (norm(norm(u_v).T) * norm(norm(dy_v).T))))
+    print(f"[parity] one sample of 2^{power}, N={N} gate={gate}: " + " ".join(f"{n}={e:.2e}" for n, e in errs.items()), flush=True)
+    for n, e in errs.items():
+        assert np.isfinite(e) and e <= (1e-6 if n == "dD" else TOL[io]), f"{n}: {e:.3e}"
