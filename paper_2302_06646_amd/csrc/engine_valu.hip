@@ -540,9 +540,14 @@ fkspec_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* 
 // throughout took 22.6 and 20.8 us there, this one 8.0 and 7.4, at 2-10 % less rounding error.
 // The LDS place of frequency f XORs its low four bits with those from 4 and from 7 on: 16 neighbouring threads meet 16 banks
 // both with neighbouring pairs of frequencies and with those of their last stage (2^9 points: two cycles there; as padded as
-// the transform's own exchanges: two and two to eight).  H = 1030, N = 1024 9.35 -> 8.65 us and 7.2 -> 6.5, H = 768 7.6 -> 7.3 and
-// 5.95 -> 5.4; N = 512 4.9 either way and 4.15 -> 4.25, N = 2048 the same.
-__device__ __forceinline__ int natural_place(uint32_t f) { return (int)(f ^ (((f >> 4) ^ (f >> 7)) & 15u)); }
+// the transform's own exchanges: two and two to eight).  H = 1030, N = 1024 9.2 -> 8.2 us and 6.9 -> 6.0, H = 768 7.0 -> 6.6 and
+// 5.3 -> 4.85; N = 2048, H = 768 10.3 -> 9.5 and 7.45 -> 7.35.  Up to 2^10 points the XORs cost more than the conflicts, and the places
+// are padded: padded and XORed, H = 300, N = 256 2.50 and 2.60 us, 2.56 and 2.63, N = 512 3.23 and 3.39, 3.05 and 3.13.
+template <int LG>
+__device__ __forceinline__ int natural_place(uint32_t f)
+{
+    return LG <= 10 ? phys<fft_pad(LG)>((int)f) : (int)(f ^ (((f >> 4) ^ (f >> 7)) & 15u));
+}
 template <int LG>
 __global__ void __launch_bounds__(Fft<LG>::T)
 spectrum_natural_kernel(const float* __restrict__ k, const float* __restrict__ D, float2* __restrict__ shat,
@@ -560,13 +565,13 @@ spectrum_natural_kernel(const float* __restrict__ k, const float* __restrict__ D
     F::template fwd<true>(x, sm, stw, tid);
     __syncthreads();                    // the last stage's points have been read
 #pragma unroll
-    for (int j = 0; j < P; ++j) sm[natural_place(F::freq_of(tid, j))] = x[j];
+    for (int j = 0; j < P; ++j) sm[natural_place<LG>(F::freq_of(tid, j))] = x[j];
     __syncthreads();
     float4* out = reinterpret_cast<float4*>(shat + ((size_t)h << LG));
 #pragma unroll
     for (int i = 0; i < P / 2; ++i) {
         const int f = 2 * (tid + i * T);
-        const float2 a = sm[natural_place(f)], b = sm[natural_place(f + 1)];
+        const float2 a = sm[natural_place<LG>(f)], b = sm[natural_place<LG>(f + 1)];
         out[tid + i * T] = make_float4(a.x + dh, a.y, b.x + dh, b.y);
     }
 }
@@ -585,13 +590,13 @@ spectrum_natural_bwd_kernel(const float2* __restrict__ dshat, float* __restrict_
     for (int i = 0; i < P / 2; ++i) {
         const int f = 2 * (tid + i * T);
         const float4 v = in[tid + i * T];
-        sm[natural_place(f)] = make_float2(v.x, v.y);
-        sm[natural_place(f + 1)] = make_float2(v.z, v.w);
+        sm[natural_place<LG>(f)] = make_float2(v.x, v.y);
+        sm[natural_place<LG>(f + 1)] = make_float2(v.z, v.w);
     }
     __syncthreads();
     float2 x[P];
 #pragma unroll
-    for (int j = 0; j < P; ++j) x[j] = sm[natural_place(F::freq_of(tid, j))];
+    for (int j = 0; j < P; ++j) x[j] = sm[natural_place<LG>(F::freq_of(tid, j))];
     __syncthreads();
     F::template inv<true>(x, sm, stw, tid);
     if (dk) {
