@@ -298,9 +298,9 @@ using RowTw = typename std::conditional<FIRST, typename std::conditional<LG == 1
 // TWIST: N points of a single real row (see frow_conv_kernel), in and out as the real parts of x; x[n] w^-n with
 // w = exp(i pi / 2N), where n = q + d T of a thread's points: the part of d is a constant of the butterfly, that of q rides on
 // the twiddles of stage 0
-template <int LG, bool ALL = false, bool TWIST = false>
+template <int LG, bool ALL = false, bool TWIST = false, int PAD = fft_pad(LG)>
 struct Fft {
-    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG), PAD = fft_pad(LG);
+    static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG);
     static constexpr bool FINE = TWIST && row_fine(LG);
 
     template <int s>
@@ -889,12 +889,16 @@ frow_kspec_kernel(const float* __restrict__ k, const float* __restrict__ D, floa
             make_float4((x[2 * i].x + dh) * scale, x[2 * i].y * scale, (x[2 * i + 1].x + dh) * scale, x[2 * i + 1].y * scale);
 }
 
-template <int LG>
+// Paddings of the convolution at N = 8192, two workgroups on a compute unit: behind every eight slots up to eight rows a unit, behind
+// every sixteen beyond (us, eight and sixteen: 512 rows 17.2 and 18.7, 600 23.4 and 25.1, 1024 30.6 and 31.8, 2048 57.2 and 57.2, 3200 88.8
+// and 87.3, 4096 111.6 and 109.6; the backward kernel, and one workgroup on a unit: sixteen or no difference).
+constexpr int conv_pad(int LG, int64_t rows) { return LG == 13 && rows <= 2048 ? 3 : fft_pad(LG); }
+template <int LG, int PAD>
 __global__ void __launch_bounds__(RowFft<LG>::T) __attribute__((amdgpu_waves_per_eu(4)))
 frow_conv_kernel(const float* __restrict__ in, const float2* __restrict__ kspec, float* __restrict__ out, int conj, int B, int H,
                  const float2* __restrict__ stw)
 {
-    using F = RowFft<LG>;
+    using F = Fft<LG, true, true, PAD>;
     extern __shared__ float2 sm[];
     const int item = item_of(B * H), tid = threadIdx.x;
     if (item >= B * H) return;
@@ -1074,14 +1078,20 @@ hipError_t rows_kspec_go(const float* k, const float* D, float2* kspec, int64_t 
 }
 // workgroups for a list of items (see item_of)
 dim3 item_grid(int64_t items) { return dim3((unsigned)((items + 7) / 8 * 8)); }
+template <int LG, int PAD>
+hipError_t rows_conv_launch(const float* in, const float2* kspec, float* out, bool conj, const Problem& pr, const Tables& tb, hipStream_t st)
+{
+    const hipError_t e = set_lds(frow_conv_kernel<LG, PAD>, lds_bytes(LG));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((frow_conv_kernel<LG, PAD>), item_grid(pr.B * pr.H), dim3(RowFft<LG>::T), lds_bytes(LG), st, in, kspec, out,
+                       conj ? 1 : 0, (int)pr.B, (int)pr.H, tb.stw);
+    return hipGetLastError();
+}
 template <int LG>
 hipError_t rows_conv_go(const float* in, const float2* kspec, float* out, bool conj, const Problem& pr, const Tables& tb, hipStream_t st)
 {
-    const hipError_t e = set_lds(frow_conv_kernel<LG>, lds_bytes(LG));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(frow_conv_kernel<LG>, item_grid(pr.B * pr.H), dim3(RowFft<LG>::T), lds_bytes(LG), st, in, kspec, out, conj ? 1 : 0,
-                       (int)pr.B, (int)pr.H, tb.stw);
-    return hipGetLastError();
+    return conv_pad(LG, pr.B * pr.H) == 3 ? rows_conv_launch<LG, conv_pad(LG, 0)>(in, kspec, out, conj, pr, tb, st)
+                                          : rows_conv_launch<LG, fft_pad(LG)>(in, kspec, out, conj, pr, tb, st);
 }
 template <int LG>
 hipError_t rows_bwd_go(const float* dy, const float* u, const float2* kspec, float* du, float* dk, float* dD, void* acc, int nsplit,

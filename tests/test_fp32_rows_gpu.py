@@ -101,3 +101,9 @@ def test_sums_of_many_shares(N, B, H):
 def test_shares_of_short_rows(B, H):
     assert lc.longconv_workspace_bytes(B, H, 2048, lc.F32, 1) >= lc.longconv_workspace_bytes(B - 1, H, 2048, lc.F32, 1)
     check_sampled(_inputs(2048, B, H), sample_heads(H, B, seed=B + H))
+
+
+# N = 8192: the last number of rows whose convolution pads its exchanges in one way, and the first of the other
+@pytest.mark.parametrize("B,H", [(2, 1024), (3, 683)])
+def test_many_rows_of_8192(B, H):
+    check_sampled(_inputs(8192, B, H), sample_heads(H, B, seed=H))
