@@ -49,7 +49,7 @@ constexpr int span_log2(int LG, int s)
 // and 8, 2^15 11 and 6.  Measured, fp32 us: backward N = 512 (2^10) B=16 H=256 18.8 and 20.3, N = 1024 (2^11) B=64 H=256 90.1 and 87.1,
 // N = 16384 (single rows of 2^14) B=4 H=64 49.0 and 46.7, N = 65536 (2^14) B=2 H=32 129.3 and 125.8; step N = 4096 (rows of 2^12) B=32
 // H=1024 1333 and 1308.
-template <int K = 3>
+template <int K>
 __host__ __device__ constexpr int phys(int p) { return p + (p >> K); }
 constexpr int fft_pad(int LG) { return LG >= 11 ? 4 : 3; }
 // whether the backward kernel parks the transform of u in memory (see fbwd_kernel)
@@ -57,7 +57,6 @@ constexpr bool valu_parks(int LG) { return LG >= 14; }
 constexpr bool row_parks(int LG) { return points_log2(LG) == 4; }        // (frow_bwd_kernel)
 // which single rows take the butterflies' constants (N = 2048: and the twist's, on the way in) in two parts; see frow_conv_kernel
 constexpr bool row_fine(int LG) { return LG <= 12; }
-constexpr size_t lds_bytes(int LG) { return sizeof(float2) * ((size_t(1) << LG) * 9 / 8); }
 
 // ---- butterflies in registers -------------------------------------------------------------------------------------
 // v * exp(-+ 2 pi i m / 32): m a compile-time constant after unrolling.  FINE (even m only, the butterflies' own): constants in two
@@ -301,6 +300,7 @@ using RowTw = typename std::conditional<FIRST, typename std::conditional<LG == 1
 template <int LG, bool ALL = false, bool TWIST = false, int PAD = fft_pad(LG)>
 struct Fft {
     static constexpr int N = 1 << LG, P = 1 << points_log2(LG), T = N / P, S = stages(LG);
+    static constexpr size_t LDS = sizeof(float2) * phys<PAD>(N);
     static constexpr bool FINE = TWIST && row_fine(LG);
 
     template <int s>
@@ -1048,12 +1048,12 @@ hipError_t kspec_go(const float* k, const float* D, float2* kspec, int64_t H, in
     const dim3 grid(1u << log2R, (unsigned)H);
     hipError_t e;
     if (!consumer) {
-        if ((e = set_lds(fkspec_kernel<LG, true>, lds_bytes(LG))) != hipSuccess) return e;
-        hipLaunchKernelGGL((fkspec_kernel<LG, true>), grid, dim3(Fft<LG>::T), lds_bytes(LG), st, k, D, kspec, N, log2R,
+        if ((e = set_lds(fkspec_kernel<LG, true>, Fft<LG>::LDS)) != hipSuccess) return e;
+        hipLaunchKernelGGL((fkspec_kernel<LG, true>), grid, dim3(Fft<LG>::T), Fft<LG>::LDS, st, k, D, kspec, N, log2R,
                            SpecOrder{}, scale, tb.tw, tb.ftw);
     } else {
-        if ((e = set_lds(fkspec_kernel<LG, false>, lds_bytes(LG))) != hipSuccess) return e;
-        hipLaunchKernelGGL((fkspec_kernel<LG, false>), grid, dim3(Fft<LG>::T), lds_bytes(LG), st, k, D, kspec, N, log2R,
+        if ((e = set_lds(fkspec_kernel<LG, false>, Fft<LG>::LDS)) != hipSuccess) return e;
+        hipLaunchKernelGGL((fkspec_kernel<LG, false>), grid, dim3(Fft<LG>::T), Fft<LG>::LDS, st, k, D, kspec, N, log2R,
                            *consumer, scale, tb.tw, tb.ftw);
     }
     return hipGetLastError();
@@ -1071,9 +1071,9 @@ hipError_t kspec_go(const float* k, const float* D, float2* kspec, int64_t H, in
 template <int LG>
 hipError_t rows_kspec_go(const float* k, const float* D, float2* kspec, int64_t H, float scale, const Tables& tb, hipStream_t st)
 {
-    const hipError_t e = set_lds(frow_kspec_kernel<LG>, lds_bytes(LG));
+    const hipError_t e = set_lds(frow_kspec_kernel<LG>, RowFft<LG>::LDS);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(frow_kspec_kernel<LG>, dim3((unsigned)H), dim3(RowFft<LG>::T), lds_bytes(LG), st, k, D, kspec, scale, tb.stw);
+    hipLaunchKernelGGL(frow_kspec_kernel<LG>, dim3((unsigned)H), dim3(RowFft<LG>::T), RowFft<LG>::LDS, st, k, D, kspec, scale, tb.stw);
     return hipGetLastError();
 }
 // workgroups for a list of items (see item_of)
@@ -1081,9 +1081,10 @@ dim3 item_grid(int64_t items) { return dim3((unsigned)((items + 7) / 8 * 8)); }
 template <int LG, int PAD>
 hipError_t rows_conv_launch(const float* in, const float2* kspec, float* out, bool conj, const Problem& pr, const Tables& tb, hipStream_t st)
 {
-    const hipError_t e = set_lds(frow_conv_kernel<LG, PAD>, lds_bytes(LG));
+    constexpr size_t lds = Fft<LG, true, true, PAD>::LDS;
+    const hipError_t e = set_lds(frow_conv_kernel<LG, PAD>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((frow_conv_kernel<LG, PAD>), item_grid(pr.B * pr.H), dim3(RowFft<LG>::T), lds_bytes(LG), st, in, kspec, out,
+    hipLaunchKernelGGL((frow_conv_kernel<LG, PAD>), item_grid(pr.B * pr.H), dim3(RowFft<LG>::T), lds, st, in, kspec, out,
                        conj ? 1 : 0, (int)pr.B, (int)pr.H, tb.stw);
     return hipGetLastError();
 }
@@ -1097,9 +1098,9 @@ template <int LG>
 hipError_t rows_bwd_go(const float* dy, const float* u, const float2* kspec, float* du, float* dk, float* dD, void* acc, int nsplit,
                        const Problem& pr, float scale, const Tables& tb, hipStream_t st)
 {
-    const hipError_t e = set_lds(frow_bwd_kernel<LG>, lds_bytes(LG));
+    const hipError_t e = set_lds(frow_bwd_kernel<LG>, RowFft<LG>::LDS);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(frow_bwd_kernel<LG>, item_grid(pr.H * nsplit), dim3(RowFft<LG>::T), lds_bytes(LG), st, dy, u, kspec, du, dk, dD,
+    hipLaunchKernelGGL(frow_bwd_kernel<LG>, item_grid(pr.H * nsplit), dim3(RowFft<LG>::T), RowFft<LG>::LDS, st, dy, u, kspec, du, dk, dD,
                        (float4*)acc, (int)pr.B, (int)pr.H, nsplit, scale, tb.stw);
     return hipGetLastError();
 }
@@ -1107,17 +1108,17 @@ hipError_t rows_bwd_go(const float* dy, const float* u, const float2* kspec, flo
 template <int LG>
 hipError_t natural_go(const float* k, const float* D, float2* shat, int64_t H, const Tables& tb, hipStream_t st)
 {
-    const hipError_t e = set_lds(spectrum_natural_kernel<LG>, lds_bytes(LG));
+    const hipError_t e = set_lds(spectrum_natural_kernel<LG>, Fft<LG>::LDS);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(spectrum_natural_kernel<LG>, dim3((unsigned)H), dim3(Fft<LG>::T), lds_bytes(LG), st, k, D, shat, tb.stw);
+    hipLaunchKernelGGL(spectrum_natural_kernel<LG>, dim3((unsigned)H), dim3(Fft<LG>::T), Fft<LG>::LDS, st, k, D, shat, tb.stw);
     return hipGetLastError();
 }
 template <int LG>
 hipError_t natural_bwd_go(const float2* dshat, float* dk, float* dD, int64_t H, const Tables& tb, hipStream_t st)
 {
-    const hipError_t e = set_lds(spectrum_natural_bwd_kernel<LG>, lds_bytes(LG));
+    const hipError_t e = set_lds(spectrum_natural_bwd_kernel<LG>, Fft<LG>::LDS);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(spectrum_natural_bwd_kernel<LG>, dim3((unsigned)H), dim3(Fft<LG>::T), lds_bytes(LG), st, dshat, dk, dD,
+    hipLaunchKernelGGL(spectrum_natural_bwd_kernel<LG>, dim3((unsigned)H), dim3(Fft<LG>::T), Fft<LG>::LDS, st, dshat, dk, dD,
                        tb.stw);
     return hipGetLastError();
 }
@@ -1127,10 +1128,10 @@ hipError_t conv_go(const void* in, const float2* kspec, void* out, float2* ws, b
                    const Tables& tb, hipStream_t st)
 {
     using T = typename IO::T;
-    const hipError_t e = set_lds(fconv_kernel<LG, IO, CHUNK>, lds_bytes(LG));
+    const hipError_t e = set_lds(fconv_kernel<LG, IO, CHUNK>, Fft<LG>::LDS);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fconv_kernel<LG, IO, CHUNK>), dim3(pr.npairs, (unsigned)pr.H, 1u << log2R), dim3(Fft<LG>::T),
-                       lds_bytes(LG), st, (const T*)in, kspec, (T*)out, ws, conj ? 1 : 0, pr.B, pr.H, pr.N, log2R, tb.tw,
+                       Fft<LG>::LDS, st, (const T*)in, kspec, (T*)out, ws, conj ? 1 : 0, pr.B, pr.H, pr.N, log2R, tb.tw,
                        tb.ftw);
     return hipGetLastError();
 }
@@ -1154,10 +1155,10 @@ hipError_t bwd_go(const void* dy, const void* u, const float2* kspec, void* du, 
                   float* dD, void* zbuf, int nsplit, const Problem& pr, const Plan& pl, const Tables& tb, hipStream_t st)
 {
     using T = typename IO::T;
-    const hipError_t e = set_lds(fbwd_kernel<LG, IO, CHUNK>, lds_bytes(LG));
+    const hipError_t e = set_lds(fbwd_kernel<LG, IO, CHUNK>, Fft<LG>::LDS);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fbwd_kernel<LG, IO, CHUNK>), dim3(nsplit, (unsigned)pr.H, 1u << pl.log2R), dim3(Fft<LG>::T),
-                       lds_bytes(LG), st, (const T*)dy, (const T*)u, kspec, (T*)du, ws_du, dk, ws_A, dD, (float4*)zbuf, pr.B, pr.H, pr.N,
+                       Fft<LG>::LDS, st, (const T*)dy, (const T*)u, kspec, (T*)du, ws_du, dk, ws_A, dD, (float4*)zbuf, pr.B, pr.H, pr.N,
                        pr.npairs, pl.log2R, pl.dkscale, tb.tw, tb.ftw);
     return hipGetLastError();
 }
