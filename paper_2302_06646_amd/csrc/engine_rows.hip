@@ -1360,7 +1360,9 @@ rbwd_kernel(const BwdArgs<typename IO::T> q)
 // bf16: B=1, H=768 16.5 -> 8.1; B=5, H=64 12.0 -> 9.7; B=16, H=256 20.3 -> 14.4; B=16, H=768 37.4 -> 30.2; B=64, H=1024
 // 137 -> 110.  (Gated N = 1024 spills 50 registers and more and is 1.5 times as slow as the pipeline.)  With the factors' words kept
 // once (keep_words) N = 1024 spills none, where it had 6 to 14, B=1, H=768 7.9 -> 6.8, B=16, H=768 31.1 -> 29.6, and N = 512 has
-// three waves per SIMD in place of two: B=64, H=1024 60.2 -> 54.7.
+// three waves per SIMD in place of two: B=64, H=1024 60.2 -> 54.7.  With the gate N = 256 and 512 have registers enough either way; fp16
+// at N = 256 keeps the exchanged halves, too (words alone and with them: B=32, H=1024 23.2 and 21.0 us, B=64, H=512 19.4 and 18.5; bf16 21.3 and 22.9,
+// out of band 22.4 and 22.0; N = 512, B=16, H=256 8.9 and 9.2, B=32, H=300 19.4 and 19.1).
 template <int LG, class IO, bool DU, bool GATE, int NWV>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 rbwd1_kernel(const BwdArgs<typename IO::T> q)
@@ -1433,7 +1435,7 @@ rbwd1_kernel(const BwdArgs<typename IO::T> q)
     auto iter = [&](auto mode, int p) {
         using M = decltype(mode);
         h4 od[NP][2], ou[NP][2];
-        keep_words(K, kk);
+        if constexpr (!(GATE && LG == 8 && !BF)) keep_words(K, kk);
         f4 wr[2], wi[2], yr[2], yi[2], v[2];
         H8U m[2], n[2];
         uint32_t wy[NP][4], o[NP][4], og[NP][4];
