@@ -1655,6 +1655,10 @@ hipError_t rconv_run(const void* in, const float2* kspec, void* out, const Probl
         const int bpi = (int)((pr.B + C::RPI - 1) / C::RPI), items = bpi * (int)pr.H;
         e = resident(rconv1_kernel<LG, IO, CONJ, GATE>, 256, 0, cap);
         if (e != hipSuccess) return e;
+        // With the gate rows of 256 samples in bf16 would be held by seven workgroups of a compute unit; five, in longer runs, are
+        // faster (us, seven and five: B=40, H=1024 14.1 and 12.6, B=64, H=512 11.1 and 10.4, B=24, H=512 5.9 and 5.45, B=16, H=768
+        // 5.8 and 5.5; B=48, H=700 11.1 and 11.8, B=64, H=768 15.85 and 16.2).
+        if (LG == 8 && GATE && IsBf<IO>::v) cap = cap < 5 * compute_units() ? cap : 5 * compute_units();
         const int nb = even_grid((items + 3) / 4, cap);
         hipLaunchKernelGGL((rconv1_kernel<LG, IO, CONJ, GATE>), dim3(nb), dim3(256), 0, st, (const T*)in, kspec, (T*)out,
                            (const T*)pr.gate, (int)pr.B, (int)pr.H, bpi, items, pr.pad, tab);

@@ -179,3 +179,16 @@ def test_shares_of_dD(N, io, B, H):
     # stay below eps / 2 times the chain's length times the sum of magnitudes, and are far below it
     chain = 8 * (B * N // 8 // 256 // max(1, min(256, B * N // 8192)) + 2) + 16
     assert torch.all((outs[0].double() - want).abs() <= 6e-8 * chain * size)
+
+
+# N = 256: as many pairs of rows as the forward launch takes waves at once (bf16, a device of 256 compute units: 5 workgroups of 4 waves
+# on each), and one more, with a last row that has no partner
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("B,H", [(8, 1280), (3, 2561)])
+def test_gated_rows_of_256(B, H, io):
+    inp, g_s, g_v = _inputs(256, io, B, H, seed=11)
+    y = _run(inp, g_s)[0]
+    assert np.all(np.isfinite(y))
+    hs = sorted({0, 1, H // 2, H - 2, H - 1, *np.random.default_rng(H).choice(H, size=24, replace=False).tolist()})
+    want = gated.gated_fwd(inp.u[:, hs], inp.k[hs].astype(np.float64), inp.D[hs].astype(np.float64), g_v[:, hs])
+    _compare({"y": y[:, hs]}, {"y": want}, TOL[io], f"gated rows of 256, B={B} H={H} io={wl.DTYPE_NAMES[io]}")
