@@ -126,14 +126,17 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
     int h = i0 / B, b = i0 - h * B;                  // row of phase 1
     int ho = h, bo = b;                              // row that is stored
     int hl = h, bl = b;                              // row that is asked for
-    // (With the gate memory is reached through descriptors: a lane's 64-bit addresses cost 14 to 26 spilled registers at N = 8192.
-    // Without it plain addresses are as fast, and 3 % faster where a workgroup has one row.)
+    // With the gate memory is reached through descriptors: a lane's 64-bit addresses cost 14 to 26 spilled registers at N = 8192 (with
+    // descriptors 1 and 4; B=16, H=256 bf16 61.8 and 58.8 us).  Without it plain addresses are as fast, and 3 % faster where a workgroup
+    // has one row.  At N = 16384 nothing is spilled either way (fp16 plain and descriptors: B=7, H=193 43.3 and 42.8, B=16, H=256 109.7 and
+    // 110.9; bf16 45.5 and 46.0, 118.5 and 119.7, B=2, H=128 11.7 and 12.0).
+    constexpr bool DESC = GATE && !(LG == 14 && BF);
     u4w pf[PC];
     const auto ask = [&]() {
         const typename IO::T* p = in + row_off(bl, hl, H, L::N);
 #pragma unroll
         for (int i = 0; i < PC; ++i)
-            pf[i] = GATE ? row_load(row_rsrc(p, L::N * 2), 16 * tid, i * 16 * L::NT) : reinterpret_cast<const u4w*>(p)[tid + i * L::NT];
+            pf[i] = DESC ? row_load(row_rsrc(p, L::N * 2), 16 * tid, i * 16 * L::NT) : reinterpret_cast<const u4w*>(p)[tid + i * L::NT];
         if (++bl == B) { bl = 0; ++hl; }
     };
     ask();
@@ -153,7 +156,7 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
 #pragma unroll
             for (int ke = 0; ke < TE; ++ke) {
                 const int u = ((wave * L::KB + j) * TE + ke) * 64;
-                ks[j][ke].w = GATE ? __builtin_bit_cast(uint4, row_load(row_rsrc(s, L::N * 4), 16 * lane, 16 * u)) : s[u + lane];
+                ks[j][ke].w = DESC ? __builtin_bit_cast(uint4, row_load(row_rsrc(s, L::N * 4), 16 * lane, 16 * u)) : s[u + lane];
             }
         es0 = spec_exp_of(kspec, H, 2 * (int64_t)L::N)[h];
     };
@@ -232,7 +235,7 @@ lconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
 #pragma unroll
         for (int i = 0; i < PC; ++i) {
             const u4w v = *reinterpret_cast<const u4w*>(mine + i * L::STEP);
-            if (GATE) row_store(row_rsrc(p, L::N * 2), 16 * tid, i * 16 * L::NT, v);
+            if (DESC) row_store(row_rsrc(p, L::N * 2), 16 * tid, i * 16 * L::NT, v);
             else put_once(reinterpret_cast<u4w*>(p) + tid + i * L::NT, v);
         }
         if (++bo == B) { bo = 0; ++ho; }
