@@ -531,7 +531,7 @@ __device__ __forceinline__ int chunk_run_n(int r)
 // which phases 1 and 3 (conjugated) share.  The next row is prefetched in registers; a bf16 row outside the band is scaled by
 // a power of two (band_or_exact).
 // -------------------------------------------------------------------------------------
-template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE>
+template <int LG, class IO, int NWV, int NB, bool CONJ, bool GATE, bool RUNS>
 __global__ void __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2)))
 coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ kspec,
                      typename IO::T* __restrict__ out, const typename IO::T* __restrict__ gate, int64_t B, int64_t H,
@@ -704,20 +704,22 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
                 }
             }
         }
-        const bool more = it + 1 < it1;
+        const bool more = RUNS && it + 1 < it1;
 
         // ---- phase 1, in place.  The next row is asked for piece by piece: asked for at once, the requests of eight waves held the
         // later four of them back by some 2500 cycles of 33000 per row, and the others at the barrier (forward, B=32, H=128 fp16
-        // 260 -> 251 us, B=7, H=100 bf16 62.6 -> 60.9; one row per workgroup, B=2, H=128, 0.5 us slower)
+        // 246 -> 241 us, B=7, H=193 bf16 110.0 -> 105.1, fp16 107.0 -> 102.8).  RUNS: there are workgroups with a second row; with one
+        // each, the requests that ask for nothing cost 0.1 to 0.3 us (fp16, B=1, H=128 26.3 and, without, 26.0; bf16, B=2, H=64 26.4 and
+        // 26.3; with the gate they cost nothing, 33.9 and 34.2 at B=2, H=128, and that kernel has no such form).
         static_assert(C::TC == 16 * NWV && NB == 4 && RPL % 4 == 0, "two groups of two batches of tiles per wave");
         const int next = more ? it + 1 : it;
         phase1_inplace<LG, NB, true>(xb, t1f, vt, F1, K.F16, c1, wave * 8, lane, [&](int b) __attribute__((always_inline)) {
-            if (b == 0) fetch(next, more, q0);
-            else fetch(next, more, q1);
+            if (RUNS && b == 0) fetch(next, more, q0);
+            else if (RUNS) fetch(next, more, q1);
         });
         phase1_inplace<LG, NB, true>(xb, t1f, vt, F1, K.F16, c1, (NWV + wave) * 8, lane, [&](int b) __attribute__((always_inline)) {
-            if (b == 0) fetch(next, more, q2);
-            else fetch(next, more, q3);
+            if (RUNS && b == 0) fetch(next, more, q2);
+            else if (RUNS) fetch(next, more, q3);
         });
         __syncthreads();
         asm volatile("" : "+s"(ks));
@@ -808,6 +810,7 @@ coop_conv_row_kernel(const typename IO::T* __restrict__ in, const float2* __rest
             if constexpr (IsBf<IO>::v) measure();
             stage(0);
         }
+        if (!RUNS) break;
     }
 }
 
@@ -1251,21 +1254,28 @@ coop_kspec_rows_kernel(const float* __restrict__ k, const float* __restrict__ D,
 template <int LG>
 size_t coop_lds_bytes() { return (size_t)CC<LG>::XWORDS * 4 + (size_t)CC<LG>::TC * 8 * 16; }
 
-template <int LG, class IO, bool CONJ, bool GATE>
-hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, const Problem& pr, const Tables& tb,
-                            hipStream_t st)
+template <int LG, class IO, bool CONJ, bool GATE, bool RUNS>
+hipError_t coop_conv_row_launch(const void* in, const float2* kspec, void* out, int per, const Problem& pr, const Tables& tb,
+                                hipStream_t st)
 {
     using T = typename IO::T;
     constexpr int NWV = CC<LG>::NW;
-    const auto kern = coop_conv_row_kernel<LG, IO, NWV, NTB, CONJ, GATE>;
+    const auto kern = coop_conv_row_kernel<LG, IO, NWV, NTB, CONJ, GATE, RUNS>;
     const size_t lds = coop_staged_lds_bytes<LG>();
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const long total = pr.H * pr.B;                      // (head, row) items; the row fills a compute unit's LDS
-    const int cus = compute_units(), per = (int)((total + cus - 1) / cus);
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + per - 1) / per)), dim3(NWV * 64), lds, st, (const T*)in, kspec, (T*)out,
                        (const T*)pr.gate, pr.B, pr.H, per, tb.tw, (const unsigned char*)tb.ctab);
     return hipGetLastError();
+}
+template <int LG, class IO, bool CONJ, bool GATE>
+hipError_t coop_conv_row_go(const void* in, const float2* kspec, void* out, const Problem& pr, const Tables& tb,
+                            hipStream_t st)
+{
+    const long cus = compute_units(), per = (pr.H * pr.B + cus - 1) / cus;
+    return per > 1 || GATE ? coop_conv_row_launch<LG, IO, CONJ, GATE, true>(in, kspec, out, (int)per, pr, tb, st)
+                           : coop_conv_row_launch<LG, IO, CONJ, GATE, GATE>(in, kspec, out, 1, pr, tb, st);
 }
 
 // rows, or the inner convolution of the multi-pass split in the workspace

@@ -94,3 +94,16 @@ def test_not_a_number_stays_in_its_row(N):
     keep = [0, 1, 3, 4]
     assert np.array_equal(y0[keep], y1[keep]) and np.array_equal(du0[keep], du1[keep])
     assert not np.all(np.isfinite(y1[2])) and not np.all(np.isfinite(du1[2])) and not np.all(np.isfinite(dk1))
+
+
+# N = 32768: a row for every compute unit, and one more (workgroups of two rows)
+@pytest.mark.parametrize("io", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("H", [256, 257])
+def test_one_row_a_workgroup(H, io):
+    inp = wl.generate(_w("3", N=32768, dtype=io), B=1, H=H)
+    g = GpuRun(inp)
+    hs = sample_heads(H, 1, seed=H)
+    y, du = g.fwd()[:, hs], g.bwd(dk=False, dD=False)[0][:, hs]
+    k64, D64 = inp.k.astype(np.float64)[hs], inp.D.astype(np.float64)[hs]
+    _compare({"y": y, "du": du}, {"y": oracle.longconv_fwd(inp.u[:, hs], k64, D64),
+                                  "du": oracle.longconv_bwd(inp.dy[:, hs], inp.u[:, hs], k64, D64)[0]}, TOL[io], f"one row a workgroup, H={H}")
