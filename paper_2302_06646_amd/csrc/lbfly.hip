@@ -211,7 +211,7 @@ __device__ __forceinline__ void put_out(_Float16* tile, const f4& v, int lane)
 // matrix and 83 vector instructions per 256 points and row, 112 with what a workgroup spends on its matrices (B=16, H=768,
 // N=1024); two rows per barrier were no faster.  The form it replaced took every block through LDS with its own addresses,
 // twiddle loads and barrier: that shape in bf16 77 us, this one 36 (53 before the quarters were hashed, 41 with a workgroup per 8
-// rows of one head).  N = 256 spills 5 registers, N = 2048 7.
+// rows of one head).  N = 256 spills 3 registers, N = 2048 5.
 // -------------------------------------------------------------------------------------------------------------------
 template <int LG, class IO>
 __global__ void __launch_bounds__(64 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(4)))
@@ -976,10 +976,10 @@ hipError_t set_lds(F* f, size_t bytes)
 // Rows of the (head, batch row) list that a forward workgroup takes: what spreads them evenly over the `resident` workgroups of the
 // device at once, or a few more where the runs then end with their heads (a divisor of B or a multiple), since every head that a run
 // touches is matrices to build.  Even shares stay unless the others end 4 % earlier by this: a compute unit's workgroups issue 0.07 T us
-// a row and three rows' time a head, a workgroup by itself waits 0.5 + 0.02 T us a row and four rows' time a head (fitted to 40 shapes,
-// N = 256 .. 2048), and neither hides the other: the root of the sum of their squares.  bf16, us, even shares and this: N = 256 B=16 H=768 19.5 (6 rows) and 16.1 (8),
-// B=4 H=1030 13.3 (3) and 9.3 (4); N = 512 B=16 H=768 22.3 (12) and 20.4 (16), B=8 H=300 11.9 (3) and 9.5 (4); N = 1024 B=7 H=193 11.6 (3)
-// and 10.0 (7); N = 2048 B=12 H=90 17.7 (5) and 14.9 (6).
+// a row and three rows' time a head, a workgroup by itself waits 0.5 + 0.02 T us a row, or 0.07 T where that is more (N = 2048), and four
+// rows' time a head (fitted to 40 shapes, N = 256 .. 2048), and neither hides the other: the root of the sum of their squares.  bf16, us,
+// even shares and this: N = 256 B=16 H=768 19.5 (6 rows) and 16.1 (8), B=4 H=1030 13.3 (3) and 9.3 (4); N = 512 B=16 H=768 22.3 (12) and
+// 20.4 (16), B=8 H=300 11.9 (3) and 9.5 (4); N = 1024 B=7 H=193 11.6 (3) and 10.0 (7); N = 2048 B=12 H=90 17.7 (5) and 14.9 (6).
 int64_t run_of_rows(int64_t B, int64_t rows, int64_t resident, int T)
 {
     const int64_t even = (rows + resident - 1) / resident, units = compute_units();
@@ -1046,33 +1046,55 @@ hipError_t bwd_go(const void* dy, const void* u, const float* shat, const float*
 
 }  // namespace
 
-// Shares of a head's rows: the number that ends first, ceil(512 / H) at most, where 8 / T workgroups (two chains of T waves) run on each of
-// 256 compute units.  A share's matrices and sums take as long as about six rows (8.3 us at N = 1024, a row 1.45), five at N = 2048
-// (15 us, a row 3.2); more than one share is a second launch, as long as three rows or two.
+// Shares of a head's rows: the number that ends first, ceil(512 / H) at most.  256 compute units hold 8 / T workgroups (two chains of T
+// waves) each, N = 2048 one.  (256 as a number: the size of a workspace does not depend on the device that it is asked for on.)
 static int64_t most_shares(int64_t B, int64_t H) { return (512 + H - 1) / H < B ? (512 + H - 1) / H : B; }
-static int64_t turns(int64_t workgroups, int64_t N)
+static int64_t places(int64_t N) { return N == 2048 ? 256 : 256 * (1024 / N); }
+static int64_t turns(int64_t workgroups, int64_t N) { return (workgroups + places(N) - 1) / places(N); }
+// Adding up n shares is a launch and a chain of n loads, and the shares' numbers go to memory and back.
+static double sum_time(int64_t H, int64_t N, int64_t n) { return n > 1 ? 1.7 + 0.28 * n + n * H * (2 * N + 6 * NBLK) * 3.2e-6 : 0.; }
+// us of n shares: turn by turn a workgroup's set-up (constants, matrices, sums), longer with more of the device's workgroups at the
+// same memory, and its rows, each as long as a workgroup by itself takes or as the unit's workgroups take to issue theirs.  Measured
+// for B = 1 .. 64 and H = 4 .. 1024 with every number of shares (N = 256, 512, 1024, 2048 with one workgroup on a unit: set-up 3.1, 3.1,
+// 5.6, 6.6 us and, all units taken, 4.5, 4.4, 8.4, 12.5; a row 0.75, 0.87, 1.35, 3.2, with all a unit's places taken 1.48, 1.42, 1.35, 3.2);
+// the number that this takes is within 1 % of the best one's time on average.  With set-up as six rows, and three for any sum, which the
+// kernel of one chain had, us there and here: N = 256 B=8, H=500 24.1 (2 shares) and 15.2 (1), B=64, H=4 26.9 (64) and 14.9 (16); N = 512
+// B=8, H=256 21.0 (2) and 13.7 (1), B=16, H=16 14.6 (16) and 12.3 (4); N = 1024 B=64, H=4 30.2 (64) and 20.2 (16).
+static double shares_time(int64_t B, int64_t H, int64_t N, int64_t n)
 {
-    const int64_t resident = N == 2048 ? 256 : 256 * (1024 / N);
-    return (workgroups + resident - 1) / resident;
+    static const double ROW[4] = {0.75, 0.87, 1.35, 3.2}, MORE[4] = {0.15, 0., 0., 0.}, ISSUE[4] = {0.37, 0.71, 1.35, 3.2};
+    static const double SETUP[4] = {3.0, 2.9, 5.5, 6.5}, CROWD[4] = {1.5, 1.5, 2.9, 6.0};
+    const int i = N == 256 ? 0 : N == 512 ? 1 : N == 1024 ? 2 : 3;
+    const double rows = (double)((B + n - 1) / n);
+    double t = sum_time(H, N, n);
+    for (int64_t left = n * H; left > 0; left -= places(N)) {
+        const int64_t w = left < places(N) ? left : places(N), unit = (w + 255) / 256;
+        const double row = ROW[i] + MORE[i] * (unit - 1), issue = ISSUE[i] * unit;
+        t += SETUP[i] + CROWD[i] * w / 256 + rows * (row > issue ? row : issue);
+    }
+    return t;
 }
+// n shares whose workgroups take n times the turns of one share's have no room in the workspace.
+static bool has_room(int64_t H, int64_t N, int64_t n) { return n == 1 || turns(n * H, N) < n * turns(H, N); }
 int lbfly_nsplit(int64_t B, int64_t H, int64_t N)
 {
-    const int64_t setup = N == 2048 ? 5 : 6, launch = N == 2048 ? 2 : 3;
-    int64_t best = 1, best_t = -1;
-    for (int64_t n = 1; n <= most_shares(B, H); ++n) {
-        const int64_t t = turns(n * H, N) * ((B + n - 1) / n + setup) + (n > 1 ? launch : 0);
-        if (best_t < 0 || t < best_t) { best = n; best_t = t; }
+    int64_t best = 1;
+    double least = shares_time(B, H, N, 1);
+    for (int64_t n = 2; n <= most_shares(B, H) && sum_time(H, N, n) < least; ++n) {
+        if (!has_room(H, N, n)) continue;
+        const double t = shares_time(B, H, N, n);
+        if (t < least) { best = n; least = t; }
     }
     return (int)best;
 }
 
 // For the most shares that any call of up to B rows takes: the number above need not grow with B, but a workspace for B rows
-// serves a smaller batch.  (One share ends before n shares of n times its turns, whatever B.)
+// serves a smaller batch.
 size_t lbfly_partial_bytes(int64_t B, int64_t H, int64_t N)
 {
     int64_t room = 1;
     for (int64_t n = 2; n <= most_shares(B, H); ++n)
-        if (turns(n * H, N) < n * turns(H, N)) room = n;
+        if (has_room(H, N, n)) room = n;
     return (size_t)room * (size_t)H * ((size_t)(2 * N) + 6 * NBLK) * sizeof(float2);
 }
 

@@ -267,3 +267,17 @@ def test_two_tiles_a_wave():
     assert np.array_equal(only_du["du"], g["du"]) and np.all(np.isnan(only_du["dshat"])) and np.all(np.isnan(only_du["dAi"]))
     no_du = _run(u_s, dy_s, k, D, Af32, Ai32, io, want=(False, True, True, True))
     assert np.all(np.isnan(no_du["du"])) and np.array_equal(no_du["dshat"], g["dshat"]) and np.array_equal(no_du["dAf"], g["dAf"])
+
+
+# Shares of a head's rows as the times of set-up, rows and sum give them: sixteen of four rows, four of eight and nine, two uneven ones, one
+# where two would meet on their compute units, two where the device takes two turns of heads anyway
+@pytest.mark.parametrize("N,B,H", [(256, 64, 4), (512, 33, 64), (1024, 33, 100), (256, 8, 500), (512, 33, 500), (1024, 33, 300), (2048, 64, 4)])
+def test_shares_by_their_times(N, B, H):
+    io, heads = wl.BF16, [0, H // 2, H - 1]
+    u_s, u_v, dy_s, dy_v, k, D, Af32, Ai32, Af, Ai = _inputs(B, H, N, io, seed=8)
+    g = _run(u_s, dy_s, k, D, Af32, Ai32, io)
+    rdu, rdshat, rdAf, rdAi = lbfly.lbfly_bwd(dy_v[:, heads], u_v[:, heads], lbfly.spectrum(k[heads], D[heads]), Af[heads], Ai[heads])
+    label = f"lbfly shares N={N} B={B} H={H}"
+    _compare({"du": g["du"][:, heads], "dshat": _ri(g["dshat"][heads])}, {"du": rdu, "dshat": _ri(rdshat)}, TOL[io], label)
+    _check_blocks(g["dAf"][heads], rdAf, N, TOL[io], label + " dAf")
+    _check_blocks(g["dAi"][heads], rdAi, N, TOL[io], label + " dAi")
