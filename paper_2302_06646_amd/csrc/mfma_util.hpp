@@ -113,12 +113,13 @@ __device__ __forceinline__ void band_or_exact2(uint32_t& ma, uint32_t& mb)
     typedef unsigned short us2 __attribute__((ext_vector_type(2)));
     union { uint32_t u; us2 v; } a, b, hi;
     a.u = ma; b.u = mb;
-    hi.v = __builtin_elementwise_max(a.v, b.v);
-    // Without its sign (bf16 patterns above 0x7c00 are NaN to absmax_acc, which may keep it) a half is below 0x8000: the sum's top bit
-    // tells whether it is at or above BAND_HIGH, with no carry into the other half, and bit 14 whether it is at or above BAND_LOW.
-    hi.u &= 0x7fff7fffu;
-    constexpr uint32_t UP = (0x8000u - BAND_HIGH) * 0x10001u, LOW = BAND_LOW * 0x10001u;
-    const uint64_t big = __builtin_amdgcn_ballot_w64(((hi.u + UP) & 0x80008000u) != 0u);
+    // Unsigned halves, which leave something above BAND_HIGH - 1 if they are at or above BAND_HIGH: bf16 patterns above 0x7c00 are NaN to
+    // absmax_acc, which may keep their sign.  Below 0x8000 bit 14 tells whether a half is at or above BAND_LOW.  (As a sum whose top bits
+    // tell, with the signs cleared: images of 32 x 32, B=64, H=256, 119.4 -> 122.3 us, B=64, H=256, N=2048 with gradients of 1e-4 76.9 -> 79.1.)
+    const us2 edge = {(unsigned short)(BAND_HIGH - 1), (unsigned short)(BAND_HIGH - 1)};
+    hi.v = __builtin_elementwise_sub_sat(__builtin_elementwise_max(a.v, b.v), edge);
+    constexpr uint32_t LOW = BAND_LOW * 0x10001u;
+    const uint64_t big = __builtin_amdgcn_ballot_w64(hi.u != 0u);
     const uint64_t la = __builtin_amdgcn_ballot_w64((ma & LOW) != 0u), lb = __builtin_amdgcn_ballot_w64((mb & LOW) != 0u);
     if (__builtin_expect(big != 0 || la == 0 || lb == 0, 0)) {
         ma = absmax_wave(ma);
