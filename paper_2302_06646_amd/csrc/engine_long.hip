@@ -100,7 +100,8 @@ __global__ void fill_long_tab_kernel(uint4* tab)
 
 // -------------------------------------------------------------------------------------------------------------------
 // Convolution (forward; CONJ: du) of all rows.  Persistent workgroups with even runs of consecutive (head, row) items, two
-// barriers per row.  Bound by issue: about 75 instructions per 256 points and row at some six cycles each with two waves per SIMD.
+// barriers per row.  Bound by issue and waits of two waves per SIMD: per 256 points of a row 15 matrix and 64 vector instructions, at most
+// 400 of the 790 cycles that a SIMD takes for them.
 // B=8, H=256, N=16384 fp16: 83 us as pairs of rows in 32768-point transforms, 54 here; B=64, H=128, N=8192: 129, 91.  Four waves per
 // SIMD with four tiles each (128 registers) were tried: 2 to 4 % faster at 16384, slower at 8192 and for few rows, and only with eight
 // spilled registers or the tiles' factors rounded by themselves.

@@ -666,7 +666,7 @@ rconv_kernel(const typename IO::T* __restrict__ in, const float2* __restrict__ k
         SCHED_FENCE();
         // The spectrum before the row: requests are counted in their order, and phase 2 would have to wait for a row asked for
         // in front of its spectrum, half an iteration early, in every iteration.  (No faster where the rows come from the
-        // last-level cache; large calls run at the clock that the power budget leaves, 1.8 to 2.1 GHz.)
+        // last-level cache.)
         if (do1) {
             if (b == 0 && t > 0) load_spec();           // the next phase 2 is another head's
             if (++b == B) { b = 0; ++h; }

@@ -601,7 +601,8 @@ lb_bwd_chain(f4* lds4, const int t, const typename IO::T* __restrict__ dy, const
     }
 }
 
-// Waves 0 .. T - 1 do u's chain, the others dy's; a workgroup's barriers are the same in number on both sides.
+// Waves 0 .. T - 1 do u's chain, the others dy's.  Both meet the same barriers from code of their own: in lb_bwd_chain none stands in a
+// condition on the chain, and none may.
 template <int LG, class IO>
 __global__ void __launch_bounds__(128 << (LG - 8)) __attribute__((amdgpu_waves_per_eu(4)))
 lb_bwd_kernel(const typename IO::T* __restrict__ dy, const typename IO::T* __restrict__ u,
