@@ -216,7 +216,7 @@ def test_rows_of_one_head_apart_at_32768(io):
 
 
 # One sample outside the band in a row that otherwise lies inside it: the waves that hold the row decide by themselves whether it
-# has to be scaled, each from its own words, and a single word has to be enough.  Of either sign (bf16 patterns from 2^121 on are NaN
+# has to be scaled, each from its own words, and a single word has to be enough.  Of either sign (bf16 patterns above 2^121 are NaN
 # when read as fp16, where the maximum of |x| is taken), in the first or the last wave's words, in u alone or in dy alone: head
 # 4 place + 2 sign + tensor, rows inside the band around it.
 # Outputs are cut from a linear convolution of 2N samples, and the rounding of a transform is relative to all of it: of a sample six
